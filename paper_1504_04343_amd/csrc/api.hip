@@ -92,6 +92,15 @@ inline StridedBwd strided_bwd(const cct_conv_desc_t& d, const Geom& g) {
   sb.M = g.Cg * d.stride * d.stride;
   return sb;
 }
+// where the gathered tensor of a fused problem lies (conv_fused_split)
+inline void set_tensor(GemmTN* p, int C, int H, int W, int K) {
+  p->x_img = (long long)C * H * W;
+  p->x_plane = (long long)H * W;
+  p->x_h = H;
+  p->x_w = W;
+  p->oK = K;
+}
+
 // The operand description of one chunk of `ni` images (pack at `pack`, or null for a fit check).
 GemmTN strided_bwd_problem(const cct_conv_desc_t& d, const Geom& g, const void* pack, int Mpad,
                            int Kpad_kc, const float* dyc, float* dxc, long long ni) {
@@ -113,6 +122,7 @@ GemmTN strided_bwd_problem(const cct_conv_desc_t& d, const Geom& g, const void* 
   p.d2s = 1; p.dS = d.stride; p.dP = d.pad; p.dH = d.H; p.dW = d.W; p.dCg = g.Cg; p.dCtot = d.C;
   p.bf16 = d.precision == CCT_PREC_BF16_IN_F32_ACC;
   p.prof_flops = 2.0 * (double)ni * d.O * g.Hout * g.Wout * g.Cg * d.K * d.K;
+  set_tensor(&p, d.O, g.Hout, g.Wout, d.K);
   return p;
 }
 
@@ -139,6 +149,23 @@ GemmTN fused_fwd_problem(const cct_conv_desc_t& d, const Geom& g, const void* pa
   p.cmap = ColMap{(int)P, (long long)d.O * P};
   p.bias = bias; p.bias_gs = g.Og;
   p.bf16 = d.precision == CCT_PREC_BF16_IN_F32_ACC;
+  set_tensor(&p, d.C, d.H, d.W, d.K);
+  return p;
+}
+
+// The same pass of a strided layer read space-to-depth: its padded input as s*s*C channels on a grid s
+// times as coarse, stride 1, no padding, ceil(K/s) taps per axis.
+GemmTN s2d_fwd_problem(const cct_conv_desc_t& d, const Geom& g, const void* pack, int Mpad, int Kpad,
+                       const float* xc, float* yc, const float* bias, long long ni) {
+  GemmTN p = fused_fwd_problem(d, g, pack, Mpad, Kpad, xc, yc, bias, ni);
+  const int s = d.stride, U = (d.K + s - 1) / s;
+  p.prof_flops = 2.0 * p.M * p.Ncols * p.Kdim * p.G;
+  p.s2d = s;
+  p.gC = d.C * s * s; p.gCg = g.Cg * s * s;
+  p.gH = g.Hout - 1 + U; p.gW = g.Wout - 1 + U;
+  p.x_pad = d.pad;
+  p.gs = 1; p.gp = 0; p.gK = U; p.gKK = U * U;
+  p.Kdim = p.gCg * U * U;
   return p;
 }
 
@@ -166,7 +193,45 @@ GemmTN fused_bwd_problem(const cct_conv_desc_t& d, const Geom& g, const void* pa
   p.c_ms = HW; p.c_gs = (long long)g.Cg * HW;
   p.cmap = ColMap{(int)HW, (long long)d.C * HW};
   p.bf16 = d.precision == CCT_PREC_BF16_IN_F32_ACC;
+  set_tensor(&p, d.O, g.Hout, g.Wout, d.K);
   return p;
+}
+
+// How conv_fused_split would run a fused forward / backward-data pass.
+struct SplitPlan {
+  int kind;        // of its pack: 0 forward, 1 flipped, 2 strided backward-data, 3 space to depth
+  int Mpad, Kpad;
+};
+GemmTN split_problem(const cct_conv_desc_t& d, const Geom& g, const SplitPlan& sp, const void* pack,
+                     const float* in, float* out, const float* bias, long long ni) {
+  switch (sp.kind) {
+    case 0: return fused_fwd_problem(d, g, pack, sp.Mpad, sp.Kpad, in, out, bias, ni);
+    case 1: return fused_bwd_problem(d, g, pack, sp.Mpad, sp.Kpad, in, out, ni);
+    case 2: return strided_bwd_problem(d, g, pack, sp.Mpad, sp.Kpad, in, out, ni);
+    default: return s2d_fwd_problem(d, g, pack, sp.Mpad, sp.Kpad, in, out, bias, ni);
+  }
+}
+// false = the kernel cannot run this pass of the layer (bf16, or shapes it cannot stage).
+bool split_plan(const cct_conv_desc_t& d, int pass, const Geom& g, SplitPlan* sp) {
+  if (d.precision != CCT_PREC_F32 || pass == CCT_PASS_BACKWARD_WEIGHTS) return false;
+  const int s = d.stride, U = (d.K + s - 1) / s;
+  const bool fwd = pass == CCT_PASS_FORWARD;
+  if (!fwd && s == 1 && d.pad > d.K - 1) return false;
+  const long long kIn = (long long)d.C * d.H * d.W, kOut = (long long)d.O * g.Hout * g.Wout;
+  if (kIn >= kIntMax || kOut >= kIntMax || (long long)d.C * s * s >= kIntMax / 2) return false;
+  auto fits = [&](int kind, long long M, int channels, int K) {
+    const long long kp = conv_fused_split_kpad(channels, K);
+    if (M >= kIntMax - 64 || kp >= kIntMax) return false;
+    *sp = SplitPlan{kind, conv_fused_split_mpad((int)M), (int)kp};
+    return conv_fused_split_fits(split_problem(d, g, *sp, nullptr, nullptr, nullptr, nullptr, 1));
+  };
+  if (!fwd) {
+    if (s == 1) return fits(1, g.Cg, g.Og, d.K);
+    const StridedBwd sb = strided_bwd(d, g);
+    return fits(2, (long long)g.Cg * s * s, g.Og, sb.U);
+  }
+  if (fits(0, g.Og, g.Cg, d.K)) return true;
+  return (s == 2 || s == 4) && U >= 2 && fits(3, g.Og, g.Cg * s * s, U);
 }
 
 inline int esize(const cct_conv_desc_t& d) { return d.precision == CCT_PREC_BF16_IN_F32_ACC ? 2 : 4; }
@@ -183,13 +248,16 @@ struct Layout {
   int Mpad = 0, Kpad = 0;  // pack padding (TN GEMM)
   int Kpad_kc = 0;         // fused passes: K padding of the channel-contiguous pack
   int S = 1, split_len = 0;  // NT GEMM
+  int split = 0;    // fused forward / backward-data on conv_fused_split, as sp says
+  SplitPlan sp;
   int t2_opad = 0;  // Type-2 backward-data with the inverse lifting gathered by the GEMM: padded Og
 };
 
 constexpr int kDbiasBlocks = 64;
 
+// allow_split = false: without conv_fused_split, whose pack takes half as much again as the fp32 one.
 bool make_layout(const cct_conv_desc_t& d, int pass, int type, const Geom& g, long long nc,
-                 Layout* L) {
+                 Layout* L, bool allow_split = true) {
   const long long ncols = nc * g.Pc;
   if (ncols <= 0 || ncols >= kIntMax - 256) return false;
   if ((long long)d.C * g.DKi * g.DKj >= kIntMax || (long long)d.O * g.RKi * g.RKj >= kIntMax)
@@ -204,7 +272,16 @@ bool make_layout(const cct_conv_desc_t& d, int pass, int type, const Geom& g, lo
   };
   const long long dt_rows = (long long)d.C * g.DKi * g.DKj;
   const long long rt_rows = (long long)d.O * g.RKi * g.RKj;
-  if (pass == CCT_PASS_FORWARD) {
+  L->split = type == CCT_LOWER_FUSED && allow_split && split_plan(d, pass, g, &L->sp);
+  if (L->split) {
+    // one column per output pixel (forward), input pixel or cell of the strided grid (backward-data)
+    const StridedBwd sb = strided_bwd(d, g);
+    const long long cols = pass == CCT_PASS_FORWARD ? g.Pc
+                           : d.stride > 1           ? (long long)sb.Ah * sb.Aw
+                                                    : (long long)d.H * d.W;
+    if (nc * cols >= kIntMax - 256) return false;
+    take((long long)d.groups * L->sp.Mpad * L->sp.Kpad * 6, &L->pack_off, &L->pack_bytes);
+  } else if (pass == CCT_PASS_FORWARD) {
     int BM, BN, BK;
     gemm_tn_tile(g.Mr, (int)ncols, &BM, &BN, &BK);
     L->Mpad = (int)align_up(g.Mr, BM);
@@ -321,7 +398,8 @@ bool type_supported(const cct_conv_desc_t& d, int pass, int type) {
                                                      (int)kc, nullptr, nullptr, 1)))
         return false;
     }
-    if (pass == CCT_PASS_BACKWARD_DATA && d.stride > 1) {
+    SplitPlan sp;
+    if (pass == CCT_PASS_BACKWARD_DATA && d.stride > 1 && !split_plan(d, pass, gg, &sp)) {
       const StridedBwd sb = strided_bwd(d, gg);
       if ((long long)gg.Cg * d.stride * d.stride >= kIntMax || (long long)sb.Ah * sb.Aw >= kIntMax)
         return false;
@@ -388,7 +466,11 @@ double model_cost(const cct_conv_desc_t& d, int pass, int type) {
     return std::min(1.0, tiles / 512.0);
   };
   double index_bytes = 0.0, gemm_bytes = 0.0, launches = 2.0, rate = kGemmFlopsPerSec;
-  if (pass == CCT_PASS_FORWARD && type == CCT_LOWER_FUSED) {
+  SplitPlan sp;
+  if (type == CCT_LOWER_FUSED && split_plan(d, pass, g, &sp)) {
+    const GemmTN q = split_problem(d, g, sp, nullptr, nullptr, nullptr, nullptr, 1);
+    return std::max(conv_fused_split_seconds(q, d.N), (x_bytes + y_bytes) / kGemmBytesPerSec) + launches * kLaunchSec;
+  } else if (pass == CCT_PASS_FORWARD && type == CCT_LOWER_FUSED) {
     // no lowered matrix at all; building the operand in the kernel costs the GEMM some of its rate
     gemm_bytes = x_bytes + y_bytes;
     rate *= kFusedGemmFactor * eff_fused(g.Mr) * fill(g.Mr, cols) * short_k(g.Kd);
@@ -512,9 +594,12 @@ long long default_chunk(const cct_conv_desc_t& d, int pass, int type, const Geom
 // Largest chunk whose layout fits `bytes`; 0 if not even one image fits.
 long long chunk_for_workspace(const cct_conv_desc_t& d, int pass, int type, const Geom& g,
                               size_t bytes, Layout* L) {
+  bool split = true;
   auto fits = [&](long long nc) {
-    return make_layout(d, pass, type, g, nc, L) && (unsigned long long)L->total <= bytes;
+    return make_layout(d, pass, type, g, nc, L, split) && (unsigned long long)L->total <= bytes;
   };
+  // a workspace too small for the split kernel matrix still holds the fp32 one
+  if (!fits(1)) split = false;
   if (!fits(1)) return 0;
   long long lo = 1, hi = d.N;
   if (fits(hi)) return hi;
@@ -696,6 +781,21 @@ int scratch_address(void** out) {
   return CCT_OK;
 }
 
+// A fused forward / backward-data pass on conv_fused_split: one kernel per chunk of nc images.
+int run_split(const cct_conv_desc_t& d, const Geom& g, int pass, const Layout& L, long long nc,
+              const float* in, const float* w, const float* bias, float* out, char* ws, hipStream_t st) {
+  const bool fwd = pass == CCT_PASS_FORWARD;
+  const long long x_img = (long long)d.C * d.H * d.W, y_img = (long long)d.O * g.Hout * g.Wout;
+  void* pack = ws + L.pack_off;
+  int rc = launch_pack_split(w, pack, L.sp.kind, d.groups, g.Og, g.Cg, d.K, d.stride, L.sp.Mpad, st);
+  for (long long n0 = 0; n0 < d.N && !rc; n0 += nc) {
+    const long long ni = std::min<long long>(nc, d.N - n0);
+    rc = launch_conv_fused_split(split_problem(d, g, L.sp, pack, in + n0 * (fwd ? x_img : y_img),
+                                               out + n0 * (fwd ? y_img : x_img), bias, ni), st);
+  }
+  return rc;
+}
+
 // The forward pass.  static_scratch: the workspace is the library's scratch array, whose address
 // is looked up only after every argument and size check has passed.
 int forward_on_workspace(const cct_conv_desc_t* desc, const float* x, const float* w,
@@ -727,6 +827,8 @@ int forward_on_workspace(const cct_conv_desc_t* desc, const float* x, const floa
   const int es = esize(d);
   const long long P = (long long)g.Hout * g.Wout;
 
+  if (L.split)
+    return run_split(d, g, CCT_PASS_FORWARD, L, nc, x, w, bias, y, ws, st);
   // the fused pass: the operand description of one chunk (lowering, multiply and lifting in one
   // kernel: the GEMM gathers its B tiles from x)
   auto fused_chunk = [&](const float* xc, float* yc, long long ni, bool kc) {
@@ -841,6 +943,8 @@ int cct_conv_backward_data(const cct_conv_desc_t* desc, const float* w, const fl
   const long long P = (long long)g.Hout * g.Wout;
   const long long HW = (long long)d.H * d.W;
 
+  if (L.split)
+    return run_split(d, g, CCT_PASS_BACKWARD_DATA, L, nc, dy, w, nullptr, dx, ws, st);
   if (type == CCT_LOWER_FUSED && d.stride > 1) {
     // one kernel per chunk: the s*s residue classes of dx as one stride-1 convolution of dy
     void* pack = ws + L.pack_off;

@@ -83,6 +83,11 @@ struct GemmTN {
   // position (a, b) of image n is pixel (h, w) = (a*dS + rh - dP, b*dS + rw - dP) of channel
   // g*dCg + ci of the dCtot-channel, dH x dW tensor at C; pixels outside the tensor are dropped.
   int d2s, dS, dP, dH, dW, dCg, dCtot;
+  // Where the gathered tensor lies for conv_fused_split: elements between images and channels, height
+  // and width; s2d = 2 or 4 reads it space-to-depth after padding it by x_pad (gC, gH, gW, gCg, gK then
+  // are those of the regrouped layer); oK = kernel size of the layer itself.
+  long long x_img, x_plane;
+  int x_h, x_w, x_pad, s2d, oK;
   int force_bm;       // row tile to use (64 / 96 / 128; Mpad a multiple of it); 0 = gemm_tn_tile's choice
   double prof_flops;  // algorithmic flops to book for the launch when they differ from 2*M*N*K*G (else 0)
   unsigned d_divSS_M, d_divS_M;  // fast division by dS*dS and by dS
@@ -137,6 +142,18 @@ int launch_conv_fused_kc(const GemmTN& p, hipStream_t st);
 int conv_fused_kc_bf16_mpad(int M);
 bool conv_fused_kc_bf16_fits(const GemmTN& p);
 int launch_conv_fused_kc_bf16(const GemmTN& p, hipStream_t st);
+// The channel-contiguous fused kernel for fp32 operands as sums of three bf16 terms
+// (conv_fused_split.hip); its pack holds the three terms, 3 * Mpad * Kpad bf16 per group, and is
+// written by launch_pack_split (kind: 0 forward, 1 flipped, 2 strided backward-data, 3 space to depth).
+int conv_fused_split_mpad(int M);
+long long conv_fused_split_kpad(int channels_per_group, int K);
+bool conv_fused_split_fits(const GemmTN& p);
+int launch_pack_split(const float* w, void* pack, int kind, int G, int Og, int Cg, int K, int s, int Mpad,
+                      hipStream_t st);
+int launch_conv_fused_split(const GemmTN& p, hipStream_t st);
+// Its time on nimg images by the optimizer's cost model (p describes one image).
+double conv_fused_split_seconds(const GemmTN& p, int nimg);
+
 // Fused backward-weights pass: split partial products of dy (NCHW, read in place) with the
 // Type-1 lowering of x built in LDS.  Cpart[s][q][oo][(ci,i,j)], compact, S splits of split_len
 // positions (a multiple of 32) over the nimg*Hout*Wout positions.

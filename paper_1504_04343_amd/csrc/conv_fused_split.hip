@@ -1,0 +1,736 @@
+// Fused forward / backward-data pass (the "Fusion" of Sec. 2.1) for fp32 operands on the bf16 matrix
+// cores: every operand is the exact sum of three bf16 terms and a product is six
+// v_mfma_f32_32x32x16_bf16 (split_bf16.h).
+//
+// Product: C[m][pos] = sum_{grp, tap, c} K^[grp][tap][m][c] * xpad[n, grp*16 + c, r*s + i, c*s + j]
+//   - a workgroup owns BM rows x 128 consecutive positions; a wave owns 32 rows x (all 128 | half of
+//     them) positions, two accumulators per 32 x 32 block;
+//   - per channel group of 16 it stages the zero-padded input rows its positions can touch as cells
+//     (row, column) in a two-slot LDS ring, split while they are staged.  A cell is three terms of
+//     16 channels, 32 bytes each, 112 bytes from the next (28 l mod 32 for l = 0..7, four banks
+//     each, covers the 32 banks once: 16-byte reads of eight consecutive cells do not conflict);
+//   - one K tile = one tap of one channel group = 16 reduction indices.  The B operand of a lane is
+//     16 bytes per term of its position's cell at the tap, read one block ahead of its six MFMAs;
+//   - the kernel matrix comes packed and split as [group][tile][term][row][16] and never passes
+//     through LDS: a lane loads the 16 bytes of its row and term straight from the pack, AD tiles
+//     ahead, the tile and term in the scalar offset.  With all four waves stacked along the rows
+//     no two waves read the same rows, which is why a wave is 32 x 128 and not 64 x 64: the pack is
+//     read once per workgroup and tile (12 KiB per 768 MFMA cycles of a wave) and the cells four
+//     times from LDS (48 of 128 bytes per cycle), where 64 x 64 waves would ask 24 KiB of the L1;
+//   - the cells of the next group are fetched and written in up to four steps of 8 channels, one per
+//     tap, so that they cost 8 registers; the workgroup meets once per channel group.
+//   - KT: the kernel size where it is compiled in (3, 5: all taps of a group unrolled); 0 = any K.
+//   - S: 1 = the tensor itself; 2, 4 = space to depth: the padded input is read as a tensor of S*S
+//     times as many channels on a grid S times as coarse (channel = (ci, dh, dw)), which turns a
+//     layer of stride S into an unpadded one of stride 1 with ceil(K/S) taps.
+#include <stdio.h>
+
+#include <algorithm>
+#include <cmath>
+
+#include "cct_internal.h"
+#include "conv_fused_kc_common.h"
+#include "gemm_common.h"
+#include "split_bf16.h"
+
+namespace cct {
+namespace {
+
+using namespace kc;
+constexpr int CB = 112;  // bytes between cells in LDS
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // 16 bytes, dword aligned
+
+// K tiles per channel group: the taps, padded (zero tiles) to what the tile loop takes at a time
+// (AD tiles; see launch_rows for the sizes that are compiled in)
+__host__ __device__ constexpr int tiles_per_group(int K) {
+  return K == 3 || K == 5 ? K * K : (K * K + 1) / 2 * 2;
+}
+
+// One output as a plain fp32 sum over its window, for results that an infinity made NaN.  Taps that
+// exist only in the regrouped kernel of a strided layer (index >= oK) are no terms of the sum.
+template <int S>
+__device__ float plain_sum(const GemmTN& p, const KcGeom& fg, int g, int m, int n, int r, int c) {
+  const int tpg = tiles_per_group(p.gK);
+  const unsigned short* A = reinterpret_cast<const unsigned short*>(p.A) + (long long)g * p.a_gs * 3;
+  const float* X = reinterpret_cast<const float*>(p.B) + (long long)n * p.x_img;
+  const int ss = p.d2s ? p.dS * p.dS : 1;
+  const int rh = p.d2s ? (m % ss) / p.dS : 0, rw = p.d2s ? (m % ss) % p.dS : 0;
+  float sum = 0.f;
+#pragma unroll 1
+  for (int ch = 0; ch < p.gCg; ++ch) {
+    const int grp = ch / CG, cc = ch - grp * CG;
+    const int dh = S > 1 ? (ch % (S * S)) / S : 0, dw = S > 1 ? ch % S : 0;
+    const float* Xc = X + (long long)((g * p.gCg + ch) / (S * S)) * p.x_plane;
+#pragma unroll 1
+    for (int tap = 0; tap < fg.KK; ++tap) {
+      const int i = tap / p.gK, j = tap - i * p.gK;
+      int h = r * p.gs + i - p.gp, w = c * p.gs + j - p.gp;
+      if (S > 1) {
+        h = h * S + dh - p.x_pad;
+        w = w * S + dw - p.x_pad;
+      }
+      if (h < 0 || h >= p.x_h || w < 0 || w >= p.x_w) continue;
+      if (S > 1 && (i * S + dh >= p.oK || j * S + dw >= p.oK)) continue;
+      if (p.d2s && (rh + p.dS * (p.gK - 1 - i) >= p.oK || rw + p.dS * (p.gK - 1 - j) >= p.oK)) continue;
+      const unsigned short* a = A + (((long long)(grp * tpg + tap) * 3) * p.Mpad + m) * CG + cc;
+      const long long term = (long long)p.Mpad * CG;
+      const float wv = (__uint_as_float((unsigned)a[0] << 16) + __uint_as_float((unsigned)a[term] << 16)) +
+                       __uint_as_float((unsigned)a[2 * term] << 16);
+      sum = fmaf(Xc[(long long)h * p.x_w + w], wv, sum);
+      if (sum != sum) return sum;
+    }
+  }
+  return sum;
+}
+
+// cells per thread: sizes without an unrolled group take a third one (7 x 7 windows on wide rows)
+constexpr int kCells(int KT) { return KT ? 2 : 3; }
+
+template <int WAVES_M, int KT, int S>
+__global__ __launch_bounds__(NT, 2) void conv_fused_split(GemmTN p, KcGeom fg, int tiles_m, int tiles_n) {
+  constexpr int QU = kCells(KT);  // cells per thread and slot
+  constexpr int MB = 32;
+  constexpr int BM = MB * WAVES_M;
+  constexpr int WAVES_N = 4 / WAVES_M;
+  constexpr int WN = BN / (MB * WAVES_N);
+  static_assert(WAVES_M * WAVES_N == 4, "4 waves per workgroup");
+
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_b[];
+  unsigned char* Xs = smem_b;  // [2][R][CB]
+  const int slot_b = fg.R * CB;
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave_m = wave / WAVES_N, wave_n = wave % WAVES_N;
+  const int lane_lo = lane & 31;  // row / column inside a block
+  const int lane_hi = lane >> 5;  // which half of the 16 channels the lane supplies
+
+  // consecutive workgroup ids go round-robin over the 8 XCDs: give every XCD a contiguous run of
+  // column tiles with the M tiles of one column tile next to each other (they share x through L2)
+  int bid = blockIdx.x;
+  {
+    const int total = tiles_m * tiles_n;
+    const int per = total >> 3, rem = total & 7;
+    const int xcd = bid & 7, idx = bid >> 3;
+    bid = xcd * per + min(xcd, rem) + idx;
+  }
+  const int tile_n = bid / tiles_m;
+  const int tile_m = bid - tile_n * tiles_m;
+  const int g = blockIdx.y;
+  const int m0 = tile_m * BM;
+
+  // ---- which positions, images and output rows does this workgroup cover ---------------------
+  const int P = p.gHout * p.gWout;
+  int n0, ce;  // positions [n0, ce) of the chunk
+  if (fg.tpi > 0) {
+    const int img = tile_n / fg.tpi;
+    n0 = img * P + (tile_n - img * fg.tpi) * BN;
+    ce = min(n0 + BN, (img + 1) * P);
+  } else {
+    n0 = tile_n * BN;
+    ce = min(n0 + BN, p.Ncols);
+  }
+  const int n_f = n0 / P;
+  const int a_f = (n0 - n_f * P) / p.gWout;
+  const int n_l = (ce - 1) / P;
+  const int a_l = ((ce - 1) - n_l * P) / p.gWout;
+  const int rows_first = ((n_f == n_l ? a_l : p.gHout - 1) - a_f) * p.gs + p.gK;
+  const int len_first = rows_first * fg.Wp;
+  const int len_full = ((p.gHout - 1) * p.gs + p.gK) * fg.Wp;
+  const int rows_last = n_l == n_f ? rows_first : a_l * p.gs + p.gK;
+  const int r_actual = (n_l == n_f ? 0 : len_first + (n_l - n_f - 1) * len_full) + rows_last * fg.Wp;
+
+  // ---- staging: a thread owns cells tid and tid + 256 of every group.  A cell's byte offset inside
+  // the tensor never changes; dead cells (padding, rows this workgroup does not need) get an offset
+  // that fails the buffer range check and load as zero; the channel enters through the scalar offset
+  // of the buffer load.  With S > 1 the pixels of a cell are dead one by one: rows lo_h .. ok_h - 1 and
+  // columns lo_w .. ok_w - 1 of the cell exist.
+  // (`slack` elements before the first image, so that a cell that starts in the padding has an offset)
+  const long long slack = S > 1 ? (long long)p.x_pad * (p.x_w + 1) : 0;
+  const float* Xb = reinterpret_cast<const float*>(p.B) + (long long)n_f * p.x_img - slack;
+  unsigned voff[QU];
+  int lo_h[QU], ok_h[QU], lo_w[QU], ok_w[QU];
+#pragma unroll
+  for (int u = 0; u < QU; ++u) {
+    const int q = tid + u * NT;
+    voff[u] = 0x80000000u;
+    lo_h[u] = ok_h[u] = lo_w[u] = ok_w[u] = 0;
+    if (q < r_actual) {
+      int seg = 0, rem = q, a_lo = a_f;
+      if (q >= len_first) {
+        const int qq = q - len_first;
+        seg = 1 + qq / len_full;
+        rem = qq - (seg - 1) * len_full;
+        a_lo = 0;
+      }
+      const int row = rem / fg.Wp, wp = rem - row * fg.Wp;
+      int h = a_lo * p.gs + row - p.gp, w = wp - p.gp;
+      if (h >= 0 && h < p.gH && w >= 0 && w < p.gW) {
+        if (S > 1) {
+          h = h * S - p.x_pad;
+          w = w * S - p.x_pad;
+          lo_h[u] = -h;
+          lo_w[u] = -w;
+          ok_h[u] = p.x_h - h;
+          ok_w[u] = p.x_w - w;
+        }
+        voff[u] = (unsigned)((seg * p.x_img + slack + (long long)h * p.x_w + w) * 4);
+      }
+    }
+  }
+  // byte offset of channel c of group grp: a channel past the last one repeats it (its kernel values
+  // are zero); S > 1: 16 channels are 16 / (S*S) whole planes
+  const unsigned plane_b = (unsigned)p.x_plane * 4u, row_b = (unsigned)p.x_w * 4u;
+  const __amdgpu_buffer_rsrc_t x_rs =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(Xb), 0, 0x7fffffff, 0x00020000);
+  auto chan_b = [&](int grp, int c) -> unsigned {
+    if (S == 1) return (unsigned)(g * p.gCg + min(grp * CG + c, p.gCg - 1)) * plane_b;
+    constexpr int SS = S * S;
+    const int pl = min(grp * (CG / SS) + c / SS, p.gCg / SS - 1);
+    return (unsigned)(g * (p.gCg / SS) + pl) * plane_b + (unsigned)((c / S) % S) * row_b + (c % S) * 4u;
+  };
+  // no cell of this workgroup lies in the tensor's last image (padded: nor in its first), so loads of S
+  // pixels may run past the ends of a row
+  const bool inner = S > 1 && n_l + 1 < p.Ncols / P && (p.x_pad == 0 || n_f > 0);
+  // step = 2 * (cell u) + (channel half): 8 channels of a cell
+  auto stage_load = [&](float (&stg)[8], int grp, int step) {
+    const int u = step >> 1, v = step & 1;
+    if ((tid & ~63) + u * NT < fg.R) {  // whole waves; lanes past R hold dead cells
+      const unsigned vo = voff[u];
+      if (S > 1 && inner) {
+        // S consecutive pixels of a row of the cell are S channels: one load; pixels beyond the
+        // row (its neighbours', inside the tensor) are cleared when they are stored
+#pragma unroll
+        for (int e = 0; e < 8; e += S) {
+          const int c = v * 8 + e;
+          const int dh = (c / S) % S, vv = (int)(dh >= lo_h[u] && dh < ok_h[u] ? vo : 0x80000000u), co = (int)chan_b(grp, c);
+          if constexpr (S == 4) {
+            const f32x4 t = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(x_rs, vv, co, 0));
+#pragma unroll
+            for (int k = 0; k < 4; ++k) stg[e + k] = t[k];
+          } else if constexpr (S == 2) {
+            const f32x2 t = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(x_rs, vv, co, 0));
+            stg[e] = t[0];
+            stg[e + 1] = t[1];
+          }
+        }
+        return;
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int c = v * 8 + e;
+        unsigned vv = vo;
+        if (S > 1) {
+          const int dh = (c / S) % S, dw = c % S;
+          vv = dh >= lo_h[u] && dh < ok_h[u] && dw >= lo_w[u] && dw < ok_w[u] ? vo : 0x80000000u;
+        }
+        stg[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(x_rs, (int)vv, (int)chan_b(grp, c), 0));
+      }
+    }
+  };
+  auto stage_store = [&](const float (&stg)[8], int slot, int step) {
+    const int u = step >> 1, v = step & 1;
+    const int q = tid + u * NT;
+    if (q < fg.R) {
+      u32x4 h, m, l;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        unsigned a, b, c;
+        float x0 = stg[2 * e], x1 = stg[2 * e + 1];
+        if (S > 1) {
+          const int d0 = (2 * e) % S, d1 = (2 * e + 1) % S;
+          x0 = d0 >= lo_w[u] && d0 < ok_w[u] ? x0 : 0.f;
+          x1 = d1 >= lo_w[u] && d1 < ok_w[u] ? x1 : 0.f;
+        }
+        split_pair(x0, x1, &a, &b, &c);
+        h[e] = a;
+        m[e] = b;
+        l[e] = c;
+      }
+      u32x4* dst = reinterpret_cast<u32x4*>(Xs + slot * slot_b + q * CB + v * 16);
+      dst[0] = h;
+      dst[2] = m;
+      dst[4] = l;
+    }
+  };
+  {
+    float first[2 * QU][8];
+#pragma unroll
+    for (int s = 0; s < 2 * QU; ++s) stage_load(first[s], 0, s);
+#pragma unroll
+    for (int s = 0; s < 2 * QU; ++s) stage_store(first[s], 0, s);
+  }
+  // The next group's four steps, FL at a time: loaded in tile `first`, stored in tile `last`, so that
+  // the MFMAs between cover the way to memory.  Register budget decides FL; 5 x 5 kernels have the
+  // tiles to go one by one.
+  constexpr int FL = KT == 5 ? 1 : KT == 3 && S == 1 ? 4 : 2;  // KT == 0: one cell
+  float stg[FL][8];
+
+  // ---- kernel-matrix operands straight from the pack (L2), AD tiles ahead
+  constexpr int AD = KT == 3 ? 3 : KT == 5 ? 5 : 2;
+  const int tpg = KT ? KT * KT : tiles_per_group(p.gK);
+  const int ktiles = fg.ngroups * tpg;
+  const unsigned short* Abase = reinterpret_cast<const unsigned short*>(p.A) +
+                                ((long long)g * p.a_gs * 3 + (long long)(m0 + wave_m * MB) * CG);
+  const __amdgpu_buffer_rsrc_t a_rs =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned short*>(Abase), 0, 0x7fffffff, 0x00020000);
+  const int a_voff = (lane_lo * CG + lane_hi * 8) * 2;  // bytes inside a term
+  const unsigned term_b = (unsigned)p.Mpad * CG * 2u;
+  u32x4 a[AD][3];
+  auto load_a = [&](int set, int t) {
+    const unsigned so = (unsigned)min(t, ktiles - 1) * (3u * term_b);
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+      a[set][q] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(a_rs, a_voff, (int)(so + q * term_b), 0));
+  };
+
+  floatx16 acc_h[WN], acc_c[WN];  // h*h, and the corrections
+#pragma unroll
+  for (int j = 0; j < WN; ++j)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc_h[j][r] = acc_c[j][r] = 0.f;
+
+  // per-lane byte offset of each owned position's cell
+  const int bn = wave_n * WN * MB + lane_lo;
+  int bbase[WN];
+#pragma unroll
+  for (int j = 0; j < WN; ++j) {
+    const int col = n0 + bn + j * MB;
+    int cb = 0;
+    if (col < ce) {
+      const int n = col / P, pix = col - n * P;
+      const int r = pix / p.gWout, c = pix - r * p.gWout;
+      const int seg = n == n_f ? 0 : len_first + (n - n_f - 1) * len_full;
+      const int a_lo = n == n_f ? a_f : 0;
+      cb = seg + (r - a_lo) * p.gs * fg.Wp + c * p.gs;
+    }
+    bbase[j] = cb * CB + lane_hi * 16;
+  }
+
+#pragma unroll
+  for (int e = 0; e < AD; ++e) load_a(e, e);
+  __syncthreads();  // slot 0 is visible
+
+  // operand sets of B: the two blocks that are read and multiplied in turn; with one block per tile
+  // the set goes with the tile
+  constexpr int NB = WN == 1 ? AD : 2;
+  u32x4 b[NB][3];
+  auto read_b = [&](int set, int j, int off) {
+    const u32x4* src = reinterpret_cast<const u32x4*>(Xs + bbase[j] + off);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) b[set][q] = src[2 * q];
+  };
+  read_b(0, 0, 0);
+  int slot = 0;
+
+  // One tile: block j's operand is read while block j - 1 is multiplied, the next tile's first
+  // block (at byte offset `nxt`) behind the last but one; the registers of this tile's A operand are
+  // reloaded with tile t + AD behind its last MFMA.  In the last tile of a group (`turn`) the
+  // workgroup meets before the next group's first read: every cell of it has been published by
+  // then, and nobody reads the other slot's old cells any more.
+  auto mfma6 = [&](int set, int bs, int j) {
+    __builtin_amdgcn_sched_barrier(0);
+#define CCT_M(X, Y, ACC)                                                                       \
+  ACC = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[set][X]),          \
+                                                __builtin_bit_cast(bf16x8, b[bs][Y]), ACC, 0, 0, 0)
+    CCT_M(2, 0, acc_c[j]);
+    CCT_M(0, 2, acc_c[j]);
+    CCT_M(1, 1, acc_c[j]);
+    CCT_M(1, 0, acc_c[j]);
+    CCT_M(0, 1, acc_c[j]);
+    CCT_M(0, 0, acc_h[j]);
+#undef CCT_M
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto tile = [&](int set, int t, int cur, int nxt, bool turn) {
+#pragma unroll
+    for (int j = 0; j < WN; ++j) {
+      if (j + 1 < WN) {
+        read_b((j + 1) & 1, j + 1, cur);
+      } else {
+        if (turn) __syncthreads();
+        read_b(WN == 1 ? (set + 1) % AD : 0, 0, nxt);
+      }
+      mfma6(set, WN == 1 ? set : j & 1, j);
+    }
+    load_a(set, t + AD);
+  };
+  static_assert(WN == 1 || WN % 2 == 0, "block 0 of every tile uses operand set 0");
+
+  if constexpr (KT != 0) {
+    constexpr int KK = KT * KT;
+    for (int grp = 0; grp < fg.ngroups; ++grp) {
+      const bool more = grp + 1 < fg.ngroups;
+      const int base = slot * slot_b, other = (slot ^ 1) * slot_b;
+#pragma unroll
+      for (int tt = 0; tt < KK; ++tt) {
+        if (more) {
+          constexpr int NP = 2 * QU / FL;  // phases; phase f is loaded at f * KK / NP, stored before the next
+#pragma unroll
+          for (int f = 0; f < NP; ++f) {
+            if (tt == (f + 1) * (KK - 1) / NP)
+#pragma unroll
+              for (int s = 0; s < FL; ++s) stage_store(stg[s], slot ^ 1, f * FL + s);
+            if (tt == f * (KK - 1) / NP)
+#pragma unroll
+              for (int s = 0; s < FL; ++s) stage_load(stg[s], grp + 1, f * FL + s);
+          }
+        }
+        const int ti = tt / KT, tj = tt % KT, ni = (tt + 1) / KT, nj = (tt + 1) % KT;
+        const bool last = tt == KK - 1;
+        tile(tt % AD, grp * KK + tt, base + (ti * fg.Wp + tj) * CB,
+             last ? (more ? other : base) : base + (ni * fg.Wp + nj) * CB, last && more);
+      }
+      if (more) slot ^= 1;
+    }
+  } else {
+    static_assert(FL == 2 || KT != 0, "a cell at a time");
+    const int step = max(2, tpg / (2 * QU) * 2);  // tpg is even and >= 4
+    int t = 0;
+    for (int grp = 0; grp < fg.ngroups; ++grp) {
+      const bool more = grp + 1 < fg.ngroups;
+      const int base = slot * slot_b, other = (slot ^ 1) * slot_b;
+      int ti = 0, tj = 0;
+      for (int tt = 0; tt < tpg; tt += AD) {
+#pragma unroll
+        for (int e = 0; e < AD; ++e) {
+          const int ts = tt + e;
+          if (more) {
+            // cell f is loaded in tile f * step and stored in tile (f + 1) * step, the last one (and
+            // what a short group leaves no tile for) in the group's last tile
+            if (e == 0) {
+#pragma unroll
+              for (int f = 0; f < QU; ++f) {
+                if (f > 0 && ts == f * step) {
+#pragma unroll
+                  for (int s = 0; s < 2; ++s) stage_store(stg[s], slot ^ 1, 2 * (f - 1) + s);
+                }
+                if (ts == f * step) {
+#pragma unroll
+                  for (int s = 0; s < 2; ++s) stage_load(stg[s], grp + 1, 2 * f + s);
+                }
+              }
+            }
+            if (e == AD - 1 && ts == tpg - 1) {
+#pragma unroll
+              for (int f = 0; f < QU; ++f) {
+                if (f * step >= tpg) {
+#pragma unroll
+                  for (int s = 0; s < 2; ++s) stage_load(stg[s], grp + 1, 2 * f + s);
+                }
+                if ((f + 1) * step >= tpg || f == QU - 1) {
+#pragma unroll
+                  for (int s = 0; s < 2; ++s) stage_store(stg[s], slot ^ 1, 2 * f + s);
+                }
+              }
+            }
+          }
+          const bool last = ts == tpg - 1;
+          const int cur = base + (ti * fg.Wp + tj) * CB;
+          if (++tj == p.gK) {
+            tj = 0;
+            if (++ti == p.gK) ti = 0;  // zero tile: any cell of the group
+          }
+          tile(e, t, cur, last ? (more ? other : base) : base + (ti * fg.Wp + tj) * CB, last && more);
+          ++t;
+        }
+      }
+      if (more) slot ^= 1;
+    }
+  }
+
+  // ---- epilogue: Type-1 lifting + bias, or the depth-to-space store of a strided backward-data
+  // pass.  Accumulator register r is row 8*(r/4) + 4*(lane/32) + r%4 of the wave's rows: four
+  // consecutive rows per lane.
+  const int mw = m0 + wave_m * MB;
+  bool bad = false;
+#pragma unroll
+  for (int j = 0; j < WN; ++j)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      acc_h[j][r] += acc_c[j][r];
+      bad |= acc_h[j][r] != acc_h[j][r];
+    }
+  if (p.d2s) {
+    float* __restrict__ D = p.C;
+    const int ss = p.dS * p.dS;
+#pragma unroll
+    for (int j = 0; j < WN; ++j) {
+      const int col = n0 + bn + j * MB;
+      if (col >= ce) continue;
+      const int n = col / P, pix = col - n * P;
+      const int ga = pix / p.gWout, gb = pix - ga * p.gWout;
+      const long long img = ((long long)n * p.dCtot + (long long)g * p.dCg) * p.dH;
+#pragma unroll
+      for (int r4 = 0; r4 < 16; r4 += 4) {
+        // the lane's four consecutive rows m .. m+3 (m a multiple of 4)
+        const int m = mw + (r4 >> 2) * 8 + lane_hi * 4;
+        if (m >= p.M) continue;
+        const int ci = fdiv_u(m, p.d_divSS_M, p.d_divSS_sh), rem = m - ci * ss;
+        const int rh = fdiv_u(rem, p.d_divS_M, p.d_divS_sh), rw = rem - rh * p.dS;
+        const int h = ga * p.dS + rh - p.dP, w = gb * p.dS + rw - p.dP;
+        float* dst = D + ((img + (long long)ci * p.dH) + h) * p.dW + w;
+        if ((p.dS & 3) == 0) {
+          // stride a multiple of 4: the four rows are four consecutive pixels of one row of dx
+          if ((unsigned)h >= (unsigned)p.dH) continue;
+          if (w >= 0 && w + 3 < p.dW && m + 3 < p.M) {
+            f32x4u v = {acc_h[j][r4], acc_h[j][r4 + 1], acc_h[j][r4 + 2], acc_h[j][r4 + 3]};
+            *reinterpret_cast<f32x4u*>(dst) = v;  // 4-byte aligned
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (m + e < p.M && (unsigned)(w + e) < (unsigned)p.dW) dst[e] = acc_h[j][r4 + e];
+          }
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int me = m + e;
+            if (me < p.M) {
+              const int cie = fdiv_u(me, p.d_divSS_M, p.d_divSS_sh), reme = me - cie * ss;
+              const int rhe = fdiv_u(reme, p.d_divS_M, p.d_divS_sh), rwe = reme - rhe * p.dS;
+              const int he = ga * p.dS + rhe - p.dP, we = gb * p.dS + rwe - p.dP;
+              if ((unsigned)he < (unsigned)p.dH && (unsigned)we < (unsigned)p.dW)
+                D[((img + (long long)cie * p.dH) + he) * p.dW + we] = acc_h[j][r4 + e];
+            }
+          }
+        }
+      }
+    }
+  } else {
+    float* __restrict__ C = p.C + (long long)g * p.c_gs;
+    const float* bias = p.bias ? p.bias + (long long)g * p.bias_gs : nullptr;
+    const bool full_m = m0 + BM <= p.M;
+#pragma unroll
+    for (int j = 0; j < WN; ++j) {
+      const int col = n0 + bn + j * MB;
+      if (col >= ce) continue;
+      float* __restrict__ cl = C + col_offset(p.cmap, col) + (long long)(mw + lane_hi * 4) * p.c_ms;
+      const float* bl = bias ? bias + mw + lane_hi * 4 : nullptr;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int row = (r >> 2) * 8 + (r & 3);  // relative to mw + 4*lane_hi
+        if (full_m || mw + row + lane_hi * 4 < p.M) {
+          float v = acc_h[j][r];
+          if (bl) v += bl[row];
+          cl[(long long)row * p.c_ms] = v;
+        }
+      }
+    }
+  }
+  if (!bad) return;
+
+  // ---- results that are not a number: redo them one by one (split_bf16.h)
+#pragma unroll 1
+  for (int j = 0; j < WN; ++j) {
+    const int col = n0 + bn + j * MB;
+    if (col >= ce) continue;
+    const int n = col / P, pix = col - n * P;
+    const int r_ = pix / p.gWout, c_ = pix - r_ * p.gWout;
+#pragma unroll 1
+    for (int r = 0; r < 16; ++r) {
+      const int m = mw + (r >> 2) * 8 + (r & 3) + lane_hi * 4;
+      if (m >= p.M) continue;
+      float* dst;
+      if (p.d2s) {
+        const int ss = p.dS * p.dS, ci = m / ss, rem = m - ci * ss;
+        const int h = r_ * p.dS + rem / p.dS - p.dP, w = c_ * p.dS + rem % p.dS - p.dP;
+        if ((unsigned)h >= (unsigned)p.dH || (unsigned)w >= (unsigned)p.dW) continue;
+        dst = p.C + (((long long)n * p.dCtot + (long long)g * p.dCg + ci) * p.dH + h) * p.dW + w;
+      } else {
+        dst = p.C + (long long)g * p.c_gs + col_offset(p.cmap, col) + (long long)m * p.c_ms;
+      }
+      const float old = *dst;
+      if (old == old) continue;
+      float v = plain_sum<S>(p, fg, g, m, n, r_, c_);
+      if (!p.d2s && p.bias) v += p.bias[(long long)g * p.bias_gs + m];
+      *dst = v;
+    }
+  }
+}
+
+// The three terms of a kernel matrix in the layout above: pack[q][tile][term][m][16], zero padded in
+// m, in the channels of the last group and in the tiles beyond a group's taps.
+//   kind 0: m = kernel oo, channel = input channel ci, value w[oo, ci, i, j]
+//   kind 1 (backward-data, stride 1): m = input channel, channel = kernel, w[oo, ci, K-1-i, K-1-j]
+//   kind 2 (backward-data, stride s): m = (ci*s + rh)*s + rw, channel = kernel,
+//           w[oo, ci, rh + s*(U-1-i), rw + s*(U-1-j)], 0 where that index reaches K
+//   kind 3 (space to depth): m = kernel, channel = (ci*s + dh)*s + dw, w[oo, ci, i*s + dh, j*s + dw],
+//           0 where that index reaches K
+struct SplitPack {
+  int kind, G, Og, Cg, K, s, U, Mpad, tpg, ngroups;
+};
+__global__ __launch_bounds__(256) void pack_split_kernel(const float* __restrict__ w,
+                                                         unsigned short* __restrict__ pack, SplitPack d) {
+  const long long per_group = (long long)d.ngroups * d.tpg * d.Mpad * CG;
+  const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
+  if (t >= per_group * d.G) return;
+  const int q = (int)(t / per_group);
+  long long e = t - q * per_group;
+  const int c = (int)(e % CG);
+  e /= CG;
+  const int m = (int)(e % d.Mpad);
+  const int tile = (int)(e / d.Mpad);
+  const int grp = tile / d.tpg, tap = tile - grp * d.tpg;
+  const int i = tap / d.U, j = tap - i * d.U;
+  const int ch = grp * CG + c;
+  int oo = m, ci = ch, wi = i, wj = j;
+  if (d.kind == 1) {
+    oo = ch; ci = m; wi = d.K - 1 - i; wj = d.K - 1 - j;
+  } else if (d.kind == 2) {
+    const int ss = d.s * d.s, rem = m % ss;
+    oo = ch; ci = m / ss;
+    wi = rem / d.s + d.s * (d.U - 1 - i);
+    wj = rem % d.s + d.s * (d.U - 1 - j);
+  } else if (d.kind == 3) {
+    const int ss = d.s * d.s, rem = ch % ss;
+    ci = ch / ss;
+    wi = i * d.s + rem / d.s;
+    wj = j * d.s + rem % d.s;
+  }
+  float v = 0.0f;
+  if (i < d.U && oo < d.Og && ci < d.Cg && wi >= 0 && wi < d.K && wj >= 0 && wj < d.K)
+    v = w[((((long long)q * d.Og + oo) * d.Cg + ci) * d.K + wi) * d.K + wj];
+  unsigned short h, mm, l;
+  split_value(v, &h, &mm, &l);
+  unsigned short* dst = pack + ((((long long)q * d.ngroups * d.tpg + tile) * 3) * d.Mpad + m) * CG + c;
+  const long long term = (long long)d.Mpad * CG;
+  dst[0] = h;
+  dst[term] = mm;
+  dst[2 * term] = l;
+}
+
+inline long long column_tiles(const GemmTN& p, const KcGeom& fg, long long nimg) {
+  const long long P = (long long)p.gHout * p.gWout;
+  return fg.tpi > 0 ? fg.tpi * nimg : (P * nimg + BN - 1) / BN;
+}
+
+template <int WAVES_M, int KT, int S>
+int launch_variant(const GemmTN& p, const KcGeom& fg, size_t lds, hipStream_t st) {
+  constexpr int BM = 32 * WAVES_M;
+  const int tiles_m = p.Mpad / BM;
+  const long long tn = column_tiles(p, fg, p.Ncols / (p.gHout * p.gWout));
+  const long long blocks = (long long)tiles_m * tn;
+  if (blocks <= 0 || blocks >= 2147483647LL || p.G > 65535) return CCT_EUNSUPPORTED;
+  dim3 grid((unsigned)blocks, (unsigned)p.G);
+  char name[96];
+  snprintf(name, sizeof(name), "conv_fused_split<%d, %d, %d>%s", BM, KT, S, p.d2s ? " strided" : "");
+  const double nimg = (double)p.Ncols / (p.gHout * p.gWout);
+  const double x_bytes = 4.0 * nimg * p.x_img;
+  const double y_bytes = p.d2s ? 4.0 * nimg * p.dCtot * p.dH * p.dW : 4.0 * (double)p.M * p.Ncols * p.G;
+  ProfScope ps(name, p.prof_flops > 0 ? p.prof_flops : 2.0 * p.M * p.Ncols * p.Kdim * p.G,
+               x_bytes + y_bytes + 4.0 * (double)p.M * p.Kdim * p.G, st);
+  constexpr auto kern = conv_fused_split<WAVES_M, KT, S>;
+  if (const int rc = ensure_dynamic_lds<kern>(2 * kLdsCap)) return rc;
+  hipLaunchKernelGGL(kern, grid, dim3(NT), lds, st, p, fg, tiles_m, (int)tn);
+  CCT_CHECK_LAUNCH();
+  return CCT_OK;
+}
+
+template <int WAVES_M>
+int launch_rows(const GemmTN& p, const KcGeom& fg, size_t lds, hipStream_t st) {
+  if (p.s2d == 4) {
+    if (p.gK == 3) return launch_variant<WAVES_M, 3, 4>(p, fg, lds, st);
+    return p.gK == 5 ? CCT_EUNSUPPORTED : launch_variant<WAVES_M, 0, 4>(p, fg, lds, st);
+  }
+  if (p.s2d == 2) {
+    if (p.gK == 3) return launch_variant<WAVES_M, 3, 2>(p, fg, lds, st);
+    return p.gK == 5 ? CCT_EUNSUPPORTED : launch_variant<WAVES_M, 0, 2>(p, fg, lds, st);
+  }
+  if (p.gK == 3) return launch_variant<WAVES_M, 3, 1>(p, fg, lds, st);
+  if (p.gK == 5) return launch_variant<WAVES_M, 5, 1>(p, fg, lds, st);
+  return launch_variant<WAVES_M, 0, 1>(p, fg, lds, st);
+}
+
+bool split_geom(const GemmTN& p, KcGeom* fg, size_t* lds) {
+  // the pack of one group is addressed with 32-bit byte offsets
+  if (p.bf16 || (long long)p.Mpad * p.Kpad * 6 >= (1LL << 31)) return false;
+  if (p.M <= 32) return false;  // most of a tile's rows would be padding
+  if (p.s2d && p.gK == 5) return false;  // kernels of 9 and 10 (stride 2), 17 to 20 (stride 4): no form
+  GeomRules rules;
+  rules.r_step = 8;
+  rules.qu = kCells(p.gK == 3 || (p.gK == 5 && !p.s2d) ? p.gK : 0);
+  // what else runs these layers is at most half as fast, so up to half of a group's channels may be
+  // padding, and a quarter of the positions
+  rules.chan_num = 2; rules.chan_den = 1;
+  rules.tpi_num = 5; rules.tpi_den = 4;
+  // two workgroups per CU where the staged rows allow it
+  return kc::make_geom(p, 0, CB, fg, lds, kLdsCap, rules) || kc::make_geom(p, 0, CB, fg, lds, 2 * kLdsCap - 1024, rules);
+}
+
+// Row tile: the largest that divides the padded rows, smaller while the launch would not put a
+// workgroup on every CU.
+inline int split_bm(const GemmTN& p, long long tn) {
+  int BM = p.Mpad % 128 == 0 ? 128 : p.Mpad % 64 == 0 ? 64 : 32;
+  while (BM > 32 && tn * (p.Mpad / BM) * p.G < 256) BM /= 2;
+  return BM;
+}
+
+}  // namespace
+
+int conv_fused_split_mpad(int M) { return M <= 32 ? 32 : (M + 63) / 64 * 64; }
+
+long long conv_fused_split_kpad(int channels_per_group, int K) {
+  return (long long)((channels_per_group + CG - 1) / CG) * tiles_per_group(K) * CG;
+}
+
+bool conv_fused_split_fits(const GemmTN& p) {
+  KcGeom fg;
+  size_t lds;
+  return split_geom(p, &fg, &lds);
+}
+
+// Sustained rate of the tiles, padding included, plus what filling and draining a round of workgroups
+// costs; a launch that leaves CUs idle takes at least the serial chain of one workgroup.  Measured:
+// 64- and 128-row tiles 255 TFLOP/s, 32-row tiles (four waves read the same rows of the pack) 150;
+// about 6 us per round of 512 workgroups and 0.27 us per K tile of a lone workgroup.
+double conv_fused_split_seconds(const GemmTN& p, int nimg) {
+  KcGeom fg;
+  size_t lds;
+  if (!split_geom(p, &fg, &lds)) return 1.0;
+  const long long tn = column_tiles(p, fg, nimg);
+  const int BM = split_bm(p, tn);
+  const double wgs = (double)tn * (p.Mpad / BM) * p.G;
+  const double flops = 2.0 * wgs * BM * BN * p.Kpad;
+  return std::max(flops / (BM == 32 ? 150.0e12 : 255.0e12) + std::ceil(wgs / 512.0) * 6.0e-6,
+                  (double)p.Kpad / CG * 0.27e-6 + 6.0e-6);
+}
+
+int launch_pack_split(const float* w, void* pack, int kind, int G, int Og, int Cg, int K, int s, int Mpad,
+                      hipStream_t st) {
+  const int U = kind >= 2 ? (K + s - 1) / s : K;
+  const int channels = kind == 1 || kind == 2 ? Og : kind == 3 ? Cg * s * s : Cg;
+  SplitPack d{kind, G, Og, Cg, K, s, U, Mpad, tiles_per_group(U), (channels + CG - 1) / CG};
+  const long long total = (long long)G * d.ngroups * d.tpg * Mpad * CG;
+  const long long blocks = (total + 255) / 256;
+  if (blocks <= 0 || blocks >= 2147483647LL) return CCT_EUNSUPPORTED;
+  ProfScope ps("pack_split_kernel", 0.0, 4.0 * G * Og * Cg * K * K + 6.0 * total, st);
+  hipLaunchKernelGGL(pack_split_kernel, dim3((unsigned)blocks), dim3(256), 0, st, w,
+                     reinterpret_cast<unsigned short*>(pack), d);
+  CCT_CHECK_LAUNCH();
+  return CCT_OK;
+}
+
+// p.A must have been written by launch_pack_split with Mpad = conv_fused_split_mpad(M);
+// p.Kpad = conv_fused_split_kpad(...).
+int launch_conv_fused_split(const GemmTN& p0, hipStream_t st) {
+  GemmTN p = p0;
+  colmap_prepare(&p.bmap);
+  colmap_prepare(&p.cmap);
+  if (p.d2s) {
+    if (p.dS < 1 || p.M != p.dCg * p.dS * p.dS) return CCT_EINVAL;
+    make_fastdiv_parts(p.dS * p.dS, &p.d_divSS_M, &p.d_divSS_sh);
+    make_fastdiv_parts(p.dS, &p.d_divS_M, &p.d_divS_sh);
+  }
+  KcGeom fg;
+  size_t lds;
+  if (p.Mpad != conv_fused_split_mpad(p.M) || !split_geom(p, &fg, &lds)) return CCT_EUNSUPPORTED;
+  if (p.Kpad != conv_fused_split_kpad(p.gCg, p.gK)) return CCT_EINVAL;
+  switch (split_bm(p, column_tiles(p, fg, p.Ncols / (p.gHout * p.gWout)))) {
+    case 32: return launch_rows<1>(p, fg, lds, st);
+    case 64: return launch_rows<2>(p, fg, lds, st);
+    default: return launch_rows<4>(p, fg, lds, st);
+  }
+}
+
+}  // namespace cct

@@ -1,0 +1,132 @@
+"""conv_fused_split (fp32 operands as sums of three bf16 terms): the forms of the kernel at the sizes
+where they can go wrong, against the oracle.  The tolerance is the fp32 path's: six bf16 products hold
+a product of two fp32 values to 2^-25, less than the rounding of one fp32 accumulation."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1504_04343_amd import synth
+from gpu_util import TOL_F32, desc_of, dev, gpu_backward_data, gpu_forward, layer, odims, rel_err
+
+pytestmark = pytest.mark.gpu
+
+KERNEL = "conv_fused_split"
+
+#       name        N   C    H   W    O  K  s  p  g
+FORWARD = [
+    layer("m32",    2,  16,  9, 11,  36, 3, 1, 1),           # 32-row tiles, rows to spare
+    layer("m64",    7,  32, 13, 13,  64, 3, 1, 1),           # 64-row tile, tiles across images
+    layer("m128",  33,  40, 13, 13, 128, 3, 1, 1, 2),        # channels past a group's last one
+    layer("m192",  26,  16, 28, 28, 192, 3, 1, 0),           # rows no multiple of 128, one channel group
+    layer("c9",     3,   9, 12, 17,  33, 3, 1, 2),           # channels that fill half of a group
+    layer("k2",     5,  48, 10, 10,  40, 2, 1, 1),           # four taps
+    layer("k4",     2,  24, 15, 12,  70, 4, 1, 2),
+    layer("k5",     4,  48, 27, 27, 130, 5, 1, 2),           # tiles cut per image
+    layer("k7",     2,  16, 37, 40,  36, 7, 1, 3),           # odd tap count: zero tile; three cells per thread
+    layer("k6",     3,  20, 14, 14,  44, 6, 1, 0),
+    layer("wide",   2,  16, 14, 56,  64, 3, 1, 1),           # one workgroup per CU
+    layer("s2cells", 3, 32, 15, 17,  48, 3, 2, 1),           # strided windows over the tensor's own cells
+    layer("s2d2",   5,  16, 57, 57,  40, 5, 2, 0),           # space to depth by 2 (three taps), odd plane
+    layer("s2d2p",  5,  12, 57, 56,  64, 3, 2, 1),           # two taps, padded
+    layer("s2d2k7", 4,   6, 64, 61,  33, 7, 2, 3),           # four taps
+    layer("s2d4",   5,   3, 63, 65,  96, 11, 4, 0),
+    layer("s2d4p",  4,   2, 64, 63,  40, 8, 4, 3),
+    layer("s2d4one", 1,  3, 67, 67,  36, 11, 4, 2),          # the tensor's only image
+]
+BACKWARD = [
+    layer("b32",    2,  36,  9, 11,  16, 3, 1, 1),
+    layer("b128",  33, 128, 13, 13,  40, 3, 1, 1),
+    layer("b_k5",   4,  48, 27, 27,  64, 5, 1, 2),
+    layer("b_p0",   3,  33, 12, 10,  25, 4, 1, 0),
+    layer("b_s4",   3,   3, 63, 65,  32, 11, 4, 0),          # depth to space, 16-byte stores
+    layer("b_s2",   4,  20, 21, 23,  48, 3, 2, 1),
+    layer("b_s3",   4,  10, 21, 23,  48, 5, 3, 2),
+]
+
+
+@pytest.fixture(scope="module")
+def B():
+    import torch
+    assert torch.cuda.is_available()
+    from paper_1504_04343_amd import binding
+    return binding
+
+
+def ran(B, call):
+    """The call's result and the names of the kernels it launched."""
+    B.cct_profile_enable(True)
+    got = call()
+    B.cct_profile_enable(False)
+    return got, [e["name"] for e in B.cct_profile_read()]
+
+
+def ids(layers):
+    return [L.name for L in layers]
+
+
+@pytest.mark.parametrize("L", FORWARD, ids=ids(FORWARD))
+def test_forward(B, L):
+    x, w, b = synth.make_x(L, 3), synth.make_w(L, 3), synth.make_bias(L, 3)
+    got, names = ran(B, lambda: gpu_forward(B, L, x, w, b, B.LOWER_FUSED))
+    assert any(n.startswith(KERNEL) for n in names), names
+    assert rel_err(got, oracle.conv_forward(odims(oracle, L), x, w, b)) <= TOL_F32
+
+
+@pytest.mark.parametrize("L", BACKWARD, ids=ids(BACKWARD))
+def test_backward_data(B, L):
+    w, dy = synth.make_w(L, 3), synth.make_dy(L, 3)
+    got, names = ran(B, lambda: gpu_backward_data(B, L, w, dy, B.LOWER_FUSED))
+    assert any(n.startswith(KERNEL) for n in names), names
+    assert rel_err(got, oracle.conv_backward_data(odims(oracle, L), w, dy)) <= TOL_F32
+
+
+def test_precision(B):
+    """Closer to 64 bits than an fp32 accumulation of 2304 products can be expected to come: the sums'
+    one rounding per 16 products measures 2.3e-7 (2-norm), one per 2 products 6e-7."""
+    L = layer("prec", 8, 256, 13, 13, 128, 3, 1, 1, x_dist="relu_normal")
+    x, w = synth.make_x(L, 1), synth.make_w(L, 1)
+    got = gpu_forward(B, L, x, w, None, B.LOWER_FUSED).astype(np.float64)
+    want = oracle.conv_forward(odims(oracle, L), x, w, None)
+    assert np.linalg.norm(got - want) / np.linalg.norm(want) <= 4e-7
+
+
+SPECIAL = [("plain", layer("nf", 3, 16, 13, 13, 40, 3, 1, 1)),
+           ("s2d", layer("nf2", 3, 3, 31, 31, 40, 7, 4, 0)),
+           ("zero_tile", layer("nf7", 2, 16, 13, 13, 40, 7, 1, 3))]
+
+
+@pytest.mark.parametrize("L", [L for _, L in SPECIAL], ids=[n for n, _ in SPECIAL])
+def test_not_finite_inputs(B, L):
+    """Infinities, NaN and values beyond bf16's range reach exactly the outputs they reach in fp32."""
+    x, w, b = synth.make_x(L, 5), synth.make_w(L, 5), synth.make_bias(L, 5)
+    x[0, 0, 0, 0], x[1, 1, 5, 6], x[1, 2, 12, 12], x[-1, 1, 4, 4] = np.inf, -np.inf, np.nan, 3.4e38
+    x[0, 2, 9, 9] = np.float32(1e38)
+    w[3, 1, 1, 2], w[7, 0, 0, 0], w[9, 0, 2, 2] = np.inf, np.nan, 3.4e38
+    w[11] = 0.0
+    got, names = ran(B, lambda: gpu_forward(B, L, x, w, b, B.LOWER_FUSED))
+    assert any(n.startswith(KERNEL) for n in names), names
+    od = odims(oracle, L)
+    want = oracle.conv_forward(od, x, w, b)
+    assert (np.isnan(got) == np.isnan(want)).all()
+    over = np.abs(want) > np.finfo(np.float32).max     # infinite, or beyond fp32
+    assert (np.isinf(got) == (over & ~np.isnan(want))).all()
+    inf = np.isinf(got)
+    assert (np.sign(got[inf]) == np.sign(want[inf])).all()
+    ok = np.isfinite(got)
+    big = ok & (np.abs(want) > 1e30)
+    assert (np.abs(got[big] - want[big]) <= 1e-5 * np.abs(want[big])).all()
+    assert rel_err(got[ok & ~big], want[ok & ~big]) <= TOL_F32
+
+
+def test_workspace_for_the_fp32_kernel_matrix_is_still_enough(B):
+    """A workspace that holds the fp32 kernel matrix but not its three terms runs the fp32 kernel."""
+    import torch
+    L = layer("ws", 4, 64, 13, 13, 128, 3, 1, 1)
+    x, w, b = synth.make_x(L, 3), synth.make_w(L, 3), synth.make_bias(L, 3)
+    d = desc_of(B, L, B.LOWER_FUSED)
+    full = B.cct_conv_workspace_bytes(d, B.PASS_FORWARD)
+    ws = torch.empty(full * 2 // 3, dtype=torch.uint8, device="cuda")
+    y = torch.full((L.N, L.O, L.Hout, L.Wout), float("nan"), device="cuda")
+    _, names = ran(B, lambda: (B.cct_conv_forward(d, dev(x), dev(w), dev(b), y, ws), torch.cuda.synchronize()))
+    assert not any(n.startswith(KERNEL) for n in names), names
+    assert rel_err(y.cpu().numpy(), oracle.conv_forward(odims(oracle, L), x, w, b)) <= TOL_F32
