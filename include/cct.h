@@ -207,7 +207,10 @@ int cct_conv_backward_data(const cct_conv_desc_t* desc, const float* w, const fl
  *   dw[o,ci,i,j] = sum_{n,r,c} dy[n,o,r,c] * x[n,q*Cg+ci,r*stride+i-pad,c*stride+j-pad]
  *   dbias[o]     = sum_{n,r,c} dy[n,o,r,c]
  * Computed as D^ transposed times the inverse-lifted dy, reduced over all rows of the
- * batched lowered matrix in fixed order (bit-reproducible run to run).
+ * batched lowered matrix in fixed order (bit-reproducible run to run).  With lowering AUTO (any
+ * precision) or FUSED, larger layers run on copies of x and dy in the workspace that are
+ * regrouped by image (8 images of a pixel side by side), never on a lowered matrix; a workspace
+ * without room for the copies of 32 images runs the picked layout.
  * x, dy: device, read.  dw: device, written.  dbias: device, O floats, may be NULL.
  */
 int cct_conv_backward_weights(const cct_conv_desc_t* desc, const float* x, const float* dy,

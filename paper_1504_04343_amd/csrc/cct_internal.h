@@ -168,6 +168,17 @@ struct ConvBwdW {
 bool conv_bwdw_fused_fits(int C, int H, int W, int K, int s, int pad, int Hout, int Wout, int Cg,
                           int Og, int O);
 int launch_conv_bwdw_fused(const ConvBwdW& p, hipStream_t st);
+// Backward-weights pass on granules of 8 images (conv_bwdw_img.hip), fp32 as three bf16 terms or bf16:
+// plan for nimg images at a time and the workspace it needs.  false = sizes it cannot address.
+struct BwdwImgPlan {
+  int BM, terms, S, split_cols;
+  long long xs_off, ds_off, part_off, sums_off, total;  // workspace layout (bytes)
+  double seconds;  // estimate for the optimizer's cost model
+};
+bool bwdw_img_plan(const cct_conv_desc_t& d, long long nimg, BwdwImgPlan* P);
+// One chunk of nimg images; accumulate: add to dw and dbias instead of writing them.
+int launch_bwdw_img(const cct_conv_desc_t& d, const BwdwImgPlan& P, int nimg, const float* x,
+                    const float* dy, float* dw, float* dbias, int accumulate, char* ws, hipStream_t st);
 // Tile sizes the launchers will use for a problem (so that the planner can pad the packs).
 void gemm_tn_tile(int M, int Ncols, int* BM, int* BN, int* BK);
 void gemm_nt_tile(int M, int N, int* BM, int* BN, int* BK);

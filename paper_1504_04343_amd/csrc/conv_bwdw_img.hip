@@ -1,0 +1,590 @@
+// Backward-weights pass on the bf16 matrix cores with the images as the contiguous reduction index.
+//
+//     dw[o][(ci,i,j)] = sum_{n, r, c} dy[n, o, r, c] * xpad[n, ci, r*s + i, c*s + j]
+//
+// A lane of v_mfma_f32_32x32x16_bf16 takes 8 consecutive reduction indices of its row as one 16-byte
+// operand.  Taken along a row of the image those 8 values would start at any column (the tap shifts
+// them); taken over 8 IMAGES at one pixel they are one aligned granule whatever the tap.  So the pass is
+//   1. bwdw_img_prep: x (zero padded) and dy are rewritten once as granules of 8 images,
+//          xs[image group][padded row][padded column][term][channel],  ds[image group][pixel][term][kernel],
+//      in bf16: one term (bf16 operands), or three whose sum is the fp32 value (split_bf16.h).  The same
+//      kernel sums dy for the bias gradient, which reads all of dy anyway;
+//   2. conv_bwdw_img: the matrix product, column = (image group, output pixel) = 8 reduction indices;
+//      row n of the second operand is a tap of a channel, i.e. a constant offset from the column's cell;
+//   3. bwdw_img_reduce: the splits' partial products are added in split order.
+// Nothing of the size of the lowered matrix exists (no K*K blow-up).
+//
+// The product: a workgroup owns BM kernels x 256 lowered rows, ordered (block of 32 channels, tap,
+// channel) so that neighbouring lanes read neighbouring granules; a wave owns 64 x 64.  A stage is SLOTS
+// (column, term) pairs of both operands, moved from memory into LDS by buffer loads that write LDS
+// directly: no registers, no vector instruction, no conversion in the loop.  Two stages alternate, one
+// meeting of the workgroup per stage; operand reads are 32 consecutive granules, which do not conflict.
+// Per 16 reduction indices a wave reads 12 KiB of LDS for 24 MFMAs (768 matrix-core cycles), half of
+// what LDS can deliver, and a 128 x 256 workgroup fetches 36 KiB of L2 for 1536 cycles of its CU.
+#include <stdio.h>
+
+#include <algorithm>
+
+#include "cct_internal.h"
+#include "gemm_common.h"
+#include "split_bf16.h"
+
+namespace cct {
+namespace {
+
+constexpr int kImg = 8;       // images per granule
+constexpr int kGran = 16;     // bytes of a granule
+constexpr int BN = 256;       // lowered rows per workgroup
+constexpr int kChanBlock = 32;
+constexpr int kPrepPx = 32, kPrepCh = 32;  // pixels and channels a workgroup of the first step rewrites
+
+// ---- 1. granules of 8 images ------------------------------------------------------------------
+
+// One tensor of the first step: [nimg][C][H][W] -> [group][H + 2*pad][W + 2*pad][TERMS][C] granules.
+struct PrepJob {
+  const float* src;
+  uint4* dst;
+  float* sums;  // bias gradient: [group * pixel tiles][C] partial sums, or null
+  int C, H, W, pad, Wp, pixels;  // pixels: (H + 2*pad) * (W + 2*pad)
+  int tiles_px, tiles_c;
+  unsigned mWp, mTpx, mTc;
+  int sWp, sTpx, sTc;
+};
+
+// Bound by memory: every value is read once (rows of 32 pixels) and written as 2 * TERMS bytes (runs of
+// 32 granules); the transposition goes through LDS.
+template <int TERMS>
+__global__ __launch_bounds__(256) void bwdw_img_prep(PrepJob j0, PrepJob j1, int blocks0, int nimg) {
+  constexpr int ROW = kPrepCh + 1;  // granules between pixels in LDS: 16-byte accesses spread over the banks
+  __shared__ uint4 buf[TERMS][kPrepPx * ROW];
+  const bool second = (int)blockIdx.x >= blocks0;
+  const PrepJob& j = second ? j1 : j0;
+  const int b = second ? (int)blockIdx.x - blocks0 : (int)blockIdx.x;
+  // channel tile fastest: the tiles of one pixel range write the same lines
+  const int bp = fdiv_u(b, j.mTc, j.sTc), tc = b - bp * j.tiles_c;
+  const int ig = fdiv_u(bp, j.mTpx, j.sTpx), tp = bp - ig * j.tiles_px;
+  const int tid = threadIdx.x;
+  const int px = tid & 31, cr = tid >> 5;
+  const int q = tp * kPrepPx + px;
+  const int hp = fdiv_u(q, j.mWp, j.sWp), wp = q - hp * j.Wp;
+  const int h = hp - j.pad, w = wp - j.pad;
+  const bool inside = q < j.pixels && h >= 0 && h < j.H && w >= 0 && w < j.W;
+  const long long plane = (long long)j.H * j.W, img = (long long)j.C * plane;
+  const float* src = j.src + (long long)ig * kImg * img + (long long)h * j.W + w;
+  const int nv = min(kImg, nimg - ig * kImg);
+  float v[kPrepCh / 8][kImg];
+#pragma unroll
+  for (int it = 0; it < kPrepCh / 8; ++it) {
+    const int c = tc * kPrepCh + it * 8 + cr;
+#pragma unroll
+    for (int e = 0; e < kImg; ++e) v[it][e] = inside && c < j.C && e < nv ? src[c * plane + e * img] : 0.f;
+  }
+#pragma unroll
+  for (int it = 0; it < kPrepCh / 8; ++it) {
+    const int cl = it * 8 + cr;
+    uint4 t[TERMS];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float a = v[it][2 * e], c = v[it][2 * e + 1];
+      unsigned hh, mm, ll;
+      if (TERMS == 3) {
+        split_pair(a, c, &hh, &mm, &ll);
+        reinterpret_cast<unsigned*>(&t[1])[e] = mm;
+        reinterpret_cast<unsigned*>(&t[TERMS - 1])[e] = ll;
+      } else {
+        hh = cvt_pk_bf16(a, c);
+      }
+      reinterpret_cast<unsigned*>(&t[0])[e] = hh;
+    }
+#pragma unroll
+    for (int k = 0; k < TERMS; ++k) buf[k][px * ROW + cl] = t[k];
+    if (j.sums) {
+      float s = ((v[it][0] + v[it][1]) + (v[it][2] + v[it][3])) + ((v[it][4] + v[it][5]) + (v[it][6] + v[it][7]));
+#pragma unroll
+      for (int off = 16; off > 0; off >>= 1) s += __shfl_down(s, off, 32);
+      const int c = tc * kPrepCh + cl;
+      if (px == 0 && c < j.C) j.sums[(long long)bp * j.C + c] = s;
+    }
+  }
+  __syncthreads();
+  const int c = tid & 31, r0 = tid >> 5;
+  const int ch = tc * kPrepCh + c;
+  if (ch >= j.C) return;
+#pragma unroll
+  for (int it = 0; it < kPrepPx * TERMS / 8; ++it) {
+    const int u = it * 8 + r0, p = u / TERMS, k = u - p * TERMS;
+    const int qq = tp * kPrepPx + p;
+    if (qq < j.pixels) j.dst[(((long long)ig * j.pixels + qq) * TERMS + k) * j.C + ch] = buf[k][p * ROW + c];
+  }
+}
+
+// ---- 2. the product -----------------------------------------------------------------------------
+
+struct ImgGemm {
+  const unsigned char *xs, *ds;
+  float* part;  // [S][G][M][N], n = (channel block, tap, channel)
+  int M, N, G;
+  int Cg, Og, C, O, K, KK, s, Wp;
+  long long img_cells;  // padded pixels per image
+  int P, Wout;
+  int ncols, split_cols, S, tiles_m, tiles_n;
+  unsigned mP, mWout;
+  int sP, sWout;
+};
+
+typedef __attribute__((address_space(3))) void* lds_ptr;
+
+template <int BM, int TERMS, int SLOTS>
+__global__ __launch_bounds__(BM * 4, 2) void conv_bwdw_img(ImgGemm p) {
+  constexpr int NW = BM / 16;           // waves: 64 rows x 64 lowered rows each
+  constexpr int WAVES_N = BN / 64;
+  constexpr int NCOL = SLOTS / TERMS;   // columns of 8 images per stage
+  static_assert(SLOTS % TERMS == 0 && NCOL % 2 == 0, "a product takes two columns");
+  constexpr int STAGE = SLOTS * (BM + BN) * kGran;
+  // A wave moves the granules of CPW columns, or a WPC-th of one column: one cell address per column.
+  constexpr int CPW = NCOL > NW ? NCOL / NW : 1, WPC = NW > NCOL ? NW / NCOL : 1;
+  constexpr int A_UNITS = TERMS * (BM / 64), A_PER = (A_UNITS + WPC - 1) / WPC;  // of 64 granules
+  constexpr int B_PARTS = BN / 64 / WPC;                                       // row parts per wave
+  static_assert(CPW * NW == NCOL * WPC && (WPC == 1 || A_UNITS <= 2 * A_PER) && WPC <= 2, "whole loads");
+
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_i[];  // [2][A: SLOTS*BM | B: SLOTS*BN]
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave_m = wave / WAVES_N, wave_n = wave % WAVES_N;
+  const int lane_lo = lane & 31, lane_hi = lane >> 5;
+
+  // consecutive workgroup ids go round-robin over the 8 XCDs: give every XCD a contiguous run of
+  // (split, tile) pairs, tile fastest, so that the tiles of one split share both operands through L2
+  int bid = blockIdx.x;
+  {
+    const int total = p.tiles_m * p.tiles_n * p.S;
+    const int per = total >> 3, rem = total & 7;
+    const int xcd = bid & 7, slot = bid >> 3;
+    bid = xcd * per + min(xcd, rem) + slot;
+  }
+  const int ntiles = p.tiles_m * p.tiles_n;
+  const int s = bid / ntiles, tile = bid - s * ntiles;
+  const int tile_m = tile / p.tiles_n, tile_n = tile - tile_m * p.tiles_n;
+  const int g = blockIdx.y;
+  const int m0 = tile_m * BM, n0 = tile_n * BN;
+  const int c_begin = s * p.split_cols, c_end = min(p.ncols, c_begin + p.split_cols);
+
+  // A thread loads the same rows of both operands in every stage: constant byte offsets from the column's
+  // granules.  Rows past the last one repeat it (their products are not stored).
+  const int sub = wave % WPC;
+  unsigned a_voff[BM / 64], b_voff[B_PARTS];
+#pragma unroll
+  for (int u = 0; u < BM / 64; ++u) a_voff[u] = (unsigned)min(m0 + u * 64 + lane, p.M - 1) * kGran;
+#pragma unroll
+  for (int u = 0; u < B_PARTS; ++u) {
+    const int n = min(n0 + (sub * B_PARTS + u) * 64 + lane, p.N - 1);
+    const int cb = n / (p.KK * kChanBlock), width = min(kChanBlock, p.Cg - cb * kChanBlock);
+    const int rem = n - cb * p.KK * kChanBlock, tap = rem / width, cl = rem - tap * width;
+    const int i = tap / p.K, j = tap - i * p.K;
+    b_voff[u] = (unsigned)(((long long)(i * p.Wp + j) * TERMS * p.C + cb * kChanBlock + cl) * kGran);
+  }
+  const unsigned char* Ag = p.ds + (long long)g * p.Og * kGran;
+  const unsigned char* Bg = p.xs + (long long)g * p.Cg * kGran;
+  const long long a_col = (long long)TERMS * p.O * kGran, b_cell = (long long)TERMS * p.C * kGran;
+
+  // Columns past the end of the split have an empty range: they load as zeros.
+  auto load_stage = [&](int buf, int c0) {
+    unsigned char* As = smem_i + buf * STAGE;
+    unsigned char* Bs = As + SLOTS * BM * kGran;
+#pragma unroll
+    for (int v = 0; v < CPW; ++v) {
+      const int cc = wave / WPC + v * NW;
+      const int col = c0 + cc, cl = min(col, c_end - 1), range = col < c_end ? 0x7fffffff : 0;
+      const int ig = fdiv_u(cl, p.mP, p.sP), pix = cl - ig * p.P;
+      const int r_ = fdiv_u(pix, p.mWout, p.sWout), c_ = pix - r_ * p.Wout;
+      const long long cell = ig * p.img_cells + (long long)(r_ * p.s) * p.Wp + c_ * p.s;
+      const __amdgpu_buffer_rsrc_t ra =
+          __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(Ag + cl * a_col), 0, range, 0x00020000);
+      const __amdgpu_buffer_rsrc_t rb =
+          __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(Bg + cell * b_cell), 0, range, 0x00020000);
+#pragma unroll
+      for (int k = 0; k < TERMS; ++k)
+#pragma unroll
+        for (int u = 0; u < B_PARTS; ++u)
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(
+              rb, (lds_ptr)(Bs + ((cc * TERMS + k) * BN + (sub * B_PARTS + u) * 64) * kGran), 16, (int)b_voff[u],
+              k * p.C * kGran, 0, 0);
+#pragma unroll
+      for (int k = 0; k < TERMS; ++k)
+#pragma unroll
+        for (int u = 0; u < BM / 64; ++u) {
+          constexpr int half = A_PER;
+          const int unit = k * (BM / 64) + u;  // the first A_PER units are the first wave's
+          if (WPC == 1 || (unit / half) == sub)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_ptr)(As + ((cc * TERMS + k) * BM + u * 64) * kGran), 16,
+                                                     (int)a_voff[u], k * p.O * kGran, 0, 0);
+        }
+    }
+  };
+
+  // three terms: h*h alone in one accumulator, the corrections in the other (split_bf16.h)
+  floatx16 acc[2][2], acc_c[TERMS == 3 ? 2 : 1][TERMS == 3 ? 2 : 1];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        acc[i][j][r] = 0.f;
+        if constexpr (TERMS == 3) acc_c[i][j][r] = 0.f;
+      }
+
+  const int stages = (c_end - c_begin + NCOL - 1) / NCOL;  // <= 0 for an empty split
+  if (stages > 0) load_stage(0, c_begin);
+  const int a_lds = (lane_hi * TERMS * BM + wave_m * 64 + lane_lo) * kGran;
+  const int b_lds = SLOTS * BM * kGran + (lane_hi * TERMS * BN + wave_n * 64 + lane_lo) * kGran;
+  for (int t = 0; t < stages; ++t) {
+    // this stage's loads have landed and nobody reads the other buffer any more
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+    __syncthreads();
+    if (t + 1 < stages) load_stage((t + 1) & 1, c_begin + (t + 1) * NCOL);
+    const unsigned char* st = smem_i + (t & 1) * STAGE;
+#pragma unroll
+    for (int kb = 0; kb < NCOL / 2; ++kb) {
+      bf16x8 a[2][TERMS], b[2][TERMS];
+#pragma unroll
+      for (int k = 0; k < TERMS; ++k)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          a[i][k] = *reinterpret_cast<const bf16x8*>(st + a_lds + ((2 * kb * TERMS + k) * BM + i * 32) * kGran);
+          b[i][k] = *reinterpret_cast<const bf16x8*>(st + b_lds + ((2 * kb * TERMS + k) * BN + i * 32) * kGran);
+        }
+#define CCT_M(X, Y, ACC)                                                                    \
+  _Pragma("unroll") for (int i = 0; i < 2; ++i) _Pragma("unroll") for (int j = 0; j < 2; ++j) \
+      ACC[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][X], b[j][Y], ACC[i][j], 0, 0, 0)
+      if constexpr (TERMS == 3) {
+        CCT_M(0, 0, acc);
+        CCT_M(0, 1, acc_c);
+        CCT_M(1, 0, acc_c);
+        CCT_M(1, 1, acc_c);
+        CCT_M(0, 2, acc_c);
+        CCT_M(2, 0, acc_c);
+      } else {
+        CCT_M(0, 0, acc);
+      }
+#undef CCT_M
+    }
+  }
+
+  float* __restrict__ C = p.part + ((long long)s * p.G + g) * p.M * p.N;
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int n = n0 + wave_n * 64 + j * 32 + lane_lo;
+    if (n >= p.N) continue;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int m = m0 + wave_m * 64 + i * 32 + (r >> 2) * 8 + lane_hi * 4 + (r & 3);
+        float v = acc[i][j][r];
+        if constexpr (TERMS == 3) v += acc_c[i][j][r];
+        if (m < p.M) C[(long long)m * p.N + n] = v;
+      }
+  }
+}
+
+// ---- 3. sum of the splits -----------------------------------------------------------------------
+
+struct ImgReduce {
+  const float* part;
+  float* dw;
+  const float* sums;  // bias partial sums [nsums][O], or null
+  float* dbias;
+  const float *x, *dy;  // the chunk's tensors, for results that are not a number
+  int M, N, G, S, K, KK, Cg, Og, C, O, H, W, Hout, Wout, s, pad, nimg;
+  int nsums, accumulate, blocks_dw, exact_nan, strips;
+};
+
+constexpr int kSumCh = 4, kStrips = 256 / kSumCh;
+
+// The last blocks sum the bias gradient.
+// exact_nan: results of split operands that an infinity made NaN are summed again in plain fp32
+// (split_bf16.h), the whole workgroup on one at a time.
+__global__ __launch_bounds__(256) void bwdw_img_reduce(ImgReduce p) {
+  __shared__ float red[256];
+  const int tid = threadIdx.x;
+  if ((int)blockIdx.x >= p.blocks_dw) {
+    // strips of partial sums per kernel, four loads of a strip in flight
+    const int o = ((int)blockIdx.x - p.blocks_dw) * kSumCh + tid % kSumCh;
+    float v = 0.f;
+    if (o < p.O) {
+      const float* src = p.sums + o;
+      int k = tid / kSumCh;
+      for (; k + 3 * kStrips < p.nsums; k += 4 * kStrips) {
+        float u[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) u[e] = src[(long long)(k + e * kStrips) * p.O];
+        v += (u[0] + u[1]) + (u[2] + u[3]);
+      }
+      for (; k < p.nsums; k += kStrips) v += src[(long long)k * p.O];
+    }
+    red[tid] = v;
+    __syncthreads();
+    if (tid < kSumCh && o < p.O) {
+      float sum = 0.f;
+#pragma unroll
+      for (int k = 0; k < kStrips; ++k) sum += red[k * kSumCh + tid];
+      p.dbias[o] = p.accumulate ? p.dbias[o] + sum : sum;
+    }
+    return;
+  }
+  // a workgroup takes 256 weights, or 64 with a quarter of the splits per wave
+  const int wid = p.strips == 4 ? tid & 63 : tid, strip = p.strips == 4 ? tid >> 6 : 0;
+  const long long per = (long long)p.M * p.N, total = per * p.G;
+  const long long t = (long long)blockIdx.x * (256 / p.strips) + wid;
+  float sum = 0.f;
+  int g = 0, m = 0, ci = 0, tap = 0;
+  long long wi = 0;
+  if (t < total) {
+    const float* src = p.part + t;
+    const int share = (p.S + p.strips - 1) / p.strips, end = min(p.S, (strip + 1) * share);
+    int k = strip * share;
+    for (; k + 8 <= end; k += 8) {
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = src[(k + u) * total];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) sum += v[u];
+    }
+    for (; k < end; ++k) sum += src[k * total];
+    g = (int)(t / per);
+    const int e = (int)(t - g * per);
+    m = e / p.N;
+    const int n = e - m * p.N;
+    const int cb = n / (p.KK * kChanBlock), width = min(kChanBlock, p.Cg - cb * kChanBlock);
+    const int rem = n - cb * p.KK * kChanBlock;
+    tap = rem / width;
+    ci = cb * kChanBlock + rem - tap * width;
+    wi = ((long long)(g * p.Og + m) * p.Cg + ci) * p.KK + tap;
+  }
+  if (p.strips == 4) {
+    red[tid] = sum;
+    __syncthreads();
+    sum = ((red[wid] + red[64 + wid]) + red[128 + wid]) + red[192 + wid];
+  }
+  if (p.exact_nan) {
+    __shared__ int redo[256];
+    __shared__ int any;
+    if (tid == 0) any = 0;
+    __syncthreads();
+    const bool bad = strip == 0 && t < total && sum != sum;
+    redo[tid] = bad;
+    if (bad) any = 1;
+    __syncthreads();
+    if (any) {
+      __shared__ int key[3];
+#pragma unroll 1
+      for (int who = 0; who < 256; ++who) {
+        if (!redo[who]) continue;  // the same for all threads
+        if (tid == who) {
+          key[0] = g * p.Og + m;
+          key[1] = g * p.Cg + ci;
+          key[2] = tap;
+        }
+        __syncthreads();
+        const int i = key[2] / p.K, jj = key[2] - i * p.K;
+        const long long P = (long long)p.Hout * p.Wout, cells = P * p.nimg;
+        float v = 0.f;
+        for (long long q = tid; q < cells; q += 256) {
+          const int n = (int)(q / P), pix = (int)(q - n * P);
+          const int r = pix / p.Wout, c = pix - r * p.Wout;
+          const int h = r * p.s + i - p.pad, w = c * p.s + jj - p.pad;
+          if (h < 0 || h >= p.H || w < 0 || w >= p.W) continue;
+          v = fmaf(p.dy[((long long)n * p.O + key[0]) * P + pix],
+                   p.x[(((long long)n * p.C + key[1]) * p.H + h) * p.W + w], v);
+          if (v != v) break;
+        }
+        red[tid] = v;
+        __syncthreads();
+#pragma unroll 1
+        for (int off = 128; off > 0; off >>= 1) {
+          if (tid < off) red[tid] += red[tid + off];
+          __syncthreads();
+        }
+        if (tid == who) sum = red[0];
+        __syncthreads();
+      }
+    }
+  }
+  if (strip == 0 && t < total) p.dw[wi] = p.accumulate ? p.dw[wi] + sum : sum;
+}
+
+// ---- host -----------------------------------------------------------------------------------------
+
+inline int out_size(int in, int K, int s, int pad) { return (in + 2 * pad - K) / s + 1; }
+
+inline int row_tile(int M) { return M % 128 == 0 || M % 128 > 64 ? 128 : 64; }
+
+template <int BM, int TERMS, int SLOTS>
+int launch_product(const ImgGemm& p, dim3 grid, hipStream_t st) {
+  constexpr int lds = 2 * SLOTS * (BM + BN) * kGran;
+  constexpr auto kern = conv_bwdw_img<BM, TERMS, SLOTS>;
+  if (const int rc = ensure_dynamic_lds<kern>(lds)) return rc;
+  hipLaunchKernelGGL(kern, grid, dim3(BM * 4), lds, st, p);
+  CCT_CHECK_LAUNCH();
+  return CCT_OK;
+}
+
+}  // namespace
+
+bool bwdw_img_plan(const cct_conv_desc_t& d, long long nimg, BwdwImgPlan* P) {
+  const int Hout = out_size(d.H, d.K, d.stride, d.pad), Wout = out_size(d.W, d.K, d.stride, d.pad);
+  const int Cg = d.C / d.groups, Og = d.O / d.groups;
+  const long long terms = d.precision == CCT_PREC_F32 ? 3 : 1;
+  const long long Hp = d.H + 2LL * d.pad, Wp = d.W + 2LL * d.pad;
+  const long long pix = (long long)Hout * Wout, N = (long long)Cg * d.K * d.K;
+  const long long groups_of_images = (nimg + kImg - 1) / kImg;
+  const long long cols = groups_of_images * pix;
+  if (d.groups > 65535 || N >= (1LL << 30) || Hp * Wp >= (1LL << 24) || cols >= (1LL << 30)) return false;
+  // a tap's offset from its column's cell, a term's from its granule: 32-bit byte offsets
+  if (((d.K - 1) * Wp + d.K) * terms * d.C * kGran >= (1LL << 31) || terms * d.O * kGran >= (1LL << 31) ||
+      terms * d.C * kGran >= (1LL << 31))
+    return false;
+  const long long tx = (Hp * Wp + kPrepPx - 1) / kPrepPx, ty = (pix + kPrepPx - 1) / kPrepPx;
+  const long long ctx = (d.C + kPrepCh - 1) / kPrepCh, cty = (d.O + kPrepCh - 1) / kPrepCh;
+  if (groups_of_images * (tx * ctx + ty * cty) >= (1LL << 30)) return false;
+  P->BM = row_tile(Og);
+  P->terms = (int)terms;
+  const long long ncol = terms == 1 ? 8 : P->BM == 128 ? 4 : 2;  // columns per stage
+  const long long tiles = ((Og + P->BM - 1) / P->BM) * ((N + BN - 1) / BN) * d.groups;
+  const long long slots = P->BM == 128 ? 256 : 512;              // workgroups the chip holds
+  const long long out_bytes = 4LL * d.O * N;
+  // Splits, from the whole batch: whole rounds of workgroups (a last round that is nearly empty costs as
+  // much as a full one), the number of rounds that is estimated fastest, partial products within 256 MiB,
+  // at least two stages each.  A smaller chunk takes at most as many, so that its plan is no larger.
+  const double sec_col = 2.0 * P->BM * BN * kImg / ((terms == 3 ? 230.0e12 : 600.0e12) / slots);
+  auto cut = [&](long long ncols, long long want, long long* S, long long* len) {
+    *len = ((ncols + want - 1) / want + ncol - 1) / ncol * ncol;
+    *S = (ncols + *len - 1) / *len;
+  };
+  auto at_most = [&](long long ncols) { return (ncols + 2 * ncol - 1) / (2 * ncol); };
+  const long long all = (d.N + kImg - 1) / kImg * pix;
+  long long want = 0, S, len;
+  double best = 0.0;
+  for (int rounds = 1; rounds <= 4; ++rounds) {
+    long long w = std::max(1LL, rounds * slots / tiles);
+    w = std::min(w, std::max(1LL, (256LL << 20) / out_bytes));
+    w = std::min(w, at_most(all));
+    cut(all, w, &S, &len);
+    const double sec = (double)((tiles * S + slots - 1) / slots) * ((double)len * sec_col + 9.0e-6) +
+                       (double)out_bytes * S * 2.0 / 8.0e12 + (double)S * 1.5e-8;
+    if (want == 0 || sec < best) {
+      best = sec;
+      want = w;
+    }
+  }
+  want = std::min(want, at_most(cols));
+  cut(cols, want, &S, &len);
+  if (all >= (1LL << 30) || tiles * S >= (1LL << 31)) return false;
+  P->S = (int)S;
+  P->split_cols = (int)len;
+  // a pixel with few channels is a short run of granules: 3 channels measured 1.2 TB/s
+  const double runs = std::max(1.0, 10.0 / d.C);
+  const double moved = (double)groups_of_images * kImg *
+                       ((double)d.C * (4.0 * d.H * d.W + 2.0 * terms * Hp * Wp) * runs + (double)d.O * pix * (4.0 + 2.0 * terms));
+  P->seconds = best + moved / 4.0e12 + 2.0e-6;
+  long long off = 0;
+  auto take = [&](long long bytes, long long* o) {
+    *o = off;
+    off += (bytes + 255) / 256 * 256;
+  };
+  take(groups_of_images * Hp * Wp * terms * d.C * kGran, &P->xs_off);
+  take(cols * terms * d.O * kGran, &P->ds_off);
+  take(want * out_bytes, &P->part_off);
+  take(groups_of_images * ty * d.O * 4, &P->sums_off);
+  P->total = off;
+  return true;
+}
+
+int launch_bwdw_img(const cct_conv_desc_t& d, const BwdwImgPlan& P, int nimg, const float* x, const float* dy,
+                    float* dw, float* dbias, int accumulate, char* ws, hipStream_t st) {
+  const int Hout = out_size(d.H, d.K, d.stride, d.pad), Wout = out_size(d.W, d.K, d.stride, d.pad);
+  const int Cg = d.C / d.groups, Og = d.O / d.groups, KK = d.K * d.K, pix = Hout * Wout;
+  const int Hp = d.H + 2 * d.pad, Wp = d.W + 2 * d.pad, igs = (nimg + kImg - 1) / kImg;
+  auto job = [&](const float* src, long long dst_off, int C, int H, int W, int pad) {
+    PrepJob j;
+    memset(&j, 0, sizeof(j));
+    j.src = src;
+    j.dst = reinterpret_cast<uint4*>(ws + dst_off);
+    j.C = C; j.H = H; j.W = W; j.pad = pad;
+    j.Wp = W + 2 * pad;
+    j.pixels = (H + 2 * pad) * j.Wp;
+    j.tiles_px = (j.pixels + kPrepPx - 1) / kPrepPx;
+    j.tiles_c = (C + kPrepCh - 1) / kPrepCh;
+    make_fastdiv_parts(j.Wp, &j.mWp, &j.sWp);
+    make_fastdiv_parts(j.tiles_px, &j.mTpx, &j.sTpx);
+    make_fastdiv_parts(j.tiles_c, &j.mTc, &j.sTc);
+    return j;
+  };
+  const PrepJob jx = job(x, P.xs_off, d.C, d.H, d.W, d.pad);
+  PrepJob jy = job(dy, P.ds_off, d.O, Hout, Wout, 0);
+  jy.sums = dbias ? reinterpret_cast<float*>(ws + P.sums_off) : nullptr;
+  const int bx = igs * jx.tiles_px * jx.tiles_c, by = igs * jy.tiles_px * jy.tiles_c;
+  const double xn = (double)nimg * d.C * d.H * d.W, yn = (double)nimg * d.O * pix;
+  {
+    ProfScope ps(P.terms == 3 ? "bwdw_img_prep<3>" : "bwdw_img_prep<1>", 0.0, (4.0 + 2.0 * P.terms) * (xn + yn), st);
+    if (P.terms == 3)
+      hipLaunchKernelGGL(bwdw_img_prep<3>, dim3((unsigned)(bx + by)), dim3(256), 0, st, jx, jy, bx, nimg);
+    else
+      hipLaunchKernelGGL(bwdw_img_prep<1>, dim3((unsigned)(bx + by)), dim3(256), 0, st, jx, jy, bx, nimg);
+    CCT_CHECK_LAUNCH();
+  }
+  ImgGemm q;
+  memset(&q, 0, sizeof(q));
+  q.xs = reinterpret_cast<const unsigned char*>(ws + P.xs_off);
+  q.ds = reinterpret_cast<const unsigned char*>(ws + P.ds_off);
+  q.part = reinterpret_cast<float*>(ws + P.part_off);
+  q.M = Og; q.N = Cg * KK; q.G = d.groups;
+  q.Cg = Cg; q.Og = Og; q.C = d.C; q.O = d.O; q.K = d.K; q.KK = KK; q.s = d.stride; q.Wp = Wp;
+  q.img_cells = (long long)Hp * Wp;
+  q.P = pix; q.Wout = Wout;
+  q.ncols = igs * pix;
+  q.split_cols = P.split_cols;
+  q.S = P.S;
+  q.tiles_m = (Og + P.BM - 1) / P.BM;
+  q.tiles_n = (q.N + BN - 1) / BN;
+  make_fastdiv_parts(pix, &q.mP, &q.sP);
+  make_fastdiv_parts(Wout, &q.mWout, &q.sWout);
+  const long long blocks = (long long)q.tiles_m * q.tiles_n * q.S;
+  if (blocks <= 0 || blocks >= 2147483647LL || d.groups > 65535) return CCT_EUNSUPPORTED;
+  {
+    char name[96];
+    snprintf(name, sizeof(name), "conv_bwdw_img<%d, %d>", P.BM, P.terms);
+    ProfScope ps(name, 2.0 * yn * Cg * KK, 2.0 * P.terms * (xn + yn) + 4.0 * q.S * (double)d.O * q.N, st);
+    const dim3 grid((unsigned)blocks, (unsigned)d.groups);
+    int rc;
+    if (P.BM == 128)
+      rc = P.terms == 3 ? launch_product<128, 3, 12>(q, grid, st) : launch_product<128, 1, 8>(q, grid, st);
+    else
+      rc = P.terms == 3 ? launch_product<64, 3, 6>(q, grid, st) : launch_product<64, 1, 8>(q, grid, st);
+    if (rc) return rc;
+  }
+  ImgReduce r;
+  memset(&r, 0, sizeof(r));
+  r.part = q.part; r.dw = dw; r.sums = jy.sums; r.dbias = dbias; r.x = x; r.dy = dy;
+  r.M = Og; r.N = q.N; r.G = d.groups; r.S = q.S; r.K = d.K; r.KK = KK; r.Cg = Cg; r.Og = Og;
+  r.C = d.C; r.O = d.O; r.H = d.H; r.W = d.W; r.Hout = Hout; r.Wout = Wout; r.s = d.stride; r.pad = d.pad;
+  r.nimg = nimg;
+  r.nsums = igs * jy.tiles_px;
+  r.accumulate = accumulate;
+  r.exact_nan = P.terms == 3;
+  const long long total = (long long)d.O * q.N;
+  // few weights: more loads in flight per weight
+  r.strips = total < 256 * 1024 && q.S >= 8 ? 4 : 1;
+  const long long rb = (total * r.strips + 255) / 256, db = dbias ? (d.O + kSumCh - 1) / kSumCh : 0;
+  if (rb + db >= 2147483647LL) return CCT_EUNSUPPORTED;
+  r.blocks_dw = (int)rb;
+  ProfScope ps("bwdw_img_reduce", 0.0, 4.0 * total * (q.S + 1), st);
+  hipLaunchKernelGGL(bwdw_img_reduce, dim3((unsigned)(rb + db)), dim3(256), 0, st, r);
+  CCT_CHECK_LAUNCH();
+  return CCT_OK;
+}
+
+}  // namespace cct

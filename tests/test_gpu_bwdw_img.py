@@ -1,0 +1,97 @@
+"""conv_bwdw_img (backward-weights on granules of 8 images) at the sizes where it can go wrong, against
+the oracle.  fp32 tolerance: three bf16 terms hold a product of two fp32 values to 2^-25; bf16: the
+operands' rounding."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1504_04343_amd import synth
+from gpu_util import TOL_BF16, TOL_F32, desc_of, dev, gpu_backward_weights, layer, odims, rel_err
+
+pytestmark = pytest.mark.gpu
+
+KERNEL = "conv_bwdw_img"
+
+#          name         N    C   H   W    O  K  s  p  g
+LAYERS = [
+    layer("m128",     64, 192, 13, 13, 128, 3, 1, 1),
+    layer("m64",      90, 384, 13, 13,  64, 3, 1, 1),           # 64-row tile; last granule holds 2 images
+    layer("m192",     33, 192, 13, 13, 192, 3, 1, 1),           # one image in the last granule
+    layer("m130",     40, 240, 14, 13, 260, 3, 1, 0, 2),        # rows beyond a tile; channels 3*32 + 24
+    layer("c48",      25,  96, 20, 17, 256, 5, 1, 2, 2),        # a short last channel block
+    layer("c70",      41, 170, 21, 17, 100, 2, 1, 1),           # even kernel; 100 of 128 rows
+    layer("s2",       48, 192, 25, 23, 128, 3, 2, 1),
+    layer("k1",       64, 512, 20, 14, 192, 1, 1, 0),           # a single tap
+]
+
+
+@pytest.fixture(scope="module")
+def B():
+    import torch
+    assert torch.cuda.is_available()
+    from paper_1504_04343_amd import binding
+    return binding
+
+
+def ran(B, call):
+    B.cct_profile_enable(True)
+    got = call()
+    B.cct_profile_enable(False)
+    return got, [e["name"] for e in B.cct_profile_read()]
+
+
+def check(got, L, x, dy, tol):
+    dw, db = oracle.conv_backward_weights(odims(oracle, L), x, dy)
+    assert rel_err(got[0], dw) <= tol
+    if got[1] is not None:
+        assert rel_err(got[1], db) <= TOL_F32
+
+
+@pytest.mark.parametrize("bf16", [False, True], ids=["f32", "bf16"])
+@pytest.mark.parametrize("L", LAYERS, ids=[L.name for L in LAYERS])
+def test_backward_weights(B, L, bf16):
+    x, dy = synth.make_x(L, 3), synth.make_dy(L, 3)
+    got, names = ran(B, lambda: gpu_backward_weights(B, L, x, dy, 0, int(bf16), want_dbias=L.N != 33))
+    assert any(n.startswith(KERNEL) for n in names), names
+    check(got, L, x, dy, TOL_BF16 if bf16 else TOL_F32)
+
+
+@pytest.mark.parametrize("chunk", [40, 56, 8])
+def test_chunks(B, chunk):
+    """A workspace for fewer images takes the batch in chunks that add up (the last one shorter); one for
+    too few runs the kernel that needs no copy of the tensors."""
+    L = layer("chunks", 100, 192, 13, 13, 128, 3, 1, 1)
+    x, dy = synth.make_x(L, 4), synth.make_dy(L, 4)
+    got, names = ran(B, lambda: gpu_backward_weights(B, L, x, dy, chunk=chunk))
+    assert any(n.startswith(KERNEL) for n in names) == (chunk >= 32), names
+    check(got, L, x, dy, TOL_F32)
+
+
+def test_precision(B):
+    """No further from 64 bits than the fp32 matrix instructions' sums (measured 8e-7 in the 2-norm)."""
+    L = layer("prec", 64, 192, 13, 13, 128, 3, 1, 1, x_dist="relu_normal")
+    x, dy = synth.make_x(L, 1), synth.make_dy(L, 1)
+    got = gpu_backward_weights(B, L, x, dy)[0].astype(np.float64)
+    want = oracle.conv_backward_weights(odims(oracle, L), x, dy)[0]
+    assert np.linalg.norm(got - want) / np.linalg.norm(want) <= 8e-7
+
+
+def test_not_finite_inputs(B):
+    """Infinities, NaN and values beyond bf16's range reach exactly the weights they reach in fp32."""
+    L = layer("nf", 48, 192, 13, 13, 128, 3, 1, 1)
+    x, dy = synth.make_x(L, 5), synth.make_dy(L, 5)
+    x[0, 0, 0, 0], x[1, 1, 5, 6], x[1, 2, 12, 12], x[-1, 3, 4, 4] = np.inf, -np.inf, np.nan, 3.4e38
+    dy[3, 7, 0, 0], dy[47, 9, 12, 12] = np.inf, 3.4e38
+    dy[:, 11] = 0.0
+    (got, _), names = ran(B, lambda: gpu_backward_weights(B, L, x, dy))
+    assert any(n.startswith(KERNEL) for n in names), names
+    want, _ = oracle.conv_backward_weights(odims(oracle, L), x, dy)
+    assert (np.isnan(got) == np.isnan(want)).all()
+    over = np.abs(want) > np.finfo(np.float32).max
+    assert (np.isinf(got) == (over & ~np.isnan(want))).all()
+    inf = np.isinf(got)
+    assert (np.sign(got[inf]) == np.sign(want[inf])).all()
+    ok = np.isfinite(got)
+    big = ok & (np.abs(want) > 1e30)
+    assert (np.abs(got[big] - want[big]) <= 1e-5 * np.abs(want[big])).all()
+    assert rel_err(got[ok & ~big], want[ok & ~big]) <= TOL_F32
