@@ -146,14 +146,14 @@ int cct_lowering_cost(const cct_conv_desc_t* desc, cct_pass_t pass, cct_lowering
  *
  * Fully connected layers (K == H == W, pad 0, groups 1, fp32, lowering AUTO or TYPE1: one output
  * pixel per image, the m = 1 case of Sec. 2.1 where every lowering is a reshape of x) run as plain
- * matrix products on x, w and dy in place, never chunked: the recommended workspace holds the
- * split partial products of the forward pass (a few times N*O floats), or a packed copy of dy
- * (about N*O floats) and, for the backward-data pass, its split partial products (a few times
- * N*C*K*K floats).  With a smaller workspace these two passes use fewer splits, and a workspace
- * too small for the unsplit product (forward: N*O floats; backward: the packed dy) sends the layer
- * through the general, chunked path.  The forward
- * pass of such a layer with C*K*K a multiple of 32 reads w with 16-byte loads: w must be 16-byte
- * aligned (CCT_EINVAL otherwise; force another lowering for a misaligned tensor).
+ * matrix products on x, w and dy in place, never chunked: the recommended workspace holds a packed
+ * copy of the small operand (x of a forward pass over more than 32 images, dy of the others, 6 bytes
+ * per value) and the split partial products of the forward pass (a few times N*O floats) or of the
+ * backward-data pass (a few times N*C*K*K floats).  With a smaller workspace these two passes use
+ * fewer splits, and a workspace too small for the unsplit product (forward: N*O floats; backward:
+ * the packed dy) sends the layer through the general, chunked path.  The forward pass of such a layer
+ * with C*K*K a multiple of 32 reads w with 16-byte loads: w must be 16-byte aligned (CCT_EINVAL
+ * otherwise; force another lowering for a misaligned tensor).
  */
 int cct_conv_workspace_bytes(const cct_conv_desc_t* desc, cct_pass_t pass, size_t* bytes);
 int cct_conv_workspace_bytes_for_chunk(const cct_conv_desc_t* desc, cct_pass_t pass,

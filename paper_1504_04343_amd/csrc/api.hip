@@ -250,6 +250,7 @@ struct Layout {
   int S = 1, split_len = 0;  // NT GEMM
   int split = 0;    // fused forward / backward-data on conv_fused_split, as sp says
   SplitPlan sp;
+  int gsplit = 0;   // forward / backward-data of a 1 x 1 layer in place on gemm_split
   int img = 0;      // backward-weights on granules of 8 images, as ip says
   BwdwImgPlan ip;
   int t2_opad = 0;  // Type-2 backward-data with the inverse lifting gathered by the GEMM: padded Og
@@ -276,6 +277,36 @@ bool bwdw_img_wins(const cct_conv_desc_t& d, int type) {
   return bwdw_img_plan(d, d.N, &p) && p.seconds < allowance * layout_cost(d, CCT_PASS_BACKWARD_WEIGHTS, type);
 }
 
+// 1 x 1 kernels at stride 1 without padding: every lowering is the identity, so the forward and
+// backward-data passes are products on the tensors in place.
+inline bool pointwise(const cct_conv_desc_t& d) { return d.K == 1 && d.stride == 1 && d.pad == 0; }
+
+GemmTN pointwise_problem(const cct_conv_desc_t& d, int pass, const Geom& g, const Layout& L, const void* pack,
+                         const float* in, float* out, const float* bias, long long ni) {
+  const long long HW = (long long)d.H * d.W;
+  const bool fwd = pass == CCT_PASS_FORWARD;
+  GemmTN p;
+  std::memset(&p, 0, sizeof(p));
+  p.M = fwd ? g.Og : g.Cg; p.Kdim = fwd ? g.Cg : g.Og; p.Ncols = (int)(ni * HW); p.G = d.groups;
+  p.A = pack; p.Mpad = L.Mpad; p.Kpad = L.Kpad;
+  p.a_gs = (long long)L.Mpad * L.Kpad;
+  p.B = in; p.b_ks = HW; p.b_gs = (long long)p.Kdim * HW;
+  p.bmap = ColMap{(int)HW, (long long)(fwd ? d.C : d.O) * HW};
+  p.C = out; p.c_ms = HW; p.c_gs = (long long)p.M * HW;
+  p.cmap = ColMap{(int)HW, (long long)(fwd ? d.O : d.C) * HW};
+  p.bias = bias; p.bias_gs = g.Og;
+  return p;
+}
+// Can gemm_split run them?  Sets the padding of its pack.
+bool pointwise_split(const cct_conv_desc_t& d, int pass, const Geom& g, long long nc, Layout* L) {
+  if (!pointwise(d) || d.precision != CCT_PREC_F32 || pass == CCT_PASS_BACKWARD_WEIGHTS) return false;
+  if (nc * d.H * d.W >= kIntMax - 256 || (long long)d.H * d.W >= kIntMax) return false;
+  const bool fwd = pass == CCT_PASS_FORWARD;
+  L->Mpad = gemm_split_mpad(fwd ? g.Og : g.Cg);
+  L->Kpad = gemm_split_kpad(fwd ? g.Cg : g.Og);
+  return gemm_split_fits(pointwise_problem(d, pass, g, *L, nullptr, nullptr, nullptr, nullptr, nc), false);
+}
+
 // allow_split = false: without conv_fused_split, whose pack takes half as much again as the fp32 one,
 // and without the granules of conv_bwdw_img.
 bool make_layout(const cct_conv_desc_t& d, int pass, int type, const Geom& g, long long nc,
@@ -294,8 +325,11 @@ bool make_layout(const cct_conv_desc_t& d, int pass, int type, const Geom& g, lo
   };
   const long long dt_rows = (long long)d.C * g.DKi * g.DKj;
   const long long rt_rows = (long long)d.O * g.RKi * g.RKj;
+  L->gsplit = allow_split && pointwise_split(d, pass, g, nc, L);
   L->split = type == CCT_LOWER_FUSED && allow_split && split_plan(d, pass, g, &L->sp);
-  if (L->split) {
+  if (L->gsplit) {
+    take((long long)d.groups * L->Mpad * L->Kpad * 6, &L->pack_off, &L->pack_bytes);
+  } else if (L->split) {
     // one column per output pixel (forward), input pixel or cell of the strided grid (backward-data)
     const StridedBwd sb = strided_bwd(d, g);
     const long long cols = pass == CCT_PASS_FORWARD ? g.Pc
@@ -837,6 +871,23 @@ int run_split(const cct_conv_desc_t& d, const Geom& g, int pass, const Layout& L
   return rc;
 }
 
+// Forward / backward-data of a 1 x 1 layer as products on the tensors in place.
+int run_pointwise(const cct_conv_desc_t& d, const Geom& g, int pass, const Layout& L, long long nc, const float* in,
+                  const float* w, const float* bias, float* out, char* ws, hipStream_t st) {
+  const bool fwd = pass == CCT_PASS_FORWARD;
+  const long long HW = (long long)d.H * d.W, in_img = (fwd ? d.C : d.O) * HW, out_img = (fwd ? d.O : d.C) * HW;
+  const int M = fwd ? g.Og : g.Cg, Kd = fwd ? g.Cg : g.Og;
+  void* pack = ws + L.pack_off;
+  int rc = launch_pack_rows_split(w, pack, d.groups, M, L.Mpad, L.Kpad, Kd, d.groups * Kd, fwd ? g.Cg : 1,
+                                  fwd ? 1 : g.Cg, (long long)g.Og * g.Cg, st);
+  for (long long n0 = 0; n0 < d.N && !rc; n0 += nc) {
+    const long long ni = std::min<long long>(nc, d.N - n0);
+    rc = launch_gemm_split(pointwise_problem(d, pass, g, L, pack, in + n0 * in_img, out + n0 * out_img, bias, ni),
+                           d.groups * Kd, false, st);
+  }
+  return rc;
+}
+
 // The forward pass.  static_scratch: the workspace is the library's scratch array, whose address
 // is looked up only after every argument and size check has passed.
 int forward_on_workspace(const cct_conv_desc_t* desc, const float* x, const float* w,
@@ -868,6 +919,8 @@ int forward_on_workspace(const cct_conv_desc_t* desc, const float* x, const floa
   const int es = esize(d);
   const long long P = (long long)g.Hout * g.Wout;
 
+  if (L.gsplit)
+    return run_pointwise(d, g, CCT_PASS_FORWARD, L, nc, x, w, bias, y, ws, st);
   if (L.split)
     return run_split(d, g, CCT_PASS_FORWARD, L, nc, x, w, bias, y, ws, st);
   // the fused pass: the operand description of one chunk (lowering, multiply and lifting in one
@@ -984,6 +1037,8 @@ int cct_conv_backward_data(const cct_conv_desc_t* desc, const float* w, const fl
   const long long P = (long long)g.Hout * g.Wout;
   const long long HW = (long long)d.H * d.W;
 
+  if (L.gsplit)
+    return run_pointwise(d, g, CCT_PASS_BACKWARD_DATA, L, nc, dy, w, nullptr, dx, ws, st);
   if (L.split)
     return run_split(d, g, CCT_PASS_BACKWARD_DATA, L, nc, dy, w, nullptr, dx, ws, st);
   if (type == CCT_LOWER_FUSED && d.stride > 1) {

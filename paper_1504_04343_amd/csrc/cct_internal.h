@@ -63,7 +63,8 @@ struct GemmTN {
   long long c_ms, c_gs;
   ColMap cmap;
   const float* bias;   // nullable; bias[g*bias_gs + m]
-  int bias_gs;
+  int bias_gs;         // < 0 (gemm_split): bias[col]
+  long long a_ms;      // != 0 (gemm_split): A is fp32, k-contiguous rows a_ms apart, groups a_gs apart
   int M, Ncols, Kdim;  // true sizes per group
   int G;
   int bf16;            // operands are bf16 (A packed bf16, B bf16 plain rows)
@@ -168,6 +169,19 @@ struct ConvBwdW {
 bool conv_bwdw_fused_fits(int C, int H, int W, int K, int s, int pad, int Hout, int Wout, int Cg,
                           int Og, int O);
 int launch_conv_bwdw_fused(const ConvBwdW& p, hipStream_t st);
+// The same arithmetic for products whose B is a tensor in place (gemm_split.hip): GemmTN with the pack of
+// launch_pack_rows_split, B column-contiguous through bmap or, with bt, k-contiguous rows b_ks apart.
+// With a_ms set A is read in place as well: bt and up to 32 rows.
+// G groups of Kdim indices, the last one shorter when Ktotal < G * Kdim.
+int gemm_split_mpad(int M);
+int gemm_split_kpad(int K);
+bool gemm_split_fits(const GemmTN& p, bool bt);
+int gemm_split_bm(int Mpad, long long tiles_n, int K, int G);
+int launch_gemm_split(const GemmTN& p, int Ktotal, bool bt, hipStream_t st);
+// pack of element (m, k) of group g = src[g*sg + m*sm + k*sk]
+int launch_pack_rows_split(const float* src, void* pack, int G, int M, int Mpad, int Kpad, int Kdim, int Ktotal,
+                           long long sm, long long sk, long long sg, hipStream_t st);
+
 // Backward-weights pass on granules of 8 images (conv_bwdw_img.hip), fp32 as three bf16 terms or bf16:
 // plan for nimg images at a time and the workspace it needs.  false = sizes it cannot address.
 struct BwdwImgPlan {
@@ -191,6 +205,7 @@ struct FcPlan {
   long long pack_off, part_off, scratch_off, total;  // workspace layout (bytes)
   int BM, Mpad, Kpad;   // packed dy of the two backward passes (Kpad: rows of one split)
   int S, split_len;     // splits of the contraction: forward over F, backward-data over O
+  int split;            // on gemm_split, the small operand packed as three bf16 terms
 };
 // max_bytes < 0: the recommended plan; otherwise a plan within max_bytes of workspace (the forward
 // pass then uses fewer splits).  false = the descriptor is not such a layer, the pass cannot take

@@ -11,7 +11,9 @@
 // N*O outputs (few tiles) and a long contraction, so it is split over F into partial products
 // that a second kernel sums in split order together with the bias (bit-reproducible, no atomics).
 // The backward-data product has N*F outputs, still too few tiles at CaffeNet's batch, and is split
-// over O the same way when O has a suitable divisor (the splits run as the groups of one launch).
+// over O the same way (the splits run as the groups of one launch).  The products run on gemm_split; the
+// fp32 kernels are for workspaces without room for its packed operand and for backward-weights passes
+// over up to 32 images.
 #include <algorithm>
 #include <cstring>
 
@@ -120,6 +122,101 @@ int launch_fc_sum_splits(const float* part, float* out, int S, long long total, 
 
 }  // namespace
 
+namespace {
+
+// The plan on gemm_split.  The row operand (x of the forward pass, dy of the others) is packed as three
+// bf16 terms, w and x are read in place.  The contraction is cut into the number of splits S that is
+// estimated fastest: rounds of workgroups (512 of 128 rows or 1024 of 64 fit the chip) times their
+// stages, against the partial products that are written and read once more.  Measured, fc6 at batch 256
+// (19.3 GFLOP per pass): forward 1 / 4 / 8 / 16 splits 310 / 130 / 117 / 123 us, backward-data 1 / 4 / 7 /
+// 16 splits 198 / 141 / 126 / 158; before, on the fp32 matrix instructions, 195 and 214.  false = sizes or a workspace that it
+// cannot take, or a backward-weights pass over up to 32 images, whose product is one short stage of
+// 32 images: the fp32 kernel wastes less there (fc6, one image: 36 us against 43).
+bool fc_plan_split(const cct_conv_desc_t& d, int pass, long long max_bytes, long long F, FcPlan* P) {
+  const long long NO = 4LL * d.N * d.O;
+  const long long cap = max_bytes < 0 ? kFcMaxPartBytes : std::min(kFcMaxPartBytes, max_bytes);
+  const bool fwd = pass == CCT_PASS_FORWARD, bwdw = pass == CCT_PASS_BACKWARD_WEIGHTS;
+  if (bwdw && d.N <= 32) return false;
+  const int M = bwdw ? d.O : d.N;                                  // rows
+  const long long Kd = fwd ? F : bwdw ? d.N : d.O, cols = fwd ? d.O : F;
+  const long long out = 4LL * M * cols;
+  GemmTN p;
+  std::memset(&p, 0, sizeof(p));
+  p.M = M; p.Mpad = gemm_split_mpad(M);
+  p.Ncols = (int)cols; p.b_ks = F;
+  p.bmap = ColMap{kIntMax, 0};
+  // a split of S, the number of them, and their workspace (backward-data: room for a number of equal
+  // splits where there is one)
+  auto len = [&](long long S) { return S == 1 ? Kd : align_up((Kd + S - 1) / S, 32); };
+  auto count = [&](long long S) { return (Kd + len(S) - 1) / len(S); };
+  auto room = [&](long long S) {
+    const long long n = count(S);
+    for (long long v = n; !fwd && v < 2 * n; ++v)
+      if (Kd % v == 0) return v;
+    return n;
+  };
+  auto pack = [&](long long S) {
+    if (fwd && d.N <= 32) return 0LL;  // few rows: read in place by every workgroup
+    const long long bytes = 6LL * count(S) * p.Mpad * gemm_split_kpad((int)len(S));
+    // forward: whole multiples of y, like the partial products behind it
+    return fwd ? (bytes + NO - 1) / NO * NO : align_up(bytes, kAlign);
+  };
+  auto need = [&](long long S) {
+    return align_up(pack(S) + (count(S) > 1 ? room(S) * out : 0), kAlign) +
+           (bwdw ? align_up(4LL * d.O * kDbiasBlocks, kAlign) : 0);
+  };
+  const long long tiles_n = (cols + 127) / 128;
+  auto seconds = [&](long long S) {
+    const long long n = count(S);
+    const int BM = gemm_split_bm(p.Mpad, tiles_n, (int)len(S), (int)n);
+    const long long wgs = tiles_n * (p.Mpad / BM) * n, slots = BM == 128 ? 512 : 1024;
+    const double stage = 2.0 * BM * 128 * 32 / ((BM == 128 ? 230.0e12 : BM == 64 ? 200.0e12 : 120.0e12) / slots);
+    return (double)((wgs + slots - 1) / slots) * ((len(S) + 31) / 32 * stage + 4.0e-6) +
+           (n > 1 ? 2.0 * n * out / 6.0e12 : 0.0);
+  };
+  long long S = 1;
+  if (!bwdw) {
+    double best = need(1) <= cap ? seconds(1) : 1e30;
+    for (long long sp = 2; sp <= 64 && Kd / sp >= kFcMinSplitRows; ++sp) {
+      if (need(sp) > cap) continue;
+      const double t = seconds(sp);
+      if (t < best) {
+        best = t;
+        S = sp;
+      }
+    }
+  }
+  if (max_bytes >= 0 && need(S) > max_bytes) return false;
+  p.Kdim = (int)len(S); p.Kpad = gemm_split_kpad(p.Kdim);
+  if (!gemm_split_fits(p, fwd)) return false;
+  P->split = 1;
+  P->split_len = p.Kdim;
+  P->S = (int)count(S);
+  P->Mpad = p.Mpad;
+  P->Kpad = p.Kpad;
+  P->pack_off = 0;
+  P->part_off = pack(S);
+  P->scratch_off = pack(S);  // backward-weights: no partial products
+  P->total = std::max<long long>(need(S), kAlign);
+  return true;
+}
+
+GemmTN fc_split_problem(const FcPlan& P, int M, int Ncols, const void* pack, const float* B, float* C) {
+  GemmTN p;
+  std::memset(&p, 0, sizeof(p));
+  p.A = pack;
+  p.a_gs = (long long)P.Mpad * P.Kpad;
+  p.Mpad = P.Mpad; p.Kpad = P.Kpad;
+  p.B = B; p.b_ks = P.F;
+  p.bmap = ColMap{kIntMax, 0};
+  p.C = C; p.c_ms = Ncols; p.c_gs = (long long)M * Ncols;
+  p.cmap = ColMap{kIntMax, 0};
+  p.M = M; p.Ncols = Ncols; p.Kdim = P.split_len; p.G = P.S;
+  return p;
+}
+
+}  // namespace
+
 bool fc_plan(const cct_conv_desc_t& d, int pass, long long max_bytes, FcPlan* P) {
   if (d.K != d.H || d.K != d.W || d.pad != 0 || d.groups != 1) return false;
   if (d.precision != CCT_PREC_F32) return false;
@@ -130,6 +227,7 @@ bool fc_plan(const cct_conv_desc_t& d, int pass, long long max_bytes, FcPlan* P)
     return false;
   std::memset(P, 0, sizeof(*P));
   P->F = (int)F;
+  if (fc_plan_split(d, pass, max_bytes, F, P)) return true;
   long long off = 0;
   auto take = [&](long long bytes, long long* o) {
     *o = off;
@@ -191,7 +289,26 @@ bool fc_plan(const cct_conv_desc_t& d, int pass, long long max_bytes, FcPlan* P)
 
 int fc_forward(const cct_conv_desc_t& d, const FcPlan& P, const float* x, const float* w,
                const float* bias, float* y, char* ws, hipStream_t st) {
-  if (reinterpret_cast<uintptr_t>(w) % 16) return CCT_EINVAL;
+  if (P.F % 32 == 0 && reinterpret_cast<uintptr_t>(w) % 16) return CCT_EINVAL;
+  if (P.split) {
+    void* pack = ws + P.pack_off;
+    float* part = reinterpret_cast<float*>(ws + P.part_off);
+    GemmTN p = fc_split_problem(P, d.N, d.O, pack, w, P.S > 1 ? part : y);
+    int rc;
+    if (d.N <= 32) {
+      p.A = x; p.a_ms = P.F; p.a_gs = P.split_len;
+    } else if ((rc = launch_pack_rows_split(x, pack, P.S, d.N, P.Mpad, P.Kpad, P.split_len, P.F, P.F, 1,
+                                            P.split_len, st)) != 0) {
+      return rc;
+    }
+    p.b_gs = P.split_len;
+    if (P.S == 1) {
+      p.bias = bias; p.bias_gs = -1;
+    }
+    rc = launch_gemm_split(p, P.F, true, st);
+    if (rc || P.S == 1) return rc;
+    return launch_fc_sum_splits(part, y, P.S, (long long)d.N * d.O, d.O, bias, st);
+  }
   GemmNT q;
   std::memset(&q, 0, sizeof(q));
   q.A = x; q.a_ms = P.F;
@@ -207,6 +324,17 @@ int fc_forward(const cct_conv_desc_t& d, const FcPlan& P, const float* x, const 
 
 int fc_backward_data(const cct_conv_desc_t& d, const FcPlan& P, const float* w, const float* dy,
                      float* dx, char* ws, hipStream_t st) {
+  if (P.split) {
+    void* pk = ws + P.pack_off;
+    float* part = reinterpret_cast<float*>(ws + P.part_off);
+    int rc = launch_pack_rows_split(dy, pk, P.S, d.N, P.Mpad, P.Kpad, P.split_len, d.O, d.O, 1, P.split_len, st);
+    if (rc) return rc;
+    GemmTN p = fc_split_problem(P, d.N, P.F, pk, w, P.S > 1 ? part : dx);
+    p.b_gs = (long long)P.split_len * P.F;
+    rc = launch_gemm_split(p, d.O, false, st);
+    if (rc || P.S == 1) return rc;
+    return launch_fc_sum_splits(part, dx, P.S, (long long)d.N * P.F, 1, nullptr, st);
+  }
   float* pack = reinterpret_cast<float*>(ws + P.pack_off);
   // pack[s][oo][n] = dy[n][s*split_len + oo]
   int rc = launch_fc_pack(dy, pack, d.O, d.N, P.S * P.Kpad, P.Mpad, 1, P.split_len, P.Kpad, st);
@@ -232,9 +360,10 @@ int fc_backward_data(const cct_conv_desc_t& d, const FcPlan& P, const float* w, 
   return launch_fc_sum_splits(part, dx, P.S, (long long)d.N * P.F, 1, nullptr, st);
 }
 
-int fc_backward_weights(const cct_conv_desc_t& d, const FcPlan& P, const float* x, const float* dy,
-                        float* dw, float* dbias, char* ws, hipStream_t st) {
-  float* pack = reinterpret_cast<float*>(ws + P.pack_off);
+namespace {
+// The product on the fp32 matrix instructions, for workspaces that hold dy once.
+int fc_weights_f32(const cct_conv_desc_t& d, const FcPlan& P, const float* x, const float* dy, float* dw,
+                   float* pack, hipStream_t st) {
   int rc = launch_fc_pack(dy, pack, d.N, d.O, P.Kpad, P.Mpad, 0, d.N, P.Kpad, st);  // pack[n][o] = dy[n][o]
   if (rc) return rc;
   GemmTN p;
@@ -248,7 +377,22 @@ int fc_backward_weights(const cct_conv_desc_t& d, const FcPlan& P, const float* 
   p.cmap = ColMap{kIntMax, 0};
   p.M = d.O; p.Ncols = P.F; p.Kdim = d.N; p.G = 1;
   p.force_bm = P.BM;
-  rc = launch_gemm_tn(p, st);
+  return launch_gemm_tn(p, st);
+}
+
+}  // namespace
+
+int fc_backward_weights(const cct_conv_desc_t& d, const FcPlan& P, const float* x, const float* dy,
+                        float* dw, float* dbias, char* ws, hipStream_t st) {
+  float* pack = reinterpret_cast<float*>(ws + P.pack_off);
+  int rc;
+  if (P.split) {
+    rc = launch_pack_rows_split(dy, pack, 1, d.O, P.Mpad, P.Kpad, d.N, d.N, 1, d.O, 0, st);
+    if (rc) return rc;
+    rc = launch_gemm_split(fc_split_problem(P, d.O, P.F, pack, x, dw), d.N, false, st);
+  } else {
+    rc = fc_weights_f32(d, P, x, dy, dw, pack, st);
+  }
   if (rc) return rc;
   if (dbias) {
     const int nblk = std::max(1, std::min({d.N, kDbiasBlocks, (2048 + d.O - 1) / d.O}));

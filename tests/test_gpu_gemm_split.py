@@ -1,0 +1,123 @@
+"""gemm_split (products with an operand in place, fp32 as three bf16 terms): fully connected layers and
+1 x 1 kernels at the sizes where it can go wrong, against the oracle.  Three bf16 terms hold a product of
+two fp32 values to 2^-25: the fp32 path's tolerance."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1504_04343_amd import synth
+from gpu_util import TOL_F32, desc_of, dev, gpu_backward_data, gpu_backward_weights, gpu_forward, layer, odims, rel_err
+
+pytestmark = pytest.mark.gpu
+
+KERNEL = "gemm_split"
+
+#          name      N   C   H  W    O  K
+FC = [
+    layer("one",      1,  64, 4, 4, 130, 4),             # one image, rows in place, columns past a tile
+    layer("n32",     32,  37, 3, 3,  65, 3),             # 333 features: the last stage ends inside a row
+    layer("n33",     33,  37, 3, 3,  65, 3),             # the same with packed rows
+    layer("n65",     65,   7, 1, 1, 129, 1),             # fewer features than a stage
+    layer("n130",   130, 113, 5, 5, 257, 5),             # 2825 features, 128-row tiles and a split tail
+    layer("n200",   200, 300, 1, 1, 1000, 1),
+    layer("prime",    4,  49, 1, 1, 1951, 1),            # splits of unequal length
+]
+POINTWISE = [
+    layer("p_small",  2,   5, 7,  9,  18, 1),
+    layer("p_odd",    9,  67, 13, 11,  70, 1),           # channels and rows past a tile, tiles across images
+    layer("p_groups", 5, 100, 14, 14, 130, 1, 1, 0, 2),
+    layer("p_m128",  40, 160, 28, 28, 256, 1),           # 128 rows, 160 = 5 tiles: the last stage is half
+    layer("p_one",    1, 300, 9,  9,  33, 1),
+]
+
+
+@pytest.fixture(scope="module")
+def B():
+    import torch
+    assert torch.cuda.is_available()
+    from paper_1504_04343_amd import binding
+    return binding
+
+
+def ran(B, call):
+    B.cct_profile_enable(True)
+    got = call()
+    B.cct_profile_enable(False)
+    return got, [e["name"] for e in B.cct_profile_read()]
+
+
+def split(names):
+    return any(n.startswith(KERNEL) for n in names)
+
+
+@pytest.mark.parametrize("L", FC + POINTWISE, ids=[L.name for L in FC + POINTWISE])
+def test_forward(B, L):
+    x, w, b = synth.make_x(L, 3), synth.make_w(L, 3), synth.make_bias(L, 3)
+    for bias in (b, None):
+        got, names = ran(B, lambda: gpu_forward(B, L, x, w, bias))
+        assert split(names), names
+        assert rel_err(got, oracle.conv_forward(odims(oracle, L), x, w, bias)) <= TOL_F32
+
+
+@pytest.mark.parametrize("L", FC + POINTWISE, ids=[L.name for L in FC + POINTWISE])
+def test_backward_data(B, L):
+    w, dy = synth.make_w(L, 3), synth.make_dy(L, 3)
+    got, names = ran(B, lambda: gpu_backward_data(B, L, w, dy))
+    assert split(names), names
+    assert rel_err(got, oracle.conv_backward_data(odims(oracle, L), w, dy)) <= TOL_F32
+
+
+@pytest.mark.parametrize("L", FC, ids=[L.name for L in FC])
+def test_backward_weights(B, L):
+    x, dy = synth.make_x(L, 3), synth.make_dy(L, 3)
+    (dw, db), names = ran(B, lambda: gpu_backward_weights(B, L, x, dy))
+    assert split(names) == (L.N > 32), names
+    want = oracle.conv_backward_weights(odims(oracle, L), x, dy)
+    assert rel_err(dw, want[0]) <= TOL_F32 and rel_err(db, want[1]) <= TOL_F32
+
+
+def test_kernels_that_are_only_float_aligned(B):
+    """A feature count that is no multiple of 32 never needed 16-byte aligned kernels."""
+    import torch
+    L = FC[2]
+    x, w = synth.make_x(L, 3), synth.make_w(L, 3)
+    wbuf = torch.empty(w.size + 1, device="cuda")
+    wbuf[1:] = dev(w).view(-1)
+    y = torch.empty((L.N, L.O, 1, 1), device="cuda")
+    d = desc_of(B, L)
+    B.cct_conv_forward(d, dev(x), wbuf[1:].view(w.shape), None, y, B.alloc_workspace(d, B.PASS_FORWARD))
+    assert rel_err(y.cpu().numpy(), oracle.conv_forward(odims(oracle, L), x, w, None)) <= TOL_F32
+
+
+def test_pointwise_in_chunks_and_in_the_fp32_workspace(B):
+    """A 1 x 1 layer keeps running in a workspace that holds the fp32 kernel matrix only."""
+    import torch
+    L = POINTWISE[1]
+    x, w, b = synth.make_x(L, 3), synth.make_w(L, 3), synth.make_bias(L, 3)
+    d = desc_of(B, L)
+    want = oracle.conv_forward(odims(oracle, L), x, w, b)
+    got = gpu_forward(B, L, x, w, b, chunk=2)
+    assert rel_err(got, want) <= TOL_F32
+    for lowering in (1, 2, 3):
+        got, names = ran(B, lambda: gpu_forward(B, L, x, w, b, lowering))
+        assert split(names), names
+        assert rel_err(got, want) <= TOL_F32
+
+
+@pytest.mark.parametrize("L", [FC[1], FC[4], POINTWISE[1]], ids=["direct", "packed", "pointwise"])
+def test_not_finite_inputs(B, L):
+    """Infinities, NaN and values beyond bf16's range reach exactly the outputs they reach in fp32."""
+    x, w, b = synth.make_x(L, 5), synth.make_w(L, 5), synth.make_bias(L, 5)
+    x[0, 0, 0, 0], x[1, 1, 0, 0], x[2, 2, 0, 0], x[-1, 1, 0, 0] = np.inf, -np.inf, np.nan, 3.4e38
+    w[3, 1, 0, 0], w[7, 0, 0, 0], w[9, 0, 0, 0] = np.inf, np.nan, 3.4e38
+    w[11] = 0.0
+    got, names = ran(B, lambda: gpu_forward(B, L, x, w, b))
+    assert split(names), names
+    want = oracle.conv_forward(odims(oracle, L), x, w, b)
+    assert (np.isnan(got) == np.isnan(want)).all()
+    over = np.abs(want) > np.finfo(np.float32).max
+    assert (np.isinf(got) == (over & ~np.isnan(want))).all()
+    ok = np.isfinite(got)
+    big = ok & (np.abs(want) > 1e30)
+    assert (np.abs(got[big] - want[big]) <= 1e-5 * np.abs(want[big])).all()
+    assert rel_err(got[ok & ~big], want[ok & ~big]) <= TOL_F32
