@@ -7,10 +7,9 @@
 //   ReLU      y = max(x, 0);  dx = dy where x > 0, else 0.
 //   LRN       across channels: scale = k + (alpha/size) * sum of x^2 over the `size` channels
 //             centred on the channel (zero padded), y = x * scale^(-beta); backward is the exact
-//             derivative.  A thread owns one pixel of one image and walks a segment of its
-//             channels (all of them when the batch has enough pixels to fill the chip), keeping
-//             the window in registers: x (and dy) are read once, apart from the few channels
-//             around a segment's ends, and y (dx) is written once.
+//             derivative.  A thread owns a segment of the channels of one pixel in registers:
+//             x (and dy) are read once, apart from the few channels around a segment's ends,
+//             and y (dx) is written once.
 //   dropout   y = x * scale where the caller's mask is set, else 0 (both directions).
 //   softmax loss  softmax over the classes of each image, mean negative log-likelihood of the
 //             labels; backward (prob - onehot) / N.  One workgroup per image, fixed-order sums.
@@ -120,6 +119,167 @@ __global__ __launch_bounds__(TPB) void maxpool_backward_kernel(const float* __re
   dx[t] = acc;
 }
 
+// A workgroup takes kWalk consecutive elements of the flat (plane, row, column) range of a kernel, kPer per
+// thread: the plane of its first one by a 64-bit division of uniform values, everything per thread in 32
+// bits with multiplicative division.  A tensor is then a uniform pointer and a 32-bit offset.  `load` runs
+// for all elements of a thread before `use` does, so that their loads are in flight together: the bytes
+// in flight on a CU are what bounds these kernels.  load(u, plane0, dp, r, c), use(u, ...) with the
+// plane relative to the workgroup's first one.
+constexpr int kPer = 4, kWalk = kPer * TPB;
+template <class Load, class Use>
+__device__ __forceinline__ void walk_planes(long long total, int per_plane, const FastDiv& divP, const FastDiv& divC,
+                                            Load load, Use use) {
+  const long long t0 = (long long)blockIdx.x * kWalk, plane0 = t0 / per_plane;
+  const int rem0 = (int)(t0 - plane0 * per_plane), left = (int)min((long long)kWalk, total - t0);
+  int dp[kPer], r[kPer], c[kPer];
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    const int rem = rem0 + min(u * TPB + (int)threadIdx.x, left - 1);  // past the end: the last one, unused
+    dp[u] = fdiv(rem, divP);
+    const int o = rem - dp[u] * per_plane;
+    r[u] = fdiv(o, divC);
+    c[u] = o - r[u] * divC.d;
+    load(u, plane0, dp[u], r[u], c[u]);
+  }
+#pragma unroll
+  for (int u = 0; u < kPer; ++u)
+    if (u * TPB + (int)threadIdx.x < left) use(u, plane0, dp[u], r[u], c[u]);
+}
+// the planes of one workgroup within 32-bit offsets
+inline bool walk_fits(long long per_plane, long long in_plane, long long out_plane) {
+  return per_plane < (1LL << 30) && (kWalk / per_plane + 2) * std::max(in_plane, out_plane) < (1LL << 29);
+}
+
+// Windows of K x K pixels, K >= stride.  CLIP: some windows reach past the image; none is empty, and rows
+// and columns past a clipped window's end repeat its last one (a repeated value is never greater).  Pool1
+// at batch 256 (297 MB in, 143 MB out): 183 us with one dependent load at a time and 64-bit divisions per
+// thread, 144 with all loads of four windows in flight but nine of 4 bytes each, 114 with pairs.
+// PAIRS (K = 3, stride 2, no clipping): a lane loads the first two columns of its window, 8 bytes next to
+// its neighbour's, and takes the third from the neighbour; lanes at the end of a row or wave load it.
+typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));  // 8 bytes, dword aligned
+template <int K, bool CLIP, bool PAIRS = false>
+__global__ __launch_bounds__(TPB) void maxpool_forward_window(const float* __restrict__ x, float* __restrict__ y,
+                                                              int* __restrict__ argmax, long long total, PoolGeom g,
+                                                              FastDiv divP, FastDiv divC) {
+  const int Po = g.Ho * g.Wo, P = g.H * g.W;
+  float v[kPer][K * K];
+  auto corner = [&](int r, int q, int* h0, int* w0, int* h1, int* w1) {
+    *h0 = CLIP ? max(r * g.s - g.p, 0) : r * g.s;
+    *w0 = CLIP ? max(q * g.s - g.p, 0) : q * g.s;
+    *h1 = min(r * g.s - g.p + K, g.H) - 1;
+    *w1 = min(q * g.s - g.p + K, g.W) - 1;
+  };
+  // offset of a pixel from the window's first one
+  auto off = [&](int e, int h0, int w0, int h1, int w1) {
+    const int i = e / K, j = e % K;
+    return CLIP ? (min(h0 + i, h1) - h0) * g.W + min(w0 + j, w1) - w0 : i * g.W + j;
+  };
+  walk_planes(
+      total, Po, divP, divC,
+      [&](int u, long long plane0, int dp, int r, int q) {
+        int h0, w0, h1, w1;
+        corner(r, q, &h0, &w0, &h1, &w1);
+        const float* __restrict__ xp = x + plane0 * P;
+        const unsigned base = (unsigned)(dp * P + h0 * g.W + w0);
+        if constexpr (PAIRS) {
+          const bool edge = (threadIdx.x & 63) == 63 || q == g.Wo - 1;
+#pragma unroll
+          for (int i = 0; i < 3; ++i) {
+            const f32x2u two = *reinterpret_cast<const f32x2u*>(xp + base + (unsigned)(i * g.W));
+            v[u][3 * i] = two[0];
+            v[u][3 * i + 1] = two[1];
+            v[u][3 * i + 2] = __shfl_down(two[0], 1, 64);
+            if (edge) v[u][3 * i + 2] = xp[base + (unsigned)(i * g.W + 2)];
+          }
+          return;
+        }
+#pragma unroll
+        for (int e = 0; e < K * K; ++e) v[u][e] = xp[base + (unsigned)off(e, h0, w0, h1, w1)];
+      },
+      [&](int u, long long plane0, int dp, int r, int q) {
+        int h0, w0, h1, w1;
+        corner(r, q, &h0, &w0, &h1, &w1);
+        float bv = v[u][0];
+        int best = 0;
+#pragma unroll
+        for (int e = 1; e < K * K; ++e) {
+          const bool more = v[u][e] > bv;
+          bv = more ? v[u][e] : bv;
+          best = more ? off(e, h0, w0, h1, w1) : best;
+        }
+        const unsigned t = (unsigned)(dp * Po + r * g.Wo + q);
+        (y + plane0 * Po)[t] = bv;
+        if (argmax) (argmax + plane0 * Po)[t] = h0 * g.W + w0 + best;
+      });
+}
+
+// Stride 2, windows of 2 or 3 pixels: a thread owns the 2 x 2 pixels (2a - p + 0..1, 2b - p + 0..1), which
+// only the windows a - 1 (K = 3) and a, b - 1 and b contain: at most four, read once for four pixels.
+// The windows of a pixel are added in row-major order, as the general kernels do.  Pool1 at batch 256
+// (143 MB in, 297 MB out): 155 us with the planes staged in LDS and a loop per pixel, 109 now.
+template <int K>
+__global__ __launch_bounds__(TPB) void maxpool_backward_cells(const float* __restrict__ dy,
+                                                              const int* __restrict__ argmax, float* __restrict__ dx,
+                                                              long long total, int cells, PoolGeom g, FastDiv divP,
+                                                              FastDiv divC) {
+  constexpr int NW = K - 1;  // windows per axis
+  const int Po = g.Ho * g.Wo, P = g.H * g.W;
+  float v[kPer][NW][NW];
+  int m[kPer][NW][NW];
+  walk_planes(
+      total, cells, divP, divC,
+      [&](int u, long long plane0, int dp, int a, int b) {
+        const float* __restrict__ dyp = dy + plane0 * Po;
+        const int* __restrict__ ap = argmax + plane0 * Po;
+#pragma unroll
+        for (int i = 0; i < NW; ++i)
+#pragma unroll
+          for (int j = 0; j < NW; ++j) {
+            // a window outside the grid: load the nearest one, it is ignored below
+            const int rc = min(max(a - NW + 1 + i, 0), g.Ho - 1), qc = min(max(b - NW + 1 + j, 0), g.Wo - 1);
+            const unsigned o = (unsigned)(dp * Po + rc * g.Wo + qc);
+            m[u][i][j] = ap[o];
+            v[u][i][j] = dyp[o];
+          }
+      },
+      [&](int u, long long plane0, int dp, int a, int b) {
+        float* __restrict__ out = dx + plane0 * P;
+        const int h0 = 2 * a - g.p, w0 = 2 * b - g.p;
+        bool rok[NW], qok[NW];
+#pragma unroll
+        for (int i = 0; i < NW; ++i) {
+          rok[i] = a - NW + 1 + i >= 0 && a - NW + 1 + i < g.Ho;
+          qok[i] = b - NW + 1 + i >= 0 && b - NW + 1 + i < g.Wo;
+        }
+#pragma unroll
+        for (int eh = 0; eh < 2; ++eh) {
+          const int h = h0 + eh;
+          float acc[2];
+#pragma unroll
+          for (int ew = 0; ew < 2; ++ew) {
+            const int me = h * g.W + w0 + ew;
+            float sum = 0.f;
+#pragma unroll
+            for (int i = eh ? NW - 1 : 0; i < NW; ++i)
+#pragma unroll
+              for (int j = ew ? NW - 1 : 0; j < NW; ++j)
+                sum += rok[i] && qok[j] && m[u][i][j] == me ? v[u][i][j] : 0.f;
+            acc[ew] = sum;
+          }
+          if (h < 0 || h >= g.H) continue;
+          const unsigned o = (unsigned)(dp * P + h * g.W + w0);
+          if (w0 >= 0 && w0 + 1 < g.W) {
+            const f32x2u two = {acc[0], acc[1]};
+            *reinterpret_cast<f32x2u*>(out + o) = two;
+          } else if (w0 >= 0) {
+            if (w0 < g.W) out[o] = acc[0];
+          } else if (w0 + 1 >= 0 && w0 + 1 < g.W) {
+            out[o + 1] = acc[1];
+          }
+        }
+      });
+}
+
 // The same gather with the output planes staged in LDS: a workgroup owns `np` consecutive
 // (image, channel) planes, copies their dy and argmax (np*Ho*Wo values each, contiguous in memory)
 // into LDS with coalesced loads and then walks the np*H*W input pixels, which gather from LDS in
@@ -192,15 +352,29 @@ inline unsigned stream_blocks(long long work_items) {
 // ---- local response normalisation -------------------------------------------------------------
 struct LrnGeom {
   int C;
-  int cs;  // channels per thread: blockIdx.y selects the segment [y*cs, min(C, (y+1)*cs))
   long long hw, pixels;  // H*W, N*H*W
   float a, beta, k, coef;  // alpha/size; 2*alpha*beta/size
 };
 
-constexpr long long kLrnThreads = 1 << 20;
-constexpr int kLrnMinSeg = 8;
+constexpr long long kLrnThreads = 1 << 18;
 
-template <int SIZE>
+// s^-beta.  P34: beta = 3/4 (Caffe's default), where Newton's step for z^4 s^3 = 1 makes a result good to
+// half a unit in the last place out of the hardware's approximate exponential and logarithm: with the
+// rounding errors of z*z, z*z*s and its square carried along, e = z^4 s^3 - 1 is known to 2^-40, and
+// z - z*e/4 rounds once.  About 15 instructions against powf's hundred, which were the kernels' bound.
+// Outside [2^-30, 2^30] the intermediate powers could leave the range of fp32: powf.
+template <bool P34>
+__device__ __forceinline__ float neg_power(float s, float beta) {
+  if (!P34 || !(s >= 0x1p-30f && s <= 0x1p30f)) return powf(s, -beta);
+  const float z = __builtin_amdgcn_exp2f(-0.75f * __builtin_amdgcn_logf(s));
+  const float a = z * z, al = fmaf(z, z, -a);
+  const float b = a * s, bl = fmaf(al, s, fmaf(a, s, -b));
+  const float c = b * b, cl = fmaf(2.f * b, bl, fmaf(b, b, -c));
+  const float e = fmaf(cl, s, fmaf(c, s, -1.f));
+  return fmaf(-0.25f * e, z, z);
+}
+
+template <int SIZE, bool P34, int CS>
 __global__ __launch_bounds__(TPB) void lrn_forward_kernel(const float* __restrict__ x,
                                                           float* __restrict__ y, LrnGeom g) {
   constexpr int HALF = (SIZE - 1) / 2;
@@ -209,29 +383,25 @@ __global__ __launch_bounds__(TPB) void lrn_forward_kernel(const float* __restric
   const long long n = t / g.hw, pix = t - n * g.hw;
   const float* xp = x + n * g.C * g.hw + pix;  // channel c of this pixel is xp[c*hw]
   float* yp = y + n * g.C * g.hw + pix;
-  const int c0 = blockIdx.y * g.cs, c1 = min(g.C, c0 + g.cs);
-  float xs[SIZE];  // x of channels c-HALF .. c+HALF
+  const int c0 = blockIdx.y * CS;
+  float xs[CS + 2 * HALF];  // x of channels c0-HALF ..
 #pragma unroll
-  for (int i = 0; i < SIZE; ++i) {
+  for (int i = 0; i < CS + 2 * HALF; ++i) {
     const int ch = c0 + i - HALF;
     xs[i] = (ch >= 0 && ch < g.C) ? xp[ch * g.hw] : 0.f;
   }
-  for (int c = c0; c < c1; ++c) {
+#pragma unroll
+  for (int i = 0; i < CS; ++i) {
+    if (c0 + i >= g.C) break;
     float sum = 0.f;
 #pragma unroll
-    for (int i = 0; i < SIZE; ++i) sum += xs[i] * xs[i];
-    yp[c * g.hw] = xs[HALF] * powf(g.k + g.a * sum, -g.beta);
-#pragma unroll
-    for (int i = 0; i + 1 < SIZE; ++i) xs[i] = xs[i + 1];
-    const int nx = c + HALF + 1;
-    xs[SIZE - 1] = nx < g.C ? xp[nx * g.hw] : 0.f;
+    for (int k = 0; k < SIZE; ++k) sum += xs[i + k] * xs[i + k];
+    yp[(c0 + i) * g.hw] = xs[i + HALF] * neg_power<P34>(g.k + g.a * sum, g.beta);
   }
 }
 
 // dx[c] = dy[c]*scale[c]^-beta - coef * x[c] * sum_{|c'-c| <= HALF} dy[c'] x[c'] scale[c']^(-beta-1).
-// Iteration j computes the terms of channel j and emits channel j - HALF, whose window is then
-// complete; a thread that owns channels c0 .. c1-1 therefore runs j over c0-HALF .. c1-1+HALF.
-template <int SIZE>
+template <int SIZE, bool P34, int CS>
 __global__ __launch_bounds__(TPB) void lrn_backward_kernel(const float* __restrict__ x,
                                                            const float* __restrict__ dy,
                                                            float* __restrict__ dx, LrnGeom g) {
@@ -242,48 +412,41 @@ __global__ __launch_bounds__(TPB) void lrn_backward_kernel(const float* __restri
   const float* xp = x + n * g.C * g.hw + pix;
   const float* gp = dy + n * g.C * g.hw + pix;
   float* op = dx + n * g.C * g.hw + pix;
-  const int c0 = blockIdx.y * g.cs, c1 = min(g.C, c0 + g.cs);
-  float xs[SIZE];      // x of channels j-HALF .. j+HALF
-  float tr[SIZE];      // cross terms of channels j-SIZE+1 .. j
-  float ur[HALF + 1];  // direct terms dy*scale^-beta of channels j-HALF .. j
+  const int c0 = blockIdx.y * CS;
+  float xs[CS + 4 * HALF];  // x of channels c0-2*HALF ..
+  float gs[CS + 2 * HALF];  // dy of channels c0-HALF .., then the direct terms dy*scale^-beta
+  float tr[CS + 2 * HALF];  // cross terms of the same channels
 #pragma unroll
-  for (int i = 0; i < SIZE; ++i) {
-    const int ch = c0 - HALF + i - HALF;
+  for (int i = 0; i < CS + 4 * HALF; ++i) {
+    const int ch = c0 + i - 2 * HALF;
     xs[i] = (ch >= 0 && ch < g.C) ? xp[ch * g.hw] : 0.f;
-    tr[i] = 0.f;
   }
 #pragma unroll
-  for (int i = 0; i <= HALF; ++i) ur[i] = 0.f;
-  for (int j = c0 - HALF; j < c1 + HALF; ++j) {
-    // shift the term windows and append channel j
+  for (int i = 0; i < CS + 2 * HALF; ++i) {
+    const int ch = c0 + i - HALF;
+    gs[i] = (ch >= 0 && ch < g.C) ? gp[ch * g.hw] : 0.f;
+  }
 #pragma unroll
-    for (int i = 0; i + 1 < SIZE; ++i) tr[i] = tr[i + 1];
-#pragma unroll
-    for (int i = 0; i < HALF; ++i) ur[i] = ur[i + 1];
-    float tj = 0.f, uj = 0.f;
-    if (j >= 0 && j < g.C) {
+  for (int i = 0; i < CS + 2 * HALF; ++i) {
+    const int ch = c0 + i - HALF;
+    tr[i] = 0.f;
+    if (ch >= 0 && ch < g.C) {
       float sum = 0.f;
 #pragma unroll
-      for (int i = 0; i < SIZE; ++i) sum += xs[i] * xs[i];
+      for (int k = 0; k < SIZE; ++k) sum += xs[i + k] * xs[i + k];
       const float scale = g.k + g.a * sum;
-      const float pw = powf(scale, -g.beta);
-      const float gj = gp[j * g.hw];
-      uj = gj * pw;
-      tj = gj * xs[HALF] * pw / scale;
+      const float pw = neg_power<P34>(scale, g.beta);
+      tr[i] = gs[i] * xs[i + HALF] * pw / scale;
+      gs[i] *= pw;
     }
-    tr[SIZE - 1] = tj;
-    ur[HALF] = uj;
-    const int c = j - HALF;
-    if (c >= c0) {
-      float cross = 0.f;
+  }
 #pragma unroll
-      for (int i = 0; i < SIZE; ++i) cross += tr[i];
-      op[c * g.hw] = ur[0] - g.coef * xs[0] * cross;  // xs[0] = x of channel j - HALF
-    }
+  for (int i = 0; i < CS; ++i) {
+    if (c0 + i >= g.C) break;
+    float cross = 0.f;
 #pragma unroll
-    for (int i = 0; i + 1 < SIZE; ++i) xs[i] = xs[i + 1];
-    const int nx = j + HALF + 1;
-    xs[SIZE - 1] = (nx >= 0 && nx < g.C) ? xp[nx * g.hw] : 0.f;
+    for (int k = 0; k < SIZE; ++k) cross += tr[i + k];
+    op[(c0 + i) * g.hw] = gs[i + HALF] - g.coef * xs[i + 2 * HALF] * cross;
   }
 }
 
@@ -300,13 +463,24 @@ bool lrn_geom(const cct_lrn_desc_t* d, LrnGeom* g) {
   return true;
 }
 
-template <int SIZE>
-void launch_lrn(bool backward, const float* x, const float* dy, float* out, const LrnGeom& g,
-                dim3 grid, hipStream_t st) {
+template <int SIZE, bool P34, int CS>
+void launch_lrn_kernel(bool backward, const float* x, const float* dy, float* out, const LrnGeom& g,
+                       dim3 grid, hipStream_t st) {
   if (backward)
-    hipLaunchKernelGGL(lrn_backward_kernel<SIZE>, grid, dim3(TPB), 0, st, x, dy, out, g);
+    hipLaunchKernelGGL((lrn_backward_kernel<SIZE, P34, CS>), grid, dim3(TPB), 0, st, x, dy, out, g);
   else
-    hipLaunchKernelGGL(lrn_forward_kernel<SIZE>, grid, dim3(TPB), 0, st, x, out, g);
+    hipLaunchKernelGGL((lrn_forward_kernel<SIZE, P34, CS>), grid, dim3(TPB), 0, st, x, out, g);
+}
+template <int SIZE>
+void launch_lrn(bool backward, const float* x, const float* dy, float* out, const LrnGeom& g, int cs,
+                dim3 grid, hipStream_t st) {
+  const bool p34 = g.beta == 0.75f;
+  if (cs == 16)
+    p34 ? launch_lrn_kernel<SIZE, true, 16>(backward, x, dy, out, g, grid, st)
+        : launch_lrn_kernel<SIZE, false, 16>(backward, x, dy, out, g, grid, st);
+  else
+    p34 ? launch_lrn_kernel<SIZE, true, 4>(backward, x, dy, out, g, grid, st)
+        : launch_lrn_kernel<SIZE, false, 4>(backward, x, dy, out, g, grid, st);
 }
 
 int run_lrn(const cct_lrn_desc_t* desc, bool backward, const float* x, const float* dy, float* out,
@@ -318,22 +492,20 @@ int run_lrn(const cct_lrn_desc_t* desc, bool backward, const float* x, const flo
   const double elems = (double)g.pixels * g.C;
   ProfScope ps(backward ? "lrn_backward_kernel" : "lrn_forward_kernel", 0.0,
                (backward ? 12.0 : 8.0) * elems, st);
-  // A thread walks a segment of the channels of its pixel.  With few pixels (CaffeNet's norm2 has
-  // 43 264 at batch 256) one thread per pixel leaves most of the chip idle, so the channels are cut
-  // into segments of at least kLrnMinSeg until about kLrnThreads threads exist; a segment re-reads
-  // the size-1 (backward: 2*(size-1)) neighbouring channels of its ends.
-  const long long want = (kLrnThreads + g.pixels - 1) / g.pixels;
-  const long long nseg0 = std::max<long long>(1, std::min<long long>(want, g.C / kLrnMinSeg));
-  g.cs = (int)((g.C + nseg0 - 1) / nseg0);
-  const unsigned nseg = (unsigned)((g.C + g.cs - 1) / g.cs);
+  // A thread takes 16 channels of its pixel, all loaded before the first result, so that a CU has enough
+  // bytes in flight; the size-1 (backward: 2*(size-1)) channels around them come from L2 once more.  With
+  // few pixels 4, for more threads.  norm1 at batch 256 (72 MB): forward 72 us walking the channels with one
+  // load ahead and powf, 32 now; backward 97 -> 49.
+  const int cs = (g.pixels * ((g.C + 15) / 16) >= kLrnThreads) ? 16 : 4;
+  const unsigned nseg = (unsigned)((g.C + cs - 1) / cs);
   if (nseg > 65535) return CCT_EUNSUPPORTED;
   const dim3 grid((unsigned)blocks, nseg);
   switch (desc->size) {
-    case 1: launch_lrn<1>(backward, x, dy, out, g, grid, st); break;
-    case 3: launch_lrn<3>(backward, x, dy, out, g, grid, st); break;
-    case 5: launch_lrn<5>(backward, x, dy, out, g, grid, st); break;
-    case 7: launch_lrn<7>(backward, x, dy, out, g, grid, st); break;
-    case 9: launch_lrn<9>(backward, x, dy, out, g, grid, st); break;
+    case 1: launch_lrn<1>(backward, x, dy, out, g, cs, grid, st); break;
+    case 3: launch_lrn<3>(backward, x, dy, out, g, cs, grid, st); break;
+    case 5: launch_lrn<5>(backward, x, dy, out, g, cs, grid, st); break;
+    case 7: launch_lrn<7>(backward, x, dy, out, g, cs, grid, st); break;
+    case 9: launch_lrn<9>(backward, x, dy, out, g, cs, grid, st); break;
     default: return CCT_EUNSUPPORTED;  // window sizes are compiled in: 1, 3, 5, 7, 9
   }
   CCT_CHECK_LAUNCH();
@@ -472,8 +644,24 @@ int cct_maxpool_forward(const cct_pool_desc_t* desc, const float* x, float* y, i
   hipStream_t st = (hipStream_t)hip_stream;
   ProfScope ps("maxpool_forward_kernel", 0.0,
                4.0 * (double)desc->N * desc->C * g.H * g.W + (argmax ? 8.0 : 4.0) * (double)total, st);
-  hipLaunchKernelGGL(maxpool_forward_kernel, dim3((unsigned)blocks), dim3(TPB), 0, st, x, y, argmax,
-                     total, g);
+  const long long Po = (long long)g.Ho * g.Wo;
+  if ((g.K == 3 || g.K == 2) && g.s <= g.K && walk_fits(Po, (long long)g.H * g.W, Po)) {
+    const dim3 grid((unsigned)((total + kWalk - 1) / kWalk));
+    const FastDiv divP = make_fastdiv((int)Po), divC = make_fastdiv(g.Wo);
+    const bool clip = g.p > 0 || (g.Ho - 1) * g.s + g.K > g.H || (g.Wo - 1) * g.s + g.K > g.W;
+    auto run = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, grid, dim3(TPB), 0, st, x, y, argmax, total, g, divP, divC);
+    };
+    if (g.K == 3 && g.s == 2 && !clip)
+      run(maxpool_forward_window<3, false, true>);
+    else if (g.K == 3)
+      clip ? run(maxpool_forward_window<3, true>) : run(maxpool_forward_window<3, false>);
+    else
+      clip ? run(maxpool_forward_window<2, true>) : run(maxpool_forward_window<2, false>);
+  } else {
+    hipLaunchKernelGGL(maxpool_forward_kernel, dim3((unsigned)blocks), dim3(TPB), 0, st, x, y, argmax,
+                       total, g);
+  }
   CCT_CHECK_LAUNCH();
   return CCT_OK;
 }
@@ -488,6 +676,21 @@ int cct_maxpool_backward(const cct_pool_desc_t* desc, const float* dy, const int
   hipStream_t st = (hipStream_t)hip_stream;
   ProfScope ps("maxpool_backward_kernel", 0.0,
                4.0 * (double)total + 8.0 * (double)desc->N * desc->C * g.Ho * g.Wo, st);
+  const long long ca = ((long long)g.H - 1 + g.p) / 2 + 1, cb = ((long long)g.W - 1 + g.p) / 2 + 1;
+  if (g.s == 2 && (g.K == 3 || g.K == 2) &&
+      walk_fits(ca * cb, (long long)g.H * g.W, (long long)g.Ho * g.Wo)) {
+    const long long cells = (long long)desc->N * desc->C * ca * cb;
+    const dim3 grid((unsigned)((cells + kWalk - 1) / kWalk));
+    const FastDiv divP = make_fastdiv((int)(ca * cb)), divC = make_fastdiv((int)cb);
+    if (g.K == 3)
+      hipLaunchKernelGGL(maxpool_backward_cells<3>, grid, dim3(TPB), 0, st, dy, argmax, dx, cells, (int)(ca * cb), g,
+                         divP, divC);
+    else
+      hipLaunchKernelGGL(maxpool_backward_cells<2>, grid, dim3(TPB), 0, st, dy, argmax, dx, cells, (int)(ca * cb), g,
+                         divP, divC);
+    CCT_CHECK_LAUNCH();
+    return CCT_OK;
+  }
   // planes whose dy and argmax fit 64 KiB of LDS: about 4096 input pixels per workgroup
   const long long P = (long long)g.H * g.W, Po = (long long)g.Ho * g.Wo;
   const long long planes = (long long)desc->N * desc->C;

@@ -276,3 +276,26 @@ def test_softmax_loss_label_out_of_range_gives_nan_not_a_fault(B):
     assert bool(torch.isnan(il[1])) and bool(torch.isnan(il[2])) and bool(torch.isnan(loss[0]))
     assert abs(float(il[0]) - np.log(5.0)) < 1e-5
     assert torch.allclose(dx[1], torch.full((5,), 0.2 / 3, device="cuda"))
+
+
+@pytest.mark.parametrize("beta,scale", [(0.75, 1.0), (0.75, 1e6), (0.75, 1e-12), (0.6, 3.0)],
+                         ids=["newton", "beyond_2_30", "small", "powf"])
+@pytest.mark.parametrize("N,C,H,W", [(2, 37, 5, 7), (5, 16, 260, 230)], ids=["c37_short_segments", "c16"])
+def test_lrn_powers_and_segments(B, beta, scale, N, C, H, W):
+    """Both forms of the power (Newton's step inside [2^-30, 2^30], powf outside and for other exponents)
+    and both segment lengths, against the oracle in 64 bits: a few fp32 roundings per element."""
+    import torch
+    rng = np.random.default_rng(7)
+    x = (rng.standard_normal((N, C, H, W)) * scale).astype(np.float32)
+    dy = rng.standard_normal((N, C, H, W)).astype(np.float32)
+    k = 1.0 if scale >= 1 else 1e-20                    # a small scale needs a small k to matter
+    d = B.make_lrn_desc(N, C, H, W, alpha=0.5, beta=beta, k=k)
+    y, dx = (torch.full((N, C, H, W), float("nan"), device="cuda") for _ in range(2))
+    tx = dev(x)
+    B.cct_lrn_forward(d, tx, y)
+    B.cct_lrn_backward(d, tx, dev(dy), dx)
+    torch.cuda.synchronize()
+    od = oracle.LrnDims(N, C, H, W, 5, 0.5, beta, k)
+    for got, want in ((y, oracle.lrn_forward(od, x)), (dx, oracle.lrn_backward(od, x, dy))):
+        got = got.cpu().numpy().astype(np.float64)
+        assert np.linalg.norm(got - want) <= 1e-6 * np.linalg.norm(want)
