@@ -217,6 +217,10 @@ bool split_plan(const cct_conv_desc_t& d, int pass, const Geom& g, SplitPlan* sp
   const int s = d.stride, U = (d.K + s - 1) / s;
   const bool fwd = pass == CCT_PASS_FORWARD;
   if (!fwd && s == 1 && d.pad > d.K - 1) return false;
+  // Many channels into at most a 32-row tile of kernels: all four waves read the same rows of the pack and
+  // Type 3, whose rows are kernels x taps, is the faster one (128 images of 28 x 28, 512 -> 16 channels:
+  // 167 us against 231; 1024 -> 32: 506 against 520).
+  if (fwd && s == 1 && d.K <= 3 && g.Og <= 32 && g.Cg >= 128) return false;
   const long long kIn = (long long)d.C * d.H * d.W, kOut = (long long)d.O * g.Hout * g.Wout;
   if (kIn >= kIntMax || kOut >= kIntMax || (long long)d.C * s * s >= kIntMax / 2) return false;
   auto fits = [&](int kind, long long M, int channels, int K) {
@@ -232,6 +236,18 @@ bool split_plan(const cct_conv_desc_t& d, int pass, const Geom& g, SplitPlan* sp
   }
   if (fits(0, g.Og, g.Cg, d.K)) return true;
   return (s == 2 || s == 4) && U >= 2 && fits(3, g.Og, g.Cg * s * s, U);
+}
+
+double split_cost(const cct_conv_desc_t& d, int pass, const Geom& g, const SplitPlan& sp);
+double fused_fp32_cost(const cct_conv_desc_t& d, int pass);
+
+// Does a fused pass run on conv_fused_split?  An explicit FUSED does wherever it can; AUTO where the
+// estimate says so: with few channels or kernels much of a tile is padding and the fp32 fused kernels do
+// less of it (22 images of 23 x 23, 8 channels, 32 kernels: 16 us against 23).
+bool use_split(const cct_conv_desc_t& d, int pass, const Geom& g, SplitPlan* sp) {
+  if (!split_plan(d, pass, g, sp)) return false;
+  if (d.lowering != CCT_LOWER_AUTO || (pass == CCT_PASS_BACKWARD_DATA && d.stride > 1)) return true;
+  return split_cost(d, pass, g, *sp) <= fused_fp32_cost(d, pass);
 }
 
 inline int esize(const cct_conv_desc_t& d) { return d.precision == CCT_PREC_BF16_IN_F32_ACC ? 2 : 4; }
@@ -250,6 +266,7 @@ struct Layout {
   int S = 1, split_len = 0;  // NT GEMM
   int split = 0;    // fused forward / backward-data on conv_fused_split, as sp says
   SplitPlan sp;
+  int tsplit = 0;   // Type-3 forward / Type-1 backward-data on gemm_split, x / dy read in place
   int gsplit = 0;   // forward / backward-data of a 1 x 1 layer in place on gemm_split
   int img = 0;      // backward-weights on granules of 8 images, as ip says
   BwdwImgPlan ip;
@@ -266,20 +283,36 @@ double layout_cost(const cct_conv_desc_t& d, int pass, int type);
 // Backward-weights on granules of 8 images (conv_bwdw_img.hip): what AUTO runs where the estimates say
 // that rewriting x and dy once pays (they are re-read as often as the product has tiles), and how FUSED
 // computes fp32 layers by the same rule.  The other estimates leave out the bias gradient's pass over
-// dy, hence the tenth (in bf16 also a launch that rewrites dy).  Measured over 500 layers of 1 to 1024 images: up to 2.9 times as fast where it
+// dy; in bf16 they are 40 % short of what the materialised layouts take.  Measured over 500 layers of 1 to 1024 images: up to 2.9 times as fast where it
 // is chosen (conv3 at batch 1024: 2880 -> 1590 us), at most 15 % slower for single calls under 40 us;
 // it stays off for a single image (conv3: 31 us against 38), 3 channels (conv1 at batch 256: 697 us
 // against 997) and 1 x 1 kernels at stride 2 (they use a quarter of the x that would be rewritten).
 bool bwdw_img_wins(const cct_conv_desc_t& d, int type) {
   if (d.lowering != CCT_LOWER_AUTO && !(type == CCT_LOWER_FUSED && d.precision == CCT_PREC_F32)) return false;
   BwdwImgPlan p;
-  const double allowance = d.precision == CCT_PREC_F32 ? 1.1 : 1.4;
-  return bwdw_img_plan(d, d.N, &p) && p.seconds < allowance * layout_cost(d, CCT_PASS_BACKWARD_WEIGHTS, type);
+  if (!bwdw_img_plan(d, d.N, &p)) return false;
+  const double cost = layout_cost(d, CCT_PASS_BACKWARD_WEIGHTS, type);
+  if (d.precision != CCT_PREC_F32) return p.seconds < 1.4 * cost;
+  const Geom g = make_geom(d, CCT_LOWER_TYPE1);
+  // few kernels: Types 2 and 3, which take the taps into the rows, are better than their estimates
+  // (53 images of 41 x 41, two groups of 171 channels and 19 kernels: 259 us against 294)
+  if (2 * g.Og < p.BM) return p.seconds < 0.85 * cost;
+  return p.seconds < cost + 4.0 * d.N * d.O * g.Hout * g.Wout / 4.0e12 + 4.0e-6;
 }
 
 // 1 x 1 kernels at stride 1 without padding: every lowering is the identity, so the forward and
 // backward-data passes are products on the tensors in place.
 inline bool pointwise(const cct_conv_desc_t& d) { return d.K == 1 && d.stride == 1 && d.pad == 0; }
+
+// A product over up to 32 channels is one stage of gemm_split or less: all of it is filling, draining and
+// writing the result, where the fp32 kernel with its 64-, 96- or 128-row tiles is as good unless it pads more
+// rows (84 images of 40 x 40, 32 -> 480 channels: 80 us against 92; 170 images of 42 x 42, 25 -> 391
+// channels, 512 rows against 448: 385 us against 263).
+inline bool short_product(int M, int K) {
+  int BM, BN, BK;
+  gemm_tn_tile(M, 1, &BM, &BN, &BK);
+  return K <= 32 && align_up(M, BM) <= gemm_split_mpad(M);
+}
 
 GemmTN pointwise_problem(const cct_conv_desc_t& d, int pass, const Geom& g, const Layout& L, const void* pack,
                          const float* in, float* out, const float* bias, long long ni) {
@@ -302,9 +335,27 @@ bool pointwise_split(const cct_conv_desc_t& d, int pass, const Geom& g, long lon
   if (!pointwise(d) || d.precision != CCT_PREC_F32 || pass == CCT_PASS_BACKWARD_WEIGHTS) return false;
   if (nc * d.H * d.W >= kIntMax - 256 || (long long)d.H * d.W >= kIntMax) return false;
   const bool fwd = pass == CCT_PASS_FORWARD;
+  if (short_product(fwd ? g.Og : g.Cg, fwd ? g.Cg : g.Og)) return false;
   L->Mpad = gemm_split_mpad(fwd ? g.Og : g.Cg);
   L->Kpad = gemm_split_kpad(fwd ? g.Cg : g.Og);
   return gemm_split_fits(pointwise_problem(d, pass, g, *L, nullptr, nullptr, nullptr, nullptr, nc), false);
+}
+
+// Type 3 forward (D^ is x itself) and Type 1 backward-data (dR^ is dy itself) in fp32: the product on
+// gemm_split with the tensor in place; only the larger matrix on the other side is materialised.
+bool tensor_split(const cct_conv_desc_t& d, int pass, int type, const Geom& g, long long nc, Layout* L) {
+  const bool fwd = pass == CCT_PASS_FORWARD && type == CCT_LOWER_TYPE3;
+  const bool bwd = pass == CCT_PASS_BACKWARD_DATA && type == CCT_LOWER_TYPE1;
+  if (!(fwd || bwd) || d.precision != CCT_PREC_F32 || pointwise(d)) return false;
+  GemmTN p;
+  std::memset(&p, 0, sizeof(p));
+  p.M = fwd ? g.Mr : g.Kd; p.Kdim = fwd ? g.Kd : g.Mr; p.Ncols = (int)(nc * g.Pc); p.G = d.groups;
+  if (p.M >= kIntMax - 64 || short_product(p.M, p.Kdim)) return false;
+  L->Mpad = p.Mpad = gemm_split_mpad(p.M);
+  L->Kpad = p.Kpad = gemm_split_kpad(p.Kdim);
+  p.b_ks = g.Pc;
+  p.bmap = ColMap{(int)g.Pc, (long long)(fwd ? d.C : d.O) * g.Pc};
+  return gemm_split_fits(p, false);
 }
 
 // allow_split = false: without conv_fused_split, whose pack takes half as much again as the fp32 one,
@@ -326,8 +377,15 @@ bool make_layout(const cct_conv_desc_t& d, int pass, int type, const Geom& g, lo
   const long long dt_rows = (long long)d.C * g.DKi * g.DKj;
   const long long rt_rows = (long long)d.O * g.RKi * g.RKj;
   L->gsplit = allow_split && pointwise_split(d, pass, g, nc, L);
-  L->split = type == CCT_LOWER_FUSED && allow_split && split_plan(d, pass, g, &L->sp);
-  if (L->gsplit) {
+  L->tsplit = allow_split && tensor_split(d, pass, type, g, nc, L);
+  L->split = type == CCT_LOWER_FUSED && allow_split && use_split(d, pass, g, &L->sp);
+  if (L->tsplit) {
+    take((long long)d.groups * L->Mpad * L->Kpad * 6, &L->pack_off, &L->pack_bytes);
+    if (pass == CCT_PASS_FORWARD)
+      take(rt_rows * L->ld * 4, &L->rt_off, &L->rt_bytes);
+    else
+      take(dt_rows * L->ld * 4, &L->dt_off, &L->dt_bytes);
+  } else if (L->gsplit) {
     take((long long)d.groups * L->Mpad * L->Kpad * 6, &L->pack_off, &L->pack_bytes);
   } else if (L->split) {
     // one column per output pixel (forward), input pixel or cell of the strided grid (backward-data)
@@ -498,7 +556,7 @@ constexpr double kFusedGemmFactor = 0.95; // fused kernels vs the GEMM on a mate
 //      + max(t_mfma, t_mem) + 0.3 * min(t_mfma, t_mem),  t_mfma = GEMM flops / MFMA rate,
 //        t_mem = GEMM bytes / GEMM stream rate              (loads mostly overlap the MFMAs)
 //      + launches * launch latency
-double layout_cost(const cct_conv_desc_t& d, int pass, int type) {
+double kernel_cost(const cct_conv_desc_t& d, int pass, int type) {
   const Geom g = make_geom(d, type);
   const double es = esize(d);
   const double N = d.N;
@@ -527,14 +585,17 @@ double layout_cost(const cct_conv_desc_t& d, int pass, int type) {
     return std::min(1.0, tiles / 512.0);
   };
   double index_bytes = 0.0, gemm_bytes = 0.0, launches = 2.0, rate = kGemmFlopsPerSec;
-  SplitPlan sp;
-  if (type == CCT_LOWER_FUSED && split_plan(d, pass, g, &sp)) {
-    const GemmTN q = split_problem(d, g, sp, nullptr, nullptr, nullptr, nullptr, 1);
-    return std::max(conv_fused_split_seconds(q, d.N), (x_bytes + y_bytes) / kGemmBytesPerSec) + launches * kLaunchSec;
-  } else if (pass == CCT_PASS_FORWARD && type == CCT_LOWER_FUSED) {
+  if (pass == CCT_PASS_FORWARD && type == CCT_LOWER_FUSED) {
     // no lowered matrix at all; building the operand in the kernel costs the GEMM some of its rate
     gemm_bytes = x_bytes + y_bytes;
     rate *= kFusedGemmFactor * eff_fused(g.Mr) * fill(g.Mr, cols) * short_k(g.Kd);
+  } else if (Layout L; tensor_split(d, pass, type, g, 1, &L)) {
+    const bool fwd = pass == CCT_PASS_FORWARD;
+    const double side = (fwd ? rt_elems : dt_elems) * 4.0;  // written by the product, read by lift / inverse lowering
+    const double t = gemm_split_seconds(L.Mpad, fwd ? g.Kd : g.Mr, (long long)cols, d.groups);
+    // small tensors: the gather's chain of K*K taps (K = 7: 30 us where the bytes take 8)
+    return (side + (fwd ? y_bytes : x_bytes)) / kStreamBytesPerSec + d.K * d.K * 0.35e-6 +
+           std::max(t, ((fwd ? x_bytes : y_bytes) + side) / kGemmBytesPerSec) + 3.0 * kLaunchSec;
   } else if (pass == CCT_PASS_FORWARD) {
     index_bytes += x_bytes + dt_elems * es;      // lowering: read x, write D^T
     gemm_bytes += dt_elems * es;                 // GEMM reads D^T
@@ -600,7 +661,25 @@ double layout_cost(const cct_conv_desc_t& d, int pass, int type) {
          launches * kLaunchSec;
 }
 
-// The same with the kernel that FUSED runs for an fp32 backward-weights pass.
+double fused_fp32_cost(const cct_conv_desc_t& d, int pass) {
+  return kernel_cost(d, pass, CCT_LOWER_FUSED);
+}
+double split_cost(const cct_conv_desc_t& d, int pass, const Geom& g, const SplitPlan& sp) {
+  const GemmTN q = split_problem(d, g, sp, nullptr, nullptr, nullptr, nullptr, 1);
+  const double bytes = 4.0 * d.N * ((double)d.C * d.H * d.W + (double)d.O * g.Hout * g.Wout);
+  return std::max(conv_fused_split_seconds(q, d.N), bytes / kGemmBytesPerSec) + 2.0 * kLaunchSec;
+}
+// The same with the faster of the kernels that FUSED has for an fp32 forward / backward-data pass.
+double layout_cost(const cct_conv_desc_t& d, int pass, int type) {
+  const double c = kernel_cost(d, pass, type);
+  if (type != CCT_LOWER_FUSED) return c;
+  const Geom g = make_geom(d, type);
+  SplitPlan sp;
+  if (!split_plan(d, pass, g, &sp)) return c;
+  const double s = split_cost(d, pass, g, sp);
+  return pass == CCT_PASS_BACKWARD_DATA && d.stride > 1 ? s : std::min(c, s);
+}
+// ... and with the one for an fp32 backward-weights pass.
 double model_cost(const cct_conv_desc_t& d, int pass, int type) {
   const double c = layout_cost(d, pass, type);
   BwdwImgPlan p;
@@ -888,6 +967,38 @@ int run_pointwise(const cct_conv_desc_t& d, const Geom& g, int pass, const Layou
   return rc;
 }
 
+// Type 3 forward / Type 1 backward-data with the tensor in place: product, then lifting / inverse lowering.
+int run_tensor_split(const cct_conv_desc_t& d, const Geom& g, int pass, const Layout& L, long long nc, const float* in,
+                     const float* w, const float* bias, float* out, char* ws, hipStream_t st) {
+  const bool fwd = pass == CCT_PASS_FORWARD;
+  const int KK = d.K * d.K, M = fwd ? g.Mr : g.Kd, Kd = fwd ? g.Kd : g.Mr;
+  const long long in_img = (fwd ? d.C : d.O) * g.Pc;
+  const long long out_img = fwd ? (long long)d.O * g.Hout * g.Wout : (long long)d.C * d.H * d.W;
+  void* pack = ws + L.pack_off;
+  float* side = reinterpret_cast<float*>(ws + (fwd ? L.rt_off : L.dt_off));
+  // forward: rows (oo, i, j), k = ci; backward-data: rows (ci, i, j), k = oo
+  int rc = launch_pack_rows_split(w, pack, d.groups, M, L.Mpad, L.Kpad, Kd, d.groups * Kd,
+                                  fwd ? (long long)g.Cg * KK : KK, fwd ? KK : (long long)g.Cg * KK,
+                                  (long long)g.Og * g.Cg * KK, st, KK);
+  for (long long n0 = 0; n0 < d.N && !rc; n0 += nc) {
+    const int ni = (int)std::min<long long>(nc, d.N - n0);
+    GemmTN p;
+    std::memset(&p, 0, sizeof(p));
+    p.A = pack; p.Mpad = L.Mpad; p.Kpad = L.Kpad;
+    p.a_gs = (long long)L.Mpad * L.Kpad;
+    p.B = in + n0 * in_img; p.b_ks = g.Pc; p.b_gs = (long long)Kd * g.Pc;
+    p.bmap = ColMap{(int)g.Pc, in_img};
+    p.C = side; p.c_ms = L.ld; p.c_gs = (long long)M * L.ld;
+    p.cmap = kPlain;
+    p.M = M; p.Ncols = (int)(ni * g.Pc); p.Kdim = Kd; p.G = d.groups;
+    rc = launch_gemm_split(p, d.groups * Kd, false, st);
+    if (rc) break;
+    rc = fwd ? launch_lift(side, L.ld, out + n0 * out_img, bias, ni, d.O, g.lift, st)
+             : launch_inv_lower(side, L.ld, out + n0 * out_img, ni, d.C, g.lower, st);
+  }
+  return rc;
+}
+
 // The forward pass.  static_scratch: the workspace is the library's scratch array, whose address
 // is looked up only after every argument and size check has passed.
 int forward_on_workspace(const cct_conv_desc_t* desc, const float* x, const float* w,
@@ -919,6 +1030,8 @@ int forward_on_workspace(const cct_conv_desc_t* desc, const float* x, const floa
   const int es = esize(d);
   const long long P = (long long)g.Hout * g.Wout;
 
+  if (L.tsplit)
+    return run_tensor_split(d, g, CCT_PASS_FORWARD, L, nc, x, w, bias, y, ws, st);
   if (L.gsplit)
     return run_pointwise(d, g, CCT_PASS_FORWARD, L, nc, x, w, bias, y, ws, st);
   if (L.split)
@@ -1037,6 +1150,8 @@ int cct_conv_backward_data(const cct_conv_desc_t* desc, const float* w, const fl
   const long long P = (long long)g.Hout * g.Wout;
   const long long HW = (long long)d.H * d.W;
 
+  if (L.tsplit)
+    return run_tensor_split(d, g, CCT_PASS_BACKWARD_DATA, L, nc, dy, w, nullptr, dx, ws, st);
   if (L.gsplit)
     return run_pointwise(d, g, CCT_PASS_BACKWARD_DATA, L, nc, dy, w, nullptr, dx, ws, st);
   if (L.split)

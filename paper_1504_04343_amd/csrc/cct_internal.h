@@ -178,9 +178,10 @@ int gemm_split_kpad(int K);
 bool gemm_split_fits(const GemmTN& p, bool bt);
 int gemm_split_bm(int Mpad, long long tiles_n, int K, int G);
 int launch_gemm_split(const GemmTN& p, int Ktotal, bool bt, hipStream_t st);
-// pack of element (m, k) of group g = src[g*sg + m*sm + k*sk]
+double gemm_split_seconds(int Mpad, int K, long long cols, long long G);
+// pack of element (m, k) of group g = src[g*sg + (m / taps)*sm + m % taps + k*sk]
 int launch_pack_rows_split(const float* src, void* pack, int G, int M, int Mpad, int Kpad, int Kdim, int Ktotal,
-                           long long sm, long long sk, long long sg, hipStream_t st);
+                           long long sm, long long sk, long long sg, hipStream_t st, int taps = 1);
 
 // Backward-weights pass on granules of 8 images (conv_bwdw_img.hip), fp32 as three bf16 terms or bf16:
 // plan for nimg images at a time and the workspace it needs.  false = sizes it cannot address.

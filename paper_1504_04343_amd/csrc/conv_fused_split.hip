@@ -645,7 +645,11 @@ int launch_rows(const GemmTN& p, const KcGeom& fg, size_t lds, hipStream_t st) {
 bool split_geom(const GemmTN& p, KcGeom* fg, size_t* lds) {
   // the pack of one group is addressed with 32-bit byte offsets
   if (p.bf16 || (long long)p.Mpad * p.Kpad * 6 >= (1LL << 31)) return false;
-  if (p.M <= 32) return false;  // most of a tile's rows would be padding
+  // Rows and channels are padded to whole tiles and groups: below two fifths of useful work the fp32 fused
+  // kernels and the products on materialised matrices are the faster ones (160 images of 55 x 55, 8 channels
+  // padded to 16 and 38 kernels to 64: 124 us against 184; half of it useful, 16 kernels on 352 channels,
+  // 30 images of 52 x 52: 222 against 117).
+  if (5LL * p.M * p.gCg < 2LL * p.Mpad * ((p.gCg + CG - 1) / CG * CG)) return false;
   if (p.s2d && p.gK == 5) return false;  // kernels of 9 and 10 (stride 2), 17 to 20 (stride 4): no form
   GeomRules rules;
   rules.r_step = 8;
@@ -683,7 +687,8 @@ bool conv_fused_split_fits(const GemmTN& p) {
 // Sustained rate of the tiles, padding included, plus what filling and draining a round of workgroups
 // costs; a launch that leaves CUs idle takes at least the serial chain of one workgroup.  Measured:
 // 64- and 128-row tiles 255 TFLOP/s, 32-row tiles (four waves read the same rows of the pack) 150;
-// about 6 us per round of 512 workgroups and 0.27 us per K tile of a lone workgroup.
+// about 6 us per round of 512 workgroups; a lone workgroup takes 0.27 us per K tile and at least 2.7 us per
+// channel group, the way of the next group's cells from memory.
 double conv_fused_split_seconds(const GemmTN& p, int nimg) {
   KcGeom fg;
   size_t lds;
@@ -692,8 +697,9 @@ double conv_fused_split_seconds(const GemmTN& p, int nimg) {
   const int BM = split_bm(p, tn);
   const double wgs = (double)tn * (p.Mpad / BM) * p.G;
   const double flops = 2.0 * wgs * BM * BN * p.Kpad;
+  const double group = std::max(tiles_per_group(p.gK) * 0.27e-6, 2.7e-6);
   return std::max(flops / (BM == 32 ? 150.0e12 : 255.0e12) + std::ceil(wgs / 512.0) * 6.0e-6,
-                  (double)p.Kpad / CG * 0.27e-6 + 6.0e-6);
+                  (double)fg.ngroups * group + 6.0e-6);
 }
 
 int launch_pack_split(const float* w, void* pack, int kind, int G, int Og, int Cg, int K, int s, int Mpad,

@@ -126,8 +126,8 @@ namespace {
 
 // The plan on gemm_split.  The row operand (x of the forward pass, dy of the others) is packed as three
 // bf16 terms, w and x are read in place.  The contraction is cut into the number of splits S that is
-// estimated fastest: rounds of workgroups (512 of 128 rows or 1024 of 64 fit the chip) times their
-// stages, against the partial products that are written and read once more.  Measured, fc6 at batch 256
+// estimated fastest: rounds of workgroups times their stages, against the partial products that are
+// written and read once more.  Measured, fc6 at batch 256
 // (19.3 GFLOP per pass): forward 1 / 4 / 8 / 16 splits 310 / 130 / 117 / 123 us, backward-data 1 / 4 / 7 /
 // 16 splits 198 / 141 / 126 / 158; before, on the fp32 matrix instructions, 195 and 214.  false = sizes or a workspace that it
 // cannot take, or a backward-weights pass over up to 32 images, whose product is one short stage of
@@ -165,20 +165,16 @@ bool fc_plan_split(const cct_conv_desc_t& d, int pass, long long max_bytes, long
     return align_up(pack(S) + (count(S) > 1 ? room(S) * out : 0), kAlign) +
            (bwdw ? align_up(4LL * d.O * kDbiasBlocks, kAlign) : 0);
   };
-  const long long tiles_n = (cols + 127) / 128;
   auto seconds = [&](long long S) {
     const long long n = count(S);
-    const int BM = gemm_split_bm(p.Mpad, tiles_n, (int)len(S), (int)n);
-    const long long wgs = tiles_n * (p.Mpad / BM) * n, slots = BM == 128 ? 512 : 1024;
-    const double stage = 2.0 * BM * 128 * 32 / ((BM == 128 ? 230.0e12 : BM == 64 ? 200.0e12 : 120.0e12) / slots);
-    return (double)((wgs + slots - 1) / slots) * ((len(S) + 31) / 32 * stage + 4.0e-6) +
+    return gemm_split_seconds(p.Mpad, (int)len(S), cols, n) +
            (n > 1 ? 2.0 * n * out / 6.0e12 : 0.0);
   };
   long long S = 1;
   if (!bwdw) {
     double best = need(1) <= cap ? seconds(1) : 1e30;
     for (long long sp = 2; sp <= 64 && Kd / sp >= kFcMinSplitRows; ++sp) {
-      if (need(sp) > cap) continue;
+      if ((sp > 16 && sp % 4) || need(sp) > cap) continue;
       const double t = seconds(sp);
       if (t < best) {
         best = t;

@@ -321,11 +321,12 @@ __global__ __launch_bounds__(NT, WAVES_M == 4 ? 2 : 4) void gemm_split(GemmTN p,
   }
 }
 
-// pack[g][tile][term][m][16] = the terms of src[m * sm + (g * Kdim + k) * sk + group offset], zero padded
-// in m and k: k runs over kd = min(Kdim, Ktotal - g * Kdim) indices of the split.
+// pack[g][tile][term][m][16] = the terms of src[g * sg + (m / taps) * sm + m % taps + k * sk], zero padded in
+// m and k: k runs over min(Kdim, Ktotal - g * Kdim) indices.
 struct RowsPack {
   int G, M, Mpad, Kpad, Kdim, Ktotal;
-  long long sm, sk, sg;  // sg: elements between groups (channel groups: whole matrices; splits: Kdim * sk)
+  long long sm, sk, sg;
+  int taps;
 };
 __global__ __launch_bounds__(256) void pack_rows_split_kernel(const float* __restrict__ src,
                                                               unsigned short* __restrict__ pack, RowsPack d) {
@@ -339,7 +340,8 @@ __global__ __launch_bounds__(256) void pack_rows_split_kernel(const float* __res
   const int tile = (int)(r / d.Mpad), m = (int)(r - (long long)tile * d.Mpad);
   const int k0 = tile * TK + half * 8;
   const int kd = min(d.Kdim, d.Ktotal - g * d.Kdim);
-  const float* s = src + g * d.sg + m * d.sm + k0 * d.sk;
+  const int row = m / d.taps;
+  const float* s = src + g * d.sg + row * d.sm + (m - row * d.taps) + k0 * d.sk;
   unsigned short h[8], mm[8], l[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
@@ -401,6 +403,19 @@ int gemm_split_bm(int Mpad, long long tiles_n, int K, int G) {
   return BM;
 }
 
+// Rounds of workgroups (512 of 128 rows fit the chip, 1024 of fewer) times their stages at the measured
+// rates, 4 us to fill and drain a round.  Where the fullest CU holds fewer of them than fit, each is faster,
+// but a lone workgroup of 128 rows still takes two thirds as long as one of two.
+double gemm_split_seconds(int Mpad, int K, long long cols, long long G) {
+  const long long tiles_n = (cols + BN - 1) / BN;
+  const int BM = gemm_split_bm(Mpad, tiles_n, K, (int)G);
+  const long long wgs = tiles_n * (Mpad / BM) * G, slots = BM == 128 ? 512 : 1024;
+  const double stage = 2.0 * BM * BN * 32 / ((BM == 128 ? 230.0e12 : BM == 64 ? 200.0e12 : 120.0e12) / slots);
+  const double rounds = (double)((wgs + slots - 1) / slots);
+  const double share = std::min(1.0, 0.3 + 0.7 * (double)((wgs + 255) / 256) / (slots / 256));
+  return rounds * ((K + 31) / 32 * stage * share + 4.0e-6);
+}
+
 int launch_gemm_split(const GemmTN& p0, int Ktotal, bool bt, hipStream_t st) {
   GemmTN p = p0;
   colmap_prepare(&p.bmap);
@@ -418,8 +433,8 @@ int launch_gemm_split(const GemmTN& p0, int Ktotal, bool bt, hipStream_t st) {
 }
 
 int launch_pack_rows_split(const float* src, void* pack, int G, int M, int Mpad, int Kpad, int Kdim, int Ktotal,
-                           long long sm, long long sk, long long sg, hipStream_t st) {
-  const RowsPack d{G, M, Mpad, Kpad, Kdim, Ktotal, sm, sk, sg};
+                           long long sm, long long sk, long long sg, hipStream_t st, int taps) {
+  const RowsPack d{G, M, Mpad, Kpad, Kdim, Ktotal, sm, sk, sg, taps};
   const long long total = (long long)Kpad / 8 * Mpad * G, blocks = (total + 255) / 256;
   if (blocks <= 0 || blocks >= 2147483647LL) return CCT_EUNSUPPORTED;
   ProfScope ps("pack_rows_split_kernel", 0.0, 4.0 * M * (double)Ktotal + 48.0 * total, st);

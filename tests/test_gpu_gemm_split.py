@@ -23,7 +23,7 @@ FC = [
     layer("prime",    4,  49, 1, 1, 1951, 1),            # splits of unequal length
 ]
 POINTWISE = [
-    layer("p_small",  2,   5, 7,  9,  18, 1),
+    layer("p_small",  2,  33, 7,  9,  34, 1),
     layer("p_odd",    9,  67, 13, 11,  70, 1),           # channels and rows past a tile, tiles across images
     layer("p_groups", 5, 100, 14, 14, 130, 1, 1, 0, 2),
     layer("p_m128",  40, 160, 28, 28, 256, 1),           # 128 rows, 160 = 5 tiles: the last stage is half
@@ -102,6 +102,27 @@ def test_pointwise_in_chunks_and_in_the_fp32_workspace(B):
         got, names = ran(B, lambda: gpu_forward(B, L, x, w, b, lowering))
         assert split(names), names
         assert rel_err(got, want) <= TOL_F32
+
+
+# Type 3 forward and Type 1 backward-data: the tensor in place, the other side's matrix lifted afterwards
+TENSOR = [
+    layer("t_small",  3,  36, 9, 11,  38, 3, 1, 1),
+    layer("t_groups", 9, 130, 13, 13, 70, 3, 1, 1, 2),   # 315 and 585 rows, tiles across images
+    layer("t_stride", 5,  67, 23, 21, 37, 5, 2, 2),
+    layer("t_wide",  33,  40, 28, 28, 33, 3, 1, 0),
+]
+
+
+@pytest.mark.parametrize("chunk", [None, 2], ids=["whole", "chunks"])
+@pytest.mark.parametrize("L", TENSOR, ids=[L.name for L in TENSOR])
+def test_materialised_on_one_side(B, L, chunk):
+    x, w, b, dy = synth.make_x(L, 3), synth.make_w(L, 3), synth.make_bias(L, 3), synth.make_dy(L, 3)
+    got, names = ran(B, lambda: gpu_forward(B, L, x, w, b, 3, chunk=chunk))
+    assert split(names) and not any("lower" in n for n in names), names
+    assert rel_err(got, oracle.conv_forward(odims(oracle, L), x, w, b)) <= TOL_F32
+    got, names = ran(B, lambda: gpu_backward_data(B, L, w, dy, 1, chunk=chunk))
+    assert split(names), names
+    assert rel_err(got, oracle.conv_backward_data(odims(oracle, L), w, dy)) <= TOL_F32
 
 
 @pytest.mark.parametrize("L", [FC[1], FC[4], POINTWISE[1]], ids=["direct", "packed", "pointwise"])

@@ -15,10 +15,11 @@ KERNEL = "conv_fused_split"
 #       name        N   C    H   W    O  K  s  p  g
 FORWARD = [
     layer("m32",    2,  16,  9, 11,  36, 3, 1, 1),           # 32-row tiles, rows to spare
+    layer("m16",    3,  80, 12, 14,  16, 3, 1, 1),           # half of a 32-row tile
     layer("m64",    7,  32, 13, 13,  64, 3, 1, 1),           # 64-row tile, tiles across images
     layer("m128",  33,  40, 13, 13, 128, 3, 1, 1, 2),        # channels past a group's last one
     layer("m192",  26,  16, 28, 28, 192, 3, 1, 0),           # rows no multiple of 128, one channel group
-    layer("c9",     3,   9, 12, 17,  33, 3, 1, 2),           # channels that fill half of a group
+    layer("c9",     3,   9, 12, 17,  61, 3, 1, 2),           # channels that fill half of a group
     layer("k2",     5,  48, 10, 10,  40, 2, 1, 1),           # four taps
     layer("k4",     2,  24, 15, 12,  70, 4, 1, 2),
     layer("k5",     4,  48, 27, 27, 130, 5, 1, 2),           # tiles cut per image
@@ -28,12 +29,13 @@ FORWARD = [
     layer("s2cells", 3, 32, 15, 17,  48, 3, 2, 1),           # strided windows over the tensor's own cells
     layer("s2d2",   5,  16, 57, 57,  40, 5, 2, 0),           # space to depth by 2 (three taps), odd plane
     layer("s2d2p",  5,  12, 57, 56,  64, 3, 2, 1),           # two taps, padded
-    layer("s2d2k7", 4,   6, 64, 61,  33, 7, 2, 3),           # four taps
+    layer("s2d2k7", 4,   6, 64, 61,  37, 7, 2, 3),           # four taps
     layer("s2d4",   5,   3, 63, 65,  96, 11, 4, 0),
     layer("s2d4p",  4,   2, 64, 63,  40, 8, 4, 3),
     layer("s2d4one", 1,  3, 67, 67,  36, 11, 4, 2),          # the tensor's only image
 ]
 BACKWARD = [
+    layer("b20",    3,  20,  9, 11,  64, 3, 1, 1),           # part of a 32-row tile
     layer("b32",    2,  36,  9, 11,  16, 3, 1, 1),
     layer("b128",  33, 128, 13, 13,  40, 3, 1, 1),
     layer("b_k5",   4,  48, 27, 27,  64, 5, 1, 2),
