@@ -268,14 +268,16 @@ struct Layout {
   SplitPlan sp;
   int tsplit = 0;   // Type-3 forward / Type-1 backward-data on gemm_split, x / dy read in place
   int gsplit = 0;   // forward / backward-data of a 1 x 1 layer in place on gemm_split
+  int gran = 0;     // bf16 forward / backward-data on granules of 8 channels, as gp says
+  GranulesPlan gp;
   int img = 0;      // backward-weights on granules of 8 images, as ip says
   BwdwImgPlan ip;
   int t2_opad = 0;  // Type-2 backward-data with the inverse lifting gathered by the GEMM: padded Og
 };
 
 constexpr int kDbiasBlocks = 64;
-// Chunks of fewer images (of a larger batch) are not worth rewriting as granules of 8: each chunk adds
-// its own partial products to dw.
+// Chunks of fewer images (of a larger batch) are not worth rewriting as granules: each chunk adds its own
+// partial products to dw, or rewrites the kernels.
 constexpr int kImgLeastChunk = 32;
 
 double layout_cost(const cct_conv_desc_t& d, int pass, int type);
@@ -358,6 +360,16 @@ bool tensor_split(const cct_conv_desc_t& d, int pass, int type, const Geom& g, l
   return gemm_split_fits(p, false);
 }
 
+// Forward / backward-data in bf16 on granules of 8 channels (conv_granules.hip): what AUTO runs where the
+// estimates say that rewriting the tensor once pays; those of the other layouts are a fifth short.  Measured
+// over 60 layers: 1.05 to 2.8 times as fast where it is chosen; up to about ten images of 13 x 13 the
+// contraction of a lone workgroup is the longer way (256 -> 384 channels, 9 images: 42 us against 53).
+bool granules_win(const cct_conv_desc_t& d, int pass, int type) {
+  if (d.lowering != CCT_LOWER_AUTO || d.precision != CCT_PREC_BF16_IN_F32_ACC) return false;
+  GranulesPlan p;
+  return granules_plan(d, pass, d.N, &p) && p.seconds < 1.2 * layout_cost(d, pass, type);
+}
+
 // allow_split = false: without conv_fused_split, whose pack takes half as much again as the fp32 one,
 // and without the granules of conv_bwdw_img.
 bool make_layout(const cct_conv_desc_t& d, int pass, int type, const Geom& g, long long nc,
@@ -376,6 +388,13 @@ bool make_layout(const cct_conv_desc_t& d, int pass, int type, const Geom& g, lo
   };
   const long long dt_rows = (long long)d.C * g.DKi * g.DKj;
   const long long rt_rows = (long long)d.O * g.RKi * g.RKj;
+  L->gran = allow_split && pass != CCT_PASS_BACKWARD_WEIGHTS && nc >= std::min(d.N, kImgLeastChunk) &&
+            granules_win(d, pass, type);
+  if (L->gran) {
+    if (!granules_plan(d, pass, nc, &L->gp)) return false;
+    L->total = L->gp.total;
+    return true;
+  }
   L->gsplit = allow_split && pointwise_split(d, pass, g, nc, L);
   L->tsplit = allow_split && tensor_split(d, pass, type, g, nc, L);
   L->split = type == CCT_LOWER_FUSED && allow_split && use_split(d, pass, g, &L->sp);
@@ -534,7 +553,8 @@ bool type_supported(const cct_conv_desc_t& d, int pass, int type) {
   }
   const Geom g = make_geom(d, type);
   Layout L;
-  if (!make_layout(d, pass, type, g, 1, &L, pass != CCT_PASS_BACKWARD_WEIGHTS)) return false;
+  if (!make_layout(d, pass, type, g, 1, &L, pass != CCT_PASS_BACKWARD_WEIGHTS && d.precision == CCT_PREC_F32))
+    return false;
   return L.total <= kMaxOneImageBytes;
 }
 
@@ -748,9 +768,10 @@ long long chunk_for_workspace(const cct_conv_desc_t& d, int pass, int type, cons
   auto fits = [&](long long nc) {
     return make_layout(d, pass, type, g, nc, L, split) && (unsigned long long)L->total <= bytes;
   };
-  // a workspace too small for the split kernel matrix still holds the fp32 one; granules of 8 images
-  // need chunks of some size
-  long long lo = pass == CCT_PASS_BACKWARD_WEIGHTS ? std::min(d.N, kImgLeastChunk) : 1, hi = d.N;
+  // a workspace too small for the split kernel matrix still holds the fp32 one; granules need chunks of
+  // some size
+  const bool granules = pass == CCT_PASS_BACKWARD_WEIGHTS || d.precision != CCT_PREC_F32;
+  long long lo = granules ? std::min(d.N, kImgLeastChunk) : 1, hi = d.N;
   if (!fits(lo)) {
     split = false;
     lo = 1;
@@ -999,6 +1020,20 @@ int run_tensor_split(const cct_conv_desc_t& d, const Geom& g, int pass, const La
   return rc;
 }
 
+// bf16 forward / backward-data on granules, a chunk of nc images at a time.
+int run_granules(const cct_conv_desc_t& d, const Geom& g, int pass, const Layout& L, long long nc, const float* in,
+                 const float* w, const float* bias, float* out, char* ws, hipStream_t st) {
+  const long long x_img = (long long)d.C * d.H * d.W, y_img = (long long)d.O * g.Hout * g.Wout;
+  const bool fwd = pass == CCT_PASS_FORWARD;
+  int rc = CCT_OK;
+  for (long long n0 = 0; n0 < d.N && !rc; n0 += nc) {
+    const int ni = (int)std::min<long long>(nc, d.N - n0);
+    rc = launch_granules(d, pass, L.gp, ni, in + n0 * (fwd ? x_img : y_img), w, bias, out + n0 * (fwd ? y_img : x_img),
+                         ws, st);
+  }
+  return rc;
+}
+
 // The forward pass.  static_scratch: the workspace is the library's scratch array, whose address
 // is looked up only after every argument and size check has passed.
 int forward_on_workspace(const cct_conv_desc_t* desc, const float* x, const float* w,
@@ -1030,6 +1065,8 @@ int forward_on_workspace(const cct_conv_desc_t* desc, const float* x, const floa
   const int es = esize(d);
   const long long P = (long long)g.Hout * g.Wout;
 
+  if (L.gran)
+    return run_granules(d, g, CCT_PASS_FORWARD, L, nc, x, w, bias, y, ws, st);
   if (L.tsplit)
     return run_tensor_split(d, g, CCT_PASS_FORWARD, L, nc, x, w, bias, y, ws, st);
   if (L.gsplit)
@@ -1150,6 +1187,8 @@ int cct_conv_backward_data(const cct_conv_desc_t* desc, const float* w, const fl
   const long long P = (long long)g.Hout * g.Wout;
   const long long HW = (long long)d.H * d.W;
 
+  if (L.gran)
+    return run_granules(d, g, CCT_PASS_BACKWARD_DATA, L, nc, dy, w, nullptr, dx, ws, st);
   if (L.tsplit)
     return run_tensor_split(d, g, CCT_PASS_BACKWARD_DATA, L, nc, dy, w, nullptr, dx, ws, st);
   if (L.gsplit)

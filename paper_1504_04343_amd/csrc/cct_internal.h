@@ -194,6 +194,15 @@ bool bwdw_img_plan(const cct_conv_desc_t& d, long long nimg, BwdwImgPlan* P);
 // One chunk of nimg images; accumulate: add to dw and dbias instead of writing them.
 int launch_bwdw_img(const cct_conv_desc_t& d, const BwdwImgPlan& P, int nimg, const float* x,
                     const float* dy, float* dw, float* dbias, int accumulate, char* ws, hipStream_t st);
+// Forward / stride-1 backward-data pass for bf16 operands on granules of 8 channels (conv_granules.hip).
+struct GranulesPlan {
+  int BM;
+  long long xs_off, ks_off, total;  // workspace layout (bytes)
+  double seconds;
+};
+bool granules_plan(const cct_conv_desc_t& d, int pass, long long nimg, GranulesPlan* P);
+int launch_granules(const cct_conv_desc_t& d, int pass, const GranulesPlan& P, int nimg, const float* in,
+                    const float* w, const float* bias, float* out, char* ws, hipStream_t st);
 // Tile sizes the launchers will use for a problem (so that the planner can pad the packs).
 void gemm_tn_tile(int M, int Ncols, int* BM, int* BN, int* BK);
 void gemm_nt_tile(int M, int N, int* BM, int* BN, int* BK);

@@ -14,27 +14,24 @@
 //   3. bwdw_img_reduce: the splits' partial products are added in split order.
 // Nothing of the size of the lowered matrix exists (no K*K blow-up).
 //
-// The product: a workgroup owns BM kernels x 256 lowered rows, ordered (block of 32 channels, tap,
-// channel) so that neighbouring lanes read neighbouring granules; a wave owns 64 x 64.  A stage is SLOTS
-// (column, term) pairs of both operands, moved from memory into LDS by buffer loads that write LDS
-// directly: no registers, no vector instruction, no conversion in the loop.  Two stages alternate, one
-// meeting of the workgroup per stage; operand reads are 32 consecutive granules, which do not conflict.
-// Per 16 reduction indices a wave reads 12 KiB of LDS for 24 MFMAs (768 matrix-core cycles), half of
-// what LDS can deliver, and a 128 x 256 workgroup fetches 36 KiB of L2 for 1536 cycles of its CU.
+// The product (granule_product.h): a workgroup owns BM kernels x 256 lowered rows, ordered (block of 32
+// channels, tap, channel) so that neighbouring lanes read neighbouring granules.
+//
+// Measured (whole pass with the bias gradient; before: dy and x read in place by fp32 matrix
+// instructions, or bf16 lowered matrices): conv3 at batch 1024 2880 -> 1590 us, of it 1290 the product
+// (237 TFLOP/s of fp32 results, 1420 of bf16 MFMAs: the matrix cores' rate here) and 300 the rewriting
+// (3.7 TB/s); conv2 at batch 256 1215 -> 700; conv4 at batch 256 with bf16 operands 355 -> 125.
 #include <stdio.h>
 
 #include <algorithm>
 
 #include "cct_internal.h"
-#include "gemm_common.h"
-#include "split_bf16.h"
+#include "granule_product.h"
 
 namespace cct {
 namespace {
 
 constexpr int kImg = 8;       // images per granule
-constexpr int kGran = 16;     // bytes of a granule
-constexpr int BN = 256;       // lowered rows per workgroup
 constexpr int kChanBlock = 32;
 constexpr int kPrepPx = 32, kPrepCh = 32;  // pixels and channels a workgroup of the first step rewrites
 
@@ -132,29 +129,13 @@ struct ImgGemm {
   int sP, sWout;
 };
 
-typedef __attribute__((address_space(3))) void* lds_ptr;
-
 template <int BM, int TERMS, int SLOTS>
 __global__ __launch_bounds__(BM * 4, 2) void conv_bwdw_img(ImgGemm p) {
-  constexpr int NW = BM / 16;           // waves: 64 rows x 64 lowered rows each
-  constexpr int WAVES_N = BN / 64;
-  constexpr int NCOL = SLOTS / TERMS;   // columns of 8 images per stage
-  static_assert(SLOTS % TERMS == 0 && NCOL % 2 == 0, "a product takes two columns");
-  constexpr int STAGE = SLOTS * (BM + BN) * kGran;
-  // A wave moves the granules of CPW columns, or a WPC-th of one column: one cell address per column.
-  constexpr int CPW = NCOL > NW ? NCOL / NW : 1, WPC = NW > NCOL ? NW / NCOL : 1;
-  constexpr int A_UNITS = TERMS * (BM / 64), A_PER = (A_UNITS + WPC - 1) / WPC;  // of 64 granules
-  constexpr int B_PARTS = BN / 64 / WPC;                                       // row parts per wave
-  static_assert(CPW * NW == NCOL * WPC && (WPC == 1 || A_UNITS <= 2 * A_PER) && WPC <= 2, "whole loads");
-
+  using GP = GranuleProduct<BM, TERMS, SLOTS>;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_i[];  // [2][A: SLOTS*BM | B: SLOTS*BN]
+  GP gp;
 
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wave_m = wave / WAVES_N, wave_n = wave % WAVES_N;
-  const int lane_lo = lane & 31, lane_hi = lane >> 5;
-
+  const int lane = threadIdx.x & 63;
   // consecutive workgroup ids go round-robin over the 8 XCDs: give every XCD a contiguous run of
   // (split, tile) pairs, tile fastest, so that the tiles of one split share both operands through L2
   int bid = blockIdx.x;
@@ -171,123 +152,31 @@ __global__ __launch_bounds__(BM * 4, 2) void conv_bwdw_img(ImgGemm p) {
   const int m0 = tile_m * BM, n0 = tile_n * BN;
   const int c_begin = s * p.split_cols, c_end = min(p.ncols, c_begin + p.split_cols);
 
-  // A thread loads the same rows of both operands in every stage: constant byte offsets from the column's
-  // granules.  Rows past the last one repeat it (their products are not stored).
-  const int sub = wave % WPC;
-  unsigned a_voff[BM / 64], b_voff[B_PARTS];
+  // rows past the last one repeat it (their products are not stored)
 #pragma unroll
-  for (int u = 0; u < BM / 64; ++u) a_voff[u] = (unsigned)min(m0 + u * 64 + lane, p.M - 1) * kGran;
+  for (int u = 0; u < GP::A_PARTS; ++u) gp.a_voff[u] = (unsigned)min(m0 + u * 64 + lane, p.M - 1) * kGran;
 #pragma unroll
-  for (int u = 0; u < B_PARTS; ++u) {
-    const int n = min(n0 + (sub * B_PARTS + u) * 64 + lane, p.N - 1);
+  for (int u = 0; u < GP::B_PARTS; ++u) {
+    const int n = min(n0 + gp.b_part(u) * 64 + lane, p.N - 1);
     const int cb = n / (p.KK * kChanBlock), width = min(kChanBlock, p.Cg - cb * kChanBlock);
     const int rem = n - cb * p.KK * kChanBlock, tap = rem / width, cl = rem - tap * width;
     const int i = tap / p.K, j = tap - i * p.K;
-    b_voff[u] = (unsigned)(((long long)(i * p.Wp + j) * TERMS * p.C + cb * kChanBlock + cl) * kGran);
+    gp.b_voff[u] = (unsigned)(((long long)(i * p.Wp + j) * TERMS * p.C + cb * kChanBlock + cl) * kGran);
   }
-  const unsigned char* Ag = p.ds + (long long)g * p.Og * kGran;
   const unsigned char* Bg = p.xs + (long long)g * p.Cg * kGran;
-  const long long a_col = (long long)TERMS * p.O * kGran, b_cell = (long long)TERMS * p.C * kGran;
-
-  // Columns past the end of the split have an empty range: they load as zeros.
-  auto load_stage = [&](int buf, int c0) {
-    unsigned char* As = smem_i + buf * STAGE;
-    unsigned char* Bs = As + SLOTS * BM * kGran;
-#pragma unroll
-    for (int v = 0; v < CPW; ++v) {
-      const int cc = wave / WPC + v * NW;
-      const int col = c0 + cc, cl = min(col, c_end - 1), range = col < c_end ? 0x7fffffff : 0;
-      const int ig = fdiv_u(cl, p.mP, p.sP), pix = cl - ig * p.P;
-      const int r_ = fdiv_u(pix, p.mWout, p.sWout), c_ = pix - r_ * p.Wout;
-      const long long cell = ig * p.img_cells + (long long)(r_ * p.s) * p.Wp + c_ * p.s;
-      const __amdgpu_buffer_rsrc_t ra =
-          __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(Ag + cl * a_col), 0, range, 0x00020000);
-      const __amdgpu_buffer_rsrc_t rb =
-          __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(Bg + cell * b_cell), 0, range, 0x00020000);
-#pragma unroll
-      for (int k = 0; k < TERMS; ++k)
-#pragma unroll
-        for (int u = 0; u < B_PARTS; ++u)
-          __builtin_amdgcn_raw_ptr_buffer_load_lds(
-              rb, (lds_ptr)(Bs + ((cc * TERMS + k) * BN + (sub * B_PARTS + u) * 64) * kGran), 16, (int)b_voff[u],
-              k * p.C * kGran, 0, 0);
-#pragma unroll
-      for (int k = 0; k < TERMS; ++k)
-#pragma unroll
-        for (int u = 0; u < BM / 64; ++u) {
-          constexpr int half = A_PER;
-          const int unit = k * (BM / 64) + u;  // the first A_PER units are the first wave's
-          if (WPC == 1 || (unit / half) == sub)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_ptr)(As + ((cc * TERMS + k) * BM + u * 64) * kGran), 16,
-                                                     (int)a_voff[u], k * p.O * kGran, 0, 0);
-        }
-    }
-  };
-
-  // three terms: h*h alone in one accumulator, the corrections in the other (split_bf16.h)
-  floatx16 acc[2][2], acc_c[TERMS == 3 ? 2 : 1][TERMS == 3 ? 2 : 1];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        acc[i][j][r] = 0.f;
-        if constexpr (TERMS == 3) acc_c[i][j][r] = 0.f;
-      }
-
-  const int stages = (c_end - c_begin + NCOL - 1) / NCOL;  // <= 0 for an empty split
-  if (stages > 0) load_stage(0, c_begin);
-  const int a_lds = (lane_hi * TERMS * BM + wave_m * 64 + lane_lo) * kGran;
-  const int b_lds = SLOTS * BM * kGran + (lane_hi * TERMS * BN + wave_n * 64 + lane_lo) * kGran;
-  for (int t = 0; t < stages; ++t) {
-    // this stage's loads have landed and nobody reads the other buffer any more
-    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
-    __syncthreads();
-    if (t + 1 < stages) load_stage((t + 1) & 1, c_begin + (t + 1) * NCOL);
-    const unsigned char* st = smem_i + (t & 1) * STAGE;
-#pragma unroll
-    for (int kb = 0; kb < NCOL / 2; ++kb) {
-      bf16x8 a[2][TERMS], b[2][TERMS];
-#pragma unroll
-      for (int k = 0; k < TERMS; ++k)
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          a[i][k] = *reinterpret_cast<const bf16x8*>(st + a_lds + ((2 * kb * TERMS + k) * BM + i * 32) * kGran);
-          b[i][k] = *reinterpret_cast<const bf16x8*>(st + b_lds + ((2 * kb * TERMS + k) * BN + i * 32) * kGran);
-        }
-#define CCT_M(X, Y, ACC)                                                                    \
-  _Pragma("unroll") for (int i = 0; i < 2; ++i) _Pragma("unroll") for (int j = 0; j < 2; ++j) \
-      ACC[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][X], b[j][Y], ACC[i][j], 0, 0, 0)
-      if constexpr (TERMS == 3) {
-        CCT_M(0, 0, acc);
-        CCT_M(0, 1, acc_c);
-        CCT_M(1, 0, acc_c);
-        CCT_M(1, 1, acc_c);
-        CCT_M(0, 2, acc_c);
-        CCT_M(2, 0, acc_c);
-      } else {
-        CCT_M(0, 0, acc);
-      }
-#undef CCT_M
-    }
-  }
+  const long long b_cell = (long long)TERMS * p.C * kGran;
+  gp.run(smem_i, c_begin, c_end, p.ds + (long long)g * p.Og * kGran, (long long)TERMS * p.O * kGran, p.O * kGran,
+         p.C * kGran, [&](int col) {
+           const int ig = fdiv_u(col, p.mP, p.sP), pix = col - ig * p.P;
+           const int r = fdiv_u(pix, p.mWout, p.sWout), c = pix - r * p.Wout;
+           return Bg + (ig * p.img_cells + (long long)(r * p.s) * p.Wp + c * p.s) * b_cell;
+         });
 
   float* __restrict__ C = p.part + ((long long)s * p.G + g) * p.M * p.N;
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int n = n0 + wave_n * 64 + j * 32 + lane_lo;
-    if (n >= p.N) continue;
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = m0 + wave_m * 64 + i * 32 + (r >> 2) * 8 + lane_hi * 4 + (r & 3);
-        float v = acc[i][j][r];
-        if constexpr (TERMS == 3) v += acc_c[i][j][r];
-        if (m < p.M) C[(long long)m * p.N + n] = v;
-      }
-  }
+  gp.for_each([&](int row, int column, float v) {
+    const int m = m0 + row, n = n0 + column;
+    if (m < p.M && n < p.N) C[(long long)m * p.N + n] = v;
+  });
 }
 
 // ---- 3. sum of the splits -----------------------------------------------------------------------

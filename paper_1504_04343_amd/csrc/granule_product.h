@@ -1,0 +1,149 @@
+// The matrix product of two operands that lie in memory as granules: 8 consecutive reduction indices of one
+// row as 16 bytes of bf16, one term (bf16 operands) or three whose sum is the fp32 value (split_bf16.h).
+// A column is the 8 reduction indices of a granule.
+//
+// A workgroup computes BM x 256 results, a wave 64 x 64.  A stage is SLOTS (column, term) pairs of both
+// operands, moved from memory into LDS by buffer loads that write LDS directly: no registers, no vector
+// instruction, no conversion in the loop.  Two stages alternate, one meeting of the workgroup per stage;
+// operand reads are 32 consecutive granules, which do not conflict.  With three terms a wave reads 12 KiB
+// of LDS for 24 MFMAs (768 matrix-core cycles) per 16 reduction indices, half of what LDS can deliver, and
+// a 128 x 256 workgroup fetches 36 KiB of L2 for 1536 cycles of its CU.  With one term LDS and the matrix
+// cores are equally busy.
+#pragma once
+#include "cct_internal.h"
+#include "gemm_common.h"
+#include "split_bf16.h"
+
+namespace cct {
+namespace {
+
+constexpr int kGran = 16;  // bytes of a granule
+constexpr int BN = 256;    // columns of the result per workgroup
+
+typedef __attribute__((address_space(3))) void* lds_ptr;
+
+template <int BM, int TERMS, int SLOTS>
+struct GranuleProduct {
+  static constexpr int NW = BM / 16;  // waves
+  static constexpr int WAVES_N = BN / 64;
+  static constexpr int NCOL = SLOTS / TERMS;  // columns per stage
+  static_assert(SLOTS % TERMS == 0 && NCOL % 2 == 0, "an MFMA takes two columns");
+  static constexpr int STAGE = SLOTS * (BM + BN) * kGran;
+  static constexpr int LDS = 2 * STAGE;
+  // A wave moves the granules of CPW columns, or a WPC-th of one column: one address per column.
+  static constexpr int CPW = NCOL > NW ? NCOL / NW : 1, WPC = NW > NCOL ? NW / NCOL : 1;
+  static constexpr int A_PARTS = BM / 64, B_PARTS = BN / 64 / WPC;  // loads of 64 rows, per wave for B
+  static constexpr int A_UNITS = TERMS * A_PARTS, A_PER = (A_UNITS + WPC - 1) / WPC;
+  static_assert(CPW * NW == NCOL * WPC && WPC <= 2, "whole loads");
+
+  // byte offsets of the rows a lane loads, from a column's granules: the same in every stage
+  unsigned a_voff[A_PARTS], b_voff[B_PARTS];
+  // three terms: h*h alone in one accumulator, the corrections in the other
+  floatx16 acc[2][2], acc_c[TERMS == 3 ? 2 : 1][TERMS == 3 ? 2 : 1];
+
+  static __device__ __forceinline__ int wave() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6); }
+  // which 64 rows of B b_voff[u] stands for
+  __device__ __forceinline__ int b_part(int u) const { return wave() % WPC * B_PARTS + u; }
+
+  // Columns [c_begin, c_end): A's lie a_col apart, B's at b_at(column); terms lie a_term / b_term apart.
+  template <class BAt>
+  __device__ __forceinline__ void run(unsigned char* smem, int c_begin, int c_end, const unsigned char* A,
+                                      long long a_col, int a_term, int b_term, BAt b_at) {
+    const int lane = threadIdx.x & 63, w = wave(), sub = w % WPC;
+    // columns past the end have an empty range: they load as zeros
+    auto load_stage = [&](int buf, int c0) {
+      unsigned char* As = smem + buf * STAGE;
+      unsigned char* Bs = As + SLOTS * BM * kGran;
+#pragma unroll
+      for (int v = 0; v < CPW; ++v) {
+        const int cc = w / WPC + v * NW;
+        const int col = c0 + cc, cl = min(col, c_end - 1), range = col < c_end ? 0x7fffffff : 0;
+        const __amdgpu_buffer_rsrc_t ra =
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(A + cl * a_col), 0, range, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rb =
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(b_at(cl)), 0, range, 0x00020000);
+#pragma unroll
+        for (int k = 0; k < TERMS; ++k)
+#pragma unroll
+          for (int u = 0; u < B_PARTS; ++u)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                rb, (lds_ptr)(Bs + ((cc * TERMS + k) * BN + (sub * B_PARTS + u) * 64) * kGran), 16, (int)b_voff[u],
+                k * b_term, 0, 0);
+#pragma unroll
+        for (int k = 0; k < TERMS; ++k)
+#pragma unroll
+          for (int u = 0; u < A_PARTS; ++u)  // the first A_PER units are the first wave's
+            if (WPC == 1 || (k * A_PARTS + u) / A_PER == sub)
+              __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_ptr)(As + ((cc * TERMS + k) * BM + u * 64) * kGran),
+                                                       16, (int)a_voff[u], k * a_term, 0, 0);
+      }
+    };
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          acc[i][j][r] = 0.f;
+          if constexpr (TERMS == 3) acc_c[i][j][r] = 0.f;
+        }
+
+    const int stages = (c_end - c_begin + NCOL - 1) / NCOL;  // <= 0 for an empty range
+    if (stages > 0) load_stage(0, c_begin);
+    const int lo = lane & 31, hi = lane >> 5;
+    const int a_lds = (hi * TERMS * BM + w / WAVES_N * 64 + lo) * kGran;
+    const int b_lds = SLOTS * BM * kGran + (hi * TERMS * BN + w % WAVES_N * 64 + lo) * kGran;
+    for (int t = 0; t < stages; ++t) {
+      // this stage's loads have landed and nobody reads the other buffer any more
+      __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+      __syncthreads();
+      if (t + 1 < stages) load_stage((t + 1) & 1, c_begin + (t + 1) * NCOL);
+      const unsigned char* st = smem + (t & 1) * STAGE;
+#pragma unroll
+      for (int kb = 0; kb < NCOL / 2; ++kb) {
+        bf16x8 a[2][TERMS], b[2][TERMS];
+#pragma unroll
+        for (int k = 0; k < TERMS; ++k)
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            a[i][k] = *reinterpret_cast<const bf16x8*>(st + a_lds + ((2 * kb * TERMS + k) * BM + i * 32) * kGran);
+            b[i][k] = *reinterpret_cast<const bf16x8*>(st + b_lds + ((2 * kb * TERMS + k) * BN + i * 32) * kGran);
+          }
+#define CCT_M(X, Y, ACC)                                                                    \
+  _Pragma("unroll") for (int i = 0; i < 2; ++i) _Pragma("unroll") for (int j = 0; j < 2; ++j) \
+      ACC[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][X], b[j][Y], ACC[i][j], 0, 0, 0)
+        if constexpr (TERMS == 3) {
+          CCT_M(0, 0, acc);
+          CCT_M(0, 1, acc_c);
+          CCT_M(1, 0, acc_c);
+          CCT_M(1, 1, acc_c);
+          CCT_M(0, 2, acc_c);
+          CCT_M(2, 0, acc_c);
+        } else {
+          CCT_M(0, 0, acc);
+        }
+#undef CCT_M
+      }
+    }
+  }
+
+  // f(row, column, value) for every result of the lane, relative to the workgroup's tile
+  template <class F>
+  __device__ __forceinline__ void for_each(F f) const {
+    const int lane = threadIdx.x & 63, w = wave();
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          float v = acc[i][j][r];
+          if constexpr (TERMS == 3) v += acc_c[i][j][r];
+          f(w / WAVES_N * 64 + i * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3),
+            w % WAVES_N * 64 + j * 32 + (lane & 31), v);
+        }
+  }
+};
+
+}  // namespace
+}  // namespace cct
