@@ -445,7 +445,7 @@ int launch_bwdw_img(const cct_conv_desc_t& d, const BwdwImgPlan& P, int nimg, co
   if (blocks <= 0 || blocks >= 2147483647LL || d.groups > 65535) return CCT_EUNSUPPORTED;
   {
     char name[96];
-    snprintf(name, sizeof(name), "conv_bwdw_img<%d, %d>", P.BM, P.terms);
+    snprintf(name, sizeof(name), "conv_bwdw_img<%d, %d, %d>", P.BM, P.terms, P.terms == 1 ? 8 : P.BM == 128 ? 12 : 6);
     ProfScope ps(name, 2.0 * yn * Cg * KK, 2.0 * P.terms * (xn + yn) + 4.0 * q.S * (double)d.O * q.N, st);
     const dim3 grid((unsigned)blocks, (unsigned)d.groups);
     int rc;

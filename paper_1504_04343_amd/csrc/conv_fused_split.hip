@@ -614,7 +614,7 @@ int launch_variant(const GemmTN& p, const KcGeom& fg, size_t lds, hipStream_t st
   if (blocks <= 0 || blocks >= 2147483647LL || p.G > 65535) return CCT_EUNSUPPORTED;
   dim3 grid((unsigned)blocks, (unsigned)p.G);
   char name[96];
-  snprintf(name, sizeof(name), "conv_fused_split<%d, %d, %d>%s", BM, KT, S, p.d2s ? " strided" : "");
+  snprintf(name, sizeof(name), "conv_fused_split<%d, %d, %d>%s", WAVES_M, KT, S, p.d2s ? " strided" : "");
   const double nimg = (double)p.Ncols / (p.gHout * p.gWout);
   const double x_bytes = 4.0 * nimg * p.x_img;
   const double y_bytes = p.d2s ? 4.0 * nimg * p.dCtot * p.dH * p.dW : 4.0 * (double)p.M * p.Ncols * p.G;
