@@ -290,6 +290,33 @@ __global__ __launch_bounds__(NT, 2) void conv_fused_split(GemmTN p, KcGeom fg, i
   for (int j = 0; j < WN; ++j)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc_h[j][r] = acc_c[j][r] = 0.f;
+  // The h*h chain rounds once per tile.  Waves of up to 64 columns have the registers to break it every 36
+  // tiles or so, which keeps the error of small layers below that of the lowered layouts (their sums come in
+  // K or K*K parts: 11 images of 27 x 27, two groups of 128 -> 48 channels, K = 5: 2-norm 2.2e-7 there,
+  // 3.4e-7 with one chain, 1.2e-7 with parts; the time is the same within 1 %).  Against one fp32 chain a single one is a third of the error already.
+  constexpr bool PARTS = WN <= 2;
+  floatx16 total[PARTS ? WN : 1];
+  const int part = max(1, 36 / tpg);  // channel groups
+  int left = part;
+  if constexpr (PARTS) {
+#pragma unroll
+    for (int j = 0; j < WN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) total[j][r] = 0.f;
+  }
+  auto end_group = [&]() {
+    if constexpr (PARTS) {
+      if (--left > 0) return;
+      left = part;
+#pragma unroll
+      for (int j = 0; j < WN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          total[j][r] += acc_h[j][r];
+          acc_h[j][r] = 0.f;
+        }
+    }
+  };
 
   // per-lane byte offset of each owned position's cell
   const int bn = wave_n * WN * MB + lane_lo;
@@ -382,6 +409,7 @@ __global__ __launch_bounds__(NT, 2) void conv_fused_split(GemmTN p, KcGeom fg, i
         tile(tt % AD, grp * KK + tt, base + (ti * fg.Wp + tj) * CB,
              last ? (more ? other : base) : base + (ni * fg.Wp + nj) * CB, last && more);
       }
+      end_group();
       if (more) slot ^= 1;
     }
   } else {
@@ -436,6 +464,7 @@ __global__ __launch_bounds__(NT, 2) void conv_fused_split(GemmTN p, KcGeom fg, i
           ++t;
         }
       }
+      end_group();
       if (more) slot ^= 1;
     }
   }
@@ -449,6 +478,7 @@ __global__ __launch_bounds__(NT, 2) void conv_fused_split(GemmTN p, KcGeom fg, i
   for (int j = 0; j < WN; ++j)
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
+      if constexpr (PARTS) acc_h[j][r] += total[j][r];
       acc_h[j][r] += acc_c[j][r];
       bad |= acc_h[j][r] != acc_h[j][r];
     }

@@ -92,6 +92,21 @@ def test_precision(B):
     assert np.linalg.norm(got - want) / np.linalg.norm(want) <= 4e-7
 
 
+@pytest.mark.parametrize("L", [layer("p32", 11, 96, 27, 27, 256, 5, 1, 2, 2), layer("p64", 49, 384, 13, 13, 256, 3, 1, 1, 2),
+                               layer("p_k7", 6, 80, 28, 28, 352, 7, 2, 3)], ids=lambda L: L.name)
+def test_precision_of_small_layers(B, L):
+    """32- and 64-row tiles sum the contraction in parts of about 36 roundings.  The error of a part is a random
+    walk, 2^-24 / sqrt(3) * sqrt(36 / 2) = 1.5e-7 of the part's sum, and falls with the root of the number of
+    parts; as one chain of 200 to 350 roundings these come out at 2e-7 to 4e-7."""
+    rng = np.random.default_rng(7)
+    w = rng.standard_normal((L.O, L.C // L.groups, L.K, L.K), dtype=np.float32)
+    dy = rng.standard_normal((L.N, L.O, L.Hout, L.Wout), dtype=np.float32)
+    got, names = ran(B, lambda: gpu_backward_data(B, L, w, dy, B.LOWER_FUSED))
+    assert any(n.startswith((KERNEL + "<1", KERNEL + "<2")) for n in names), names
+    want = oracle.conv_backward_data(odims(oracle, L), w, dy)
+    assert np.linalg.norm(got.astype(np.float64) - want) / np.linalg.norm(want) <= 1.5e-7
+
+
 SPECIAL = [("plain", layer("nf", 3, 16, 13, 13, 40, 3, 1, 1)),
            ("s2d", layer("nf2", 3, 3, 31, 31, 40, 7, 4, 0)),
            ("zero_tile", layer("nf7", 2, 16, 13, 13, 40, 7, 1, 3))]
