@@ -226,10 +226,10 @@ __global__ __launch_bounds__(256) void bwdw_img_reduce(ImgReduce p) {
   }
   // a workgroup takes 256 weights, or 64 with a quarter of the splits per wave
   const int wid = p.strips == 4 ? tid & 63 : tid, strip = p.strips == 4 ? tid >> 6 : 0;
-  const long long per = (long long)p.M * p.N, total = per * p.G;
-  const long long t = (long long)blockIdx.x * (256 / p.strips) + wid;
+  const long long total = (long long)p.M * p.N * p.G;
+  const long long t0 = (long long)blockIdx.x * (256 / p.strips), t = t0 + wid;
   float sum = 0.f;
-  int g = 0, m = 0, ci = 0, tap = 0;
+  int o = 0, ci = 0, tap = 0;
   long long wi = 0;
   if (t < total) {
     const float* src = p.part + t;
@@ -243,15 +243,16 @@ __global__ __launch_bounds__(256) void bwdw_img_reduce(ImgReduce p) {
       for (int u = 0; u < 8; ++u) sum += v[u];
     }
     for (; k < end; ++k) sum += src[k * total];
-    g = (int)(t / per);
-    const int e = (int)(t - g * per);
-    m = e / p.N;
-    const int n = e - m * p.N;
+    // A group may hold more than 2^31 weights: the workgroup's first row (of all groups) in 64 bits, the
+    // rest from there.
+    const long long row0 = t0 / p.N;
+    const int n0 = (int)(t0 - row0 * p.N) + wid, rows = n0 / p.N, n = n0 - rows * p.N;
+    o = (int)row0 + rows;
     const int cb = n / (p.KK * kChanBlock), width = min(kChanBlock, p.Cg - cb * kChanBlock);
     const int rem = n - cb * p.KK * kChanBlock;
     tap = rem / width;
     ci = cb * kChanBlock + rem - tap * width;
-    wi = ((long long)(g * p.Og + m) * p.Cg + ci) * p.KK + tap;
+    wi = ((long long)o * p.Cg + ci) * p.KK + tap;
   }
   if (p.strips == 4) {
     red[tid] = sum;
@@ -273,8 +274,8 @@ __global__ __launch_bounds__(256) void bwdw_img_reduce(ImgReduce p) {
       for (int who = 0; who < 256; ++who) {
         if (!redo[who]) continue;  // the same for all threads
         if (tid == who) {
-          key[0] = g * p.Og + m;
-          key[1] = g * p.Cg + ci;
+          key[0] = o;
+          key[1] = o / p.Og * p.Cg + ci;
           key[2] = tap;
         }
         __syncthreads();

@@ -95,3 +95,26 @@ def test_not_finite_inputs(B):
     big = ok & (np.abs(want) > 1e30)
     assert (np.abs(got[big] - want[big]) <= 1e-5 * np.abs(want[big])).all()
     assert rel_err(got[ok & ~big], want[ok & ~big]) <= TOL_F32
+
+
+def test_more_weights_than_31_bits_count(B):
+    """2.4e9 weights in one group: an index that passes through 32 bits turns negative from row 14564 on.
+    Rows on both sides of it against 64-bit sums, and the floats in front of dw stay as they were."""
+    import torch
+    N, C, H, O, K = 32, 16384, 5, 16384, 3
+    assert O * C * K * K > 2 ** 31
+    rng = np.random.default_rng(9)
+    x = rng.standard_normal((N, C, H, H), dtype=np.float32)
+    dy = rng.standard_normal((N, O, H - K + 1, H - K + 1), dtype=np.float32)
+    d = B.make_desc(N, C, H, H, O, K)
+    ws = B.alloc_workspace(d, B.PASS_BACKWARD_WEIGHTS, N)
+    front = 1 << 16
+    buf = torch.full((front + O * C * K * K,), 7.0, device="cuda")
+    dw = buf[front:].view(O, C, K, K)
+    _, names = ran(B, lambda: (B.cct_conv_backward_weights(d, dev(x), dev(dy), dw, None, ws), torch.cuda.synchronize()))
+    assert any(n.startswith(KERNEL) for n in names), names
+    assert bool((buf[:front] == 7.0).all())
+    rows = [0, 1, 14563, 14564, O - 1]
+    win = np.lib.stride_tricks.sliding_window_view(x, (K, K), (2, 3)).astype(np.float64)   # [N][C][r][c][K][K]
+    want = np.tensordot(dy[:, rows].astype(np.float64), win, ((0, 2, 3), (0, 2, 3)))       # [rows][C][K][K]
+    assert rel_err(dw[rows].cpu().numpy(), want) <= TOL_F32
