@@ -252,6 +252,22 @@ bool use_split(const cct_conv_desc_t& d, int pass, const Geom& g, SplitPlan* sp)
 
 inline int esize(const cct_conv_desc_t& d) { return d.precision == CCT_PREC_BF16_IN_F32_ACC ? 2 : 4; }
 
+// Can the channel-contiguous kernels run the strided backward-data pass (U x U sub-kernels)?  Sets the padding
+// of their pack.
+bool strided_kc_fits(const cct_conv_desc_t& d, const Geom& g, int* Mpad, int* Kpad_kc) {
+  const bool bf16 = d.precision == CCT_PREC_BF16_IN_F32_ACC;
+  const StridedBwd sb = strided_bwd(d, g);
+  if ((long long)g.Cg * d.stride * d.stride >= kIntMax || (long long)sb.Ah * sb.Aw >= kIntMax) return false;
+  int BM, BN, BK;
+  gemm_tn_tile(sb.M, sb.Ah * sb.Aw, &BM, &BN, &BK);
+  const long long kc = conv_fused_kc_kpad(g.Og, sb.U, bf16);
+  if (kc >= kIntMax) return false;
+  *Mpad = bf16 ? conv_fused_kc_bf16_mpad(sb.M) : (int)align_up(sb.M, BM);
+  *Kpad_kc = (int)kc;
+  const GemmTN p = strided_bwd_problem(d, g, nullptr, *Mpad, *Kpad_kc, nullptr, nullptr, 1);
+  return bf16 ? conv_fused_kc_bf16_fits(p) : conv_fused_kc_fits(p);
+}
+
 // Workspace layout of one pass for a given chunk size.
 struct Layout {
   long long pack_off = 0, pack_bytes = 0;
@@ -433,17 +449,12 @@ bool make_layout(const cct_conv_desc_t& d, int pass, int type, const Geom& g, lo
       if (type != CCT_LOWER_TYPE1) take(rt_rows * L->ld * 4, &L->rt_off, &L->rt_bytes);
     }
   } else if (pass == CCT_PASS_BACKWARD_DATA && type == CCT_LOWER_FUSED && d.stride > 1) {
-    // a stride-1 convolution of dy with s*s sub-kernels of U x U taps: M = Cg*s*s, K dim = Og*U*U
+    // a stride-1 convolution of dy with s*s sub-kernels of U x U taps: M = Cg*s*s, K dim = Og*U*U.  A workspace
+    // without room for the split pack does not change what these kernels can stage.
     const StridedBwd sb = strided_bwd(d, g);
-    if (nc * sb.Ah * sb.Aw >= kIntMax - 256 || (long long)g.Cg * d.stride * d.stride >= kIntMax)
-      return false;
-    int BM, BN, BK;
-    gemm_tn_tile(sb.M, (int)(nc * sb.Ah * sb.Aw), &BM, &BN, &BK);
-    L->Mpad = es == 2 ? conv_fused_kc_bf16_mpad(sb.M) : (int)align_up(sb.M, BM);
-    const long long kc = conv_fused_kc_kpad(g.Og, sb.U, es == 2);
-    if (kc >= kIntMax) return false;
-    L->Kpad = L->Kpad_kc = (int)kc;
-    take((long long)d.groups * L->Mpad * kc * 4, &L->pack_off, &L->pack_bytes);
+    if (nc * sb.Ah * sb.Aw >= kIntMax - 256 || !strided_kc_fits(d, g, &L->Mpad, &L->Kpad_kc)) return false;
+    L->Kpad = L->Kpad_kc;
+    take((long long)d.groups * L->Mpad * L->Kpad_kc * 4, &L->pack_off, &L->pack_bytes);
   } else if (pass == CCT_PASS_BACKWARD_DATA && type == CCT_LOWER_FUSED) {
     // a stride-1 convolution of dy with the flipped kernels: M = Cg, K dim = Og*K*K
     if (nc * d.H * d.W >= kIntMax - 256) return false;
@@ -537,18 +548,10 @@ bool type_supported(const cct_conv_desc_t& d, int pass, int type) {
         return false;
     }
     SplitPlan sp;
-    if (pass == CCT_PASS_BACKWARD_DATA && d.stride > 1 && !split_plan(d, pass, gg, &sp)) {
-      const StridedBwd sb = strided_bwd(d, gg);
-      if ((long long)gg.Cg * d.stride * d.stride >= kIntMax || (long long)sb.Ah * sb.Aw >= kIntMax)
-        return false;
-      int BM, BN, BK;
-      gemm_tn_tile(sb.M, sb.Ah * sb.Aw, &BM, &BN, &BK);
-      const long long kc = conv_fused_kc_kpad(gg.Og, sb.U, bf16);
-      if (kc >= kIntMax) return false;
-      const int mpad = bf16 ? conv_fused_kc_bf16_mpad(sb.M) : (int)align_up(sb.M, BM);
-      const GemmTN p = strided_bwd_problem(d, gg, nullptr, mpad, (int)kc, nullptr, nullptr, 1);
-      if (!(bf16 ? conv_fused_kc_bf16_fits(p) : conv_fused_kc_fits(p))) return false;
-    }
+    int mpad, kpad;
+    if (pass == CCT_PASS_BACKWARD_DATA && d.stride > 1 && !split_plan(d, pass, gg, &sp) &&
+        !strided_kc_fits(d, gg, &mpad, &kpad))
+      return false;
     if ((long long)d.C * d.H * d.W >= kIntMax) return false;  // 32-bit offsets inside one image
   }
   const Geom g = make_geom(d, type);

@@ -287,3 +287,22 @@ def test_fully_connected_layers_are_planned_as_matrix_products(B):
                B.make_desc(N, 3, 5, 5, O, 5)):
         Fg = (dd.C // dd.groups) * dd.K * dd.K
         assert B.cct_conv_workspace_bytes(dd, B.PASS_FORWARD) >= 2 * dd.O * Fg
+
+
+def backward_data_code(B, d, nbytes):
+    """Return code of a backward-data call with that much workspace and addresses that are never read: a
+    refusal comes before the first launch."""
+    lib = ctypes.CDLL(B.LIB_PATH)
+    fake = ctypes.c_void_p(0x10000)
+    return lib.cct_conv_backward_data(ctypes.byref(d), fake, fake, fake, fake, ctypes.c_size_t(nbytes), None)
+
+
+@pytest.mark.parametrize("layer", [(4, 32, 27, 27, 40, 3, 2, 1), (4, 10, 21, 21, 40, 5, 3, 2), (4, 64, 27, 27, 40, 5, 2, 2)])
+def test_strided_fused_backward_data_needs_room_for_the_only_kernel_that_runs_it(B, layer):
+    """40 kernels are padded to 48 channels, which only the split kernel takes: below its pack there is no
+    fused kernel, so the call is refused on the host instead of failing at its launch."""
+    d = B.make_desc(*layer, lowering=B.LOWER_FUSED)
+    need = B.cct_conv_workspace_bytes_for_chunk(d, B.PASS_BACKWARD_DATA, 1)
+    assert need == B.cct_conv_workspace_bytes(d, B.PASS_BACKWARD_DATA)
+    for nbytes in (need - 256, need * 4 // 5 // 256 * 256):
+        assert backward_data_code(B, d, nbytes) == B.EWORKSPACE
