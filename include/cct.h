@@ -143,6 +143,8 @@ int cct_lowering_cost(const cct_conv_desc_t* desc, cct_pass_t pass, cct_lowering
  * to process `images_per_chunk` images (1..N) at a time.  Any workspace at least as large
  * as the 1-image size is accepted by cct_conv_*; a larger one means larger chunks, up to
  * the whole batch.  desc->lowering == AUTO is resolved with cct_pick_lowering.  Host only.
+ * A call with AUTO and less than the recommended size runs the layout that the cost model expects to be
+ * fastest in the workspace it was given, of any type: CCT_EWORKSPACE means that no layout holds one image.
  *
  * Fully connected layers (K == H == W, pad 0, groups 1, fp32, lowering AUTO or TYPE1: one output
  * pixel per image, the m = 1 case of Sec. 2.1 where every lowering is a reshape of x) run as plain
@@ -177,8 +179,8 @@ int cct_conv_forward(const cct_conv_desc_t* desc, const float* x, const float* w
  * ends).  The call allocates and
  * frees nothing, on the host side it only looks up that array's device address the first time it
  * runs on a device.  The batch is processed in chunks of as many images as fit the array;
- * CCT_ESCRATCH (nothing enqueued) if the buffers of a single image do not fit, which can only
- * happen with a materialised layout (the fused layout AUTO prefers needs the packed kernels only).
+ * CCT_ESCRATCH (nothing enqueued) if the buffers of a single image do not fit: with a materialised
+ * layout, or where the packed kernels alone exceed the array (AUTO runs any layout that fits).
  * All calls on one GPU share the array, which keeps the previous call's contents (every kernel
  * writes what it later reads, nothing needs to start at zero): calls that may overlap in time on
  * the same GPU, e.g. on two streams, race and must be serialised by the caller.
@@ -209,8 +211,8 @@ int cct_conv_backward_data(const cct_conv_desc_t* desc, const float* w, const fl
  * Computed as D^ transposed times the inverse-lifted dy, reduced over all rows of the
  * batched lowered matrix in fixed order (bit-reproducible run to run).  With lowering AUTO (any
  * precision) or FUSED, larger layers run on copies of x and dy in the workspace that are
- * regrouped by image (8 images of a pixel side by side), never on a lowered matrix; a workspace
- * without room for the copies of 32 images runs the picked layout.
+ * regrouped by image (8 images of a pixel side by side), never on a lowered matrix; with less than the
+ * recommended workspace only where chunks of the images that fit, at least 32, are still worth it.
  * x, dy: device, read.  dw: device, written.  dbias: device, O floats, may be NULL.
  */
 int cct_conv_backward_weights(const cct_conv_desc_t* desc, const float* x, const float* dy,

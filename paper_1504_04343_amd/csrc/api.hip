@@ -298,10 +298,17 @@ constexpr int kImgLeastChunk = 32;
 
 double layout_cost(const cct_conv_desc_t& d, int pass, int type);
 
+// What an estimate of a layout without granules stands for: in bf16 it is 40 % (backward-weights) or a fifth
+// short of what the kernels take, and in fp32 it leaves out the bias gradient's pass over dy.
+double plain_seconds(const cct_conv_desc_t& d, int pass, const Geom& g, double cost) {
+  const bool bwdw = pass == CCT_PASS_BACKWARD_WEIGHTS;
+  if (d.precision != CCT_PREC_F32) return (bwdw ? 1.4 : 1.2) * cost;
+  return bwdw ? cost + 4.0 * d.N * d.O * g.Hout * g.Wout / 4.0e12 + 4.0e-6 : cost;
+}
+
 // Backward-weights on granules of 8 images (conv_bwdw_img.hip): what AUTO runs where the estimates say
 // that rewriting x and dy once pays (they are re-read as often as the product has tiles), and how FUSED
-// computes fp32 layers by the same rule.  The other estimates leave out the bias gradient's pass over
-// dy; in bf16 they are 40 % short of what the materialised layouts take.  Measured over 500 layers of 1 to 1024 images: up to 2.9 times as fast where it
+// computes fp32 layers by the same rule.  Measured over 500 layers of 1 to 1024 images: up to 2.9 times as fast where it
 // is chosen (conv3 at batch 1024: 2880 -> 1590 us), at most 15 % slower for single calls under 40 us;
 // it stays off for a single image (conv3: 31 us against 38), 3 channels (conv1 at batch 256: 697 us
 // against 997) and 1 x 1 kernels at stride 2 (they use a quarter of the x that would be rewritten).
@@ -309,13 +316,12 @@ bool bwdw_img_wins(const cct_conv_desc_t& d, int type) {
   if (d.lowering != CCT_LOWER_AUTO && !(type == CCT_LOWER_FUSED && d.precision == CCT_PREC_F32)) return false;
   BwdwImgPlan p;
   if (!bwdw_img_plan(d, d.N, &p)) return false;
-  const double cost = layout_cost(d, CCT_PASS_BACKWARD_WEIGHTS, type);
-  if (d.precision != CCT_PREC_F32) return p.seconds < 1.4 * cost;
   const Geom g = make_geom(d, CCT_LOWER_TYPE1);
+  const double cost = layout_cost(d, CCT_PASS_BACKWARD_WEIGHTS, type);
   // few kernels: Types 2 and 3, which take the taps into the rows, are better than their estimates
   // (53 images of 41 x 41, two groups of 171 channels and 19 kernels: 259 us against 294)
-  if (2 * g.Og < p.BM) return p.seconds < 0.85 * cost;
-  return p.seconds < cost + 4.0 * d.N * d.O * g.Hout * g.Wout / 4.0e12 + 4.0e-6;
+  if (d.precision == CCT_PREC_F32 && 2 * g.Og < p.BM) return p.seconds < 0.85 * cost;
+  return p.seconds < plain_seconds(d, CCT_PASS_BACKWARD_WEIGHTS, g, cost);
 }
 
 // 1 x 1 kernels at stride 1 without padding: every lowering is the identity, so the forward and
@@ -377,13 +383,14 @@ bool tensor_split(const cct_conv_desc_t& d, int pass, int type, const Geom& g, l
 }
 
 // Forward / backward-data in bf16 on granules of 8 channels (conv_granules.hip): what AUTO runs where the
-// estimates say that rewriting the tensor once pays; those of the other layouts are a fifth short.  Measured
+// estimates say that rewriting the tensor once pays.  Measured
 // over 60 layers: 1.05 to 2.8 times as fast where it is chosen; up to about ten images of 13 x 13 the
 // contraction of a lone workgroup is the longer way (256 -> 384 channels, 9 images: 42 us against 53).
 bool granules_win(const cct_conv_desc_t& d, int pass, int type) {
   if (d.lowering != CCT_LOWER_AUTO || d.precision != CCT_PREC_BF16_IN_F32_ACC) return false;
   GranulesPlan p;
-  return granules_plan(d, pass, d.N, &p) && p.seconds < 1.2 * layout_cost(d, pass, type);
+  return granules_plan(d, pass, d.N, &p) &&
+         p.seconds < plain_seconds(d, pass, make_geom(d, type), layout_cost(d, pass, type));
 }
 
 // allow_split = false: without conv_fused_split, whose pack takes half as much again as the fp32 one,
@@ -766,14 +773,13 @@ long long default_chunk(const cct_conv_desc_t& d, int pass, int type, const Geom
 
 // Largest chunk whose layout fits `bytes`; 0 if not even one image fits.
 long long chunk_for_workspace(const cct_conv_desc_t& d, int pass, int type, const Geom& g,
-                              size_t bytes, Layout* L) {
-  bool split = true;
+                              size_t bytes, Layout* L, bool split = true) {
   auto fits = [&](long long nc) {
     return make_layout(d, pass, type, g, nc, L, split) && (unsigned long long)L->total <= bytes;
   };
   // a workspace too small for the split kernel matrix still holds the fp32 one; granules need chunks of
   // some size
-  const bool granules = pass == CCT_PASS_BACKWARD_WEIGHTS || d.precision != CCT_PREC_F32;
+  const bool granules = split && (pass == CCT_PASS_BACKWARD_WEIGHTS || d.precision != CCT_PREC_F32);
   long long lo = granules ? std::min(d.N, kImgLeastChunk) : 1, hi = d.N;
   if (!fits(lo)) {
     split = false;
@@ -787,6 +793,64 @@ long long chunk_for_workspace(const cct_conv_desc_t& d, int pass, int type, cons
   }
   fits(lo);
   return lo;
+}
+
+// The bf16 fused kernel, for which kernel_cost's fp32 rate is no measure: 500 TFLOP/s of padded rows and the
+// chain of a workgroup's channel groups (backward-data of conv4 at 124 / 212 / 256 images 86 / 125 / 157 us).
+double fused_bf16_seconds(const cct_conv_desc_t& d, int pass, const Geom& g) {
+  const StridedBwd sb = strided_bwd(d, g);
+  const bool fwd = pass == CCT_PASS_FORWARD, strided = !fwd && d.stride > 1;
+  const double cols = (double)d.N * (fwd ? (double)g.Hout * g.Wout : strided ? (double)sb.Ah * sb.Aw : (double)d.H * d.W);
+  const int rows = fwd ? g.Og : strided ? sb.M : g.Cg, taps = strided ? sb.U * sb.U : d.K * d.K;
+  const int groups = ((fwd ? g.Cg : g.Og) + 15) / 16;
+  return 2.0 * cols * conv_fused_kc_bf16_mpad(rows) * groups * 16.0 * taps * d.groups / 500.0e12 + groups * 2.5e-6 +
+         2.0 * kLaunchSec;
+}
+
+// Estimated time of the whole batch in chunks of nc images on layout L.
+double chunked_seconds(const cct_conv_desc_t& d, int pass, int type, const Geom& g, const Layout& L, long long nc) {
+  cct_conv_desc_t c = d;
+  c.N = (int)nc;
+  double one;
+  BwdwImgPlan ip;
+  if (L.gran) one = L.gp.seconds;
+  else if (L.img) one = bwdw_img_plan(c, nc, &ip) ? ip.seconds : 1.0;
+  else if (L.split) one = split_cost(c, pass, g, L.sp);
+  else if (type == CCT_LOWER_FUSED && d.precision != CCT_PREC_F32) one = fused_bf16_seconds(c, pass, g);
+  else one = plain_seconds(c, pass, g, kernel_cost(c, pass, type));
+  return (double)((d.N + nc - 1) / nc) * one;
+}
+
+// The layout of a call that is given `bytes` of workspace: the picked one (*type, *g) where it holds as many
+// images as its recommended workspace does.  With less, launches repeat per chunk: the layout with the shortest
+// estimate among those that fit, without the granules and, for AUTO, of any type (128 -> 32 channels, 3 x 3,
+// 232 images of 55 x 55 picks Type 3 with 3.8 MB an image; 300 KB hold the fused layout of the whole batch).
+// Returns the images per chunk, 0 if no layout fits.
+long long layout_for_workspace(const cct_conv_desc_t& d, int pass, size_t bytes, int* type, Geom* g, Layout* L) {
+  long long nc = chunk_for_workspace(d, pass, *type, *g, bytes, L);
+  if (nc == d.N || (nc > 0 && nc >= default_chunk(d, pass, *type, *g))) return nc;
+  double best = nc > 0 ? chunked_seconds(d, pass, *type, *g, *L, nc) : 0.0;
+  auto consider = [&](int t, const Geom& tg, bool split) {
+    Layout tl;
+    const long long n = chunk_for_workspace(d, pass, t, tg, bytes, &tl, split);
+    if (n < 1) return;
+    const double s = chunked_seconds(d, pass, t, tg, tl, n);
+    if (nc < 1 || s < best) {
+      best = s;
+      nc = n;
+      *type = t;
+      *g = tg;
+      *L = tl;
+    }
+  };
+  const int picked = *type;
+  for (int t = CCT_LOWER_TYPE1; t <= CCT_LOWER_FUSED; ++t) {
+    if (t != picked && (d.lowering != CCT_LOWER_AUTO || !type_supported(d, pass, t))) continue;
+    const Geom tg = make_geom(d, t);
+    if (t != picked) consider(t, tg, true);
+    consider(t, tg, false);
+  }
+  return nc;
 }
 
 PackDesc make_pack(const cct_conv_desc_t& d, const Geom& g, const Layout& L, int transposed) {
@@ -1054,7 +1118,7 @@ int forward_on_workspace(const cct_conv_desc_t* desc, const float* x, const floa
   const bool fc = fc_plan(d, CCT_PASS_FORWARD, ws_cap(workspace_bytes), &fp);
   Layout L;
   const long long nc =
-      fc ? d.N : chunk_for_workspace(d, CCT_PASS_FORWARD, type, g, workspace_bytes, &L);
+      fc ? d.N : layout_for_workspace(d, CCT_PASS_FORWARD, workspace_bytes, &type, &g, &L);
   if (nc < 1) return static_scratch ? CCT_ESCRATCH : CCT_EWORKSPACE;
   if (static_scratch) {
     rc = scratch_address(&workspace);
@@ -1182,7 +1246,7 @@ int cct_conv_backward_data(const cct_conv_desc_t* desc, const float* w, const fl
   if (fc_plan(d, CCT_PASS_BACKWARD_DATA, ws_cap(workspace_bytes), &fp))
     return fc_backward_data(d, fp, w, dy, dx, static_cast<char*>(workspace), (hipStream_t)hip_stream);
   Layout L;
-  const long long nc = chunk_for_workspace(d, CCT_PASS_BACKWARD_DATA, type, g, workspace_bytes, &L);
+  const long long nc = layout_for_workspace(d, CCT_PASS_BACKWARD_DATA, workspace_bytes, &type, &g, &L);
   if (nc < 1) return CCT_EWORKSPACE;
   hipStream_t st = (hipStream_t)hip_stream;
   char* ws = static_cast<char*>(workspace);
@@ -1323,7 +1387,7 @@ int cct_conv_backward_weights(const cct_conv_desc_t* desc, const float* x, const
                                (hipStream_t)hip_stream);
   Layout L;
   const long long nc =
-      chunk_for_workspace(d, CCT_PASS_BACKWARD_WEIGHTS, type, g, workspace_bytes, &L);
+      layout_for_workspace(d, CCT_PASS_BACKWARD_WEIGHTS, workspace_bytes, &type, &g, &L);
   if (nc < 1) return CCT_EWORKSPACE;
   hipStream_t st = (hipStream_t)hip_stream;
   char* ws = static_cast<char*>(workspace);
