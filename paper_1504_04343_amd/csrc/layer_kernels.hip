@@ -352,11 +352,13 @@ inline unsigned stream_blocks(long long work_items) {
 // ---- local response normalisation -------------------------------------------------------------
 struct LrnGeom {
   int C;
+  unsigned segments;     // of the channels, one per thread and grid row
   long long hw, pixels;  // H*W, N*H*W
   float a, beta, k, coef;  // alpha/size; 2*alpha*beta/size
 };
 
 constexpr long long kLrnThreads = 1 << 18;
+constexpr unsigned kMaxGridRows = 65535;
 
 // s^-beta.  P34: beta = 3/4 (Caffe's default), where Newton's step for z^4 s^3 = 1 makes a result good to
 // half a unit in the last place out of the hardware's approximate exponential and logarithm: with the
@@ -383,20 +385,23 @@ __global__ __launch_bounds__(TPB) void lrn_forward_kernel(const float* __restric
   const long long n = t / g.hw, pix = t - n * g.hw;
   const float* xp = x + n * g.C * g.hw + pix;  // channel c of this pixel is xp[c*hw]
   float* yp = y + n * g.C * g.hw + pix;
-  const int c0 = blockIdx.y * CS;
-  float xs[CS + 2 * HALF];  // x of channels c0-HALF ..
+  // one turn unless there are more segments than a grid has rows
+  for (unsigned seg = blockIdx.y; seg < g.segments; seg += gridDim.y) {
+    const int c0 = (int)(seg * CS);
+    float xs[CS + 2 * HALF];  // x of channels c0-HALF ..
 #pragma unroll
-  for (int i = 0; i < CS + 2 * HALF; ++i) {
-    const int ch = c0 + i - HALF;
-    xs[i] = (ch >= 0 && ch < g.C) ? xp[ch * g.hw] : 0.f;
-  }
+    for (int i = 0; i < CS + 2 * HALF; ++i) {
+      const int ch = c0 + i - HALF;
+      xs[i] = (ch >= 0 && ch < g.C) ? xp[ch * g.hw] : 0.f;
+    }
 #pragma unroll
-  for (int i = 0; i < CS; ++i) {
-    if (c0 + i >= g.C) break;
-    float sum = 0.f;
+    for (int i = 0; i < CS; ++i) {
+      if (c0 + i >= g.C) break;
+      float sum = 0.f;
 #pragma unroll
-    for (int k = 0; k < SIZE; ++k) sum += xs[i + k] * xs[i + k];
-    yp[(c0 + i) * g.hw] = xs[i + HALF] * neg_power<P34>(g.k + g.a * sum, g.beta);
+      for (int k = 0; k < SIZE; ++k) sum += xs[i + k] * xs[i + k];
+      yp[(c0 + i) * g.hw] = xs[i + HALF] * neg_power<P34>(g.k + g.a * sum, g.beta);
+    }
   }
 }
 
@@ -412,41 +417,43 @@ __global__ __launch_bounds__(TPB) void lrn_backward_kernel(const float* __restri
   const float* xp = x + n * g.C * g.hw + pix;
   const float* gp = dy + n * g.C * g.hw + pix;
   float* op = dx + n * g.C * g.hw + pix;
-  const int c0 = blockIdx.y * CS;
-  float xs[CS + 4 * HALF];  // x of channels c0-2*HALF ..
-  float gs[CS + 2 * HALF];  // dy of channels c0-HALF .., then the direct terms dy*scale^-beta
-  float tr[CS + 2 * HALF];  // cross terms of the same channels
+  for (unsigned seg = blockIdx.y; seg < g.segments; seg += gridDim.y) {
+    const int c0 = (int)(seg * CS);
+    float xs[CS + 4 * HALF];  // x of channels c0-2*HALF ..
+    float gs[CS + 2 * HALF];  // dy of channels c0-HALF .., then the direct terms dy*scale^-beta
+    float tr[CS + 2 * HALF];  // cross terms of the same channels
 #pragma unroll
-  for (int i = 0; i < CS + 4 * HALF; ++i) {
-    const int ch = c0 + i - 2 * HALF;
-    xs[i] = (ch >= 0 && ch < g.C) ? xp[ch * g.hw] : 0.f;
-  }
-#pragma unroll
-  for (int i = 0; i < CS + 2 * HALF; ++i) {
-    const int ch = c0 + i - HALF;
-    gs[i] = (ch >= 0 && ch < g.C) ? gp[ch * g.hw] : 0.f;
-  }
-#pragma unroll
-  for (int i = 0; i < CS + 2 * HALF; ++i) {
-    const int ch = c0 + i - HALF;
-    tr[i] = 0.f;
-    if (ch >= 0 && ch < g.C) {
-      float sum = 0.f;
-#pragma unroll
-      for (int k = 0; k < SIZE; ++k) sum += xs[i + k] * xs[i + k];
-      const float scale = g.k + g.a * sum;
-      const float pw = neg_power<P34>(scale, g.beta);
-      tr[i] = gs[i] * xs[i + HALF] * pw / scale;
-      gs[i] *= pw;
+    for (int i = 0; i < CS + 4 * HALF; ++i) {
+      const int ch = c0 + i - 2 * HALF;
+      xs[i] = (ch >= 0 && ch < g.C) ? xp[ch * g.hw] : 0.f;
     }
-  }
 #pragma unroll
-  for (int i = 0; i < CS; ++i) {
-    if (c0 + i >= g.C) break;
-    float cross = 0.f;
+    for (int i = 0; i < CS + 2 * HALF; ++i) {
+      const int ch = c0 + i - HALF;
+      gs[i] = (ch >= 0 && ch < g.C) ? gp[ch * g.hw] : 0.f;
+    }
 #pragma unroll
-    for (int k = 0; k < SIZE; ++k) cross += tr[i + k];
-    op[(c0 + i) * g.hw] = gs[i + HALF] - g.coef * xs[i + 2 * HALF] * cross;
+    for (int i = 0; i < CS + 2 * HALF; ++i) {
+      const int ch = c0 + i - HALF;
+      tr[i] = 0.f;
+      if (ch >= 0 && ch < g.C) {
+        float sum = 0.f;
+#pragma unroll
+        for (int k = 0; k < SIZE; ++k) sum += xs[i + k] * xs[i + k];
+        const float scale = g.k + g.a * sum;
+        const float pw = neg_power<P34>(scale, g.beta);
+        tr[i] = gs[i] * xs[i + HALF] * pw / scale;
+        gs[i] *= pw;
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < CS; ++i) {
+      if (c0 + i >= g.C) break;
+      float cross = 0.f;
+#pragma unroll
+      for (int k = 0; k < SIZE; ++k) cross += tr[i + k];
+      op[(c0 + i) * g.hw] = gs[i + HALF] - g.coef * xs[i + 2 * HALF] * cross;
+    }
   }
 }
 
@@ -497,9 +504,8 @@ int run_lrn(const cct_lrn_desc_t* desc, bool backward, const float* x, const flo
   // few pixels 4, for more threads.  norm1 at batch 256 (72 MB): forward 72 us walking the channels with one
   // load ahead and powf, 32 now; backward 97 -> 49.
   const int cs = (g.pixels * ((g.C + 15) / 16) >= kLrnThreads) ? 16 : 4;
-  const unsigned nseg = (unsigned)((g.C + cs - 1) / cs);
-  if (nseg > 65535) return CCT_EUNSUPPORTED;
-  const dim3 grid((unsigned)blocks, nseg);
+  g.segments = (unsigned)(((long long)g.C + cs - 1) / cs);
+  const dim3 grid((unsigned)blocks, std::min(g.segments, kMaxGridRows));
   switch (desc->size) {
     case 1: launch_lrn<1>(backward, x, dy, out, g, cs, grid, st); break;
     case 3: launch_lrn<3>(backward, x, dy, out, g, cs, grid, st); break;

@@ -299,3 +299,22 @@ def test_lrn_powers_and_segments(B, beta, scale, N, C, H, W):
     for got, want in ((y, oracle.lrn_forward(od, x)), (dx, oracle.lrn_backward(od, x, dy))):
         got = got.cpu().numpy().astype(np.float64)
         assert np.linalg.norm(got - want) <= 1e-6 * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("N,C,H,W", [(2, 300000, 2, 2), (2, 1100000, 4, 4)], ids=["segments_of_4", "segments_of_16"])
+def test_lrn_with_more_segments_than_a_grid_has_rows(B, N, C, H, W):
+    """75 000 and 68 750 segments of channels: a thread takes several of them."""
+    import torch
+    rng = np.random.default_rng(11)
+    x = rng.standard_normal((N, C, H, W), dtype=np.float32)
+    dy = rng.standard_normal((N, C, H, W), dtype=np.float32)
+    d = B.make_lrn_desc(N, C, H, W, alpha=0.5)
+    y, dx = (torch.full((N, C, H, W), float("nan"), device="cuda") for _ in range(2))
+    tx = dev(x)
+    B.cct_lrn_forward(d, tx, y)
+    B.cct_lrn_backward(d, tx, dev(dy), dx)
+    torch.cuda.synchronize()
+    od = oracle.LrnDims(N, C, H, W, 5, 0.5, 0.75, 1.0)
+    for got, want in ((y, oracle.lrn_forward(od, x)), (dx, oracle.lrn_backward(od, x, dy))):
+        got = got.cpu().numpy().astype(np.float64)
+        assert np.linalg.norm(got - want) <= 1e-6 * np.linalg.norm(want)
