@@ -214,14 +214,15 @@ __global__ __launch_bounds__(256) void bwdw_img_reduce(ImgReduce p) {
       }
       for (; k < p.nsums; k += kStrips) v += src[(long long)k * p.O];
     }
+    // the strips in a tree: one after the other they would add as much error as 32 levels of it
     red[tid] = v;
     __syncthreads();
-    if (tid < kSumCh && o < p.O) {
-      float sum = 0.f;
 #pragma unroll
-      for (int k = 0; k < kStrips; ++k) sum += red[k * kSumCh + tid];
-      p.dbias[o] = p.accumulate ? p.dbias[o] + sum : sum;
+    for (int off = 128; off >= kSumCh; off >>= 1) {
+      if (tid < off) red[tid] += red[tid + off];
+      __syncthreads();
     }
+    if (tid < kSumCh && o < p.O) p.dbias[o] = p.accumulate ? p.dbias[o] + red[tid] : red[tid];
     return;
   }
   // a workgroup takes 256 weights, or 64 with a quarter of the splits per wave

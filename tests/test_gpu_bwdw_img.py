@@ -76,6 +76,20 @@ def test_precision(B):
     assert np.linalg.norm(got - want) / np.linalg.norm(want) <= 8e-7
 
 
+# Random signs: a level of a pairwise sum adds about half a unit in the last place, 2^-25, of the result (2-norm).
+@pytest.mark.parametrize("L,kernel,levels", [
+    (layer("conv", 50, 384, 13, 13, 256, 3, 1, 1, 2), KERNEL, 14),      # 8 images, 32 pixels, 64 strips
+    (layer("fc", 256, 16, 2, 2, 4096, 2), "dbias_columns", 8)], ids=["conv", "fc"])
+def test_bias_gradient_is_summed_pairwise(B, L, kernel, levels):
+    rng = np.random.default_rng(3)
+    x = rng.standard_normal((L.N, L.C, L.H, L.W), dtype=np.float32)
+    dy = rng.standard_normal((L.N, L.O, L.Hout, L.Wout), dtype=np.float32)
+    (_, db), names = ran(B, lambda: gpu_backward_weights(B, L, x, dy))
+    assert any(n.startswith(kernel) for n in names), names
+    want = dy.astype(np.float64).sum((0, 2, 3))
+    assert np.linalg.norm(db - want) / np.linalg.norm(want) <= 2.0 ** -25 * levels ** 0.5
+
+
 def test_not_finite_inputs(B):
     """Infinities, NaN and values beyond bf16's range reach exactly the weights they reach in fp32."""
     L = layer("nf", 48, 192, 13, 13, 128, 3, 1, 1)
