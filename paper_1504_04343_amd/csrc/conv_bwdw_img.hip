@@ -119,7 +119,7 @@ __global__ __launch_bounds__(256) void bwdw_img_prep(PrepJob j0, PrepJob j1, int
 
 struct ImgGemm {
   const unsigned char *xs, *ds;
-  float* part;  // [S][G][M][N], n = (channel block, tap, channel)
+  float* part;  // [S][G][M][N], n = (channel block, tap, channel); three terms: scaled as they are
   int M, N, G;
   int Cg, Og, C, O, K, KK, s, Wp;
   long long img_cells;  // padded pixels per image
@@ -186,15 +186,15 @@ struct ImgReduce {
   float* dw;
   const float* sums;  // bias partial sums [nsums][O], or null
   float* dbias;
-  const float *x, *dy;  // the chunk's tensors, for results that are not a number
+  const float *x, *dy;  // the chunk's tensors, for results that are not finite
   int M, N, G, S, K, KK, Cg, Og, C, O, H, W, Hout, Wout, s, pad, nimg;
-  int nsums, accumulate, blocks_dw, exact_nan, strips;
+  int nsums, accumulate, blocks_dw, split, strips;
 };
 
 constexpr int kSumCh = 4, kStrips = 256 / kSumCh;
 
 // The last blocks sum the bias gradient.
-// exact_nan: results of split operands that an infinity made NaN are summed again in plain fp32
+// split: the operands were split and scaled; results that are not finite are summed again in plain fp32
 // (split_bf16.h), the whole workgroup on one at a time.
 __global__ __launch_bounds__(256) void bwdw_img_reduce(ImgReduce p) {
   __shared__ float red[256];
@@ -260,12 +260,13 @@ __global__ __launch_bounds__(256) void bwdw_img_reduce(ImgReduce p) {
     __syncthreads();
     sum = ((red[wid] + red[64 + wid]) + red[128 + wid]) + red[192 + wid];
   }
-  if (p.exact_nan) {
+  if (p.split) {
     __shared__ int redo[256];
     __shared__ int any;
     if (tid == 0) any = 0;
     __syncthreads();
-    const bool bad = strip == 0 && t < total && sum != sum;
+    const bool bad = strip == 0 && t < total && !finite(sum);
+    sum *= kSplitUnscale;
     redo[tid] = bad;
     if (bad) any = 1;
     __syncthreads();
@@ -465,7 +466,7 @@ int launch_bwdw_img(const cct_conv_desc_t& d, const BwdwImgPlan& P, int nimg, co
   r.nimg = nimg;
   r.nsums = igs * jy.tiles_px;
   r.accumulate = accumulate;
-  r.exact_nan = P.terms == 3;
+  r.split = P.terms == 3;
   const long long total = (long long)d.O * q.N;
   // few weights: more loads in flight per weight
   r.strips = total < 256 * 1024 && q.S >= 8 ? 4 : 1;

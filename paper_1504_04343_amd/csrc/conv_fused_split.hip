@@ -46,7 +46,7 @@ __host__ __device__ constexpr int tiles_per_group(int K) {
   return K == 3 || K == 5 ? K * K : (K * K + 1) / 2 * 2;
 }
 
-// One output as a plain fp32 sum over its window, for results that an infinity made NaN.  Taps that
+// One output as a plain fp32 sum over its window, for results that are not finite.  Taps that
 // exist only in the regrouped kernel of a strided layer (index >= oK) are no terms of the sum.
 template <int S>
 __device__ float plain_sum(const GemmTN& p, const KcGeom& fg, int g, int m, int n, int r, int c) {
@@ -74,9 +74,7 @@ __device__ float plain_sum(const GemmTN& p, const KcGeom& fg, int g, int m, int 
       if (p.d2s && (rh + p.dS * (p.gK - 1 - i) >= p.oK || rw + p.dS * (p.gK - 1 - j) >= p.oK)) continue;
       const unsigned short* a = A + (((long long)(grp * tpg + tap) * 3) * p.Mpad + m) * CG + cc;
       const long long term = (long long)p.Mpad * CG;
-      const float wv = (__uint_as_float((unsigned)a[0] << 16) + __uint_as_float((unsigned)a[term] << 16)) +
-                       __uint_as_float((unsigned)a[2 * term] << 16);
-      sum = fmaf(Xc[(long long)h * p.x_w + w], wv, sum);
+      sum = fmaf(Xc[(long long)h * p.x_w + w], join_value(a[0], a[term], a[2 * term]), sum);
       if (sum != sum) return sum;
     }
   }
@@ -480,7 +478,8 @@ __global__ __launch_bounds__(NT, 2) void conv_fused_split(GemmTN p, KcGeom fg, i
     for (int r = 0; r < 16; ++r) {
       if constexpr (PARTS) acc_h[j][r] += total[j][r];
       acc_h[j][r] += acc_c[j][r];
-      bad |= acc_h[j][r] != acc_h[j][r];
+      bad |= !finite(acc_h[j][r]);
+      acc_h[j][r] *= kSplitUnscale;
     }
   if (p.d2s) {
     float* __restrict__ D = p.C;
@@ -550,7 +549,7 @@ __global__ __launch_bounds__(NT, 2) void conv_fused_split(GemmTN p, KcGeom fg, i
   }
   if (!bad) return;
 
-  // ---- results that are not a number: redo them one by one (split_bf16.h)
+  // ---- results that are not finite: redo them one by one (split_bf16.h)
 #pragma unroll 1
   for (int j = 0; j < WN; ++j) {
     const int col = n0 + bn + j * MB;
@@ -570,8 +569,7 @@ __global__ __launch_bounds__(NT, 2) void conv_fused_split(GemmTN p, KcGeom fg, i
       } else {
         dst = p.C + (long long)g * p.c_gs + col_offset(p.cmap, col) + (long long)m * p.c_ms;
       }
-      const float old = *dst;
-      if (old == old) continue;
+      if (finite(*dst)) continue;
       float v = plain_sum<S>(p, fg, g, m, n, r_, c_);
       if (!p.d2s && p.bias) v += p.bias[(long long)g * p.bias_gs + m];
       *dst = v;

@@ -37,7 +37,7 @@ typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // 16 byt
 constexpr int KPAD = 32;                    // the pack is padded to whole stages of any form
 constexpr int PLANE = BN * 16 + 64;         // bytes of one (term, 8 k) plane in LDS
 
-// One result as a plain fp32 sum, for results that an infinity made NaN (split_bf16.h).
+// One result as a plain fp32 sum, for results that are not finite (split_bf16.h).
 template <bool BT, bool DIRECT>
 __device__ float plain_product(const GemmTN& p, int g, int kd, int m, int col) {
   const unsigned short* A = reinterpret_cast<const unsigned short*>(p.A) + (long long)g * p.a_gs * 3;
@@ -52,8 +52,7 @@ __device__ float plain_product(const GemmTN& p, int g, int kd, int m, int col) {
       av = reinterpret_cast<const float*>(p.A)[g * p.a_gs + m * p.a_ms + k];
     } else {
       const unsigned short* a = A + ((long long)(k / TK) * 3 * p.Mpad + m) * TK + k % TK;
-      av = (__uint_as_float((unsigned)a[0] << 16) + __uint_as_float((unsigned)a[term] << 16)) +
-           __uint_as_float((unsigned)a[2 * term] << 16);
+      av = join_value(a[0], a[term], a[2 * term]);
     }
     sum = fmaf(av, B[BT ? (long long)k : k * p.b_ks], sum);
     if (sum != sum) return sum;
@@ -296,13 +295,14 @@ __global__ __launch_bounds__(NT, WAVES_M == 4 ? 2 : 4) void gemm_split(GemmTN p,
       const int m = mw + (r >> 2) * 8 + lane_hi * 4 + (r & 3);
       if (m >= p.M) continue;
       float v = acc_h[j][r] + acc_c[j][r];
-      bad |= v != v;
+      bad |= !finite(v);
+      v *= kSplitUnscale;
       if (bias) v += bias[p.bias_gs < 0 ? col : m];
       cl[(long long)m * p.c_ms] = v;
     }
   }
   if (!bad) return;
-  // results that are not a number: redo them one by one (split_bf16.h)
+  // results that are not finite: redo them one by one (split_bf16.h)
 #pragma unroll 1
   for (int j = 0; j < WN; ++j) {
     const int col = n0 + wave_n * WN * 32 + j * 32 + lane_lo;
@@ -312,8 +312,7 @@ __global__ __launch_bounds__(NT, WAVES_M == 4 ? 2 : 4) void gemm_split(GemmTN p,
       const int m = mw + (r >> 2) * 8 + lane_hi * 4 + (r & 3);
       if (m >= p.M) continue;
       float* d = C + col_offset(p.cmap, col) + (long long)m * p.c_ms;
-      const float old = *d;
-      if (old == old) continue;
+      if (finite(*d)) continue;
       float v = plain_product<BT, DIRECT>(p, g, kd, m, col);
       if (bias) v += bias[p.bias_gs < 0 ? col : m];
       *d = v;

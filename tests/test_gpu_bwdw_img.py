@@ -90,6 +90,17 @@ def test_bias_gradient_is_summed_pairwise(B, L, kernel, levels):
     assert np.linalg.norm(db - want) / np.linalg.norm(want) <= 2.0 ** -25 * levels ** 0.5
 
 
+@pytest.mark.parametrize("e,f", [(-118, 88), (-70, 40), (70, -50), (103, -83), (110, -90)], ids=lambda e: "2^%d" % e)
+def test_range_of_fp32(B, e, f):
+    """An operand of any magnitude that fp32 holds keeps its 24 bits (error as in test_precision)."""
+    L = layer("range", 48, 192, 13, 13, 128, 3, 1, 1)
+    x, dy = np.ldexp(synth.make_x(L, 4), e).astype(np.float32), np.ldexp(synth.make_dy(L, 4), f).astype(np.float32)
+    (dw, _), names = ran(B, lambda: gpu_backward_weights(B, L, x, dy))
+    assert any(n.startswith(KERNEL) for n in names), names
+    want = oracle.conv_backward_weights(odims(oracle, L), x, dy)[0]
+    assert np.linalg.norm(dw.astype(np.float64) - want) <= 8e-7 * np.linalg.norm(want)
+
+
 def test_not_finite_inputs(B):
     """Infinities, NaN and values beyond bf16's range reach exactly the weights they reach in fp32."""
     L = layer("nf", 48, 192, 13, 13, 128, 3, 1, 1)

@@ -125,6 +125,22 @@ def test_materialised_on_one_side(B, L, chunk):
     assert rel_err(got, oracle.conv_backward_data(odims(oracle, L), w, dy)) <= TOL_F32
 
 
+@pytest.mark.parametrize("e,f", [(-118, 88), (-70, 40), (70, -50), (103, -83), (110, -90)], ids=lambda e: "2^%d" % e)
+@pytest.mark.parametrize("L", [FC[1], FC[4], POINTWISE[1]], ids=["direct", "packed", "pointwise"])
+def test_range_of_fp32(B, L, e, f):
+    """An operand of any magnitude that fp32 holds keeps its 24 bits: the bound of an fp32 chain of 400 products."""
+    x, w = np.ldexp(synth.make_x(L, 4), e).astype(np.float32), np.ldexp(synth.make_w(L, 4), f).astype(np.float32)
+    dy = np.ldexp(synth.make_dy(L, 4), e).astype(np.float32)
+    got, names = ran(B, lambda: gpu_forward(B, L, x, w, None))
+    assert split(names), names
+    want = oracle.conv_forward(odims(oracle, L), x, w, None)
+    assert np.linalg.norm(got.astype(np.float64) - want) <= 5e-7 * np.linalg.norm(want)
+    got, names = ran(B, lambda: gpu_backward_data(B, L, w, dy))
+    assert split(names), names
+    want = oracle.conv_backward_data(odims(oracle, L), w, dy)
+    assert np.linalg.norm(got.astype(np.float64) - want) <= 5e-7 * np.linalg.norm(want)
+
+
 @pytest.mark.parametrize("L", [FC[1], FC[4], POINTWISE[1]], ids=["direct", "packed", "pointwise"])
 def test_not_finite_inputs(B, L):
     """Infinities, NaN and values beyond bf16's range reach exactly the outputs they reach in fp32."""

@@ -107,6 +107,26 @@ def test_precision_of_small_layers(B, L):
     assert np.linalg.norm(got.astype(np.float64) - want) / np.linalg.norm(want) <= 1.5e-7
 
 
+@pytest.mark.parametrize("e,f", [(-118, 88), (-70, 40), (70, -50), (103, -83), (110, -90)], ids=lambda e: "2^%d" % e)
+@pytest.mark.parametrize("L", [layer("r_k3", 2, 40, 13, 13, 70, 3, 1, 1), layer("r_s2d", 2, 3, 31, 31, 40, 11, 4, 0)],
+                         ids=lambda L: L.name)
+def test_range_of_fp32(B, L, e, f):
+    """An operand of any magnitude that fp32 holds keeps its 24 bits (2^-118: the terms' last bits would lie below
+    bf16's smallest number; 2^103 and 2^110: values that do not scale), the other one brings the results to 2^-30 or 2^20.
+    The bound is that of an fp32 chain of 400 products, 2^-24 / sqrt(3) * sqrt(400 / 2)."""
+    x, w = synth.make_x(L, 4), synth.make_w(L, 4)
+    x, w = np.ldexp(x, e).astype(np.float32), np.ldexp(w, f).astype(np.float32)
+    dy = np.ldexp(synth.make_dy(L, 4), e).astype(np.float32)
+    got, names = ran(B, lambda: gpu_forward(B, L, x, w, None, B.LOWER_FUSED))
+    assert any(n.startswith(KERNEL) for n in names), names
+    want = oracle.conv_forward(odims(oracle, L), x, w, None)
+    assert np.linalg.norm(got.astype(np.float64) - want) <= 5e-7 * np.linalg.norm(want)
+    got, names = ran(B, lambda: gpu_backward_data(B, L, w, dy, B.LOWER_FUSED))
+    assert any(n.startswith(KERNEL) for n in names), names
+    want = oracle.conv_backward_data(odims(oracle, L), w, dy)
+    assert np.linalg.norm(got.astype(np.float64) - want) <= 5e-7 * np.linalg.norm(want)
+
+
 SPECIAL = [("plain", layer("nf", 3, 16, 13, 13, 40, 3, 1, 1)),
            ("s2d", layer("nf2", 3, 3, 31, 31, 40, 7, 4, 0)),
            ("zero_tile", layer("nf7", 2, 16, 13, 13, 40, 7, 1, 3))]
