@@ -187,7 +187,9 @@ struct ImgReduce {
   const float* sums;  // bias partial sums [nsums][O], or null
   float* dbias;
   const float *x, *dy;  // the chunk's tensors, for results that are not finite
-  int M, N, G, S, K, KK, Cg, Og, C, O, H, W, Hout, Wout, s, pad, nimg;
+  int M, N, G, S, K, KK, Cg, Og, C, O, H, W, P, Wout, s, pad, nimg;
+  unsigned mWout;
+  int sWout;
   int nsums, accumulate, blocks_dw, split, strips;
 };
 
@@ -263,15 +265,41 @@ __global__ __launch_bounds__(256) void bwdw_img_reduce(ImgReduce p) {
   if (p.split) {
     __shared__ int redo[256];
     __shared__ int any;
+    const int P = p.P;
+    // the operands of weight (oo, channel cc, tap i, j) at pixel pix of image n, zeros outside the image: the loads
+    // do not depend on a branch, so that a thread has several in flight
+    auto operands = [&](int oo, int cc, int i, int j, int n, int pix, float* a, float* b) {
+      const int r = fdiv_u(pix, p.mWout, p.sWout), c = pix - r * p.Wout;
+      const int h = r * p.s + i - p.pad, w = c * p.s + j - p.pad;
+      const bool ok = n < p.nimg && h >= 0 && h < p.H && w >= 0 && w < p.W;
+      const float va = p.dy[ok ? ((long long)n * p.O + oo) * P + pix : 0];
+      const float vb = p.x[ok ? (((long long)n * p.C + cc) * p.H + h) * p.W + w : 0];
+      *a = ok ? va : 0.f;
+      *b = ok ? vb : 0.f;
+    };
+    bool bad = strip == 0 && t < total && !finite(sum);
+    sum *= kSplitUnscale;
+    if (bad) {  // where a NaN went in, most weights are decided here, all at once
+      float v = 0.f;
+      for (int q = 0; q < 64 && q < P && v == v; ++q) {
+        float a, b;
+        operands(o, o / p.Og * p.Cg + ci, tap / p.K, tap % p.K, 0, q, &a, &b);
+        v = fmaf(a, b, v);
+      }
+      if (v != v) {
+        sum = v;
+        bad = false;
+      }
+    }
     if (tid == 0) any = 0;
     __syncthreads();
-    const bool bad = strip == 0 && t < total && !finite(sum);
-    sum *= kSplitUnscale;
     redo[tid] = bad;
     if (bad) any = 1;
     __syncthreads();
     if (any) {
       __shared__ int key[3];
+      __shared__ int found;  // a NaN, which no other product changes: the threads stop as they see it
+      volatile int* stop = &found;
 #pragma unroll 1
       for (int who = 0; who < 256; ++who) {
         if (!redo[who]) continue;  // the same for all threads
@@ -279,21 +307,37 @@ __global__ __launch_bounds__(256) void bwdw_img_reduce(ImgReduce p) {
           key[0] = o;
           key[1] = o / p.Og * p.Cg + ci;
           key[2] = tap;
+          found = 0;
         }
         __syncthreads();
         const int i = key[2] / p.K, jj = key[2] - i * p.K;
-        const long long P = (long long)p.Hout * p.Wout, cells = P * p.nimg;
-        float v = 0.f;
-        for (long long q = tid; q < cells; q += 256) {
-          const int n = (int)(q / P), pix = (int)(q - n * P);
-          const int r = pix / p.Wout, c = pix - r * p.Wout;
-          const int h = r * p.s + i - p.pad, w = c * p.s + jj - p.pad;
-          if (h < 0 || h >= p.H || w < 0 || w >= p.W) continue;
-          v = fmaf(p.dy[((long long)n * p.O + key[0]) * P + pix],
-                   p.x[(((long long)n * p.C + key[1]) * p.H + h) * p.W + w], v);
-          if (v != v) break;
+        // a thread's pixels advance by 4 * 256: image and pixel by adding, no division by P
+        float v[4] = {0.f, 0.f, 0.f, 0.f};
+        int n[4], pix[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          n[u] = (tid + u * 256) / p.P;
+          pix[u] = tid + u * 256 - n[u] * p.P;
         }
-        red[tid] = v;
+        const int dn = 1024 / p.P, dpix = 1024 - dn * p.P;
+        while (n[0] < p.nimg && !*stop) {
+          float a[4], b[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            operands(key[0], key[1], i, jj, n[u], pix[u], &a[u], &b[u]);
+            n[u] += dn;
+            pix[u] += dpix;
+            if (pix[u] >= p.P) {
+              pix[u] -= p.P;
+              ++n[u];
+            }
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u) v[u] = fmaf(a[u], b[u], v[u]);
+          const float sum4 = (v[0] + v[1]) + (v[2] + v[3]);
+          if (sum4 != sum4) *stop = 1;
+        }
+        red[tid] = (v[0] + v[1]) + (v[2] + v[3]);
         __syncthreads();
 #pragma unroll 1
         for (int off = 128; off > 0; off >>= 1) {
@@ -462,7 +506,7 @@ int launch_bwdw_img(const cct_conv_desc_t& d, const BwdwImgPlan& P, int nimg, co
   memset(&r, 0, sizeof(r));
   r.part = q.part; r.dw = dw; r.sums = jy.sums; r.dbias = dbias; r.x = x; r.dy = dy;
   r.M = Og; r.N = q.N; r.G = d.groups; r.S = q.S; r.K = d.K; r.KK = KK; r.Cg = Cg; r.Og = Og;
-  r.C = d.C; r.O = d.O; r.H = d.H; r.W = d.W; r.Hout = Hout; r.Wout = Wout; r.s = d.stride; r.pad = d.pad;
+  r.C = d.C; r.O = d.O; r.H = d.H; r.W = d.W; r.P = pix; r.Wout = Wout; r.mWout = q.mWout; r.sWout = q.sWout; r.s = d.stride; r.pad = d.pad;
   r.nimg = nimg;
   r.nsums = igs * jy.tiles_px;
   r.accumulate = accumulate;

@@ -46,46 +46,41 @@ __host__ __device__ constexpr int tiles_per_group(int K) {
   return K == 3 || K == 5 ? K * K : (K * K + 1) / 2 * 2;
 }
 
-// One output as a plain fp32 sum over its window, for results that are not finite.  Taps that
-// exist only in the regrouped kernel of a strided layer (index >= oK) are no terms of the sum.
+// For results that are not finite: the operands of a product (channel, tap i, j) in plain fp32.
+__device__ __forceinline__ float kernel_value(const GemmTN& p, int g, int m, int ch, int tap) {
+  const int grp = ch / CG;
+  const unsigned short* a = reinterpret_cast<const unsigned short*>(p.A) + (long long)g * p.a_gs * 3 +
+                            (((long long)(grp * tiles_per_group(p.gK) + tap) * 3) * p.Mpad + m) * CG + (ch - grp * CG);
+  const long long term = (long long)p.Mpad * CG;
+  return join_value(a[0], a[term], a[2 * term]);
+}
+struct Output {
+  int m, n, r, c;
+};
+// The pixel that tap (i, j) of channel ch reads for output (n, r, c); null outside the tensor and for taps that
+// exist only in the regrouped kernel of a strided layer (index >= oK).
 template <int S>
-__device__ float plain_sum(const GemmTN& p, const KcGeom& fg, int g, int m, int n, int r, int c) {
-  const int tpg = tiles_per_group(p.gK);
-  const unsigned short* A = reinterpret_cast<const unsigned short*>(p.A) + (long long)g * p.a_gs * 3;
-  const float* X = reinterpret_cast<const float*>(p.B) + (long long)n * p.x_img;
-  const int ss = p.d2s ? p.dS * p.dS : 1;
-  const int rh = p.d2s ? (m % ss) / p.dS : 0, rw = p.d2s ? (m % ss) % p.dS : 0;
-  float sum = 0.f;
-#pragma unroll 1
-  for (int ch = 0; ch < p.gCg; ++ch) {
-    const int grp = ch / CG, cc = ch - grp * CG;
-    const int dh = S > 1 ? (ch % (S * S)) / S : 0, dw = S > 1 ? ch % S : 0;
-    const float* Xc = X + (long long)((g * p.gCg + ch) / (S * S)) * p.x_plane;
-#pragma unroll 1
-    for (int tap = 0; tap < fg.KK; ++tap) {
-      const int i = tap / p.gK, j = tap - i * p.gK;
-      int h = r * p.gs + i - p.gp, w = c * p.gs + j - p.gp;
-      if (S > 1) {
-        h = h * S + dh - p.x_pad;
-        w = w * S + dw - p.x_pad;
-      }
-      if (h < 0 || h >= p.x_h || w < 0 || w >= p.x_w) continue;
-      if (S > 1 && (i * S + dh >= p.oK || j * S + dw >= p.oK)) continue;
-      if (p.d2s && (rh + p.dS * (p.gK - 1 - i) >= p.oK || rw + p.dS * (p.gK - 1 - j) >= p.oK)) continue;
-      const unsigned short* a = A + (((long long)(grp * tpg + tap) * 3) * p.Mpad + m) * CG + cc;
-      const long long term = (long long)p.Mpad * CG;
-      sum = fmaf(Xc[(long long)h * p.x_w + w], join_value(a[0], a[term], a[2 * term]), sum);
-      if (sum != sum) return sum;
-    }
+__device__ __forceinline__ const float* pixel_of(const GemmTN& p, int g, int n, int r, int c, int ch, int i, int j) {
+  int h = r * p.gs + i - p.gp, w = c * p.gs + j - p.gp;
+  if (S > 1) {
+    const int dh = (ch % (S * S)) / S, dw = ch % S;
+    if (i * S + dh >= p.oK || j * S + dw >= p.oK) return nullptr;
+    h = h * S + dh - p.x_pad;
+    w = w * S + dw - p.x_pad;
   }
-  return sum;
+  if (h < 0 || h >= p.x_h || w < 0 || w >= p.x_w) return nullptr;
+  return reinterpret_cast<const float*>(p.B) + (long long)n * p.x_img +
+         (long long)((g * p.gCg + ch) / (S * S)) * p.x_plane + (long long)h * p.x_w + w;
 }
 
 // cells per thread: sizes without an unrolled group take a third one (7 x 7 windows on wide rows)
 constexpr int kCells(int KT) { return KT ? 2 : 3; }
 
+// waves per SIMD that the registers have room for (the smallest form fits four)
+constexpr int waves_per_simd(int WAVES_M, int KT, int S) { return WAVES_M == 1 && KT == 0 && S == 1 ? 4 : 2; }
+
 template <int WAVES_M, int KT, int S>
-__global__ __launch_bounds__(NT, 2) void conv_fused_split(GemmTN p, KcGeom fg, int tiles_m, int tiles_n) {
+__global__ __launch_bounds__(NT, waves_per_simd(WAVES_M, KT, S)) void conv_fused_split(GemmTN p, KcGeom fg, int tiles_m, int tiles_n) {
   constexpr int QU = kCells(KT);  // cells per thread and slot
   constexpr int MB = 32;
   constexpr int BM = MB * WAVES_M;
@@ -547,32 +542,95 @@ __global__ __launch_bounds__(NT, 2) void conv_fused_split(GemmTN p, KcGeom fg, i
       }
     }
   }
-  if (!bad) return;
+  if (!__any(bad)) return;
 
-  // ---- results that are not finite: redo them one by one (split_bf16.h)
+  // ---- Blocks with results that are not finite: again in plain fp32 (split_bf16.h).  A block of fp32 products
+  // costs a few times one of split ones whatever is in it (256 images of conv3 with one infinity each: 331 us
+  // without, 4.3 ms with it).  It also multiplies zeros that stand for no pixel or no tap: where one may have met
+  // a value that is not finite, a NaN is summed once more without them.
 #pragma unroll 1
   for (int j = 0; j < WN; ++j) {
     const int col = n0 + bn + j * MB;
-    if (col >= ce) continue;
-    const int n = col / P, pix = col - n * P;
-    const int r_ = pix / p.gWout, c_ = pix - r_ * p.gWout;
-#pragma unroll 1
+    const int n = min(col, ce - 1) / P, pix = min(col, ce - 1) - n * P, r_ = pix / p.gWout, c_ = pix - r_ * p.gWout;
+    auto address = [&](int m) -> float* {  // null: no such result
+      if (col >= ce || m >= p.M) return nullptr;
+      if (!p.d2s) return p.C + (long long)g * p.c_gs + col_offset(p.cmap, col) + (long long)m * p.c_ms;
+      const int ss = p.dS * p.dS, ci = m / ss, rem = m - ci * ss;
+      const int h = r_ * p.dS + rem / p.dS - p.dP, w = c_ * p.dS + rem % p.dS - p.dP;
+      if ((unsigned)h >= (unsigned)p.dH || (unsigned)w >= (unsigned)p.dW) return nullptr;
+      return p.C + (((long long)n * p.dCtot + (long long)g * p.dCg + ci) * p.dH + h) * p.dW + w;
+    };
+    int first = mw + lane_hi * 4;
+    asm volatile("" : "+v"(first));  // what depends on the rows is not kept for all blocks
+    auto row = [&](int r) { return first + (r >> 2) * 8 + (r & 3); };
+    auto store = [&](int r, float v) {
+      if (!p.d2s && p.bias) v += p.bias[(long long)g * p.bias_gs + row(r)];
+      *address(row(r)) = v;
+    };
+    unsigned todo = 0;
+#pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const int m = mw + (r >> 2) * 8 + (r & 3) + lane_hi * 4;
-      if (m >= p.M) continue;
-      float* dst;
-      if (p.d2s) {
-        const int ss = p.dS * p.dS, ci = m / ss, rem = m - ci * ss;
-        const int h = r_ * p.dS + rem / p.dS - p.dP, w = c_ * p.dS + rem % p.dS - p.dP;
-        if ((unsigned)h >= (unsigned)p.dH || (unsigned)w >= (unsigned)p.dW) continue;
-        dst = p.C + (((long long)n * p.dCtot + (long long)g * p.dCg + ci) * p.dH + h) * p.dW + w;
-      } else {
-        dst = p.C + (long long)g * p.c_gs + col_offset(p.cmap, col) + (long long)m * p.c_ms;
-      }
-      if (finite(*dst)) continue;
-      float v = plain_sum<S>(p, fg, g, m, n, r_, c_);
-      if (!p.d2s && p.bias) v += p.bias[(long long)g * p.bias_gs + m];
-      *dst = v;
+      const float* at = address(row(r));
+      if (at && !finite(*at)) todo |= 1u << r;
+    }
+    if (!__any(todo)) continue;
+    // step = (pair of channels, tap); which rows and columns hold values that are not finite, which columns
+    // read outside the tensor
+    bool a_bad = false, b_bad = false, b_out = false;
+    auto doubts = [&]() {  // the results whose NaN may come from a zero that is no product
+      const unsigned long long bad_rows = __ballot(a_bad), bad_cols = __ballot(b_bad), out_cols = __ballot(b_out);
+      auto halves = [](unsigned long long v) { return (unsigned)(v | v >> 32); };
+      if (p.d2s && halves(bad_cols) >> lane_lo & 1) return 0xffffu;
+      if (!(halves(out_cols) >> lane_lo & 1)) return 0u;
+      const unsigned rows = halves(bad_rows) >> (lane_hi * 4);
+      return (rows & 0xfu) | (rows >> 4 & 0xf0u) | (rows >> 8 & 0xf00u) | (rows >> 12 & 0xf000u);
+    };
+    const floatx16 v = fp32_block(
+        (p.gCg + 1) / 2 * fg.KK,
+        [&](int s) {
+          const int ch = s / fg.KK * 2 + lane_hi;
+          const float a = ch < p.gCg ? kernel_value(p, g, mw + lane_lo, ch, s % fg.KK) : 0.f;
+          a_bad |= !finite(a);
+          return a;
+        },
+        [&](int s) {
+          const int ch = s / fg.KK * 2 + lane_hi, tap = s % fg.KK;
+          const float* at = ch < p.gCg ? pixel_of<S>(p, g, n, r_, c_, ch, tap / p.gK, tap % p.gK) : nullptr;
+          b_out |= !at;
+          const float b = at ? *at : 0.f;
+          b_bad |= !finite(b);
+          return b;
+        },
+        [&](const floatx16& acc) { return numbers(acc, todo) | (todo & doubts()); });
+    const unsigned doubt = doubts();
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      if (!(todo >> r & 1) || (v[r] != v[r] && (doubt >> r & 1))) continue;
+      store(r, v[r]);
+      todo &= ~(1u << r);
+    }
+    for (int r = 0; r < 16; ++r) {
+      const bool mine = todo >> r & 1;
+      if (!__any(mine)) continue;
+      const float sum = fp32_sum(
+          mine, p.gCg * fg.KK,
+          [&](int who) {
+            return Output{mw + (r >> 2) * 8 + (who >> 5) * 4 + (r & 3), __shfl(n, who, 64), __shfl(r_, who, 64),
+                          __shfl(c_, who, 64)};
+          },
+          [&](const Output& o, int k, float* x, float* y) {
+            const int ch = k / fg.KK, tap = k - ch * fg.KK, i = tap / p.gK, jj = tap - i * p.gK;
+            const float* at = pixel_of<S>(p, g, o.n, o.r, o.c, ch, i, jj);
+            if (!at) return false;
+            if (p.d2s) {
+              const int rem = o.m % (p.dS * p.dS), rh = rem / p.dS, rw = rem % p.dS;
+              if (rh + p.dS * (p.gK - 1 - i) >= p.oK || rw + p.dS * (p.gK - 1 - jj) >= p.oK) return false;
+            }
+            *x = kernel_value(p, g, o.m, ch, tap);
+            *y = *at;
+            return true;
+          });
+      if (mine) store(r, sum);
     }
   }
 }

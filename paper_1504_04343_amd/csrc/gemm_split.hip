@@ -37,31 +37,8 @@ typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // 16 byt
 constexpr int KPAD = 32;                    // the pack is padded to whole stages of any form
 constexpr int PLANE = BN * 16 + 64;         // bytes of one (term, 8 k) plane in LDS
 
-// One result as a plain fp32 sum, for results that are not finite (split_bf16.h).
-template <bool BT, bool DIRECT>
-__device__ float plain_product(const GemmTN& p, int g, int kd, int m, int col) {
-  const unsigned short* A = reinterpret_cast<const unsigned short*>(p.A) + (long long)g * p.a_gs * 3;
-  const float* B = reinterpret_cast<const float*>(p.B) + (long long)g * p.b_gs +
-                   (BT ? (long long)col * p.b_ks : col_offset(p.bmap, col));
-  const long long term = (long long)p.Mpad * TK;
-  float sum = 0.f;
-#pragma unroll 1
-  for (int k = 0; k < kd; ++k) {
-    float av;
-    if constexpr (DIRECT) {
-      av = reinterpret_cast<const float*>(p.A)[g * p.a_gs + m * p.a_ms + k];
-    } else {
-      const unsigned short* a = A + ((long long)(k / TK) * 3 * p.Mpad + m) * TK + k % TK;
-      av = join_value(a[0], a[term], a[2 * term]);
-    }
-    sum = fmaf(av, B[BT ? (long long)k : k * p.b_ks], sum);
-    if (sum != sum) return sum;
-  }
-  return sum;
-}
-
 template <int WAVES_M, bool BT, bool DIRECT>
-__global__ __launch_bounds__(NT, WAVES_M == 4 ? 2 : 4) void gemm_split(GemmTN p, int Ktotal, int tiles_m, int tiles_n) {
+__global__ __launch_bounds__(NT, WAVES_M == 4 ? 2 : WAVES_M == 1 && !BT ? 6 : 4) void gemm_split(GemmTN p, int Ktotal, int tiles_m, int tiles_n) {
   constexpr int WAVES_N = 4 / WAVES_M;
   constexpr int WN = BN / (32 * WAVES_N);
   constexpr int BM = 32 * WAVES_M;
@@ -301,21 +278,48 @@ __global__ __launch_bounds__(NT, WAVES_M == 4 ? 2 : 4) void gemm_split(GemmTN p,
       cl[(long long)m * p.c_ms] = v;
     }
   }
-  if (!bad) return;
-  // results that are not finite: redo them one by one (split_bf16.h)
+  if (!__any(bad)) return;
+  // blocks with results that are not finite: again in plain fp32 (split_bf16.h)
+  const GemmTN& q = first_argument<GemmTN>();
+  float* Cq = q.C + (long long)g * q.c_gs;
+  const float* Bq = reinterpret_cast<const float*>(q.B) + (long long)g * q.b_gs;
+  const float* bq = q.bias ? q.bias + (q.bias_gs < 0 ? 0 : (long long)g * q.bias_gs) : nullptr;
 #pragma unroll 1
   for (int j = 0; j < WN; ++j) {
-    const int col = n0 + wave_n * WN * 32 + j * 32 + lane_lo;
-    if (col >= p.Ncols) continue;
-#pragma unroll 1
+    const int col = n0 + wave_n * WN * 32 + j * 32 + lane_lo, c = min(col, q.Ncols - 1);
+    float* cl = Cq + col_offset(q.cmap, c) + (long long)(mw + lane_hi * 4) * q.c_ms;
+    unsigned todo = 0;
+#pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const int m = mw + (r >> 2) * 8 + lane_hi * 4 + (r & 3);
-      if (m >= p.M) continue;
-      float* d = C + col_offset(p.cmap, col) + (long long)m * p.c_ms;
-      if (finite(*d)) continue;
-      float v = plain_product<BT, DIRECT>(p, g, kd, m, col);
-      if (bias) v += bias[p.bias_gs < 0 ? col : m];
-      *d = v;
+      const int rr = (r >> 2) * 8 + (r & 3);
+      if (col < q.Ncols && mw + lane_hi * 4 + rr < q.M && !finite(cl[(long long)rr * q.c_ms])) todo |= 1u << r;
+    }
+    if (!__any(todo)) continue;
+    const float* bc = Bq + (BT ? (long long)c * q.b_ks : col_offset(q.bmap, c));
+    const int m = min(mw + lane_lo, q.M - 1);
+    const floatx16 v = fp32_block(
+        (kd + 1) / 2,
+        [&](int s) {
+          const int k = 2 * s + lane_hi;
+          if (k >= kd) return 0.f;
+          if constexpr (DIRECT) return reinterpret_cast<const float*>(q.A)[g * q.a_gs + m * q.a_ms + k];
+          const unsigned short* ak = reinterpret_cast<const unsigned short*>(q.A) + (long long)g * q.a_gs * 3 +
+                                     ((long long)(k / TK) * 3 * q.Mpad + m) * TK + k % TK;
+          const long long term = (long long)q.Mpad * TK;
+          return join_value(ak[0], ak[term], ak[2 * term]);
+        },
+        [&](int s) {
+          const int k = 2 * s + lane_hi;
+          return k < kd ? bc[BT ? (long long)k : k * q.b_ks] : 0.f;
+        },
+        [&](const floatx16& acc) { return numbers(acc, todo); });
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      if (!(todo >> r & 1)) continue;
+      const int rr = (r >> 2) * 8 + (r & 3);
+      float sum = v[r];
+      if (bq) sum += bq[q.bias_gs < 0 ? col : mw + lane_hi * 4 + rr];
+      cl[(long long)rr * q.c_ms] = sum;
     }
   }
 }

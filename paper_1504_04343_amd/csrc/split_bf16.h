@@ -20,10 +20,11 @@
 // came out with a relative error of 1.5e-5.)  It costs one multiplication per split value, at most 1 % of a pass.
 //
 // Not finite: inf - inf makes m and l NaN, and 0 * inf appears between the terms, so a result that an infinity
-// touches comes out NaN; a value of 2^104 or a result of 2^80 overflows.  The kernels recompute every result
-// that is not finite in plain fp32 before they end (redo_not_finite; one that is real is met again).
+// touches comes out NaN; a value of 2^104 or a result of 2^80 overflows.  The kernels recompute the blocks with
+// results that are not finite in plain fp32 before they end (a value that is real is met again).
 #pragma once
 #include "cct_internal.h"
+#include "gemm_common.h"
 
 namespace cct {
 namespace {
@@ -78,6 +79,80 @@ __device__ __forceinline__ float join_value(unsigned short h, unsigned short m, 
 }
 
 __device__ __forceinline__ bool finite(float v) { return __builtin_fabsf(v) < __builtin_inff(); }
+
+// The kernel's first argument, read again: what only the code behind it needs is not kept in scalar registers
+// through the kernel.
+template <class T>
+__device__ __forceinline__ const T& first_argument() {
+  auto at = __builtin_amdgcn_kernarg_segment_ptr();
+  asm("" : "+s"(at));
+  return *(const T*)at;
+}
+
+// A 32 x 32 block of results in plain fp32: every step is two products, a(s) and b(s) those of a lane's row and
+// column (lane & 31) and half (lane >> 5); 8 steps' loads are in flight.  open(acc): which of its results a lane
+// still waits for (a NaN stays one).
+template <class A, class B, class Open>
+__device__ __forceinline__ floatx16 fp32_block(int steps, A a, B b, Open open) {
+  floatx16 acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+#pragma unroll 1
+  for (int s = 0; s < steps; s += 8) {
+    float x[8], y[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      x[u] = s + u < steps ? a(s + u) : 0.f;
+      y[u] = s + u < steps ? b(s + u) : 0.f;
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[u], y[u], acc, 0, 0, 0);
+    if (!__any(open(acc))) break;
+  }
+  return acc;
+}
+// the results among `todo` that are no NaN
+__device__ __forceinline__ unsigned numbers(const floatx16& acc, unsigned todo) {
+#pragma unroll
+  for (int r = 0; r < 16; ++r)
+    if (acc[r] != acc[r]) todo &= ~(1u << r);
+  return todo;
+}
+
+// One result per lane with `todo` in plain fp32: what(lane) describes a lane's result (all lanes call it),
+// term(that, k, &x, &y) gives its k-th product, false if there is none.  A NaN among the first 64 decides; the
+// other results take the whole wave one by one.  Returns the lane's own sum.
+template <class What, class Term>
+__device__ __forceinline__ float fp32_sum(bool todo, int terms, What what, Term term) {
+  const int lane = threadIdx.x & 63;
+  float mine = 0.f;
+  const auto own = what(lane);
+  for (int k = 0; k < min(terms, 64) && todo; ++k) {
+    float x, y;
+    if (term(own, k, &x, &y)) mine = fmaf(x, y, mine);
+    todo = mine == mine;
+  }
+  unsigned long long left = __ballot(todo);
+  while (left) {
+    const int who = __ffsll(left) - 1;
+    left &= left - 1;
+    const auto result = what(who);
+    float sum = 0.f;
+#pragma unroll 1
+    for (int k0 = lane; k0 - lane < terms && !__any(sum != sum); k0 += 256) {
+      float x[4], y[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (k0 + u * 64 >= terms || !term(result, k0 + u * 64, &x[u], &y[u])) x[u] = y[u] = 0.f;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) sum = fmaf(x[u], y[u], sum);
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+    if (lane == who) mine = sum;
+  }
+  return mine;
+}
 
 }  // namespace
 }  // namespace cct

@@ -158,3 +158,44 @@ def test_not_finite_inputs(B, L):
     big = ok & (np.abs(want) > 1e30)
     assert (np.abs(got[big] - want[big]) <= 1e-5 * np.abs(want[big])).all()
     assert rel_err(got[ok & ~big], want[ok & ~big]) <= TOL_F32
+
+
+def not_finite(t, rows, big=3.4e38):
+    t[rows[0]].reshape(-1)[0], t[rows[1]].reshape(-1)[3], t[rows[2]].reshape(-1)[5], t[rows[3]].reshape(-1)[1] = \
+        np.inf, -np.inf, np.nan, big
+    return t
+
+
+def check_not_finite(got, want):
+    assert (np.isnan(got) == np.isnan(want)).all()
+    over = np.abs(want) > np.finfo(np.float32).max
+    assert (np.isinf(got) == (over & ~np.isnan(want))).all()
+    ok = np.isfinite(got)
+    big = ok & (np.abs(want) > 1e30)
+    assert (np.abs(got[big] - want[big]) <= 1e-5 * np.abs(want[big])).all()
+    assert rel_err(got[ok & ~big], want[ok & ~big]) <= TOL_F32
+
+
+@pytest.mark.parametrize("L,lowering", [(FC[2], 0), (FC[4], 0), (POINTWISE[1], 0), (TENSOR[0], 1), (TENSOR[2], 1)],
+                         ids=["fc_n33", "fc_n130", "pointwise", "type1", "type1_stride"])
+def test_not_finite_backward(B, L, lowering):
+    """Both operands of the backward passes: fully connected, 1 x 1, Type 1 backward-data with dy in place."""
+    x, w = not_finite(synth.make_x(L, 5), (0, 1, 1, -1)), not_finite(synth.make_w(L, 5), (3, 7, 9, 12), 1.0)
+    dy = not_finite(synth.make_dy(L, 5), (0, 1, 1, -1))
+    got, names = ran(B, lambda: gpu_backward_data(B, L, w, dy, lowering))
+    assert split(names), names
+    check_not_finite(got, oracle.conv_backward_data(odims(oracle, L), w, dy))
+    if L.K == L.H:
+        (dw, db), names = ran(B, lambda: gpu_backward_weights(B, L, x, dy))
+        assert split(names), names
+        want = oracle.conv_backward_weights(odims(oracle, L), x, dy)
+        check_not_finite(dw, want[0])
+        check_not_finite(db, want[1])
+
+
+@pytest.mark.parametrize("L", [TENSOR[0], TENSOR[2]], ids=["t_small", "t_stride"])
+def test_not_finite_forward_with_the_tensor_in_place(B, L):
+    x, w = not_finite(synth.make_x(L, 5), (0, 1, 1, -1)), not_finite(synth.make_w(L, 5), (3, 7, 9, 12), 1.0)
+    got, names = ran(B, lambda: gpu_forward(B, L, x, w, synth.make_bias(L, 5), 3))
+    assert split(names), names
+    check_not_finite(got, oracle.conv_forward(odims(oracle, L), x, w, synth.make_bias(L, 5)))

@@ -155,6 +155,48 @@ def test_not_finite_inputs(B, L):
     assert rel_err(got[ok & ~big], want[ok & ~big]) <= TOL_F32
 
 
+def check_not_finite(got, want):
+    """got: fp32, want: 64 bits."""
+    assert (np.isnan(got) == np.isnan(want)).all()
+    over = np.abs(want) > np.finfo(np.float32).max
+    assert (np.isinf(got) == (over & ~np.isnan(want))).all()
+    inf = np.isinf(got)
+    assert (np.sign(got[inf]) == np.sign(want[inf])).all()
+    ok = np.isfinite(got)
+    big = ok & (np.abs(want) > 1e30)
+    assert (np.abs(got[big] - want[big]) <= 1e-5 * np.abs(want[big])).all()
+    assert rel_err(got[ok & ~big], want[ok & ~big]) <= TOL_F32
+
+
+@pytest.mark.parametrize("L", [layer("nf_s1", 3, 40, 13, 13, 16, 3, 1, 1), layer("nf_k4", 3, 33, 12, 10, 25, 4, 1, 0),
+                               layer("nf_s2", 3, 20, 21, 23, 48, 3, 2, 1), layer("nf_s4", 3, 3, 31, 33, 32, 11, 4, 0)],
+                         ids=lambda L: L.name)
+def test_not_finite_backward_data(B, L):
+    w, dy = synth.make_w(L, 5), synth.make_dy(L, 5)
+    dy[0, 0, 0, 0], dy[1, 1, 2, 3], dy[1, 2, -1, -1], dy[-1, 1, 1, 1] = np.inf, -np.inf, np.nan, 3.4e38
+    w[3, 1, 1, 2], w[7, 0, 0, 0], w[9, 2, 2, 2] = np.inf, np.nan, 3.4e38
+    got, names = ran(B, lambda: gpu_backward_data(B, L, w, dy, B.LOWER_FUSED))
+    assert any(n.startswith(KERNEL) for n in names), names
+    check_not_finite(got, oracle.conv_backward_data(odims(oracle, L), w, dy))
+
+
+@pytest.mark.parametrize("value", [np.inf, np.nan], ids=["inf", "nan"])
+@pytest.mark.parametrize("L", [layer("d_s1", 3, 40, 13, 13, 40, 3, 1, 1), layer("d_s2", 3, 20, 21, 23, 48, 3, 2, 1)],
+                         ids=lambda L: L.name)
+def test_many_not_finite_values(B, L, value):
+    """Some values everywhere and all of one image: blocks in which many or all results are not finite."""
+    x, w, dy = synth.make_x(L, 5), synth.make_w(L, 5), synth.make_dy(L, 5)
+    for t in (x, dy):
+        t.reshape(-1)[::701] = value
+        t[1] = value
+        t[2] = np.abs(t[2])                    # infinities of one sign there
+    got, names = ran(B, lambda: gpu_forward(B, L, x, w, None, B.LOWER_FUSED))
+    assert any(n.startswith(KERNEL) for n in names), names
+    check_not_finite(got, oracle.conv_forward(odims(oracle, L), x, w, None))
+    check_not_finite(gpu_backward_data(B, L, np.abs(w), dy, B.LOWER_FUSED),
+                     oracle.conv_backward_data(odims(oracle, L), np.abs(w), dy))
+
+
 def test_workspace_for_the_fp32_kernel_matrix_is_still_enough(B):
     """A workspace that holds the fp32 kernel matrix but not its three terms runs the fp32 kernel."""
     import torch
