@@ -38,7 +38,23 @@ bool desc_ok(const cct_conv_desc_t* d) {
   return true;
 }
 
-// Geometry of one lowering layout for one descriptor.
+// How conv_fused_split would run a fused forward / backward-data pass.
+struct SplitPlan {
+  int kind;        // of its pack: 0 forward, 1 flipped, 2 strided backward-data, 3 space to depth
+  int Mpad, Kpad;
+};
+
+// What the rules and estimates answered for a descriptor, layout and pass: asked several times while a call is
+// planned, computed once (a forward call of a small layer spent 0.5 us on planning, 0.2 now).
+struct Asked {
+  int split_plan = -1, img_plan = -1, img = -1, gran = -1;  // -1: not yet
+  double kernel_cost = -1.0, split_cost = -1.0;
+  SplitPlan sp;
+  BwdwImgPlan ip;    // for the whole batch
+  GranulesPlan gp;
+};
+
+// Geometry of one lowering layout for one descriptor; belongs to one pass.
 struct Geom {
   int Hout, Wout, Cg, Og;
   WinMap lower;  // x  <-> D^   (tensor plane H x W)
@@ -47,6 +63,7 @@ struct Geom {
   long long Pc;  // matrix columns (positions) per image
   int Mr;        // rows of R^T per group  = Og*RKi*RKj
   int Kd;        // rows of D^T per group  = Cg*DKi*DKj
+  mutable Asked asked;
 };
 
 Geom make_geom(const cct_conv_desc_t& d, int type) {
@@ -197,11 +214,6 @@ GemmTN fused_bwd_problem(const cct_conv_desc_t& d, const Geom& g, const void* pa
   return p;
 }
 
-// How conv_fused_split would run a fused forward / backward-data pass.
-struct SplitPlan {
-  int kind;        // of its pack: 0 forward, 1 flipped, 2 strided backward-data, 3 space to depth
-  int Mpad, Kpad;
-};
 GemmTN split_problem(const cct_conv_desc_t& d, const Geom& g, const SplitPlan& sp, const void* pack,
                      const float* in, float* out, const float* bias, long long ni) {
   switch (sp.kind) {
@@ -212,7 +224,7 @@ GemmTN split_problem(const cct_conv_desc_t& d, const Geom& g, const SplitPlan& s
   }
 }
 // false = the kernel cannot run this pass of the layer (bf16, or shapes it cannot stage).
-bool split_plan(const cct_conv_desc_t& d, int pass, const Geom& g, SplitPlan* sp) {
+bool find_split_plan(const cct_conv_desc_t& d, int pass, const Geom& g, SplitPlan* sp) {
   if (d.precision != CCT_PREC_F32 || pass == CCT_PASS_BACKWARD_WEIGHTS) return false;
   const int s = d.stride, U = (d.K + s - 1) / s;
   const bool fwd = pass == CCT_PASS_FORWARD;
@@ -238,8 +250,14 @@ bool split_plan(const cct_conv_desc_t& d, int pass, const Geom& g, SplitPlan* sp
   return (s == 2 || s == 4) && U >= 2 && fits(3, g.Og, g.Cg * s * s, U);
 }
 
+bool split_plan(const cct_conv_desc_t& d, int pass, const Geom& g, SplitPlan* sp) {
+  if (g.asked.split_plan < 0) g.asked.split_plan = find_split_plan(d, pass, g, &g.asked.sp);
+  if (g.asked.split_plan) *sp = g.asked.sp;
+  return g.asked.split_plan;
+}
+
 double split_cost(const cct_conv_desc_t& d, int pass, const Geom& g, const SplitPlan& sp);
-double fused_fp32_cost(const cct_conv_desc_t& d, int pass);
+double kernel_cost(const cct_conv_desc_t& d, int pass, int type, const Geom& g);
 
 // Does a fused pass run on conv_fused_split?  An explicit FUSED does wherever it can; AUTO where the
 // estimate says so: with few channels or kernels much of a tile is padding and the fp32 fused kernels do
@@ -247,7 +265,7 @@ double fused_fp32_cost(const cct_conv_desc_t& d, int pass);
 bool use_split(const cct_conv_desc_t& d, int pass, const Geom& g, SplitPlan* sp) {
   if (!split_plan(d, pass, g, sp)) return false;
   if (d.lowering != CCT_LOWER_AUTO || (pass == CCT_PASS_BACKWARD_DATA && d.stride > 1)) return true;
-  return split_cost(d, pass, g, *sp) <= fused_fp32_cost(d, pass);
+  return split_cost(d, pass, g, *sp) <= kernel_cost(d, pass, CCT_LOWER_FUSED, g);
 }
 
 inline int esize(const cct_conv_desc_t& d) { return d.precision == CCT_PREC_BF16_IN_F32_ACC ? 2 : 4; }
@@ -296,7 +314,7 @@ constexpr int kDbiasBlocks = 64;
 // partial products to dw, or rewrites the kernels.
 constexpr int kImgLeastChunk = 32;
 
-double layout_cost(const cct_conv_desc_t& d, int pass, int type);
+double layout_cost(const cct_conv_desc_t& d, int pass, int type, const Geom& g);
 
 // What an estimate of a layout without granules stands for: in bf16 it is 40 % (backward-weights) or a fifth
 // short of what the kernels take, and in fp32 it leaves out the bias gradient's pass over dy.
@@ -312,16 +330,23 @@ double plain_seconds(const cct_conv_desc_t& d, int pass, const Geom& g, double c
 // is chosen (conv3 at batch 1024: 2880 -> 1590 us), at most 15 % slower for single calls under 40 us;
 // it stays off for a single image (conv3: 31 us against 38), 3 channels (conv1 at batch 256: 697 us
 // against 997) and 1 x 1 kernels at stride 2 (they use a quarter of the x that would be rewritten).
-bool bwdw_img_wins(const cct_conv_desc_t& d, int type) {
+bool batch_img_plan(const cct_conv_desc_t& d, const Geom& g) {
+  if (g.asked.img_plan < 0) g.asked.img_plan = bwdw_img_plan(d, d.N, &g.asked.ip);
+  return g.asked.img_plan;
+}
+bool bwdw_img_wins(const cct_conv_desc_t& d, int type, const Geom& g) {
   if (d.lowering != CCT_LOWER_AUTO && !(type == CCT_LOWER_FUSED && d.precision == CCT_PREC_F32)) return false;
-  BwdwImgPlan p;
-  if (!bwdw_img_plan(d, d.N, &p)) return false;
-  const Geom g = make_geom(d, CCT_LOWER_TYPE1);
-  const double cost = layout_cost(d, CCT_PASS_BACKWARD_WEIGHTS, type);
-  // few kernels: Types 2 and 3, which take the taps into the rows, are better than their estimates
-  // (53 images of 41 x 41, two groups of 171 channels and 19 kernels: 259 us against 294)
-  if (d.precision == CCT_PREC_F32 && 2 * g.Og < p.BM) return p.seconds < 0.85 * cost;
-  return p.seconds < plain_seconds(d, CCT_PASS_BACKWARD_WEIGHTS, g, cost);
+  if (g.asked.img >= 0) return g.asked.img;
+  const BwdwImgPlan& p = g.asked.ip;
+  auto wins = [&]() {
+    if (!batch_img_plan(d, g)) return false;
+    const double cost = layout_cost(d, CCT_PASS_BACKWARD_WEIGHTS, type, g);
+    // few kernels: Types 2 and 3, which take the taps into the rows, are better than their estimates
+    // (53 images of 41 x 41, two groups of 171 channels and 19 kernels: 259 us against 294)
+    if (d.precision == CCT_PREC_F32 && 2 * g.Og < p.BM) return p.seconds < 0.85 * cost;
+    return p.seconds < plain_seconds(d, CCT_PASS_BACKWARD_WEIGHTS, g, cost);
+  };
+  return g.asked.img = wins();
 }
 
 // 1 x 1 kernels at stride 1 without padding: every lowering is the identity, so the forward and
@@ -386,11 +411,12 @@ bool tensor_split(const cct_conv_desc_t& d, int pass, int type, const Geom& g, l
 // estimates say that rewriting the tensor once pays.  Measured
 // over 60 layers: 1.05 to 2.8 times as fast where it is chosen; up to about ten images of 13 x 13 the
 // contraction of a lone workgroup is the longer way (256 -> 384 channels, 9 images: 42 us against 53).
-bool granules_win(const cct_conv_desc_t& d, int pass, int type) {
+bool granules_win(const cct_conv_desc_t& d, int pass, int type, const Geom& g) {
   if (d.lowering != CCT_LOWER_AUTO || d.precision != CCT_PREC_BF16_IN_F32_ACC) return false;
-  GranulesPlan p;
-  return granules_plan(d, pass, d.N, &p) &&
-         p.seconds < plain_seconds(d, pass, make_geom(d, type), layout_cost(d, pass, type));
+  if (g.asked.gran < 0)
+    g.asked.gran = granules_plan(d, pass, d.N, &g.asked.gp) &&
+                   g.asked.gp.seconds < plain_seconds(d, pass, g, layout_cost(d, pass, type, g));
+  return g.asked.gran;
 }
 
 // allow_split = false: without conv_fused_split, whose pack takes half as much again as the fp32 one,
@@ -412,9 +438,10 @@ bool make_layout(const cct_conv_desc_t& d, int pass, int type, const Geom& g, lo
   const long long dt_rows = (long long)d.C * g.DKi * g.DKj;
   const long long rt_rows = (long long)d.O * g.RKi * g.RKj;
   L->gran = allow_split && pass != CCT_PASS_BACKWARD_WEIGHTS && nc >= std::min(d.N, kImgLeastChunk) &&
-            granules_win(d, pass, type);
+            granules_win(d, pass, type, g);
   if (L->gran) {
-    if (!granules_plan(d, pass, nc, &L->gp)) return false;
+    if (nc == d.N) L->gp = g.asked.gp;
+    else if (!granules_plan(d, pass, nc, &L->gp)) return false;
     L->total = L->gp.total;
     return true;
   }
@@ -490,8 +517,9 @@ bool make_layout(const cct_conv_desc_t& d, int pass, int type, const Geom& g, lo
     if ((type != CCT_LOWER_TYPE1 || es == 2) && !L->t2_opad)
       take(rt_rows * L->ld * es, &L->rt_off, &L->rt_bytes);
     if (type != CCT_LOWER_TYPE3) take(dt_rows * L->ld * 4, &L->dt_off, &L->dt_bytes);
-  } else if (allow_split && nc >= std::min(d.N, kImgLeastChunk) && bwdw_img_wins(d, type)) {
-    if (!bwdw_img_plan(d, nc, &L->ip)) return false;
+  } else if (allow_split && nc >= std::min(d.N, kImgLeastChunk) && bwdw_img_wins(d, type, g)) {
+    if (nc == d.N) L->ip = g.asked.ip;
+    else if (!bwdw_img_plan(d, nc, &L->ip)) return false;
     L->img = 1;
     off = L->ip.total;
   } else {
@@ -520,12 +548,14 @@ bool make_layout(const cct_conv_desc_t& d, int pass, int type, const Geom& g, lo
   return true;
 }
 
-bool type_supported(const cct_conv_desc_t& d, int pass, int type) {
+// Can the layout run the pass?  Its geometry is in *out then.
+bool type_supported(const cct_conv_desc_t& d, int pass, int type, Geom* out) {
   if (type < CCT_LOWER_TYPE1 || type > CCT_LOWER_FUSED) return false;
+  *out = make_geom(d, type);
   if (d.groups > 65535) return false;  // groups are the second grid dimension of every GEMM launch
   if (type == CCT_LOWER_FUSED) {
     const bool bf16 = d.precision == CCT_PREC_BF16_IN_F32_ACC;
-    const Geom gg = make_geom(d, CCT_LOWER_FUSED);
+    const Geom& gg = *out;
     // backward-weights: the input rows of 32 positions must fit in LDS; an unpadded layer can
     // also gather its lowered rows inside the split-K GEMM (fp32 operands only)
     if (pass == CCT_PASS_BACKWARD_WEIGHTS) {
@@ -561,9 +591,8 @@ bool type_supported(const cct_conv_desc_t& d, int pass, int type) {
       return false;
     if ((long long)d.C * d.H * d.W >= kIntMax) return false;  // 32-bit offsets inside one image
   }
-  const Geom g = make_geom(d, type);
   Layout L;
-  if (!make_layout(d, pass, type, g, 1, &L, pass != CCT_PASS_BACKWARD_WEIGHTS && d.precision == CCT_PREC_F32))
+  if (!make_layout(d, pass, type, *out, 1, &L, pass != CCT_PASS_BACKWARD_WEIGHTS && d.precision == CCT_PREC_F32))
     return false;
   return L.total <= kMaxOneImageBytes;
 }
@@ -586,8 +615,7 @@ constexpr double kFusedGemmFactor = 0.95; // fused kernels vs the GEMM on a mate
 //      + max(t_mfma, t_mem) + 0.3 * min(t_mfma, t_mem),  t_mfma = GEMM flops / MFMA rate,
 //        t_mem = GEMM bytes / GEMM stream rate              (loads mostly overlap the MFMAs)
 //      + launches * launch latency
-double kernel_cost(const cct_conv_desc_t& d, int pass, int type) {
-  const Geom g = make_geom(d, type);
+double find_kernel_cost(const cct_conv_desc_t& d, int pass, int type, const Geom& g) {
   const double es = esize(d);
   const double N = d.N;
   const double cols = N * (double)g.Pc;
@@ -691,50 +719,55 @@ double kernel_cost(const cct_conv_desc_t& d, int pass, int type) {
          launches * kLaunchSec;
 }
 
-double fused_fp32_cost(const cct_conv_desc_t& d, int pass) {
-  return kernel_cost(d, pass, CCT_LOWER_FUSED);
+double kernel_cost(const cct_conv_desc_t& d, int pass, int type, const Geom& g) {
+  if (g.asked.kernel_cost < 0) g.asked.kernel_cost = find_kernel_cost(d, pass, type, g);
+  return g.asked.kernel_cost;
 }
 double split_cost(const cct_conv_desc_t& d, int pass, const Geom& g, const SplitPlan& sp) {
-  const GemmTN q = split_problem(d, g, sp, nullptr, nullptr, nullptr, nullptr, 1);
-  const double bytes = 4.0 * d.N * ((double)d.C * d.H * d.W + (double)d.O * g.Hout * g.Wout);
-  return std::max(conv_fused_split_seconds(q, d.N), bytes / kGemmBytesPerSec) + 2.0 * kLaunchSec;
+  if (g.asked.split_cost < 0) {
+    const GemmTN q = split_problem(d, g, sp, nullptr, nullptr, nullptr, nullptr, 1);
+    const double bytes = 4.0 * d.N * ((double)d.C * d.H * d.W + (double)d.O * g.Hout * g.Wout);
+    g.asked.split_cost = std::max(conv_fused_split_seconds(q, d.N), bytes / kGemmBytesPerSec) + 2.0 * kLaunchSec;
+  }
+  return g.asked.split_cost;
 }
 // The same with the faster of the kernels that FUSED has for an fp32 forward / backward-data pass.
-double layout_cost(const cct_conv_desc_t& d, int pass, int type) {
-  const double c = kernel_cost(d, pass, type);
+double layout_cost(const cct_conv_desc_t& d, int pass, int type, const Geom& g) {
+  const double c = kernel_cost(d, pass, type, g);
   if (type != CCT_LOWER_FUSED) return c;
-  const Geom g = make_geom(d, type);
   SplitPlan sp;
   if (!split_plan(d, pass, g, &sp)) return c;
   const double s = split_cost(d, pass, g, sp);
   return pass == CCT_PASS_BACKWARD_DATA && d.stride > 1 ? s : std::min(c, s);
 }
 // ... and with the one for an fp32 backward-weights pass.
-double model_cost(const cct_conv_desc_t& d, int pass, int type) {
-  const double c = layout_cost(d, pass, type);
-  BwdwImgPlan p;
+double model_cost(const cct_conv_desc_t& d, int pass, int type, const Geom& g) {
+  const double c = layout_cost(d, pass, type, g);
   if (pass == CCT_PASS_BACKWARD_WEIGHTS && type == CCT_LOWER_FUSED && d.precision == CCT_PREC_F32 &&
-      bwdw_img_plan(d, d.N, &p))
-    return std::min(c, p.seconds);
+      batch_img_plan(d, g))
+    return std::min(c, g.asked.ip.seconds);
   return c;
 }
 
-int pick(const cct_conv_desc_t& d, int pass) {
-  if (d.K == 1 && d.stride == 1 && d.pad == 0 && type_supported(d, pass, CCT_LOWER_TYPE1))
+// The layout that AUTO runs (0: none) and its geometry.
+int pick(const cct_conv_desc_t& d, int pass, Geom* out) {
+  if (d.K == 1 && d.stride == 1 && d.pad == 0 && type_supported(d, pass, CCT_LOWER_TYPE1, out))
     return CCT_LOWER_TYPE1;
   // one output pixel per image (a fully connected layer): every lowering is a reshape of x, and
   // AUTO / TYPE1 run it as plain matrix products (fully_connected.hip)
   if (d.K == d.H && d.K == d.W && d.pad == 0 && d.groups == 1 && d.precision == CCT_PREC_F32 &&
-      type_supported(d, pass, CCT_LOWER_TYPE1))
+      type_supported(d, pass, CCT_LOWER_TYPE1, out))
     return CCT_LOWER_TYPE1;
   int best = 0;
   double best_cost = 0.0;
+  Geom g;
   for (int t = CCT_LOWER_TYPE1; t <= CCT_LOWER_FUSED; ++t) {
-    if (!type_supported(d, pass, t)) continue;
-    const double c = model_cost(d, pass, t);
+    if (!type_supported(d, pass, t, &g)) continue;
+    const double c = model_cost(d, pass, t, g);
     if (!best || c < best_cost) {
       best = t;
       best_cost = c;
+      *out = g;
     }
   }
   return best;
@@ -744,16 +777,9 @@ int pick(const cct_conv_desc_t& d, int pass) {
 int resolve(const cct_conv_desc_t* desc, int pass, int* type, Geom* g) {
   if (!desc_ok(desc)) return CCT_EINVAL;
   if (pass < CCT_PASS_FORWARD || pass > CCT_PASS_BACKWARD_WEIGHTS) return CCT_EINVAL;
-  int t = desc->lowering;
-  if (t == CCT_LOWER_AUTO) {
-    t = pick(*desc, pass);
-    if (!t) return CCT_EUNSUPPORTED;
-  } else if (!type_supported(*desc, pass, t)) {
-    return CCT_EUNSUPPORTED;
-  }
-  *type = t;
-  *g = make_geom(*desc, t);
-  return CCT_OK;
+  *type = desc->lowering;
+  if (*type == CCT_LOWER_AUTO) return (*type = pick(*desc, pass, g)) ? CCT_OK : CCT_EUNSUPPORTED;
+  return type_supported(*desc, pass, *type, g) ? CCT_OK : CCT_EUNSUPPORTED;
 }
 
 long long default_chunk(const cct_conv_desc_t& d, int pass, int type, const Geom& g) {
@@ -781,12 +807,15 @@ long long chunk_for_workspace(const cct_conv_desc_t& d, int pass, int type, cons
   // some size
   const bool granules = split && (pass == CCT_PASS_BACKWARD_WEIGHTS || d.precision != CCT_PREC_F32);
   long long lo = granules ? std::min(d.N, kImgLeastChunk) : 1, hi = d.N;
-  if (!fits(lo)) {
-    split = false;
-    lo = 1;
-  }
-  if (!fits(lo)) return 0;
   if (fits(hi)) return hi;
+  if (!fits(lo)) {
+    lo = 1;
+    if (split) {
+      split = false;
+      if (fits(hi)) return hi;
+    }
+    if (!fits(lo)) return 0;
+  }
   while (lo < hi) {
     const long long mid = (lo + hi + 1) / 2;
     if (fits(mid)) lo = mid; else hi = mid - 1;
@@ -808,16 +837,17 @@ double fused_bf16_seconds(const cct_conv_desc_t& d, int pass, const Geom& g) {
 }
 
 // Estimated time of the whole batch in chunks of nc images on layout L.
-double chunked_seconds(const cct_conv_desc_t& d, int pass, int type, const Geom& g, const Layout& L, long long nc) {
+double chunked_seconds(const cct_conv_desc_t& d, int pass, int type, const Layout& L, long long nc) {
   cct_conv_desc_t c = d;
   c.N = (int)nc;
+  const Geom g = make_geom(c, type);
   double one;
   BwdwImgPlan ip;
   if (L.gran) one = L.gp.seconds;
   else if (L.img) one = bwdw_img_plan(c, nc, &ip) ? ip.seconds : 1.0;
   else if (L.split) one = split_cost(c, pass, g, L.sp);
   else if (type == CCT_LOWER_FUSED && d.precision != CCT_PREC_F32) one = fused_bf16_seconds(c, pass, g);
-  else one = plain_seconds(c, pass, g, kernel_cost(c, pass, type));
+  else one = plain_seconds(c, pass, g, kernel_cost(c, pass, type, g));
   return (double)((d.N + nc - 1) / nc) * one;
 }
 
@@ -829,12 +859,12 @@ double chunked_seconds(const cct_conv_desc_t& d, int pass, int type, const Geom&
 long long layout_for_workspace(const cct_conv_desc_t& d, int pass, size_t bytes, int* type, Geom* g, Layout* L) {
   long long nc = chunk_for_workspace(d, pass, *type, *g, bytes, L);
   if (nc == d.N || (nc > 0 && nc >= default_chunk(d, pass, *type, *g))) return nc;
-  double best = nc > 0 ? chunked_seconds(d, pass, *type, *g, *L, nc) : 0.0;
+  double best = nc > 0 ? chunked_seconds(d, pass, *type, *L, nc) : 0.0;
   auto consider = [&](int t, const Geom& tg, bool split) {
     Layout tl;
     const long long n = chunk_for_workspace(d, pass, t, tg, bytes, &tl, split);
     if (n < 1) return;
-    const double s = chunked_seconds(d, pass, t, tg, tl, n);
+    const double s = chunked_seconds(d, pass, t, tl, n);
     if (nc < 1 || s < best) {
       best = s;
       nc = n;
@@ -844,11 +874,14 @@ long long layout_for_workspace(const cct_conv_desc_t& d, int pass, size_t bytes,
     }
   };
   const int picked = *type;
+  Geom tg;
   for (int t = CCT_LOWER_TYPE1; t <= CCT_LOWER_FUSED; ++t) {
-    if (t != picked && (d.lowering != CCT_LOWER_AUTO || !type_supported(d, pass, t))) continue;
-    const Geom tg = make_geom(d, t);
-    if (t != picked) consider(t, tg, true);
-    consider(t, tg, false);
+    if (t == picked) {
+      consider(t, make_geom(d, t), false);
+    } else if (d.lowering == CCT_LOWER_AUTO && type_supported(d, pass, t, &tg)) {
+      consider(t, tg, true);
+      consider(t, tg, false);
+    }
   }
   return nc;
 }
@@ -922,7 +955,8 @@ int cct_lowered_ld(const cct_conv_desc_t* desc, cct_lowering_t lowering, int64_t
 int cct_pick_lowering(const cct_conv_desc_t* desc, cct_pass_t pass, cct_lowering_t* picked) {
   if (!desc_ok(desc) || !picked) return CCT_EINVAL;
   if (pass < CCT_PASS_FORWARD || pass > CCT_PASS_BACKWARD_WEIGHTS) return CCT_EINVAL;
-  const int t = pick(*desc, pass);
+  Geom g;
+  const int t = pick(*desc, pass, &g);
   if (!t) return CCT_EUNSUPPORTED;
   *picked = (cct_lowering_t)t;
   return CCT_OK;
@@ -933,8 +967,9 @@ int cct_lowering_cost(const cct_conv_desc_t* desc, cct_pass_t pass, cct_lowering
   if (!desc_ok(desc) || !seconds) return CCT_EINVAL;
   if (pass < CCT_PASS_FORWARD || pass > CCT_PASS_BACKWARD_WEIGHTS) return CCT_EINVAL;
   if (lowering < CCT_LOWER_TYPE1 || lowering > CCT_LOWER_FUSED) return CCT_EINVAL;
-  if (!type_supported(*desc, pass, lowering)) return CCT_EUNSUPPORTED;
-  *seconds = model_cost(*desc, pass, lowering);
+  Geom g;
+  if (!type_supported(*desc, pass, lowering, &g)) return CCT_EUNSUPPORTED;
+  *seconds = model_cost(*desc, pass, lowering, g);
   return CCT_OK;
 }
 

@@ -277,11 +277,14 @@ void set_hip_error(hipError_t e);
 class ProfScope {
  public:
   ProfScope(const char* name, double flops, double bytes, hipStream_t st);
+  // The name as for printf, written only while recording: formatting it took 0.2 us of every launch.
+  ProfScope(double flops, double bytes, hipStream_t st, const char* format, ...) __attribute__((format(printf, 5, 6)));
   ~ProfScope();
   ProfScope(const ProfScope&) = delete;
   ProfScope& operator=(const ProfScope&) = delete;
 
  private:
+  void start(const char* name, double flops, double bytes);
   hipStream_t st_;
   long long idx_;
 };

@@ -17,8 +17,6 @@
 // changes from chunk to chunk uniform: a thread owns fixed cells of the plane and fixed dy rows,
 // its byte offsets never change, and the chunk's row / image / position enters through the base
 // and the scalar offset of buffer loads, whose range check also supplies the zeros of the padding.
-#include <stdio.h>
-
 #include "cct_internal.h"
 #include "gemm_common.h"
 
@@ -400,12 +398,10 @@ int launch_variant(const ConvBwdW& p, BwdwGeom fg, size_t lds, hipStream_t st) {
   if (tiles <= 0 || p.S < 1 || tiles * p.S >= 2147483647LL || p.G > 65535) return CCT_EUNSUPPORTED;
   if (p.split_len % BK) return CCT_EINVAL;
   dim3 grid((unsigned)(tiles * p.S), (unsigned)p.G);
-  char name[96];
-  snprintf(name, sizeof(name), "conv_bwdw_fused_f32<%d, %d, %d, %d, %d>", BM, WM, WN, fg.V, fg.XR);
-  ProfScope ps(name, 2.0 * fg.M * fg.N * (double)fg.ncols * p.G,
+  ProfScope ps(2.0 * fg.M * fg.N * (double)fg.ncols * p.G,
                4.0 * ((double)p.nimg * p.C * p.H * p.W + (double)p.nimg * p.O * fg.P +
                       (double)fg.M * fg.N * p.S * p.G),
-               st);
+               st, "conv_bwdw_fused_f32<%d, %d, %d, %d, %d>", BM, WM, WN, fg.V, fg.XR);
   int rc;
   if (fg.V == 2)
     rc = launch_kernel<BM, WM, WN, 2, 8>(p, fg, lds, grid, tiles_m, tiles_n, st);

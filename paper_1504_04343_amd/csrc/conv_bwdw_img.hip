@@ -21,8 +21,6 @@
 // instructions, or bf16 lowered matrices): conv3 at batch 1024 2880 -> 1590 us, of it 1290 the product
 // (237 TFLOP/s of fp32 results, 1420 of bf16 MFMAs: the matrix cores' rate here) and 300 the rewriting
 // (3.7 TB/s); conv2 at batch 256 1215 -> 700; conv4 at batch 256 with bf16 operands 355 -> 125.
-#include <stdio.h>
-
 #include <algorithm>
 
 #include "cct_internal.h"
@@ -491,9 +489,8 @@ int launch_bwdw_img(const cct_conv_desc_t& d, const BwdwImgPlan& P, int nimg, co
   const long long blocks = (long long)q.tiles_m * q.tiles_n * q.S;
   if (blocks <= 0 || blocks >= 2147483647LL || d.groups > 65535) return CCT_EUNSUPPORTED;
   {
-    char name[96];
-    snprintf(name, sizeof(name), "conv_bwdw_img<%d, %d, %d>", P.BM, P.terms, P.terms == 1 ? 8 : P.BM == 128 ? 12 : 6);
-    ProfScope ps(name, 2.0 * yn * Cg * KK, 2.0 * P.terms * (xn + yn) + 4.0 * q.S * (double)d.O * q.N, st);
+    ProfScope ps(2.0 * yn * Cg * KK, 2.0 * P.terms * (xn + yn) + 4.0 * q.S * (double)d.O * q.N, st,
+                 "conv_bwdw_img<%d, %d, %d>", P.BM, P.terms, P.terms == 1 ? 8 : P.BM == 128 ? 12 : 6);
     const dim3 grid((unsigned)blocks, (unsigned)d.groups);
     int rc;
     if (P.BM == 128)

@@ -13,8 +13,6 @@
 // are in flight while the current 16 are multiplied); when all channels of a group number 16 or
 // fewer they are staged once.  The kernel matrix K^ goes through the same double-buffered LDS
 // tiles as in the plain GEMM, and the epilogue is the Type-1 lifting + bias add.
-#include <stdio.h>
-
 #include "cct_internal.h"
 #include "gemm_common.h"
 
@@ -358,11 +356,10 @@ int launch_variant(const GemmTN& p, const FusedGeom& fg, bool ring, size_t lds, 
   const long long blocks = (long long)tiles_m * tiles_n;
   if (blocks <= 0 || blocks >= 2147483647LL || p.G > 65535) return CCT_EUNSUPPORTED;
   dim3 grid((unsigned)blocks, (unsigned)p.G);
-  char name[96];
-  snprintf(name, sizeof(name), "conv_fused_f32<%d, %d, %d, %s>", BM, WM, WN, ring ? "true" : "false");
   const double x_bytes = 4.0 * ((double)p.Ncols / (p.gHout * p.gWout)) * p.gC * p.gH * p.gW;
-  ProfScope ps(name, 2.0 * p.M * p.Ncols * p.Kdim * p.G,
-               x_bytes + 4.0 * ((double)p.M * p.Ncols + (double)p.M * p.Kdim) * p.G, st);
+  ProfScope ps(2.0 * p.M * p.Ncols * p.Kdim * p.G,
+               x_bytes + 4.0 * ((double)p.M * p.Ncols + (double)p.M * p.Kdim) * p.G, st,
+               "conv_fused_f32<%d, %d, %d, %s>", BM, WM, WN, ring ? "true" : "false");
   constexpr int kLdsCap = 80 * 1024;  // what launch_conv_fused admits
   if (ring) {
     constexpr auto kern = conv_fused_f32<BM, WM, WN, true>;

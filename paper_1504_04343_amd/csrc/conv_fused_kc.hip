@@ -30,8 +30,6 @@
 //   - reduction index q*8 + half*4 + e goes to MFMA (q, e), lane half `half`, on both sides;
 //   - epilogue = Type-1 lifting + bias, as in the plain GEMM, or the depth-to-space store of a
 //     strided backward-data pass.
-#include <stdio.h>
-
 #include <algorithm>
 
 #include "cct_internal.h"
@@ -456,13 +454,12 @@ int launch_variant(const GemmTN& p, const KcGeom& fg, size_t lds, hipStream_t st
   if (blocks <= 0 || blocks >= 2147483647LL || p.G > 65535) return CCT_EUNSUPPORTED;
   const int tiles_n = (int)tn;
   dim3 grid((unsigned)blocks, (unsigned)p.G);
-  char name[96];
-  snprintf(name, sizeof(name), "conv_fused_kc_f32<%d, %d, %d>%s", BM, WM, WN, p.d2s ? " strided" : "");
   const double nimg = (double)p.Ncols / (p.gHout * p.gWout);
   const double x_bytes = 4.0 * nimg * p.gC * p.gH * p.gW;
   const double y_bytes = p.d2s ? 4.0 * nimg * p.dCtot * p.dH * p.dW : 4.0 * (double)p.M * p.Ncols * p.G;
-  ProfScope ps(name, p.prof_flops > 0 ? p.prof_flops : 2.0 * p.M * p.Ncols * p.Kdim * p.G,
-               x_bytes + y_bytes + 4.0 * (double)p.M * p.Kdim * p.G, st);
+  ProfScope ps(p.prof_flops > 0 ? p.prof_flops : 2.0 * p.M * p.Ncols * p.Kdim * p.G,
+               x_bytes + y_bytes + 4.0 * (double)p.M * p.Kdim * p.G, st,
+               "conv_fused_kc_f32<%d, %d, %d>%s", BM, WM, WN, p.d2s ? " strided" : "");
   constexpr auto kern = conv_fused_kc_f32<BM, WM, WN>;
   if (const int rc = ensure_dynamic_lds<kern>(kLdsCap)) return rc;
   hipLaunchKernelGGL(kern, grid, dim3(NT), lds, st, p, fg, tiles_m, tiles_n);

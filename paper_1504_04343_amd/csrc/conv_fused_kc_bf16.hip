@@ -15,8 +15,6 @@
 // in the scalar offset of a buffer load), the B operand is one 16-byte LDS read per block and tap,
 // and the workgroup synchronises once per channel group (when the next group's cells are
 // published), not once per tile.
-#include <stdio.h>
-
 #include <algorithm>
 
 #include "cct_internal.h"
@@ -346,13 +344,12 @@ int launch_variant(const GemmTN& p, const KcGeom& fg, size_t lds, hipStream_t st
   if (blocks <= 0 || blocks >= 2147483647LL || p.G > 65535) return CCT_EUNSUPPORTED;
   const int tiles_n = (int)tn;
   dim3 grid((unsigned)blocks, (unsigned)p.G);
-  char name[96];
-  snprintf(name, sizeof(name), "conv_fused_kc_bf16<%d, %d, %d>%s", BM, WM, WN, p.d2s ? " strided" : "");
   const double nimg = (double)p.Ncols / (p.gHout * p.gWout);
   const double x_bytes = 4.0 * nimg * p.gC * p.gH * p.gW;
   const double y_bytes = p.d2s ? 4.0 * nimg * p.dCtot * p.dH * p.dW : 4.0 * (double)p.M * p.Ncols * p.G;
-  ProfScope ps(name, p.prof_flops > 0 ? p.prof_flops : 2.0 * p.M * p.Ncols * p.Kdim * p.G,
-               x_bytes + y_bytes + 2.0 * (double)p.M * p.Kdim * p.G, st);
+  ProfScope ps(p.prof_flops > 0 ? p.prof_flops : 2.0 * p.M * p.Ncols * p.Kdim * p.G,
+               x_bytes + y_bytes + 2.0 * (double)p.M * p.Kdim * p.G, st,
+               "conv_fused_kc_bf16<%d, %d, %d>%s", BM, WM, WN, p.d2s ? " strided" : "");
   constexpr auto kern = conv_fused_kc_bf16<BM, WM, WN>;
   if (const int rc = ensure_dynamic_lds<kern>(kLdsCap)) return rc;
   hipLaunchKernelGGL(kern, grid, dim3(NT), lds, st, p, fg, tiles_m, tiles_n);

@@ -23,8 +23,6 @@
 //   - S: 1 = the tensor itself; 2, 4 = space to depth: the padded input is read as a tensor of S*S
 //     times as many channels on a grid S times as coarse (channel = (ci, dh, dw)), which turns a
 //     layer of stride S into an unpadded one of stride 1 with ceil(K/S) taps.
-#include <stdio.h>
-
 #include <algorithm>
 #include <cmath>
 
@@ -699,13 +697,12 @@ int launch_variant(const GemmTN& p, const KcGeom& fg, size_t lds, hipStream_t st
   const long long blocks = (long long)tiles_m * tn;
   if (blocks <= 0 || blocks >= 2147483647LL || p.G > 65535) return CCT_EUNSUPPORTED;
   dim3 grid((unsigned)blocks, (unsigned)p.G);
-  char name[96];
-  snprintf(name, sizeof(name), "conv_fused_split<%d, %d, %d>%s", WAVES_M, KT, S, p.d2s ? " strided" : "");
   const double nimg = (double)p.Ncols / (p.gHout * p.gWout);
   const double x_bytes = 4.0 * nimg * p.x_img;
   const double y_bytes = p.d2s ? 4.0 * nimg * p.dCtot * p.dH * p.dW : 4.0 * (double)p.M * p.Ncols * p.G;
-  ProfScope ps(name, p.prof_flops > 0 ? p.prof_flops : 2.0 * p.M * p.Ncols * p.Kdim * p.G,
-               x_bytes + y_bytes + 4.0 * (double)p.M * p.Kdim * p.G, st);
+  ProfScope ps(p.prof_flops > 0 ? p.prof_flops : 2.0 * p.M * p.Ncols * p.Kdim * p.G,
+               x_bytes + y_bytes + 4.0 * (double)p.M * p.Kdim * p.G, st,
+               "conv_fused_split<%d, %d, %d>%s", WAVES_M, KT, S, p.d2s ? " strided" : "");
   constexpr auto kern = conv_fused_split<WAVES_M, KT, S>;
   if (const int rc = ensure_dynamic_lds<kern>(2 * kLdsCap)) return rc;
   hipLaunchKernelGGL(kern, grid, dim3(NT), lds, st, p, fg, tiles_m, (int)tn);

@@ -11,8 +11,6 @@
 // Measured at batch 256, the pass with its rewriting: conv4 (57.4 GFLOP) forward 170 -> 113 us (of it 88 the
 // product, 650 TFLOP/s), backward-data 157 -> 95; conv2 (115 GFLOP) 244 -> 227 and 251 -> 221; a 1 x 1 layer,
 // 69 images of 42 x 42, 452 -> 58 channels, 175 -> 95 and 174 -> 74.
-#include <stdio.h>
-
 #include <algorithm>
 
 #include "cct_internal.h"
@@ -241,10 +239,8 @@ int launch_granules(const cct_conv_desc_t& d, int pass, const GranulesPlan& P, i
   make_fastdiv_parts(d.K, &p.mK, &p.sK);
   const long long tiles = (long long)p.tiles_m * p.tiles_n;
   if (tiles <= 0 || tiles >= 2147483647LL || d.groups > 65535) return CCT_EUNSUPPORTED;
-  char name[96];
-  snprintf(name, sizeof(name), "conv_granules<%d>", P.BM);
-  ProfScope ps(name, 2.0 * c.M * (double)p.npos * c.Cg * KK * d.groups,
-               16.0 * q.x_total + 4.0 * p.out_img * nimg + 16.0 * kg, st);
+  ProfScope ps(2.0 * c.M * (double)p.npos * c.Cg * KK * d.groups,
+               16.0 * q.x_total + 4.0 * p.out_img * nimg + 16.0 * kg, st, "conv_granules<%d>", P.BM);
   const dim3 grid((unsigned)tiles, (unsigned)d.groups);
   return P.BM == 128 ? launch_product<128>(p, grid, st) : launch_product<64>(p, grid, st);
 }

@@ -147,8 +147,9 @@ bool fc_plan_split(const cct_conv_desc_t& d, int pass, long long max_bytes, long
   p.bmap = ColMap{kIntMax, 0};
   // a split of S, the number of them, and their workspace (backward-data: room for a number of equal
   // splits where there is one)
-  auto len = [&](long long S) { return S == 1 ? Kd : align_up((Kd + S - 1) / S, 32); };
-  auto count = [&](long long S) { return (Kd + len(S) - 1) / len(S); };
+  // (Kd < 2^31: 32-bit divisions, this runs for every number of splits of every call)
+  auto len = [&](long long S) { return S == 1 ? Kd : align_up(((unsigned)Kd + (unsigned)S - 1) / (unsigned)S, 32); };
+  auto count = [&](long long S) -> long long { return ((unsigned)Kd + (unsigned)len(S) - 1) / (unsigned)len(S); };
   auto room = [&](long long S) {
     const long long n = count(S);
     for (long long v = n; !fwd && v < 2 * n; ++v)
@@ -173,10 +174,9 @@ bool fc_plan_split(const cct_conv_desc_t& d, int pass, long long max_bytes, long
   long long S = 1;
   if (!bwdw) {
     double best = need(1) <= cap ? seconds(1) : 1e30;
-    for (long long sp = 2; sp <= 64 && Kd / sp >= kFcMinSplitRows; ++sp) {
-      if ((sp > 16 && sp % 4) || need(sp) > cap) continue;
+    for (int sp = 2; sp <= 64 && Kd >= (long long)sp * kFcMinSplitRows; sp += sp < 16 ? 1 : 4) {
       const double t = seconds(sp);
-      if (t < best) {
+      if (t < best && need(sp) <= cap) {
         best = t;
         S = sp;
       }

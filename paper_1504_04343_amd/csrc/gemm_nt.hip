@@ -9,8 +9,6 @@
 // Both operands are contiguous along the reduction dimension, and they stay that way in LDS
 // ([row][k], rows padded by 4 floats): no transposition anywhere, 16-byte global loads, LDS
 // writes and LDS reads.
-#include <stdio.h>
-
 #include "cct_internal.h"
 #include "gemm_common.h"
 
@@ -463,12 +461,10 @@ int launch_bf16(const GemmNT& p, hipStream_t st) {
       reinterpret_cast<uintptr_t>(p.A) % 16 || reinterpret_cast<uintptr_t>(p.B) % 16)
     return CCT_EINVAL;
   dim3 grid((unsigned)(tiles * p.S), (unsigned)p.G);
-  char name[96];
-  snprintf(name, sizeof(name), "gemm_nt_bf16<%d, %d, %d, %d, %d>", BM, BN, BK, WM, WN);
-  ProfScope ps(name, 2.0 * p.M * p.N * p.Ncols * p.G,
+  ProfScope ps(2.0 * p.M * p.N * p.Ncols * p.G,
                (2.0 * ((double)p.M * p.Ncols + (double)p.N * p.Ncols) + 4.0 * (double)p.M * p.N * p.S) *
                    p.G,
-               st);
+               st, "gemm_nt_bf16<%d, %d, %d, %d, %d>", BM, BN, BK, WM, WN);
   hipLaunchKernelGGL((gemm_nt_bf16<BM, BN, BK, WM, WN>), grid, dim3(NT), 0, st, p, tiles_m, tiles_n);
   CCT_CHECK_LAUNCH();
   return CCT_OK;
@@ -482,7 +478,6 @@ int launch_f32(const GemmNT& p, hipStream_t st) {
   if (tiles <= 0 || p.S < 1 || tiles * p.S >= 2147483647LL || p.G > 65535) return CCT_EUNSUPPORTED;
   if (p.split_len % BK) return CCT_EINVAL;
   dim3 grid((unsigned)(tiles * p.S), (unsigned)p.G);
-  char name[96];
   NtGather ng;
   memset(&ng, 0, sizeof(ng));
   if (p.gather) {
@@ -497,10 +492,10 @@ int launch_f32(const GemmNT& p, hipStream_t st) {
     make_fastdiv_parts(p.gWout, &ng.mWout, &ng.sWout);
     make_fastdiv_parts(p.gK * p.gK, &ng.mKK, &ng.sKK);
     make_fastdiv_parts(p.gK, &ng.mK, &ng.sK);
-    snprintf(name, sizeof(name), "gemm_nt_f32<%d, %d, %d, %d, %d, gather>", BM, BN, BK, WM, WN);
     const double x_bytes = 4.0 * ((double)p.Ncols / P) * p.gC * p.gH * p.gW;
-    ProfScope ps(name, 2.0 * p.M * p.N * p.Ncols * p.G,
-                 x_bytes + 4.0 * ((double)p.M * p.Ncols + (double)p.M * p.N * p.S) * p.G, st);
+    ProfScope ps(2.0 * p.M * p.N * p.Ncols * p.G,
+                 x_bytes + 4.0 * ((double)p.M * p.Ncols + (double)p.M * p.N * p.S) * p.G, st,
+                 "gemm_nt_f32<%d, %d, %d, %d, %d, gather>", BM, BN, BK, WM, WN);
     hipLaunchKernelGGL((gemm_nt_f32<BM, BN, BK, WM, WN, false, true>), grid, dim3(NT), 0, st, p, ng,
                        tiles_m, tiles_n);
     CCT_CHECK_LAUNCH();
@@ -510,11 +505,9 @@ int launch_f32(const GemmNT& p, hipStream_t st) {
   if (p.b_ns % 4 || p.b_gs % 4 || reinterpret_cast<uintptr_t>(p.B) % 16) return CCT_EINVAL;
   const bool avec = p.amap.P == 2147483647 && p.a_ms % 4 == 0 && p.a_gs % 4 == 0 &&
                     reinterpret_cast<uintptr_t>(p.A) % 16 == 0;
-  snprintf(name, sizeof(name), "gemm_nt_f32<%d, %d, %d, %d, %d, %s>", BM, BN, BK, WM, WN,
-           avec ? "true" : "false");
-  ProfScope ps(name, 2.0 * p.M * p.N * p.Ncols * p.G,
+  ProfScope ps(2.0 * p.M * p.N * p.Ncols * p.G,
                4.0 * ((double)p.M * p.Ncols + (double)p.N * p.Ncols + (double)p.M * p.N * p.S) * p.G,
-               st);
+               st, "gemm_nt_f32<%d, %d, %d, %d, %d, %s>", BM, BN, BK, WM, WN, avec ? "true" : "false");
   if (avec)
     hipLaunchKernelGGL((gemm_nt_f32<BM, BN, BK, WM, WN, true, false>), grid, dim3(NT), 0, st, p, ng,
                        tiles_m, tiles_n);

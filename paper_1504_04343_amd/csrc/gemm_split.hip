@@ -19,8 +19,6 @@
 // Measured (before: fp32 matrix instructions): fc6 at batch 256, 19.3 GFLOP, forward 195 -> 117 us,
 // backward-weights 192 -> 126; one image of fc6 (151 MB of w) 50 -> 36 us; 1 x 1 kernels, 128 images of
 // 28 x 28, 256 -> 64 channels, 52 -> 41 us.
-#include <stdio.h>
-
 #include <algorithm>
 
 #include "cct_internal.h"
@@ -371,10 +369,9 @@ int launch_variant(const GemmTN& p, int Ktotal, hipStream_t st) {
   const int tiles_m = p.Mpad / (32 * WAVES_M), tiles_n = (p.Ncols + BN - 1) / BN;
   const long long blocks = (long long)tiles_m * tiles_n;
   if (blocks <= 0 || blocks >= 2147483647LL || p.G < 1 || p.G > 65535) return CCT_EUNSUPPORTED;
-  char name[96];
-  snprintf(name, sizeof(name), "gemm_split<%d, %s>", 32 * WAVES_M, BT ? "k-contiguous" : "in place");
   const double mk = (double)p.M * p.Kdim * p.G, kn = (double)p.Kdim * p.Ncols * p.G;
-  ProfScope ps(name, 2.0 * p.M * kn, 6.0 * mk + 4.0 * kn + 4.0 * (double)p.M * p.Ncols * p.G, st);
+  ProfScope ps(2.0 * p.M * kn, 6.0 * mk + 4.0 * kn + 4.0 * (double)p.M * p.Ncols * p.G, st,
+               "gemm_split<%d, %s>", 32 * WAVES_M, BT ? "k-contiguous" : "in place");
   hipLaunchKernelGGL((gemm_split<WAVES_M, BT, DIRECT>), dim3((unsigned)blocks, (unsigned)p.G), dim3(NT), 0, st, p, Ktotal,
                      tiles_m, tiles_n);
   CCT_CHECK_LAUNCH();
@@ -402,7 +399,8 @@ bool gemm_split_fits(const GemmTN& p, bool bt) {
 // backward-weights product, 135 against 149).
 int gemm_split_bm(int Mpad, long long tiles_n, int K, int G) {
   int BM = Mpad % 128 == 0 && K > 128 ? 128 : Mpad % 64 == 0 ? 64 : 32;
-  while (BM > 32 && tiles_n * (Mpad / BM) * G < 256) BM /= 2;
+  long long wgs = tiles_n * ((unsigned)Mpad / (unsigned)BM) * G;
+  for (; BM > 32 && wgs < 256; BM /= 2) wgs *= 2;
   return BM;
 }
 
@@ -412,10 +410,12 @@ int gemm_split_bm(int Mpad, long long tiles_n, int K, int G) {
 double gemm_split_seconds(int Mpad, int K, long long cols, long long G) {
   const long long tiles_n = (cols + BN - 1) / BN;
   const int BM = gemm_split_bm(Mpad, tiles_n, K, (int)G);
-  const long long wgs = tiles_n * (Mpad / BM) * G, slots = BM == 128 ? 512 : 1024;
-  const double stage = 2.0 * BM * BN * 32 / ((BM == 128 ? 230.0e12 : BM == 64 ? 200.0e12 : 120.0e12) / slots);
-  const double rounds = (double)((wgs + slots - 1) / slots);
-  const double share = std::min(1.0, 0.3 + 0.7 * (double)((wgs + 255) / 256) / (slots / 256));
+  const int log_bm = BM == 128 ? 7 : BM == 64 ? 6 : 5, log_slots = BM == 128 ? 9 : 10;
+  const unsigned long long wgs = (unsigned long long)tiles_n * (Mpad >> log_bm) * G, slots = 1ULL << log_slots;
+  const double flops = BM == 128 ? 1.0 / 230.0e12 : BM == 64 ? 1.0 / 200.0e12 : 1.0 / 120.0e12;
+  const double stage = 2.0 * BM * BN * 32 * flops * (double)slots;
+  const double rounds = (double)((wgs + slots - 1) >> log_slots);
+  const double share = std::min(1.0, 0.3 + 0.7 * (double)((wgs + 255) >> 8) * (256.0 / (double)slots));
   return rounds * ((K + 31) / 32 * stage * share + 4.0e-6);
 }
 

@@ -12,8 +12,6 @@
 // v_mfma_f32_32x32x8_bf16_1k (bf16 operands) with fp32 accumulators.  K is walked in steps
 // of BK through a double-buffered LDS stage; the global loads of step t+1 are issued before
 // the MFMAs of step t.
-#include <stdio.h>
-
 #include "cct_internal.h"
 #include "gemm_common.h"
 
@@ -524,7 +522,6 @@ int launch_f32(const GemmTN& p, hipStream_t st) {
                    (reinterpret_cast<uintptr_t>(p.B) % 16 == 0) && p.b_ld_guard % BN == 0 &&
                    p.b_ld_guard >= p.Ncols && p.b_ks >= p.b_ld_guard;
   dim3 grid((unsigned)blocks, (unsigned)p.G);
-  char name[96];
   // fused lowering: tap table in LDS when it fits 24 KiB (and the kernel size fits 15 bits)
   const size_t tab_bytes = (size_t)p.Kpad * sizeof(int2);
   const bool tab_ok = tab_bytes <= 24576 && p.gK < 32768;
@@ -540,12 +537,12 @@ int launch_f32(const GemmTN& p, hipStream_t st) {
                               (p.Ncols - 1) % p.bmap.P;
     if ((max_col + (long long)(p.Kdim + 1) * p.b_ks) * 4 < (1LL << 31)) gather_fast |= 2;
   }
-  snprintf(name, sizeof(name), "gemm_tn_f32<%d, %d, %d, %d, %d, %d>", BM, BN, BK, WM, WN, bmode);
   // algorithmic bytes: operands once + result once (fused lowering: the tensor x, not D^)
   const double b_bytes = p.gather ? 4.0 * ((double)p.Ncols / (p.gHout * p.gWout)) * p.gC * p.gH * p.gW
                                   : 4.0 * (double)p.Kdim * p.Ncols * p.G;
-  ProfScope ps(name, 2.0 * p.M * p.Ncols * p.Kdim * p.G,
-               b_bytes + 4.0 * ((double)p.M * p.Ncols + (double)p.M * p.Kdim) * p.G, st);
+  ProfScope ps(2.0 * p.M * p.Ncols * p.Kdim * p.G,
+               b_bytes + 4.0 * ((double)p.M * p.Ncols + (double)p.M * p.Kdim) * p.G, st,
+               "gemm_tn_f32<%d, %d, %d, %d, %d, %d>", BM, BN, BK, WM, WN, bmode);
   if (bmode == 4) {
     const long long taps = (long long)p.tKi * p.tKj;
     if (p.gCpad % BK || p.Kpad != taps * p.gCpad || taps * BN * 4 > 32768 || p.gs != 1 ||
@@ -579,11 +576,9 @@ int launch_bf16(const GemmTN& p, hipStream_t st) {
   if (!plainB || p.b_ks % 8 || p.b_gs % 8 || reinterpret_cast<uintptr_t>(p.B) % 16)
     return CCT_EUNSUPPORTED;
   dim3 grid((unsigned)blocks, (unsigned)p.G);
-  char name[96];
-  snprintf(name, sizeof(name), "gemm_tn_bf16<%d, %d, %d, %d, %d>", BM, BN, BK, WM, WN);
-  ProfScope ps(name, 2.0 * p.M * p.Ncols * p.Kdim * p.G,
+  ProfScope ps(2.0 * p.M * p.Ncols * p.Kdim * p.G,
                ((double)p.Kdim * p.Ncols * 2.0 + (double)p.M * p.Ncols * 4.0 + (double)p.M * p.Kdim * 2.0) * p.G,
-               st);
+               st, "gemm_tn_bf16<%d, %d, %d, %d, %d>", BM, BN, BK, WM, WN);
   hipLaunchKernelGGL((gemm_tn_bf16<BM, BN, BK, WM, WN>), grid, dim3(NT), 0, st, p, tiles_m, tiles_n);
   CCT_CHECK_LAUNCH();
   return CCT_OK;

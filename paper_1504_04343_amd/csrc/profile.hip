@@ -1,5 +1,8 @@
 // Optional per-kernel timing with HIP events on the launching stream (measurement aid for
 // bench.py; off by default, nothing is recorded and no event is created when off).
+#include <stdarg.h>
+#include <stdio.h>
+
 #include <map>
 #include <mutex>
 #include <string>
@@ -17,7 +20,7 @@ struct Record {
 };
 
 std::mutex g_mu;
-bool g_on = false;
+std::atomic<bool> g_on{false};
 std::vector<Record> g_records;
 constexpr size_t kMaxRecords = 1 << 16;
 
@@ -31,8 +34,21 @@ void clear_records() {
 
 }  // namespace
 
-ProfScope::ProfScope(const char* name, double flops, double bytes, hipStream_t st)
-    : st_(st), idx_(-1) {
+ProfScope::ProfScope(const char* name, double flops, double bytes, hipStream_t st) : st_(st), idx_(-1) {
+  if (g_on) start(name, flops, bytes);
+}
+
+ProfScope::ProfScope(double flops, double bytes, hipStream_t st, const char* format, ...) : st_(st), idx_(-1) {
+  if (!g_on) return;
+  char name[96];
+  va_list args;
+  va_start(args, format);
+  vsnprintf(name, sizeof(name), format, args);
+  va_end(args);
+  start(name, flops, bytes);
+}
+
+void ProfScope::start(const char* name, double flops, double bytes) {
   std::lock_guard<std::mutex> lk(g_mu);
   if (!g_on || g_records.size() >= kMaxRecords) return;
   Record r;
@@ -44,7 +60,7 @@ ProfScope::ProfScope(const char* name, double flops, double bytes, hipStream_t s
     (void)hipEventDestroy(r.start);
     return;
   }
-  (void)hipEventRecord(r.start, st);
+  (void)hipEventRecord(r.start, st_);
   g_records.push_back(r);
   idx_ = (long long)g_records.size() - 1;
 }
