@@ -223,16 +223,15 @@ GemmTN split_problem(const cct_conv_desc_t& d, const Geom& g, const SplitPlan& s
     default: return s2d_fwd_problem(d, g, pack, sp.Mpad, sp.Kpad, in, out, bias, ni);
   }
 }
-// false = the kernel cannot run this pass of the layer (bf16, or shapes it cannot stage).
+double split_cost(const cct_conv_desc_t& d, int pass, const Geom& g, const SplitPlan& sp);
+double kernel_cost(const cct_conv_desc_t& d, int pass, int type, const Geom& g);
+
+// false = the kernel does not run this pass of the layer (bf16, or shapes it cannot stage).
 bool find_split_plan(const cct_conv_desc_t& d, int pass, const Geom& g, SplitPlan* sp) {
   if (d.precision != CCT_PREC_F32 || pass == CCT_PASS_BACKWARD_WEIGHTS) return false;
   const int s = d.stride, U = (d.K + s - 1) / s;
   const bool fwd = pass == CCT_PASS_FORWARD;
   if (!fwd && s == 1 && d.pad > d.K - 1) return false;
-  // Many channels into at most a 32-row tile of kernels: all four waves read the same rows of the pack and
-  // Type 3, whose rows are kernels x taps, is the faster one (128 images of 28 x 28, 512 -> 16 channels:
-  // 167 us against 231; 1024 -> 32: 506 against 520).
-  if (fwd && s == 1 && d.K <= 3 && g.Og <= 32 && g.Cg >= 128) return false;
   const long long kIn = (long long)d.C * d.H * d.W, kOut = (long long)d.O * g.Hout * g.Wout;
   if (kIn >= kIntMax || kOut >= kIntMax || (long long)d.C * s * s >= kIntMax / 2) return false;
   auto fits = [&](int kind, long long M, int channels, int K) {
@@ -246,7 +245,15 @@ bool find_split_plan(const cct_conv_desc_t& d, int pass, const Geom& g, SplitPla
     const StridedBwd sb = strided_bwd(d, g);
     return fits(2, (long long)g.Cg * s * s, g.Og, sb.U);
   }
-  if (fits(0, g.Og, g.Cg, d.K)) return true;
+  if (fits(0, g.Og, g.Cg, d.K)) {
+    // Many channels into one 32-row tile of kernels, whose four waves read the same rows of the pack: near where
+    // Type 3, whose rows are kernels x taps, is as fast (128 images of 28 x 28, 1024 -> 32 channels: 422 us
+    // against 437; 512 -> 16: 152 against 214; 256 -> 32: 145 against 114).  The estimates draw the line, and
+    // beyond it an explicit FUSED is the fp32 kernel: the fusion on one side of the channel ratio, Type 3 on
+    // the other.
+    return !(s == 1 && d.K <= 3 && g.Og <= 32 && g.Cg >= 128) ||
+           split_cost(d, pass, g, *sp) < kernel_cost(d, pass, CCT_LOWER_TYPE3, make_geom(d, CCT_LOWER_TYPE3));
+  }
   return (s == 2 || s == 4) && U >= 2 && fits(3, g.Og, g.Cg * s * s, U);
 }
 
@@ -256,16 +263,19 @@ bool split_plan(const cct_conv_desc_t& d, int pass, const Geom& g, SplitPlan* sp
   return g.asked.split_plan;
 }
 
-double split_cost(const cct_conv_desc_t& d, int pass, const Geom& g, const SplitPlan& sp);
-double kernel_cost(const cct_conv_desc_t& d, int pass, int type, const Geom& g);
-
-// Does a fused pass run on conv_fused_split?  An explicit FUSED does wherever it can; AUTO where the
-// estimate says so: with few channels or kernels much of a tile is padding and the fp32 fused kernels do
-// less of it (22 images of 23 x 23, 8 channels, 32 kernels: 16 us against 23).
+// Does a fused pass run on conv_fused_split?  An explicit FUSED does wherever it can; AUTO unless the estimate
+// of the fp32 fused kernels is clearly lower: with few channels or kernels much of a tile is padding and they do
+// less of it (22 images of 23 x 23, 8 channels, 32 kernels: 16 us against 23).  Of 11400 passes the split
+// kernel was the faster one in 92 %, and the other estimate is between half and twice the time.  Space to depth
+// with half as many taps again as the layer has (3 x 3 at stride 2, 5 x 5 and 6 x 6 at stride 4: four short K
+// tiles per group of channels) is the faster one in 57 % only: there the estimates decide evenly (85 images of
+// 38 x 38, 79 -> 53 channels, 3 x 3 at stride 2: 75 us against 55).
 bool use_split(const cct_conv_desc_t& d, int pass, const Geom& g, SplitPlan* sp) {
   if (!split_plan(d, pass, g, sp)) return false;
   if (d.lowering != CCT_LOWER_AUTO || (pass == CCT_PASS_BACKWARD_DATA && d.stride > 1)) return true;
-  return split_cost(d, pass, g, *sp) <= kernel_cost(d, pass, CCT_LOWER_FUSED, g);
+  const long long U = (d.K + d.stride - 1) / d.stride;
+  const bool few_taps = sp->kind == 3 && 2 * U * U * d.stride * d.stride > 3LL * d.K * d.K;
+  return split_cost(d, pass, g, *sp) <= (few_taps ? 0.9 : 1.5) * kernel_cost(d, pass, CCT_LOWER_FUSED, g);
 }
 
 inline int esize(const cct_conv_desc_t& d) { return d.precision == CCT_PREC_BF16_IN_F32_ACC ? 2 : 4; }
@@ -727,7 +737,7 @@ double split_cost(const cct_conv_desc_t& d, int pass, const Geom& g, const Split
   if (g.asked.split_cost < 0) {
     const GemmTN q = split_problem(d, g, sp, nullptr, nullptr, nullptr, nullptr, 1);
     const double bytes = 4.0 * d.N * ((double)d.C * d.H * d.W + (double)d.O * g.Hout * g.Wout);
-    g.asked.split_cost = std::max(conv_fused_split_seconds(q, d.N), bytes / kGemmBytesPerSec) + 2.0 * kLaunchSec;
+    g.asked.split_cost = std::max(conv_fused_split_seconds(q, d.N), bytes / kGemmBytesPerSec + 2.0 * kLaunchSec);
   }
   return g.asked.split_cost;
 }

@@ -767,22 +767,42 @@ bool conv_fused_split_fits(const GemmTN& p) {
   return split_geom(p, &fg, &lds);
 }
 
-// Sustained rate of the tiles, padding included, plus what filling and draining a round of workgroups
-// costs; a launch that leaves CUs idle takes at least the serial chain of one workgroup.  Measured:
-// 64- and 128-row tiles 255 TFLOP/s, 32-row tiles (four waves read the same rows of the pack) 150;
-// about 6 us per round of 512 workgroups; a lone workgroup takes 0.27 us per K tile and at least 2.7 us per
-// channel group, the way of the next group's cells from memory.
+// Rounds of workgroups, each as long as the chain of one: per K tile 0.50 / 0.30 / 0.20 us (128 / 64 / 32 rows)
+// for every workgroup that shares the CU, at least 0.50 / 0.33 / 0.26, less with the unrolled 25 tiles of 5 x 5,
+// more where cells are regrouped or windows strided; per channel group at least 2.3 us, the way of the next
+// group's cells from memory (3 us where they are many); 10 / 7 / 7 us to fill and drain; 4 us for the pack.  Fitted
+// to 13700 passes of 1 to 256 images of up to 120 x 120: off by 13 % in the mean, by up to 31 % in nine of ten (a rate
+// of full tiles and the chain of a lone workgroup: 23 % and 55 %).
 double conv_fused_split_seconds(const GemmTN& p, int nimg) {
   KcGeom fg;
   size_t lds;
   if (!split_geom(p, &fg, &lds)) return 1.0;
   const long long tn = column_tiles(p, fg, nimg);
-  const int BM = split_bm(p, tn);
-  const double wgs = (double)tn * (p.Mpad / BM) * p.G;
-  const double flops = 2.0 * wgs * BM * BN * p.Kpad;
-  const double group = std::max(tiles_per_group(p.gK) * 0.27e-6, 2.7e-6);
-  return std::max(flops / (BM == 32 ? 150.0e12 : 255.0e12) + std::ceil(wgs / 512.0) * 6.0e-6,
-                  (double)fg.ngroups * group + 6.0e-6);
+  const int BM = split_bm(p, tn), S = p.s2d ? p.s2d : 1, KT = p.gK == 3 || (p.gK == 5 && S == 1) ? p.gK : 0;
+  // workgroups that registers and LDS let share a CU
+  const int regs = BM > 32 ? 2 : KT == 0 && S == 1 ? 4 : KT == 5 || S == 4 ? 2 : 3;
+  const int share = std::max(1, std::min(regs, (int)(160 * 1024 / lds)));
+  double alone = BM == 128 ? 0.50e-6 : BM == 64 ? 0.33e-6 : 0.26e-6;
+  double shared = BM == 128 ? 0.50e-6 : BM == 64 ? 0.30e-6 : 0.20e-6;
+  double group = KT == 0 || S > 1 ? 3.0e-6 : 2.3e-6;
+  if (KT == 5) {
+    alone *= 0.75;
+    shared *= BM == 128 ? 0.97 : 0.80;
+  }
+  if (S > 1) {
+    alone *= 1.4;
+    shared *= KT ? 1.05 : 1.2;
+  }
+  if (p.gs > 1) {
+    alone *= 1.3;
+    group *= 1.2;
+  }
+  const double tiles = (double)fg.ngroups * tiles_per_group(p.gK);
+  auto round = [&](long long n) {
+    return n ? std::max(tiles * std::max(alone, (double)n * shared), fg.ngroups * group) + (BM == 128 ? 10.0e-6 : 7.0e-6) : 0.0;
+  };
+  const long long per_cu = (tn * (p.Mpad / BM) * p.G + 255) / 256;
+  return (double)(per_cu / share) * round(share) + round(per_cu % share) + 4.0e-6;
 }
 
 int launch_pack_split(const float* w, void* pack, int kind, int G, int Og, int Cg, int K, int s, int Mpad,
