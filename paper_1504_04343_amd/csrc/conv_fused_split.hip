@@ -464,14 +464,14 @@ __global__ __launch_bounds__(NT, waves_per_simd(WAVES_M, KT, S)) void conv_fused
   // pass.  Accumulator register r is row 8*(r/4) + 4*(lane/32) + r%4 of the wave's rows: four
   // consecutive rows per lane.
   const int mw = m0 + wave_m * MB;
-  bool bad = false;
+  float check = 0.f;  // NaN once a result is not finite
 #pragma unroll
   for (int j = 0; j < WN; ++j)
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       if constexpr (PARTS) acc_h[j][r] += total[j][r];
       acc_h[j][r] += acc_c[j][r];
-      bad |= !finite(acc_h[j][r]);
+      check = fmaf(acc_h[j][r], 0.f, check);
       acc_h[j][r] *= kSplitUnscale;
     }
   if (p.d2s) {
@@ -540,7 +540,7 @@ __global__ __launch_bounds__(NT, waves_per_simd(WAVES_M, KT, S)) void conv_fused
       }
     }
   }
-  if (!__any(bad)) return;
+  if (!__any(check != check)) return;
 
   // ---- Blocks with results that are not finite: again in plain fp32 (split_bf16.h).  A block of fp32 products
   // costs a few times one of split ones whatever is in it (256 images of conv3 with one infinity each: 331 us

@@ -259,7 +259,9 @@ __global__ __launch_bounds__(NT, WAVES_M == 4 ? 2 : WAVES_M == 1 && !BT ? 6 : 4)
   const int mw = m0 + wave_m * 32;
   float* __restrict__ C = p.C + (long long)g * p.c_gs;
   const float* bias = p.bias ? p.bias + (p.bias_gs < 0 ? 0 : (long long)g * p.bias_gs) : nullptr;
-  bool bad = false;
+  // NaN once a result is not finite: one instruction each (compares, whose answers are collected in scalar masks,
+  // took 2 % of fc6's products and 4 % of a 4096 -> 1000 layer's)
+  float check = 0.f;
 #pragma unroll
   for (int j = 0; j < WN; ++j) {
     const int col = n0 + wave_n * WN * 32 + j * 32 + lane_lo;
@@ -270,13 +272,13 @@ __global__ __launch_bounds__(NT, WAVES_M == 4 ? 2 : WAVES_M == 1 && !BT ? 6 : 4)
       const int m = mw + (r >> 2) * 8 + lane_hi * 4 + (r & 3);
       if (m >= p.M) continue;
       float v = acc_h[j][r] + acc_c[j][r];
-      bad |= !finite(v);
+      check = fmaf(v, 0.f, check);
       v *= kSplitUnscale;
       if (bias) v += bias[p.bias_gs < 0 ? col : m];
       cl[(long long)m * p.c_ms] = v;
     }
   }
-  if (!__any(bad)) return;
+  if (!__any(check != check)) return;
   // blocks with results that are not finite: again in plain fp32 (split_bf16.h)
   const GemmTN& q = first_argument<GemmTN>();
   float* Cq = q.C + (long long)g * q.c_gs;
