@@ -132,7 +132,9 @@ namespace {
 // 16 splits 198 / 141 / 126 / 158; before, on the fp32 matrix instructions, 195 and 214.  false = sizes or a workspace that it
 // cannot take, or a backward-weights pass over up to 32 images, whose product is one short stage of
 // 32 images: the fp32 kernel wastes less there (fc6, one image: 36 us against 43).
-bool fc_plan_split(const cct_conv_desc_t& d, int pass, long long max_bytes, long long F, FcPlan* P) {
+// *estimate: its seconds; *limited: without the workspace's limit there is a faster one.
+bool fc_plan_split(const cct_conv_desc_t& d, int pass, long long max_bytes, long long F, FcPlan* P, double* estimate,
+                   bool* limited) {
   const long long NO = 4LL * d.N * d.O;
   const long long cap = max_bytes < 0 ? kFcMaxPartBytes : std::min(kFcMaxPartBytes, max_bytes);
   const bool fwd = pass == CCT_PASS_FORWARD, bwdw = pass == CCT_PASS_BACKWARD_WEIGHTS;
@@ -172,16 +174,21 @@ bool fc_plan_split(const cct_conv_desc_t& d, int pass, long long max_bytes, long
            (n > 1 ? 2.0 * n * out / 6.0e12 : 0.0);
   };
   long long S = 1;
+  double best = !bwdw && need(1) <= cap ? seconds(1) : 1e30;
+  *limited = false;
   if (!bwdw) {
-    double best = need(1) <= cap ? seconds(1) : 1e30;
     for (int sp = 2; sp <= 64 && Kd >= (long long)sp * kFcMinSplitRows; sp += sp < 16 ? 1 : 4) {
       const double t = seconds(sp);
-      if (t < best && need(sp) <= cap) {
+      if (t >= best) continue;
+      if (need(sp) <= cap) {
         best = t;
         S = sp;
+      } else {
+        *limited = true;
       }
     }
   }
+  *estimate = best;
   if (max_bytes >= 0 && need(S) > max_bytes) return false;
   p.Kdim = (int)len(S); p.Kpad = gemm_split_kpad(p.Kdim);
   if (!gemm_split_fits(p, fwd)) return false;
@@ -213,17 +220,9 @@ GemmTN fc_split_problem(const FcPlan& P, int M, int Ncols, const void* pack, con
 
 }  // namespace
 
-bool fc_plan(const cct_conv_desc_t& d, int pass, long long max_bytes, FcPlan* P) {
-  if (d.K != d.H || d.K != d.W || d.pad != 0 || d.groups != 1) return false;
-  if (d.precision != CCT_PREC_F32) return false;
-  if (d.lowering != CCT_LOWER_AUTO && d.lowering != CCT_LOWER_TYPE1) return false;
-  const long long F = (long long)d.C * d.K * d.K;
-  if (F >= kIntMax - 256 || (long long)d.N * d.O >= kIntMax || (long long)d.N * F >= (1LL << 40) ||
-      (long long)d.O * F >= (1LL << 40))
-    return false;
-  std::memset(P, 0, sizeof(*P));
-  P->F = (int)F;
-  if (fc_plan_split(d, pass, max_bytes, F, P)) return true;
+// The plan on the fp32 matrix instructions.
+namespace {
+bool fc_plan_f32(const cct_conv_desc_t& d, int pass, long long max_bytes, long long F, FcPlan* P, double* estimate) {
   long long off = 0;
   auto take = [&](long long bytes, long long* o) {
     *o = off;
@@ -280,7 +279,39 @@ bool fc_plan(const cct_conv_desc_t& d, int pass, long long max_bytes, FcPlan* P)
     take(4LL * d.O * kDbiasBlocks, &P->scratch_off);
   }
   P->total = std::max<long long>(off, kAlign);
+  // Rounds of 512 workgroups at 110 TFLOP/s.  Forward: up to one per CU, a workgroup takes 0.6 of the time it takes
+  // beside another (37 images, 4640 features, 3076 kernels, 4 splits: 50 us).  Backward-data: 1.2 in any number (12
+  // images, 5184 features, 359 kernels: 37 us; 458, 1728 and 1556: 77).
+  const long long rows = pass == CCT_PASS_BACKWARD_WEIGHTS ? d.O : d.N, cols = pass == CCT_PASS_FORWARD ? d.O : F;
+  const long long len = pass == CCT_PASS_BACKWARD_WEIGHTS ? d.N : P->split_len;
+  const long long wgs = ((rows + BM - 1) / BM) * ((cols + BN - 1) / BN) * P->S;
+  *estimate = (double)((wgs + 511) / 512) * 2.0 * BM * BN * (double)len / (110.0e12 / 512) * (pass == CCT_PASS_BACKWARD_DATA ? 1.2 : wgs <= 256 ? 0.6 : 1.0) +
+              (P->S > 1 ? 8.0 * P->S * rows * cols / 6.0e12 : 0.0);
   return max_bytes < 0 || P->total <= max_bytes;
+}
+}  // namespace
+
+bool fc_plan(const cct_conv_desc_t& d, int pass, long long max_bytes, FcPlan* P) {
+  if (d.K != d.H || d.K != d.W || d.pad != 0 || d.groups != 1) return false;
+  if (d.precision != CCT_PREC_F32) return false;
+  if (d.lowering != CCT_LOWER_AUTO && d.lowering != CCT_LOWER_TYPE1) return false;
+  const long long F = (long long)d.C * d.K * d.K;
+  if (F >= kIntMax - 256 || (long long)d.N * d.O >= kIntMax || (long long)d.N * F >= (1LL << 40) ||
+      (long long)d.O * F >= (1LL << 40))
+    return false;
+  std::memset(P, 0, sizeof(*P));
+  P->F = (int)F;
+  // Fewer splits than are worth it, because their partial products and the packed operand (1.5 times the fp32
+  // one) do not fit: the fp32 plan may split more (37 images, 4640 features, 3076 kernels in a quarter of the
+  // workspace: 150 us unsplit, 52 with four fp32 splits).
+  FcPlan f32 = *P;
+  double split_seconds, f32_seconds;
+  bool limited;
+  if (!fc_plan_split(d, pass, max_bytes, F, P, &split_seconds, &limited))
+    return fc_plan_f32(d, pass, max_bytes, F, P, &f32_seconds);
+  if (limited && max_bytes >= 0 && fc_plan_f32(d, pass, max_bytes, F, &f32, &f32_seconds) && f32_seconds < split_seconds)
+    *P = f32;
+  return true;
 }
 
 int fc_forward(const cct_conv_desc_t& d, const FcPlan& P, const float* x, const float* w,

@@ -103,3 +103,22 @@ def test_granules_only_where_their_chunks_pay(B):
         assert any(n.startswith(name) for n in names), names
         got[name] = dx.cpu().numpy()
     assert rel_err(*got.values()) <= TOL_BF16
+
+
+@pytest.mark.parametrize("run,L,share", [(forward, layer("fwd", 37, 290, 4, 4, 3076, 4, 1, 0), 4),
+                                         (backward_data, layer("bwd", 56, 21, 7, 7, 4056, 7, 1, 0), 5)],
+                         ids=lambda v: getattr(v, "__name__", None))
+def test_fully_connected_layers_keep_their_splits(B, run, L, share):
+    """Part of the workspace: the bf16-split product would run with fewer splits than it wants, the fp32 plan with
+    more of them is the faster one; with all of it, the bf16-split product runs."""
+    import torch
+    d, p = desc_of(B, L), B.PASS_FORWARD if run is forward else B.PASS_BACKWARD_DATA
+    full = B.cct_conv_workspace_bytes(d, p)
+    for nbytes, split in ((full, True), (full // share, False)):
+        B.cct_profile_enable(True)
+        err = run(B, L, nbytes)
+        torch.cuda.synchronize()
+        B.cct_profile_enable(False)
+        names = [e["name"] for e in B.cct_profile_read()]
+        assert err <= TOL_F32
+        assert any(n.startswith("gemm_split") for n in names) == split, names
