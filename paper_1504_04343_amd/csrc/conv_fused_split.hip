@@ -733,6 +733,12 @@ bool split_geom(const GemmTN& p, KcGeom* fg, size_t* lds) {
   // padded to 16 and 38 kernels to 64: 124 us against 184; half of it useful, 16 kernels on 352 channels,
   // 30 images of 52 x 52: 222 against 117).
   if (5LL * p.M * p.gCg < 2LL * p.Mpad * ((p.gCg + CG - 1) / CG * CG)) return false;
+  // Regrouped, an image holds only the pixels that the kernels reach: the real one, which the staged cells are
+  // addressed in (32-bit byte offsets from the workgroup's first image), may be larger.
+  if (p.s2d) {
+    const long long T = (BN - 1) / ((long long)p.gHout * p.gWout) + 2;  // images 128 positions can touch
+    if ((T + 1) * p.x_img + (long long)p.x_pad * (p.x_w + 1) >= (1LL << 29)) return false;
+  }
   if (p.s2d && p.gK == 5) return false;  // kernels of 9 and 10 (stride 2), 17 to 20 (stride 4): no form
   GeomRules rules;
   rules.r_step = 8;

@@ -107,6 +107,23 @@ def test_precision_of_small_layers(B, L):
     assert np.linalg.norm(got.astype(np.float64) - want) / np.linalg.norm(want) <= 1.5e-7
 
 
+def test_images_larger_than_their_regrouped_form(B):
+    """Stride 4, 8 x 8 kernels, 11 x 11 pixels: only 8 x 8 of them are read, but the 128 images of a workgroup lie
+    19.4 MB apart.  Whole numbers with sums below 2^24: exact in any order."""
+    import torch
+    L = layer("apart", 129, 40000, 11, 11, 16, 8, 4, 0)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    ints = lambda lo, hi, *shape: torch.randint(lo, hi, shape, generator=gen, device="cuda", dtype=torch.float32)
+    x, w, b = ints(-1, 2, L.N, L.C, L.H, L.W), ints(-2, 3, L.O, L.C, L.K, L.K), ints(-9, 10, L.O)
+    y = torch.full((L.N, L.O, 1, 1), float("nan"), device="cuda")
+    d = desc_of(B, L, B.LOWER_FUSED)
+    B.cct_conv_forward(d, x, w, b, y, B.alloc_workspace(d, B.PASS_FORWARD, None))
+    want = b.double().expand(L.N, L.O).clone()
+    for c in range(0, L.C, 4000):
+        want += x[:, c:c + 4000, :8, :8].reshape(L.N, -1).double() @ w[:, c:c + 4000].reshape(L.O, -1).double().T
+    assert torch.equal(y.double().view(L.N, L.O), want)
+
+
 @pytest.mark.parametrize("e,f", [(-118, 88), (-70, 40), (70, -50), (103, -83), (110, -90)], ids=lambda e: "2^%d" % e)
 @pytest.mark.parametrize("L", [layer("r_k3", 2, 40, 13, 13, 70, 3, 1, 1), layer("r_s2d", 2, 3, 31, 31, 40, 11, 4, 0)],
                          ids=lambda L: L.name)
