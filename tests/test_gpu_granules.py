@@ -6,7 +6,7 @@ import pytest
 
 import oracle
 from paper_1504_04343_amd import synth
-from gpu_util import TOL_BF16, gpu_backward_data, gpu_forward, layer, odims, rel_err
+from gpu_util import TOL_BF16, dev, gpu_backward_data, gpu_forward, layer, odims, rel_err
 
 pytestmark = pytest.mark.gpu
 
@@ -76,3 +76,40 @@ def test_backward_data(B, L):
     assert any(n.startswith(KERNEL) for n in names), names
     assert rel_err(got, oracle.conv_backward_data(odims(oracle, L), w, dy)) <= TOL_BF16
     assert rel_err(got, oracle.conv_backward_data(odims(oracle, L), rounded(w), rounded(dy))) <= TOL_ROUNDED
+
+
+def pass_bytes(L, backward, images):
+    """Workspace of the granules of so many images and of the kernels."""
+    C, M, P = (L.O, L.C, L.Hout + 2 * (L.K - 1 - L.pad)) if backward else (L.C, L.O, L.H + 2 * L.pad)
+    Q = L.Wout + 2 * (L.K - 1 - L.pad) if backward else L.W + 2 * L.pad
+    n8, up = -(-C // L.groups // 8), lambda v: -(-v // 256) * 256
+    return up(images * L.groups * n8 * P * Q * 16) + up(n8 * L.K ** 2 * M * 16)
+
+
+@pytest.mark.parametrize("backward,L", [(False, FORWARD[3]), (False, FORWARD[4]),
+                                        (True, layer("b_odd", 73, 106, 21, 19, 130, 5, 1, 2, 2))],
+                         ids=lambda v: getattr(v, "name", None))
+def test_in_chunks(B, backward, L):
+    """A workspace for 37 images (33 of the 40): granules, with a last chunk shorter than the first.  One for less
+    than 32: the other kernels."""
+    import torch
+    x, w, b, dy = (m(L, 3) for m in (synth.make_x, synth.make_w, synth.make_bias, synth.make_dy))
+    d = B.make_desc(L.N, L.C, L.H, L.W, L.O, L.K, L.stride, L.pad, L.groups, 0, 1)
+    p = B.PASS_BACKWARD_DATA if backward else B.PASS_FORWARD
+    assert pass_bytes(L, backward, L.N) == B.cct_conv_workspace_bytes(d, p)
+    for images in (min(37, L.N - 7), 31):
+        ws = torch.empty(pass_bytes(L, backward, images), dtype=torch.uint8, device="cuda")
+        out = torch.full((x if backward else dy).shape, float("nan"), device="cuda")
+        B.cct_profile_enable(True)
+        if backward:
+            B.cct_conv_backward_data(d, dev(w), dev(dy), out, ws)
+        else:
+            B.cct_conv_forward(d, dev(x), dev(w), dev(b), out, ws)
+        torch.cuda.synchronize()
+        B.cct_profile_enable(False)
+        launches = sum(e["launches"] for e in B.cct_profile_read() if e["name"].startswith(KERNEL))
+        assert launches == (2 if images > 31 else 0)
+        for f, tol in ((lambda a: a, TOL_BF16), (rounded, TOL_ROUNDED)):
+            want = (oracle.conv_backward_data(odims(oracle, L), f(w), f(dy)) if backward else
+                    oracle.conv_forward(odims(oracle, L), f(x), f(w), b))
+            assert rel_err(out.cpu().numpy(), want) <= tol
