@@ -337,7 +337,8 @@ double plain_seconds(const cct_conv_desc_t& d, int pass, const Geom& g, double c
 // Backward-weights on granules of 8 images (conv_bwdw_img.hip): what AUTO runs where the estimates say
 // that rewriting x and dy once pays (they are re-read as often as the product has tiles), and how FUSED
 // computes fp32 layers by the same rule.  Measured over 500 layers of 1 to 1024 images: up to 2.9 times as fast where it
-// is chosen (conv3 at batch 1024: 2880 -> 1590 us), at most 15 % slower for single calls under 40 us;
+// is chosen (conv3 at batch 1024: 2880 -> 1590 us).  Calls under 35 us, whose three launches weigh: 2 % of them
+// are more than 15 % slower, by up to 8 us (7 images of 12 x 12, 243 -> 51 channels: 22 us against 30);
 // it stays off for a single image (conv3: 31 us against 38), 3 channels (conv1 at batch 256: 697 us
 // against 997) and 1 x 1 kernels at stride 2 (they use a quarter of the x that would be rewritten).
 bool batch_img_plan(const cct_conv_desc_t& d, const Geom& g) {
@@ -418,9 +419,10 @@ bool tensor_split(const cct_conv_desc_t& d, int pass, int type, const Geom& g, l
 }
 
 // Forward / backward-data in bf16 on granules of 8 channels (conv_granules.hip): what AUTO runs where the
-// estimates say that rewriting the tensor once pays.  Measured
-// over 60 layers: 1.05 to 2.8 times as fast where it is chosen; up to about ten images of 13 x 13 the
-// contraction of a lone workgroup is the longer way (256 -> 384 channels, 9 images: 42 us against 53).
+// estimates say that rewriting the tensor once pays.  Measured over 4000 layers where it is chosen: 1.7 times as
+// fast in the geometric mean, 1.6 % of them more than 5 % slower (few tiles of many taps and channels at stride 4: 20
+// images of 52 x 52, 260 -> 28 channels, 5 x 5, 87 us against 129).  Asking for a wider margin there loses more
+// than it saves: the others of up to 64 tiles are 1.6 times as fast.
 bool granules_win(const cct_conv_desc_t& d, int pass, int type, const Geom& g) {
   if (d.lowering != CCT_LOWER_AUTO || d.precision != CCT_PREC_BF16_IN_F32_ACC) return false;
   if (g.asked.gran < 0)
