@@ -154,8 +154,9 @@ int cct_lowering_cost(const cct_conv_desc_t* desc, cct_pass_t pass, cct_lowering
  * backward-data pass (a few times N*C*K*K floats).  With a smaller workspace these two passes use
  * fewer splits, and a workspace too small for the unsplit product (forward: N*O floats; backward:
  * the packed dy) sends the layer through the general, chunked path.  The forward pass of such a layer
- * with C*K*K a multiple of 32 reads w with 16-byte loads: w must be 16-byte aligned (CCT_EINVAL
- * otherwise; force another lowering for a misaligned tensor).
+ * with C*K*K a multiple of 32 asks for a w that is 16-byte aligned, whichever of its kernels runs (one
+ * of them, in a small workspace, reads w with 16-byte loads): CCT_EINVAL otherwise; force another
+ * lowering for a misaligned tensor.
  */
 int cct_conv_workspace_bytes(const cct_conv_desc_t* desc, cct_pass_t pass, size_t* bytes);
 int cct_conv_workspace_bytes_for_chunk(const cct_conv_desc_t* desc, cct_pass_t pass,
@@ -276,7 +277,7 @@ int cct_maxpool_backward(const cct_pool_desc_t* desc, const float* dy, const int
  * from the forward pass).  x, y, dy, dx: device, contiguous NCHW fp32, N*C*H*W elements; y / dx
  * are overwritten and must not alias x.  size must be 1, 3, 5, 7 or 9 (CCT_EUNSUPPORTED
  * otherwise), k > 0, alpha >= 0 (CCT_EINVAL otherwise).  CaffeNet: size 5, alpha 1e-4, beta 0.75,
- * k 1.  Arithmetic is fp32 (powf).
+ * k 1.  Arithmetic is fp32: powf, for beta 0.75 a Newton step to the last bit or two of the result.
  */
 typedef struct {
   int32_t N, C, H, W;

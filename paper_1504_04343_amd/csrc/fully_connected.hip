@@ -147,8 +147,9 @@ bool fc_plan_split(const cct_conv_desc_t& d, int pass, long long max_bytes, long
   p.M = M; p.Mpad = gemm_split_mpad(M);
   p.Ncols = (int)cols; p.b_ks = F;
   p.bmap = ColMap{kIntMax, 0};
-  // a split of S, the number of them, and their workspace (backward-data: room for a number of equal
-  // splits where there is one)
+  // A split of S, the number of them, and their workspace.  The sizes keep the form that they had when all splits
+  // were equal, which callers may count on: forward a multiple of y, backward-data a number of dx that divides the
+  // contraction.  The kernels need neither; up to one y, and up to twice the partial products, are spare.
   // (Kd < 2^31: 32-bit divisions, this runs for every number of splits of every call)
   auto len = [&](long long S) { return S == 1 ? Kd : align_up(((unsigned)Kd + (unsigned)S - 1) / (unsigned)S, 32); };
   auto count = [&](long long S) -> long long { return ((unsigned)Kd + (unsigned)len(S) - 1) / (unsigned)len(S); };
