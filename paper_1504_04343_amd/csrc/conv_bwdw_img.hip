@@ -18,9 +18,9 @@
 // channels, tap, channel) so that neighbouring lanes read neighbouring granules.
 //
 // Measured (whole pass with the bias gradient; before: dy and x read in place by fp32 matrix
-// instructions, or bf16 lowered matrices): conv3 at batch 1024 2880 -> 1590 us, of it 1290 the product
-// (237 TFLOP/s of fp32 results, 1420 of bf16 MFMAs: the matrix cores' rate here) and 300 the rewriting
-// (3.7 TB/s); conv2 at batch 256 1215 -> 700; conv4 at batch 256 with bf16 operands 355 -> 125.
+// instructions, or bf16 lowered matrices): conv3 at batch 1024 2880 -> 1550 us, of it 1255 the product
+// (244 TFLOP/s of fp32 results, 1460 of bf16 MFMAs: the card's power limit) and 280 the rewriting
+// (3.9 TB/s); conv2 at batch 256 1215 -> 690; conv4 at batch 256 with bf16 operands 355 -> 125.
 #include <algorithm>
 
 #include "cct_internal.h"
@@ -128,7 +128,7 @@ struct ImgGemm {
 };
 
 template <int BM, int TERMS, int SLOTS>
-__global__ __launch_bounds__(BM * 4, 2) void conv_bwdw_img(ImgGemm p) {
+__global__ __launch_bounds__(granule_waves(BM, TERMS) * 64, 2) void conv_bwdw_img(ImgGemm p) {
   using GP = GranuleProduct<BM, TERMS, SLOTS>;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_i[];  // [2][A: SLOTS*BM | B: SLOTS*BN]
   GP gp;
@@ -354,14 +354,25 @@ __global__ __launch_bounds__(256) void bwdw_img_reduce(ImgReduce p) {
 
 inline int out_size(int in, int K, int s, int pad) { return (in + 2 * pad - K) / s + 1; }
 
-inline int row_tile(int M) { return M % 128 == 0 || M % 128 > 64 ? 128 : 64; }
+// What a tile of three terms costs, in rows of a 128-row one: with fewer rows the same columns are read for fewer
+// products (256 images of 28 x 28, 64 channels, 3 x 3: 128 kernels 155 us, 96 in a tile of 96 rows 129 and of 128 rows
+// 154, 64 96; 384 kernels in two groups as 4 tiles of 96 267, as 6 of 64 293).
+constexpr int tile_weight(int bm) { return bm == 128 ? 128 : bm == 96 ? 104 : 76; }
+
+inline int row_tile(int M, int terms) {
+  if (terms == 1) return M % 128 == 0 || M % 128 > 64 ? 128 : 64;
+  int best = 128;
+  for (int bm : {96, 64})
+    if ((M + bm - 1) / bm * tile_weight(bm) < (M + best - 1) / best * tile_weight(best)) best = bm;
+  return best;
+}
 
 template <int BM, int TERMS, int SLOTS>
 int launch_product(const ImgGemm& p, dim3 grid, hipStream_t st) {
-  constexpr int lds = 2 * SLOTS * (BM + BN) * kGran;
+  constexpr int lds = GranuleProduct<BM, TERMS, SLOTS>::LDS;
   constexpr auto kern = conv_bwdw_img<BM, TERMS, SLOTS>;
   if (const int rc = ensure_dynamic_lds<kern>(lds)) return rc;
-  hipLaunchKernelGGL(kern, grid, dim3(BM * 4), lds, st, p);
+  hipLaunchKernelGGL(kern, grid, dim3(granule_waves(BM, TERMS) * 64), lds, st, p);
   CCT_CHECK_LAUNCH();
   return CCT_OK;
 }
@@ -384,16 +395,16 @@ bool bwdw_img_plan(const cct_conv_desc_t& d, long long nimg, BwdwImgPlan* P) {
   const long long tx = (Hp * Wp + kPrepPx - 1) / kPrepPx, ty = (pix + kPrepPx - 1) / kPrepPx;
   const long long ctx = (d.C + kPrepCh - 1) / kPrepCh, cty = (d.O + kPrepCh - 1) / kPrepCh;
   if (groups_of_images * (tx * ctx + ty * cty) >= (1LL << 30)) return false;
-  P->BM = row_tile(Og);
+  P->BM = row_tile(Og, (int)terms);
   P->terms = (int)terms;
-  const long long ncol = terms == 1 ? 8 : P->BM == 128 ? 4 : 2;  // columns per stage
+  const long long ncol = terms == 1 ? 8 : 4;  // columns per stage
   const long long tiles = ((Og + P->BM - 1) / P->BM) * ((N + BN - 1) / BN) * d.groups;
-  const long long slots = P->BM == 128 ? 256 : 512;              // workgroups the chip holds
+  const long long slots = terms == 3 || P->BM == 128 ? 256 : 512;  // workgroups the chip holds
   const long long out_bytes = 4LL * d.O * N;
   // Splits, from the whole batch: whole rounds of workgroups (a last round that is nearly empty costs as
   // much as a full one), the number of rounds that is estimated fastest, partial products within 256 MiB,
   // at least two stages each.  A smaller chunk takes at most as many, so that its plan is no larger.
-  const double sec_col = 2.0 * P->BM * BN * kImg / ((terms == 3 ? 230.0e12 : 600.0e12) / slots);
+  const double sec_col = 2.0 * (terms == 3 ? tile_weight(P->BM) * 1.0 : P->BM * 1.0) * BN * kImg / ((terms == 3 ? 245.0e12 : 600.0e12) / slots);
   auto cut = [&](long long ncols, long long want, long long* S, long long* len) {
     *len = ((ncols + want - 1) / want + ncol - 1) / ncol * ncol;
     *S = (ncols + *len - 1) / *len;
@@ -490,13 +501,15 @@ int launch_bwdw_img(const cct_conv_desc_t& d, const BwdwImgPlan& P, int nimg, co
   if (blocks <= 0 || blocks >= 2147483647LL || d.groups > 65535) return CCT_EUNSUPPORTED;
   {
     ProfScope ps(2.0 * yn * Cg * KK, 2.0 * P.terms * (xn + yn) + 4.0 * q.S * (double)d.O * q.N, st,
-                 "conv_bwdw_img<%d, %d, %d>", P.BM, P.terms, P.terms == 1 ? 8 : P.BM == 128 ? 12 : 6);
+                 "conv_bwdw_img<%d, %d, %d>", P.BM, P.terms, P.terms == 1 ? 8 : 12);
     const dim3 grid((unsigned)blocks, (unsigned)d.groups);
     int rc;
     if (P.BM == 128)
       rc = P.terms == 3 ? launch_product<128, 3, 12>(q, grid, st) : launch_product<128, 1, 8>(q, grid, st);
+    else if (P.BM == 96)
+      rc = launch_product<96, 3, 12>(q, grid, st);
     else
-      rc = P.terms == 3 ? launch_product<64, 3, 6>(q, grid, st) : launch_product<64, 1, 8>(q, grid, st);
+      rc = P.terms == 3 ? launch_product<64, 3, 12>(q, grid, st) : launch_product<64, 1, 8>(q, grid, st);
     if (rc) return rc;
   }
   ImgReduce r;

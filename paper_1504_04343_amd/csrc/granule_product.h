@@ -2,13 +2,19 @@
 // row as 16 bytes of bf16, one term (bf16 operands) or three whose sum is the fp32 value (split_bf16.h).
 // A column is the 8 reduction indices of a granule.
 //
-// A workgroup computes BM x 256 results, a wave 64 x 64.  A stage is SLOTS (column, term) pairs of both
-// operands, moved from memory into LDS by buffer loads that write LDS directly: no registers, no vector
+// A workgroup computes BM x 256 results with waves of up to 64 x 64.  A stage is SLOTS (column, term) pairs of
+// both operands, moved from memory into LDS by buffer loads that write LDS directly: no registers, no vector
 // instruction, no conversion in the loop.  Two stages alternate, one meeting of the workgroup per stage;
-// operand reads are 32 consecutive granules, which do not conflict.  With three terms a wave reads 12 KiB
-// of LDS for 24 MFMAs (768 matrix-core cycles) per 16 reduction indices, half of what LDS can deliver, and
-// a 128 x 256 workgroup fetches 36 KiB of L2 for 1536 cycles of its CU.  With one term LDS and the matrix
-// cores are equally busy.
+// operand reads are 16 consecutive granules of four columns, which do not conflict.
+//
+// v_mfma_f32_16x16x32_bf16 and not 32x32x16: at the card's power limit, which large products run into, it is
+// the faster one (operands in registers, 2 waves per SIMD, random normals: 2200 against 1870 TFLOP/s; zeros:
+// 2450 both), because an accumulator is read and written half as often per flop; it also rounds half as
+// often.  Measured with three terms, 128 rows: conv2's backward-weights product (114.7 GFLOP) 604 -> 537 us,
+// conv3's at batch 1024 (306 GFLOP) 1319 -> 1255.  A wave of 64 x 64 reads 24 KiB of LDS for 96 MFMAs (1536
+// matrix-core cycles) per 32 reduction indices, three quarters of what LDS can deliver to four SIMDs, and a
+// 128 x 256 workgroup fetches 72 KiB of L2 for 3072 cycles of its CU.  With one term LDS and the matrix cores
+// are equally busy.
 #pragma once
 #include "cct_internal.h"
 #include "gemm_common.h"
@@ -22,24 +28,29 @@ constexpr int BN = 256;    // columns of the result per workgroup
 
 typedef __attribute__((address_space(3))) void* lds_ptr;
 
+// waves of a workgroup
+constexpr int granule_waves(int BM, int TERMS) { return TERMS == 3 ? 8 : BM / 16; }
+
 template <int BM, int TERMS, int SLOTS>
 struct GranuleProduct {
-  static constexpr int NW = BM / 16;  // waves
+  static constexpr int NW = granule_waves(BM, TERMS);
   static constexpr int WAVES_N = BN / 64;
   static constexpr int NCOL = SLOTS / TERMS;  // columns per stage
-  static_assert(SLOTS % TERMS == 0 && NCOL % 2 == 0, "an MFMA takes two columns");
-  static constexpr int STAGE = SLOTS * (BM + BN) * kGran;
+  static_assert(SLOTS % TERMS == 0 && NCOL % 4 == 0, "an MFMA takes four columns");
+  static constexpr int BMP = (BM + 63) / 64 * 64;  // rows as they are loaded
+  static constexpr int STAGE = SLOTS * (BMP + BN) * kGran;
   static constexpr int LDS = 2 * STAGE;
   // A wave moves the granules of CPW columns, or a WPC-th of one column: one address per column.
   static constexpr int CPW = NCOL > NW ? NCOL / NW : 1, WPC = NW > NCOL ? NW / NCOL : 1;
-  static constexpr int A_PARTS = BM / 64, B_PARTS = BN / 64 / WPC;  // loads of 64 rows, per wave for B
+  static constexpr int A_PARTS = BMP / 64, B_PARTS = BN / 64 / WPC;  // loads of 64 rows, per wave for B
   static constexpr int A_UNITS = TERMS * A_PARTS, A_PER = (A_UNITS + WPC - 1) / WPC;
   static_assert(CPW * NW == NCOL * WPC && WPC <= 2, "whole loads");
 
   // byte offsets of the rows a lane loads, from a column's granules: the same in every stage
   unsigned a_voff[A_PARTS], b_voff[B_PARTS];
+  static constexpr int RB = BM / (16 * NW / WAVES_N);  // blocks of 16 rows per wave; 4 blocks of 16 columns
   // three terms: h*h alone in one accumulator, the corrections in the other
-  floatx16 acc[2][2], acc_c[TERMS == 3 ? 2 : 1][TERMS == 3 ? 2 : 1];
+  f32x4 acc[RB][4], acc_c[TERMS == 3 ? RB : 1][TERMS == 3 ? 4 : 1];
 
   static __device__ __forceinline__ int wave() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6); }
   // which 64 rows of B b_voff[u] stands for
@@ -53,7 +64,7 @@ struct GranuleProduct {
     // columns past the end have an empty range: they load as zeros
     auto load_stage = [&](int buf, int c0) {
       unsigned char* As = smem + buf * STAGE;
-      unsigned char* Bs = As + SLOTS * BM * kGran;
+      unsigned char* Bs = As + SLOTS * BMP * kGran;
 #pragma unroll
       for (int v = 0; v < CPW; ++v) {
         const int cc = w / WPC + v * NW;
@@ -74,25 +85,25 @@ struct GranuleProduct {
 #pragma unroll
           for (int u = 0; u < A_PARTS; ++u)  // the first A_PER units are the first wave's
             if (WPC == 1 || (k * A_PARTS + u) / A_PER == sub)
-              __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_ptr)(As + ((cc * TERMS + k) * BM + u * 64) * kGran),
+              __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_ptr)(As + ((cc * TERMS + k) * BMP + u * 64) * kGran),
                                                        16, (int)a_voff[u], k * a_term, 0, 0);
       }
     };
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < RB; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+      for (int j = 0; j < 4; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
+        for (int r = 0; r < 4; ++r) {
           acc[i][j][r] = 0.f;
           if constexpr (TERMS == 3) acc_c[i][j][r] = 0.f;
         }
 
     const int stages = (c_end - c_begin + NCOL - 1) / NCOL;  // <= 0 for an empty range
     if (stages > 0) load_stage(0, c_begin);
-    const int lo = lane & 31, hi = lane >> 5;
-    const int a_lds = (hi * TERMS * BM + w / WAVES_N * 64 + lo) * kGran;
-    const int b_lds = SLOTS * BM * kGran + (hi * TERMS * BN + w % WAVES_N * 64 + lo) * kGran;
+    const int lo = lane & 15, kg = lane >> 4;  // row of a block, column of the four
+    const int a_lds = (kg * TERMS * BMP + w / WAVES_N * (16 * RB) + lo) * kGran;
+    const int b_lds = SLOTS * BMP * kGran + (kg * TERMS * BN + w % WAVES_N * 64 + lo) * kGran;
     for (int t = 0; t < stages; ++t) {
       // this stage's loads have landed and nobody reads the other buffer any more
       __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
@@ -100,29 +111,40 @@ struct GranuleProduct {
       if (t + 1 < stages) load_stage((t + 1) & 1, c_begin + (t + 1) * NCOL);
       const unsigned char* st = smem + (t & 1) * STAGE;
 #pragma unroll
-      for (int kb = 0; kb < NCOL / 2; ++kb) {
-        bf16x8 a[2][TERMS], b[2][TERMS];
+      for (int kb = 0; kb < NCOL / 4; ++kb) {
+        bf16x8 a[RB][TERMS], b[2][TERMS];
+        auto read_a = [&](int i) {
 #pragma unroll
-        for (int k = 0; k < TERMS; ++k)
+          for (int k = 0; k < TERMS; ++k)
+            a[i][k] = *reinterpret_cast<const bf16x8*>(st + a_lds + ((4 * kb * TERMS + k) * BMP + i * 16) * kGran);
+        };
+        auto read_b = [&](int set, int j) {
 #pragma unroll
-          for (int i = 0; i < 2; ++i) {
-            a[i][k] = *reinterpret_cast<const bf16x8*>(st + a_lds + ((2 * kb * TERMS + k) * BM + i * 32) * kGran);
-            b[i][k] = *reinterpret_cast<const bf16x8*>(st + b_lds + ((2 * kb * TERMS + k) * BN + i * 32) * kGran);
-          }
-#define CCT_M(X, Y, ACC)                                                                    \
-  _Pragma("unroll") for (int i = 0; i < 2; ++i) _Pragma("unroll") for (int j = 0; j < 2; ++j) \
-      ACC[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][X], b[j][Y], ACC[i][j], 0, 0, 0)
-        if constexpr (TERMS == 3) {
-          CCT_M(0, 0, acc);
-          CCT_M(0, 1, acc_c);
-          CCT_M(1, 0, acc_c);
-          CCT_M(1, 1, acc_c);
-          CCT_M(0, 2, acc_c);
-          CCT_M(2, 0, acc_c);
-        } else {
-          CCT_M(0, 0, acc);
-        }
+          for (int k = 0; k < TERMS; ++k)
+            b[set][k] = *reinterpret_cast<const bf16x8*>(st + b_lds + ((4 * kb * TERMS + k) * BN + j * 16) * kGran);
+        };
+        read_a(0);
+        read_b(0, 0);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int i = 0; i < RB; ++i) {
+            // the next operands behind these MFMAs: in the first column of blocks the rows, then the next column
+            if (j == 0 && i + 1 < RB) read_a(i + 1);
+            if (i == RB - 1 && j + 1 < 4) read_b((j + 1) & 1, j + 1);
+            __builtin_amdgcn_sched_barrier(0);
+#define CCT_M(X, Y, ACC) ACC[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i][X], b[j & 1][Y], ACC[i][j], 0, 0, 0)
+            if constexpr (TERMS == 3) {
+              CCT_M(2, 0, acc_c);
+              CCT_M(0, 2, acc_c);
+              CCT_M(1, 1, acc_c);
+              CCT_M(1, 0, acc_c);
+              CCT_M(0, 1, acc_c);
+            }
+            CCT_M(0, 0, acc);
 #undef CCT_M
+            __builtin_amdgcn_sched_barrier(0);
+          }
       }
     }
   }
@@ -132,15 +154,14 @@ struct GranuleProduct {
   __device__ __forceinline__ void for_each(F f) const {
     const int lane = threadIdx.x & 63, w = wave();
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < 4; ++j)
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < RB; ++i)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
+        for (int r = 0; r < 4; ++r) {
           float v = acc[i][j][r];
           if constexpr (TERMS == 3) v += acc_c[i][j][r];
-          f(w / WAVES_N * 64 + i * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3),
-            w % WAVES_N * 64 + j * 32 + (lane & 31), v);
+          f(w / WAVES_N * (16 * RB) + i * 16 + (lane >> 4) * 4 + r, w % WAVES_N * 64 + j * 16 + (lane & 15), v);
         }
   }
 };

@@ -143,3 +143,13 @@ def test_more_weights_than_31_bits_count(B):
     win = np.lib.stride_tricks.sliding_window_view(x, (K, K), (2, 3)).astype(np.float64)   # [N][C][r][c][K][K]
     want = np.tensordot(dy[:, rows].astype(np.float64), win, ((0, 2, 3), (0, 2, 3)))       # [rows][C][K][K]
     assert rel_err(dw[rows].cpu().numpy(), want) <= TOL_F32
+
+
+@pytest.mark.parametrize("L", [layer("r90", 42, 100, 14, 12, 90, 3, 1, 1), layer("r161", 35, 130, 11, 13, 322, 3, 1, 1, 2),
+                               layer("r192", 32, 33, 9, 17, 192, 5, 1, 2)], ids=["r90", "r161", "r192"])
+def test_tiles_of_96_rows(B, L):
+    """Rows that end inside a tile, columns that end inside a stage of four; a tile's 96 rows are loaded as 128."""
+    x, dy = synth.make_x(L, 5), synth.make_dy(L, 5)
+    got, names = ran(B, lambda: gpu_backward_weights(B, L, x, dy))
+    assert any(n.startswith(KERNEL + "<96") for n in names), names
+    check(got, L, x, dy, TOL_F32)
