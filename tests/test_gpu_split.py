@@ -226,3 +226,23 @@ def test_workspace_for_the_fp32_kernel_matrix_is_still_enough(B):
     _, names = ran(B, lambda: (B.cct_conv_forward(d, dev(x), dev(w), dev(b), y, ws), torch.cuda.synchronize()))
     assert not any(n.startswith(KERNEL) for n in names), names
     assert rel_err(y.cpu().numpy(), oracle.conv_forward(odims(oracle, L), x, w, b)) <= TOL_F32
+
+
+# tiles of 128 and 96 rows (256 column tiles), rows to spare, one channel group and an odd number of them
+FORMS = [layer("t96", 200, 24, 13, 13, 96, 3, 1, 1), layer("t80_k5", 200, 16, 13, 13, 80, 5, 1, 2),
+         layer("t96_k4", 200, 40, 13, 13, 90, 4, 1, 2), layer("t96_s2d", 150, 3, 67, 67, 96, 11, 4, 0),
+         layer("t128_k5", 200, 48, 13, 13, 128, 5, 1, 2), layer("t128_k2", 240, 16, 13, 13, 128, 2, 1, 0),
+         layer("t64_k5", 200, 48, 13, 13, 60, 5, 1, 2), layer("t32_k3", 9, 80, 13, 13, 30, 3, 1, 1)]
+
+
+@pytest.mark.parametrize("L", FORMS, ids=ids(FORMS))
+def test_row_tiles(B, L):
+    x, w, b = synth.make_x(L, 6), synth.make_w(L, 6), synth.make_bias(L, 6)
+    got, names = ran(B, lambda: gpu_forward(B, L, x, w, b, B.LOWER_FUSED))
+    form = {"t96": "<2, 3", "t80": "<2, 3", "t12": "<4, 2", "t64": "<2, 2", "t32": "<1, 2"}[L.name[:3]]
+    assert any(n.startswith(KERNEL + form) for n in names), names
+    want = oracle.conv_forward(odims(oracle, L), x, w, b)
+    assert rel_err(got, want) <= TOL_F32
+    # values that are not finite, met by whole tiles and by the rows and positions of another wave
+    x[0, 0, 0, 0], x[1, 1, 5, 6], x[-1, 2, 12, 12], w[3, 1, 1, 1], w[-1, 0, 0, 0] = np.inf, -np.inf, np.nan, 3.4e38, np.inf
+    check_not_finite(gpu_forward(B, L, x, w, b, B.LOWER_FUSED), oracle.conv_forward(odims(oracle, L), x, w, b))
