@@ -8,7 +8,10 @@ there is no fallback: importing this module raises if libcct.so is missing.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
+
+import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libcct.so")
@@ -204,46 +207,58 @@ def cct_calibration_copy(src, dst) -> None:
 
 # ---- device entry points -----------------------------------------------------------------
 
+# A call of a small layer is as long as what happens here and in the launches, so that every tensor is looked at
+# with few calls (shapes compare as tuples without a copy), the shapes of a descriptor are asked once per value of
+# it, and the stream is asked for its number only (a Stream object for it takes 1.5 us).
+
 def _ptr(t, name, shape=None, optional=False):
-    import torch
     if t is None:
         if optional:
             return None
         raise ValueError("%s is required" % name)
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise TypeError("%s must be a torch tensor on the GPU" % name)
-    if t.dtype != torch.float32 or not t.is_contiguous():
+    if t.dtype is not torch.float32 or not t.is_contiguous():
         raise TypeError("%s must be contiguous fp32" % name)
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != shape:
         raise ValueError("%s has shape %s, expected %s" % (name, tuple(t.shape), tuple(shape)))
     return t.data_ptr()
 
 
-def _stream():
-    import torch
-    return torch.cuda.current_stream().cuda_stream
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
+if _raw_stream is not None and _device is not None:
+    def _stream():  # the tensors of the call have initialised the device
+        return _raw_stream(_device())
+else:
+    def _stream():
+        return torch.cuda.current_stream().cuda_stream
 
 
 def _ws(workspace):
-    import torch
     if not isinstance(workspace, torch.Tensor) or not workspace.is_cuda or \
-            workspace.dtype != torch.uint8 or not workspace.is_contiguous():
+            workspace.dtype is not torch.uint8 or not workspace.is_contiguous():
         raise TypeError("workspace must be a contiguous uint8 torch tensor on the GPU")
     return workspace.data_ptr(), workspace.numel()
 
 
 def alloc_workspace(desc: ConvDesc, pass_: int, images_per_chunk: int | None = None):
     """Caller-side helper: a uint8 device tensor of the queried size."""
-    import torch
     n = cct_conv_workspace_bytes(desc, pass_) if images_per_chunk is None else \
         cct_conv_workspace_bytes_for_chunk(desc, pass_, images_per_chunk)
     return torch.empty(n, dtype=torch.uint8, device="cuda")
 
 
-def _shapes(desc: ConvDesc):
+@functools.lru_cache(maxsize=1024)
+def _shapes_of(fields: bytes):
+    desc = ConvDesc.from_buffer_copy(fields)
     ho, wo = cct_conv_output_dims(desc)
     return ((desc.N, desc.C, desc.H, desc.W), (desc.O, desc.C // desc.groups, desc.K, desc.K),
             (desc.N, desc.O, ho, wo))
+
+
+def _shapes(desc: ConvDesc):
+    return _shapes_of(bytes(desc))
 
 
 def cct_conv_forward(desc: ConvDesc, x, w, bias, y, workspace) -> None:
@@ -299,6 +314,13 @@ def cct_pool_output_dims(desc: PoolDesc):
     return ho.value, wo.value
 
 
+@functools.lru_cache(maxsize=1024)
+def _pool_shapes_of(fields: bytes):
+    desc = PoolDesc.from_buffer_copy(fields)
+    ho, wo = cct_pool_output_dims(desc)
+    return (desc.N, desc.C, desc.H, desc.W), (desc.N, desc.C, ho, wo)
+
+
 def cct_relu_forward(x, y) -> None:
     _check(_lib.cct_relu_forward(_ptr(x, "x"), _ptr(y, "y", x.shape), x.numel(), _stream()),
            "cct_relu_forward")
@@ -310,27 +332,24 @@ def cct_relu_backward(x, dy, dx) -> None:
 
 
 def _iptr(t, name, shape):
-    import torch
-    if not isinstance(t, torch.Tensor) or not t.is_cuda or t.dtype != torch.int32 or \
-            not t.is_contiguous() or tuple(t.shape) != tuple(shape):
+    if not isinstance(t, torch.Tensor) or not t.is_cuda or t.dtype is not torch.int32 or \
+            not t.is_contiguous() or t.shape != shape:
         raise TypeError("%s must be a contiguous int32 GPU tensor of shape %s" % (name, tuple(shape)))
     return t.data_ptr()
 
 
 def cct_maxpool_forward(desc: PoolDesc, x, y, argmax=None) -> None:
-    ho, wo = cct_pool_output_dims(desc)
-    ys = (desc.N, desc.C, ho, wo)
-    _check(_lib.cct_maxpool_forward(ctypes.byref(desc), _ptr(x, "x", (desc.N, desc.C, desc.H, desc.W)),
+    xs, ys = _pool_shapes_of(bytes(desc))
+    _check(_lib.cct_maxpool_forward(ctypes.byref(desc), _ptr(x, "x", xs),
                                     _ptr(y, "y", ys),
                                     None if argmax is None else _iptr(argmax, "argmax", ys),
                                     _stream()), "cct_maxpool_forward")
 
 
 def cct_maxpool_backward(desc: PoolDesc, dy, argmax, dx) -> None:
-    ho, wo = cct_pool_output_dims(desc)
-    ys = (desc.N, desc.C, ho, wo)
+    xs, ys = _pool_shapes_of(bytes(desc))
     _check(_lib.cct_maxpool_backward(ctypes.byref(desc), _ptr(dy, "dy", ys), _iptr(argmax, "argmax", ys),
-                                     _ptr(dx, "dx", (desc.N, desc.C, desc.H, desc.W)), _stream()),
+                                     _ptr(dx, "dx", xs), _stream()),
            "cct_maxpool_backward")
 
 
@@ -351,9 +370,8 @@ def cct_lrn_backward(desc: LrnDesc, x, dy, dx) -> None:
 
 
 def _u8ptr(t, name, shape):
-    import torch
-    if not isinstance(t, torch.Tensor) or not t.is_cuda or t.dtype != torch.uint8 or \
-            not t.is_contiguous() or tuple(t.shape) != tuple(shape):
+    if not isinstance(t, torch.Tensor) or not t.is_cuda or t.dtype is not torch.uint8 or \
+            not t.is_contiguous() or t.shape != shape:
         raise TypeError("%s must be a contiguous uint8 GPU tensor of shape %s" % (name, tuple(shape)))
     return t.data_ptr()
 
