@@ -1173,6 +1173,8 @@ int forward_on_workspace(const cct_conv_desc_t* desc, const float* x, const floa
   }
   if (fc)
     return fc_forward(d, fp, x, w, bias, y, static_cast<char*>(workspace), (hipStream_t)hip_stream);
+  if (d.lowering == CCT_LOWER_AUTO && conv_small_fits(d, g.Hout, g.Wout))
+    return launch_conv_small(d, g.Hout, g.Wout, x, w, bias, y, (hipStream_t)hip_stream);
   hipStream_t st = (hipStream_t)hip_stream;
   char* ws = static_cast<char*>(workspace);
   const int bf16 = d.precision == CCT_PREC_BF16_IN_F32_ACC;

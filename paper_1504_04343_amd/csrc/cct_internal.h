@@ -203,6 +203,10 @@ struct GranulesPlan {
 bool granules_plan(const cct_conv_desc_t& d, int pass, long long nimg, GranulesPlan* P);
 int launch_granules(const cct_conv_desc_t& d, int pass, const GranulesPlan& P, int nimg, const float* in,
                     const float* w, const float* bias, float* out, char* ws, hipStream_t st);
+// Forward pass of the smallest layers in one launch, without a workspace (conv_small.hip).
+bool conv_small_fits(const cct_conv_desc_t& d, int Hout, int Wout);
+int launch_conv_small(const cct_conv_desc_t& d, int Hout, int Wout, const float* x, const float* w, const float* bias,
+                      float* y, hipStream_t st);
 // Tile sizes the launchers will use for a problem (so that the planner can pad the packs).
 void gemm_tn_tile(int M, int Ncols, int* BM, int* BN, int* BK);
 void gemm_nt_tile(int M, int N, int* BM, int* BN, int* BK);
