@@ -24,10 +24,12 @@
 //     one; with an odd number of tiles the last one is paired with zeros.
 // 16x16x32 and not 32x32x16 for the reasons in granule_product.h, and because rows then come in blocks of 16:
 // 96 kernels run as 2 x 48 rows instead of 128.  Measured, us, 32x32x16 -> 16x16x32: conv1 forward (96 rows) 472
-// -> 405, conv2 forward 490 -> 460, backward-data 613 -> 600, conv3 at batch 1024 1238 -> 1160 and 1273 -> 1187;
-// 50 images of conv5, one workgroup per CU: forward 72 -> 75, backward-data 53 -> 53.  48-row tiles for conv2's
-// backward-data (48 rows on 64) were slower than the padding, 800 against 730: four waves then ask the L1 for the
-// same 9 KiB per 576 MFMA cycles.  Splitting and loading in pieces between the MFMAs: no gain (conv5 75 -> 78).
+// -> 403, conv2 forward 490 -> 450, backward-data 613 -> 586, conv3 at batch 1024 1238 -> 1141 and 1273 -> 1182;
+// 64 images of 28 x 28, 64 channels: K = 7 to 64 kernels 149 -> 111, K = 5 to 96 kernels 106 -> 87.  Lone workgroups
+// of 64 and 32 rows are a little slower: 50 images of conv5 forward 72 -> 75, backward-data 53 -> 53, 4 images of
+// 28 x 28, 64 -> 128, K = 3, 17.8 -> 18.9.  48-row tiles for conv2's backward-data (48 rows on 64) were slower than
+// the padding, 800 against 730: four waves then ask the L1 for the same 9 KiB per 576 MFMA cycles.  Splitting and
+// loading in pieces between the MFMAs gave nothing (conv5 75 -> 78), nor did kernel values four pairs ahead.
 //   - KT: the kernel size where it is compiled in (3, 5: all taps of a group unrolled); 0 = any K.
 //   - S: 1 = the tensor itself; 2, 4 = space to depth: the padded input is read as a tensor of S*S
 //     times as many channels on a grid S times as coarse (channel = (ci, dh, dw)), which turns a
@@ -84,7 +86,7 @@ __device__ __forceinline__ const float* pixel_of(const GemmTN& p, int g, int n, 
 constexpr int kCells(int KT) { return KT ? 2 : 3; }
 
 template <int WAVES_M, int RB, int KT, int S>
-__global__ __launch_bounds__(NT, WAVES_M * RB == 2 && S == 1 ? 3 : 2) void conv_fused_split(GemmTN p, KcGeom fg, int tiles_m, int tiles_n) {
+__global__ __launch_bounds__(NT, 2) void conv_fused_split(GemmTN p, KcGeom fg, int tiles_m, int tiles_n) {
   constexpr int QU = kCells(KT);  // cells per thread and slot
   constexpr int MW = 16 * RB;     // rows of a wave
   constexpr int BM = MW * WAVES_M;
@@ -260,9 +262,9 @@ __global__ __launch_bounds__(NT, WAVES_M * RB == 2 && S == 1 ? 3 : 2) void conv_
     for (int s = 0; s < 2 * QU; ++s) stage_store(first[s], 0, s);
   }
   // The next group's four steps, FL at a time: loaded before one pair of tiles, stored before a later one, so that
-  // the MFMAs between cover the way to memory.  Register budget decides FL; 5 x 5 kernels have the tiles to go
-  // one by one.
-  constexpr int FL = KT == 5 ? 1 : KT == 3 && WAVES_M * RB <= 4 ? 4 : 2;  // KT == 0: one cell
+  // the MFMAs between cover the way to memory.  Register budget decides FL; where it is short, 5 x 5 kernels have
+  // the tiles to go one by one.
+  constexpr int FL = KT != 0 && WAVES_M * RB <= 4 && S == 1 ? 4 : KT == 5 ? 1 : 2;  // KT == 0: one cell
   float stg[FL][8];
 
   // ---- kernel-matrix operands straight from the pack (L2), two pairs of tiles ahead
@@ -348,9 +350,10 @@ __global__ __launch_bounds__(NT, WAVES_M * RB == 2 && S == 1 ? 3 : 2) void conv_
   load_a(1);
 
   // operand sets of B: FAR blocks are multiplied together while the next FAR are read; two where the registers
-  // allow it, so that an accumulator's MFMAs are further apart (conv2's backward-data 612 -> 600 us).  `off`: where
+  // allow it, so that an accumulator's MFMAs are further apart (conv2's backward-data 612 -> 600 us;
+  // held to 168 registers for three workgroups of 32 rows per CU they spill: 256 -> 21 channels, K = 3, 67 -> 125).  `off`: where
   // the lane's tile of the pair lies from the position's first cell
-  constexpr int NB = RB * WN <= 8 ? 4 : 2, FAR = NB / 2;
+  constexpr int NB = RB * WN <= 8 && S < 4 ? 4 : 2, FAR = NB / 2;
   u32x4 b[NB][3];
   auto read_b = [&](int set, int j, int off) {
     const u32x4* src = reinterpret_cast<const u32x4*>(Xs + bbase[j] + off);
@@ -469,17 +472,23 @@ __global__ __launch_bounds__(NT, WAVES_M * RB == 2 && S == 1 ? 3 : 2) void conv_
 #pragma unroll
     for (int s = 0; s < FL; ++s) stage_load(stg[s], 1, s);
   int pp = 0, grp = 0, slot = 0;  // slot: KT == 0
-  int cur = offsets[lane_hi];
+  // the lane's offset of the pair `ahead` of this one, read from LDS a pair before it is needed
+  auto offset = [&](int ahead) {
+    const bool wraps = pp + ahead >= period;
+    return offsets[2 * (wraps ? pp + ahead - period : pp + ahead) + lane_hi] + (!KT && wraps ? slot_b - slot : slot);
+  };
+  int cur = offset(0), nxt = offset(1);
 #pragma unroll
   for (int j = 0; j < FAR; ++j) read_b(j, j, cur);
   auto pair = [&](int set) {
     const bool wraps = pp + 1 == period;
-    if (!KT && wraps) slot = slot_b - slot;
-    const int nxt = offsets[(wraps ? 0 : 2 * pp + 2) + lane_hi] + slot;
+    const int then = offset(2);
     const bool turn = stage(pp, grp);
     multiply(set, cur, nxt, turn);
     load_a(set);
     cur = nxt;
+    nxt = then;
+    if (!KT && wraps) slot = slot_b - slot;
     pp = wraps ? 0 : pp + 1;
     grp += wraps ? (KT ? 2 : 1) : 0;
     end_pair();
@@ -832,8 +841,7 @@ double conv_fused_split_seconds(const GemmTN& p, int nimg) {
   const long long tn = column_tiles(p, fg, nimg);
   const int BM = split_bm(p, tn), S = p.s2d ? p.s2d : 1, KT = p.gK == 3 || (p.gK == 5 && S == 1) ? p.gK : 0;
   // workgroups that registers and LDS let share a CU
-  const int regs = BM == 32 && S == 1 ? 3 : 2;
-  const int share = std::max(1, std::min(regs, (int)(160 * 1024 / lds)));
+  const int share = std::max(1, std::min(2, (int)(160 * 1024 / lds)));
   double alone = BM == 128 ? 0.50e-6 : BM == 96 ? 0.43e-6 : BM == 64 ? 0.33e-6 : 0.26e-6;
   double shared = BM == 128 ? 0.48e-6 : BM == 96 ? 0.41e-6 : BM == 64 ? 0.30e-6 : 0.20e-6;
   double group = KT == 0 || S > 1 ? 3.0e-6 : 2.3e-6;
