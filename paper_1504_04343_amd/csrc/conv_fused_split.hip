@@ -350,9 +350,10 @@ __global__ __launch_bounds__(NT, 2) void conv_fused_split(GemmTN p, KcGeom fg, i
   load_a(1);
 
   // operand sets of B: FAR blocks are multiplied together while the next FAR are read; two where the registers
-  // allow it, so that an accumulator's MFMAs are further apart (conv2's backward-data 612 -> 600 us;
-  // held to 168 registers for three workgroups of 32 rows per CU they spill: 256 -> 21 channels, K = 3, 67 -> 125).  `off`: where
-  // the lane's tile of the pair lies from the position's first cell
+  // allow it, so that an accumulator's MFMAs are further apart (conv2's backward-data 612 -> 600 us; 32 rows need
+  // more than the 168 registers of three workgroups per CU for it: held to them the loop spilled, 64 images of
+  // 28 x 28, 256 -> 21 channels, K = 3, 125 us instead of 67).  `off`: where the lane's tile of the pair lies from
+  // the position's first cell
   constexpr int NB = RB * WN <= 8 && S < 4 ? 4 : 2, FAR = NB / 2;
   u32x4 b[NB][3];
   auto read_b = [&](int set, int j, int off) {
