@@ -1,36 +1,40 @@
 // Fused forward / backward-data pass (the "Fusion" of Sec. 2.1) for fp32 operands on the bf16 matrix
 // cores: every operand is the exact sum of three bf16 terms and a product is six
-// v_mfma_f32_16x16x32_bf16 (split_bf16.h).
+// bf16 MFMAs (split_bf16.h).
 //
 // Product: C[m][pos] = sum_{grp, tap, c} K^[grp][tap][m][c] * xpad[n, grp*16 + c, r*s + i, c*s + j]
 //   - a workgroup owns BM rows x 128 consecutive positions; a wave owns 32 or 48 rows x (all 128 | half |
-//     a quarter of them) positions, two accumulators per 16 x 16 block;
+//     a quarter of them) positions, two accumulators per block of results;
 //   - per channel group of 16 it stages the zero-padded input rows its positions can touch as cells
 //     (row, column) in a two-slot LDS ring, split while they are staged.  A cell is three terms of 16 bytes
 //     for each half of its 16 channels; the halves lie apart, so that cells are 48 bytes = three 16-byte
 //     slots from the next and reads of consecutive cells do not conflict;
-//   - a tile is one tap of one channel group, a pair of tiles the 32 reduction indices of an MFMA: lanes 0-31
-//     supply the first, lanes 32-63 the second.  The B operand of a lane is 16 bytes per term of its position's
-//     cell at its tap, read ahead of the MFMAs; where a tile's cells begin stands in a table in LDS;
+//   - a tile is one tap of one channel group: 16 reduction indices.  The B operand of a lane is 16 bytes per
+//     term of its position's cell at its tap, read ahead of the MFMAs;
 //   - the kernel matrix comes packed and split as [group][tile][term][row][16] and never passes
-//     through LDS: a lane loads the 16 bytes of its row, tile and term straight from the pack, two pairs
-//     ahead, the pair and term in the scalar offset.  With all four waves stacked along the rows
+//     through LDS: a lane loads the 16 bytes of its row, tile and term straight from the pack, some tiles
+//     ahead, the tile and term in the scalar offset.  With all four waves stacked along the rows
 //     no two waves read the same rows, which is why a wave is 32 x 128 and not 64 x 64: the pack is
-//     read once per workgroup and pair (24 KiB per 1536 MFMA cycles of a wave) and the cells four
+//     read once per workgroup and tile (12 KiB per 768 MFMA cycles of a wave) and the cells four
 //     times from LDS (48 of 128 bytes per cycle), where 64 x 64 waves would ask 24 KiB of the L1;
 //   - the cells of the next group are fetched and written in up to four steps of 8 channels, spread over the
-//     pairs; the workgroup meets when they are published.
-//   - An odd number of taps (KT: 3, 5) makes pairs that take the last tap of one group and the first of the next
-//     one; with an odd number of tiles the last one is paired with zeros.
-// 16x16x32 and not 32x32x16 for the reasons in granule_product.h, and because rows then come in blocks of 16:
-// 96 kernels run as 2 x 48 rows instead of 128.  Measured, us, 32x32x16 -> 16x16x32: conv1 forward (96 rows) 472
-// -> 403, conv2 forward 490 -> 450, backward-data 613 -> 586, conv3 at batch 1024 1238 -> 1141 and 1273 -> 1182;
-// 64 images of 28 x 28, 64 channels: K = 7 to 64 kernels 149 -> 111, K = 5 to 96 kernels 106 -> 87.  Lone workgroups
-// of 64 and 32 rows are a little slower: 50 images of conv5 forward 72 -> 75, backward-data 53 -> 53, 4 images of
-// 28 x 28, 64 -> 128, K = 3, 17.8 -> 18.9.  48-row tiles for conv2's backward-data (48 rows on 64) were slower than
-// the padding, 800 against 730: four waves then ask the L1 for the same 9 KiB per 576 MFMA cycles.  Splitting and
-// loading in pieces between the MFMAs gave nothing (conv5 75 -> 78), nor did kernel values four pairs ahead.
-//   - KT: the kernel size where it is compiled in (3, 5: all taps of a group unrolled); 0 = any K.
+//     tiles; the workgroup meets when they are published.
+// Two forms, by the edge MB of the blocks of results (which runs where: split_block):
+//   - 16: v_mfma_f32_16x16x32_bf16 takes a pair of tiles, lanes 0-31 supply the first and lanes 32-63 the second;
+//     where a tile's cells begin stands in a table in LDS.  Any K.  An odd number of taps (3 x 3, 5 x 5) makes pairs
+//     that take the last tap of one group and the first of the next one; with an odd number of tiles the last one is
+//     paired with zeros.  It does more per watt (granule_product.h), which large launches are bound by, and rows come
+//     in blocks of 16: 96 kernels run as 2 x 48 rows.  Measured, us, 32 -> 16: conv1 forward (96 rows) 472 -> 403,
+//     conv2 forward 490 -> 450, backward-data 613 -> 586, conv3 at batch 1024 1238 -> 1141 and 1273 -> 1182; 64 images
+//     of 28 x 28, 64 channels: K = 7 to 64 kernels 149 -> 111.
+//   - 32: v_mfma_f32_32x32x16_bf16 takes one tile; 3 x 3 and 5 x 5 kernels, all taps of a group unrolled, so that
+//     nothing is looked up or decided between the MFMAs of a lone wave.  16 -> 32: 50 images of conv5 forward
+//     71.7 -> 68.6, 4 images of 28 x 28, 64 -> 128, K = 3, 18.9 -> 17.8, 48 workgroups of K = 5 24.4 -> 21.1; over 9100
+//     layers 0.93 (K = 3) and 0.86 times (K = 5) the time on 32 rows, 0.94 and 0.95 on 64.
+// 48-row tiles for conv2's backward-data (48 rows on 64) were slower than the padding, 800 against 730: four waves
+// then ask the L1 for the same 9 KiB per 576 MFMA cycles.  Splitting and loading in pieces between the MFMAs gave
+// nothing (conv5 75 -> 78), nor did kernel values four pairs ahead.
+//   - KT: the kernel size where it is compiled in (3, 5); 0 = any K.
 //   - S: 1 = the tensor itself; 2, 4 = space to depth: the padded input is read as a tensor of S*S
 //     times as many channels on a grid S times as coarse (channel = (ci, dh, dw)), which turns a
 //     layer of stride S into an unpadded one of stride 1 with ceil(K/S) taps.
@@ -49,8 +53,8 @@ using namespace kc;
 constexpr int CB = 48;  // bytes between cells in LDS, of each half of their channels
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // 16 bytes, dword aligned
 
-// K tiles per channel group: the taps, padded (zero tiles) to what the tile loop takes at a time
-// (AD tiles; see launch_rows for the sizes that are compiled in)
+// K tiles per channel group: the taps; an even number (a zero tile) where K is not compiled in and pairs of tiles stay
+// inside a group
 __host__ __device__ constexpr int tiles_per_group(int K) {
   return K == 3 || K == 5 ? K * K : (K * K + 1) / 2 * 2;
 }
@@ -82,17 +86,19 @@ __device__ __forceinline__ const float* pixel_of(const GemmTN& p, int g, int n, 
          (long long)((g * p.gCg + ch) / (S * S)) * p.x_plane + (long long)h * p.x_w + w;
 }
 
-// cells per thread: sizes without an unrolled group take a third one (7 x 7 windows on wide rows)
+// cells per thread: sizes that are not compiled in take a third one (7 x 7 windows on wide rows)
 constexpr int kCells(int KT) { return KT ? 2 : 3; }
 
-template <int WAVES_M, int RB, int KT, int S>
+template <int WAVES_M, int RB, int KT, int S, int MB>
 __global__ __launch_bounds__(NT, 2) void conv_fused_split(GemmTN p, KcGeom fg, int tiles_m, int tiles_n) {
   constexpr int QU = kCells(KT);  // cells per thread and slot
   constexpr int MW = 16 * RB;     // rows of a wave
   constexpr int BM = MW * WAVES_M;
   constexpr int WAVES_N = 4 / WAVES_M;
-  constexpr int WN = BN / (16 * WAVES_N);  // blocks of 16 positions of a wave
+  constexpr int WN = BN / (MB * WAVES_N);  // blocks of MB positions of a wave
+  constexpr int QB = MW * MB / 256;        // a lane's results in a block column: quads of consecutive rows
   static_assert(WAVES_M * WAVES_N == 4, "4 waves per workgroup");
+  static_assert(MB == 16 || (MB == 32 && RB == 2 && KT != 0), "32 x 32 blocks: waves of 32 rows, unrolled taps");
 
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_b[];
   unsigned char* Xs = smem_b;  // [2 slots][2 halves][R][CB]
@@ -102,9 +108,11 @@ __global__ __launch_bounds__(NT, 2) void conv_fused_split(GemmTN p, KcGeom fg, i
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wave_m = wave / WAVES_N, wave_n = wave % WAVES_N;
-  const int lane_lo = lane & 15;        // row / column inside a block
-  const int lane_hi = lane >> 5;        // which tile of a pair the lane supplies
-  const int lane_ch = (lane >> 4) & 1;  // and which half of its 16 channels
+  const int lane_lo = lane & (MB - 1);                             // row / column inside a block
+  const int lane_hi = lane >> 5;                                   // which tile of a pair the lane supplies
+  const int lane_ch = MB == 16 ? (lane >> 4) & 1 : lane_hi;        // which half of a tile's 16 channels
+  const int row4 = MB == 16 ? (lane >> 4) * 4 : lane_hi * 4;       // the lane's rows of a block: row4 .. row4 + 3
+  auto quad = [](int i) { return MB == 16 ? 16 * i : 8 * i; };     // + this, for quad i
 
   // consecutive workgroup ids go round-robin over the 8 XCDs: give every XCD a contiguous run of
   // column tiles with the M tiles of one column tile next to each other (they share x through L2)
@@ -261,80 +269,12 @@ __global__ __launch_bounds__(NT, 2) void conv_fused_split(GemmTN p, KcGeom fg, i
 #pragma unroll
     for (int s = 0; s < 2 * QU; ++s) stage_store(first[s], 0, s);
   }
-  // The next group's four steps, FL at a time: loaded before one pair of tiles, stored before a later one, so that
-  // the MFMAs between cover the way to memory.  Register budget decides FL; where it is short, 5 x 5 kernels have
-  // the tiles to go one by one.
-  constexpr int FL = KT != 0 && WAVES_M * RB <= 4 && S == 1 ? 4 : KT == 5 ? 1 : 2;  // KT == 0: one cell
-  float stg[FL][8];
-
-  // ---- kernel-matrix operands straight from the pack (L2), two pairs of tiles ahead
-  const int tpg = KT ? KT * KT : tiles_per_group(p.gK);
-  const int ktiles = fg.ngroups * tpg, pairs = (ktiles + 1) / 2;
-  const unsigned short* Abase = reinterpret_cast<const unsigned short*>(p.A) +
-                                ((long long)g * p.a_gs * 3 + (long long)(m0 + wave_m * MW) * CG);
-  const __amdgpu_buffer_rsrc_t a_rs =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned short*>(Abase), 0, 0x7fffffff, 0x00020000);
-  const unsigned term_b = (unsigned)p.Mpad * CG * 2u;
-  const unsigned a_voff = (lane_lo * CG + lane_ch * 8) * 2 + lane_hi * (3u * term_b);
-  const unsigned a_half = lane_hi ? 0x80000000u : a_voff;  // the last tile has no partner: zeros
-  u32x4 a[2][RB][3];
-  const unsigned a_last = (unsigned)(pairs - 1) * (6u * term_b);
-  unsigned so = 0;
-  auto load_a = [&](int set) {  // the next pair, at the end the last one again
-    const unsigned vo = so == a_last && (ktiles & 1) ? a_half : a_voff;
-#pragma unroll
-    for (int i = 0; i < RB; ++i)
-#pragma unroll
-      for (int q = 0; q < 3; ++q)
-        a[set][i][q] = __builtin_bit_cast(
-            u32x4, __builtin_amdgcn_raw_buffer_load_b128(a_rs, (int)(vo + i * 16 * CG * 2), (int)(so + q * term_b), 0));
-    so = min(so + 6u * term_b, a_last);
-  };
-
-  f32x4 acc_h[RB][WN], acc_c[RB][WN];  // h*h, and the corrections
-#pragma unroll
-  for (int i = 0; i < RB; ++i)
-#pragma unroll
-    for (int j = 0; j < WN; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) acc_h[i][j][r] = acc_c[i][j][r] = 0.f;
-  // The h*h chain rounds as it goes.  Waves with few blocks have the registers to break it every 8 pairs, which keeps
-  // the error of small layers below that of the lowered layouts (their sums come in K or K*K parts: 11 images of
-  // 27 x 27, two groups of 128 -> 48 channels, K = 5: 2-norm 2.2e-7 there, 3.4e-7 with one chain, 1.2e-7 with parts;
-  // the time is the same within 1 %).  Against one fp32 chain a single one is a third of the error already.
-  constexpr bool PARTS = RB * WN <= 8;
-  f32x4 total[PARTS ? RB : 1][PARTS ? WN : 1];
-  int left = 8;
-  if constexpr (PARTS) {
-#pragma unroll
-    for (int i = 0; i < RB; ++i)
-#pragma unroll
-      for (int j = 0; j < WN; ++j)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) total[i][j][r] = 0.f;
-  }
-  auto end_pair = [&]() {
-    if constexpr (PARTS) {
-      if (--left > 0) return;
-      left = 8;
-#pragma unroll
-      for (int i = 0; i < RB; ++i)
-#pragma unroll
-        for (int j = 0; j < WN; ++j)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            total[i][j][r] += acc_h[i][j][r];
-            acc_h[i][j][r] = 0.f;
-          }
-    }
-  };
-
   // per-lane byte offset of each owned position's cell
-  const int bn = wave_n * WN * 16 + lane_lo;
+  const int bn = wave_n * WN * MB + lane_lo;
   int bbase[WN];
 #pragma unroll
   for (int j = 0; j < WN; ++j) {
-    const int col = n0 + bn + j * 16;
+    const int col = n0 + bn + j * MB;
     int cb = 0;
     if (col < ce) {
       const int n = col / P, pix = col - n * P;
@@ -346,190 +286,405 @@ __global__ __launch_bounds__(NT, 2) void conv_fused_split(GemmTN p, KcGeom fg, i
     bbase[j] = cb * CB + lane_ch * half_b;
   }
 
-  load_a(0);
-  load_a(1);
+  // ---- kernel-matrix operands straight from the pack (L2)
+  const int tpg = KT ? KT * KT : tiles_per_group(p.gK);
+  const int ktiles = fg.ngroups * tpg;
+  const unsigned short* Abase = reinterpret_cast<const unsigned short*>(p.A) +
+                                ((long long)g * p.a_gs * 3 + (long long)(m0 + wave_m * MW) * CG);
+  const __amdgpu_buffer_rsrc_t a_rs =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned short*>(Abase), 0, 0x7fffffff, 0x00020000);
+  const unsigned term_b = (unsigned)p.Mpad * CG * 2u;
+  const unsigned a_row = (lane_lo * CG + lane_ch * 8) * 2;  // bytes inside a term
 
-  // operand sets of B: FAR blocks are multiplied together while the next FAR are read; two where the registers
-  // allow it, so that an accumulator's MFMAs are further apart (conv2's backward-data 612 -> 600 us; 32 rows need
-  // more than the 168 registers of three workgroups per CU for it: held to them the loop spilled, 64 images of
-  // 28 x 28, 256 -> 21 channels, K = 3, 125 us instead of 67).  `off`: where the lane's tile of the pair lies from
-  // the position's first cell
-  constexpr int NB = RB * WN <= 8 && S < 4 ? 4 : 2, FAR = NB / 2;
-  u32x4 b[NB][3];
-  auto read_b = [&](int set, int j, int off) {
-    const u32x4* src = reinterpret_cast<const u32x4*>(Xs + bbase[j] + off);
+  f32x4 out[QB][WN];  // the results
+  if constexpr (MB == 16) {
+    // The next group's four steps, FL at a time: loaded before one pair of tiles, stored before a later one, so that
+    // the MFMAs between cover the way to memory.  Register budget decides FL; where it is short, 5 x 5 kernels have
+    // the tiles to go one by one.
+    constexpr int FL = KT != 0 && WAVES_M * RB <= 4 ? 4 : KT == 5 ? 1 : 2;  // KT == 0: one cell
+    float stg[FL][8];
+
+    // operands two pairs of tiles ahead
+    const int pairs = (ktiles + 1) / 2;
+    const unsigned a_voff = a_row + lane_hi * (3u * term_b);
+    const unsigned a_half = lane_hi ? 0x80000000u : a_voff;  // the last tile has no partner: zeros
+    u32x4 a[2][RB][3];
+    const unsigned a_last = (unsigned)(pairs - 1) * (6u * term_b);
+    unsigned so = 0;
+    auto load_a = [&](int set) {  // the next pair, at the end the last one again
+      const unsigned vo = so == a_last && (ktiles & 1) ? a_half : a_voff;
 #pragma unroll
-    for (int q = 0; q < 3; ++q) b[set][q] = src[q];
-  };
-  auto mfma6 = [&](int set, int j, int bs) {  // FAR blocks from j
-    __builtin_amdgcn_sched_barrier(0);
+      for (int i = 0; i < RB; ++i)
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+          a[set][i][q] = __builtin_bit_cast(
+              u32x4, __builtin_amdgcn_raw_buffer_load_b128(a_rs, (int)(vo + i * 16 * CG * 2), (int)(so + q * term_b), 0));
+      so = min(so + 6u * term_b, a_last);
+    };
+
+    f32x4 acc_h[RB][WN], acc_c[RB][WN];  // h*h, and the corrections
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+      for (int j = 0; j < WN; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc_h[i][j][r] = acc_c[i][j][r] = 0.f;
+    // The h*h chain rounds as it goes.  Waves with few blocks have the registers to break it every 8 pairs, which keeps
+    // the error of small layers below that of the lowered layouts (their sums come in K or K*K parts: 11 images of
+    // 27 x 27, two groups of 128 -> 48 channels, K = 5: 2-norm 2.2e-7 there, 3.4e-7 with one chain, 1.2e-7 with parts;
+    // the time is the same within 1 %).  Against one fp32 chain a single one is a third of the error already.
+    constexpr bool PARTS = RB * WN <= 8;
+    f32x4 total[PARTS ? RB : 1][PARTS ? WN : 1];
+    int left = 8;
+    if constexpr (PARTS) {
+#pragma unroll
+      for (int i = 0; i < RB; ++i)
+#pragma unroll
+        for (int j = 0; j < WN; ++j)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) total[i][j][r] = 0.f;
+    }
+    auto end_pair = [&]() {
+      if constexpr (PARTS) {
+        if (--left > 0) return;
+        left = 8;
+#pragma unroll
+        for (int i = 0; i < RB; ++i)
+#pragma unroll
+          for (int j = 0; j < WN; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              total[i][j][r] += acc_h[i][j][r];
+              acc_h[i][j][r] = 0.f;
+            }
+      }
+    };
+
+    load_a(0);
+    load_a(1);
+
+    // operand sets of B: FAR blocks are multiplied together while the next FAR are read; two where the registers
+    // allow it, so that an accumulator's MFMAs are further apart (conv2's backward-data 612 -> 600 us; 32 rows need
+    // more than the 168 registers of three workgroups per CU for it: held to them the loop spilled, 64 images of
+    // 28 x 28, 256 -> 21 channels, K = 3, 125 us instead of 67).  `off`: where the lane's tile of the pair lies from
+    // the position's first cell
+    constexpr int NB = RB * WN <= 8 && S < 4 ? 4 : 2, FAR = NB / 2;
+    u32x4 b[NB][3];
+    auto read_b = [&](int set, int j, int off) {
+      const u32x4* src = reinterpret_cast<const u32x4*>(Xs + bbase[j] + off);
+#pragma unroll
+      for (int q = 0; q < 3; ++q) b[set][q] = src[q];
+    };
+    auto mfma6 = [&](int set, int j, int bs) {  // FAR blocks from j
+      __builtin_amdgcn_sched_barrier(0);
 #define CCT_M(X, Y, ACC)                                                                                  \
-  _Pragma("unroll") for (int jj = 0; jj < FAR; ++jj) _Pragma("unroll") for (int i = 0; i < RB; ++i)       \
-      ACC[i][j + jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(                                           \
-          __builtin_bit_cast(bf16x8, a[set][i][X]), __builtin_bit_cast(bf16x8, b[bs + jj][Y]), ACC[i][j + jj], 0, 0, 0)
-    CCT_M(2, 0, acc_c);
-    CCT_M(0, 2, acc_c);
-    CCT_M(1, 1, acc_c);
-    CCT_M(1, 0, acc_c);
-    CCT_M(0, 1, acc_c);
-    CCT_M(0, 0, acc_h);
+    _Pragma("unroll") for (int jj = 0; jj < FAR; ++jj) _Pragma("unroll") for (int i = 0; i < RB; ++i)       \
+        ACC[i][j + jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(                                           \
+            __builtin_bit_cast(bf16x8, a[set][i][X]), __builtin_bit_cast(bf16x8, b[bs + jj][Y]), ACC[i][j + jj], 0, 0, 0)
+      CCT_M(2, 0, acc_c);
+      CCT_M(0, 2, acc_c);
+      CCT_M(1, 1, acc_c);
+      CCT_M(1, 0, acc_c);
+      CCT_M(0, 1, acc_c);
+      CCT_M(0, 0, acc_h);
 #undef CCT_M
-    __builtin_amdgcn_sched_barrier(0);
-  };
-  // One pair of tiles: FAR blocks' operands are read while the FAR before them are multiplied, the next pair's first
-  // ones (at byte offset `nxt`) behind the last but FAR.  Where the next pair reads cells that were staged meanwhile
-  // (`turn`) the workgroup meets before that read: every one of them has been published by then.
-  auto multiply = [&](int set, int cur, int nxt, bool turn) {
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    // One pair of tiles: FAR blocks' operands are read while the FAR before them are multiplied, the next pair's first
+    // ones (at byte offset `nxt`) behind the last but FAR.  Where the next pair reads cells that were staged meanwhile
+    // (`turn`) the workgroup meets before that read: every one of them has been published by then.
+    auto multiply = [&](int set, int cur, int nxt, bool turn) {
 #pragma unroll
-    for (int j = 0; j < WN; j += FAR) {
-      const int ahead = j + FAR, bs = (set * WN + ahead) % NB;
-      if (ahead == WN && turn) __syncthreads();
+      for (int j = 0; j < WN; j += FAR) {
+        const int ahead = j + FAR, bs = (set * WN + ahead) % NB;
+        if (ahead == WN && turn) __syncthreads();
 #pragma unroll
-      for (int jj = 0; jj < FAR; ++jj) {
-        if (ahead < WN)
-          read_b(bs + jj, ahead + jj, cur);
-        else
-          read_b(bs + jj, jj, nxt);
+        for (int jj = 0; jj < FAR; ++jj) {
+          if (ahead < WN)
+            read_b(bs + jj, ahead + jj, cur);
+          else
+            read_b(bs + jj, jj, nxt);
+        }
+        mfma6(set, j, (set * WN + j) % NB);
       }
-      mfma6(set, j, (set * WN + j) % NB);
-    }
-  };
-  static_assert(2 * WN % NB == 0, "block 0 of every other pair uses operand set 0");
+    };
+    static_assert(2 * WN % NB == 0, "block 0 of every other pair uses operand set 0");
 
-  // ---- the tiles in turn: channel group, tap; groups alternate between the two slots.  A period of pairs begins
-  // with channel group `grp`.  An odd number of taps (KT) makes it two groups, KK pairs, of which pair H takes the
-  // last tap of the one and the first of the other; otherwise it is one group.
-  constexpr int KK = KT * KT, H = KK / 2, NP = 2 * QU / FL;
-  const int period = KT ? KK : tpg / 2;
-  int* offsets = reinterpret_cast<int*>(Xs + 2 * slot_b);  // of a period's tiles, from the position's first cell
-  for (int e = tid; e < 2 * period; e += NT) {
-    const int tap = KT ? e % KK : e < fg.KK ? e : 0;  // zero tile: any cell of the group
-    int off = (tap / p.gK * fg.Wp + tap % p.gK) * CB;
-    // the only group's last tile has no partner: any cells, its kernel values are zeros
-    if (KT && e >= KK) off = fg.ngroups == 1 ? 0 : off + slot_b;
-    offsets[e] = off;
-  }
-  __syncthreads();  // slot 0 and the offsets are visible
-
-  // Staging, before pair `pp` of a period; true: the next pair reads cells that this staged.  In the odd form the
-  // workgroup meets once more behind pair H, before it stages into the slot that is free then.
-  auto stage = [&](int pp, int grp) -> bool {
-    if constexpr (KT != 0) {
-      // phase f is stored before the (f + 1)-th of NP pairs spread over the group's share of the period; the next
-      // phase's loads go out at once
-      constexpr int N1 = H - 1, N2 = KK - 1 - H;
-      unsigned events = 0;
-#pragma unroll
-      for (int f = 0; f < NP; ++f) events |= 1u << (f + 1) * N1 / NP | 1u << (H + (f + 1) * N2 / NP);
-      if (!(events >> pp & 1)) return false;
-      const bool late = pp >= H;
-      const int to = grp + (late ? 2 : 1);
-      if (to >= fg.ngroups) return false;
-#pragma unroll
-      for (int f = 0; f < NP; ++f) {
-        if (pp == (f + 1) * N1 / NP || pp == H + (f + 1) * N2 / NP) {
-          if (f == 0 && late) __syncthreads();  // nobody reads slot 0 any more
-#pragma unroll
-          for (int s = 0; s < FL; ++s) stage_store(stg[s], late ? 0 : 1, f * FL + s);
-          if (f + 1 < NP || to + 1 < fg.ngroups)
-#pragma unroll
-            for (int s = 0; s < FL; ++s) stage_load(stg[s], f + 1 < NP ? to : to + 1, (f + 1) % NP * FL + s);
-        }
-      }
-      return pp == H - 1 || pp == KK - 1;
-    } else {
-      static_assert(FL == 2 || KT != 0, "a cell at a time");
-      if (grp + 1 >= fg.ngroups) return false;
-      // cell f is loaded in pair f * step and stored in pair (f + 1) * step, the last one (and what a short group
-      // leaves no pair for) in the group's last pair
-      const int step = max(1, period / QU), slot = (grp + 1) & 1;
-#pragma unroll
-      for (int f = 0; f < QU; ++f) {
-        if (f > 0 && pp == f * step) {
-#pragma unroll
-          for (int s = 0; s < 2; ++s) stage_store(stg[s], slot, 2 * (f - 1) + s);
-        }
-        if (pp == f * step) {
-#pragma unroll
-          for (int s = 0; s < 2; ++s) stage_load(stg[s], grp + 1, 2 * f + s);
-        }
-      }
-      if (pp != period - 1) return false;
-#pragma unroll
-      for (int f = 0; f < QU; ++f) {
-        if (f * step >= period) {
-#pragma unroll
-          for (int s = 0; s < 2; ++s) stage_load(stg[s], grp + 1, 2 * f + s);
-        }
-        if ((f + 1) * step >= period || f == QU - 1) {
-#pragma unroll
-          for (int s = 0; s < 2; ++s) stage_store(stg[s], slot, 2 * f + s);
-        }
-      }
-      return true;
+    // ---- the tiles in turn: channel group, tap; groups alternate between the two slots.  A period of pairs begins
+    // with channel group `grp`.  An odd number of taps (KT) makes it two groups, KK pairs, of which pair H takes the
+    // last tap of the one and the first of the other; otherwise it is one group.
+    constexpr int KK = KT * KT, H = KK / 2, NP = 2 * QU / FL;
+    const int period = KT ? KK : tpg / 2;
+    int* offsets = reinterpret_cast<int*>(Xs + 2 * slot_b);  // of a period's tiles, from the position's first cell
+    for (int e = tid; e < 2 * period; e += NT) {
+      const int tap = KT ? e % KK : e < fg.KK ? e : 0;  // zero tile: any cell of the group
+      int off = (tap / p.gK * fg.Wp + tap % p.gK) * CB;
+      // the only group's last tile has no partner: any cells, its kernel values are zeros
+      if (KT && e >= KK) off = fg.ngroups == 1 ? 0 : off + slot_b;
+      offsets[e] = off;
     }
-  };
-  if (KT != 0 && fg.ngroups > 1)
+    __syncthreads();  // slot 0 and the offsets are visible
+
+    // Staging, before pair `pp` of a period; true: the next pair reads cells that this staged.  In the odd form the
+    // workgroup meets once more behind pair H, before it stages into the slot that is free then.
+    auto stage = [&](int pp, int grp) -> bool {
+      if constexpr (KT != 0) {
+        // phase f is stored before the (f + 1)-th of NP pairs spread over the group's share of the period; the next
+        // phase's loads go out at once
+        constexpr int N1 = H - 1, N2 = KK - 1 - H;
+        unsigned events = 0;
 #pragma unroll
-    for (int s = 0; s < FL; ++s) stage_load(stg[s], 1, s);
-  int pp = 0, grp = 0, slot = 0;  // slot: KT == 0
-  // the lane's offset of the pair `ahead` of this one, read from LDS a pair before it is needed
-  auto offset = [&](int ahead) {
-    const bool wraps = pp + ahead >= period;
-    return offsets[2 * (wraps ? pp + ahead - period : pp + ahead) + lane_hi] + (!KT && wraps ? slot_b - slot : slot);
-  };
-  int cur = offset(0), nxt = offset(1);
+        for (int f = 0; f < NP; ++f) events |= 1u << (f + 1) * N1 / NP | 1u << (H + (f + 1) * N2 / NP);
+        if (!(events >> pp & 1)) return false;
+        const bool late = pp >= H;
+        const int to = grp + (late ? 2 : 1);
+        if (to >= fg.ngroups) return false;
 #pragma unroll
-  for (int j = 0; j < FAR; ++j) read_b(j, j, cur);
-  auto pair = [&](int set) {
-    const bool wraps = pp + 1 == period;
-    const int then = offset(2);
-    const bool turn = stage(pp, grp);
-    multiply(set, cur, nxt, turn);
-    load_a(set);
-    cur = nxt;
-    nxt = then;
-    if (!KT && wraps) slot = slot_b - slot;
-    pp = wraps ? 0 : pp + 1;
-    grp += wraps ? (KT ? 2 : 1) : 0;
-    end_pair();
-  };
-  for (int t = pairs; t > 1; t -= 2) {
-    pair(0);
-    pair(1);
+        for (int f = 0; f < NP; ++f) {
+          if (pp == (f + 1) * N1 / NP || pp == H + (f + 1) * N2 / NP) {
+            if (f == 0 && late) __syncthreads();  // nobody reads slot 0 any more
+#pragma unroll
+            for (int s = 0; s < FL; ++s) stage_store(stg[s], late ? 0 : 1, f * FL + s);
+            if (f + 1 < NP || to + 1 < fg.ngroups)
+#pragma unroll
+              for (int s = 0; s < FL; ++s) stage_load(stg[s], f + 1 < NP ? to : to + 1, (f + 1) % NP * FL + s);
+          }
+        }
+        return pp == H - 1 || pp == KK - 1;
+      } else {
+        static_assert(FL == 2 || KT != 0, "a cell at a time");
+        if (grp + 1 >= fg.ngroups) return false;
+        // cell f is loaded in pair f * step and stored in pair (f + 1) * step, the last one (and what a short group
+        // leaves no pair for) in the group's last pair
+        const int step = max(1, period / QU), slot = (grp + 1) & 1;
+#pragma unroll
+        for (int f = 0; f < QU; ++f) {
+          if (f > 0 && pp == f * step) {
+#pragma unroll
+            for (int s = 0; s < 2; ++s) stage_store(stg[s], slot, 2 * (f - 1) + s);
+          }
+          if (pp == f * step) {
+#pragma unroll
+            for (int s = 0; s < 2; ++s) stage_load(stg[s], grp + 1, 2 * f + s);
+          }
+        }
+        if (pp != period - 1) return false;
+#pragma unroll
+        for (int f = 0; f < QU; ++f) {
+          if (f * step >= period) {
+#pragma unroll
+            for (int s = 0; s < 2; ++s) stage_load(stg[s], grp + 1, 2 * f + s);
+          }
+          if ((f + 1) * step >= period || f == QU - 1) {
+#pragma unroll
+            for (int s = 0; s < 2; ++s) stage_store(stg[s], slot, 2 * f + s);
+          }
+        }
+        return true;
+      }
+    };
+    if (KT != 0 && fg.ngroups > 1)
+#pragma unroll
+      for (int s = 0; s < FL; ++s) stage_load(stg[s], 1, s);
+    int pp = 0, grp = 0, slot = 0;  // slot: KT == 0
+    // the lane's offset of the pair `ahead` of this one, read from LDS a pair before it is needed
+    auto offset = [&](int ahead) {
+      const bool wraps = pp + ahead >= period;
+      return offsets[2 * (wraps ? pp + ahead - period : pp + ahead) + lane_hi] + (!KT && wraps ? slot_b - slot : slot);
+    };
+    int cur = offset(0), nxt = offset(1);
+#pragma unroll
+    for (int j = 0; j < FAR; ++j) read_b(j, j, cur);
+    auto pair = [&](int set) {
+      const bool wraps = pp + 1 == period;
+      const int then = offset(2);
+      const bool turn = stage(pp, grp);
+      multiply(set, cur, nxt, turn);
+      load_a(set);
+      cur = nxt;
+      nxt = then;
+      if (!KT && wraps) slot = slot_b - slot;
+      pp = wraps ? 0 : pp + 1;
+      grp += wraps ? (KT ? 2 : 1) : 0;
+      end_pair();
+    };
+    for (int t = pairs; t > 1; t -= 2) {
+      pair(0);
+      pair(1);
+    }
+    if (pairs & 1) pair(0);
+
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+      for (int j = 0; j < WN; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          if constexpr (PARTS) acc_h[i][j][r] += total[i][j][r];
+          out[i][j][r] = acc_h[i][j][r] + acc_c[i][j][r];
+        }
+  } else {
+    // The next group's four steps, FL at a time: loaded in one tile, stored in a later one
+    constexpr int FL = KT == 5 ? 1 : S == 1 ? 4 : 2;
+    float stg[FL][8];
+
+    // kernel values AD tiles ahead
+    constexpr int AD = KT == 3 ? 3 : 5;
+    u32x4 a[AD][3];
+    auto load_a = [&](int set, int t) {
+      const unsigned so = (unsigned)min(t, ktiles - 1) * (3u * term_b);
+#pragma unroll
+      for (int q = 0; q < 3; ++q)
+        a[set][q] = __builtin_bit_cast(
+            u32x4, __builtin_amdgcn_raw_buffer_load_b128(a_rs, (int)a_row, (int)(so + q * term_b), 0));
+    };
+
+    floatx16 acc_h[WN], acc_c[WN];  // h*h, and the corrections
+#pragma unroll
+    for (int j = 0; j < WN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc_h[j][r] = acc_c[j][r] = 0.f;
+    // Parts as above: a group of 3 x 3 or two, half a group of 5 x 5 or a whole one, the longer ones where there are many,
+    // whose sum rounds too (2-norm, parts of 16 tiles -> these: 4 images of 28 x 28, 64 channels, K = 3 9.2e-8 -> 8.0e-8;
+    // 49 of 13 x 13, 192 channels, K = 3 1.00e-7 -> 1.02e-7, with one group 0.95e-7, but 463 -> 480 us in conv1's
+    // backward-data; 11 of 27 x 27, 48 channels, K = 5 9.6e-8 -> 9.2e-8; 4 of 13 x 13, 256 channels, K = 5 1.26e-7
+    // -> 1.27e-7).  A group's part is added in the first tile of the next one, behind that tile's corrections: its last
+    // MFMA is long done by then.
+    constexpr bool PARTS = WN <= 2;
+    floatx16 total[PARTS ? WN : 1];
+    if constexpr (PARTS) {
+#pragma unroll
+      for (int j = 0; j < WN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) total[j][r] = 0.f;
+    }
+    const bool short_parts = fg.ngroups <= (KT == 3 ? 4 : 8);
+    auto end_part = [&](int j) {
+      if constexpr (PARTS) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          total[j][r] += acc_h[j][r];
+          acc_h[j][r] = 0.f;
+        }
+      }
+    };
+
+#pragma unroll
+    for (int e = 0; e < AD; ++e) load_a(e, e);
+    __syncthreads();  // slot 0 is visible
+
+    // operand sets of B: the two blocks that are read and multiplied in turn; with one block per tile
+    // the set goes with the tile
+    constexpr int NB = WN == 1 ? AD : 2;
+    u32x4 b[NB][3];
+    auto read_b = [&](int set, int j, int off) {
+      const u32x4* src = reinterpret_cast<const u32x4*>(Xs + bbase[j] + off);
+#pragma unroll
+      for (int q = 0; q < 3; ++q) b[set][q] = src[q];
+    };
+    read_b(0, 0, 0);
+    int slot = 0;
+
+    // One tile: block j's operand is read while block j - 1 is multiplied, the next tile's first
+    // block (at byte offset `nxt`) behind the last but one; the registers of this tile's A operand are
+    // reloaded with tile t + AD behind its last MFMA.  In the last tile of a group (`turn`) the
+    // workgroup meets before the next group's first read: every cell of it has been published by
+    // then, and nobody reads the other slot's old cells any more.
+    auto mfma6 = [&](int set, int bs, int j, bool next_part) {
+      __builtin_amdgcn_sched_barrier(0);
+#define CCT_M(X, Y, ACC)                                                                       \
+    ACC = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[set][X]),          \
+                                                  __builtin_bit_cast(bf16x8, b[bs][Y]), ACC, 0, 0, 0)
+      CCT_M(2, 0, acc_c[j]);
+      CCT_M(0, 2, acc_c[j]);
+      CCT_M(1, 1, acc_c[j]);
+      CCT_M(1, 0, acc_c[j]);
+      CCT_M(0, 1, acc_c[j]);
+      if (next_part) end_part(j);
+      CCT_M(0, 0, acc_h[j]);
+#undef CCT_M
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    auto tile = [&](int set, int t, int cur, int nxt, bool turn, bool next_part) {
+#pragma unroll
+      for (int j = 0; j < WN; ++j) {
+        if (j + 1 < WN) {
+          read_b((j + 1) & 1, j + 1, cur);
+        } else {
+          if (turn) __syncthreads();
+          read_b(WN == 1 ? (set + 1) % AD : 0, 0, nxt);
+        }
+        mfma6(set, WN == 1 ? set : j & 1, j, next_part);
+      }
+      load_a(set, t + AD);
+    };
+    static_assert(WN == 1 || WN % 2 == 0, "block 0 of every tile uses operand set 0");
+
+    constexpr int KK = KT * KT;
+    for (int grp = 0; grp < fg.ngroups; ++grp) {
+      const bool more = grp + 1 < fg.ngroups;
+      const int base = slot * slot_b, other = (slot ^ 1) * slot_b;
+#pragma unroll
+      for (int tt = 0; tt < KK; ++tt) {
+        if (more) {
+          constexpr int NP = 2 * QU / FL;  // phases; phase f is loaded at f * KK / NP, stored before the next
+#pragma unroll
+          for (int f = 0; f < NP; ++f) {
+            if (tt == (f + 1) * (KK - 1) / NP)
+#pragma unroll
+              for (int s = 0; s < FL; ++s) stage_store(stg[s], slot ^ 1, f * FL + s);
+            if (tt == f * (KK - 1) / NP)
+#pragma unroll
+              for (int s = 0; s < FL; ++s) stage_load(stg[s], grp + 1, f * FL + s);
+          }
+        }
+        const int ti = tt / KT, tj = tt % KT, ni = (tt + 1) / KT, nj = (tt + 1) % KT;
+        const bool last = tt == KK - 1;
+        tile(tt % AD, grp * KK + tt, base + (ti * fg.Wp + tj) * CB,
+             last ? (more ? other : base) : base + (ni * fg.Wp + nj) * CB, last && more,
+             tt == 0 && (KT == 5 || short_parts || !(grp & 1)));
+        if (KT == 5 && tt == KK / 2 && short_parts)
+#pragma unroll
+          for (int j = 0; j < WN; ++j) end_part(j);
+      }
+      if (more) slot ^= 1;
+    }
+#pragma unroll
+    for (int j = 0; j < WN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        if constexpr (PARTS) acc_h[j][r] += total[j][r];
+        out[r / 4][j][r % 4] = acc_h[j][r] + acc_c[j][r];
+      }
   }
-  if (pairs & 1) pair(0);
 
   // ---- epilogue: Type-1 lifting + bias, or the depth-to-space store of a strided backward-data
-  // pass.  Accumulator register r of block i is row 16*i + 4*(lane/16) + r of the wave's rows: four
-  // consecutive rows per lane.
-  const int mw = m0 + wave_m * MW, row4 = (lane >> 4) * 4;
+  // pass
+  const int mw = m0 + wave_m * MW;
   float check = 0.f;  // NaN once a result is not finite
 #pragma unroll
-  for (int i = 0; i < RB; ++i)
+  for (int i = 0; i < QB; ++i)
 #pragma unroll
     for (int j = 0; j < WN; ++j)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        if constexpr (PARTS) acc_h[i][j][r] += total[i][j][r];
-        acc_h[i][j][r] += acc_c[i][j][r];
-        check = fmaf(acc_h[i][j][r], 0.f, check);
-        acc_h[i][j][r] *= kSplitUnscale;
+        check = fmaf(out[i][j][r], 0.f, check);
+        out[i][j][r] *= kSplitUnscale;
       }
   if (p.d2s) {
     float* __restrict__ D = p.C;
     const int ss = p.dS * p.dS;
 #pragma unroll
     for (int j = 0; j < WN; ++j) {
-      const int col = n0 + bn + j * 16;
+      const int col = n0 + bn + j * MB;
       if (col >= ce) continue;
       const int n = col / P, pix = col - n * P;
       const int ga = pix / p.gWout, gb = pix - ga * p.gWout;
       const long long img = ((long long)n * p.dCtot + (long long)g * p.dCg) * p.dH;
 #pragma unroll
-      for (int i = 0; i < RB; ++i) {
+      for (int i = 0; i < QB; ++i) {
         // the lane's four consecutive rows m .. m+3 (m a multiple of 4)
-        const int m = mw + i * 16 + row4;
+        const int m = mw + quad(i) + row4;
         if (m >= p.M) continue;
         const int ci = fdiv_u(m, p.d_divSS_M, p.d_divSS_sh), rem = m - ci * ss;
         const int rh = fdiv_u(rem, p.d_divS_M, p.d_divS_sh), rw = rem - rh * p.dS;
@@ -539,11 +694,11 @@ __global__ __launch_bounds__(NT, 2) void conv_fused_split(GemmTN p, KcGeom fg, i
           // stride a multiple of 4: the four rows are four consecutive pixels of one row of dx
           if ((unsigned)h >= (unsigned)p.dH) continue;
           if (w >= 0 && w + 3 < p.dW && m + 3 < p.M) {
-            *reinterpret_cast<f32x4u*>(dst) = acc_h[i][j];  // 4-byte aligned
+            *reinterpret_cast<f32x4u*>(dst) = out[i][j];  // 4-byte aligned
           } else {
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-              if (m + e < p.M && (unsigned)(w + e) < (unsigned)p.dW) dst[e] = acc_h[i][j][e];
+              if (m + e < p.M && (unsigned)(w + e) < (unsigned)p.dW) dst[e] = out[i][j][e];
           }
         } else {
 #pragma unroll
@@ -554,7 +709,7 @@ __global__ __launch_bounds__(NT, 2) void conv_fused_split(GemmTN p, KcGeom fg, i
               const int rhe = fdiv_u(reme, p.d_divS_M, p.d_divS_sh), rwe = reme - rhe * p.dS;
               const int he = ga * p.dS + rhe - p.dP, we = gb * p.dS + rwe - p.dP;
               if ((unsigned)he < (unsigned)p.dH && (unsigned)we < (unsigned)p.dW)
-                D[((img + (long long)cie * p.dH) + he) * p.dW + we] = acc_h[i][j][e];
+                D[((img + (long long)cie * p.dH) + he) * p.dW + we] = out[i][j][e];
             }
           }
         }
@@ -566,17 +721,17 @@ __global__ __launch_bounds__(NT, 2) void conv_fused_split(GemmTN p, KcGeom fg, i
     const bool full_m = m0 + BM <= p.M;
 #pragma unroll
     for (int j = 0; j < WN; ++j) {
-      const int col = n0 + bn + j * 16;
+      const int col = n0 + bn + j * MB;
       if (col >= ce) continue;
       float* __restrict__ cl = C + col_offset(p.cmap, col) + (long long)(mw + row4) * p.c_ms;
       const float* bl = bias ? bias + mw + row4 : nullptr;
 #pragma unroll
-      for (int i = 0; i < RB; ++i)
+      for (int i = 0; i < QB; ++i)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int row = i * 16 + r;  // relative to mw + row4
+          const int row = quad(i) + r;  // relative to mw + row4
           if (full_m || mw + row + row4 < p.M) {
-            float v = acc_h[i][j][r];
+            float v = out[i][j][r];
             if (bl) v += bl[row];
             cl[(long long)row * p.c_ms] = v;
           }
@@ -590,11 +745,12 @@ __global__ __launch_bounds__(NT, 2) void conv_fused_split(GemmTN p, KcGeom fg, i
   // costs a few times one of split ones whatever is in it (256 images of conv3 with one infinity each: 331 us
   // without, 4.3 ms with it).  It also multiplies zeros that stand for no pixel or no tap: where one may have met
   // a value that is not finite, a NaN is summed once more without them.
+  constexpr int WB = WN * MB / 32;
 #pragma unroll 1
-  for (int blk = 0; blk < WN / 2 * ((RB + 1) / 2); ++blk) {
+  for (int blk = 0; blk < WB * ((RB + 1) / 2); ++blk) {
     // 32 rows (the last ones may be another wave's: not looked at) x 32 positions
-    const int r0 = mw + blk / (WN / 2) * 32, rows_end = min(mw + MW, p.M), lo = lane & 31;
-    const int col = n0 + wave_n * WN * 16 + blk % (WN / 2) * 32 + lo;
+    const int r0 = mw + blk / WB * 32, rows_end = min(mw + MW, p.M), lo = lane & 31;
+    const int col = n0 + wave_n * WN * MB + blk % WB * 32 + lo;
     const int n = min(col, ce - 1) / P, pix = min(col, ce - 1) - n * P, r_ = pix / p.gWout, c_ = pix - r_ * p.gWout;
     auto address = [&](int m) -> float* {  // null: no such result
       if (col >= ce || m >= rows_end) return nullptr;
@@ -735,7 +891,7 @@ inline long long column_tiles(const GemmTN& p, const KcGeom& fg, long long nimg)
   return fg.tpi > 0 ? fg.tpi * nimg : (P * nimg + BN - 1) / BN;
 }
 
-template <int WAVES_M, int RB, int KT, int S>
+template <int WAVES_M, int RB, int KT, int S, int MB>
 int launch_variant(const GemmTN& p, const KcGeom& fg, size_t lds, hipStream_t st) {
   constexpr int BM = 16 * RB * WAVES_M;
   const int tiles_m = (p.M + BM - 1) / BM;
@@ -749,30 +905,35 @@ int launch_variant(const GemmTN& p, const KcGeom& fg, size_t lds, hipStream_t st
   const double y_bytes = p.d2s ? 4.0 * nimg * p.dCtot * p.dH * p.dW : 4.0 * (double)p.M * p.Ncols * p.G;
   ProfScope ps(p.prof_flops > 0 ? p.prof_flops : 2.0 * p.M * p.Ncols * p.Kdim * p.G,
                x_bytes + y_bytes + 4.0 * (double)p.M * p.Kdim * p.G, st,
-               "conv_fused_split<%d, %d, %d, %d>%s", WAVES_M, RB, KT, S, p.d2s ? " strided" : "");
-  constexpr auto kern = conv_fused_split<WAVES_M, RB, KT, S>;
+               "conv_fused_split<%d, %d, %d, %d, %d>%s", WAVES_M, RB, KT, S, MB, p.d2s ? " strided" : "");
+  constexpr auto kern = conv_fused_split<WAVES_M, RB, KT, S, MB>;
   if (const int rc = ensure_dynamic_lds<kern>(2 * kLdsCap)) return rc;
   hipLaunchKernelGGL(kern, grid, dim3(NT), lds, st, p, fg, tiles_m, (int)tn);
   CCT_CHECK_LAUNCH();
   return CCT_OK;
 }
 
-template <int WAVES_M, int RB>
+template <int WAVES_M, int RB, int MB>
 int launch_rows(const GemmTN& p, const KcGeom& fg, size_t lds, hipStream_t st) {
   if (p.s2d == 4) {
-    if (p.gK == 3) return launch_variant<WAVES_M, RB, 3, 4>(p, fg, lds, st);
-    return p.gK == 5 ? CCT_EUNSUPPORTED : launch_variant<WAVES_M, RB, 0, 4>(p, fg, lds, st);
+    if (p.gK == 3) return launch_variant<WAVES_M, RB, 3, 4, MB>(p, fg, lds, st);
+    return p.gK == 5 ? CCT_EUNSUPPORTED : launch_variant<WAVES_M, RB, 0, 4, 16>(p, fg, lds, st);
   }
   if (p.s2d == 2) {
-    if (p.gK == 3) return launch_variant<WAVES_M, RB, 3, 2>(p, fg, lds, st);
-    return p.gK == 5 ? CCT_EUNSUPPORTED : launch_variant<WAVES_M, RB, 0, 2>(p, fg, lds, st);
+    if (p.gK == 3) return launch_variant<WAVES_M, RB, 3, 2, MB>(p, fg, lds, st);
+    return p.gK == 5 ? CCT_EUNSUPPORTED : launch_variant<WAVES_M, RB, 0, 2, 16>(p, fg, lds, st);
   }
-  if (p.gK == 3) return launch_variant<WAVES_M, RB, 3, 1>(p, fg, lds, st);
-  if (p.gK == 5) return launch_variant<WAVES_M, RB, 5, 1>(p, fg, lds, st);
-  return launch_variant<WAVES_M, RB, 0, 1>(p, fg, lds, st);
+  if (p.gK == 3) return launch_variant<WAVES_M, RB, 3, 1, MB>(p, fg, lds, st);
+  if (p.gK == 5) return launch_variant<WAVES_M, RB, 5, 1, MB>(p, fg, lds, st);
+  return launch_variant<WAVES_M, RB, 0, 1, 16>(p, fg, lds, st);
 }
 
+// the kernel size where it is compiled in
+inline int compiled_k(const GemmTN& p) { return p.gK == 3 || (p.gK == 5 && !p.s2d) ? p.gK : 0; }
+
 bool split_geom(const GemmTN& p, KcGeom* fg, size_t* lds) {
+  // one tap: a period of one pair, while the kernel reads offsets two pairs ahead (1 x 1 kernels have no windows to stage)
+  if (p.gK < 2) return false;
   // the pack of one group is addressed with 32-bit byte offsets
   if (p.bf16 || (long long)p.Mpad * p.Kpad * 6 >= (1LL << 31)) return false;
   // Rows and channels are padded to whole tiles and groups: below two fifths of useful work the fp32 fused
@@ -789,7 +950,7 @@ bool split_geom(const GemmTN& p, KcGeom* fg, size_t* lds) {
   if (p.s2d && p.gK == 5) return false;  // kernels of 9 and 10 (stride 2), 17 to 20 (stride 4): no form
   GeomRules rules;
   rules.r_step = 16;  // half a slot is a multiple of 256 bytes
-  rules.qu = kCells(p.gK == 3 || (p.gK == 5 && !p.s2d) ? p.gK : 0);
+  rules.qu = kCells(compiled_k(p));
   // what else runs these layers is at most half as fast, so up to half of a group's channels may be
   // padding, and a quarter of the positions
   rules.chan_num = 2; rules.chan_den = 1;
@@ -813,6 +974,25 @@ inline int split_bm(const GemmTN& p, long long tn) {
   if (BM == 128 && row_tiles(p, 96) * 96 < row_tiles(p, 128) * 128) BM = 96;
   while (BM > 32 && tn * row_tiles(p, BM) * p.G < 256) BM = BM == 96 ? 64 : BM / 2;
   return BM;
+}
+
+// workgroups that registers (165 of the smallest unrolled form) and LDS let share a CU
+inline int workgroups_per_cu(const GemmTN& p, size_t lds, int rows) {
+  return std::max(1, std::min(rows == 32 && compiled_k(p) == 3 && p.s2d < 4 ? 3 : 2, (int)(160 * 1024 / lds)));
+}
+
+// Edge of the MFMA's blocks.  Unrolled taps in blocks of 32 x 32 for 32 and 64 rows (16 x 16 take 1.05 to 1.2 times as
+// long), and for 128 where a workgroup has its CU alone (1.12 times) or the launch is too short to run into the power
+// limit (one group of 3 x 3: 1.05; from 128 tiles in a row up 0.99, conv2 and conv3 at large batches 0.92 to 0.95).
+// 5 x 5 on 64 rows meets it in a long launch of long chains, from 3 rounds of 4 groups up (0.98; conv2's
+// backward-data 0.96).
+inline int split_block(const GemmTN& p, const KcGeom& fg, size_t lds, long long tn, int rows) {
+  const int KT = compiled_k(p), share = workgroups_per_cu(p, lds, rows);
+  if (!KT || rows == 96) return 16;
+  if (rows == 32 || share == 1) return 32;
+  const long long per_cu = (tn * row_tiles(p, rows) * p.G + 255) / 256, rounds = (per_cu + share - 1) / share;
+  if (rows == 64) return KT == 5 && rounds >= 3 && fg.ngroups >= 4 ? 16 : 32;
+  return fg.ngroups * tiles_per_group(p.gK) * rounds < (KT == 5 ? 50 : 128) ? 32 : 16;
 }
 
 }  // namespace
@@ -896,11 +1076,15 @@ int launch_conv_fused_split(const GemmTN& p0, hipStream_t st) {
   size_t lds;
   if (p.Mpad != conv_fused_split_mpad(p.M) || !split_geom(p, &fg, &lds)) return CCT_EUNSUPPORTED;
   if (p.Kpad != conv_fused_split_kpad(p.gCg, p.gK)) return CCT_EINVAL;
-  switch (split_bm(p, column_tiles(p, fg, p.Ncols / (p.gHout * p.gWout)))) {
-    case 32: return launch_rows<1, 2>(p, fg, lds, st);
-    case 64: return launch_rows<2, 2>(p, fg, lds, st);
-    case 96: return launch_rows<2, 3>(p, fg, lds, st);
-    default: return launch_rows<4, 2>(p, fg, lds, st);
+  const long long tn = column_tiles(p, fg, p.Ncols / (p.gHout * p.gWout));
+  const int rows = split_bm(p, tn), block = split_block(p, fg, lds, tn, rows);
+  switch (rows) {
+    case 32: return launch_rows<1, 2, 32>(p, fg, lds, st);
+    case 64:
+      if (block == 16 && p.gK == 5) return launch_variant<2, 2, 5, 1, 16>(p, fg, lds, st);
+      return launch_rows<2, 2, 32>(p, fg, lds, st);
+    case 96: return launch_rows<2, 3, 16>(p, fg, lds, st);
+    default: return block == 32 ? launch_rows<4, 2, 32>(p, fg, lds, st) : launch_rows<4, 2, 16>(p, fg, lds, st);
   }
 }
 

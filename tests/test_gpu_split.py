@@ -246,3 +246,25 @@ def test_row_tiles(B, L):
     # values that are not finite, met by whole tiles and by the rows and positions of another wave
     x[0, 0, 0, 0], x[1, 1, 5, 6], x[-1, 2, 12, 12], w[3, 1, 1, 1], w[-1, 0, 0, 0] = np.inf, -np.inf, np.nan, 3.4e38, np.inf
     check_not_finite(gpu_forward(B, L, x, w, b, B.LOWER_FUSED), oracle.conv_forward(odims(oracle, L), x, w, b))
+
+
+# The form of the kernel by what a launch holds: unrolled taps in blocks of 32 x 32 for lone workgroups and short
+# launches, pairs of taps in blocks of 16 x 16 for long ones.
+BLOCKS = [(layer("lone32_k3", 4, 64, 28, 28, 128, 3, 1, 1), "<1, 2, 3, 1, 32>"),
+          (layer("lone32_k5", 2, 48, 27, 27, 128, 5, 1, 2), "<1, 2, 5, 1, 32>"),
+          (layer("lone32_s2d", 2, 32, 27, 27, 40, 5, 2, 2), "<1, 2, 3, 2, 32>"),
+          (layer("lone32_s4", 1, 3, 67, 67, 36, 11, 4, 0), "<1, 2, 3, 4, 32>"),
+          (layer("lone64_k3", 50, 40, 27, 27, 60, 3, 1, 1), "<2, 2, 3, 1, 32>"),
+          (layer("lone64_k5", 50, 32, 27, 27, 60, 5, 1, 2), "<2, 2, 5, 1, 32>"),
+          (layer("brief128", 200, 16, 13, 13, 128, 3, 1, 1), "<4, 2, 3, 1, 32>"),
+          (layer("wide128", 8, 16, 64, 80, 128, 3, 1, 1), "<4, 2, 3, 1, 32>"),
+          (layer("long64_k5", 180, 64, 27, 27, 40, 5, 1, 2), "<2, 2, 5, 1, 16>"),
+          (layer("long128_k5", 200, 48, 13, 13, 128, 5, 1, 2), "<4, 2, 5, 1, 16>")]
+
+
+@pytest.mark.parametrize("L,form", BLOCKS, ids=[L.name for L, _ in BLOCKS])
+def test_form_follows_the_launch(B, L, form):
+    x, w, b = synth.make_x(L, 7), synth.make_w(L, 7), synth.make_bias(L, 7)
+    got, names = ran(B, lambda: gpu_forward(B, L, x, w, b, B.LOWER_FUSED))
+    assert any(n == KERNEL + form for n in names), names
+    assert rel_err(got, oracle.conv_forward(odims(oracle, L), x, w, b)) <= TOL_F32
