@@ -246,13 +246,12 @@ bool find_split_plan(const cct_conv_desc_t& d, int pass, const Geom& g, SplitPla
     return fits(2, (long long)g.Cg * s * s, g.Og, sb.U);
   }
   if (fits(0, g.Og, g.Cg, d.K)) {
-    // Many channels into one 32-row tile of kernels, whose four waves read the same rows of the pack: near where
-    // Type 3, whose rows are kernels x taps, is as fast (128 images of 28 x 28, 1024 -> 32 channels: 422 us
-    // against 437; 512 -> 16: 152 against 214; 256 -> 32: 145 against 114).  The estimates draw the line, and
-    // beyond it an explicit FUSED is the fp32 kernel: the fusion on one side of the channel ratio, Type 3 on
-    // the other.
-    return !(s == 1 && d.K <= 3 && g.Og <= 32 && g.Cg >= 128) ||
-           split_cost(d, pass, g, *sp) < kernel_cost(d, pass, CCT_LOWER_TYPE3, make_geom(d, CCT_LOWER_TYPE3));
+    // Many channels into one 32-row tile of kernels, whose four waves read the same rows of the pack: where the
+    // launch fills the chip Type 3, whose rows are kernels x taps, is as fast or faster from 32 channels per kernel up (128
+    // images of 28 x 28, 1024 -> 32 channels: 422 us against 437; 512 -> 16: 152 against 214; 256 -> 32: 145
+    // against 114), and beyond that line an explicit FUSED is the fp32 kernel: the fusion on one side of the channel
+    // ratio, Type 3 on the other.
+    return !(s == 1 && d.K <= 3 && g.Og <= 32 && g.Cg >= 32 * g.Og && d.N * g.Pc * d.groups >= 256 * 128);
   }
   return (s == 2 || s == 4) && U >= 2 && fits(3, g.Og, g.Cg * s * s, U);
 }
@@ -265,17 +264,13 @@ bool split_plan(const cct_conv_desc_t& d, int pass, const Geom& g, SplitPlan* sp
 
 // Does a fused pass run on conv_fused_split?  An explicit FUSED does wherever it can; AUTO unless the estimate
 // of the fp32 fused kernels is clearly lower: with few channels or kernels much of a tile is padding and they do
-// less of it (22 images of 23 x 23, 8 channels, 32 kernels: 16 us against 23).  Of 11400 passes the split
-// kernel was the faster one in 92 %, and the other estimate is between half and twice the time.  Space to depth
-// with half as many taps again as the layer has (3 x 3 at stride 2, 5 x 5 and 6 x 6 at stride 4: four short K
-// tiles per group of channels) is the faster one in 57 % only: there the estimates decide evenly (85 images of
-// 38 x 38, 79 -> 53 channels, 3 x 3 at stride 2: 75 us against 55).
+// less of it (22 images of 23 x 23, 8 channels, 32 kernels: 16 us against 23).  Of 2130 passes that both run the split
+// kernel was the faster one in 96 %, of those where its estimate is 1 to 1.5 times the other in 70 %: the other estimate is
+// low there, 0.6 times the time.
 bool use_split(const cct_conv_desc_t& d, int pass, const Geom& g, SplitPlan* sp) {
   if (!split_plan(d, pass, g, sp)) return false;
   if (d.lowering != CCT_LOWER_AUTO || (pass == CCT_PASS_BACKWARD_DATA && d.stride > 1)) return true;
-  const long long U = (d.K + d.stride - 1) / d.stride;
-  const bool few_taps = sp->kind == 3 && 2 * U * U * d.stride * d.stride > 3LL * d.K * d.K;
-  return split_cost(d, pass, g, *sp) <= (few_taps ? 0.9 : 1.5) * kernel_cost(d, pass, CCT_LOWER_FUSED, g);
+  return split_cost(d, pass, g, *sp) <= 1.5 * kernel_cost(d, pass, CCT_LOWER_FUSED, g);
 }
 
 inline int esize(const cct_conv_desc_t& d) { return d.precision == CCT_PREC_BF16_IN_F32_ACC ? 2 : 4; }
@@ -663,9 +658,13 @@ double find_kernel_cost(const cct_conv_desc_t& d, int pass, int type, const Geom
     const bool fwd = pass == CCT_PASS_FORWARD;
     const double side = (fwd ? rt_elems : dt_elems) * 4.0;  // written by the product, read by lift / inverse lowering
     const double t = gemm_split_seconds(L.Mpad, fwd ? g.Kd : g.Mr, (long long)cols, d.groups);
-    // small tensors: the gather's chain of K*K taps (K = 7: 30 us where the bytes take 8)
-    return (side + (fwd ? y_bytes : x_bytes)) / kStreamBytesPerSec + d.K * d.K * 0.35e-6 +
-           std::max(t, ((fwd ? x_bytes : y_bytes) + side) / kGemmBytesPerSec) + 3.0 * kLaunchSec;
+    const double product = std::max(t, ((fwd ? x_bytes : y_bytes) + side) / kGemmBytesPerSec);
+    // The product, its result through memory, the gather's chain of taps.  Fitted to 21000 passes: off by 10 % in the
+    // mean, 23 % in nine of ten (4 TB/s, 0.35 us per tap and three launches of 4 us: a third too much in the mean
+    // and twice what passes under 15 us take).
+    const double U = (d.K + d.stride - 1) / d.stride;  // taps per axis that a pixel of dx receives
+    return fwd ? product + side / 5.3e12 + y_bytes / 1.06e12 + d.K * d.K * 0.28e-6 + 2.3e-6
+               : product + side / 3.6e12 + x_bytes / 2.5e12 + U * U * 0.35e-6 + 2.5e-6;
   } else if (pass == CCT_PASS_FORWARD) {
     index_bytes += x_bytes + dt_elems * es;      // lowering: read x, write D^T
     gemm_bytes += dt_elems * es;                 // GEMM reads D^T

@@ -967,15 +967,6 @@ bool split_geom(const GemmTN& p, KcGeom* fg, size_t* lds) {
 
 inline int row_tiles(const GemmTN& p, int BM) { return (p.M + BM - 1) / BM; }
 
-// Row tile: of 128 or 64 rows, 96 instead of 128 where the rows then take less padding; smaller while the launch
-// would not put a workgroup on every CU.
-inline int split_bm(const GemmTN& p, long long tn) {
-  int BM = p.Mpad % 128 == 0 ? 128 : p.Mpad % 64 == 0 ? 64 : 32;
-  if (BM == 128 && row_tiles(p, 96) * 96 < row_tiles(p, 128) * 128) BM = 96;
-  while (BM > 32 && tn * row_tiles(p, BM) * p.G < 256) BM = BM == 96 ? 64 : BM / 2;
-  return BM;
-}
-
 // workgroups that registers (165 of the smallest unrolled form) and LDS let share a CU
 inline int workgroups_per_cu(const GemmTN& p, size_t lds, int rows) {
   return std::max(1, std::min(rows == 32 && compiled_k(p) == 3 && p.s2d < 4 ? 3 : 2, (int)(160 * 1024 / lds)));
@@ -995,6 +986,54 @@ inline int split_block(const GemmTN& p, const KcGeom& fg, size_t lds, long long 
   return fg.ngroups * tiles_per_group(p.gK) * rounds < (KT == 5 ? 50 : 128) ? 32 : 16;
 }
 
+// A launch: rows of a workgroup, edge of the MFMA's blocks, what it is estimated to take.
+struct Tile {
+  int rows, block;
+  double us;
+};
+
+// Rounds of workgroups, each as long as the chain of one: us per K tile of a workgroup that has its CU alone, what
+// every further one on the CU adds, and per round to fill and drain; per channel group the staging that its tiles do
+// not hide, and what each cell of a thread beyond the first adds to that; the two launches; 9 us per million values of
+// the pack.  Fitted to 58900 launches of 24800 passes (1 to 512 images of up to 240 x 240, each pass with every tile that it can
+// take), without what memory bounds: off by 5 to 7 % in the mean and by up to 11 to 16 % in nine of ten, by form.
+Tile estimate(const GemmTN& p, const KcGeom& fg, size_t lds, long long tn, int rows) {
+  struct Rate {
+    double tile, next, fill;
+  };
+  struct Form {
+    Rate of[5];  // 32, 64, 96, 128 rows, 128 rows in 32 x 32 blocks
+    double group, cell, launches;
+  };
+  static constexpr Form forms[5] = {
+      // any K, 3, 5; regrouped: any K, 3
+      {{{0.172, 0.076, 4.3}, {0.266, 0.144, 6.6}, {0.370, 0.210, 9.0}, {0.461, 0.294, 10.7}, {}}, 0.90, 0.49, 3.5},
+      {{{0.206, 0.118, 3.6}, {0.278, 0.215, 6.2}, {0.460, 0.250, 8.3}, {0.551, 0.333, 9.8}, {0.451, 0.468, 8.3}}, 0.0, 0.36, 3.9},
+      {{{0.149, 0.117, 4.5}, {0.229, 0.232, 7.1}, {0.414, 0.245, 9.6}, {0.512, 0.312, 11.4}, {0.382, 0.469, 12.2}}, 0.0, 0.0, 3.2},
+      {{{0.177, 0.063, 3.5}, {0.274, 0.116, 7.1}, {0.369, 0.192, 11.1}, {0.467, 0.280, 14.3}, {}}, 1.28, 0.80, 5.9},
+      {{{0.242, 0.091, 3.3}, {0.319, 0.173, 6.2}, {0.505, 0.213, 8.7}, {0.578, 0.304, 11.6}, {0.524, 0.385, 10.8}}, 0.0, 0.73, 6.1}};
+  const int S = p.s2d ? p.s2d : 1, KT = compiled_k(p);
+  const Form& f = forms[S > 1 ? (KT ? 4 : 3) : KT == 3 ? 1 : KT == 5 ? 2 : 0];
+  const int share = workgroups_per_cu(p, lds, rows), block = split_block(p, fg, lds, tn, rows);
+  const Rate& r = f.of[rows == 128 && block == 32 ? 4 : rows / 32 - 1];
+  const long long per_cu = (tn * row_tiles(p, rows) * p.G + 255) / 256;
+  const double tiles = (double)fg.ngroups * tiles_per_group(p.gK);
+  const double staging = fg.ngroups * (f.group + f.cell * ((fg.R + NT - 1) / NT - 1) + (p.gs > 1 ? 0.9 : 0.0));
+  auto round = [&](long long n) { return n ? tiles * (r.tile + (double)(n - 1) * r.next) + staging + r.fill : 0.0; };
+  return {rows, block, (double)(per_cu / share) * round(share) + round(per_cu % share) + f.launches +
+                           9.0e-6 * p.G * p.Mpad * tiles * CG};
+}
+
+// Row tile: of 128 or 64 rows, 96 instead of 128 where the rows then take less padding; smaller while the launch
+// would not put a workgroup on every CU.
+Tile split_tile(const GemmTN& p, const KcGeom& fg, size_t lds, long long tn) {
+  auto fills = [&](int rows) { return tn * row_tiles(p, rows) * p.G >= 256; };
+  int rows = p.Mpad % 128 == 0 ? 128 : p.Mpad % 64 == 0 ? 64 : 32;
+  if (rows == 128 && row_tiles(p, 96) * 96 < row_tiles(p, 128) * 128) rows = 96;
+  while (rows > 32 && !fills(rows)) rows = rows == 96 ? 64 : rows / 2;
+  return estimate(p, fg, lds, tn, rows);
+}
+
 }  // namespace
 
 int conv_fused_split_mpad(int M) { return M <= 32 ? 32 : (M + 63) / 64 * 64; }
@@ -1009,41 +1048,11 @@ bool conv_fused_split_fits(const GemmTN& p) {
   return split_geom(p, &fg, &lds);
 }
 
-// Rounds of workgroups, each as long as the chain of one: per K tile 0.48 / 0.41 / 0.30 / 0.20 us (128 / 96 / 64 / 32
-// rows) for every workgroup that shares the CU, at least 0.50 / 0.43 / 0.33 / 0.26, less with the unrolled 25 tiles of 5 x 5,
-// more where cells are regrouped or windows strided; per channel group at least 2.3 us, the way of the next
-// group's cells from memory (3 us where they are many); 10 / 7 / 7 us to fill and drain; 4 us for the pack.  Fitted
-// to 13700 passes of 1 to 256 images of up to 120 x 120: off by 13 % in the mean, by up to 31 % in nine of ten (a rate
-// of full tiles and the chain of a lone workgroup: 23 % and 55 %).
 double conv_fused_split_seconds(const GemmTN& p, int nimg) {
   KcGeom fg;
   size_t lds;
   if (!split_geom(p, &fg, &lds)) return 1.0;
-  const long long tn = column_tiles(p, fg, nimg);
-  const int BM = split_bm(p, tn), S = p.s2d ? p.s2d : 1, KT = p.gK == 3 || (p.gK == 5 && S == 1) ? p.gK : 0;
-  // workgroups that registers and LDS let share a CU
-  const int share = std::max(1, std::min(2, (int)(160 * 1024 / lds)));
-  double alone = BM == 128 ? 0.50e-6 : BM == 96 ? 0.43e-6 : BM == 64 ? 0.33e-6 : 0.26e-6;
-  double shared = BM == 128 ? 0.48e-6 : BM == 96 ? 0.41e-6 : BM == 64 ? 0.30e-6 : 0.20e-6;
-  double group = KT == 0 || S > 1 ? 3.0e-6 : 2.3e-6;
-  if (KT == 5) {
-    alone *= 0.75;
-    shared *= BM >= 96 ? 0.97 : 0.80;
-  }
-  if (S > 1) {
-    alone *= 1.4;
-    shared *= KT ? 1.05 : 1.2;
-  }
-  if (p.gs > 1) {
-    alone *= 1.3;
-    group *= 1.2;
-  }
-  const double tiles = (double)fg.ngroups * tiles_per_group(p.gK);
-  auto round = [&](long long n) {
-    return n ? std::max(tiles * std::max(alone, (double)n * shared), fg.ngroups * group) + (BM >= 96 ? 10.0e-6 : 7.0e-6) : 0.0;
-  };
-  const long long per_cu = (tn * row_tiles(p, BM) * p.G + 255) / 256;
-  return (double)(per_cu / share) * round(share) + round(per_cu % share) + 4.0e-6;
+  return 1e-6 * split_tile(p, fg, lds, column_tiles(p, fg, nimg)).us;
 }
 
 int launch_pack_split(const float* w, void* pack, int kind, int G, int Og, int Cg, int K, int s, int Mpad,
@@ -1076,15 +1085,14 @@ int launch_conv_fused_split(const GemmTN& p0, hipStream_t st) {
   size_t lds;
   if (p.Mpad != conv_fused_split_mpad(p.M) || !split_geom(p, &fg, &lds)) return CCT_EUNSUPPORTED;
   if (p.Kpad != conv_fused_split_kpad(p.gCg, p.gK)) return CCT_EINVAL;
-  const long long tn = column_tiles(p, fg, p.Ncols / (p.gHout * p.gWout));
-  const int rows = split_bm(p, tn), block = split_block(p, fg, lds, tn, rows);
-  switch (rows) {
+  const Tile t = split_tile(p, fg, lds, column_tiles(p, fg, p.Ncols / (p.gHout * p.gWout)));
+  switch (t.rows) {
     case 32: return launch_rows<1, 2, 32>(p, fg, lds, st);
     case 64:
-      if (block == 16 && p.gK == 5) return launch_variant<2, 2, 5, 1, 16>(p, fg, lds, st);
+      if (t.block == 16 && p.gK == 5) return launch_variant<2, 2, 5, 1, 16>(p, fg, lds, st);
       return launch_rows<2, 2, 32>(p, fg, lds, st);
     case 96: return launch_rows<2, 3, 16>(p, fg, lds, st);
-    default: return block == 32 ? launch_rows<4, 2, 32>(p, fg, lds, st) : launch_rows<4, 2, 16>(p, fg, lds, st);
+    default: return t.block == 32 ? launch_rows<4, 2, 32>(p, fg, lds, st) : launch_rows<4, 2, 16>(p, fg, lds, st);
   }
 }
 

@@ -306,3 +306,24 @@ def test_strided_fused_backward_data_needs_room_for_the_only_kernel_that_runs_it
     assert need == B.cct_conv_workspace_bytes(d, B.PASS_BACKWARD_DATA)
     for nbytes in (need - 256, need * 4 // 5 // 256 * 256):
         assert backward_data_code(B, d, nbytes) == B.EWORKSPACE
+
+
+# Layers on which estimates that had not followed the kernels led to another layout; us measured (Type 1, 2, 3, fused)
+MEASURED = [
+    # N    C   H   W    O   K  s  p  g   pass  fastest
+    ((85, 32, 7, 7, 32, 6, 1, 3, 1), 0, 4),        # 85, 39, 43, 24
+    ((106, 16, 8, 8, 176, 7, 1, 3, 1), 0, 4),      # 98, 57, 96, 34
+    ((1, 42, 9, 9, 101, 5, 1, 2, 1), 0, 3),        # 102, 33, 12, 20
+    ((1, 80, 33, 33, 64, 3, 1, 0, 1), 0, 3),       # 48, 29, 13, 20
+    ((1, 64, 7, 7, 128, 5, 2, 2, 1), 0, 3),        # 139, 40, 13, 65
+    ((7, 4, 80, 80, 384, 11, 4, 0, 1), 1, 1),      # 26, 242, -, 64
+    ((2, 5, 26, 26, 227, 11, 4, 5, 1), 1, 1),      # 17, 133, 1302, 39
+    ((1, 277, 8, 8, 203, 7, 1, 0, 1), 1, 1),       # 41, 138, 786, 156
+    ((15, 273, 18, 18, 51, 7, 1, 3, 1), 1, 4),     # 161, 116, 227, 72
+    ((38, 192, 7, 7, 16, 6, 1, 0, 1), 1, 4),       # 29, 23, 69, 16
+]
+
+
+@pytest.mark.parametrize("shape,pass_,fastest", MEASURED, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_selector_picks_the_measured_layout(B, shape, pass_, fastest):
+    assert B.cct_pick_lowering(B.make_desc(*shape), pass_) == fastest
