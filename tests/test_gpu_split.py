@@ -268,3 +268,16 @@ def test_form_follows_the_launch(B, L, form):
     got, names = ran(B, lambda: gpu_forward(B, L, x, w, b, B.LOWER_FUSED))
     assert any(n == KERNEL + form for n in names), names
     assert rel_err(got, oracle.conv_forward(odims(oracle, L), x, w, b)) <= TOL_F32
+
+
+@pytest.mark.parametrize("L,form", [(layer("rows450", 200, 16, 13, 13, 450, 3, 1, 1), "<2, 3, 3, 1, 16>"),
+                                    (layer("rows449", 240, 32, 13, 13, 449, 3, 1, 1), "<4, 2, 3, 1, 32>"),
+                                    (layer("rows464_few", 24, 16, 17, 17, 464, 3, 1, 1), "<2, 2, 3, 1, 32>"),
+                                    (layer("rows470_k2", 200, 16, 13, 13, 470, 2, 1, 0), "<4, 2, 0, 1, 16>")],
+                         ids=lambda v: v.name if hasattr(v, "name") else v)
+def test_rows_that_96_and_128_fill(B, L, form):
+    """Five tiles of 96 rows or four of 128: the one with the lower estimate, smaller tiles where four leave CUs empty."""
+    x, w = synth.make_x(L, 8), synth.make_w(L, 8)
+    got, names = ran(B, lambda: gpu_forward(B, L, x, w, None, B.LOWER_FUSED))
+    assert any(n == KERNEL + form for n in names), names
+    assert rel_err(got, oracle.conv_forward(odims(oracle, L), x, w, None)) <= TOL_F32
