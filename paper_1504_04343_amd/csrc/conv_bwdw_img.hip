@@ -129,7 +129,7 @@ struct ImgGemm {
 
 template <int BM, int TERMS, int SLOTS>
 __global__ __launch_bounds__(granule_waves(BM, TERMS) * 64, 2) void conv_bwdw_img(ImgGemm p) {
-  using GP = GranuleProduct<BM, TERMS, SLOTS>;
+  using GP = GranuleProduct<BM, TERMS, SLOTS, 16>;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_i[];  // [2][A: SLOTS*BM | B: SLOTS*BN]
   GP gp;
 
@@ -369,7 +369,7 @@ inline int row_tile(int M, int terms) {
 
 template <int BM, int TERMS, int SLOTS>
 int launch_product(const ImgGemm& p, dim3 grid, hipStream_t st) {
-  constexpr int lds = GranuleProduct<BM, TERMS, SLOTS>::LDS;
+  constexpr int lds = GranuleProduct<BM, TERMS, SLOTS, 16>::LDS;
   constexpr auto kern = conv_bwdw_img<BM, TERMS, SLOTS>;
   if (const int rc = ensure_dynamic_lds<kern>(lds)) return rc;
   hipLaunchKernelGGL(kern, grid, dim3(granule_waves(BM, TERMS) * 64), lds, st, p);

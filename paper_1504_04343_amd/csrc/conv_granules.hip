@@ -93,7 +93,7 @@ struct GranGemm {
 
 template <int BM>
 __global__ __launch_bounds__(BM * 4, 2) void conv_granules(GranGemm p) {
-  using GP = GranuleProduct<BM, 1, SLOTS>;
+  using GP = GranuleProduct<BM, 1, SLOTS, 32>;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_g[];
   GP gp;
   const int lane = threadIdx.x & 63;
@@ -142,7 +142,7 @@ __global__ __launch_bounds__(BM * 4, 2) void conv_granules(GranGemm p) {
 template <int BM>
 int launch_product(const GranGemm& p, dim3 grid, hipStream_t st) {
   constexpr auto kern = conv_granules<BM>;
-  constexpr int lds = GranuleProduct<BM, 1, SLOTS>::LDS;
+  constexpr int lds = GranuleProduct<BM, 1, SLOTS, 32>::LDS;
   if (const int rc = ensure_dynamic_lds<kern>(lds)) return rc;
   hipLaunchKernelGGL(kern, grid, dim3(BM * 4), lds, st, p);
   CCT_CHECK_LAUNCH();

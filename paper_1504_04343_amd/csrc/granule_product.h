@@ -7,15 +7,20 @@
 // instruction, no conversion in the loop.  Two stages alternate, one meeting of the workgroup per stage;
 // operand reads are 16 consecutive granules of four columns, which do not conflict.
 //
-// v_mfma_f32_16x16x32_bf16 and not 32x32x16: at the card's power limit, which large products run into, it is
-// the faster one (operands in registers, 2 waves per SIMD, random normals: 2200 against 1870 TFLOP/s; zeros:
-// 2450 both), because an accumulator is read and written half as often per flop; it also rounds half as
-// often.  Measured with three terms, 128 rows: conv2's backward-weights product (114.7 GFLOP) 604 -> 537 us,
-// conv3's at batch 1024 (306 GFLOP) 1319 -> 1255.  A wave of 64 x 64 reads 24 KiB of LDS for 96 MFMAs (1536
-// matrix-core cycles) per 32 reduction indices, three quarters of what LDS can deliver to four SIMDs, and a
-// 128 x 256 workgroup fetches 72 KiB of L2 for 3072 cycles of its CU.  With one term LDS and the matrix cores
-// are equally busy.
+// Blocks of 16 x 16 (v_mfma_f32_16x16x32_bf16) and not of 32 x 32 (32x32x16): at the card's power limit, which large
+// products run into, they are the faster ones (operands in registers, 2 waves per SIMD, random normals: 2200 against
+// 1870 TFLOP/s; zeros: 2450 both), because an accumulator is read and written half as often per flop; the results round
+// alike (2-norm against 64 bits the same to four digits).  Measured with three terms, 128 rows: conv2's
+// backward-weights product (114.7 GFLOP) 604 -> 537 us, conv3's at batch 1024 (306 GFLOP) 1319 -> 1255.
+// 32 x 32 where the results go straight to the output tensor (conv_granules), in rows of 128 bytes instead of 64: over 3400
+// bf16 layers forward 1 to 3 % faster, backward-data 2 to 5 % on 128 rows; partial products (conv_bwdw_img) 2 % slower.
+//
+// A wave of 64 x 64 reads 24 KiB of LDS for 96 MFMAs (1536 matrix-core cycles) per 32 reduction indices, three quarters
+// of what LDS can deliver to four SIMDs, and a 128 x 256 workgroup fetches 72 KiB of L2 for 3072 cycles of its CU.
+// With one term LDS and the matrix cores are equally busy.
 #pragma once
+#include <type_traits>
+
 #include "cct_internal.h"
 #include "gemm_common.h"
 #include "split_bf16.h"
@@ -31,8 +36,18 @@ typedef __attribute__((address_space(3))) void* lds_ptr;
 // waves of a workgroup
 constexpr int granule_waves(int BM, int TERMS) { return TERMS == 3 ? 8 : BM / 16; }
 
-template <int BM, int TERMS, int SLOTS>
+__device__ __forceinline__ f32x4 granule_mfma(bf16x8 a, bf16x8 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ floatx16 granule_mfma(bf16x8 a, bf16x8 b, floatx16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+
+// MB: rows and columns of a block of results, 16 or 32
+template <int BM, int TERMS, int SLOTS, int MB>
 struct GranuleProduct {
+  static constexpr int JB = 64 / MB;  // blocks of a wave's 64 columns; columns that an MFMA takes
+  using Acc = std::conditional_t<MB == 32, floatx16, f32x4>;
   static constexpr int NW = granule_waves(BM, TERMS);
   static constexpr int WAVES_N = BN / 64;
   static constexpr int NCOL = SLOTS / TERMS;  // columns per stage
@@ -48,9 +63,9 @@ struct GranuleProduct {
 
   // byte offsets of the rows a lane loads, from a column's granules: the same in every stage
   unsigned a_voff[A_PARTS], b_voff[B_PARTS];
-  static constexpr int RB = BM / (16 * NW / WAVES_N);  // blocks of 16 rows per wave; 4 blocks of 16 columns
+  static constexpr int RB = BM / (MB * NW / WAVES_N);  // blocks of rows per wave
   // three terms: h*h alone in one accumulator, the corrections in the other
-  f32x4 acc[RB][4], acc_c[TERMS == 3 ? RB : 1][TERMS == 3 ? 4 : 1];
+  Acc acc[RB][JB], acc_c[TERMS == 3 ? RB : 1][TERMS == 3 ? JB : 1];
 
   static __device__ __forceinline__ int wave() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6); }
   // which 64 rows of B b_voff[u] stands for
@@ -92,17 +107,20 @@ struct GranuleProduct {
 #pragma unroll
     for (int i = 0; i < RB; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+      for (int j = 0; j < JB; ++j)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
+        for (int r = 0; r < MB * MB / 64; ++r) {
           acc[i][j][r] = 0.f;
           if constexpr (TERMS == 3) acc_c[i][j][r] = 0.f;
         }
 
+    // operands read behind the MFMAs before them; one term has a single MFMA per block, which is too little to read
+    // behind (1 to 4 % slower)
+    constexpr bool AHEAD = TERMS == 3;
     const int stages = (c_end - c_begin + NCOL - 1) / NCOL;  // <= 0 for an empty range
     if (stages > 0) load_stage(0, c_begin);
-    const int lo = lane & 15, kg = lane >> 4;  // row of a block, column of the four
-    const int a_lds = (kg * TERMS * BMP + w / WAVES_N * (16 * RB) + lo) * kGran;
+    const int lo = lane % MB, kg = lane / MB;  // row of a block, which of the JB columns
+    const int a_lds = (kg * TERMS * BMP + w / WAVES_N * (MB * RB) + lo) * kGran;
     const int b_lds = SLOTS * BMP * kGran + (kg * TERMS * BN + w % WAVES_N * 64 + lo) * kGran;
     for (int t = 0; t < stages; ++t) {
       // this stage's loads have landed and nobody reads the other buffer any more
@@ -111,29 +129,36 @@ struct GranuleProduct {
       if (t + 1 < stages) load_stage((t + 1) & 1, c_begin + (t + 1) * NCOL);
       const unsigned char* st = smem + (t & 1) * STAGE;
 #pragma unroll
-      for (int kb = 0; kb < NCOL / 4; ++kb) {
-        bf16x8 a[RB][TERMS], b[2][TERMS];
+      for (int kb = 0; kb < NCOL / JB; ++kb) {
+        bf16x8 a[RB][TERMS], b[AHEAD ? 2 : JB][TERMS];
         auto read_a = [&](int i) {
 #pragma unroll
           for (int k = 0; k < TERMS; ++k)
-            a[i][k] = *reinterpret_cast<const bf16x8*>(st + a_lds + ((4 * kb * TERMS + k) * BMP + i * 16) * kGran);
+            a[i][k] = *reinterpret_cast<const bf16x8*>(st + a_lds + ((JB * kb * TERMS + k) * BMP + i * MB) * kGran);
         };
         auto read_b = [&](int set, int j) {
 #pragma unroll
           for (int k = 0; k < TERMS; ++k)
-            b[set][k] = *reinterpret_cast<const bf16x8*>(st + b_lds + ((4 * kb * TERMS + k) * BN + j * 16) * kGran);
+            b[set][k] = *reinterpret_cast<const bf16x8*>(st + b_lds + ((JB * kb * TERMS + k) * BN + j * MB) * kGran);
         };
-        read_a(0);
-        read_b(0, 0);
+        if constexpr (AHEAD) {
+          read_a(0);
+          read_b(0, 0);
+        } else {
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+          for (int i = 0; i < RB; ++i) read_a(i);
+#pragma unroll
+          for (int j = 0; j < JB; ++j) read_b(j, j);
+        }
+#pragma unroll
+        for (int j = 0; j < JB; ++j)
 #pragma unroll
           for (int i = 0; i < RB; ++i) {
             // the next operands behind these MFMAs: in the first column of blocks the rows, then the next column
-            if (j == 0 && i + 1 < RB) read_a(i + 1);
-            if (i == RB - 1 && j + 1 < 4) read_b((j + 1) & 1, j + 1);
-            __builtin_amdgcn_sched_barrier(0);
-#define CCT_M(X, Y, ACC) ACC[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i][X], b[j & 1][Y], ACC[i][j], 0, 0, 0)
+            if (AHEAD && j == 0 && i + 1 < RB) read_a(i + 1);
+            if (AHEAD && i == RB - 1 && j + 1 < JB) read_b((j + 1) & 1, j + 1);
+            if (AHEAD) __builtin_amdgcn_sched_barrier(0);
+#define CCT_M(X, Y, ACC) ACC[i][j] = granule_mfma(a[i][X], b[AHEAD ? j & 1 : j][Y], ACC[i][j])
             if constexpr (TERMS == 3) {
               CCT_M(2, 0, acc_c);
               CCT_M(0, 2, acc_c);
@@ -143,7 +168,7 @@ struct GranuleProduct {
             }
             CCT_M(0, 0, acc);
 #undef CCT_M
-            __builtin_amdgcn_sched_barrier(0);
+            if (AHEAD) __builtin_amdgcn_sched_barrier(0);
           }
       }
     }
@@ -154,14 +179,15 @@ struct GranuleProduct {
   __device__ __forceinline__ void for_each(F f) const {
     const int lane = threadIdx.x & 63, w = wave();
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < JB; ++j)
 #pragma unroll
       for (int i = 0; i < RB; ++i)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
+        for (int r = 0; r < MB * MB / 64; ++r) {
           float v = acc[i][j][r];
           if constexpr (TERMS == 3) v += acc_c[i][j][r];
-          f(w / WAVES_N * (16 * RB) + i * 16 + (lane >> 4) * 4 + r, w % WAVES_N * 64 + j * 16 + (lane & 15), v);
+          // four consecutive rows per lane and quad of registers
+          f(w / WAVES_N * (MB * RB) + i * MB + r / 4 * 8 + lane / MB * 4 + r % 4, w % WAVES_N * 64 + j * MB + lane % MB, v);
         }
   }
 };
