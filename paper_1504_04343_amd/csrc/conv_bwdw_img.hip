@@ -395,7 +395,11 @@ bool bwdw_img_plan(const cct_conv_desc_t& d, long long nimg, BwdwImgPlan* P) {
   const long long tx = (Hp * Wp + kPrepPx - 1) / kPrepPx, ty = (pix + kPrepPx - 1) / kPrepPx;
   const long long ctx = (d.C + kPrepCh - 1) / kPrepCh, cty = (d.O + kPrepCh - 1) / kPrepCh;
   if (groups_of_images * (tx * ctx + ty * cty) >= (1LL << 30)) return false;
-  P->BM = row_tile(Og, (int)terms);
+  auto at_most = [&](long long ncols, long long ncol) { return (ncols + 2 * ncol - 1) / (2 * ncol); };
+  const long long all = (d.N + kImg - 1) / kImg * pix, tiles_64 = ((Og + 63) / 64) * ((N + BN - 1) / BN) * d.groups;
+  // Where even tiles of 64 rows and two stages are few, the chain of one counts (up to 512 of them larger tiles take
+  // 1.1 times the time, 1.05 up to 1024, 0.99 up to 4096, 0.89 beyond)
+  P->BM = terms == 3 && std::min(tiles_64, 768LL) * std::min(at_most(all, 4), 768LL) < 768 ? 64 : row_tile(Og, (int)terms);
   P->terms = (int)terms;
   const long long ncol = terms == 1 ? 8 : 4;  // columns per stage
   const long long tiles = ((Og + P->BM - 1) / P->BM) * ((N + BN - 1) / BN) * d.groups;
@@ -404,19 +408,19 @@ bool bwdw_img_plan(const cct_conv_desc_t& d, long long nimg, BwdwImgPlan* P) {
   // Splits, from the whole batch: whole rounds of workgroups (a last round that is nearly empty costs as
   // much as a full one), the number of rounds that is estimated fastest, partial products within 256 MiB,
   // at least two stages each.  A smaller chunk takes at most as many, so that its plan is no larger.
-  const double sec_col = 2.0 * (terms == 3 ? tile_weight(P->BM) * 1.0 : P->BM * 1.0) * BN * kImg / ((terms == 3 ? 245.0e12 : 600.0e12) / slots);
+  // (Rows as they are: 64 of three terms take 0.94 times what they took as two workgroups of four waves per CU; priced
+  // at their weight, 76, layers went to other kernels that this one runs in 0.7 times the time, 2 % of 9156.)
+  const double sec_col = 2.0 * P->BM * BN * kImg / ((terms == 3 ? 245.0e12 : 600.0e12) / slots);
   auto cut = [&](long long ncols, long long want, long long* S, long long* len) {
     *len = ((ncols + want - 1) / want + ncol - 1) / ncol * ncol;
     *S = (ncols + *len - 1) / *len;
   };
-  auto at_most = [&](long long ncols) { return (ncols + 2 * ncol - 1) / (2 * ncol); };
-  const long long all = (d.N + kImg - 1) / kImg * pix;
   long long want = 0, S, len;
   double best = 0.0;
   for (int rounds = 1; rounds <= 4; ++rounds) {
     long long w = std::max(1LL, rounds * slots / tiles);
     w = std::min(w, std::max(1LL, (256LL << 20) / out_bytes));
-    w = std::min(w, at_most(all));
+    w = std::min(w, at_most(all, ncol));
     cut(all, w, &S, &len);
     const double sec = (double)((tiles * S + slots - 1) / slots) * ((double)len * sec_col + 9.0e-6) +
                        (double)out_bytes * S * 2.0 / 8.0e12 + (double)S * 1.5e-8;
@@ -425,7 +429,7 @@ bool bwdw_img_plan(const cct_conv_desc_t& d, long long nimg, BwdwImgPlan* P) {
       want = w;
     }
   }
-  want = std::min(want, at_most(cols));
+  want = std::min(want, at_most(cols, ncol));
   cut(cols, want, &S, &len);
   if (all >= (1LL << 30) || tiles * S >= (1LL << 31)) return false;
   P->S = (int)S;

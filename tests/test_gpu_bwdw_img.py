@@ -153,3 +153,15 @@ def test_tiles_of_96_rows(B, L):
     got, names = ran(B, lambda: gpu_backward_weights(B, L, x, dy))
     assert any(n.startswith(KERNEL + "<96") for n in names), names
     check(got, L, x, dy, TOL_F32)
+
+
+@pytest.mark.parametrize("L", [layer("few64", 27, 33, 11, 11, 9, 7, 4, 3), layer("few64_g", 119, 64, 14, 14, 16, 5, 1, 2),
+                               layer("short86", 11, 17, 15, 15, 86, 7, 1, 3), layer("short112", 52, 64, 7, 7, 112, 7, 2, 3)],
+                         ids=lambda L: L.name)
+def test_tiles_of_64_rows(B, L):
+    """Few kernels, and launches too short for larger tiles (14 against 50 us on a lowered matrix, 41 against 84; 25
+    against 30 in a tile of 96 rows, 26 against 31 in one of 128)."""
+    x, dy = synth.make_x(L, 6), synth.make_dy(L, 6)
+    got, names = ran(B, lambda: gpu_backward_weights(B, L, x, dy))
+    assert any(n.startswith(KERNEL + "<64") for n in names), names
+    check(got, L, x, dy, TOL_F32)
