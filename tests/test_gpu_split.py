@@ -83,8 +83,8 @@ def test_backward_data(B, L):
 
 
 def test_precision(B):
-    """Closer to 64 bits than an fp32 accumulation of 2304 products can be expected to come: the sums'
-    one rounding per 16 products measures 2.3e-7 (2-norm), one per 2 products 6e-7."""
+    """Closer to 64 bits than an fp32 accumulation of 2304 products can be expected to come: an MFMA's sums of 16
+    products measure 2.3e-7 (2-norm) as one chain and less in parts, sums of 2 products 6e-7."""
     L = layer("prec", 8, 256, 13, 13, 128, 3, 1, 1, x_dist="relu_normal")
     x, w = synth.make_x(L, 1), synth.make_w(L, 1)
     got = gpu_forward(B, L, x, w, None, B.LOWER_FUSED).astype(np.float64)
@@ -95,14 +95,15 @@ def test_precision(B):
 @pytest.mark.parametrize("L", [layer("p32", 11, 96, 27, 27, 256, 5, 1, 2, 2), layer("p64", 49, 384, 13, 13, 256, 3, 1, 1, 2),
                                layer("p_k7", 6, 80, 28, 28, 352, 7, 2, 3)], ids=lambda L: L.name)
 def test_precision_of_small_layers(B, L):
-    """32- and 64-row tiles sum the contraction in parts of about 36 roundings.  The error of a part is a random
-    walk, 2^-24 / sqrt(3) * sqrt(36 / 2) = 1.5e-7 of the part's sum, and falls with the root of the number of
-    parts; as one chain of 200 to 350 roundings these come out at 2e-7 to 4e-7."""
+    """32- and 64-row tiles sum the contraction in parts of 8 pairs of tiles (K = 7) or 9 to 25 tiles.  The error of a
+    part is a random walk, at most 2^-24 / sqrt(3) * sqrt(25 / 2) = 1.2e-7 of the part's sum, and falls with the root of
+    the number of parts, whose own sum adds as much again at most; as one chain of 200 to 350 roundings these come out
+    at 2e-7 to 4e-7."""
     rng = np.random.default_rng(7)
     w = rng.standard_normal((L.O, L.C // L.groups, L.K, L.K), dtype=np.float32)
     dy = rng.standard_normal((L.N, L.O, L.Hout, L.Wout), dtype=np.float32)
     got, names = ran(B, lambda: gpu_backward_data(B, L, w, dy, B.LOWER_FUSED))
-    assert any(n.startswith((KERNEL + "<1", KERNEL + "<2")) for n in names), names
+    assert any(n.startswith((KERNEL + "<1, 2", KERNEL + "<2, 2")) for n in names), names
     want = oracle.conv_backward_data(odims(oracle, L), w, dy)
     assert np.linalg.norm(got.astype(np.float64) - want) / np.linalg.norm(want) <= 1.5e-7
 
@@ -228,6 +229,16 @@ def test_workspace_for_the_fp32_kernel_matrix_is_still_enough(B):
     assert rel_err(y.cpu().numpy(), oracle.conv_forward(odims(oracle, L), x, w, b)) <= TOL_F32
 
 
+# The 2-norm error of up to 1600 products with every partial product in its place: the six bf16 products hold 2^-25 of
+# each, the chain of at most 75 roundings 2^-24 / sqrt(3) * sqrt(75 / 2) = 2.1e-7.  A third term lost or read from the
+# wrong place is 2^-18 / sqrt(3) of a product and more, 2e-6; m * m left out 1e-6.
+ALL_TERMS = 3e-7
+
+
+def norm_err(got, want):
+    return np.linalg.norm(got.astype(np.float64) - want) / np.linalg.norm(want)
+
+
 # tiles of 128 and 96 rows (256 column tiles), rows to spare, one channel group and an odd number of them
 FORMS = [layer("t96", 200, 24, 13, 13, 96, 3, 1, 1), layer("t80_k5", 200, 16, 13, 13, 80, 5, 1, 2),
          layer("t96_k4", 200, 40, 13, 13, 90, 4, 1, 2), layer("t96_s2d", 150, 3, 67, 67, 96, 11, 4, 0),
@@ -243,6 +254,7 @@ def test_row_tiles(B, L):
     assert any(n.startswith(KERNEL + form) for n in names), names
     want = oracle.conv_forward(odims(oracle, L), x, w, b)
     assert rel_err(got, want) <= TOL_F32
+    assert norm_err(got, want) <= ALL_TERMS
     # values that are not finite, met by whole tiles and by the rows and positions of another wave
     x[0, 0, 0, 0], x[1, 1, 5, 6], x[-1, 2, 12, 12], w[3, 1, 1, 1], w[-1, 0, 0, 0] = np.inf, -np.inf, np.nan, 3.4e38, np.inf
     check_not_finite(gpu_forward(B, L, x, w, b, B.LOWER_FUSED), oracle.conv_forward(odims(oracle, L), x, w, b))
@@ -267,7 +279,9 @@ def test_form_follows_the_launch(B, L, form):
     x, w, b = synth.make_x(L, 7), synth.make_w(L, 7), synth.make_bias(L, 7)
     got, names = ran(B, lambda: gpu_forward(B, L, x, w, b, B.LOWER_FUSED))
     assert any(n == KERNEL + form for n in names), names
-    assert rel_err(got, oracle.conv_forward(odims(oracle, L), x, w, b)) <= TOL_F32
+    want = oracle.conv_forward(odims(oracle, L), x, w, b)
+    assert rel_err(got, want) <= TOL_F32
+    assert norm_err(got, want) <= ALL_TERMS
 
 
 @pytest.mark.parametrize("L,form", [(layer("rows450", 200, 16, 13, 13, 450, 3, 1, 1), "<2, 3, 3, 1, 16>"),
@@ -280,4 +294,38 @@ def test_rows_that_96_and_128_fill(B, L, form):
     x, w = synth.make_x(L, 8), synth.make_w(L, 8)
     got, names = ran(B, lambda: gpu_forward(B, L, x, w, None, B.LOWER_FUSED))
     assert any(n == KERNEL + form for n in names), names
-    assert rel_err(got, oracle.conv_forward(odims(oracle, L), x, w, None)) <= TOL_F32
+    want = oracle.conv_forward(odims(oracle, L), x, w, None)
+    assert rel_err(got, want) <= TOL_F32
+    assert norm_err(got, want) <= ALL_TERMS
+
+
+# Backward-data on tiles of 96 rows: stride 1, two groups, and the strided form, whose rows are channels x residues and
+# whose results are stored depth to space (stride 2: rows 48 .. 95 belong to the waves whose last 16 rows are a half-filled
+# block of the repair; stride 3: rows that end inside a quad)
+BACKWARD_96 = [layer("b96", 200, 96, 13, 13, 40, 3, 1, 1), layer("b90_g", 130, 180, 13, 13, 64, 5, 1, 2, 2),
+               layer("b96_k4", 200, 70, 13, 13, 24, 4, 1, 2), layer("b96_s2", 200, 24, 26, 26, 48, 3, 2, 1),
+               layer("b90_s3", 200, 10, 39, 39, 40, 5, 3, 1), layer("b80_s4", 150, 5, 60, 60, 32, 8, 4, 2)]
+
+
+@pytest.mark.parametrize("L", BACKWARD_96, ids=ids(BACKWARD_96))
+def test_backward_data_on_96_rows(B, L):
+    w, dy = synth.make_w(L, 6), synth.make_dy(L, 6)
+    got, names = ran(B, lambda: gpu_backward_data(B, L, w, dy, B.LOWER_FUSED))
+    assert any(n.startswith(KERNEL + "<2, 3") for n in names), names
+    want = oracle.conv_backward_data(odims(oracle, L), w, dy)
+    assert rel_err(got, want) <= TOL_F32
+    assert norm_err(got, want) <= ALL_TERMS
+    # values that are not finite, in every block of a wave's rows
+    dy[0, 0, 0, 0], dy[1, 1, 5, 6], dy[-1, 2, -1, -1] = np.inf, -np.inf, np.nan
+    w[3, 1, 1, 1], w[5, -1, 0, 0], w[7, L.C // L.groups // 2, 1, 0] = 3.4e38, np.inf, np.nan
+    check_not_finite(gpu_backward_data(B, L, w, dy, B.LOWER_FUSED), oracle.conv_backward_data(odims(oracle, L), w, dy))
+
+
+def test_forward_on_96_rows_in_groups(B):
+    L = layer("g96", 130, 40, 13, 13, 190, 3, 1, 1, 2)
+    x, w, b = synth.make_x(L, 6), synth.make_w(L, 6), synth.make_bias(L, 6)
+    got, names = ran(B, lambda: gpu_forward(B, L, x, w, b, B.LOWER_FUSED))
+    assert any(n.startswith(KERNEL + "<2, 3") for n in names), names
+    want = oracle.conv_forward(odims(oracle, L), x, w, b)
+    assert rel_err(got, want) <= TOL_F32
+    assert norm_err(got, want) <= ALL_TERMS
