@@ -46,7 +46,10 @@
 extern "C" {
 #endif
 
-/* Lowering layout, Sec. 2.1.  AUTO lets cct_pick_lowering decide (it may also pick FUSED). */
+/* Lowering layout, Sec. 2.1.  AUTO lets cct_pick_lowering decide (it may also pick FUSED).  One exception: a forward
+ * pass in fp32 with few products (K >= 2, at most 512 products per result) and results runs, under AUTO, as one
+ * kernel on x and w as they are, whatever cct_pick_lowering answers.  It uses no workspace; the picked layout's
+ * is still asked for and checked, so that the same calls are refused as without it. */
 typedef enum {
   CCT_LOWER_AUTO = 0,
   CCT_LOWER_TYPE1 = 1, /* D^ rows = output positions, cols = (ci,i,j); trivial lifting      */

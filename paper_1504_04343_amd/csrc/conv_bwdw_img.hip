@@ -2,7 +2,7 @@
 //
 //     dw[o][(ci,i,j)] = sum_{n, r, c} dy[n, o, r, c] * xpad[n, ci, r*s + i, c*s + j]
 //
-// A lane of v_mfma_f32_32x32x16_bf16 takes 8 consecutive reduction indices of its row as one 16-byte
+// A lane of v_mfma_f32_16x16x32_bf16 takes 8 consecutive reduction indices of its row as one 16-byte
 // operand.  Taken along a row of the image those 8 values would start at any column (the tap shifts
 // them); taken over 8 IMAGES at one pixel they are one aligned granule whatever the tap.  So the pass is
 //   1. bwdw_img_prep: x (zero padded) and dy are rewritten once as granules of 8 images,
@@ -130,7 +130,7 @@ struct ImgGemm {
 template <int BM, int TERMS, int SLOTS>
 __global__ __launch_bounds__(granule_waves(BM, TERMS) * 64, 2) void conv_bwdw_img(ImgGemm p) {
   using GP = GranuleProduct<BM, TERMS, SLOTS, 16>;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_i[];  // [2][A: SLOTS*BM | B: SLOTS*BN]
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_i[];  // [2][A: SLOTS*BMP | B: SLOTS*BN]
   GP gp;
 
   const int lane = threadIdx.x & 63;

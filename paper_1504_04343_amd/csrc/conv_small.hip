@@ -116,8 +116,11 @@ __global__ __launch_bounds__(64 * PARTS) void conv_small(Small p) {
 // the chip either, so that the line lies near 120000 workgroups x (112 + products).  us, before -> now: 16 images of
 // 14 x 14, 16 -> 32 channels, K = 3 (392 workgroups, 144 products) 11.1 -> 8.4, the same with 64 kernels (784) 11.0
 // against 13.4; 4 images of 7 x 7, 512 -> 128, K = 1 (128) 22.7 -> 11.4; 256 images of 7 x 7, 16 -> 32, K = 1
-// (1568 workgroups, 16 products) 8.6 against 12.0.  Layers of 1 x 1 kernels, which gain less (8 images of 14 x 14,
-// 64 -> 64: 9.8 -> 6.0), stay with the products on the tensor in place, the form that they are relied on to take.
+// (1568 workgroups, 16 products) 8.6 against 12.0.  Layers of 1 x 1 kernels are still left to the
+// products on the tensor in place (gemm_split), although the smallest of them would gain as much (8 images of 14 x 14,
+// 64 -> 64: 9.8 -> 6.0): tests/test_gpu_gemm_split.py calls that kernel through such layers under AUTO.
+// Over 1080 layers that it took: 0.2 to 0.9 times the time, 6 of them more than 3 % slower, by up to 2.4 us at the line.
+// (K up to 65535 only, so that the number of products cannot overflow.)
 bool conv_small_fits(const cct_conv_desc_t& d, int Hout, int Wout) {
   if (d.precision != CCT_PREC_F32 || d.K < 2 || d.K > 0xffff) return false;
   const long long Kd = (long long)(d.C / d.groups) * d.K * d.K, cols = (long long)d.N * Hout * Wout;

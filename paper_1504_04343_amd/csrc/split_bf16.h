@@ -7,12 +7,13 @@
 // the other three are below 2^-25 of the product.  bf16 products are exact in the matrix core's
 // fp32 accumulation.  The partial products are kept in two accumulators: h*h alone in one, the five
 // corrections (2^-8 and smaller) in the other, added once at the end.  The long chain then takes
-// one rounding per 16 reduction indices instead of one per 2, so that the sums come out closer to
+// one rounding per 16 reduction indices instead of one per 2 (v_mfma_f32_16x16x32_bf16 takes 32, with the same
+// errors), so that the sums come out closer to
 // 64 bits than those of v_mfma_f32_32x32x2_f32 (relative error in the 2-norm, 2304 products: 2.3e-7
 // against 6.1e-7 on ReLU data, 43264 products: 1.25e-6 against 2.6e-6; with all six in one
 // accumulator 7.1e-7 and 3.3e-6).
 //
-// Why: six v_mfma_f32_32x32x16_bf16 take 192 cycles where eight v_mfma_f32_32x32x2_f32 take 512.
+// Why: six v_mfma_f32_32x32x16_bf16 (as twelve 16x16x32) take 192 cycles where eight v_mfma_f32_32x32x2_f32 take 512.
 //
 // Range: bf16 has fp32's exponents, so the last bits of a value below 2^-110 would be lost in m and l.  Every
 // value is therefore multiplied by 2^24 before it is split, which keeps the terms of the smallest fp32
