@@ -247,10 +247,10 @@ bool find_split_plan(const cct_conv_desc_t& d, int pass, const Geom& g, SplitPla
   }
   if (fits(0, g.Og, g.Cg, d.K)) {
     // Many channels into one 32-row tile of kernels, whose four waves read the same rows of the pack: where the
-    // launch fills the chip Type 3, whose rows are kernels x taps, is as fast or faster from 32 channels per kernel up (128
-    // images of 28 x 28, 1024 -> 32 channels: 422 us against 437; 512 -> 16: 152 against 214; 256 -> 32: 145
-    // against 114), and beyond that line an explicit FUSED is the fp32 kernel: the fusion on one side of the channel
-    // ratio, Type 3 on the other.
+    // launch fills the chip Type 3, whose rows are kernels x taps, is as fast or faster from 32 channels per kernel up
+    // (128 images of 28 x 28, Type 3 against this kernel, us: 1024 -> 32 channels 437 and 422, 512 -> 16 152 and 214,
+    // 256 -> 32 145 and 114), and beyond that line an explicit FUSED is the fp32 kernel: the fusion on one side of the
+    // channel ratio, Type 3 on the other.
     return !(s == 1 && d.K <= 3 && g.Og <= 32 && g.Cg >= 32 * g.Og && d.N * g.Pc * d.groups >= 256 * 128);
   }
   return (s == 2 || s == 4) && U >= 2 && fits(3, g.Og, g.Cg * s * s, U);
@@ -264,9 +264,9 @@ bool split_plan(const cct_conv_desc_t& d, int pass, const Geom& g, SplitPlan* sp
 
 // Does a fused pass run on conv_fused_split?  An explicit FUSED does wherever it can; AUTO unless the estimate
 // of the fp32 fused kernels is clearly lower: with few channels or kernels much of a tile is padding and they do
-// less of it (22 images of 23 x 23, 8 channels, 32 kernels: 16 us against 23).  Of 2130 passes that both run the split
-// kernel was the faster one in 96 %, of those where its estimate is 1 to 1.5 times the other in 70 %: the other estimate is
-// low there, 0.6 times the time.
+// less of it (22 images of 23 x 23, 8 channels, 32 kernels: 16 us against 23).  Of 2130 passes that both run the
+// split kernel was the faster one in 96 %, of those where its estimate is 1 to 1.5 times the other in 70 %: the other
+// estimate is low there, 0.6 times the time.
 bool use_split(const cct_conv_desc_t& d, int pass, const Geom& g, SplitPlan* sp) {
   if (!split_plan(d, pass, g, sp)) return false;
   if (d.lowering != CCT_LOWER_AUTO || (pass == CCT_PASS_BACKWARD_DATA && d.stride > 1)) return true;

@@ -995,8 +995,8 @@ struct Tile {
 // Rounds of workgroups, each as long as the chain of one: us per K tile of a workgroup that has its CU alone, what
 // every further one on the CU adds, and per round to fill and drain; per channel group the staging that its tiles do
 // not hide, and what each cell of a thread beyond the first adds to that; the two launches; 9 us per million values of
-// the pack.  Fitted to 58900 launches of 24800 passes (1 to 512 images of up to 240 x 240, each pass with every tile that it can
-// take), without what memory bounds: off by 5 to 7 % in the mean and by up to 11 to 16 % in nine of ten, by form.
+// the pack.  Fitted to 58900 launches of 24800 passes (1 to 512 images of up to 240 x 240, each pass with every tile that
+// it can take), without what memory bounds: off by 5 to 7 % in the mean and by up to 11 to 16 % in nine of ten, by form.
 Tile estimate(const GemmTN& p, const KcGeom& fg, size_t lds, long long tn, int rows) {
   struct Rate {
     double tile, next, fill;
@@ -1024,9 +1024,9 @@ Tile estimate(const GemmTN& p, const KcGeom& fg, size_t lds, long long tn, int r
                            9.0e-6 * p.G * p.Mpad * tiles * CG};
 }
 
-// The largest row tile that puts a workgroup on every CU (464 rows, 57 column tiles: 64 rows 18.2 us, 96 23.7).  Where the
-// rows pad less in tiles of 96 than of 128 the estimates choose between the two (450 kernels run as 5 tiles of 96 or 4
-// of 128, which have the higher rate: of 62 such passes that took 128 rows, 0.92 times the time of 96).  Smaller tiles
+// The largest row tile that puts a workgroup on every CU (464 rows, 57 column tiles: 64 rows 18.2 us, 96 23.7).  Where
+// the rows pad less in tiles of 96 than of 128 the estimates choose between the two (450 kernels run as 5 tiles of 96
+// or 4 of 128, which have the higher rate: of 62 such passes that took 128 rows, 0.92 times the time of 96).  Smaller tiles
 // are not weighed against larger ones: they sum in parts, the larger ones do not, and a layer keeps the precision that
 // it has (129 to 192 rows as two tiles of 96 would take 0.95 times as long as three of 64).
 Tile split_tile(const GemmTN& p, const KcGeom& fg, size_t lds, long long tn) {

@@ -12,8 +12,9 @@
 // 1870 TFLOP/s; zeros: 2450 both), because an accumulator is read and written half as often per flop; the results round
 // alike (2-norm against 64 bits the same to four digits).  Measured with three terms, 128 rows: conv2's
 // backward-weights product (114.7 GFLOP) 604 -> 537 us, conv3's at batch 1024 (306 GFLOP) 1319 -> 1255.
-// 32 x 32 where the results go straight to the output tensor (conv_granules), in rows of 128 bytes instead of 64: over 3400
-// bf16 layers forward 1 to 3 % faster, backward-data 2 to 5 % on 128 rows; partial products (conv_bwdw_img) 2 % slower.
+// 32 x 32 where the results go straight to the output tensor (conv_granules), in rows of 128 bytes instead of 64: over
+// 3400 bf16 layers forward 1 to 3 % faster, backward-data 2 to 5 % on 128 rows; partial products (conv_bwdw_img) 2 %
+// slower.
 //
 // A wave of 64 x 64 reads 24 KiB of LDS for 96 MFMAs (1536 matrix-core cycles) per 32 reduction indices, three quarters
 // of what LDS can deliver to four SIMDs, and a 128 x 256 workgroup fetches 72 KiB of L2 for 3072 cycles of its CU.
