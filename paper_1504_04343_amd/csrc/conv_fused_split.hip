@@ -28,9 +28,9 @@
 //     conv2 forward 490 -> 450, backward-data 613 -> 586, conv3 at batch 1024 1238 -> 1141 and 1273 -> 1182; 64 images
 //     of 28 x 28, 64 channels: K = 7 to 64 kernels 149 -> 111.
 //   - 32: v_mfma_f32_32x32x16_bf16 takes one tile; 3 x 3 and 5 x 5 kernels, all taps of a group unrolled, so that
-//     nothing is looked up or decided between the MFMAs of a lone wave.  16 -> 32: 50 images of conv5 forward
-//     71.7 -> 68.6, 4 images of 28 x 28, 64 -> 128, K = 3, 18.9 -> 17.8, 48 workgroups of K = 5 24.4 -> 21.1; over 9100
-//     layers 0.93 (K = 3) and 0.86 times (K = 5) the time on 32 rows, 0.94 and 0.95 on 64.
+//     nothing is looked up or decided between the MFMAs of a lone wave.  16 -> 32, in us: 50 images of conv5 forward
+//     71.7 -> 67.9, 4 images of 28 x 28, 64 -> 128, K = 3, 18.9 -> 18.4, 48 workgroups of K = 5 24.4 -> 21.1, 20 images of
+//     27 x 27, 192 -> 192, K = 3, 72.3 -> 67.4.
 // 48-row tiles for conv2's backward-data (48 rows on 64) were slower than the padding, 800 against 730: four waves
 // then ask the L1 for the same 9 KiB per 576 MFMA cycles.  Splitting and loading in pieces between the MFMAs gave
 // nothing (conv5 75 -> 78), nor did kernel values four pairs ahead.
@@ -301,7 +301,7 @@ __global__ __launch_bounds__(NT, 2) void conv_fused_split(GemmTN p, KcGeom fg, i
     // The next group's four steps, FL at a time: loaded before one pair of tiles, stored before a later one, so that
     // the MFMAs between cover the way to memory.  Register budget decides FL; where it is short, 5 x 5 kernels have
     // the tiles to go one by one.
-    constexpr int FL = KT != 0 && WAVES_M * RB <= 4 ? 4 : KT == 5 ? 1 : 2;  // KT == 0: one cell
+    constexpr int FL = KT != 0 && WAVES_M * RB <= 4 && S == 1 ? 4 : KT == 5 ? 1 : 2;  // KT == 0: one cell
     float stg[FL][8];
 
     // operands two pairs of tiles ahead
@@ -972,18 +972,17 @@ inline int workgroups_per_cu(const GemmTN& p, size_t lds, int rows) {
   return std::max(1, std::min(rows == 32 && compiled_k(p) == 3 && p.s2d < 4 ? 3 : 2, (int)(160 * 1024 / lds)));
 }
 
-// Edge of the MFMA's blocks.  Unrolled taps in blocks of 32 x 32 for 32 and 64 rows (16 x 16 take 1.05 to 1.2 times as
-// long), and for 128 where a workgroup has its CU alone (1.12 times) or the launch is too short to run into the power
-// limit (one group of 3 x 3: 1.05; from 128 tiles in a row up 0.99, conv2 and conv3 at large batches 0.92 to 0.95).
-// 5 x 5 on 64 rows meets it in a long launch of long chains, from 3 rounds of 4 groups up (0.98; conv2's
-// backward-data 0.96).
-inline int split_block(const GemmTN& p, const KcGeom& fg, size_t lds, long long tn, int rows) {
-  const int KT = compiled_k(p), share = workgroups_per_cu(p, lds, rows);
-  if (!KT || rows == 96) return 16;
-  if (rows == 32 || share == 1) return 32;
-  const long long per_cu = (tn * row_tiles(p, rows) * p.G + 255) / 256, rounds = (per_cu + share - 1) / share;
-  if (rows == 64) return KT == 5 && rounds >= 3 && fg.ngroups >= 4 ? 16 : 32;
-  return fg.ngroups * tiles_per_group(p.gK) * rounds < (KT == 5 ? 50 : 128) ? 32 : 16;
+// Edge of the MFMA's blocks: unrolled taps in blocks of 32 x 32 where a workgroup has its CU alone, by its cells (64 and
+// 128 rows 0.86 to 0.89 times the time of 16 x 16) or, on 64 rows, because at most half of the CUs get a second one, and on
+// 32 rows at any size (0.85 to 1.0).  Beyond that the matrix cores run into the power limit, where 16 x 16 are the faster
+// ones.  64 rows, 64 channels of 27 x 27, K = 3: 274 workgroups 0.93, 365 0.94 and 0.96, 399 0.95 and 0.98, 479 0.99 and
+// 1.02 times; K = 5: 288 0.93, 384 0.95, 504 1.00 and 1.01; conv4 at batch 256 1.05.  128 rows: 476 workgroups 1.03, 1600
+// 1.09.  The limit shows in runs of one kernel that last: bursts of 0.4 ms in turn with another form had 32 x 32 ahead by
+// 5 % on 64 rows at any size.
+inline int split_block(const GemmTN& p, size_t lds, long long tn, int rows) {
+  if (!compiled_k(p) || rows == 96) return 16;
+  if (rows == 32 || workgroups_per_cu(p, lds, rows) == 1) return 32;
+  return rows == 64 && tn * row_tiles(p, rows) * p.G <= 384 ? 32 : 16;
 }
 
 // A launch: rows of a workgroup, edge of the MFMA's blocks, what it is estimated to take.
@@ -1014,7 +1013,7 @@ Tile estimate(const GemmTN& p, const KcGeom& fg, size_t lds, long long tn, int r
       {{{0.242, 0.091, 3.3}, {0.319, 0.173, 6.2}, {0.505, 0.213, 8.7}, {0.578, 0.304, 11.6}, {0.524, 0.385, 10.8}}, 0.0, 0.73, 6.1}};
   const int S = p.s2d ? p.s2d : 1, KT = compiled_k(p);
   const Form& f = forms[S > 1 ? (KT ? 4 : 3) : KT == 3 ? 1 : KT == 5 ? 2 : 0];
-  const int share = workgroups_per_cu(p, lds, rows), block = split_block(p, fg, lds, tn, rows);
+  const int share = workgroups_per_cu(p, lds, rows), block = split_block(p, lds, tn, rows);
   const Rate& r = f.of[rows == 128 && block == 32 ? 4 : rows / 32 - 1];
   const long long per_cu = (tn * row_tiles(p, rows) * p.G + 255) / 256;
   const double tiles = (double)fg.ngroups * tiles_per_group(p.gK);
@@ -1093,9 +1092,7 @@ int launch_conv_fused_split(const GemmTN& p0, hipStream_t st) {
   const Tile t = split_tile(p, fg, lds, column_tiles(p, fg, p.Ncols / (p.gHout * p.gWout)));
   switch (t.rows) {
     case 32: return launch_rows<1, 2, 32>(p, fg, lds, st);
-    case 64:
-      if (t.block == 16 && p.gK == 5) return launch_variant<2, 2, 5, 1, 16>(p, fg, lds, st);
-      return launch_rows<2, 2, 32>(p, fg, lds, st);
+    case 64: return t.block == 32 ? launch_rows<2, 2, 32>(p, fg, lds, st) : launch_rows<2, 2, 16>(p, fg, lds, st);
     case 96: return launch_rows<2, 3, 16>(p, fg, lds, st);
     default: return t.block == 32 ? launch_rows<4, 2, 32>(p, fg, lds, st) : launch_rows<4, 2, 16>(p, fg, lds, st);
   }

@@ -260,16 +260,18 @@ def test_row_tiles(B, L):
     check_not_finite(gpu_forward(B, L, x, w, b, B.LOWER_FUSED), oracle.conv_forward(odims(oracle, L), x, w, b))
 
 
-# The form of the kernel by what a launch holds: unrolled taps in blocks of 32 x 32 for lone workgroups and short
-# launches, pairs of taps in blocks of 16 x 16 for long ones.
+# The form of the kernel by what a launch holds: unrolled taps in blocks of 32 x 32 on 32 rows and for workgroups that have
+# their CU alone (few of them, or cells that fill more than half of the LDS), pairs of taps in blocks of 16 x 16 for others.
 BLOCKS = [(layer("lone32_k3", 4, 64, 28, 28, 128, 3, 1, 1), "<1, 2, 3, 1, 32>"),
           (layer("lone32_k5", 2, 48, 27, 27, 128, 5, 1, 2), "<1, 2, 5, 1, 32>"),
           (layer("lone32_s2d", 2, 32, 27, 27, 40, 5, 2, 2), "<1, 2, 3, 2, 32>"),
           (layer("lone32_s4", 1, 3, 67, 67, 36, 11, 4, 0), "<1, 2, 3, 4, 32>"),
           (layer("lone64_k3", 50, 40, 27, 27, 60, 3, 1, 1), "<2, 2, 3, 1, 32>"),
           (layer("lone64_k5", 50, 32, 27, 27, 60, 5, 1, 2), "<2, 2, 5, 1, 32>"),
-          (layer("brief128", 200, 16, 13, 13, 128, 3, 1, 1), "<4, 2, 3, 1, 32>"),
-          (layer("wide128", 8, 16, 64, 80, 128, 3, 1, 1), "<4, 2, 3, 1, 32>"),
+          (layer("wide64", 20, 16, 40, 88, 60, 3, 1, 1), "<2, 2, 3, 1, 32>"),
+          (layer("wide128", 8, 16, 64, 88, 128, 3, 1, 1), "<4, 2, 3, 1, 32>"),
+          (layer("pairs64_k3", 68, 40, 27, 27, 60, 3, 1, 1), "<2, 2, 3, 1, 16>"),
+          (layer("pairs128_k3", 200, 16, 13, 13, 128, 3, 1, 1), "<4, 2, 3, 1, 16>"),
           (layer("long64_k5", 180, 64, 27, 27, 40, 5, 1, 2), "<2, 2, 5, 1, 16>"),
           (layer("long128_k5", 200, 48, 13, 13, 128, 5, 1, 2), "<4, 2, 5, 1, 16>")]
 
@@ -285,8 +287,8 @@ def test_form_follows_the_launch(B, L, form):
 
 
 @pytest.mark.parametrize("L,form", [(layer("rows450", 200, 16, 13, 13, 450, 3, 1, 1), "<2, 3, 3, 1, 16>"),
-                                    (layer("rows449", 240, 32, 13, 13, 449, 3, 1, 1), "<4, 2, 3, 1, 32>"),
-                                    (layer("rows464_few", 24, 16, 17, 17, 464, 3, 1, 1), "<2, 2, 3, 1, 32>"),
+                                    (layer("rows449", 240, 32, 13, 13, 449, 3, 1, 1), "<4, 2, 3, 1, 16>"),
+                                    (layer("rows464_few", 24, 16, 17, 17, 464, 3, 1, 1), "<2, 2, 3, 1, 16>"),
                                     (layer("rows470_k2", 200, 16, 13, 13, 470, 2, 1, 0), "<4, 2, 0, 1, 16>")],
                          ids=lambda v: v.name if hasattr(v, "name") else v)
 def test_rows_that_96_and_128_fill(B, L, form):
