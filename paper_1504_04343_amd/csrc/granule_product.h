@@ -13,7 +13,8 @@
 // alike (2-norm against 64 bits the same to four digits).  Measured with three terms, 128 rows: conv2's
 // backward-weights product (114.7 GFLOP) 604 -> 537 us, conv3's at batch 1024 (306 GFLOP) 1319 -> 1255.
 // 32 x 32 where the results go straight to the output tensor (conv_granules), in rows of 128 bytes instead of 64: over
-// 3400 bf16 layers forward 1 to 3 % faster, backward-data 2 to 5 % on 128 rows; partial products (conv_bwdw_img) 2 %
+// 3400 bf16 layers in bursts of 0.4 ms forward 1 to 3 % faster, backward-data 2 to 5 % on 128 rows, and in runs of one
+// pass that last 0.92 to 0.98 times the time on 128 rows, 0.98 to 1.03 on 64; partial products (conv_bwdw_img) 2 %
 // slower.
 //
 // A wave of 64 x 64 reads 24 KiB of LDS for 96 MFMAs (1536 matrix-core cycles) per 32 reduction indices, three quarters
