@@ -369,15 +369,14 @@ inline bool short_product(int M, int K) {
   return K <= 32 && align_up(M, BM) <= gemm_split_mpad(M);
 }
 
-GemmTN pointwise_problem(const cct_conv_desc_t& d, int pass, const Geom& g, const Layout& L, const void* pack,
-                         const float* in, float* out, const float* bias, long long ni) {
+GemmTN pointwise_problem(const cct_conv_desc_t& d, int pass, const Geom& g, const Layout& L, const float* in,
+                         float* out, const float* bias, long long ni) {
   const long long HW = (long long)d.H * d.W;
   const bool fwd = pass == CCT_PASS_FORWARD;
   GemmTN p;
   std::memset(&p, 0, sizeof(p));
   p.M = fwd ? g.Og : g.Cg; p.Kdim = fwd ? g.Cg : g.Og; p.Ncols = (int)(ni * HW); p.G = d.groups;
-  p.A = pack; p.Mpad = L.Mpad; p.Kpad = L.Kpad;
-  p.a_gs = (long long)L.Mpad * L.Kpad;
+  p.Mpad = L.Mpad; p.Kpad = L.Kpad;
   p.B = in; p.b_ks = HW; p.b_gs = (long long)p.Kdim * HW;
   p.bmap = ColMap{(int)HW, (long long)(fwd ? d.C : d.O) * HW};
   p.C = out; p.c_ms = HW; p.c_gs = (long long)p.M * HW;
@@ -393,7 +392,7 @@ bool pointwise_split(const cct_conv_desc_t& d, int pass, const Geom& g, long lon
   if (short_product(fwd ? g.Og : g.Cg, fwd ? g.Cg : g.Og)) return false;
   L->Mpad = gemm_split_mpad(fwd ? g.Og : g.Cg);
   L->Kpad = gemm_split_kpad(fwd ? g.Cg : g.Og);
-  return gemm_split_fits(pointwise_problem(d, pass, g, *L, nullptr, nullptr, nullptr, nullptr, nc), false);
+  return gemm_split_fits(pointwise_problem(d, pass, g, *L, nullptr, nullptr, nullptr, nc), false);
 }
 
 // Type 3 forward (D^ is x itself) and Type 1 backward-data (dR^ is dy itself) in fp32: the product on
@@ -657,14 +656,13 @@ double find_kernel_cost(const cct_conv_desc_t& d, int pass, int type, const Geom
   } else if (Layout L; tensor_split(d, pass, type, g, 1, &L)) {
     const bool fwd = pass == CCT_PASS_FORWARD;
     const double side = (fwd ? rt_elems : dt_elems) * 4.0;  // written by the product, read by lift / inverse lowering
-    const double t = gemm_split_seconds(L.Mpad, fwd ? g.Kd : g.Mr, (long long)cols, d.groups);
+    const double t = gemm_split_seconds(false, true, fwd ? g.Mr : g.Kd, fwd ? g.Kd : g.Mr, (long long)cols, d.groups);
     const double product = std::max(t, ((fwd ? x_bytes : y_bytes) + side) / kGemmBytesPerSec);
-    // The product, its result through memory, the gather's chain of taps.  Fitted to 21000 passes: off by 10 % in the
-    // mean, 23 % in nine of ten (4 TB/s, 0.35 us per tap and three launches of 4 us: a third too much in the mean
-    // and twice what passes under 15 us take).
+    // The product, its result through memory, the gather's chain of taps.  Fitted to 145 passes of 3 x 3 layers (what a
+    // tap adds: to 21000 passes with the tiles before): off by 7 % in the mean, 15 % in nine of ten.
     const double U = (d.K + d.stride - 1) / d.stride;  // taps per axis that a pixel of dx receives
-    return fwd ? product + side / 5.3e12 + y_bytes / 1.06e12 + d.K * d.K * 0.28e-6 + 2.3e-6
-               : product + side / 3.6e12 + x_bytes / 2.5e12 + U * U * 0.35e-6 + 2.5e-6;
+    return fwd ? product + side / 4.57e12 + y_bytes / 1.79e12 + d.K * d.K * 0.28e-6 + 0.8e-6
+               : product + side / 4.48e12 + x_bytes / 1.74e12 + U * U * 0.35e-6;
   } else if (pass == CCT_PASS_FORWARD) {
     index_bytes += x_bytes + dt_elems * es;      // lowering: read x, write D^T
     gemm_bytes += dt_elems * es;                 // GEMM reads D^T
@@ -1089,14 +1087,15 @@ int run_pointwise(const cct_conv_desc_t& d, const Geom& g, int pass, const Layou
                   const float* w, const float* bias, float* out, char* ws, hipStream_t st) {
   const bool fwd = pass == CCT_PASS_FORWARD;
   const long long HW = (long long)d.H * d.W, in_img = (fwd ? d.C : d.O) * HW, out_img = (fwd ? d.O : d.C) * HW;
-  const int M = fwd ? g.Og : g.Cg, Kd = fwd ? g.Cg : g.Og;
+  const int Kd = fwd ? g.Cg : g.Og;
   void* pack = ws + L.pack_off;
-  int rc = launch_pack_rows_split(w, pack, d.groups, M, L.Mpad, L.Kpad, Kd, d.groups * Kd, fwd ? g.Cg : 1,
-                                  fwd ? 1 : g.Cg, (long long)g.Og * g.Cg, st);
+  GemmTN p = pointwise_problem(d, pass, g, L, in, out, bias, std::min<long long>(nc, d.N));
+  int rc = gemm_split_operand(&p, false, w, pack, d.groups * Kd, fwd ? g.Cg : 1, fwd ? 1 : g.Cg, (long long)g.Og * g.Cg, 1, st);
   for (long long n0 = 0; n0 < d.N && !rc; n0 += nc) {
-    const long long ni = std::min<long long>(nc, d.N - n0);
-    rc = launch_gemm_split(pointwise_problem(d, pass, g, L, pack, in + n0 * in_img, out + n0 * out_img, bias, ni),
-                           d.groups * Kd, false, st);
+    p.B = in + n0 * in_img;
+    p.C = out + n0 * out_img;
+    p.Ncols = (int)(std::min<long long>(nc, d.N - n0) * HW);
+    rc = launch_gemm_split(p, d.groups * Kd, false, st);
   }
   return rc;
 }
@@ -1110,21 +1109,21 @@ int run_tensor_split(const cct_conv_desc_t& d, const Geom& g, int pass, const La
   const long long out_img = fwd ? (long long)d.O * g.Hout * g.Wout : (long long)d.C * d.H * d.W;
   void* pack = ws + L.pack_off;
   float* side = reinterpret_cast<float*>(ws + (fwd ? L.rt_off : L.dt_off));
+  GemmTN p;
+  std::memset(&p, 0, sizeof(p));
+  p.Mpad = L.Mpad; p.Kpad = L.Kpad;
+  p.b_ks = g.Pc; p.b_gs = (long long)Kd * g.Pc;
+  p.bmap = ColMap{(int)g.Pc, in_img};
+  p.C = side; p.c_ms = L.ld; p.c_gs = (long long)M * L.ld;
+  p.cmap = kPlain;
+  p.M = M; p.Ncols = (int)(std::min<long long>(nc, d.N) * g.Pc); p.Kdim = Kd; p.G = d.groups;
   // forward: rows (oo, i, j), k = ci; backward-data: rows (ci, i, j), k = oo
-  int rc = launch_pack_rows_split(w, pack, d.groups, M, L.Mpad, L.Kpad, Kd, d.groups * Kd,
-                                  fwd ? (long long)g.Cg * KK : KK, fwd ? KK : (long long)g.Cg * KK,
-                                  (long long)g.Og * g.Cg * KK, st, KK);
+  int rc = gemm_split_operand(&p, false, w, pack, d.groups * Kd, fwd ? (long long)g.Cg * KK : KK, fwd ? KK : (long long)g.Cg * KK,
+                              (long long)g.Og * g.Cg * KK, KK, st);
   for (long long n0 = 0; n0 < d.N && !rc; n0 += nc) {
     const int ni = (int)std::min<long long>(nc, d.N - n0);
-    GemmTN p;
-    std::memset(&p, 0, sizeof(p));
-    p.A = pack; p.Mpad = L.Mpad; p.Kpad = L.Kpad;
-    p.a_gs = (long long)L.Mpad * L.Kpad;
-    p.B = in + n0 * in_img; p.b_ks = g.Pc; p.b_gs = (long long)Kd * g.Pc;
-    p.bmap = ColMap{(int)g.Pc, in_img};
-    p.C = side; p.c_ms = L.ld; p.c_gs = (long long)M * L.ld;
-    p.cmap = kPlain;
-    p.M = M; p.Ncols = (int)(ni * g.Pc); p.Kdim = Kd; p.G = d.groups;
+    p.B = in + n0 * in_img;
+    p.Ncols = (int)(ni * g.Pc);
     rc = launch_gemm_split(p, d.groups * Kd, false, st);
     if (rc) break;
     rc = fwd ? launch_lift(side, L.ld, out + n0 * out_img, bias, ni, d.O, g.lift, st)

@@ -64,7 +64,9 @@ struct GemmTN {
   ColMap cmap;
   const float* bias;   // nullable; bias[g*bias_gs + m]
   int bias_gs;         // < 0 (gemm_split): bias[col]
-  long long a_ms;      // != 0 (gemm_split): A is fp32, k-contiguous rows a_ms apart, groups a_gs apart
+  long long a_ms;      // != 0 (gemm_split): A is fp32, A(m, k) at m / a_taps * a_ms + m % a_taps + k * a_ks, groups a_gs apart
+  long long a_ks, a_len, b_len;  // elements of A and B from their beginning
+  int a_taps, rb;
   int M, Ncols, Kdim;  // true sizes per group
   int G;
   int bf16;            // operands are bf16 (A packed bf16, B bf16 plain rows)
@@ -169,19 +171,17 @@ struct ConvBwdW {
 bool conv_bwdw_fused_fits(int C, int H, int W, int K, int s, int pad, int Hout, int Wout, int Cg,
                           int Og, int O);
 int launch_conv_bwdw_fused(const ConvBwdW& p, hipStream_t st);
-// The same arithmetic for products whose B is a tensor in place (gemm_split.hip): GemmTN with the pack of
-// launch_pack_rows_split, B column-contiguous through bmap or, with bt, k-contiguous rows b_ks apart.
-// With a_ms set A is read in place as well: bt and up to 32 rows.
-// G groups of Kdim indices, the last one shorter when Ktotal < G * Kdim.
+// The same arithmetic for products whose B is a tensor in place (gemm_split.hip): B column-contiguous through bmap or, with
+// bt, k-contiguous rows b_ks apart; A as gemm_split_operand sets it.
 int gemm_split_mpad(int M);
 int gemm_split_kpad(int K);
 bool gemm_split_fits(const GemmTN& p, bool bt);
-int gemm_split_bm(int Mpad, long long tiles_n, int K, int G);
 int launch_gemm_split(const GemmTN& p, int Ktotal, bool bt, hipStream_t st);
-double gemm_split_seconds(int Mpad, int K, long long cols, long long G);
-// pack of element (m, k) of group g = src[g*sg + (m / taps)*sm + m % taps + k*sk]
-int launch_pack_rows_split(const float* src, void* pack, int G, int M, int Mpad, int Kpad, int Kdim, int Ktotal,
-                           long long sm, long long sk, long long sg, hipStream_t st, int taps = 1);
+double gemm_split_seconds(bool bt, bool pack, int M, int K, long long cols, long long G);
+// Its operand A(m, k) of group g = src[g*sg + (m / taps)*sm + m % taps + k*sk]: packed into `pack` where that pays (or,
+// without one, never), else read in place.  Sets p's fields for A; the others must be set but for the tensor and the result.
+int gemm_split_operand(GemmTN* p, bool bt, const float* src, void* pack, int Ktotal, long long sm, long long sk, long long sg,
+                       int taps, hipStream_t st);
 
 // Backward-weights pass on granules of 8 images (conv_bwdw_img.hip), fp32 as three bf16 terms or bf16:
 // plan for nimg images at a time and the workspace it needs.  false = sizes it cannot address.
@@ -219,7 +219,7 @@ struct FcPlan {
   long long pack_off, part_off, scratch_off, total;  // workspace layout (bytes)
   int BM, Mpad, Kpad;   // packed dy of the two backward passes (Kpad: rows of one split)
   int S, split_len;     // splits of the contraction: forward over F, backward-data over O
-  int split;            // on gemm_split, the small operand packed as three bf16 terms
+  int split;            // on gemm_split
 };
 // max_bytes < 0: the recommended plan; otherwise a plan within max_bytes of workspace (the forward
 // pass then uses fewer splits).  false = the descriptor is not such a layer, the pass cannot take

@@ -124,12 +124,26 @@ int launch_fc_sum_splits(const float* part, float* out, int S, long long total, 
 
 namespace {
 
-// The plan on gemm_split.  The row operand (x of the forward pass, dy of the others) is packed as three
-// bf16 terms, w and x are read in place.  The contraction is cut into the number of splits S that is
-// estimated fastest: rounds of workgroups times their stages, against the partial products that are
-// written and read once more.  Measured, fc6 at batch 256
-// (19.3 GFLOP per pass): forward 1 / 4 / 8 / 16 splits 310 / 130 / 117 / 123 us, backward-data 1 / 4 / 7 /
-// 16 splits 198 / 141 / 126 / 158; before, on the fp32 matrix instructions, 195 and 214.  false = sizes or a workspace that it
+// The fewest splits by precision: a sum's rounding grows with the length of its chain (256 images of 9216 features, 2-norm:
+// chains of 1152 products 1.6e-7, of 2304 2.3e-7).  Chains are as short as tiles of 128, 64 or 32 rows need to fill the
+// chip: rounds of workgroups (512 of 128 rows, 1024 of fewer) times their stages of 32, 4 us to fill and drain a round.
+double chain_seconds(int Mpad, long long tiles_n, int K, long long G) {
+  int BM = Mpad % 128 == 0 && K > 128 ? 128 : Mpad % 64 == 0 ? 64 : 32;
+  long long wgs = tiles_n * ((unsigned)Mpad / (unsigned)BM) * G;
+  for (; BM > 32 && wgs < 256; BM /= 2) wgs *= 2;
+  const int log_slots = BM == 128 ? 9 : 10, slots = 1 << log_slots;
+  const double flops = BM == 128 ? 1.0 / 230.0e12 : BM == 64 ? 1.0 / 200.0e12 : 1.0 / 120.0e12;
+  const double stage = 2.0 * BM * 128 * 32 * flops * slots;
+  const double share = std::min(1.0, 0.3 + 0.7 * (double)((wgs + 255) >> 8) * (256.0 / slots));
+  return (double)((wgs + slots - 1) >> log_slots) * ((K + 31) / 32 * stage * share + 4.0e-6);
+}
+
+// The plan on gemm_split.  The row operand (x of the forward pass, dy of the others) is packed as three bf16 terms or
+// split in place, as gemm_split's estimates say; w and x are read in place.  The contraction is cut into the number of
+// splits S that is estimated fastest, but for precision no fewer than chain_seconds asks for: rounds of workgroups
+// times their stages, against the partial products that are written and read once more.  Measured, fc6 at batch 256
+// (19.3 GFLOP per pass): forward 1 / 2 / 8 / 27 splits 320 / 175 / 113 / 148 us, backward-data 1 / 3 / 11 / 27 splits
+// 163 / 116 / 137 / 181; a 4096 -> 1000 layer forward 1 / 4 / 8 splits 127 / 41 / 27.  false = sizes or a workspace that it
 // cannot take, or a backward-weights pass over up to 32 images, whose product is one short stage of
 // 32 images: the fp32 kernel wastes less there (fc6, one image: 36 us against 43).
 // *estimate: its seconds; *limited: without the workspace's limit there is a faster one.
@@ -171,23 +185,36 @@ bool fc_plan_split(const cct_conv_desc_t& d, int pass, long long max_bytes, long
   };
   auto seconds = [&](long long S) {
     const long long n = count(S);
-    return gemm_split_seconds(p.Mpad, (int)len(S), cols, n) +
-           (n > 1 ? 2.0 * n * out / 6.0e12 : 0.0);
+    return gemm_split_seconds(fwd, !fwd || d.N > 32, M, (int)len(S), cols, n) +
+           (n > 1 ? 2.0 * n * out / 5.5e12 + 2.5e-6 : 0.0);
   };
-  long long S = 1;
-  double best = !bwdw && need(1) <= cap ? seconds(1) : 1e30;
+  long long S = 1, least = 1;
+  double best = 1e30, shortest = 1e30;
   *limited = false;
+  auto each = [&](auto visit) {
+    visit(1LL);
+    for (int sp = 2; sp <= 64 && Kd >= (long long)sp * kFcMinSplitRows; sp += sp < 16 ? 1 : 4) visit((long long)sp);
+  };
   if (!bwdw) {
-    for (int sp = 2; sp <= 64 && Kd >= (long long)sp * kFcMinSplitRows; sp += sp < 16 ? 1 : 4) {
-      const double t = seconds(sp);
-      if (t >= best) continue;
+    each([&](long long sp) {
+      const long long n = count(sp);
+      const double t = chain_seconds(p.Mpad, (cols + 127) / 128, (int)len(sp), n) + (n > 1 ? 2.0 * n * out / 6.0e12 : 0.0);
+      if (t >= shortest) return;
       if (need(sp) <= cap) {
-        best = t;
-        S = sp;
+        shortest = t;
+        least = sp;
       } else {
         *limited = true;
       }
-    }
+    });
+    S = least;
+    each([&](long long sp) {
+      if (sp < least || need(sp) > cap) return;
+      const double t = seconds(sp);
+      if (t >= best) return;
+      best = t;
+      S = sp;
+    });
   }
   *estimate = best;
   if (max_bytes >= 0 && need(S) > max_bytes) return false;
@@ -205,11 +232,9 @@ bool fc_plan_split(const cct_conv_desc_t& d, int pass, long long max_bytes, long
   return true;
 }
 
-GemmTN fc_split_problem(const FcPlan& P, int M, int Ncols, const void* pack, const float* B, float* C) {
+GemmTN fc_split_problem(const FcPlan& P, int M, int Ncols, const float* B, float* C) {
   GemmTN p;
   std::memset(&p, 0, sizeof(p));
-  p.A = pack;
-  p.a_gs = (long long)P.Mpad * P.Kpad;
   p.Mpad = P.Mpad; p.Kpad = P.Kpad;
   p.B = B; p.b_ks = P.F;
   p.bmap = ColMap{kIntMax, 0};
@@ -321,14 +346,9 @@ int fc_forward(const cct_conv_desc_t& d, const FcPlan& P, const float* x, const 
   if (P.split) {
     void* pack = ws + P.pack_off;
     float* part = reinterpret_cast<float*>(ws + P.part_off);
-    GemmTN p = fc_split_problem(P, d.N, d.O, pack, w, P.S > 1 ? part : y);
-    int rc;
-    if (d.N <= 32) {
-      p.A = x; p.a_ms = P.F; p.a_gs = P.split_len;
-    } else if ((rc = launch_pack_rows_split(x, pack, P.S, d.N, P.Mpad, P.Kpad, P.split_len, P.F, P.F, 1,
-                                            P.split_len, st)) != 0) {
-      return rc;
-    }
+    GemmTN p = fc_split_problem(P, d.N, d.O, w, P.S > 1 ? part : y);
+    int rc = gemm_split_operand(&p, true, x, d.N <= 32 ? nullptr : pack, P.F, P.F, 1, P.split_len, 1, st);
+    if (rc) return rc;
     p.b_gs = P.split_len;
     if (P.S == 1) {
       p.bias = bias; p.bias_gs = -1;
@@ -355,9 +375,9 @@ int fc_backward_data(const cct_conv_desc_t& d, const FcPlan& P, const float* w, 
   if (P.split) {
     void* pk = ws + P.pack_off;
     float* part = reinterpret_cast<float*>(ws + P.part_off);
-    int rc = launch_pack_rows_split(dy, pk, P.S, d.N, P.Mpad, P.Kpad, P.split_len, d.O, d.O, 1, P.split_len, st);
+    GemmTN p = fc_split_problem(P, d.N, P.F, w, P.S > 1 ? part : dx);
+    int rc = gemm_split_operand(&p, false, dy, pk, d.O, d.O, 1, P.split_len, 1, st);
     if (rc) return rc;
-    GemmTN p = fc_split_problem(P, d.N, P.F, pk, w, P.S > 1 ? part : dx);
     p.b_gs = (long long)P.split_len * P.F;
     rc = launch_gemm_split(p, d.O, false, st);
     if (rc || P.S == 1) return rc;
@@ -415,9 +435,10 @@ int fc_backward_weights(const cct_conv_desc_t& d, const FcPlan& P, const float* 
   float* pack = reinterpret_cast<float*>(ws + P.pack_off);
   int rc;
   if (P.split) {
-    rc = launch_pack_rows_split(dy, pack, 1, d.O, P.Mpad, P.Kpad, d.N, d.N, 1, d.O, 0, st);
+    GemmTN p = fc_split_problem(P, d.O, P.F, x, dw);
+    rc = gemm_split_operand(&p, false, dy, pack, d.N, 1, d.O, 0, 1, st);
     if (rc) return rc;
-    rc = launch_gemm_split(fc_split_problem(P, d.O, P.F, pack, x, dw), d.N, false, st);
+    rc = launch_gemm_split(p, d.N, false, st);
   } else {
     rc = fc_weights_f32(d, P, x, dy, dw, pack, st);
   }

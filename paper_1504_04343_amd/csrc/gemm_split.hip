@@ -2,24 +2,24 @@
 // bf16 terms on the bf16 matrix cores (split_bf16.h), for products whose B is a tensor in place: x, w or
 // dy of a fully connected layer, the planes of a layer with 1 x 1 kernels.
 //
-//   - A is the small operand.  It comes packed and split, [group][tile of 16 k][term][row][16]
-//     (launch_pack_rows_split), and never passes through LDS: a lane loads the 16 bytes of its row and
-//     term straight from the pack, one stage ahead.  The waves of a workgroup are stacked along the rows,
-//     so that no two waves read the same rows where there are 128 of them.  DIRECT: up to 32 rows of a
-//     k-contiguous fp32 matrix, which every lane splits itself (one launch less);
-//   - B is staged: 128 columns x 16 or 32 k per stage, fetched two stages ahead into registers, split
-//     there and written to LDS as granules of 8 k, [term][8 k][column], which lanes write and read side by
-//     side (the planes are 64 bytes apart beyond their size, for the k-contiguous form's writes).  B is
-//     read once per row tile; BT: it lies k-contiguous (w of a forward product), 16-byte loads, otherwise
-//     column-contiguous through a column map, 4-byte loads;
+//   - a workgroup computes up to 144 rows x 128 columns with four waves; a wave owns all rows of 32 columns, blocks of
+//     16 x 16 (v_mfma_f32_16x16x32_bf16), two accumulators each;
+//   - B goes from memory into the registers of the one wave that multiplies it, which splits it there: no LDS, no
+//     meeting of waves.  A lane supplies 8 k of two neighbouring columns per stage of 32 k.  The split of the next stage is
+//     written between the MFMAs of this one, 3 or 4 instructions at a time.  Columns lie in pairs (8-byte loads and
+//     stores), one by one (odd planes), or k-contiguous (w of a forward product, 16-byte loads);
+//   - A is shared by the four waves through LDS: units of 16 rows and one term, in lane order, so that a read is 1 KiB
+//     without conflicts.  128 and 144 rows: packed that way and split once per call (launch_pack_rows_split), moved to
+//     LDS by loads that write it directly.  32 and 64 rows: fp32 values in place, any strides, split by the
+//     workgroup on their way; a launch less, and no pack to wait for;
 //   - groups are channel groups or splits of the contraction.
-// With 128 rows the matrix cores bound it: 48 MFMAs per stage and wave (1536 cycles) against about 110
-// vector instructions of splitting; two waves per SIMD and the registers to read ahead.  With 64 or 32
-// rows B's way from memory does: four waves per SIMD, stages of half the size, no reading ahead.
-// Measured (before: fp32 matrix instructions): fc6 at batch 256, 19.3 GFLOP, forward 195 -> 117 us,
-// backward-weights 192 -> 126; one image of fc6 (151 MB of w) 50 -> 36 us; 1 x 1 kernels, 128 images of
-// 28 x 28, 256 -> 64 channels, 52 -> 41 us.
+// What bounds it (fc6 at batch 256, 19.3 GFLOP per product in 98 to 110 us): the MFMAs alone take 62 us, LDS reads add 2,
+// splitting 9, waiting for memory 20.  Before, B went through LDS and A straight to registers in tiles of 128 and 64 rows,
+// always behind a pack: forward 104 -> 99 us, backward-weights 128 -> 110, backward-data 129 -> 113; 144 rows x 512 k x
+// 100352 columns, three tiles of 64 before, 126 -> 90; 256 images of 4096 -> 1000 features, forward, both gradients and what
+// lies around them, 107 -> 90.
 #include <algorithm>
+#include <type_traits>
 
 #include "cct_internal.h"
 #include "gemm_common.h"
@@ -30,283 +30,377 @@ namespace {
 
 constexpr int NT = 256;
 constexpr int BN = 128;
-constexpr int TK = 16;                      // k per tile of the pack
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // 16 bytes, dword aligned
-constexpr int KPAD = 32;                    // the pack is padded to whole stages of any form
-constexpr int PLANE = BN * 16 + 64;         // bytes of one (term, 8 k) plane in LDS
+constexpr int SK = 32;  // k per stage
+typedef __attribute__((address_space(3))) void* lds_ptr;
+typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));  // 8 bytes, dword aligned
 
-template <int WAVES_M, bool BT, bool DIRECT>
-__global__ __launch_bounds__(NT, WAVES_M == 4 ? 2 : WAVES_M == 1 && !BT ? 6 : 4) void gemm_split(GemmTN p, int Ktotal, int tiles_m, int tiles_n) {
-  constexpr int WAVES_N = 4 / WAVES_M;
-  constexpr int WN = BN / (32 * WAVES_N);
-  constexpr int BM = 32 * WAVES_M;
-  constexpr int SK = WAVES_M == 4 ? 32 : 16;  // k per stage
-  constexpr int TPS = SK / TK;                // tiles per stage
-  constexpr int GPT = BN * (SK / 8) / NT;     // granules of 8 k per thread and stage
-  constexpr int SLOT = 3 * (SK / 8) * PLANE;
-  // 128 rows: two waves per SIMD, the next block's operands are read behind the current MFMAs; fewer:
-  // four waves per SIMD hide each other's reads and the registers go there
-  constexpr int NB = WAVES_M == 4 ? 2 : 1;
+// How the operands lie.
+enum AForm { kPacked, kRows, kStrided };     // fp32: k-contiguous, or any strides
+enum BForm { kColumns, kPairs, kContiguous };  // column-contiguous: one by one, in pairs; k-contiguous
 
-  __shared__ __attribute__((aligned(16))) unsigned char Bs[2 * SLOT];
+template <int RB, BForm BF, AForm AF>
+__global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(GemmTN p, int Ktotal, int tiles_m, int tiles_n) {
+  constexpr int BM = 16 * RB;
+  constexpr bool DIRECT = AF != kPacked, BT = BF == kContiguous;
+  constexpr int UNITS = 3 * RB;
+  constexpr int SLOT = UNITS * 1024;
+  constexpr int AP = ((DIRECT ? RB : UNITS) + 3) / 4;  // what a wave moves of A per stage: rows of 16 or units
+  constexpr int RAWS = RB == 8 ? 2 : 1;  // stages of B in registers, as many as there is room for
+  // Three slots for A: the workgroup meets in front of a stage's last block of rows, behind which the next stage's first
+  // operands are read.  Two (fp32 values, whose registers come first; 9 blocks of rows): between the stages.
+  constexpr bool EARLY = !DIRECT && RB % 2 == 0;
+  constexpr int SLOTS = EARLY ? 3 : 2;
+
+  __shared__ __attribute__((aligned(16))) unsigned char As[SLOTS * SLOT];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wave_m = wave / WAVES_N, wave_n = wave % WAVES_N;
-  const int lane_lo = lane & 31, lane_hi = lane >> 5;
+  const int lo = lane & 15, kg = lane >> 4;  // row / pair of columns, which 8 k of a stage
 
-  // every XCD gets a contiguous run of column tiles, the row tiles of one next to each other (they share B)
-  int bid = blockIdx.x;
+  // every XCD gets a contiguous run of tiles, 8 row tiles at a time next to each other: what runs at a time shares
+  // both operands in its L2
+  int idx = blockIdx.x;
   {
     const int total = tiles_m * tiles_n;
     const int per = total >> 3, rem = total & 7;
-    const int xcd = bid & 7, idx = bid >> 3;
-    bid = xcd * per + min(xcd, rem) + idx;
+    const int xcd = idx & 7;
+    idx = xcd * per + min(xcd, rem) + (idx >> 3);
   }
-  const int tile_n = bid / tiles_m, tile_m = bid - tile_n * tiles_m;
+  const int strip = idx / (8 * tiles_n), inner = idx - strip * 8 * tiles_n, rows = min(8, tiles_m - strip * 8);
+  const int tile_n = inner / rows, tile_m = strip * 8 + inner - tile_n * rows;
   const int g = blockIdx.y;
   const int m0 = tile_m * BM, n0 = tile_n * BN;
   const int kd = min(p.Kdim, Ktotal - g * p.Kdim);
   const int stages = (kd + SK - 1) / SK;
-  const bool half = TPS == 2 && (kd - 1) % SK < TK;  // the last stage is one tile
 
-  // ---- B: fixed columns (or column and k for BT) per thread, the stage enters through the base
+  // ---- B: a lane supplies two neighbouring columns, 8 k of each
   const float* Bg = reinterpret_cast<const float*>(p.B) + (long long)g * p.b_gs;
   const int n_f = BT ? 0 : fdiv_u(n0, p.bmap.divM, p.bmap.divsh);
   const float* Bt = BT ? Bg + (long long)n0 * p.b_ks : Bg + (long long)n_f * p.bmap.img_stride;
-  unsigned voff[BT ? GPT : 1];
-  unsigned dst[GPT];  // byte offset of the granule's first term in a slot
-  if constexpr (BT) {
+  const int col0 = n0 + wave * 32 + 2 * lo;
+  unsigned voff[2];
 #pragma unroll
-    for (int u = 0; u < GPT; ++u) {
-      const int q = tid + u * NT, c = q / (SK / 8), kh = q % (SK / 8);
-      voff[u] = (unsigned)((long long)(min(n0 + c, p.Ncols - 1) - n0) * p.b_ks + kh * 8) * 4u;
-      dst[u] = kh * PLANE + c * 16;
+  for (int j = 0; j < 2; ++j) {
+    const int c = min(col0 + j, p.Ncols - (BF == kPairs ? 2 - j : 1));
+    voff[j] = BT ? (unsigned)((long long)(c - n0) * p.b_ks + kg * 8) * 4u
+                 : (unsigned)(col_offset(p.bmap, c) - (long long)n_f * p.bmap.img_stride + (long long)kg * 8 * p.b_ks) * 4u;
+  }
+  // k past the last one: what lies there, or zero beyond the tensor's end (A is zero there; an infinity only costs the
+  // recomputation)
+  const long long b_left = p.b_len - (Bt - reinterpret_cast<const float*>(p.B));
+  auto range = [](long long left) { return left < 0 ? 0 : left >= 0x1fffffff ? 0x7fffffff : (int)left * 4; };
+  float raw[RAWS][2][8];
+  auto load_b = [&](int set, int t) {
+    const long long at = (long long)t * SK * (BT ? 1 : p.b_ks);
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(Bt + at), 0, range(b_left - at), 0x00020000);
+    const unsigned ks = (unsigned)p.b_ks * 4u;
+#pragma unroll
+    for (int e = 0; e < (BT ? 2 : 8); ++e)
+#pragma unroll
+      for (int j = 0; j < (BF == kPairs ? 1 : 2); ++j) {
+        if constexpr (BT) {
+          const f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)voff[j], e * 16, 0));
+#pragma unroll
+          for (int i = 0; i < 4; ++i) raw[set][j][e * 4 + i] = v[i];
+        } else if constexpr (BF == kPairs) {
+          const f32x2 v = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(rs, (int)voff[0], (int)(e * ks), 0));
+          raw[set][0][e] = v[0];
+          raw[set][1][e] = v[1];
+        } else {
+          raw[set][j][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (int)voff[j], (int)(e * ks), 0));
+        }
+      }
+  };
+  // The terms of a stage in b[t & 1].  The next stage's are made between the MFMAs of this one, a quarter of a
+  // pair of values (3 or 4 instructions, less than an MFMA takes) at a time.
+  u32x4 b[2][2][3];
+  float ra = 0.f, rb = 0.f;
+  auto split_step = [&](float (&v)[2][8], int set, int n) {
+    const int j = n >> 4, e = n >> 2 & 3;
+    u32x4(&q)[3] = b[set][j];
+    // keeps a step where it is written: it would be moved in front of all MFMAs
+    if (n & 3)
+      asm volatile("" : "+v"(ra), "+v"(rb));
+    else
+      asm volatile("" : "+v"(v[j][2 * e]), "+v"(v[j][2 * e + 1]));
+    switch (n & 3) {
+      case 0:
+        ra = v[j][2 * e] * kSplitScale;
+        rb = v[j][2 * e + 1] * kSplitScale;
+        q[0][e] = cvt_pk_bf16(ra, rb);
+        break;
+      case 1:
+        ra -= bf16_lo(q[0][e]);
+        rb -= bf16_hi(q[0][e]);
+        break;
+      case 2:
+        q[1][e] = cvt_pk_bf16(ra, rb);
+        ra -= bf16_lo(q[1][e]);
+        break;
+      default:
+        rb -= bf16_hi(q[1][e]);
+        q[2][e] = cvt_pk_bf16(ra, rb);
+    }
+  };
+
+  // ---- A: through LDS.  Units of 16 rows and one term, 1 KiB, in lane order: packed ones are moved there directly,
+  // fp32 values pass through registers
+  float av[DIRECT ? AP : 1][8];
+  unsigned a_voff[DIRECT ? AP : 1];
+  const unsigned char* Ap = nullptr;
+  const float* Ad = nullptr;
+  const int last_unit = (p.Mpad - m0) / 16 * 3 - 1;
+  if constexpr (DIRECT) {
+    const int r0 = m0 / p.a_taps;
+    Ad = reinterpret_cast<const float*>(p.A) + g * p.a_gs + (long long)r0 * p.a_ms;
+#pragma unroll
+    for (int u = 0; u < AP; ++u) {
+      const int m = min(m0 + (wave + 4 * u) * 16 + lo, p.M - 1), r = m / p.a_taps;
+      a_voff[u] = (unsigned)((r - r0) * p.a_ms + (m - r * p.a_taps) + kg * 8 * p.a_ks) * 4u;
     }
   } else {
-    const int c = tid & 127;
-    voff[0] = (unsigned)(col_offset(p.bmap, min(n0 + c, p.Ncols - 1)) - (long long)n_f * p.bmap.img_stride) * 4u;
-#pragma unroll
-    for (int u = 0; u < GPT; ++u) dst[u] = ((wave >> 1) + 2 * u) * PLANE + c * 16;
+    Ap = reinterpret_cast<const unsigned char*>(p.A) + (long long)g * p.a_gs * 6 + (long long)m0 / 16 * 3072;
   }
-  float stg[2][GPT][8];
-  auto stage_load = [&](int set, int t) {
-    const int k0 = t * SK;
+  auto move_a = [&](int t, int slot) {
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<float*>(Bt + (BT ? (long long)k0 : k0 * p.b_ks)), 0, 0x7fffffff, 0x00020000);
+        const_cast<unsigned char*>(Ap + (long long)t * p.Mpad * 192), 0, 0x7fffffff, 0x00020000);
 #pragma unroll
-    for (int u = 0; u < GPT; ++u) {
-      if constexpr (BT) {
-        if (k0 + SK > kd) {  // the last stage ends inside a row
+    for (int u = 0; u < AP; ++u)
+      if (4 * u + 4 <= UNITS || wave + 4 * u < UNITS)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr)(As + slot * SLOT + (wave + 4 * u) * 1024), 16, lane * 16,
+                                                 min(wave + 4 * u, last_unit) * 1024, 0, 0);
+  };
+  const long long a_left = DIRECT ? p.a_len - (Ad - reinterpret_cast<const float*>(p.A)) : 0;
+  auto load_a = [&](int t) {
+    const long long at = (long long)t * SK * (AF == kRows ? 1 : p.a_ks);
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(Ad + at), 0, range(a_left - at), 0x00020000);
 #pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const int kh = (tid + u * NT) % (SK / 8) * 8, k = min(kh + e, kd - 1 - k0);
-            stg[set][u][e] = __builtin_bit_cast(
-                float, __builtin_amdgcn_raw_buffer_load_b32(rs, (int)(voff[u] + (unsigned)(k - kh) * 4u), 0, 0));
-          }
-          continue;
-        }
+    for (int u = 0; u < AP; ++u) {
+      if (4 * u + 4 > RB && wave + 4 * u >= RB) continue;
+      if constexpr (AF == kRows) {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-          const f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)voff[u], h * 16, 0));
+          const f32x4 x = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)a_voff[u], h * 16, 0));
 #pragma unroll
-          for (int e = 0; e < 4; ++e) stg[set][u][h * 4 + e] = v[e];
-        }
-      } else {
-        // k past the last one repeats it (A is zero there)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const int k = min(((wave >> 1) + 2 * u) * 8 + e, kd - 1 - k0);
-          stg[set][u][e] = __builtin_bit_cast(
-              float, __builtin_amdgcn_raw_buffer_load_b32(rs, (int)voff[0], (int)((unsigned)k * (unsigned)p.b_ks * 4u), 0));
-        }
-      }
-    }
-  };
-  auto stage_store = [&](int set, int slot, int u) {
-    u32x4 h, m, l;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      unsigned a, b, c;
-      split_pair(stg[set][u][2 * e], stg[set][u][2 * e + 1], &a, &b, &c);
-      h[e] = a;
-      m[e] = b;
-      l[e] = c;
-    }
-    unsigned char* d = Bs + slot * SLOT + dst[u];
-    *reinterpret_cast<u32x4*>(d) = h;
-    *reinterpret_cast<u32x4*>(d + (SK / 8) * PLANE) = m;
-    *reinterpret_cast<u32x4*>(d + 2 * (SK / 8) * PLANE) = l;
-  };
-
-  // ---- A straight from the pack (L2), a stage (two tiles) ahead
-  const unsigned short* Abase = reinterpret_cast<const unsigned short*>(p.A) +
-                                ((long long)g * p.a_gs * 3 + (long long)(m0 + wave_m * 32) * TK);
-  const __amdgpu_buffer_rsrc_t a_rs =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned short*>(Abase), 0, 0x7fffffff, 0x00020000);
-  const int a_voff = (lane_lo * TK + lane_hi * 8) * 2;
-  const unsigned term_b = (unsigned)p.Mpad * TK * 2u;
-  const int ktiles = TPS * stages;
-  u32x4 a[TPS][3];
-  // DIRECT: A lies in fp32, k-contiguous rows a_ms apart, and a lane splits the 8 values it supplies
-  const float* Ad = DIRECT ? reinterpret_cast<const float*>(p.A) + g * p.a_gs +
-                                 (long long)min(m0 + wave_m * 32 + lane_lo, p.M - 1) * p.a_ms + lane_hi * 8
-                           : nullptr;
-  auto load_a = [&](int set, int t) {
-    if constexpr (DIRECT) {
-      const int k0 = min(t, ktiles - 1) * TK, left = kd - k0 - lane_hi * 8;
-      float v[8];
-      if (k0 + TK <= kd) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const f32x4u q = *reinterpret_cast<const f32x4u*>(Ad + k0 + h * 4);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[h * 4 + e] = q[e];
+          for (int e = 0; e < 4; ++e) av[u][h * 4 + e] = x[e];
         }
       } else {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = e < left ? Ad[k0 + e] : 0.f;
+        for (int e = 0; e < 8; ++e)
+          av[u][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+              rs, (int)a_voff[u], (int)(e * (unsigned)p.a_ks * 4u), 0));
       }
+    }
+  };
+  auto store_a = [&](int t, int slot) {
+    const int over = kd - t * SK - kg * 8;  // a lane's values from here on are past the last k: zero
+#pragma unroll
+    for (int u = 0; u < AP; ++u) {
+      if (4 * u + 4 > RB && wave + 4 * u >= RB) continue;
+      u32x4 q[3];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) av[u][e] = e < over ? av[u][e] : 0.f;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        unsigned hh, mm, ll;
-        split_pair(v[2 * e], v[2 * e + 1], &hh, &mm, &ll);
-        a[set][0][e] = hh;
-        a[set][1][e] = mm;
-        a[set][2][e] = ll;
+        unsigned h, m, l;
+        split_pair(av[u][2 * e], av[u][2 * e + 1], &h, &m, &l);
+        q[0][e] = h;
+        q[1][e] = m;
+        q[2][e] = l;
       }
-      return;
+#pragma unroll
+      for (int i = 0; i < 3; ++i)
+        *reinterpret_cast<u32x4*>(As + slot * SLOT + ((wave + 4 * u) * 3 + i) * 1024 + lane * 16) = q[i];
     }
-    const unsigned so = (unsigned)min(t, ktiles - 1) * (3u * term_b);
-#pragma unroll
-    for (int q = 0; q < 3; ++q)
-      a[set][q] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(a_rs, a_voff, (int)(so + q * term_b), 0));
   };
 
-  floatx16 acc_h[WN], acc_c[WN];  // h*h, and the corrections
+  f32x4 acc_h[RB][2], acc_c[RB][2];  // h*h, and the corrections
 #pragma unroll
-  for (int j = 0; j < WN; ++j)
+  for (int i = 0; i < RB; ++i)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc_h[j][r] = acc_c[j][r] = 0.f;
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc_h[i][j][r] = acc_c[i][j][r] = 0.f;
 
-  stage_load(0, 0);
-  if (stages > 1) stage_load(1, 1);
+  const int last = stages - 1;  // past it, the last stage is fetched again: what is in flight is the same throughout
+  if constexpr (DIRECT) load_a(0); else move_a(0, 0);
+  load_b(0, 0);
+  if constexpr (DIRECT) {
+    store_a(0, 0);
+    load_a(min(1, last));
+  }
+  if constexpr (EARLY) move_a(min(1, last), 1);
+  if (RAWS == 2) load_b(1, min(1, last));
 #pragma unroll
-  for (int e = 0; e < TPS; ++e) load_a(e, e);
-#pragma unroll
-  for (int u = 0; u < GPT; ++u) stage_store(0, 0, u);
-  if (stages > 2) stage_load(0, 2);
+  for (int n = 0; n < 32; ++n) split_step(raw[0], 0, n);
+  load_b(0, min(RAWS, last));
+  if constexpr (!DIRECT) __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
 
-  const int b_lds = lane_hi * PLANE + (wave_n * WN * 32 + lane_lo) * 16;
-  u32x4 b[NB][3];
-  auto read_b = [&](int set, int j, int base) {
-#pragma unroll
-    for (int q = 0; q < 3; ++q)
-      b[set][q] = *reinterpret_cast<const u32x4*>(Bs + base + b_lds + j * 512 + q * (SK / 8) * PLANE);
+  // Two sets of A's operands; where registers decide how many workgroups share a CU, one, read term by term
+  constexpr int SETS = RB == 2 ? 1 : 2;
+  u32x4 a[SETS][3];
+  auto read_a = [&](int i, int q, int at) {
+    a[i % SETS][q] = *reinterpret_cast<const u32x4*>(As + at * SLOT + (i % RB * 3 + q) * 1024 + lane * 16);
   };
-  auto mfma6 = [&](int set, int bs, int j) {
+  auto meet = [&]() {
+    if constexpr (DIRECT) {
+      __syncthreads();
+    } else {
+      // nothing of this wave's is under way to LDS but what may be; __syncthreads() waits for that too
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  // Loads of B that may be in flight when A of the next stage has to be in place: the last ones
+  constexpr int LEFT = RAWS == 2 && EARLY ? (BT ? 4 : BF == kPairs ? 8 : 16) : 0;
+  int slot = 0;  // of A
+  auto after = [&](int v) { return v == SLOTS - 1 ? 0 : v + 1; };
+  // One stage.  A's operands of a block of rows are read behind the MFMAs of the block before; B's next ones are split
+  // behind the last 36 MFMAs (of two blocks of rows: of all), then their registers are loaded once more.
+  auto stage = [&](int t, int set) {
+    const int next = after(slot);
+    if constexpr (!EARLY) {
+      meet();  // A of this stage is visible, nobody reads the other slot any more
+      if constexpr (!DIRECT) move_a(min(t + 1, last), next);
+#pragma unroll
+      for (int q = 0; q < 3; ++q) read_a(0, 2 - q, slot);
+    }
     __builtin_amdgcn_sched_barrier(0);
-#define CCT_M(X, Y, ACC)                                                                \
-  ACC = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[set][X]),   \
-                                                __builtin_bit_cast(bf16x8, b[bs][Y]), ACC, 0, 0, 0)
-    CCT_M(2, 0, acc_c[j]);
-    CCT_M(0, 2, acc_c[j]);
-    CCT_M(1, 1, acc_c[j]);
-    CCT_M(1, 0, acc_c[j]);
-    CCT_M(0, 1, acc_c[j]);
-    CCT_M(0, 0, acc_h[j]);
-#undef CCT_M
-    __builtin_amdgcn_sched_barrier(0);
-  };
-  __syncthreads();  // slot 0 is visible
-  if (NB == 2) read_b(0, 0, 0);
-
-  // One stage: TPS tiles of WN blocks (NB = 2: block i + 1 is read while block i is multiplied).  The
-  // values of stage t + 1 (set `nset`) are split into the other slot behind the first blocks, their
-  // registers are loaded with stage t + 3; the workgroup meets before the next stage's first read.
-  auto stage = [&](int t, int slot, int nset) {
-    const bool more = t + 1 < stages;
-    const int base = slot * SLOT, other = (slot ^ 1) * SLOT;
 #pragma unroll
-    for (int i = 0; i < TPS * WN; ++i) {
-      const int tt = i / WN, j = i % WN;
-      if (NB == 1) {
-        read_b(0, j, base + tt * 2 * PLANE);
-      } else if (i + 1 < TPS * WN) {
-        read_b((i + 1) % NB, (i + 1) % WN, base + ((i + 1) / WN) * 2 * PLANE);
-      } else if (more) {
-        __syncthreads();
-        read_b(0, 0, other);
+    for (int i = 0; i < RB; ++i) {
+      if (EARLY && i == RB - 1) {
+        __builtin_amdgcn_s_waitcnt(0x0f70 | (LEFT & 15) | (LEFT >> 4 << 14));
+        meet();  // A of the next stage is visible, nobody reads the slot before this one any more
+        move_a(min(t + 2, last), after(next));
       }
-      if (tt == 0 || more || !half) mfma6(tt, i % NB, j);
-      if (j == WN - 1) load_a(tt, TPS * (t + 1) + tt);
-      if (more && i < GPT) {
-        stage_store(nset, slot ^ 1, i);
-        if (i == GPT - 1 && t + 3 < stages) stage_load(nset, t + 3);
+      auto read = [&](int q) {
+        if (i + 1 < RB) read_a(i + 1, q, slot);
+        else if (EARLY) read_a(i + 1, q, next);
+      };
+      auto mfma = [&](int k, int x, int y, f32x4 (&acc)[2]) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[i % SETS][x]),
+                                                           __builtin_bit_cast(bf16x8, b[set][j][y]), acc[j], 0, 0, 0);
+          const int n = i * 12 + k + j - (RB * 12 - (RB > 2 ? 36 : 22));
+          if (RB > 2 && n >= 0 && n < 32) split_step(raw[RAWS == 2 ? set ^ 1 : 0], set ^ 1, n);
+          if (RB == 2 && n >= 0 && n < 16) {
+            split_step(raw[RAWS == 2 ? set ^ 1 : 0], set ^ 1, 2 * n);
+            split_step(raw[RAWS == 2 ? set ^ 1 : 0], set ^ 1, 2 * n + 1);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      };
+      if (SETS == 2) read(2);
+      mfma(0, 2, 0, acc_c[i]);
+      read(SETS == 2 ? 1 : 2);
+      mfma(2, 1, 1, acc_c[i]);
+      if (SETS == 2) read(0);
+      mfma(4, 1, 0, acc_c[i]);
+      if (SETS == 1) read(1);
+      mfma(6, 0, 2, acc_c[i]);
+      mfma(8, 0, 1, acc_c[i]);
+      mfma(10, 0, 0, acc_h[i]);
+      if (SETS == 1) read(0);
+      if (DIRECT && i == (RB - 1) / 2) {
+        store_a(min(t + 1, last), next);
+        load_a(min(t + 2, last));
       }
     }
-    if (NB == 1) __syncthreads();
+    if constexpr (!DIRECT && !EARLY) __builtin_amdgcn_s_waitcnt(0x0f70);  // A of the next stage is in place
+    load_b(RAWS == 2 ? set ^ 1 : 0, min(t + 1 + RAWS, last));
+    slot = next;
   };
+  if constexpr (EARLY) {
+    meet();
+#pragma unroll
+    for (int q = 0; q < 3; ++q) read_a(0, 2 - q, 0);
+  }
   int t = 0;
   for (; t + 1 < stages; t += 2) {
-    stage(t, 0, 1);
-    stage(t + 1, 1, 0);
+    stage(t, 0);
+    stage(t + 1, 1);
   }
-  if (t < stages) stage(t, 0, 1);
+  if (t < stages) stage(t, 0);
+  if constexpr (!DIRECT) __builtin_amdgcn_s_waitcnt(0x0f70);  // nothing is moved into LDS after the end
 
-  // ---- epilogue: accumulator register r is row 8*(r/4) + 4*(lane/32) + r%4 of the wave's rows
-  const int mw = m0 + wave_m * 32;
+  // ---- epilogue: a lane holds rows 16 i + 4 kg .. + 3 of its two columns
+  const int mw = m0 + kg * 4;
   float* __restrict__ C = p.C + (long long)g * p.c_gs;
   const float* bias = p.bias ? p.bias + (p.bias_gs < 0 ? 0 : (long long)g * p.bias_gs) : nullptr;
   // NaN once a result is not finite: one instruction each (compares, whose answers are collected in scalar masks,
   // took 2 % of fc6's products and 4 % of a 4096 -> 1000 layer's)
   float check = 0.f;
+  const int c0 = min(col0, p.Ncols - 1), c1 = min(col0 + 1, p.Ncols - 1);
+  const long long o0 = col_offset(p.cmap, c0), o1 = col_offset(p.cmap, c1);
+  const bool both = __all(o1 == o0 + 1);
+  float* __restrict__ cl0 = C + o0 + (long long)mw * p.c_ms;
+  float* __restrict__ cl1 = C + o1 + (long long)mw * p.c_ms;
+  const float cb0 = bias && p.bias_gs < 0 ? bias[c0] : 0.f, cb1 = bias && p.bias_gs < 0 ? bias[c1] : 0.f;
 #pragma unroll
-  for (int j = 0; j < WN; ++j) {
-    const int col = n0 + wave_n * WN * 32 + j * 32 + lane_lo;
-    if (col >= p.Ncols) continue;
-    float* __restrict__ cl = C + col_offset(p.cmap, col);
+  for (int i = 0; i < RB; ++i)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int m = mw + (r >> 2) * 8 + lane_hi * 4 + (r & 3);
+    for (int r = 0; r < 4; ++r) {
+      const int m = mw + i * 16 + r;
+      float v[2];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        v[j] = acc_h[i][j][r] + acc_c[i][j][r];
+        check = fmaf(v[j], 0.f, check);
+        v[j] *= kSplitUnscale;
+      }
       if (m >= p.M) continue;
-      float v = acc_h[j][r] + acc_c[j][r];
-      check = fmaf(v, 0.f, check);
-      v *= kSplitUnscale;
-      if (bias) v += bias[p.bias_gs < 0 ? col : m];
-      cl[(long long)m * p.c_ms] = v;
+      if (bias) {
+        const float rb = p.bias_gs < 0 ? 0.f : bias[m];
+        v[0] += p.bias_gs < 0 ? cb0 : rb;
+        v[1] += p.bias_gs < 0 ? cb1 : rb;
+      }
+      const long long row = (long long)(i * 16 + r) * p.c_ms;
+      if (both) {
+        *reinterpret_cast<f32x2u*>(cl0 + row) = f32x2u{v[0], v[1]};
+      } else {
+        if (col0 < p.Ncols) cl0[row] = v[0];
+        if (col0 + 1 < p.Ncols) cl1[row] = v[1];
+      }
     }
-  }
   if (!__any(check != check)) return;
+  __threadfence_block();  // what the other lanes have stored is read below
   // blocks with results that are not finite: again in plain fp32 (split_bf16.h)
   const GemmTN& q = first_argument<GemmTN>();
+  const int lane_lo = lane & 31, lane_hi = lane >> 5;
   float* Cq = q.C + (long long)g * q.c_gs;
   const float* Bq = reinterpret_cast<const float*>(q.B) + (long long)g * q.b_gs;
   const float* bq = q.bias ? q.bias + (q.bias_gs < 0 ? 0 : (long long)g * q.bias_gs) : nullptr;
+  const int col = n0 + wave * 32 + lane_lo, c = min(col, q.Ncols - 1);
+  const float* bc = Bq + (BT ? (long long)c * q.b_ks : col_offset(q.bmap, c));
 #pragma unroll 1
-  for (int j = 0; j < WN; ++j) {
-    const int col = n0 + wave_n * WN * 32 + j * 32 + lane_lo, c = min(col, q.Ncols - 1);
-    float* cl = Cq + col_offset(q.cmap, c) + (long long)(mw + lane_hi * 4) * q.c_ms;
+  for (int i = 0; i < (RB + 1) / 2; ++i) {  // 32 rows; the last ones may be the next tile's: not looked at
+    const int mb = m0 + i * 32, m_end = min(m0 + BM, q.M);
+    float* cl = Cq + col_offset(q.cmap, c) + (long long)(mb + lane_hi * 4) * q.c_ms;
     unsigned todo = 0;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int rr = (r >> 2) * 8 + (r & 3);
-      if (col < q.Ncols && mw + lane_hi * 4 + rr < q.M && !finite(cl[(long long)rr * q.c_ms])) todo |= 1u << r;
+      if (col < q.Ncols && mb + lane_hi * 4 + rr < m_end && !finite(cl[(long long)rr * q.c_ms])) todo |= 1u << r;
     }
     if (!__any(todo)) continue;
-    const float* bc = Bq + (BT ? (long long)c * q.b_ks : col_offset(q.bmap, c));
-    const int m = min(mw + lane_lo, q.M - 1);
+    const int m = min(mb + lane_lo, q.M - 1);
     const floatx16 v = fp32_block(
         (kd + 1) / 2,
         [&](int s) {
           const int k = 2 * s + lane_hi;
           if (k >= kd) return 0.f;
-          if constexpr (DIRECT) return reinterpret_cast<const float*>(q.A)[g * q.a_gs + m * q.a_ms + k];
+          if constexpr (DIRECT)
+            return reinterpret_cast<const float*>(q.A)[g * q.a_gs + m / q.a_taps * q.a_ms + m % q.a_taps + k * q.a_ks];
           const unsigned short* ak = reinterpret_cast<const unsigned short*>(q.A) + (long long)g * q.a_gs * 3 +
-                                     ((long long)(k / TK) * 3 * q.Mpad + m) * TK + k % TK;
-          const long long term = (long long)q.Mpad * TK;
-          return join_value(ak[0], ak[term], ak[2 * term]);
+                                     ((long long)(k / SK) * (q.Mpad / 16) + m / 16) * 1536 + (k % SK / 8 * 16 + m % 16) * 8 + k % 8;
+          return join_value(ak[0], ak[512], ak[1024]);
         },
         [&](int s) {
           const int k = 2 * s + lane_hi;
@@ -318,14 +412,15 @@ __global__ __launch_bounds__(NT, WAVES_M == 4 ? 2 : WAVES_M == 1 && !BT ? 6 : 4)
       if (!(todo >> r & 1)) continue;
       const int rr = (r >> 2) * 8 + (r & 3);
       float sum = v[r];
-      if (bq) sum += bq[q.bias_gs < 0 ? col : mw + lane_hi * 4 + rr];
+      if (bq) sum += bq[q.bias_gs < 0 ? col : mb + lane_hi * 4 + rr];
       cl[(long long)rr * q.c_ms] = sum;
     }
   }
 }
 
-// pack[g][tile][term][m][16] = the terms of src[g * sg + (m / taps) * sm + m % taps + k * sk], zero padded in
-// m and k: k runs over min(Kdim, Ktotal - g * Kdim) indices.
+// pack[g][stage][block of 16 rows][term][lane][8] = the terms of src[g * sg + (m / taps) * sm + m % taps + k * sk], zero
+// padded in m and k, where lane stands for row m = 16 block + lane % 16 and k = 32 stage + lane / 16 * 8 + 0 .. 7: k
+// runs over min(Kdim, Ktotal - g * Kdim) indices.
 struct RowsPack {
   int G, M, Mpad, Kpad, Kdim, Ktotal;
   long long sm, sk, sg;
@@ -338,10 +433,10 @@ __global__ __launch_bounds__(256) void pack_rows_split_kernel(const float* __res
   if (t >= per * d.G) return;
   const int g = (int)(t / per);
   const long long e = t - g * per;
-  const int half = (int)(e & 1);
-  const long long r = e >> 1;
-  const int tile = (int)(r / d.Mpad), m = (int)(r - (long long)tile * d.Mpad);
-  const int k0 = tile * TK + half * 8;
+  const int lane = (int)(e & 63);
+  const long long r = e >> 6;
+  const int blocks = d.Mpad / 16, stage = (int)(r / blocks), m = (int)(r - (long long)stage * blocks) * 16 + (lane & 15);
+  const int k0 = stage * SK + (lane >> 4) * 8;
   const int kd = min(d.Kdim, d.Ktotal - g * d.Kdim);
   const int row = m / d.taps;
   const float* s = src + g * d.sg + row * d.sm + (m - row * d.taps) + k0 * d.sk;
@@ -351,8 +446,7 @@ __global__ __launch_bounds__(256) void pack_rows_split_kernel(const float* __res
     const float v = m < d.M && k0 + i < kd ? s[i * d.sk] : 0.f;
     split_value(v, &h[i], &mm[i], &l[i]);
   }
-  unsigned short* dst = pack + (((long long)g * (d.Kpad / TK) + tile) * 3 * d.Mpad + m) * TK + half * 8;
-  const long long term = (long long)d.Mpad * TK;
+  unsigned short* dst = pack + ((long long)g * d.Kpad * d.Mpad * 3) + r * 1536 + lane * 8;
   auto put = [](unsigned short* to, const unsigned short (&v)[8]) {
     uint4 q;
     q.x = v[0] | ((unsigned)v[1] << 16);
@@ -362,28 +456,14 @@ __global__ __launch_bounds__(256) void pack_rows_split_kernel(const float* __res
     *reinterpret_cast<uint4*>(to) = q;
   };
   put(dst, h);
-  put(dst + term, mm);
-  put(dst + 2 * term, l);
-}
-
-template <int WAVES_M, bool BT, bool DIRECT = false>
-int launch_variant(const GemmTN& p, int Ktotal, hipStream_t st) {
-  const int tiles_m = p.Mpad / (32 * WAVES_M), tiles_n = (p.Ncols + BN - 1) / BN;
-  const long long blocks = (long long)tiles_m * tiles_n;
-  if (blocks <= 0 || blocks >= 2147483647LL || p.G < 1 || p.G > 65535) return CCT_EUNSUPPORTED;
-  const double mk = (double)p.M * p.Kdim * p.G, kn = (double)p.Kdim * p.Ncols * p.G;
-  ProfScope ps(2.0 * p.M * kn, 6.0 * mk + 4.0 * kn + 4.0 * (double)p.M * p.Ncols * p.G, st,
-               "gemm_split<%d, %s>", 32 * WAVES_M, BT ? "k-contiguous" : "in place");
-  hipLaunchKernelGGL((gemm_split<WAVES_M, BT, DIRECT>), dim3((unsigned)blocks, (unsigned)p.G), dim3(NT), 0, st, p, Ktotal,
-                     tiles_m, tiles_n);
-  CCT_CHECK_LAUNCH();
-  return CCT_OK;
+  put(dst + 512, mm);
+  put(dst + 1024, l);
 }
 
 }  // namespace
 
 int gemm_split_mpad(int M) { return M <= 32 ? 32 : (M + 63) / 64 * 64; }
-int gemm_split_kpad(int K) { return (K + KPAD - 1) / KPAD * KPAD; }
+int gemm_split_kpad(int K) { return (K + SK - 1) / SK * SK; }
 
 // 32-bit byte offsets: the pack of one group, B inside a stage of one column tile
 bool gemm_split_fits(const GemmTN& p, bool bt) {
@@ -395,46 +475,79 @@ bool gemm_split_fits(const GemmTN& p, bool bt) {
                                 : (T + 1) * p.bmap.img_stride < (1LL << 28);
 }
 
-// Row tile: the largest that divides the padded rows, smaller while the launch would not put a workgroup
-// on every CU.  Up to 128 k a workgroup is mostly filling and draining: 64 rows put twice as many on a CU
-// (118 images of 30 x 30, 41 -> 105 channels: 43 us with 128 rows, 32 with 64; at 256 k, fc6's
-// backward-weights product, 135 against 149).
-int gemm_split_bm(int Mpad, long long tiles_n, int K, int G) {
-  int BM = Mpad % 128 == 0 && K > 128 ? 128 : Mpad % 64 == 0 ? 64 : 32;
-  long long wgs = tiles_n * ((unsigned)Mpad / (unsigned)BM) * G;
-  for (; BM > 32 && wgs < 256; BM /= 2) wgs *= 2;
-  return BM;
+namespace {
+// The forms: tiles of 32 and 64 rows, which read A in place and split it themselves, and of 128 and 144, for which it is
+// packed first.  A launch less is what counts where the chip is not full (33 to 512 images of fully connected layers,
+// up to 2 GFLOP: 0.6 to 0.8 times the time of a pack and a product); large products split A once per column tile too often.
+
+// 32-bit byte offsets in A in place, from a tile's first row and a stage's first k
+bool in_place_fits(long long sm, long long sk, int taps) { return (64 / taps + 2) * sm + taps + 32 * sk < (1LL << 29); }
+
+// What a launch takes, in us: rounds of workgroups, each as long as its stages take a workgroup that has its CU alone,
+// what every further one on the CU adds per stage and to fill and drain; the launch; the pack (4.3 us and so many per
+// million values).  Not less than its bytes at the rate the form streams at.  Fitted to 1160 products of 2 MFLOP to 200
+// GFLOP, each with every form, inputs from memory: off by 3 to 10 % in the mean; the form with the lowest estimate takes
+// 0.5 to 2 % longer than the best one in the mean.  Per stage of 32 k and workgroup: 64 rows alone 1.0, among three
+// 0.68; 144 rows alone 1.36, among two 1.11 (its MFMAs: 0.75).
+struct Form {
+  int rb, share;  // workgroups that a CU holds
+  struct Rate {
+    double stage, next, fill, launch, pack, bytes, next_fill;
+  } rate[2];  // B column-contiguous, k-contiguous
+};
+constexpr Form kForms[4] = {
+    {2, 4, {{0.885, 0.322, 1.723, 2.504, 0.00, 3.34e6, 1.138}, {1.094, 0.372, 0.000, 3.194, 0.00, 2.79e6, 0.789}}},
+    {4, 3, {{1.010, 0.517, 1.152, 3.516, 0.00, 3.74e6, 1.983}, {0.929, 0.680, 0.000, 4.514, 0.00, 4.13e6, 0.304}}},
+    {8, 2, {{1.226, 0.773, 1.057, 4.257, 5.98, 2.48e6, 3.112}, {1.034, 0.967, 1.682, 3.886, 5.10, 3.15e6, 0.000}}},
+    {9, 2, {{1.356, 0.867, 1.333, 3.711, 6.00, 2.75e6, 2.727}, {1.333, 1.106, 0.000, 4.913, 4.80, 3.02e6, 0.000}}}};
+
+double form_us(const Form& f, bool bt, int M, int K, long long cols, long long G) {
+  const Form::Rate& r = f.rate[bt];
+  const unsigned long long tiles_m = ((unsigned)M + 16u * f.rb - 1) / (16u * f.rb);
+  const unsigned long long per_cu = (tiles_m * ((cols + BN - 1) / BN) * G + 255) / 256, rounds = per_cu / f.share;
+  const int rest = (int)(per_cu - rounds * f.share), stages = (int)(((unsigned)K + SK - 1) / SK);
+  auto round = [&](int n) { return n ? stages * (r.stage + (n - 1) * r.next) + r.fill + (n - 1) * r.next_fill : 0.0; };
+  double t = (double)rounds * round(f.share) + round(rest) + r.launch;
+  if (f.rb > 4) t += 4.3 + r.pack * 1e-6 * (double)((M + 63) / 64 * 64) * (stages * (double)SK) * G;
+  const double values = (double)G * ((double)K * cols + (double)M * cols + (double)M * K);
+  return std::max(t, 4.0 * values / r.bytes + r.launch);
 }
 
-// Rounds of workgroups (512 of 128 rows fit the chip, 1024 of fewer) times their stages at the measured
-// rates, 4 us to fill and drain a round.  Where the fullest CU holds fewer of them than fit, each is faster,
-// but a lone workgroup of 128 rows still takes two thirds as long as one of two.
-double gemm_split_seconds(int Mpad, int K, long long cols, long long G) {
-  const long long tiles_n = (cols + BN - 1) / BN;
-  const int BM = gemm_split_bm(Mpad, tiles_n, K, (int)G);
-  const int log_bm = BM == 128 ? 7 : BM == 64 ? 6 : 5, log_slots = BM == 128 ? 9 : 10;
-  const unsigned long long wgs = (unsigned long long)tiles_n * (Mpad >> log_bm) * G, slots = 1ULL << log_slots;
-  const double flops = BM == 128 ? 1.0 / 230.0e12 : BM == 64 ? 1.0 / 200.0e12 : 1.0 / 120.0e12;
-  const double stage = 2.0 * BM * BN * 32 * flops * (double)slots;
-  const double rounds = (double)((wgs + slots - 1) >> log_slots);
-  const double share = std::min(1.0, 0.3 + 0.7 * (double)((wgs + 255) >> 8) * (256.0 / (double)slots));
-  return rounds * ((K + 31) / 32 * stage * share + 4.0e-6);
-}
-
-int launch_gemm_split(const GemmTN& p0, int Ktotal, bool bt, hipStream_t st) {
-  GemmTN p = p0;
-  colmap_prepare(&p.bmap);
-  colmap_prepare(&p.cmap);
-  if (p.Mpad != gemm_split_mpad(p.M) || p.Kpad != gemm_split_kpad(p.Kdim)) return CCT_EINVAL;
-  if (!gemm_split_fits(p, bt)) return CCT_EUNSUPPORTED;
-  const int BM = gemm_split_bm(p.Mpad, (p.Ncols + BN - 1) / BN, p.Kdim, p.G);
-  if (p.a_ms) return bt && p.M <= 32 ? launch_variant<1, true, true>(p, Ktotal, st) : CCT_EUNSUPPORTED;
-  if (bt) {
-    if (BM == 32) return launch_variant<1, true>(p, Ktotal, st);
-    return BM == 64 ? launch_variant<2, true>(p, Ktotal, st) : launch_variant<4, true>(p, Ktotal, st);
+template <class Fits>
+const Form* choose(bool bt, int M, int K, long long cols, long long G, Fits fits, double* us) {
+  const Form* best = nullptr;
+  for (const Form& f : kForms) {
+    if (!fits(f)) continue;
+    const double t = form_us(f, bt, M, K, cols, G);
+    if (!best || t < *us) {
+      best = &f;
+      *us = t;
+    }
   }
-  if (BM == 32) return launch_variant<1, false>(p, Ktotal, st);
-  return BM == 64 ? launch_variant<2, false>(p, Ktotal, st) : launch_variant<4, false>(p, Ktotal, st);
+  return best;
+}
+
+template <int RB, BForm BF, AForm AF>
+int launch_variant(const GemmTN& p, int Ktotal, hipStream_t st) {
+  const int tiles_m = (p.M + 16 * RB - 1) / (16 * RB), tiles_n = (p.Ncols + BN - 1) / BN;
+  const long long blocks = (long long)tiles_m * tiles_n;
+  if (blocks <= 0 || blocks >= 2147483647LL || p.G < 1 || p.G > 65535) return CCT_EUNSUPPORTED;
+  const double mk = (double)p.M * p.Kdim * p.G, kn = (double)p.Kdim * p.Ncols * p.G;
+  ProfScope ps(2.0 * p.M * kn, (AF == kPacked ? 6.0 : 4.0) * mk + 4.0 * kn + 4.0 * (double)p.M * p.Ncols * p.G, st,
+               "gemm_split<%d, %s>", 16 * RB, BF == kContiguous ? "k-contiguous" : "in place");
+  hipLaunchKernelGGL((gemm_split<RB, BF, AF>), dim3((unsigned)blocks, (unsigned)p.G), dim3(NT), 0, st, p, Ktotal,
+                     tiles_m, tiles_n);
+  CCT_CHECK_LAUNCH();
+  return CCT_OK;
+}
+
+template <BForm BF>
+int launch_columns(const GemmTN& p, int Ktotal, hipStream_t st) {
+  if (!p.a_ms) return p.rb == 8 ? launch_variant<8, BF, kPacked>(p, Ktotal, st) : launch_variant<9, BF, kPacked>(p, Ktotal, st);
+  if (p.a_ks == 1 && p.a_taps == 1)
+    return p.rb == 2 ? launch_variant<2, BF, kRows>(p, Ktotal, st) : launch_variant<4, BF, kRows>(p, Ktotal, st);
+  if constexpr (BF == kContiguous) return CCT_EUNSUPPORTED;
+  else return p.rb == 2 ? launch_variant<2, BF, kStrided>(p, Ktotal, st) : launch_variant<4, BF, kStrided>(p, Ktotal, st);
 }
 
 int launch_pack_rows_split(const float* src, void* pack, int G, int M, int Mpad, int Kpad, int Kdim, int Ktotal,
@@ -447,6 +560,49 @@ int launch_pack_rows_split(const float* src, void* pack, int G, int M, int Mpad,
                      reinterpret_cast<unsigned short*>(pack), d);
   CCT_CHECK_LAUNCH();
   return CCT_OK;
+}
+}  // namespace
+
+// `pack`: there is room for it.
+double gemm_split_seconds(bool bt, bool pack, int M, int K, long long cols, long long G) {
+  double us = 0.0;
+  choose(bt, M, K, cols, G, [&](const Form& f) { return pack || f.rb <= 4; }, &us);
+  return 1e-6 * us;
+}
+
+int gemm_split_operand(GemmTN* p, bool bt, const float* src, void* pack, int Ktotal, long long sm, long long sk, long long sg,
+                       int taps, hipStream_t st) {
+  const bool in_place = in_place_fits(sm, sk, taps);
+  double us;
+  const Form* f = choose(bt, p->M, p->Kdim, p->Ncols, p->G, [&](const Form& v) { return v.rb <= 4 ? in_place : pack != nullptr; }, &us);
+  if (!f) return CCT_EUNSUPPORTED;
+  p->rb = f->rb;
+  p->a_ms = 0;
+  if (f->rb > 4) {
+    p->A = pack;
+    p->a_gs = (long long)p->Mpad * p->Kpad;
+    return launch_pack_rows_split(src, pack, p->G, p->M, p->Mpad, p->Kpad, p->Kdim, Ktotal, sm, sk, sg, st, taps);
+  }
+  p->A = src;
+  p->a_gs = sg; p->a_ms = sm; p->a_ks = sk; p->a_taps = taps;
+  // elements of A from p->A on
+  p->a_len = (p->G - 1) * sg + (p->M - 1) / taps * sm + taps - 1 + (Ktotal - (p->G - 1) * (long long)p->Kdim - 1) * sk + 1;
+  return CCT_OK;
+}
+
+int launch_gemm_split(const GemmTN& p0, int Ktotal, bool bt, hipStream_t st) {
+  GemmTN p = p0;
+  colmap_prepare(&p.bmap);
+  colmap_prepare(&p.cmap);
+  if (p.Mpad != gemm_split_mpad(p.M) || p.Kpad != gemm_split_kpad(p.Kdim)) return CCT_EINVAL;
+  if (!gemm_split_fits(p, bt)) return CCT_EUNSUPPORTED;
+  // elements of B from p.B on
+  p.b_len = bt                        ? (long long)p.Ncols * p.b_ks
+            : p.bmap.P == 2147483647 ? Ktotal * p.b_ks
+                                     : (long long)(p.Ncols / p.bmap.P) * p.bmap.img_stride;
+  if (bt) return launch_columns<kContiguous>(p, Ktotal, st);
+  const bool pairs = p.Ncols % 2 == 0 && (p.bmap.P % 2 == 0 || p.bmap.P == 2147483647);
+  return pairs ? launch_columns<kPairs>(p, Ktotal, st) : launch_columns<kColumns>(p, Ktotal, st);
 }
 
 }  // namespace cct

@@ -199,3 +199,36 @@ def test_not_finite_forward_with_the_tensor_in_place(B, L):
     got, names = ran(B, lambda: gpu_forward(B, L, x, w, synth.make_bias(L, 5), 3))
     assert split(names), names
     check_not_finite(got, oracle.conv_forward(odims(oracle, L), x, w, synth.make_bias(L, 5)))
+
+
+# Every row tile with planes of odd and even size (columns one by one and in pairs): rows one short of a tile and one
+# beyond it, contractions that end inside a stage of 32, tiles across images, columns past a tile.
+TILES = [
+    (layer("m33_odd",    9,  67, 13, 13,  33, 1), 32),
+    (layer("m31_even",   9,  33, 14, 14,  31, 1), 32),
+    (layer("m127_even", 100, 65, 20, 20, 127, 1), 64),
+    (layer("m63_odd",  150,  97, 21, 21,  63, 1), 64),
+    (layer("m250_even", 128, 301, 14, 14, 250, 1), 128),
+    (layer("m257_odd", 160, 299, 13, 13, 255, 1), 128),
+    (layer("m143_even", 60,  33, 28, 28, 143, 1), 144),
+    (layer("m144_odd",  61,  67, 27, 27, 144, 1), 144),
+]
+
+
+@pytest.mark.parametrize("L,rows", TILES, ids=[L.name for L, _ in TILES])
+def test_row_tiles(B, L, rows):
+    x, w, b = synth.make_x(L, 6), synth.make_w(L, 6), synth.make_bias(L, 6)
+    got, names = ran(B, lambda: gpu_forward(B, L, x, w, b))
+    assert "gemm_split<%d, in place>" % rows in names, names
+    assert ("pack_rows_split_kernel" in names) == (rows > 64), names
+    assert rel_err(got, oracle.conv_forward(odims(oracle, L), x, w, b)) <= TOL_F32
+
+
+@pytest.mark.parametrize("N,F,O,rows", [(255, 4609, 2051, 128), (257, 4609, 2051, 144), (130, 2825, 257, 64)])
+def test_row_tiles_k_contiguous(B, N, F, O, rows):
+    """Fully connected forward: the kernels' columns k-contiguous, splits that end inside a stage."""
+    L = layer("fc", N, F, 1, 1, O, 1)
+    x, w, b = synth.make_x(L, 7), synth.make_w(L, 7), synth.make_bias(L, 7)
+    got, names = ran(B, lambda: gpu_forward(B, L, x, w, b))
+    assert "gemm_split<%d, k-contiguous>" % rows in names, names
+    assert rel_err(got, oracle.conv_forward(odims(oracle, L), x, w, b)) <= TOL_F32
