@@ -87,7 +87,7 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
                  : (unsigned)(col_offset(p.bmap, c) - (long long)n_f * p.bmap.img_stride + (long long)kg * 8 * p.b_ks) * 4u;
   }
   // k past the last one: what lies there, or zero beyond the tensor's end (A is zero there; an infinity only costs the
-  // recomputation)
+  // recomputation).  The range is checked against the vector offset alone: all of an address that may lie beyond goes there.
   const long long b_left = p.b_len - (Bt - reinterpret_cast<const float*>(p.B));
   auto range = [](long long left) { return left < 0 ? 0 : left >= 0x1fffffff ? 0x7fffffff : (int)left * 4; };
   float raw[RAWS][2][8];
@@ -95,21 +95,22 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
     const long long at = (long long)t * SK * (BT ? 1 : p.b_ks);
     const __amdgpu_buffer_rsrc_t rs =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(Bt + at), 0, range(b_left - at), 0x00020000);
-    const unsigned ks = (unsigned)p.b_ks * 4u;
+    unsigned ks = BT ? 4u : (unsigned)p.b_ks * 4u;
+    asm volatile("" : "+s"(ks));  // the sums below are not kept in registers between the stages
 #pragma unroll
     for (int e = 0; e < (BT ? 2 : 8); ++e)
 #pragma unroll
       for (int j = 0; j < (BF == kPairs ? 1 : 2); ++j) {
         if constexpr (BT) {
-          const f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)voff[j], e * 16, 0));
+          const f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(voff[j] + 4 * e * ks), 0, 0));
 #pragma unroll
           for (int i = 0; i < 4; ++i) raw[set][j][e * 4 + i] = v[i];
         } else if constexpr (BF == kPairs) {
-          const f32x2 v = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(rs, (int)voff[0], (int)(e * ks), 0));
+          const f32x2 v = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(rs, (int)(voff[0] + e * ks), 0, 0));
           raw[set][0][e] = v[0];
           raw[set][1][e] = v[1];
         } else {
-          raw[set][j][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (int)voff[j], (int)(e * ks), 0));
+          raw[set][j][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (int)(voff[j] + e * ks), 0, 0));
         }
       }
   };
@@ -177,13 +178,15 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
     const long long at = (long long)t * SK * (AF == kRows ? 1 : p.a_ks);
     const __amdgpu_buffer_rsrc_t rs =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(Ad + at), 0, range(a_left - at), 0x00020000);
+    unsigned ks = AF == kRows ? 4u : (unsigned)p.a_ks * 4u;
+    asm volatile("" : "+s"(ks));
 #pragma unroll
     for (int u = 0; u < AP; ++u) {
       if (4 * u + 4 > RB && wave + 4 * u >= RB) continue;
       if constexpr (AF == kRows) {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-          const f32x4 x = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)a_voff[u], h * 16, 0));
+          const f32x4 x = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(a_voff[u] + 4 * h * ks), 0, 0));
 #pragma unroll
           for (int e = 0; e < 4; ++e) av[u][h * 4 + e] = x[e];
         }
@@ -191,7 +194,7 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
 #pragma unroll
         for (int e = 0; e < 8; ++e)
           av[u][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
-              rs, (int)a_voff[u], (int)(e * (unsigned)p.a_ks * 4u), 0));
+              rs, (int)(a_voff[u] + e * ks), 0, 0));
       }
     }
   };
