@@ -334,8 +334,8 @@ double plain_seconds(const cct_conv_desc_t& d, int pass, const Geom& g, double c
 // computes fp32 layers by the same rule.  Measured over 500 layers of 1 to 1024 images: up to 2.9 times as fast where it
 // is chosen (conv3 at batch 1024: 2880 -> 1590 us).  Calls under 35 us, whose three launches weigh: 2 % of them
 // are more than 15 % slower, by up to 8 us (7 images of 12 x 12, 243 -> 51 channels: 22 us against 30);
-// it stays off for a single image (conv3: 31 us against 38), 3 channels (conv1 at batch 256: 697 us
-// against 997) and 1 x 1 kernels at stride 2 (they use a quarter of the x that would be rewritten).
+// it stays off for a single image (conv3: 31 us against 38)
+// and 1 x 1 kernels at stride 2 (they use a quarter of the x that would be rewritten).
 bool batch_img_plan(const cct_conv_desc_t& d, const Geom& g) {
   if (g.asked.img_plan < 0) g.asked.img_plan = bwdw_img_plan(d, d.N, &g.asked.ip);
   return g.asked.img_plan;
@@ -347,6 +347,7 @@ bool bwdw_img_wins(const cct_conv_desc_t& d, int type, const Geom& g) {
   auto wins = [&]() {
     if (!batch_img_plan(d, g)) return false;
     const double cost = layout_cost(d, CCT_PASS_BACKWARD_WEIGHTS, type, g);
+    if (p.few) return p.seconds < kFewMargin * plain_seconds(d, CCT_PASS_BACKWARD_WEIGHTS, g, cost);
     // few kernels: Types 2 and 3, which take the taps into the rows, are better than their estimates
     // (53 images of 41 x 41, two groups of 171 channels and 19 kernels: 259 us against 294)
     if (d.precision == CCT_PREC_F32 && 2 * g.Og < p.BM) return p.seconds < 0.85 * cost;

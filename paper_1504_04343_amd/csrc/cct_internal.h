@@ -183,12 +183,26 @@ double gemm_split_seconds(bool bt, bool pack, int M, int K, long long cols, long
 int gemm_split_operand(GemmTN* p, bool bt, const float* src, void* pack, int Ktotal, long long sm, long long sk, long long sg,
                        int taps, hipStream_t st);
 
+// The product of the backward-weights pass of layers with few channels, x and dy in place (conv_bwdw_few.hip): S partial
+// sums of dw, ordered (tap, channel), and with `sums` S rows of dbias.  A plan for fewer images is no larger.
+struct BwdwFewPlan {
+  int rb, cb, segs, seg_rows, S;
+  long long lds;
+  double seconds;  // of the whole pass
+};
+// It runs up to this many times the estimate of what would run otherwise, which is a fifth short there in the mean.
+constexpr double kFewMargin = 1.2;
+bool bwdw_few_plan(const cct_conv_desc_t& d, long long nimg, BwdwFewPlan* P);
+int launch_bwdw_few(const cct_conv_desc_t& d, const BwdwFewPlan& P, int nimg, const float* x, const float* dy, float* part,
+                    float* sums, hipStream_t st);
 // Backward-weights pass on granules of 8 images (conv_bwdw_img.hip), fp32 as three bf16 terms or bf16:
 // plan for nimg images at a time and the workspace it needs.  false = sizes it cannot address.
 struct BwdwImgPlan {
   int BM, terms, S, split_cols;
   long long xs_off, ds_off, part_off, sums_off, total;  // workspace layout (bytes)
   double seconds;  // estimate for the optimizer's cost model
+  int few;         // on conv_bwdw_few instead, as fp says
+  BwdwFewPlan fp;
 };
 bool bwdw_img_plan(const cct_conv_desc_t& d, long long nimg, BwdwImgPlan* P);
 // One chunk of nimg images; accumulate: add to dw and dbias instead of writing them.

@@ -449,6 +449,21 @@ bool bwdw_img_plan(const cct_conv_desc_t& d, long long nimg, BwdwImgPlan* P) {
   take(want * out_bytes, &P->part_off);
   take(groups_of_images * ty * d.O * 4, &P->sums_off);
   P->total = off;
+  // Few channels (with kFewMargin 2 of 388 layers take more than 4 % longer than without this kernel; at 1.0 none do, but
+  // those that stay off it lose 2 % in the mean).  Decided for the whole batch, so that a shorter last chunk runs the same way.
+  P->few = bwdw_few_plan(d, nimg, &P->fp) && (nimg < d.N || P->fp.seconds < kFewMargin * P->seconds);
+  if (nimg < d.N && P->few) {
+    BwdwImgPlan whole;
+    P->few = bwdw_img_plan(d, d.N, &whole) && whole.few;
+  }
+  if (P->few) {
+    P->seconds = P->fp.seconds;
+    P->S = P->fp.S;
+    off = 0;
+    take(P->S * out_bytes, &P->part_off);
+    take((long long)P->S * d.O * 4, &P->sums_off);
+    P->total = off;
+  }
   return true;
 }
 
@@ -472,9 +487,16 @@ int launch_bwdw_img(const cct_conv_desc_t& d, const BwdwImgPlan& P, int nimg, co
     make_fastdiv_parts(j.tiles_c, &j.mTc, &j.sTc);
     return j;
   };
-  const PrepJob jx = job(x, P.xs_off, d.C, d.H, d.W, d.pad);
+  float* part = reinterpret_cast<float*>(ws + P.part_off);
+  float* sums = dbias ? reinterpret_cast<float*>(ws + P.sums_off) : nullptr;
+  int nsums = P.S;
+  if (P.few) {
+    if (const int rc = launch_bwdw_few(d, P.fp, nimg, x, dy, part, sums, st)) return rc;
+  } else {
+    const PrepJob jx = job(x, P.xs_off, d.C, d.H, d.W, d.pad);
   PrepJob jy = job(dy, P.ds_off, d.O, Hout, Wout, 0);
-  jy.sums = dbias ? reinterpret_cast<float*>(ws + P.sums_off) : nullptr;
+  jy.sums = sums;
+  nsums = igs * jy.tiles_px;
   const int bx = igs * jx.tiles_px * jx.tiles_c, by = igs * jy.tiles_px * jy.tiles_c;
   const double xn = (double)nimg * d.C * d.H * d.W, yn = (double)nimg * d.O * pix;
   {
@@ -489,7 +511,7 @@ int launch_bwdw_img(const cct_conv_desc_t& d, const BwdwImgPlan& P, int nimg, co
   memset(&q, 0, sizeof(q));
   q.xs = reinterpret_cast<const unsigned char*>(ws + P.xs_off);
   q.ds = reinterpret_cast<const unsigned char*>(ws + P.ds_off);
-  q.part = reinterpret_cast<float*>(ws + P.part_off);
+  q.part = part;
   q.M = Og; q.N = Cg * KK; q.G = d.groups;
   q.Cg = Cg; q.Og = Og; q.C = d.C; q.O = d.O; q.K = d.K; q.KK = KK; q.s = d.stride; q.Wp = Wp;
   q.img_cells = (long long)Hp * Wp;
@@ -516,22 +538,23 @@ int launch_bwdw_img(const cct_conv_desc_t& d, const BwdwImgPlan& P, int nimg, co
       rc = P.terms == 3 ? launch_product<64, 3, 12>(q, grid, st) : launch_product<64, 1, 8>(q, grid, st);
     if (rc) return rc;
   }
+  }
   ImgReduce r;
   memset(&r, 0, sizeof(r));
-  r.part = q.part; r.dw = dw; r.sums = jy.sums; r.dbias = dbias; r.x = x; r.dy = dy;
-  r.M = Og; r.N = q.N; r.G = d.groups; r.S = q.S; r.K = d.K; r.KK = KK; r.Cg = Cg; r.Og = Og;
-  r.C = d.C; r.O = d.O; r.H = d.H; r.W = d.W; r.P = pix; r.Wout = Wout; r.mWout = q.mWout; r.sWout = q.sWout; r.s = d.stride; r.pad = d.pad;
+  r.part = part; r.dw = dw; r.sums = sums; r.dbias = dbias; r.x = x; r.dy = dy;
+  r.M = Og; r.N = Cg * KK; r.G = d.groups; r.S = P.S; r.K = d.K; r.KK = KK; r.Cg = Cg; r.Og = Og;
+  r.C = d.C; r.O = d.O; r.H = d.H; r.W = d.W; r.P = pix; r.Wout = Wout; make_fastdiv_parts(Wout, &r.mWout, &r.sWout); r.s = d.stride; r.pad = d.pad;
   r.nimg = nimg;
-  r.nsums = igs * jy.tiles_px;
+  r.nsums = nsums;
   r.accumulate = accumulate;
   r.split = P.terms == 3;
-  const long long total = (long long)d.O * q.N;
+  const long long total = (long long)d.O * r.N;
   // few weights: more loads in flight per weight
-  r.strips = total < 256 * 1024 && q.S >= 8 ? 4 : 1;
+  r.strips = total < 256 * 1024 && P.S >= 8 ? 4 : 1;
   const long long rb = (total * r.strips + 255) / 256, db = dbias ? (d.O + kSumCh - 1) / kSumCh : 0;
   if (rb + db >= 2147483647LL) return CCT_EUNSUPPORTED;
   r.blocks_dw = (int)rb;
-  ProfScope ps("bwdw_img_reduce", 0.0, 4.0 * total * (q.S + 1), st);
+  ProfScope ps("bwdw_img_reduce", 0.0, 4.0 * total * (P.S + 1), st);
   hipLaunchKernelGGL(bwdw_img_reduce, dim3((unsigned)(rb + db)), dim3(256), 0, st, r);
   CCT_CHECK_LAUNCH();
   return CCT_OK;
