@@ -177,6 +177,9 @@ int gemm_split_mpad(int M);
 int gemm_split_kpad(int K);
 bool gemm_split_fits(const GemmTN& p, bool bt);
 int launch_gemm_split(const GemmTN& p, int Ktotal, bool bt, hipStream_t st);
+// C[m][n] = sum_k A[m][k] * B[n][k] + bias[n], all compact, for a few rows
+bool gemm_split_k_fits(int M, int N, int K);
+int launch_gemm_split_k(const float* A, const float* B, const float* bias, float* C, int M, int N, int K, hipStream_t st);
 double gemm_split_seconds(bool bt, bool pack, int M, int K, long long cols, long long G);
 // Its operand A(m, k) of group g = src[g*sg + (m / taps)*sm + m % taps + k*sk]: packed into `pack` where that pays (or,
 // without one, never), else read in place.  Sets p's fields for A; the others must be set but for the tensor and the result.

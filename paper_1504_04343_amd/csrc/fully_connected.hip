@@ -16,6 +16,7 @@
 // over up to 32 images.
 #include <algorithm>
 #include <cstring>
+#include <type_traits>
 
 #include "cct_internal.h"
 #include "index_common.h"
@@ -95,6 +96,177 @@ __global__ __launch_bounds__(TPB) void fc_sum_splits_kernel(const float* __restr
     acc += bias[(int)t - n * divO.d];
   }
   y[t] = acc;
+}
+
+// dw[o][f] = sum_n dy[n][o] * x[n][f] and dbias[o] = sum_n dy[n][o] over up to 32 images, in fp32: a workgroup owns 8
+// kernels x 1024 features, a thread 4 consecutive ones, dy's values are the same for all threads.  Bound by writing dw
+// (one image of fc6, 151 MB: 43.1 us as a pack of dy, a matrix product whose stages are mostly padding, and the bias
+// gradient's launch, 29.2 now; 16 images 45.0 and 43.3), and below some MB by the one launch (12 -> 6).  17 to 32 images up
+// to 2^22 weights (15.6 and 15.0; with 2^25 the multiplications weigh, 56 and 66).
+constexpr int kOuterRows = 8;
+typedef float fc_f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // 16 bytes, dword aligned
+__global__ __launch_bounds__(TPB) void fc_outer_kernel(const float* __restrict__ x, const float* __restrict__ dy,
+                                                       float* __restrict__ dw, float* __restrict__ dbias, int N, int O, int F) {
+  const int o0 = blockIdx.y * kOuterRows;
+  const int f0 = (int)(blockIdx.x * TPB + threadIdx.x) * 4;
+  if (dbias && blockIdx.x == 0 && threadIdx.x < 64) {  // a lane sums 4 images of a kernel
+    const int o = o0 + (threadIdx.x & 7), strip = threadIdx.x >> 3;
+    float v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int n = strip * 4 + u;
+      const float q = dy[(long long)min(n, N - 1) * O + min(o, O - 1)];
+      v[u] = n < N ? q : 0.f;
+    }
+    float sum = (v[0] + v[1]) + (v[2] + v[3]);
+    sum += __shfl_xor(sum, 8, 64);
+    sum += __shfl_xor(sum, 16, 64);
+    sum += __shfl_xor(sum, 32, 64);
+    if (strip == 0 && o < O) dbias[o] = sum;
+  }
+  if (f0 >= F) return;
+  const bool whole = f0 + 4 <= F;
+  float acc[kOuterRows][4];
+#pragma unroll
+  for (int o = 0; o < kOuterRows; ++o)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[o][e] = 0.f;
+  // 4 images at a time: their loads in flight together, their products summed before they are added
+  for (int n0 = 0; n0 < N; n0 += 4) {
+    float v[4][4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const float* xn = x + (long long)min(n0 + u, N - 1) * F + f0;
+      if (whole) {
+        const fc_f32x4u q = *reinterpret_cast<const fc_f32x4u*>(xn);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[u][e] = q[e];
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[u][e] = f0 + e < F ? xn[e] : 0.f;
+      }
+    }
+    const int live = min(4, N - n0);
+    auto add = [&](auto full) {
+      constexpr bool FULL = decltype(full)::value;
+#pragma unroll
+      for (int o = 0; o < kOuterRows; ++o) {
+        float t[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          if (!FULL && u >= live) break;
+          const float g = dy[(long long)(n0 + u) * O + min(o0 + o, O - 1)];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) t[e] = fmaf(g, v[u][e], t[e]);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[o][e] += t[e];
+      }
+    };
+    if (live == 4) add(std::integral_constant<bool, true>());
+    else add(std::integral_constant<bool, false>());
+  }
+#pragma unroll
+  for (int o = 0; o < kOuterRows; ++o) {
+    if (o0 + o >= O) break;
+    float* to = dw + (long long)(o0 + o) * F + f0;
+    if (whole) {
+      *reinterpret_cast<fc_f32x4u*>(to) = fc_f32x4u{acc[o][0], acc[o][1], acc[o][2], acc[o][3]};
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (f0 + e < F) to[e] = acc[o][e];
+    }
+  }
+}
+
+// dx[n][f] = sum_o dy[n][o] * w[o][f] over up to 8 images, in fp32 (S > 1: one of S shares of the kernels, to part): a
+// workgroup owns 256 features, a lane 4 consecutive ones, its 8 waves share out the kernels; dy's values are the same for a
+// whole wave.  Bound by reading w once; the kernels are split over workgroups where the features are too few to fill the
+// chip.  One image of fc6 (151 MB) 38.2 us on 32-row tiles of the matrix cores behind a pack, 31.4 now; 4096 -> 1000
+// 14.8 -> 11; with 16 images registers leave too few waves in flight (41 and 77).
+constexpr int kRowsWaves = 8, kRowsFeatures = 256;
+template <int ROWS>
+__global__ __launch_bounds__(64 * kRowsWaves) void gemm_split_k_columns(const float* __restrict__ w, const float* __restrict__ dy,
+                                                                  float* __restrict__ out, int N, int O, int F, int share) {
+  __shared__ float red[kRowsWaves][kRowsFeatures];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int f0 = blockIdx.x * kRowsFeatures + lane * 4, fb = min(f0, F - 1);
+  const bool whole = f0 + 4 <= F;
+  const int per = (share + kRowsWaves - 1) / kRowsWaves;
+  const int o_begin = blockIdx.y * share + wave * per, o_end = min(min(O, (int)(blockIdx.y + 1) * share), o_begin + per);
+  float acc[ROWS][4];
+#pragma unroll
+  for (int n = 0; n < ROWS; ++n)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[n][e] = 0.f;
+  // 4 kernels at a time: their loads in flight together, their products summed before they are added
+  for (int o = o_begin; o < o_end; o += 4) {
+    float v[4][4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const float* wo = w + (long long)min(o + u, o_end - 1) * F + fb;
+      if (whole) {
+        const fc_f32x4u q = *reinterpret_cast<const fc_f32x4u*>(wo);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[u][e] = q[e];
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[u][e] = f0 + e < F ? wo[e] : 0.f;
+      }
+    }
+    const int live = min(4, o_end - o);
+    auto add = [&](auto full) {
+      constexpr bool FULL = decltype(full)::value;
+#pragma unroll
+      for (int n = 0; n < ROWS; ++n) {
+        const float* d = dy + (long long)min(n, N - 1) * O + o;
+        float t[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          if (!FULL && u >= live) break;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) t[e] = fmaf(d[u], v[u][e], t[e]);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[n][e] += t[e];
+      }
+    };
+    if (live == 4) add(std::integral_constant<bool, true>());
+    else add(std::integral_constant<bool, false>());
+  }
+  // the waves' sums, a row of dx at a time
+  const int t = threadIdx.x, f = blockIdx.x * kRowsFeatures + t;
+  float* to = out + (long long)blockIdx.y * N * F;
+#pragma unroll
+  for (int n = 0; n < ROWS; ++n) {
+    if (n < N) {  // the same for all
+      *reinterpret_cast<float4*>(&red[wave][lane * 4]) = make_float4(acc[n][0], acc[n][1], acc[n][2], acc[n][3]);
+      __syncthreads();
+      if (t < kRowsFeatures && f < F)
+        to[(long long)n * F + f] = ((red[0][t] + red[1][t]) + (red[2][t] + red[3][t])) + ((red[4][t] + red[5][t]) + (red[6][t] + red[7][t]));
+      __syncthreads();
+    }
+  }
+}
+
+// How many workgroups share a feature's kernels: at most 1024 workgroups of at least 32 kernels, none shared where a wave's
+// chain of 16 kernels is shorter than the second launch, which adds the shares.
+int split_k_columns_shares(int O, int F) {
+  const int blocks = (F + kRowsFeatures - 1) / kRowsFeatures;
+  return O <= 128 ? 1 : std::max(1, std::min({1024 / blocks, O / 32, 64}));
+}
+
+int launch_split_k_columns(const float* w, const float* dy, float* out, int N, int O, int F, int S, hipStream_t st) {
+  const int share = (O + S - 1) / S;
+  const dim3 grid((unsigned)((F + kRowsFeatures - 1) / kRowsFeatures), (unsigned)((O + share - 1) / share)), block(64 * kRowsWaves);
+  ProfScope ps("gemm_split_k_columns", 2.0 * N * (double)O * F, 4.0 * ((double)O * F + (double)N * (O + (double)S * F)), st);
+  if (N <= 1) hipLaunchKernelGGL(gemm_split_k_columns<1>, grid, block, 0, st, w, dy, out, N, O, F, share);
+  else if (N <= 2) hipLaunchKernelGGL(gemm_split_k_columns<2>, grid, block, 0, st, w, dy, out, N, O, F, share);
+  else if (N <= 4) hipLaunchKernelGGL(gemm_split_k_columns<4>, grid, block, 0, st, w, dy, out, N, O, F, share);
+  else hipLaunchKernelGGL(gemm_split_k_columns<8>, grid, block, 0, st, w, dy, out, N, O, F, share);
+  CCT_CHECK_LAUNCH();
+  return CCT_OK;
 }
 
 // Kpad = total rows of the pack = splits * Kpad_s
@@ -343,6 +515,8 @@ bool fc_plan(const cct_conv_desc_t& d, int pass, long long max_bytes, FcPlan* P)
 int fc_forward(const cct_conv_desc_t& d, const FcPlan& P, const float* x, const float* w,
                const float* bias, float* y, char* ws, hipStream_t st) {
   if (P.F % 32 == 0 && reinterpret_cast<uintptr_t>(w) % 16) return CCT_EINVAL;
+  if (P.split && gemm_split_k_fits(d.N, d.O, P.F))
+    return launch_gemm_split_k(x, w, bias, y, d.N, d.O, P.F, st);
   if (P.split) {
     void* pack = ws + P.pack_off;
     float* part = reinterpret_cast<float*>(ws + P.part_off);
@@ -372,6 +546,18 @@ int fc_forward(const cct_conv_desc_t& d, const FcPlan& P, const float* x, const 
 
 int fc_backward_data(const cct_conv_desc_t& d, const FcPlan& P, const float* w, const float* dy,
                      float* dx, char* ws, hipStream_t st) {
+  if (P.split && d.N <= 8) {
+    // the shares whose partial products the plan's workspace holds
+    const long long out = 4LL * d.N * P.F;
+    int S = split_k_columns_shares(d.O, P.F);
+    if (S > 1) S = (int)std::max(1LL, std::min<long long>(S, P.total / out));
+    const int share = (d.O + S - 1) / S;
+    S = (d.O + share - 1) / share;
+    float* part = reinterpret_cast<float*>(ws);
+    const int rc = launch_split_k_columns(w, dy, S > 1 ? part : dx, d.N, d.O, P.F, S, st);
+    if (rc || S == 1) return rc;
+    return launch_fc_sum_splits(part, dx, S, (long long)d.N * P.F, 1, nullptr, st);
+  }
   if (P.split) {
     void* pk = ws + P.pack_off;
     float* part = reinterpret_cast<float*>(ws + P.part_off);
@@ -434,6 +620,14 @@ int fc_backward_weights(const cct_conv_desc_t& d, const FcPlan& P, const float* 
                         float* dw, float* dbias, char* ws, hipStream_t st) {
   float* pack = reinterpret_cast<float*>(ws + P.pack_off);
   int rc;
+  const long long oy = ((long long)d.O + kOuterRows - 1) / kOuterRows;
+  if (!P.split && (d.N <= 16 || (d.N <= 32 && (long long)d.O * P.F <= (1LL << 22))) && oy <= 65535) {
+    ProfScope ps("fc_outer_kernel", 2.0 * d.N * (double)d.O * P.F, 4.0 * ((double)d.O * P.F + (double)d.N * (P.F + d.O)), st);
+    hipLaunchKernelGGL(fc_outer_kernel, dim3((unsigned)((P.F + 4 * TPB - 1) / (4 * TPB)), (unsigned)oy), dim3(TPB), 0, st, x, dy, dw,
+                       dbias, d.N, d.O, P.F);
+    CCT_CHECK_LAUNCH();
+    return CCT_OK;
+  }
   if (P.split) {
     GemmTN p = fc_split_problem(P, d.O, P.F, x, dw);
     rc = gemm_split_operand(&p, false, dy, pack, d.N, 1, d.O, 0, 1, st);

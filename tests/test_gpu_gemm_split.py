@@ -232,3 +232,31 @@ def test_row_tiles_k_contiguous(B, N, F, O, rows):
     got, names = ran(B, lambda: gpu_forward(B, L, x, w, b))
     assert "gemm_split<%d, k-contiguous>" % rows in names, names
     assert rel_err(got, oracle.conv_forward(odims(oracle, L), x, w, b)) <= TOL_F32
+
+
+@pytest.mark.parametrize("N,F,O", [(1, 9216, 1001), (2, 2047, 5), (3, 4099, 33), (4, 1, 70), (5, 2052, 6), (8, 6145, 130)])
+def test_few_images(B, N, F, O):
+    """Fully connected forward on few images: whole steps of 2048 features, a part of one, up to 3 features beyond the
+    last four; columns past a workgroup's 4.  Sums of 4 to 8 products per lane and step in fp32: its tolerance."""
+    L = layer("fc", N, F, 1, 1, O, 1)
+    x, w, b = synth.make_x(L, 8), synth.make_w(L, 8), synth.make_bias(L, 8)
+    for bias in (b, None):
+        got, names = ran(B, lambda: gpu_forward(B, L, x, w, bias))
+        assert len(names) == 1 and names[0].startswith("gemm_split_k<"), names
+        assert rel_err(got, oracle.conv_forward(odims(oracle, L), x, w, bias)) <= TOL_F32
+
+
+@pytest.mark.parametrize("N,F,O", [(1, 1023, 4099), (2, 257, 128), (3, 5, 33), (5, 1, 900), (8, 4098, 129), (16, 1025, 17),
+                                   (31, 70, 23)])
+def test_few_images_backward(B, N, F, O):
+    """The gradients: shares of the kernels and none, up to 3 features beyond the last four, kernels past a
+    workgroup's 8, up to 3 images beyond the last four.  Sums in fp32 of up to 4 products at a time: its tolerance."""
+    L = layer("fc", N, F, 1, 1, O, 1)
+    x, w, dy = synth.make_x(L, 8), synth.make_w(L, 8), synth.make_dy(L, 8)
+    got, names = ran(B, lambda: gpu_backward_data(B, L, w, dy))
+    assert any(n.startswith("gemm_split_k_columns") for n in names) == (N <= 8), names
+    assert rel_err(got, oracle.conv_backward_data(odims(oracle, L), w, dy)) <= TOL_F32
+    (dw, db), names = ran(B, lambda: gpu_backward_weights(B, L, x, dy))
+    assert names == ["fc_outer_kernel"], names
+    want = oracle.conv_backward_weights(odims(oracle, L), x, dy)
+    assert rel_err(dw, want[0]) <= TOL_F32 and rel_err(db, want[1]) <= TOL_F32
