@@ -67,6 +67,8 @@ struct GemmTN {
   long long a_ms;      // != 0 (gemm_split): A is fp32, A(m, k) at m / a_taps * a_ms + m % a_taps + k * a_ks, groups a_gs apart
   long long a_ks, a_len, b_len;  // elements of A and B from their beginning
   int a_taps, rb;
+  int pair_P, pair_cols, pair_sh;  // columns of an image as they are taken in pairs (0: no images), and of all
+  unsigned pair_M;
   int M, Ncols, Kdim;  // true sizes per group
   int G;
   int bf16;            // operands are bf16 (A packed bf16, B bf16 plain rows)

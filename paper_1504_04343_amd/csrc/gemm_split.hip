@@ -6,8 +6,8 @@
 //     16 x 16 (v_mfma_f32_16x16x32_bf16), two accumulators each;
 //   - B goes from memory into the registers of the one wave that multiplies it, which splits it there: no LDS, no
 //     meeting of waves.  A lane supplies 8 k of two neighbouring columns per stage of 32 k.  The split of the next stage is
-//     written between the MFMAs of this one, 3 or 4 instructions at a time.  Columns lie in pairs (8-byte loads and
-//     stores), one by one (odd planes), or k-contiguous (w of a forward product, 16-byte loads);
+//     written between the MFMAs of this one, 3 or 4 instructions at a time.  Columns are taken in pairs (8-byte loads and
+//     stores), one by one (planes of a few pixels), or k-contiguous (w of a forward product, 16-byte loads);
 //   - A is shared by the four waves through LDS: units of 16 rows and one term, in lane order, so that a read is 1 KiB
 //     without conflicts.  128 and 144 rows: packed that way and split once per call (launch_pack_rows_split), moved to
 //     LDS by loads that write it directly.  32 and 64 rows: fp32 values in place, any strides, split by the
@@ -74,17 +74,33 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
   const int kd = min(p.Kdim, Ktotal - g * p.Kdim);
   const int stages = (kd + SK - 1) / SK;
 
-  // ---- B: a lane supplies two neighbouring columns, 8 k of each
+  // ---- B: a lane supplies two neighbouring columns, 8 k of each.  In pairs an image has an even number of columns: where
+  // its plane is odd, the second of its last pair is no column (what it loads is not stored)
   const float* Bg = reinterpret_cast<const float*>(p.B) + (long long)g * p.b_gs;
-  const int n_f = BT ? 0 : fdiv_u(n0, p.bmap.divM, p.bmap.divsh);
+  const int n_f = BT                ? 0
+                  : BF == kColumns ? fdiv_u(n0, p.bmap.divM, p.bmap.divsh)
+                  : p.pair_P       ? fdiv_u(n0, p.pair_M, p.pair_sh)
+                                   : 0;
   const float* Bt = BT ? Bg + (long long)n0 * p.b_ks : Bg + (long long)n_f * p.bmap.img_stride;
-  const int col0 = n0 + wave * 32 + 2 * lo;
+  // which column of the matrix is column v of the tiles, and is it one?
+  auto column = [&](int v, bool* live) {
+    if constexpr (BF != kPairs) {
+      *live = v < p.Ncols;
+      return min(v, p.Ncols - 1);
+    } else {
+      const int c = min(v, p.pair_cols - 2 + (v & 1)), img = p.pair_P ? fdiv_u(c, p.pair_M, p.pair_sh) : 0;
+      const int pix = c - img * p.pair_P;
+      *live = v < p.pair_cols && pix < (p.pair_P ? p.bmap.P : p.Ncols);
+      return p.pair_P ? img * p.bmap.P + min(pix, p.bmap.P - 1) : min(pix, p.Ncols - 1);
+    }
+  };
   unsigned voff[2];
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
-    const int c = min(col0 + j, p.Ncols - (BF == kPairs ? 2 - j : 1));
-    voff[j] = BT ? (unsigned)((long long)(c - n0) * p.b_ks + kg * 8) * 4u
-                 : (unsigned)(col_offset(p.bmap, c) - (long long)n_f * p.bmap.img_stride + (long long)kg * 8 * p.b_ks) * 4u;
+    bool live;
+    const int col = column(n0 + wave * 32 + 2 * lo + j, &live);
+    voff[j] = BT ? (unsigned)((long long)(col - n0) * p.b_ks + kg * 8) * 4u
+                 : (unsigned)(col_offset(p.bmap, col) - (long long)n_f * p.bmap.img_stride + (long long)kg * 8 * p.b_ks) * 4u;
   }
   // k past the last one: what lies there, or zero beyond the tensor's end (A is zero there; an infinity only costs the
   // recomputation).  The range is checked against the vector offset alone: all of an address that may lie beyond goes there.
@@ -340,12 +356,17 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
   // NaN once a result is not finite: one instruction each (compares, whose answers are collected in scalar masks,
   // took 2 % of fc6's products and 4 % of a 4096 -> 1000 layer's)
   float check = 0.f;
-  const int c0 = min(col0, p.Ncols - 1), c1 = min(col0 + 1, p.Ncols - 1);
-  const long long o0 = col_offset(p.cmap, c0), o1 = col_offset(p.cmap, c1);
-  const bool both = __all(o1 == o0 + 1);
+  int first = n0 + wave * 32 + 2 * lo;
+  asm volatile("" : "+v"(first));  // not kept from before
+  bool live[2];
+  int col[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) col[j] = column(first + j, &live[j]);
+  const long long o0 = col_offset(p.cmap, col[0]), o1 = col_offset(p.cmap, col[1]);
+  const bool both = __all(o1 == o0 + 1 && live[1]);
   float* __restrict__ cl0 = C + o0 + (long long)mw * p.c_ms;
   float* __restrict__ cl1 = C + o1 + (long long)mw * p.c_ms;
-  const float cb0 = bias && p.bias_gs < 0 ? bias[c0] : 0.f, cb1 = bias && p.bias_gs < 0 ? bias[c1] : 0.f;
+  const float cb0 = bias && p.bias_gs < 0 ? bias[col[0]] : 0.f, cb1 = bias && p.bias_gs < 0 ? bias[col[1]] : 0.f;
 #pragma unroll
   for (int i = 0; i < RB; ++i)
 #pragma unroll
@@ -368,8 +389,8 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
       if (both) {
         *reinterpret_cast<f32x2u*>(cl0 + row) = f32x2u{v[0], v[1]};
       } else {
-        if (col0 < p.Ncols) cl0[row] = v[0];
-        if (col0 + 1 < p.Ncols) cl1[row] = v[1];
+        if (live[0]) cl0[row] = v[0];
+        if (live[1]) cl1[row] = v[1];
       }
     }
   if (!__any(check != check)) return;
@@ -380,7 +401,8 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
   float* Cq = q.C + (long long)g * q.c_gs;
   const float* Bq = reinterpret_cast<const float*>(q.B) + (long long)g * q.b_gs;
   const float* bq = q.bias ? q.bias + (q.bias_gs < 0 ? 0 : (long long)g * q.bias_gs) : nullptr;
-  const int col = n0 + wave * 32 + lane_lo, c = min(col, q.Ncols - 1);
+  bool is_col;
+  const int c = column(n0 + wave * 32 + lane_lo, &is_col);
   const float* bc = Bq + (BT ? (long long)c * q.b_ks : col_offset(q.bmap, c));
 #pragma unroll 1
   for (int i = 0; i < (RB + 1) / 2; ++i) {  // 32 rows; the last ones may be the next tile's: not looked at
@@ -390,7 +412,7 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int rr = (r >> 2) * 8 + (r & 3);
-      if (col < q.Ncols && mb + lane_hi * 4 + rr < m_end && !finite(cl[(long long)rr * q.c_ms])) todo |= 1u << r;
+      if (is_col && mb + lane_hi * 4 + rr < m_end && !finite(cl[(long long)rr * q.c_ms])) todo |= 1u << r;
     }
     if (!__any(todo)) continue;
     const int m = min(mb + lane_lo, q.M - 1);
@@ -415,7 +437,7 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
       if (!(todo >> r & 1)) continue;
       const int rr = (r >> 2) * 8 + (r & 3);
       float sum = v[r];
-      if (bq) sum += bq[q.bias_gs < 0 ? col : mb + lane_hi * 4 + rr];
+      if (bq) sum += bq[q.bias_gs < 0 ? c : mb + lane_hi * 4 + rr];
       cl[(long long)rr * q.c_ms] = sum;
     }
   }
@@ -628,7 +650,8 @@ template <class Fits>
 const Form* choose(bool bt, int M, int K, long long cols, long long G, Fits fits, double* us) {
   const Form* best = nullptr;
   for (const Form& f : kForms) {
-    if (!fits(f)) continue;
+    // (up to 32 rows 32 at a time, whatever the estimates say: 16 images of fc6 forward 45 us against 52 in tiles of 64)
+    if (!fits(f) || (f.rb == 4 && M <= 32)) continue;
     const double t = form_us(f, bt, M, K, cols, G);
     if (!best || t < *us) {
       best = &f;
@@ -640,7 +663,7 @@ const Form* choose(bool bt, int M, int K, long long cols, long long G, Fits fits
 
 template <int RB, BForm BF, AForm AF>
 int launch_variant(const GemmTN& p, int Ktotal, hipStream_t st) {
-  const int tiles_m = (p.M + 16 * RB - 1) / (16 * RB), tiles_n = (p.Ncols + BN - 1) / BN;
+  const int tiles_m = (p.M + 16 * RB - 1) / (16 * RB), tiles_n = ((BF == kPairs ? p.pair_cols : p.Ncols) + BN - 1) / BN;
   const long long blocks = (long long)tiles_m * tiles_n;
   if (blocks <= 0 || blocks >= 2147483647LL || p.G < 1 || p.G > 65535) return CCT_EUNSUPPORTED;
   const double mk = (double)p.M * p.Kdim * p.G, kn = (double)p.Kdim * p.Ncols * p.G;
@@ -725,13 +748,22 @@ int launch_gemm_split(const GemmTN& p0, int Ktotal, bool bt, hipStream_t st) {
   colmap_prepare(&p.cmap);
   if (p.Mpad != gemm_split_mpad(p.M) || p.Kpad != gemm_split_kpad(p.Kdim)) return CCT_EINVAL;
   if (!gemm_split_fits(p, bt)) return CCT_EUNSUPPORTED;
+  p.pair_P = p.pair_cols = 0;
   // elements of B from p.B on
   p.b_len = bt                        ? (long long)p.Ncols * p.b_ks
             : p.bmap.P == 2147483647 ? Ktotal * p.b_ks
                                      : (long long)(p.Ncols / p.bmap.P) * p.bmap.img_stride;
   if (bt) return launch_columns<kContiguous>(p, Ktotal, st);
-  const bool pairs = p.Ncols % 2 == 0 && (p.bmap.P % 2 == 0 || p.bmap.P == 2147483647);
-  return pairs ? launch_columns<kPairs>(p, Ktotal, st) : launch_columns<kColumns>(p, Ktotal, st);
+  // Pairs, unless the planes are so small that the columns which make them even weigh
+  const int P = p.bmap.P;
+  if (P == 2147483647) {
+    p.pair_cols = (p.Ncols + 1) / 2 * 2;
+  } else if (P % 2 == 0 || P >= 15) {
+    p.pair_P = (P + 1) / 2 * 2;
+    p.pair_cols = p.Ncols / P * p.pair_P;
+    make_fastdiv_parts(p.pair_P, &p.pair_M, &p.pair_sh);
+  }
+  return p.pair_cols ? launch_columns<kPairs>(p, Ktotal, st) : launch_columns<kColumns>(p, Ktotal, st);
 }
 
 }  // namespace cct
