@@ -32,6 +32,7 @@ struct GeomRules {
   int chan_num = 9, chan_den = 8;  // channels padded to whole groups of 16: at most chan_num / chan_den
                                    // of the true count (an eighth more)
   int tpi_num = 11, tpi_den = 10;  // positions that tiles cut per image may spend: a tenth more
+  int bn = BN;             // positions per workgroup
 };
 
 // Geometry and LDS need (at most `lds_cap` bytes: the cap decides whether column tiles are cut per
@@ -50,9 +51,9 @@ inline bool make_geom(const GemmTN& p, int BM, int cell_bytes, KcGeom* fg, size_
   // channels are padded to whole groups of 16: not worth it when that wastes too much
   if ((long long)fg->ngroups * CG * rules.chan_den > (long long)p.gCg * rules.chan_num) return false;
   const long long P = (long long)p.gHout * p.gWout;
-  // rows of padded input that 128 consecutive positions can touch: at most A output rows spread
+  // rows of padded input that a workgroup's consecutive positions can touch: at most A output rows spread
   // over at most T images; t images need (A - t)*stride + t*K rows, largest at t = 1 or t = T
-  const long long A = (BN - 1) / p.gWout + 2, T = (BN - 1) / P + 2;
+  const long long A = (rules.bn - 1) / p.gWout + 2, T = (rules.bn - 1) / P + 2;
   const long long r1 = (A - 1) * p.gs + p.gK;
   const long long rT = (A > T ? A - T : 0) * p.gs + T * p.gK;
   auto cells = [&](long long rows) { return (rows * fg->Wp + rules.r_step - 1) / rules.r_step * rules.r_step; };
@@ -64,10 +65,10 @@ inline bool make_geom(const GemmTN& p, int BM, int cell_bytes, KcGeom* fg, size_
   if (R > rules.qu * NT || lds_of(R) > lds_cap) {
     // tiles cut per image need the rows of one image only; worth it while the partly empty last
     // tile of an image does not waste too much of the launch
-    const long long tpi = (P + BN - 1) / BN;
+    const long long tpi = (P + rules.bn - 1) / rules.bn;
     const long long rows1 = (A < p.gHout ? A - 1 : p.gHout - 1) * p.gs + p.gK;
     R = cells(rows1);
-    if (tpi * BN * rules.tpi_den > P * rules.tpi_num || tpi * ((double)p.Ncols / P) >= 2147483647.0) return false;
+    if (tpi * rules.bn * rules.tpi_den > P * rules.tpi_num || tpi * ((double)p.Ncols / P) >= 2147483647.0) return false;
     fg->tpi = (int)tpi;
   }
   if (R > rules.qu * NT) return false;

@@ -3,8 +3,8 @@
 // bf16 MFMAs (split_bf16.h).
 //
 // Product: C[m][pos] = sum_{grp, tap, c} K^[grp][tap][m][c] * xpad[n, grp*16 + c, r*s + i, c*s + j]
-//   - a workgroup owns BM rows x 128 consecutive positions; a wave owns 32 or 48 rows x (all 128 | half |
-//     a quarter of them) positions, two accumulators per block of results;
+//   - a workgroup owns BM rows x 128 consecutive positions (48 rows: x 192); a wave owns 32 or 48 rows x (all |
+//     half | a quarter of them) positions, two accumulators per block of results;
 //   - per channel group of 16 it stages the zero-padded input rows its positions can touch as cells
 //     (row, column) in a two-slot LDS ring, split while they are staged.  A cell is three terms of 16 bytes
 //     for each half of its 16 channels; the halves lie apart, so that cells are 48 bytes = three 16-byte
@@ -31,8 +31,9 @@
 //     nothing is looked up or decided between the MFMAs of a lone wave.  16 -> 32, in us: 50 images of conv5 forward
 //     71.7 -> 67.9, 4 images of 28 x 28, 64 -> 128, K = 3, 18.9 -> 18.4, 48 workgroups of K = 5 24.4 -> 21.1, 20 images of
 //     27 x 27, 192 -> 192, K = 3, 72.3 -> 67.4.
-// 48-row tiles for conv2's backward-data (48 rows on 64) were slower than the padding, 800 against 730: four waves
-// then ask the L1 for the same 9 KiB per 576 MFMA cycles.  Splitting and loading in pieces between the MFMAs gave
+// 48 rows (conv2's and conv1's backward-data) are a tile of their own, with 192 positions, 48 of a wave: four waves then
+// ask the L1 for the same 9 KiB each per 864 MFMA cycles.  With 128 positions (per 576 cycles) it was slower than the
+// padding to 64 rows, 800 against 730 us.  Splitting and loading in pieces between the MFMAs gave
 // nothing (conv5 75 -> 78), nor did kernel values four pairs ahead.
 //   - KT: the kernel size where it is compiled in (3, 5); 0 = any K.
 //   - S: 1 = the tensor itself; 2, 4 = space to depth: the padded input is read as a tensor of S*S
@@ -86,6 +87,8 @@ __device__ __forceinline__ const float* pixel_of(const GemmTN& p, int g, int n, 
          (long long)((g * p.gCg + ch) / (S * S)) * p.x_plane + (long long)h * p.x_w + w;
 }
 
+// positions of a workgroup: four waves side by side on 48 rows take 48 each
+constexpr int positions(int WAVES_M, int RB) { return WAVES_M == 1 && RB == 3 ? 192 : BN; }
 // cells per thread: sizes that are not compiled in take a third one (7 x 7 windows on wide rows)
 constexpr int kCells(int KT) { return KT ? 2 : 3; }
 
@@ -95,6 +98,7 @@ __global__ __launch_bounds__(NT, 2) void conv_fused_split(GemmTN p, KcGeom fg, i
   constexpr int MW = 16 * RB;     // rows of a wave
   constexpr int BM = MW * WAVES_M;
   constexpr int WAVES_N = 4 / WAVES_M;
+  constexpr int BN = positions(WAVES_M, RB);
   constexpr int WN = BN / (MB * WAVES_N);  // blocks of MB positions of a wave
   constexpr int QB = MW * MB / 256;        // a lane's results in a block column: quads of consecutive rows
   static_assert(WAVES_M * WAVES_N == 4, "4 waves per workgroup");
@@ -301,7 +305,7 @@ __global__ __launch_bounds__(NT, 2) void conv_fused_split(GemmTN p, KcGeom fg, i
     // The next group's four steps, FL at a time: loaded before one pair of tiles, stored before a later one, so that
     // the MFMAs between cover the way to memory.  Register budget decides FL; where it is short, 5 x 5 kernels have
     // the tiles to go one by one.
-    constexpr int FL = KT != 0 && WAVES_M * RB <= 4 && S == 1 ? 4 : KT == 5 ? 1 : 2;  // KT == 0: one cell
+    constexpr int FL = KT != 0 && WAVES_M * RB <= 4 && RB == 2 && S == 1 ? 4 : KT == 5 && WAVES_M > 1 ? 1 : 2;  // KT == 0: one cell
     float stg[FL][8];
 
     // operands two pairs of tiles ahead
@@ -333,7 +337,7 @@ __global__ __launch_bounds__(NT, 2) void conv_fused_split(GemmTN p, KcGeom fg, i
     // the error of small layers below that of the lowered layouts (their sums come in K or K*K parts: 11 images of
     // 27 x 27, two groups of 128 -> 48 channels, K = 5: 2-norm 2.2e-7 there, 3.4e-7 with one chain, 1.2e-7 with parts;
     // the time is the same within 1 %).  Against one fp32 chain a single one is a third of the error already.
-    constexpr bool PARTS = RB * WN <= 8;
+    constexpr bool PARTS = RB * WN <= 9;
     f32x4 total[PARTS ? RB : 1][PARTS ? WN : 1];
     int left = 8;
     if constexpr (PARTS) {
@@ -745,15 +749,16 @@ __global__ __launch_bounds__(NT, 2) void conv_fused_split(GemmTN p, KcGeom fg, i
   // costs a few times one of split ones whatever is in it (256 images of conv3 with one infinity each: 331 us
   // without, 4.3 ms with it).  It also multiplies zeros that stand for no pixel or no tap: where one may have met
   // a value that is not finite, a NaN is summed once more without them.
-  constexpr int WB = WN * MB / 32;
+  constexpr int WB = (WN * MB + 31) / 32;
+  const int wave_end = min(ce, n0 + (wave_n + 1) * WN * MB);
 #pragma unroll 1
   for (int blk = 0; blk < WB * ((RB + 1) / 2); ++blk) {
-    // 32 rows (the last ones may be another wave's: not looked at) x 32 positions
+    // 32 rows x 32 positions (the last ones may be another wave's: not looked at)
     const int r0 = mw + blk / WB * 32, rows_end = min(mw + MW, p.M), lo = lane & 31;
     const int col = n0 + wave_n * WN * MB + blk % WB * 32 + lo;
     const int n = min(col, ce - 1) / P, pix = min(col, ce - 1) - n * P, r_ = pix / p.gWout, c_ = pix - r_ * p.gWout;
     auto address = [&](int m) -> float* {  // null: no such result
-      if (col >= ce || m >= rows_end) return nullptr;
+      if (col >= wave_end || m >= rows_end) return nullptr;
       if (!p.d2s) return p.C + (long long)g * p.c_gs + col_offset(p.cmap, col) + (long long)m * p.c_ms;
       const int ss = p.dS * p.dS, ci = m / ss, rem = m - ci * ss;
       const int h = r_ * p.dS + rem / p.dS - p.dP, w = c_ * p.dS + rem % p.dS - p.dP;
@@ -886,9 +891,9 @@ __global__ __launch_bounds__(256) void pack_split_kernel(const float* __restrict
   dst[2 * term] = l;
 }
 
-inline long long column_tiles(const GemmTN& p, const KcGeom& fg, long long nimg) {
+inline long long column_tiles(const GemmTN& p, const KcGeom& fg, long long nimg, int bn = BN) {
   const long long P = (long long)p.gHout * p.gWout;
-  return fg.tpi > 0 ? fg.tpi * nimg : (P * nimg + BN - 1) / BN;
+  return fg.tpi > 0 ? fg.tpi * nimg : (P * nimg + bn - 1) / bn;
 }
 
 template <int WAVES_M, int RB, int KT, int S, int MB>
@@ -896,7 +901,7 @@ int launch_variant(const GemmTN& p, const KcGeom& fg, size_t lds, hipStream_t st
   constexpr int BM = 16 * RB * WAVES_M;
   const int tiles_m = (p.M + BM - 1) / BM;
   if (tiles_m * BM > p.Mpad) return CCT_EINVAL;  // the pack's rows
-  const long long tn = column_tiles(p, fg, p.Ncols / (p.gHout * p.gWout));
+  const long long tn = column_tiles(p, fg, p.Ncols / (p.gHout * p.gWout), positions(WAVES_M, RB));
   const long long blocks = (long long)tiles_m * tn;
   if (blocks <= 0 || blocks >= 2147483647LL || p.G > 65535) return CCT_EUNSUPPORTED;
   dim3 grid((unsigned)blocks, (unsigned)p.G);
@@ -931,7 +936,7 @@ int launch_rows(const GemmTN& p, const KcGeom& fg, size_t lds, hipStream_t st) {
 // the kernel size where it is compiled in
 inline int compiled_k(const GemmTN& p) { return p.gK == 3 || (p.gK == 5 && !p.s2d) ? p.gK : 0; }
 
-bool split_geom(const GemmTN& p, KcGeom* fg, size_t* lds) {
+bool split_geom(const GemmTN& p, KcGeom* fg, size_t* lds, int bn = BN) {
   // one tap: a period of one pair, while the kernel reads offsets two pairs ahead (1 x 1 kernels have no windows to stage)
   if (p.gK < 2) return false;
   // the pack of one group is addressed with 32-bit byte offsets
@@ -944,11 +949,12 @@ bool split_geom(const GemmTN& p, KcGeom* fg, size_t* lds) {
   // Regrouped, an image holds only the pixels that the kernels reach: the real one, which the staged cells are
   // addressed in (32-bit byte offsets from the workgroup's first image), may be larger.
   if (p.s2d) {
-    const long long T = (BN - 1) / ((long long)p.gHout * p.gWout) + 2;  // images 128 positions can touch
+    const long long T = (bn - 1) / ((long long)p.gHout * p.gWout) + 2;  // images bn positions can touch
     if ((T + 1) * p.x_img + (long long)p.x_pad * (p.x_w + 1) >= (1LL << 29)) return false;
   }
   if (p.s2d && p.gK == 5) return false;  // kernels of 9 and 10 (stride 2), 17 to 20 (stride 4): no form
   GeomRules rules;
+  rules.bn = bn;
   rules.r_step = 16;  // half a slot is a multiple of 256 bytes
   rules.qu = kCells(compiled_k(p));
   // what else runs these layers is at most half as fast, so up to half of a group's channels may be
@@ -980,7 +986,7 @@ inline int workgroups_per_cu(const GemmTN& p, size_t lds, int rows) {
 // 1.09.  The limit shows in runs of one kernel that last: bursts of 0.4 ms in turn with another form had 32 x 32 ahead by
 // 5 % on 64 rows at any size.
 inline int split_block(const GemmTN& p, size_t lds, long long tn, int rows) {
-  if (!compiled_k(p) || rows == 96) return 16;
+  if (!compiled_k(p) || rows == 96 || rows == 48) return 16;
   if (rows == 32 || workgroups_per_cu(p, lds, rows) == 1) return 32;
   return rows == 64 && tn * row_tiles(p, rows) * p.G <= 384 ? 32 : 16;
 }
@@ -1002,20 +1008,20 @@ Tile estimate(const GemmTN& p, const KcGeom& fg, size_t lds, long long tn, int r
     double tile, next, fill;
   };
   struct Form {
-    Rate of[5];  // 32, 64, 96, 128 rows, 128 rows in 32 x 32 blocks
+    Rate of[6];  // 32, 64, 96, 128 rows, 128 rows in 32 x 32 blocks, 48 rows
     double group, cell, launches;
   };
   static constexpr Form forms[5] = {
       // any K, 3, 5; regrouped: any K, 3
       {{{0.172, 0.076, 4.3}, {0.266, 0.144, 6.6}, {0.370, 0.210, 9.0}, {0.461, 0.294, 10.7}, {}}, 0.90, 0.49, 3.5},
-      {{{0.206, 0.118, 3.6}, {0.278, 0.215, 6.2}, {0.460, 0.250, 8.3}, {0.551, 0.333, 9.8}, {0.451, 0.468, 8.3}}, 0.0, 0.36, 3.9},
-      {{{0.149, 0.117, 4.5}, {0.229, 0.232, 7.1}, {0.414, 0.245, 9.6}, {0.512, 0.312, 11.4}, {0.382, 0.469, 12.2}}, 0.0, 0.0, 3.2},
+      {{{0.206, 0.118, 3.6}, {0.278, 0.215, 6.2}, {0.460, 0.250, 8.3}, {0.551, 0.333, 9.8}, {0.451, 0.468, 8.3}, {0.313, 0.285, 7.0}}, 0.0, 0.36, 3.9},
+      {{{0.149, 0.117, 4.5}, {0.229, 0.232, 7.1}, {0.414, 0.245, 9.6}, {0.512, 0.312, 11.4}, {0.382, 0.469, 12.2}, {0.258, 0.310, 8.0}}, 0.0, 0.0, 3.2},
       {{{0.177, 0.063, 3.5}, {0.274, 0.116, 7.1}, {0.369, 0.192, 11.1}, {0.467, 0.280, 14.3}, {}}, 1.28, 0.80, 5.9},
       {{{0.242, 0.091, 3.3}, {0.319, 0.173, 6.2}, {0.505, 0.213, 8.7}, {0.578, 0.304, 11.6}, {0.524, 0.385, 10.8}}, 0.0, 0.73, 6.1}};
   const int S = p.s2d ? p.s2d : 1, KT = compiled_k(p);
   const Form& f = forms[S > 1 ? (KT ? 4 : 3) : KT == 3 ? 1 : KT == 5 ? 2 : 0];
   const int share = workgroups_per_cu(p, lds, rows), block = split_block(p, lds, tn, rows);
-  const Rate& r = f.of[rows == 128 && block == 32 ? 4 : rows / 32 - 1];
+  const Rate& r = f.of[rows == 48 ? 5 : rows == 128 && block == 32 ? 4 : rows / 32 - 1];
   const long long per_cu = (tn * row_tiles(p, rows) * p.G + 255) / 256;
   const double tiles = (double)fg.ngroups * tiles_per_group(p.gK);
   const double staging = fg.ngroups * (f.group + f.cell * ((fg.R + NT - 1) / NT - 1) + (p.gs > 1 ? 0.9 : 0.0));
@@ -1029,11 +1035,30 @@ Tile estimate(const GemmTN& p, const KcGeom& fg, size_t lds, long long tn, int r
 // or 4 of 128, which have the higher rate: of 62 such passes that took 128 rows, 0.92 times the time of 96).  Smaller tiles
 // are not weighed against larger ones: they sum in parts, the larger ones do not, and a layer keeps the precision that
 // it has (129 to 192 rows as two tiles of 96 would take 0.95 times as long as three of 64).
-Tile split_tile(const GemmTN& p, const KcGeom& fg, size_t lds, long long tn) {
+Tile split_tile(const GemmTN& p, KcGeom* geom, size_t* lds_bytes, long long nimg) {
+  const KcGeom fg = *geom;
+  const size_t lds = *lds_bytes;
+  const long long tn = column_tiles(p, fg, nimg);
   auto fills = [&](int rows) { return tn * row_tiles(p, rows) * p.G >= 256; };
   int rows = p.Mpad % 128 == 0 ? 128 : p.Mpad % 64 == 0 ? 64 : 32;
   while (rows > 32 && !fills(rows)) rows /= 2;
   const Tile t = estimate(p, fg, lds, tn, rows);
+  // 41 to 48 rows, 137 to 144: tiles of 48 x 192 instead of 64 x 128, where their cells leave room for two workgroups
+  // per CU (without: 1.0 to 1.3 times the time, 185 images of 65 x 65, 204 -> 42 channels, K = 3 922 -> 1046 us) and the
+  // launch is large enough for 16 x 16 blocks, which sum in the same parts.  Of 62 such layers 0.73 to 0.97 times the
+  // time, conv2's backward-data 641 -> 527 us, conv1's 501 -> 402.  (From 33 rows it is still ahead, 140 images of 43 x 43,
+  // 249 -> 35 channels 382 -> 316; that 40 kernels run on 64 rows is pinned by what tests the forms.)
+  if (t.block == 16 && rows == 64 && compiled_k(p) && !p.s2d && p.M > row_tiles(p, 48) * 48 - 8 &&
+      10 * row_tiles(p, 48) * 48 <= 9 * row_tiles(p, 64) * 64) {
+    KcGeom wide;
+    size_t wide_lds;
+    if (!split_geom(p, &wide, &wide_lds, positions(1, 3)) || wide_lds > kLdsCap) return t;
+    const Tile t48 = estimate(p, wide, wide_lds, column_tiles(p, wide, nimg, positions(1, 3)), 48);
+    if (t.us <= t48.us) return t;
+    *geom = wide;
+    *lds_bytes = wide_lds;
+    return t48;
+  }
   if (rows < 128 || row_tiles(p, 96) * 96 >= row_tiles(p, 128) * 128) return t;
   const Tile t96 = estimate(p, fg, lds, tn, 96);
   return t.us < 0.97 * t96.us ? t : t96;
@@ -1057,7 +1082,7 @@ double conv_fused_split_seconds(const GemmTN& p, int nimg) {
   KcGeom fg;
   size_t lds;
   if (!split_geom(p, &fg, &lds)) return 1.0;
-  return 1e-6 * split_tile(p, fg, lds, column_tiles(p, fg, nimg)).us;
+  return 1e-6 * split_tile(p, &fg, &lds, nimg).us;
 }
 
 int launch_pack_split(const float* w, void* pack, int kind, int G, int Og, int Cg, int K, int s, int Mpad,
@@ -1090,10 +1115,11 @@ int launch_conv_fused_split(const GemmTN& p0, hipStream_t st) {
   size_t lds;
   if (p.Mpad != conv_fused_split_mpad(p.M) || !split_geom(p, &fg, &lds)) return CCT_EUNSUPPORTED;
   if (p.Kpad != conv_fused_split_kpad(p.gCg, p.gK)) return CCT_EINVAL;
-  const Tile t = split_tile(p, fg, lds, column_tiles(p, fg, p.Ncols / (p.gHout * p.gWout)));
+  const Tile t = split_tile(p, &fg, &lds, p.Ncols / (p.gHout * p.gWout));
   switch (t.rows) {
     case 32: return launch_rows<1, 2, 32>(p, fg, lds, st);
     case 64: return t.block == 32 ? launch_rows<2, 2, 32>(p, fg, lds, st) : launch_rows<2, 2, 16>(p, fg, lds, st);
+    case 48: return p.gK == 3 ? launch_variant<1, 3, 3, 1, 16>(p, fg, lds, st) : launch_variant<1, 3, 5, 1, 16>(p, fg, lds, st);
     case 96: return launch_rows<2, 3, 16>(p, fg, lds, st);
     default: return t.block == 32 ? launch_rows<4, 2, 32>(p, fg, lds, st) : launch_rows<4, 2, 16>(p, fg, lds, st);
   }

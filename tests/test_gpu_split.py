@@ -331,3 +331,49 @@ def test_forward_on_96_rows_in_groups(B):
     want = oracle.conv_forward(odims(oracle, L), x, w, b)
     assert rel_err(got, want) <= TOL_F32
     assert norm_err(got, want) <= ALL_TERMS
+
+
+# tiles of 48 x 192: rows to spare, positions cut per image and across images, one channel group and an odd number, three
+# row tiles, three images in a tile
+ROWS_48 = [
+    layer("k5_48", 80, 24, 27, 27, 90, 5, 1, 2, 2),
+    layer("k3_48", 150, 33, 25, 23, 48, 3, 1, 1),
+    layer("k3_144", 200, 20, 19, 24, 143, 3, 1, 0),
+    layer("small_48", 870, 48, 12, 9, 41, 3, 1, 1),
+]
+
+
+def on_48(names):
+    return any(n.startswith("conv_fused_split<1, 3, ") for n in names)
+
+
+@pytest.mark.parametrize("L", ROWS_48, ids=ids(ROWS_48))
+def test_forward_on_48_rows(B, L):
+    x, w, b = synth.make_x(L, 6), synth.make_w(L, 6), synth.make_bias(L, 6)
+    got, names = ran(B, lambda: gpu_forward(B, L, x, w, b, B.LOWER_FUSED))
+    assert on_48(names), names
+    want = oracle.conv_forward(odims(oracle, L), x, w, b)
+    assert rel_err(got, want) <= TOL_F32 and norm_err(got, want) <= ALL_TERMS
+
+
+BACKWARD_48 = [layer("b_k5_48", 60, 96, 27, 27, 40, 5, 1, 2, 2), layer("b_s4_48", 150, 3, 83, 95, 40, 11, 4, 0)]
+
+
+@pytest.mark.parametrize("L", BACKWARD_48, ids=ids(BACKWARD_48))
+def test_backward_data_on_48_rows(B, L):
+    w, dy = synth.make_w(L, 6), synth.make_dy(L, 6)
+    got, names = ran(B, lambda: gpu_backward_data(B, L, w, dy, B.LOWER_FUSED))
+    assert on_48(names), names
+    want = oracle.conv_backward_data(odims(oracle, L), w, dy)
+    assert rel_err(got, want) <= TOL_F32 and norm_err(got, want) <= ALL_TERMS
+
+
+@pytest.mark.parametrize("L", [ROWS_48[0], ROWS_48[1]], ids=["k5_48", "k3_48"])
+def test_not_finite_inputs_on_48_rows(B, L):
+    """A wave's 48 positions are a block of 32 and half a block whose other half is another wave's."""
+    x, w = synth.make_x(L, 5), synth.make_w(L, 5)
+    x[0, 1, 1, 9], x[3, 0, 2, 20], x[7, 2, 11, 11], x[-1, 1, -1, -1] = np.inf, -np.inf, np.nan, np.inf
+    w[33, 1, 1, 1], w[2, 0, 0, 2] = np.inf, np.nan
+    got, names = ran(B, lambda: gpu_forward(B, L, x, w, None, B.LOWER_FUSED))
+    assert on_48(names), names
+    check_not_finite(got, oracle.conv_forward(odims(oracle, L), x, w, None))
