@@ -65,14 +65,22 @@ __global__ __launch_bounds__(256) void bwdw_img_prep(PrepJob j0, PrepJob j1, int
   const int h = hp - j.pad, w = wp - j.pad;
   const bool inside = q < j.pixels && h >= 0 && h < j.H && w >= 0 && w < j.W;
   const long long plane = (long long)j.H * j.W, img = (long long)j.C * plane;
-  const float* src = j.src + (long long)ig * kImg * img + (long long)h * j.W + w;
+  const float* src = j.src + (long long)ig * kImg * img + (long long)tc * kPrepCh * plane;
   const int nv = min(kImg, nimg - ig * kImg);
+  // Buffer loads whose range check supplies the zeros, so that all are on their way before the first is waited for:
+  // with a branch around each, whole groups of them were waited for in turn.  A plane is less than 2^24 pixels: 32-bit
+  // byte offsets inside a tile of channels.
   float v[kPrepCh / 8][kImg];
+  const unsigned first = (unsigned)((cr * (int)plane + h * j.W + w) * 4);
 #pragma unroll
   for (int it = 0; it < kPrepCh / 8; ++it) {
-    const int c = tc * kPrepCh + it * 8 + cr;
+    const unsigned off = inside && tc * kPrepCh + it * 8 + cr < j.C ? first + (unsigned)it * 8u * (unsigned)plane * 4u : 0x80000000u;
 #pragma unroll
-    for (int e = 0; e < kImg; ++e) v[it][e] = inside && c < j.C && e < nv ? src[c * plane + e * img] : 0.f;
+    for (int e = 0; e < kImg; ++e) {
+      const __amdgpu_buffer_rsrc_t rs =
+          __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(src + e * img), 0, e < nv ? 0x7fffffff : 0, 0x00020000);
+      v[it][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (int)off, 0, 0));
+    }
   }
 #pragma unroll
   for (int it = 0; it < kPrepCh / 8; ++it) {

@@ -27,16 +27,25 @@ constexpr int SLOTS = 8;    // columns per stage
 struct GranPrep {
   const float* src;  // [nimg][Ctot][H][W], Cg channels per group
   const float* w;
-  uint4 *xs, *ks;
+  u32x4 *xs, *ks;
   int C, G, Cg, n8, H, W, pad, Wp, pixels;       // n8 = granules of a group's channels
   int M, K, KK, Og_w, Cg_w, flipped;             // kernels: rows per group, w is [G*Og_w][Cg_w][K][K]
   long long x_total, blocks_x;
-  unsigned mWp, mPx;
-  int sWp, sPx;
+  unsigned mWp, mPx, mPer, mN8;                  // by the row width, the pixels, the granules of an image and of a group
+  int sWp, sPx, sPer, sN8;
+  double per_px, per_img;                        // 1 / pixels, 1 / granules of an image
 };
 
-__device__ __forceinline__ uint4 granule_of(const float (&v)[kCh]) {
-  return make_uint4(cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]), cvt_pk_bf16(v[4], v[5]), cvt_pk_bf16(v[6], v[7]));
+// floor(n / d) for n < 2^38, the same in a whole wave, with r = 1.0 / d: the product is off by less than one
+__device__ __forceinline__ long long uniform_div(long long n, int d, double r) {
+  long long q = (long long)((double)n * r);
+  const long long rem = n - q * d;
+  q += rem < 0 ? -1 : rem >= d ? 1 : 0;
+  return (long long)__builtin_amdgcn_readfirstlane((int)(q >> 32)) << 32 | (unsigned)__builtin_amdgcn_readfirstlane((int)q);
+}
+
+__device__ __forceinline__ u32x4 granule_of(const float (&v)[kCh]) {
+  return u32x4{cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]), cvt_pk_bf16(v[4], v[5]), cvt_pk_bf16(v[6], v[7])};
 }
 
 __global__ __launch_bounds__(256) void granule_prep(GranPrep p, int kernel_granules) {
@@ -59,22 +68,30 @@ __global__ __launch_bounds__(256) void granule_prep(GranPrep p, int kernel_granu
     p.ks[t] = granule_of(v);
     return;
   }
-  const long long b = blockIdx.x;
-  const long long t0 = b * 256, plane0 = t0 / p.pixels;  // (image, group, granule) planes
+  // Bound by memory.  64-bit divisions in every lane had been as long as the copy itself: those of a workgroup's first
+  // granule are uniform, the lanes' own start from it.  All loads are on their way at once; zeros come from the buffer's
+  // range check.
+  const long long t0 = (long long)blockIdx.x * 256, plane0 = uniform_div(t0, p.pixels, p.per_px);  // (image, group, granule)
   const int rem = (int)(t0 - plane0 * p.pixels) + threadIdx.x;
   if (t0 + threadIdx.x >= p.x_total) return;
   const int dp = fdiv_u(rem, p.mPx, p.sPx), q = rem - dp * p.pixels;
   const int hp = fdiv_u(q, p.mWp, p.sWp), h = hp - p.pad, w = q - hp * p.Wp - p.pad;
-  const long long plane = plane0 + dp;
   const int per = p.G * p.n8;
-  const long long n = plane / per;
-  const int gc = (int)(plane - n * per), g = gc / p.n8, c0 = (gc - g * p.n8) * kCh;
+  const long long n0 = uniform_div(plane0, per, p.per_img);
+  const int gc0 = (int)(plane0 - n0 * per), g0 = fdiv_u(gc0, p.mN8, p.sN8), ch0 = g0 * p.Cg + (gc0 - g0 * p.n8) * kCh;
+  const int dn = fdiv_u(gc0 + dp, p.mPer, p.sPer), gc = gc0 + dp - dn * per, g = fdiv_u(gc, p.mN8, p.sN8);
+  const int c0 = (gc - g * p.n8) * kCh, ch = g * p.Cg + c0;
   const bool inside = h >= 0 && h < p.H && w >= 0 && w < p.W;
+  // 32-bit byte offsets from the first granule's channels: more than two granules only of planes of up to 256 pixels
   const long long HW = (long long)p.H * p.W;
-  const float* s = p.src + (n * p.C + (long long)g * p.Cg + c0) * HW + (long long)h * p.W + w;
+  const __amdgpu_buffer_rsrc_t rs =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p.src + (n0 * p.C + ch0) * HW), 0, 0x7fffffff, 0x00020000);
+  const unsigned first = (unsigned)(((dn * p.C + ch - ch0) * (int)HW + h * p.W + w) * 4);
   float v[kCh];
 #pragma unroll
-  for (int e = 0; e < kCh; ++e) v[e] = inside && c0 + e < p.Cg ? s[e * HW] : 0.f;
+  for (int e = 0; e < kCh; ++e)
+    v[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+        rs, (int)(inside && c0 + e < p.Cg ? first + (unsigned)e * (unsigned)HW * 4u : 0x80000000u), 0, 0));
   p.xs[t0 + threadIdx.x] = granule_of(v);
 }
 
@@ -202,8 +219,8 @@ int launch_granules(const cct_conv_desc_t& d, int pass, const GranulesPlan& P, i
   GranPrep q;
   memset(&q, 0, sizeof(q));
   q.src = in; q.w = w;
-  q.xs = reinterpret_cast<uint4*>(ws + P.xs_off);
-  q.ks = reinterpret_cast<uint4*>(ws + P.ks_off);
+  q.xs = reinterpret_cast<u32x4*>(ws + P.xs_off);
+  q.ks = reinterpret_cast<u32x4*>(ws + P.ks_off);
   q.C = c.C; q.G = d.groups; q.Cg = c.Cg; q.n8 = n8; q.H = c.H; q.W = c.W; q.pad = c.pad;
   q.Wp = c.W + 2 * c.pad;
   q.pixels = (c.H + 2 * c.pad) * q.Wp;
@@ -213,6 +230,10 @@ int launch_granules(const cct_conv_desc_t& d, int pass, const GranulesPlan& P, i
   q.blocks_x = (q.x_total + 255) / 256;
   make_fastdiv_parts(q.Wp, &q.mWp, &q.sWp);
   make_fastdiv_parts(q.pixels, &q.mPx, &q.sPx);
+  make_fastdiv_parts(d.groups * n8, &q.mPer, &q.sPer);
+  make_fastdiv_parts(n8, &q.mN8, &q.sN8);
+  q.per_px = 1.0 / q.pixels;
+  q.per_img = 1.0 / (d.groups * n8);
   const int kg = d.groups * n8 * KK * c.M;
   const long long blocks = q.blocks_x + (kg + 255) / 256;
   if (blocks >= 2147483647LL) return CCT_EUNSUPPORTED;
