@@ -723,22 +723,19 @@ __global__ __launch_bounds__(NT, 2) void conv_fused_split(GemmTN p, KcGeom fg, i
     float* __restrict__ C = p.C + (long long)g * p.c_gs;
     const float* bias = p.bias ? p.bias + (long long)g * p.bias_gs : nullptr;
     const bool full_m = m0 + BM <= p.M;
+    float bv[QB * 4];
+    load_bias(bv, bias, p.M - 1, [&](int r) { return mw + row4 + quad(r / 4) + r % 4; });
 #pragma unroll
     for (int j = 0; j < WN; ++j) {
       const int col = n0 + bn + j * MB;
       if (col >= ce) continue;
       float* __restrict__ cl = C + col_offset(p.cmap, col) + (long long)(mw + row4) * p.c_ms;
-      const float* bl = bias ? bias + mw + row4 : nullptr;
 #pragma unroll
       for (int i = 0; i < QB; ++i)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int row = quad(i) + r;  // relative to mw + row4
-          if (full_m || mw + row + row4 < p.M) {
-            float v = out[i][j][r];
-            if (bl) v += bl[row];
-            cl[(long long)row * p.c_ms] = v;
-          }
+          if (full_m || mw + row + row4 < p.M) cl[(long long)row * p.c_ms] = out[i][j][r] + bv[i * 4 + r];
         }
     }
   }

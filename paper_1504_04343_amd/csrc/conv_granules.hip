@@ -145,15 +145,22 @@ __global__ __launch_bounds__(BM * 4, 2) void conv_granules(GranGemm p) {
   });
 
   const float* bias = p.bias ? p.bias + (long long)g * p.M : nullptr;
+  const int row0 = m0 + gp.row(0, 0);
+  float bv[GP::RB * 16];
+  load_bias(bv, bias, p.M - 1, [&](int r) { return m0 + gp.row(r / 16, r % 16); });
   float* __restrict__ out = p.out + g * p.out_group;
-  gp.for_each([&](int row, int column, float v) {
-    const int m = m0 + row, pos = n0 + column;
-    if (m < p.M && pos < p.npos) {
-      const int n = fdiv_u(pos, p.mP, p.sP);
-      if (bias) v += bias[m];
-      out[n * p.out_img + (long long)m * p.P + (pos - n * p.P)] = v;
-    }
-  });
+#pragma unroll
+  for (int j = 0; j < GP::JB; ++j) {
+    const int pos = n0 + gp.column(j);
+    if (pos >= p.npos) continue;
+    const int n = fdiv_u(pos, p.mP, p.sP);
+    float* __restrict__ at = out + n * p.out_img + (pos - n * p.P) + (long long)row0 * p.P;
+#pragma unroll
+    for (int i = 0; i < GP::RB; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (m0 + gp.row(i, r) < p.M) at[(long long)(gp.row(i, r) - gp.row(0, 0)) * p.P] = gp.acc[i][j][r] + bv[i * 16 + r];
+  }
 }
 
 template <int BM>

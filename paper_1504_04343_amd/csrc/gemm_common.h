@@ -18,6 +18,19 @@ __device__ __forceinline__ int fdiv_u(int n, unsigned M, int sh) {
   return (int)(((unsigned long long)(unsigned)n * M) >> sh);
 }
 
+// The bias values of a lane's rows row(0) .. row(N - 1) (those past `last` repeat it), or what adds nothing.  Loaded before
+// the first store: a load between the stores is waited for together with all stores before it, one trip to memory for every
+// result (conv4 at batch 256 with bf16 operands: 82 -> 71 us).
+template <int N, class Row>
+__device__ __forceinline__ void load_bias(float (&v)[N], const float* bias, int last, Row row) {
+#pragma unroll
+  for (int r = 0; r < N; ++r) v[r] = -0.f;
+  if (bias) {
+#pragma unroll
+    for (int r = 0; r < N; ++r) v[r] = bias[min(row(r), last)];
+  }
+}
+
 __device__ __forceinline__ long long col_offset(const ColMap& cm, int col) {
   const int n = fdiv_u(col, cm.divM, cm.divsh);
   return (long long)n * cm.img_stride + (col - n * cm.P);

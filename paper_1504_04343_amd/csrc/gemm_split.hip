@@ -366,7 +366,10 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
   const bool both = __all(o1 == o0 + 1 && live[1]);
   float* __restrict__ cl0 = C + o0 + (long long)mw * p.c_ms;
   float* __restrict__ cl1 = C + o1 + (long long)mw * p.c_ms;
-  const float cb0 = bias && p.bias_gs < 0 ? bias[col[0]] : 0.f, cb1 = bias && p.bias_gs < 0 ? bias[col[1]] : 0.f;
+  const bool by_col = bias && p.bias_gs < 0;
+  const float cb0 = by_col ? bias[col[0]] : -0.f, cb1 = by_col ? bias[col[1]] : -0.f;
+  float bv[RB * 4];
+  load_bias(bv, by_col ? nullptr : bias, p.M - 1, [&](int r) { return mw + r / 4 * 16 + r % 4; });
 #pragma unroll
   for (int i = 0; i < RB; ++i)
 #pragma unroll
@@ -380,11 +383,8 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
         v[j] *= kSplitUnscale;
       }
       if (m >= p.M) continue;
-      if (bias) {
-        const float rb = p.bias_gs < 0 ? 0.f : bias[m];
-        v[0] += p.bias_gs < 0 ? cb0 : rb;
-        v[1] += p.bias_gs < 0 ? cb1 : rb;
-      }
+      v[0] += by_col ? cb0 : bv[i * 4 + r];
+      v[1] += by_col ? cb1 : bv[i * 4 + r];
       const long long row = (long long)(i * 16 + r) * p.c_ms;
       if (both) {
         *reinterpret_cast<f32x2u*>(cl0 + row) = f32x2u{v[0], v[1]};

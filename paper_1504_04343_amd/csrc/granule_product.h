@@ -176,10 +176,16 @@ struct GranuleProduct {
     }
   }
 
+  // the row of result r of block row i, the column of block column j: relative to the workgroup's tile; four consecutive
+  // rows per lane and quad of registers
+  __device__ __forceinline__ int row(int i, int r) const {
+    return wave() / WAVES_N * (MB * RB) + i * MB + r / 4 * 8 + ((int)threadIdx.x & 63) / MB * 4 + r % 4;
+  }
+  __device__ __forceinline__ int column(int j) const { return wave() % WAVES_N * 64 + j * MB + ((int)threadIdx.x & 63) % MB; }
+
   // f(row, column, value) for every result of the lane, relative to the workgroup's tile
   template <class F>
   __device__ __forceinline__ void for_each(F f) const {
-    const int lane = threadIdx.x & 63, w = wave();
 #pragma unroll
     for (int j = 0; j < JB; ++j)
 #pragma unroll
@@ -188,8 +194,7 @@ struct GranuleProduct {
         for (int r = 0; r < MB * MB / 64; ++r) {
           float v = acc[i][j][r];
           if constexpr (TERMS == 3) v += acc_c[i][j][r];
-          // four consecutive rows per lane and quad of registers
-          f(w / WAVES_N * (MB * RB) + i * MB + r / 4 * 8 + lane / MB * 4 + r % 4, w % WAVES_N * 64 + j * MB + lane % MB, v);
+          f(row(i, r), column(j), v);
         }
   }
 };
