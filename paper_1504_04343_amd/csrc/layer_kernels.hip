@@ -155,7 +155,9 @@ inline bool walk_fits(long long per_plane, long long in_plane, long long out_pla
 // at batch 256 (297 MB in, 143 MB out): 183 us with one dependent load at a time and 64-bit divisions per
 // thread, 144 with all loads of four windows in flight but nine of 4 bytes each, 114 with pairs.
 // PAIRS (K = 3, stride 2, no clipping): a lane loads the first two columns of its window, 8 bytes next to
-// its neighbour's, and takes the third from the neighbour; lanes at the end of a row or wave load it.
+// its neighbour's, and takes the third from the neighbour; lanes at the end of a row or wave load it (the others ask
+// for an offset that the buffer's range check answers: behind a branch every row's load was a trip to memory of its own,
+// 116 -> 99 us).  The last element's window ends its row, so that no lane in use takes a column from one past the end.
 typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));  // 8 bytes, dword aligned
 template <int K, bool CLIP, bool PAIRS = false>
 __global__ __launch_bounds__(TPB) void maxpool_forward_window(const float* __restrict__ x, float* __restrict__ y,
@@ -169,6 +171,7 @@ __global__ __launch_bounds__(TPB) void maxpool_forward_window(const float* __res
     *h1 = min(r * g.s - g.p + K, g.H) - 1;
     *w1 = min(q * g.s - g.p + K, g.W) - 1;
   };
+  auto edge = [&](int q) { return (threadIdx.x & 63) == 63 || q == g.Wo - 1; };
   // offset of a pixel from the window's first one
   auto off = [&](int e, int h0, int w0, int h1, int w1) {
     const int i = e / K, j = e % K;
@@ -182,14 +185,16 @@ __global__ __launch_bounds__(TPB) void maxpool_forward_window(const float* __res
         const float* __restrict__ xp = x + plane0 * P;
         const unsigned base = (unsigned)(dp * P + h0 * g.W + w0);
         if constexpr (PAIRS) {
-          const bool edge = (threadIdx.x & 63) == 63 || q == g.Wo - 1;
+          const __amdgpu_buffer_rsrc_t rs =
+              __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(xp), 0, 0x7fffffff, 0x00020000);
 #pragma unroll
           for (int i = 0; i < 3; ++i) {
-            const f32x2u two = *reinterpret_cast<const f32x2u*>(xp + base + (unsigned)(i * g.W));
+            const unsigned at = (base + (unsigned)(i * g.W)) * 4u;
+            const f32x2u two = __builtin_bit_cast(f32x2u, __builtin_amdgcn_raw_buffer_load_b64(rs, (int)at, 0, 0));
             v[u][3 * i] = two[0];
             v[u][3 * i + 1] = two[1];
-            v[u][3 * i + 2] = __shfl_down(two[0], 1, 64);
-            if (edge) v[u][3 * i + 2] = xp[base + (unsigned)(i * g.W + 2)];
+            v[u][3 * i + 2] = __builtin_bit_cast(
+                float, __builtin_amdgcn_raw_buffer_load_b32(rs, (int)(edge(q) ? at + 8u : 0x80000000u), 0, 0));
           }
           return;
         }
@@ -199,6 +204,13 @@ __global__ __launch_bounds__(TPB) void maxpool_forward_window(const float* __res
       [&](int u, long long plane0, int dp, int r, int q) {
         int h0, w0, h1, w1;
         corner(r, q, &h0, &w0, &h1, &w1);
+        if constexpr (PAIRS) {
+#pragma unroll
+          for (int i = 0; i < 3; ++i) {
+            const float next = __shfl_down(v[u][3 * i], 1, 64);
+            v[u][3 * i + 2] = edge(q) ? v[u][3 * i + 2] : next;
+          }
+        }
         float bv = v[u][0];
         int best = 0;
 #pragma unroll
