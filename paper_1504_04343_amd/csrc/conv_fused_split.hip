@@ -3,7 +3,7 @@
 // bf16 MFMAs (split_bf16.h).
 //
 // Product: C[m][pos] = sum_{grp, tap, c} K^[grp][tap][m][c] * xpad[n, grp*16 + c, r*s + i, c*s + j]
-//   - a workgroup owns BM rows x 128 consecutive positions (48 rows: x 192); a wave owns 32 or 48 rows x (all |
+//   - a workgroup owns BM rows x 128 consecutive positions (48 rows: x 192, 64: also x 160); a wave owns 32 or 48 rows x (all |
 //     half | a quarter of them) positions, two accumulators per block of results;
 //   - per channel group of 16 it stages the zero-padded input rows its positions can touch as cells
 //     (row, column) in a two-slot LDS ring, split while they are staged.  A cell is three terms of 16 bytes
@@ -87,18 +87,17 @@ __device__ __forceinline__ const float* pixel_of(const GemmTN& p, int g, int n, 
          (long long)((g * p.gCg + ch) / (S * S)) * p.x_plane + (long long)h * p.x_w + w;
 }
 
-// positions of a workgroup: four waves side by side on 48 rows take 48 each
-constexpr int positions(int WAVES_M, int RB) { return WAVES_M == 1 && RB == 3 ? 192 : BN; }
+// positions of a workgroup on 48 rows, four waves with 48 each, and of the wide form on 64 rows, two with 80
+constexpr int kWide48 = 192, kWide64 = 160;
 // cells per thread: sizes that are not compiled in take a third one (7 x 7 windows on wide rows)
 constexpr int kCells(int KT) { return KT ? 2 : 3; }
 
-template <int WAVES_M, int RB, int KT, int S, int MB>
+template <int WAVES_M, int RB, int KT, int S, int MB, int BN>
 __global__ __launch_bounds__(NT, 2) void conv_fused_split(GemmTN p, KcGeom fg, int tiles_m, int tiles_n) {
   constexpr int QU = kCells(KT);  // cells per thread and slot
   constexpr int MW = 16 * RB;     // rows of a wave
   constexpr int BM = MW * WAVES_M;
   constexpr int WAVES_N = 4 / WAVES_M;
-  constexpr int BN = positions(WAVES_M, RB);
   constexpr int WN = BN / (MB * WAVES_N);  // blocks of MB positions of a wave
   constexpr int QB = MW * MB / 256;        // a lane's results in a block column: quads of consecutive rows
   static_assert(WAVES_M * WAVES_N == 4, "4 waves per workgroup");
@@ -305,7 +304,7 @@ __global__ __launch_bounds__(NT, 2) void conv_fused_split(GemmTN p, KcGeom fg, i
     // The next group's four steps, FL at a time: loaded before one pair of tiles, stored before a later one, so that
     // the MFMAs between cover the way to memory.  Register budget decides FL; where it is short, 5 x 5 kernels have
     // the tiles to go one by one.
-    constexpr int FL = KT != 0 && WAVES_M * RB <= 4 && RB == 2 && S == 1 ? 4 : KT == 5 && WAVES_M > 1 ? 1 : 2;  // KT == 0: one cell
+    constexpr int FL = KT != 0 && WAVES_M * RB <= 4 && RB == 2 && S == 1 && WN < 5 ? 4 : KT == 5 && RB * WN > 10 ? 1 : 2;  // KT == 0: one cell
     float stg[FL][8];
 
     // operands two pairs of tiles ahead
@@ -337,7 +336,7 @@ __global__ __launch_bounds__(NT, 2) void conv_fused_split(GemmTN p, KcGeom fg, i
     // the error of small layers below that of the lowered layouts (their sums come in K or K*K parts: 11 images of
     // 27 x 27, two groups of 128 -> 48 channels, K = 5: 2-norm 2.2e-7 there, 3.4e-7 with one chain, 1.2e-7 with parts;
     // the time is the same within 1 %).  Against one fp32 chain a single one is a third of the error already.
-    constexpr bool PARTS = RB * WN <= 9;
+    constexpr bool PARTS = RB * WN <= 10;
     f32x4 total[PARTS ? RB : 1][PARTS ? WN : 1];
     int left = 8;
     if constexpr (PARTS) {
@@ -893,12 +892,12 @@ inline long long column_tiles(const GemmTN& p, const KcGeom& fg, long long nimg,
   return fg.tpi > 0 ? fg.tpi * nimg : (P * nimg + bn - 1) / bn;
 }
 
-template <int WAVES_M, int RB, int KT, int S, int MB>
+template <int WAVES_M, int RB, int KT, int S, int MB, int POS = BN>
 int launch_variant(const GemmTN& p, const KcGeom& fg, size_t lds, hipStream_t st) {
   constexpr int BM = 16 * RB * WAVES_M;
   const int tiles_m = (p.M + BM - 1) / BM;
   if (tiles_m * BM > p.Mpad) return CCT_EINVAL;  // the pack's rows
-  const long long tn = column_tiles(p, fg, p.Ncols / (p.gHout * p.gWout), positions(WAVES_M, RB));
+  const long long tn = column_tiles(p, fg, p.Ncols / (p.gHout * p.gWout), POS);
   const long long blocks = (long long)tiles_m * tn;
   if (blocks <= 0 || blocks >= 2147483647LL || p.G > 65535) return CCT_EUNSUPPORTED;
   dim3 grid((unsigned)blocks, (unsigned)p.G);
@@ -907,8 +906,9 @@ int launch_variant(const GemmTN& p, const KcGeom& fg, size_t lds, hipStream_t st
   const double y_bytes = p.d2s ? 4.0 * nimg * p.dCtot * p.dH * p.dW : 4.0 * (double)p.M * p.Ncols * p.G;
   ProfScope ps(p.prof_flops > 0 ? p.prof_flops : 2.0 * p.M * p.Ncols * p.Kdim * p.G,
                x_bytes + y_bytes + 4.0 * (double)p.M * p.Kdim * p.G, st,
-               "conv_fused_split<%d, %d, %d, %d, %d>%s", WAVES_M, RB, KT, S, MB, p.d2s ? " strided" : "");
-  constexpr auto kern = conv_fused_split<WAVES_M, RB, KT, S, MB>;
+               "conv_fused_split<%d, %d, %d, %d, %d%s>%s", WAVES_M, RB, KT, S, MB,
+               POS == kWide64 ? ", wide" : "", p.d2s ? " strided" : "");
+  constexpr auto kern = conv_fused_split<WAVES_M, RB, KT, S, MB, POS>;
   if (const int rc = ensure_dynamic_lds<kern>(2 * kLdsCap)) return rc;
   hipLaunchKernelGGL(kern, grid, dim3(NT), lds, st, p, fg, tiles_m, (int)tn);
   CCT_CHECK_LAUNCH();
@@ -988,10 +988,11 @@ inline int split_block(const GemmTN& p, size_t lds, long long tn, int rows) {
   return rows == 64 && tn * row_tiles(p, rows) * p.G <= 384 ? 32 : 16;
 }
 
-// A launch: rows of a workgroup, edge of the MFMA's blocks, what it is estimated to take.
+// A launch: rows of a workgroup, edge of the MFMA's blocks, what it is estimated to take, kWide64 positions on 64 rows.
 struct Tile {
   int rows, block;
   double us;
+  bool wide;
 };
 
 // Rounds of workgroups, each as long as the chain of one: us per K tile of a workgroup that has its CU alone, what
@@ -1000,31 +1001,32 @@ struct Tile {
 // the pack.  Fitted to 58900 launches of 24800 passes (1 to 512 images of up to 240 x 240, each pass with every tile that
 // it can take), without what memory bounds: off by 5 to 7 % in the mean and by up to 11 to 16 % in nine of ten, by form.
 // 64 rows were fitted in blocks of 32 x 32; in 16 x 16 they are within 5 % of that (split_block).
-Tile estimate(const GemmTN& p, const KcGeom& fg, size_t lds, long long tn, int rows) {
+Tile estimate(const GemmTN& p, const KcGeom& fg, size_t lds, long long tn, int rows, bool wide = false) {
   struct Rate {
     double tile, next, fill;
   };
   struct Form {
-    Rate of[6];  // 32, 64, 96, 128 rows, 128 rows in 32 x 32 blocks, 48 rows
+    Rate of[7];  // 32, 64, 96, 128 rows, 128 rows in 32 x 32 blocks, 48 rows, the wide form
     double group, cell, launches;
   };
   static constexpr Form forms[5] = {
       // any K, 3, 5; regrouped: any K, 3
       {{{0.172, 0.076, 4.3}, {0.266, 0.144, 6.6}, {0.370, 0.210, 9.0}, {0.461, 0.294, 10.7}, {}}, 0.90, 0.49, 3.5},
-      {{{0.206, 0.118, 3.6}, {0.278, 0.215, 6.2}, {0.460, 0.250, 8.3}, {0.551, 0.333, 9.8}, {0.451, 0.468, 8.3}, {0.313, 0.285, 7.0}}, 0.0, 0.36, 3.9},
-      {{{0.149, 0.117, 4.5}, {0.229, 0.232, 7.1}, {0.414, 0.245, 9.6}, {0.512, 0.312, 11.4}, {0.382, 0.469, 12.2}, {0.258, 0.310, 8.0}}, 0.0, 0.0, 3.2},
+      {{{0.206, 0.118, 3.6}, {0.278, 0.215, 6.2}, {0.460, 0.250, 8.3}, {0.551, 0.333, 9.8}, {0.451, 0.468, 8.3}, {0.313, 0.285, 7.0}, {0.348, 0.150, 6.6}}, 0.0, 0.36, 3.9},
+      {{{0.149, 0.117, 4.5}, {0.229, 0.232, 7.1}, {0.414, 0.245, 9.6}, {0.512, 0.312, 11.4}, {0.382, 0.469, 12.2}, {0.258, 0.310, 8.0}, {0.270, 0.175, 7.6}}, 0.0, 0.0, 3.2},
       {{{0.177, 0.063, 3.5}, {0.274, 0.116, 7.1}, {0.369, 0.192, 11.1}, {0.467, 0.280, 14.3}, {}}, 1.28, 0.80, 5.9},
       {{{0.242, 0.091, 3.3}, {0.319, 0.173, 6.2}, {0.505, 0.213, 8.7}, {0.578, 0.304, 11.6}, {0.524, 0.385, 10.8}}, 0.0, 0.73, 6.1}};
   const int S = p.s2d ? p.s2d : 1, KT = compiled_k(p);
   const Form& f = forms[S > 1 ? (KT ? 4 : 3) : KT == 3 ? 1 : KT == 5 ? 2 : 0];
-  const int share = workgroups_per_cu(p, lds, rows), block = split_block(p, lds, tn, rows);
-  const Rate& r = f.of[rows == 48 ? 5 : rows == 128 && block == 32 ? 4 : rows / 32 - 1];
+  const int share = workgroups_per_cu(p, lds, rows), block = wide ? 16 : split_block(p, lds, tn, rows);
+  const Rate& r = f.of[wide ? 6 : rows == 48 ? 5 : rows == 128 && block == 32 ? 4 : rows / 32 - 1];
   const long long per_cu = (tn * row_tiles(p, rows) * p.G + 255) / 256;
   const double tiles = (double)fg.ngroups * tiles_per_group(p.gK);
   const double staging = fg.ngroups * (f.group + f.cell * ((fg.R + NT - 1) / NT - 1) + (p.gs > 1 ? 0.9 : 0.0));
   auto round = [&](long long n) { return n ? tiles * (r.tile + (double)(n - 1) * r.next) + staging + r.fill : 0.0; };
   return {rows, block, (double)(per_cu / share) * round(share) + round(per_cu % share) + f.launches +
-                           9.0e-6 * p.G * p.Mpad * tiles * CG};
+                           9.0e-6 * p.G * p.Mpad * tiles * CG,
+          wide};
 }
 
 // The largest row tile that puts a workgroup on every CU (464 rows, 57 column tiles: 64 rows 18.2 us, 96 23.7).  Where
@@ -1049,12 +1051,30 @@ Tile split_tile(const GemmTN& p, KcGeom* geom, size_t* lds_bytes, long long nimg
       10 * row_tiles(p, 48) * 48 <= 9 * row_tiles(p, 64) * 64) {
     KcGeom wide;
     size_t wide_lds;
-    if (!split_geom(p, &wide, &wide_lds, positions(1, 3)) || wide_lds > kLdsCap) return t;
-    const Tile t48 = estimate(p, wide, wide_lds, column_tiles(p, wide, nimg, positions(1, 3)), 48);
+    if (!split_geom(p, &wide, &wide_lds, kWide48) || wide_lds > kLdsCap) return t;
+    const Tile t48 = estimate(p, wide, wide_lds, column_tiles(p, wide, nimg, kWide48), 48);
     if (t.us <= t48.us) return t;
     *geom = wide;
     *lds_bytes = wide_lds;
     return t48;
+  }
+  // 64 rows x 160 positions instead of x 128 where that saves a round of workgroups or the launch is long, again where 16 x
+  // 16 blocks sum in the same parts: the wave's kernel values serve five blocks instead of four.  Of 90 such layers the
+  // estimates choose the faster one but for 0.1 % of the time in the mean (3.6 % at most): 33 images of 34 x 34, 236 ->
+  // 122 channels, K = 3, 598 workgroups or 478, 84 -> 64 us; 63 of 34 x 34, 241 -> 53, K = 5, 343 -> 265; 65 of 39 x 39,
+  // 268 -> 374 535 -> 486; with as many rounds as before it loses (76 images of 33 x 33, 193 -> 56, 129 -> 147).  Few
+  // channel groups stay, which fill and drain more than they multiply.
+  if (rows == 64 && t.block == 16 && compiled_k(p) && !p.s2d && fg.ngroups > (p.gK == 3 ? 4 : 8)) {
+    KcGeom wide;
+    size_t wide_lds;
+    if (split_geom(p, &wide, &wide_lds, kWide64) && wide_lds <= kLdsCap) {
+      const Tile tw = estimate(p, wide, wide_lds, column_tiles(p, wide, nimg, kWide64), 64, true);
+      if (tw.us < 0.95 * t.us) {
+        *geom = wide;
+        *lds_bytes = wide_lds;
+        return tw;
+      }
+    }
   }
   if (rows < 128 || row_tiles(p, 96) * 96 >= row_tiles(p, 128) * 128) return t;
   const Tile t96 = estimate(p, fg, lds, tn, 96);
@@ -1115,8 +1135,14 @@ int launch_conv_fused_split(const GemmTN& p0, hipStream_t st) {
   const Tile t = split_tile(p, &fg, &lds, p.Ncols / (p.gHout * p.gWout));
   switch (t.rows) {
     case 32: return launch_rows<1, 2, 32>(p, fg, lds, st);
-    case 64: return t.block == 32 ? launch_rows<2, 2, 32>(p, fg, lds, st) : launch_rows<2, 2, 16>(p, fg, lds, st);
-    case 48: return p.gK == 3 ? launch_variant<1, 3, 3, 1, 16>(p, fg, lds, st) : launch_variant<1, 3, 5, 1, 16>(p, fg, lds, st);
+    case 64:
+      if (t.wide)
+        return p.gK == 3 ? launch_variant<2, 2, 3, 1, 16, kWide64>(p, fg, lds, st)
+                         : launch_variant<2, 2, 5, 1, 16, kWide64>(p, fg, lds, st);
+      return t.block == 32 ? launch_rows<2, 2, 32>(p, fg, lds, st) : launch_rows<2, 2, 16>(p, fg, lds, st);
+    case 48:
+      return p.gK == 3 ? launch_variant<1, 3, 3, 1, 16, kWide48>(p, fg, lds, st)
+                       : launch_variant<1, 3, 5, 1, 16, kWide48>(p, fg, lds, st);
     case 96: return launch_rows<2, 3, 16>(p, fg, lds, st);
     default: return t.block == 32 ? launch_rows<4, 2, 32>(p, fg, lds, st) : launch_rows<4, 2, 16>(p, fg, lds, st);
   }

@@ -377,3 +377,18 @@ def test_not_finite_inputs_on_48_rows(B, L):
     got, names = ran(B, lambda: gpu_forward(B, L, x, w, None, B.LOWER_FUSED))
     assert on_48(names), names
     check_not_finite(got, oracle.conv_forward(odims(oracle, L), x, w, None))
+
+
+# tiles of 64 x 160: positions across images and cut per image, rows to spare, channels past a group's last one
+WIDE_64 = [layer("wide_k3", 95, 140, 26, 27, 59, 3, 1, 1), layer("wide_k5", 44, 260, 27, 27, 100, 5, 1, 2, 2)]
+
+
+@pytest.mark.parametrize("L", WIDE_64, ids=ids(WIDE_64))
+def test_forward_on_160_positions(B, L):
+    x, w, b = synth.make_x(L, 6), synth.make_w(L, 6), synth.make_bias(L, 6)
+    got, names = ran(B, lambda: gpu_forward(B, L, x, w, b, B.LOWER_FUSED))
+    assert any("wide" in n for n in names), names
+    want = oracle.conv_forward(odims(oracle, L), x, w, b)
+    assert rel_err(got, want) <= TOL_F32 and norm_err(got, want) <= ALL_TERMS
+    x[0, 1, 1, 9], x[3, 0, 2, 20], x[7, 2, 11, 11], w[33, 1, 1, 1], w[2, 0, 0, 2] = np.inf, -np.inf, np.nan, np.inf, np.nan
+    check_not_finite(gpu_forward(B, L, x, w, None, B.LOWER_FUSED), oracle.conv_forward(odims(oracle, L), x, w, None))
