@@ -81,21 +81,18 @@ __global__ __launch_bounds__(TPB) void fc_sum_splits_kernel(const float* __restr
   const long long t = (long long)blockIdx.x * TPB + threadIdx.x;
   if (t >= total) return;
   const float* src = part + t;
-  float acc = 0.0f;
-  int s = 0;
-  for (; s + 4 <= S; s += 4) {
+  // In 64 bits: 31 parts of 32 kernels each added in 32 are what such a sum's error came from.  Four loads in flight, past
+  // the end the last one again.
+  double acc = 0.0;
+  const float shift = bias ? bias[(int)t - fdiv((int)t, divO) * divO.d] : 0.f;
+  for (int s = 0; s < S; s += 4) {
     float v[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = src[(long long)(s + u) * total];
+    for (int u = 0; u < 4; ++u) v[u] = src[(long long)min(s + u, S - 1) * total];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) acc += v[u];
+    for (int u = 0; u < 4; ++u) acc = s + u < S ? acc + v[u] : acc;
   }
-  for (; s < S; ++s) acc += src[(long long)s * total];
-  if (bias) {
-    const int n = fdiv((int)t, divO);
-    acc += bias[(int)t - n * divO.d];
-  }
-  y[t] = acc;
+  y[t] = (float)(acc + shift);
 }
 
 // dw[o][f] = sum_n dy[n][o] * x[n][f] and dbias[o] = sum_n dy[n][o] over up to 32 images, in fp32: a workgroup owns 8
@@ -163,7 +160,7 @@ __global__ __launch_bounds__(TPB) void fc_outer_kernel(const float* __restrict__
         for (int e = 0; e < 4; ++e) acc[o][e] += t[e];
       }
     };
-    if (live == 4) add(std::integral_constant<bool, true>());
+    if (live == 4 && O >= 64) add(std::integral_constant<bool, true>());
     else add(std::integral_constant<bool, false>());
   }
 #pragma unroll
@@ -186,21 +183,22 @@ __global__ __launch_bounds__(TPB) void fc_outer_kernel(const float* __restrict__
 // chip.  One image of fc6 (151 MB) 38.2 us on 32-row tiles of the matrix cores behind a pack, 31.4 now; 4096 -> 1000
 // 14.8 -> 11; with 16 images registers leave too few waves in flight (41 and 77).
 constexpr int kRowsWaves = 8, kRowsFeatures = 256;
-template <int ROWS>
+template <int ROWS, class Acc = double>
 __global__ __launch_bounds__(64 * kRowsWaves) void gemm_split_k_columns(const float* __restrict__ w, const float* __restrict__ dy,
                                                                   float* __restrict__ out, int N, int O, int F, int share) {
-  __shared__ float red[kRowsWaves][kRowsFeatures];
+  __shared__ double red[kRowsWaves][kRowsFeatures];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int f0 = blockIdx.x * kRowsFeatures + lane * 4, fb = min(f0, F - 1);
   const bool whole = f0 + 4 <= F;
   const int per = (share + kRowsWaves - 1) / kRowsWaves;
   const int o_begin = blockIdx.y * share + wave * per, o_end = min(min(O, (int)(blockIdx.y + 1) * share), o_begin + per);
-  float acc[ROWS][4];
+  Acc acc[ROWS][4];
 #pragma unroll
   for (int n = 0; n < ROWS; ++n)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) acc[n][e] = 0.f;
-  // 4 kernels at a time: their loads in flight together, their products summed before they are added
+    for (int e = 0; e < 4; ++e) acc[n][e] = 0;
+  // 4 kernels at a time: their loads in flight together, their products summed in 32 bits, where there are many, and all in
+  // 64 (8 images of 512 -> 64: 2-norm 6.8e-8 in 32 bits, 4.8e-8 so and on the matrix cores)
   for (int o = o_begin; o < o_end; o += 4) {
     float v[4][4];
 #pragma unroll
@@ -221,18 +219,25 @@ __global__ __launch_bounds__(64 * kRowsWaves) void gemm_split_k_columns(const fl
 #pragma unroll
       for (int n = 0; n < ROWS; ++n) {
         const float* d = dy + (long long)min(n, N - 1) * O + o;
-        float t[4] = {0.f, 0.f, 0.f, 0.f};
+        if constexpr (FULL) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          if (!FULL && u >= live) break;
+          for (int e = 0; e < 4; ++e) {
+            float four = d[0] * v[0][e];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) t[e] = fmaf(d[u], v[u][e], t[e]);
+            for (int u = 1; u < 4; ++u) four = fmaf(d[u], v[u][e], four);
+            acc[n][e] += four;
+          }
+        } else {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            if (u >= live) break;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[n][e] = fma((Acc)d[u], (Acc)v[u][e], acc[n][e]);
+          }
         }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc[n][e] += t[e];
       }
     };
-    if (live == 4) add(std::integral_constant<bool, true>());
+    if (live == 4 && O >= 64) add(std::integral_constant<bool, true>());
     else add(std::integral_constant<bool, false>());
   }
   // the waves' sums, a row of dx at a time
@@ -241,10 +246,11 @@ __global__ __launch_bounds__(64 * kRowsWaves) void gemm_split_k_columns(const fl
 #pragma unroll
   for (int n = 0; n < ROWS; ++n) {
     if (n < N) {  // the same for all
-      *reinterpret_cast<float4*>(&red[wave][lane * 4]) = make_float4(acc[n][0], acc[n][1], acc[n][2], acc[n][3]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) red[wave][lane * 4 + e] = acc[n][e];
       __syncthreads();
       if (t < kRowsFeatures && f < F)
-        to[(long long)n * F + f] = ((red[0][t] + red[1][t]) + (red[2][t] + red[3][t])) + ((red[4][t] + red[5][t]) + (red[6][t] + red[7][t]));
+        to[(long long)n * F + f] = (float)(((red[0][t] + red[1][t]) + (red[2][t] + red[3][t])) + ((red[4][t] + red[5][t]) + (red[6][t] + red[7][t])));
       __syncthreads();
     }
   }
@@ -264,7 +270,9 @@ int launch_split_k_columns(const float* w, const float* dy, float* out, int N, i
   if (N <= 1) hipLaunchKernelGGL(gemm_split_k_columns<1>, grid, block, 0, st, w, dy, out, N, O, F, share);
   else if (N <= 2) hipLaunchKernelGGL(gemm_split_k_columns<2>, grid, block, 0, st, w, dy, out, N, O, F, share);
   else if (N <= 4) hipLaunchKernelGGL(gemm_split_k_columns<4>, grid, block, 0, st, w, dy, out, N, O, F, share);
-  else hipLaunchKernelGGL(gemm_split_k_columns<8>, grid, block, 0, st, w, dy, out, N, O, F, share);
+  // (8 rows of 64-bit sums leave too few waves in flight, fc6 38 -> 53 us; in 32 bits its error is 1.1e-7, 1.2e-7 on the matrix cores)
+  else if (O < 512) hipLaunchKernelGGL(gemm_split_k_columns<8>, grid, block, 0, st, w, dy, out, N, O, F, share);
+  else hipLaunchKernelGGL((gemm_split_k_columns<8, float>), grid, block, 0, st, w, dy, out, N, O, F, share);
   CCT_CHECK_LAUNCH();
   return CCT_OK;
 }

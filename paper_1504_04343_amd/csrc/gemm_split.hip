@@ -448,8 +448,8 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
 // split over its lanes and 8 waves, 4 consecutive k each, whose sums meet in a tree.  Bound by reading B once: a matrix
 // instruction would be 16 or 32 rows of which most are none, and splitting B costs more than 8 multiplications.
 // One image: fc6's 151 MB 46.3 us on gemm_split with its partial sums and their launch, 28.9 now; 4096 -> 1000 12.9 -> 6.7.
-// Up to 4 rows at any size (4 rows of fc6 41.8 -> 36.3), up to 8 where B has up to 2^24 values in rows of 256 and more: beyond that each
-// column's share of A, which comes from the L1, weighs (8 rows, 4096 -> 4096 22.9 and 23.8, 9216 -> 4096 41.6 and 51.1).
+// Up to 4 rows at any size (4 rows of fc6 41.8 -> 36.3), up to 8 where B has up to 2^22 values in rows of 256 and more: beyond that each
+// column's share of A, which comes from the L1, weighs (8 rows, 4096 -> 4096 27.9 and 23.8, 9216 -> 4096 51.1 and 41.6).
 constexpr int kCols = 4, kWaves = 8;
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // 16 bytes, dword aligned
 struct FewRows {
@@ -458,12 +458,12 @@ struct FewRows {
   int M, N, K;
 };
 template <int N, int OFF>
-__device__ __forceinline__ void fold(float* v, int lane, int* mine) {
+__device__ __forceinline__ void fold(double* v, int lane, int* mine) {
   if constexpr (N > 1) {
     const bool upper = lane & OFF;
 #pragma unroll
     for (int q = 0; q < N / 2; ++q) {
-      const float keep = upper ? v[q + N / 2] : v[q], give = upper ? v[q] : v[q + N / 2];
+      const double keep = upper ? v[q + N / 2] : v[q], give = upper ? v[q] : v[q + N / 2];
       v[q] = keep + __shfl_xor(give, OFF, 64);
     }
     *mine += upper ? N / 2 : 0;
@@ -474,7 +474,7 @@ __device__ __forceinline__ void fold(float* v, int lane, int* mine) {
 }
 template <int ROWS>
 __global__ __launch_bounds__(64 * kWaves) void gemm_split_k(FewRows p) {
-  __shared__ float red[kWaves][ROWS * kCols];
+  __shared__ double red[kWaves][ROWS * kCols];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int n0 = blockIdx.x * kCols;
   constexpr int STEP = kWaves * 64 * 4;
@@ -483,11 +483,11 @@ __global__ __launch_bounds__(64 * kWaves) void gemm_split_k(FewRows p) {
   for (int m = 0; m < ROWS; ++m) a[m] = p.A + (long long)min(m, p.M - 1) * p.K;
 #pragma unroll
   for (int c = 0; c < kCols; ++c) b[c] = p.B + (long long)min(n0 + c, p.N - 1) * p.K;
-  float acc[ROWS][kCols];
+  double acc[ROWS][kCols];
 #pragma unroll
   for (int m = 0; m < ROWS; ++m)
 #pragma unroll
-    for (int c = 0; c < kCols; ++c) acc[m][c] = 0.f;
+    for (int c = 0; c < kCols; ++c) acc[m][c] = 0.0;
   const int k_first = (wave * 64 + lane) * 4;
   const int whole = p.K / STEP * STEP;  // up to here every lane has its 4
   f32x4 bv[2][kCols], av[2][ROWS];
@@ -497,13 +497,19 @@ __global__ __launch_bounds__(64 * kWaves) void gemm_split_k(FewRows p) {
 #pragma unroll
     for (int m = 0; m < ROWS; ++m) av[set][m] = *reinterpret_cast<const f32x4u*>(a[m] + k);
   };
+  // Sums in 64 bits: lanes' chains and their tree in 32 rounded more than the matrix cores' chains do (2-norm, 2 rows of 136:
+  // 7.0e-8, 5.7e-8 there, 2.4e-8 so; 3 of 1000 with 32 columns 1.3e-7, 8.3e-8, 2.6e-8).  In whole steps, which are of rows of
+  // 2048 and more, four products are summed in 32 first (4.7e-8; 4 rows, 4096 -> 4096: 21 us without, 16).
   auto multiply = [&](int set) {
 #pragma unroll
     for (int m = 0; m < ROWS; ++m)
 #pragma unroll
-      for (int c = 0; c < kCols; ++c)
+      for (int c = 0; c < kCols; ++c) {
+        float four = av[set][m][0] * bv[set][c][0];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc[m][c] = fmaf(av[set][m][e], bv[set][c][e], acc[m][c]);
+        for (int e = 1; e < 4; ++e) four = fmaf(av[set][m][e], bv[set][c][e], four);
+        acc[m][c] += four;
+      }
   };
   if (whole) {
     const int last = whole - STEP;
@@ -518,23 +524,28 @@ __global__ __launch_bounds__(64 * kWaves) void gemm_split_k(FewRows p) {
   const int k_rest = whole + k_first;
   if (k_rest + 4 <= p.K) {
     load(0, k_rest);
-    multiply(0);
+#pragma unroll
+    for (int m = 0; m < ROWS; ++m)
+#pragma unroll
+      for (int c = 0; c < kCols; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[m][c] = fma((double)av[0][m][e], (double)bv[0][c][e], acc[m][c]);
   } else {
     for (int k = k_rest; k < p.K; ++k) {
-      float x[ROWS];
+      double x[ROWS];
 #pragma unroll
       for (int m = 0; m < ROWS; ++m) x[m] = a[m][k];
 #pragma unroll
       for (int c = 0; c < kCols; ++c) {
-        const float y = b[c][k];
+        const double y = b[c][k];
 #pragma unroll
-        for (int m = 0; m < ROWS; ++m) acc[m][c] = fmaf(x[m], y, acc[m][c]);
+        for (int m = 0; m < ROWS; ++m) acc[m][c] = fma(x[m], y, acc[m][c]);
       }
     }
   }
   // sums over the lanes: in every step a lane passes on half of its values and keeps the other half
   constexpr int VALUES = ROWS * kCols;
-  float v[VALUES];
+  double v[VALUES];
 #pragma unroll
   for (int q = 0; q < VALUES; ++q) v[q] = acc[q / kCols][q % kCols];
   int mine = 0;
@@ -544,11 +555,11 @@ __global__ __launch_bounds__(64 * kWaves) void gemm_split_k(FewRows p) {
   __syncthreads();
   const int t = threadIdx.x, m = t / kCols, col = n0 + t % kCols;
   if (t >= ROWS * kCols || m >= p.M || col >= p.N) return;
-  float u[kWaves];
+  double u[kWaves];
 #pragma unroll
   for (int w = 0; w < kWaves; ++w) u[w] = red[w][t];
-  const float sum = ((u[0] + u[1]) + (u[2] + u[3])) + ((u[4] + u[5]) + (u[6] + u[7]));
-  p.C[(long long)m * p.N + col] = sum + (p.bias ? p.bias[col] : 0.f);
+  const double sum = ((u[0] + u[1]) + (u[2] + u[3])) + ((u[4] + u[5]) + (u[6] + u[7]));
+  p.C[(long long)m * p.N + col] = (float)(sum + (p.bias ? p.bias[col] : 0.f));
 }
 
 // pack[g][stage][block of 16 rows][term][lane][8] = the terms of src[g * sg + (m / taps) * sm + m % taps + k * sk], zero
@@ -724,7 +735,7 @@ int gemm_split_operand(GemmTN* p, bool bt, const float* src, void* pack, int Kto
   return CCT_OK;
 }
 
-bool gemm_split_k_fits(int M, int N, int K) { return M <= 4 || (M <= 8 && K >= 256 && (long long)N * K <= (1LL << 24)); }
+bool gemm_split_k_fits(int M, int N, int K) { return M <= 4 || (M <= 8 && K >= 256 && (long long)N * K <= (1LL << 22)); }
 
 int launch_gemm_split_k(const float* A, const float* B, const float* bias, float* C, int M, int N, int K, hipStream_t st) {
   if (M < 1 || M > 8 || N < 1 || K < 1) return CCT_EUNSUPPORTED;
