@@ -19,8 +19,8 @@
 //
 // Measured (whole pass with the bias gradient; before: dy and x read in place by fp32 matrix
 // instructions, or bf16 lowered matrices): conv3 at batch 1024 2880 -> 1550 us, of it 1255 the product
-// (244 TFLOP/s of fp32 results, 1460 of bf16 MFMAs: the card's power limit) and 280 the rewriting
-// (3.9 TB/s); conv2 at batch 256 1215 -> 690; conv4 at batch 256 with bf16 operands 355 -> 125.
+// (244 TFLOP/s of fp32 results, 1460 of bf16 MFMAs: the card's power limit) and 240 the rewriting
+// (4.6 TB/s); conv2 at batch 256 1215 -> 690; conv4 at batch 256 with bf16 operands 355 -> 125.
 #include <algorithm>
 
 #include "cct_internal.h"
@@ -67,7 +67,7 @@ __global__ __launch_bounds__(256) void bwdw_img_prep(PrepJob j0, PrepJob j1, int
   const long long plane = (long long)j.H * j.W, img = (long long)j.C * plane;
   const float* src = j.src + (long long)ig * kImg * img + (long long)tc * kPrepCh * plane;
   const int nv = min(kImg, nimg - ig * kImg);
-  // Buffer loads whose range check supplies the zeros, so that all are on their way before the first is waited for:
+  // conv2 at batch 256 145 -> 118 us.  Buffer loads whose range check supplies the zeros, so that all are on their way before the first is waited for:
   // with a branch around each, whole groups of them were waited for in turn.  A plane is less than 2^24 pixels: 32-bit
   // byte offsets inside a tile of channels.
   float v[kPrepCh / 8][kImg];

@@ -8,8 +8,8 @@
 //      neighbouring granules.  The epilogue writes NCHW and adds the bias.
 // The fused kernel (conv_fused_kc_bf16) rounds x again in every workgroup and waits for it once per 16
 // channels; here nothing but operand reads and MFMAs is left in the loop, for one extra pass over x.
-// Measured at batch 256, the pass with its rewriting: conv4 (57.4 GFLOP) forward 170 -> 113 us (of it 88 the
-// product, 650 TFLOP/s), backward-data 157 -> 95; conv2 (115 GFLOP) 244 -> 227 and 251 -> 221; a 1 x 1 layer,
+// Measured at batch 256, the pass with its rewriting: conv4 (57.4 GFLOP) forward 170 -> 96 us (of it 72 the
+// product, 800 TFLOP/s), backward-data 157 -> 95; conv2 (115 GFLOP) 244 -> 227 and 251 -> 221; a 1 x 1 layer,
 // 69 images of 42 x 42, 452 -> 58 channels, 175 -> 95 and 174 -> 74.
 #include <algorithm>
 

@@ -177,7 +177,7 @@ __global__ __launch_bounds__(TPB) void fc_outer_kernel(const float* __restrict__
   }
 }
 
-// dx[n][f] = sum_o dy[n][o] * w[o][f] over up to 8 images, in fp32 (S > 1: one of S shares of the kernels, to part): a
+// dx[n][f] = sum_o dy[n][o] * w[o][f] over up to 8 images (S > 1: one of S shares of the kernels, to part): a
 // workgroup owns 256 features, a lane 4 consecutive ones, its 8 waves share out the kernels; dy's values are the same for a
 // whole wave.  Bound by reading w once; the kernels are split over workgroups where the features are too few to fill the
 // chip.  One image of fc6 (151 MB) 38.2 us on 32-row tiles of the matrix cores behind a pack, 31.4 now; 4096 -> 1000

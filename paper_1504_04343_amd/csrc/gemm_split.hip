@@ -444,10 +444,10 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
 }
 
 // The product of up to 8 rows with a k-contiguous B (a fully connected layer's forward pass on few images) in one launch
-// and in plain fp32: C[m][col] = sum_k A[m][k] * B[col][k] + bias[col].  A workgroup owns 4 columns; the contraction is
+// and without splitting: C[m][col] = sum_k A[m][k] * B[col][k] + bias[col].  A workgroup owns 4 columns; the contraction is
 // split over its lanes and 8 waves, 4 consecutive k each, whose sums meet in a tree.  Bound by reading B once: a matrix
 // instruction would be 16 or 32 rows of which most are none, and splitting B costs more than 8 multiplications.
-// One image: fc6's 151 MB 46.3 us on gemm_split with its partial sums and their launch, 28.9 now; 4096 -> 1000 12.9 -> 6.7.
+// One image: fc6's 151 MB 46.3 us on gemm_split with its partial sums and their launch, 26.9 now; 4096 -> 1000 12.9 -> 6.7.
 // Up to 4 rows at any size (4 rows of fc6 41.8 -> 36.3), up to 8 where B has up to 2^22 values in rows of 256 and more: beyond that each
 // column's share of A, which comes from the L1, weighs (8 rows, 4096 -> 4096 27.9 and 23.8, 9216 -> 4096 51.1 and 41.6).
 constexpr int kCols = 4, kWaves = 8;

@@ -260,3 +260,16 @@ def test_few_images_backward(B, N, F, O):
     assert names == ["fc_outer_kernel"], names
     want = oracle.conv_backward_weights(odims(oracle, L), x, dy)
     assert rel_err(dw, want[0]) <= TOL_F32 and rel_err(db, want[1]) <= TOL_F32
+
+
+@pytest.mark.parametrize("L", [layer("plane9", 310, 40, 3, 3, 50, 1), layer("plane15", 211, 72, 3, 5, 130, 1),
+                               layer("plane25", 101, 40, 5, 5, 33, 1), layer("plane1x7", 333, 33, 1, 7, 70, 1)],
+                         ids=lambda L: L.name)
+def test_odd_planes(B, L):
+    """Planes of an odd number of pixels: pairs of pixels whose last one has no second half from 15 pixels on, single
+    columns below; tiles across images."""
+    x, w, b, dy = synth.make_x(L, 9), synth.make_w(L, 9), synth.make_bias(L, 9), synth.make_dy(L, 9)
+    got, names = ran(B, lambda: gpu_forward(B, L, x, w, b))
+    assert any(n.startswith("gemm_split") for n in names), names
+    assert rel_err(got, oracle.conv_forward(odims(oracle, L), x, w, b)) <= TOL_F32
+    assert rel_err(gpu_backward_data(B, L, w, dy), oracle.conv_backward_data(odims(oracle, L), w, dy)) <= TOL_F32
