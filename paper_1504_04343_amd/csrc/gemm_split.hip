@@ -753,6 +753,17 @@ int launch_gemm_split_k(const float* A, const float* B, const float* bias, float
   return CCT_OK;
 }
 
+// Pairs, unless the planes are so small that the columns which make them even weigh, or these take the count past 32
+// bits (an odd plane's is up to a fifteenth more than the tensor's columns, which may be up to 2^31 - 257).
+int gemm_split_pair_columns(int P, int Ncols, int* pair_P) {
+  *pair_P = 0;
+  if (P == 2147483647) return (Ncols + 1) / 2 * 2;
+  const long long even = P + P % 2, cols = Ncols / P * even;
+  if ((P % 2 && P < 15) || cols > 2147483647LL - (BN - 1)) return 0;
+  *pair_P = (int)even;
+  return (int)cols;
+}
+
 int launch_gemm_split(const GemmTN& p0, int Ktotal, bool bt, hipStream_t st) {
   GemmTN p = p0;
   colmap_prepare(&p.bmap);
@@ -765,15 +776,8 @@ int launch_gemm_split(const GemmTN& p0, int Ktotal, bool bt, hipStream_t st) {
             : p.bmap.P == 2147483647 ? Ktotal * p.b_ks
                                      : (long long)(p.Ncols / p.bmap.P) * p.bmap.img_stride;
   if (bt) return launch_columns<kContiguous>(p, Ktotal, st);
-  // Pairs, unless the planes are so small that the columns which make them even weigh
-  const int P = p.bmap.P;
-  if (P == 2147483647) {
-    p.pair_cols = (p.Ncols + 1) / 2 * 2;
-  } else if (P % 2 == 0 || P >= 15) {
-    p.pair_P = (P + 1) / 2 * 2;
-    p.pair_cols = p.Ncols / P * p.pair_P;
-    make_fastdiv_parts(p.pair_P, &p.pair_M, &p.pair_sh);
-  }
+  p.pair_cols = gemm_split_pair_columns(p.bmap.P, p.Ncols, &p.pair_P);
+  if (p.pair_P) make_fastdiv_parts(p.pair_P, &p.pair_M, &p.pair_sh);
   return p.pair_cols ? launch_columns<kPairs>(p, Ktotal, st) : launch_columns<kColumns>(p, Ktotal, st);
 }
 

@@ -327,3 +327,24 @@ MEASURED = [
 @pytest.mark.parametrize("shape,pass_,fastest", MEASURED, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
 def test_selector_picks_the_measured_layout(B, shape, pass_, fastest):
     assert B.cct_pick_lowering(B.make_desc(*shape), pass_) == fastest
+
+
+def test_pairs_of_columns_stay_within_32_bits(B):
+    """gemm_split takes planes of an odd number of pixels with one column more per image: where that, or the last tile
+    of 128 behind it, leaves 32 bits, the columns go one by one.  Up to 2^31 - 257 of them are accepted."""
+    pair_columns = getattr(ctypes.CDLL(B.LIB_PATH), "_ZN3cct23gemm_split_pair_columnsEiiPi")
+    for P in (15, 17, 63, 169, 46341, 2**20 + 1, 9, 13, 14, 196, 2**31 - 1):
+        step = P if P < 2**31 - 1 else 1
+        most = 2**31 - 257 if P < 2**31 - 1 else 2**29 - 1
+        even = min(P + P % 2, 2**31 - 2)
+        edge = [n // even * step for n in (2**31 - 1 - 128, 2**31 - 1, 2**31 + even)]
+        for n in {step, 7 * step, most // step * step, *(e + k * step for e in edge for k in (-1, 0, 1))}:
+            if not 0 < n <= most:
+                continue
+            pair = ctypes.c_int(-1)
+            got = pair_columns(P, n, ctypes.byref(pair))
+            want = n // P * even if P < 2**31 - 1 else (n + 1) // 2 * 2
+            if (P % 2 and P < 15) or want + 127 > 2**31 - 1:
+                assert (got, pair.value) == (0, 0), (P, n)
+            else:
+                assert (got, pair.value) == (want, even if P < 2**31 - 1 else 0), (P, n)
