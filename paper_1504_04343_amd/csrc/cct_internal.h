@@ -181,9 +181,6 @@ bool gemm_split_fits(const GemmTN& p, bool bt);
 int launch_gemm_split(const GemmTN& p, int Ktotal, bool bt, hipStream_t st);
 // Columns as they are taken in pairs from planes of P pixels (2^31 - 1: no images), *pair_P of an image; 0: one by one.
 int gemm_split_pair_columns(int P, int Ncols, int* pair_P);
-// C[m][n] = sum_k A[m][k] * B[n][k] + bias[n], all compact, for a few rows
-bool gemm_split_k_fits(int M, int N, int K);
-int launch_gemm_split_k(const float* A, const float* B, const float* bias, float* C, int M, int N, int K, hipStream_t st);
 double gemm_split_seconds(bool bt, bool pack, int M, int K, long long cols, long long G);
 // Its operand A(m, k) of group g = src[g*sg + (m / taps)*sm + m % taps + k*sk]: packed into `pack` where that pays (or,
 // without one, never), else read in place.  Sets p's fields for A; the others must be set but for the tensor and the result.

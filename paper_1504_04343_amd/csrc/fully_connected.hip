@@ -95,13 +95,150 @@ __global__ __launch_bounds__(TPB) void fc_sum_splits_kernel(const float* __restr
   y[t] = (float)(acc + shift);
 }
 
+typedef float fc_f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // 16 bytes, dword aligned
+
+// The product of up to 8 rows with a k-contiguous B (a fully connected layer's forward pass on few images) in one launch
+// and without splitting: C[m][col] = sum_k A[m][k] * B[col][k] + bias[col].  A workgroup owns 4 columns; the contraction is
+// split over its lanes and 8 waves, 4 consecutive k each, whose sums meet in a tree.  Bound by reading B once: a matrix
+// instruction would be 16 or 32 rows of which most are none, and splitting B costs more than 8 multiplications.
+// One image: fc6's 151 MB 46.3 us on gemm_split with its partial sums and their launch, 26.9 now; 4096 -> 1000 12.9 -> 6.7.
+// Up to 4 rows at any size (4 rows of fc6 41.8 -> 36.3), up to 8 where B has up to 2^22 values in rows of 256 and more: beyond that each
+// column's share of A, which comes from the L1, weighs (8 rows, 4096 -> 4096 27.9 and 23.8, 9216 -> 4096 51.1 and 41.6).
+constexpr int kCols = 4, kWaves = 8;
+struct FewRows {
+  const float *A, *B, *bias;
+  float* C;
+  int M, N, K;
+};
+template <int N, int OFF>
+__device__ __forceinline__ void fold(double* v, int lane, int* mine) {
+  if constexpr (N > 1) {
+    const bool upper = lane & OFF;
+#pragma unroll
+    for (int q = 0; q < N / 2; ++q) {
+      const double keep = upper ? v[q + N / 2] : v[q], give = upper ? v[q] : v[q + N / 2];
+      v[q] = keep + __shfl_xor(give, OFF, 64);
+    }
+    *mine += upper ? N / 2 : 0;
+  } else {
+    v[0] += __shfl_xor(v[0], OFF, 64);
+  }
+  if constexpr (OFF > 1) fold<(N > 1 ? N / 2 : 1), OFF / 2>(v, lane, mine);
+}
+template <int ROWS>
+__global__ __launch_bounds__(64 * kWaves) void fc_forward_few(FewRows p) {
+  __shared__ double red[kWaves][ROWS * kCols];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int n0 = blockIdx.x * kCols;
+  constexpr int STEP = kWaves * 64 * 4;
+  const float *a[ROWS], *b[kCols];
+#pragma unroll
+  for (int m = 0; m < ROWS; ++m) a[m] = p.A + (long long)min(m, p.M - 1) * p.K;
+#pragma unroll
+  for (int c = 0; c < kCols; ++c) b[c] = p.B + (long long)min(n0 + c, p.N - 1) * p.K;
+  double acc[ROWS][kCols];
+#pragma unroll
+  for (int m = 0; m < ROWS; ++m)
+#pragma unroll
+    for (int c = 0; c < kCols; ++c) acc[m][c] = 0.0;
+  const int k_first = (wave * 64 + lane) * 4;
+  const int whole = p.K / STEP * STEP;  // up to here every lane has its 4
+  fc_f32x4u bv[2][kCols], av[2][ROWS];
+  auto load = [&](int set, int k) {
+#pragma unroll
+    for (int c = 0; c < kCols; ++c) bv[set][c] = *reinterpret_cast<const fc_f32x4u*>(b[c] + k);
+#pragma unroll
+    for (int m = 0; m < ROWS; ++m) av[set][m] = *reinterpret_cast<const fc_f32x4u*>(a[m] + k);
+  };
+  // Sums in 64 bits: lanes' chains and their tree in 32 rounded more than the matrix cores' chains do (2-norm, 2 rows of 136:
+  // 7.0e-8, 5.7e-8 there, 2.4e-8 so; 3 of 1000 with 32 columns 1.3e-7, 8.3e-8, 2.6e-8).  In whole steps, which are of rows of
+  // 2048 and more, four products are summed in 32 first (4.7e-8; 4 rows, 4096 -> 4096: 21 us without, 16).
+  auto multiply = [&](int set) {
+#pragma unroll
+    for (int m = 0; m < ROWS; ++m)
+#pragma unroll
+      for (int c = 0; c < kCols; ++c) {
+        float four = av[set][m][0] * bv[set][c][0];
+#pragma unroll
+        for (int e = 1; e < 4; ++e) four = fmaf(av[set][m][e], bv[set][c][e], four);
+        acc[m][c] += four;
+      }
+  };
+  if (whole) {
+    const int last = whole - STEP;
+    load(0, k_first);
+    for (int k = 0; k < whole; k += 2 * STEP) {
+      load(1, k_first + min(k + STEP, last));
+      multiply(0);
+      load(0, k_first + min(k + 2 * STEP, last));
+      if (k + STEP < whole) multiply(1);
+    }
+  }
+  const int k_rest = whole + k_first;
+  if (k_rest + 4 <= p.K) {
+    load(0, k_rest);
+#pragma unroll
+    for (int m = 0; m < ROWS; ++m)
+#pragma unroll
+      for (int c = 0; c < kCols; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[m][c] = fma((double)av[0][m][e], (double)bv[0][c][e], acc[m][c]);
+  } else {
+    for (int k = k_rest; k < p.K; ++k) {
+      double x[ROWS];
+#pragma unroll
+      for (int m = 0; m < ROWS; ++m) x[m] = a[m][k];
+#pragma unroll
+      for (int c = 0; c < kCols; ++c) {
+        const double y = b[c][k];
+#pragma unroll
+        for (int m = 0; m < ROWS; ++m) acc[m][c] = fma(x[m], y, acc[m][c]);
+      }
+    }
+  }
+  // sums over the lanes: in every step a lane passes on half of its values and keeps the other half
+  constexpr int VALUES = ROWS * kCols;
+  double v[VALUES];
+#pragma unroll
+  for (int q = 0; q < VALUES; ++q) v[q] = acc[q / kCols][q % kCols];
+  int mine = 0;
+  fold<VALUES, 32>(v, lane, &mine);
+  constexpr int REST = 64 / VALUES;  // lanes that hold the same value
+  if (lane % REST == 0) red[wave][mine] = v[0];
+  __syncthreads();
+  const int t = threadIdx.x, m = t / kCols, col = n0 + t % kCols;
+  if (t >= ROWS * kCols || m >= p.M || col >= p.N) return;
+  double u[kWaves];
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) u[w] = red[w][t];
+  const double sum = ((u[0] + u[1]) + (u[2] + u[3])) + ((u[4] + u[5]) + (u[6] + u[7]));
+  p.C[(long long)m * p.N + col] = (float)(sum + (p.bias ? p.bias[col] : 0.f));
+}
+
+bool forward_few_fits(int M, int N, int K) { return M <= 4 || (M <= 8 && K >= 256 && (long long)N * K <= (1LL << 22)); }
+
+int launch_forward_few(const float* A, const float* B, const float* bias, float* C, int M, int N, int K, hipStream_t st) {
+  if (M < 1 || M > 8 || N < 1 || K < 1) return CCT_EUNSUPPORTED;
+  const FewRows p{A, B, bias, C, M, N, K};
+  const dim3 grid((unsigned)((N + kCols - 1) / kCols)), block(64 * kWaves);
+  const int rows = M <= 2 ? M : M <= 4 ? 4 : 8;
+  ProfScope ps(2.0 * M * N * K, 4.0 * ((double)M * K + (double)N * K + (double)M * N), st, "fc_forward_few<%d>", rows);
+  switch (rows) {
+    case 1: hipLaunchKernelGGL(fc_forward_few<1>, grid, block, 0, st, p); break;
+    case 2: hipLaunchKernelGGL(fc_forward_few<2>, grid, block, 0, st, p); break;
+    case 4: hipLaunchKernelGGL(fc_forward_few<4>, grid, block, 0, st, p); break;
+    default: hipLaunchKernelGGL(fc_forward_few<8>, grid, block, 0, st, p);
+  }
+  CCT_CHECK_LAUNCH();
+  return CCT_OK;
+}
+
 // dw[o][f] = sum_n dy[n][o] * x[n][f] and dbias[o] = sum_n dy[n][o] over up to 32 images, in fp32: a workgroup owns 8
 // kernels x 1024 features, a thread 4 consecutive ones, dy's values are the same for all threads.  Bound by writing dw
 // (one image of fc6, 151 MB: 43.1 us as a pack of dy, a matrix product whose stages are mostly padding, and the bias
 // gradient's launch, 29.2 now; 16 images 45.0 and 43.3), and below some MB by the one launch (12 -> 6).  17 to 32 images up
 // to 2^22 weights (15.6 and 15.0; with 2^25 the multiplications weigh, 56 and 66).
 constexpr int kOuterRows = 8;
-typedef float fc_f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // 16 bytes, dword aligned
 __global__ __launch_bounds__(TPB) void fc_outer_kernel(const float* __restrict__ x, const float* __restrict__ dy,
                                                        float* __restrict__ dw, float* __restrict__ dbias, int N, int O, int F) {
   const int o0 = blockIdx.y * kOuterRows;
@@ -184,7 +321,7 @@ __global__ __launch_bounds__(TPB) void fc_outer_kernel(const float* __restrict__
 // 14.8 -> 11; with 16 images registers leave too few waves in flight (41 and 77).
 constexpr int kRowsWaves = 8, kRowsFeatures = 256;
 template <int ROWS, class Acc = double>
-__global__ __launch_bounds__(64 * kRowsWaves) void gemm_split_k_columns(const float* __restrict__ w, const float* __restrict__ dy,
+__global__ __launch_bounds__(64 * kRowsWaves) void fc_backward_data_few(const float* __restrict__ w, const float* __restrict__ dy,
                                                                   float* __restrict__ out, int N, int O, int F, int share) {
   __shared__ double red[kRowsWaves][kRowsFeatures];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -258,21 +395,21 @@ __global__ __launch_bounds__(64 * kRowsWaves) void gemm_split_k_columns(const fl
 
 // How many workgroups share a feature's kernels: at most 1024 workgroups of at least 32 kernels, none shared where a wave's
 // chain of 16 kernels is shorter than the second launch, which adds the shares.
-int split_k_columns_shares(int O, int F) {
+int backward_data_few_shares(int O, int F) {
   const int blocks = (F + kRowsFeatures - 1) / kRowsFeatures;
   return O <= 128 ? 1 : std::max(1, std::min({1024 / blocks, O / 32, 64}));
 }
 
-int launch_split_k_columns(const float* w, const float* dy, float* out, int N, int O, int F, int S, hipStream_t st) {
+int launch_backward_data_few(const float* w, const float* dy, float* out, int N, int O, int F, int S, hipStream_t st) {
   const int share = (O + S - 1) / S;
   const dim3 grid((unsigned)((F + kRowsFeatures - 1) / kRowsFeatures), (unsigned)((O + share - 1) / share)), block(64 * kRowsWaves);
-  ProfScope ps("gemm_split_k_columns", 2.0 * N * (double)O * F, 4.0 * ((double)O * F + (double)N * (O + (double)S * F)), st);
-  if (N <= 1) hipLaunchKernelGGL(gemm_split_k_columns<1>, grid, block, 0, st, w, dy, out, N, O, F, share);
-  else if (N <= 2) hipLaunchKernelGGL(gemm_split_k_columns<2>, grid, block, 0, st, w, dy, out, N, O, F, share);
-  else if (N <= 4) hipLaunchKernelGGL(gemm_split_k_columns<4>, grid, block, 0, st, w, dy, out, N, O, F, share);
+  ProfScope ps("fc_backward_data_few", 2.0 * N * (double)O * F, 4.0 * ((double)O * F + (double)N * (O + (double)S * F)), st);
+  if (N <= 1) hipLaunchKernelGGL(fc_backward_data_few<1>, grid, block, 0, st, w, dy, out, N, O, F, share);
+  else if (N <= 2) hipLaunchKernelGGL(fc_backward_data_few<2>, grid, block, 0, st, w, dy, out, N, O, F, share);
+  else if (N <= 4) hipLaunchKernelGGL(fc_backward_data_few<4>, grid, block, 0, st, w, dy, out, N, O, F, share);
   // (8 rows of 64-bit sums leave too few waves in flight, fc6 38 -> 53 us; in 32 bits its error is 1.1e-7, 1.2e-7 on the matrix cores)
-  else if (O < 512) hipLaunchKernelGGL(gemm_split_k_columns<8>, grid, block, 0, st, w, dy, out, N, O, F, share);
-  else hipLaunchKernelGGL((gemm_split_k_columns<8, float>), grid, block, 0, st, w, dy, out, N, O, F, share);
+  else if (O < 512) hipLaunchKernelGGL(fc_backward_data_few<8>, grid, block, 0, st, w, dy, out, N, O, F, share);
+  else hipLaunchKernelGGL((fc_backward_data_few<8, float>), grid, block, 0, st, w, dy, out, N, O, F, share);
   CCT_CHECK_LAUNCH();
   return CCT_OK;
 }
@@ -523,8 +660,8 @@ bool fc_plan(const cct_conv_desc_t& d, int pass, long long max_bytes, FcPlan* P)
 int fc_forward(const cct_conv_desc_t& d, const FcPlan& P, const float* x, const float* w,
                const float* bias, float* y, char* ws, hipStream_t st) {
   if (P.F % 32 == 0 && reinterpret_cast<uintptr_t>(w) % 16) return CCT_EINVAL;
-  if (P.split && gemm_split_k_fits(d.N, d.O, P.F))
-    return launch_gemm_split_k(x, w, bias, y, d.N, d.O, P.F, st);
+  if (P.split && forward_few_fits(d.N, d.O, P.F))
+    return launch_forward_few(x, w, bias, y, d.N, d.O, P.F, st);
   if (P.split) {
     void* pack = ws + P.pack_off;
     float* part = reinterpret_cast<float*>(ws + P.part_off);
@@ -557,12 +694,12 @@ int fc_backward_data(const cct_conv_desc_t& d, const FcPlan& P, const float* w, 
   if (P.split && d.N <= 8) {
     // the shares whose partial products the plan's workspace holds
     const long long out = 4LL * d.N * P.F;
-    int S = split_k_columns_shares(d.O, P.F);
+    int S = backward_data_few_shares(d.O, P.F);
     if (S > 1) S = (int)std::max(1LL, std::min<long long>(S, P.total / out));
     const int share = (d.O + S - 1) / S;
     S = (d.O + share - 1) / share;
     float* part = reinterpret_cast<float*>(ws);
-    const int rc = launch_split_k_columns(w, dy, S > 1 ? part : dx, d.N, d.O, P.F, S, st);
+    const int rc = launch_backward_data_few(w, dy, S > 1 ? part : dx, d.N, d.O, P.F, S, st);
     if (rc || S == 1) return rc;
     return launch_fc_sum_splits(part, dx, S, (long long)d.N * P.F, 1, nullptr, st);
   }

@@ -443,125 +443,6 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
   }
 }
 
-// The product of up to 8 rows with a k-contiguous B (a fully connected layer's forward pass on few images) in one launch
-// and without splitting: C[m][col] = sum_k A[m][k] * B[col][k] + bias[col].  A workgroup owns 4 columns; the contraction is
-// split over its lanes and 8 waves, 4 consecutive k each, whose sums meet in a tree.  Bound by reading B once: a matrix
-// instruction would be 16 or 32 rows of which most are none, and splitting B costs more than 8 multiplications.
-// One image: fc6's 151 MB 46.3 us on gemm_split with its partial sums and their launch, 26.9 now; 4096 -> 1000 12.9 -> 6.7.
-// Up to 4 rows at any size (4 rows of fc6 41.8 -> 36.3), up to 8 where B has up to 2^22 values in rows of 256 and more: beyond that each
-// column's share of A, which comes from the L1, weighs (8 rows, 4096 -> 4096 27.9 and 23.8, 9216 -> 4096 51.1 and 41.6).
-constexpr int kCols = 4, kWaves = 8;
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // 16 bytes, dword aligned
-struct FewRows {
-  const float *A, *B, *bias;
-  float* C;
-  int M, N, K;
-};
-template <int N, int OFF>
-__device__ __forceinline__ void fold(double* v, int lane, int* mine) {
-  if constexpr (N > 1) {
-    const bool upper = lane & OFF;
-#pragma unroll
-    for (int q = 0; q < N / 2; ++q) {
-      const double keep = upper ? v[q + N / 2] : v[q], give = upper ? v[q] : v[q + N / 2];
-      v[q] = keep + __shfl_xor(give, OFF, 64);
-    }
-    *mine += upper ? N / 2 : 0;
-  } else {
-    v[0] += __shfl_xor(v[0], OFF, 64);
-  }
-  if constexpr (OFF > 1) fold<(N > 1 ? N / 2 : 1), OFF / 2>(v, lane, mine);
-}
-template <int ROWS>
-__global__ __launch_bounds__(64 * kWaves) void gemm_split_k(FewRows p) {
-  __shared__ double red[kWaves][ROWS * kCols];
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const int n0 = blockIdx.x * kCols;
-  constexpr int STEP = kWaves * 64 * 4;
-  const float *a[ROWS], *b[kCols];
-#pragma unroll
-  for (int m = 0; m < ROWS; ++m) a[m] = p.A + (long long)min(m, p.M - 1) * p.K;
-#pragma unroll
-  for (int c = 0; c < kCols; ++c) b[c] = p.B + (long long)min(n0 + c, p.N - 1) * p.K;
-  double acc[ROWS][kCols];
-#pragma unroll
-  for (int m = 0; m < ROWS; ++m)
-#pragma unroll
-    for (int c = 0; c < kCols; ++c) acc[m][c] = 0.0;
-  const int k_first = (wave * 64 + lane) * 4;
-  const int whole = p.K / STEP * STEP;  // up to here every lane has its 4
-  f32x4 bv[2][kCols], av[2][ROWS];
-  auto load = [&](int set, int k) {
-#pragma unroll
-    for (int c = 0; c < kCols; ++c) bv[set][c] = *reinterpret_cast<const f32x4u*>(b[c] + k);
-#pragma unroll
-    for (int m = 0; m < ROWS; ++m) av[set][m] = *reinterpret_cast<const f32x4u*>(a[m] + k);
-  };
-  // Sums in 64 bits: lanes' chains and their tree in 32 rounded more than the matrix cores' chains do (2-norm, 2 rows of 136:
-  // 7.0e-8, 5.7e-8 there, 2.4e-8 so; 3 of 1000 with 32 columns 1.3e-7, 8.3e-8, 2.6e-8).  In whole steps, which are of rows of
-  // 2048 and more, four products are summed in 32 first (4.7e-8; 4 rows, 4096 -> 4096: 21 us without, 16).
-  auto multiply = [&](int set) {
-#pragma unroll
-    for (int m = 0; m < ROWS; ++m)
-#pragma unroll
-      for (int c = 0; c < kCols; ++c) {
-        float four = av[set][m][0] * bv[set][c][0];
-#pragma unroll
-        for (int e = 1; e < 4; ++e) four = fmaf(av[set][m][e], bv[set][c][e], four);
-        acc[m][c] += four;
-      }
-  };
-  if (whole) {
-    const int last = whole - STEP;
-    load(0, k_first);
-    for (int k = 0; k < whole; k += 2 * STEP) {
-      load(1, k_first + min(k + STEP, last));
-      multiply(0);
-      load(0, k_first + min(k + 2 * STEP, last));
-      if (k + STEP < whole) multiply(1);
-    }
-  }
-  const int k_rest = whole + k_first;
-  if (k_rest + 4 <= p.K) {
-    load(0, k_rest);
-#pragma unroll
-    for (int m = 0; m < ROWS; ++m)
-#pragma unroll
-      for (int c = 0; c < kCols; ++c)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc[m][c] = fma((double)av[0][m][e], (double)bv[0][c][e], acc[m][c]);
-  } else {
-    for (int k = k_rest; k < p.K; ++k) {
-      double x[ROWS];
-#pragma unroll
-      for (int m = 0; m < ROWS; ++m) x[m] = a[m][k];
-#pragma unroll
-      for (int c = 0; c < kCols; ++c) {
-        const double y = b[c][k];
-#pragma unroll
-        for (int m = 0; m < ROWS; ++m) acc[m][c] = fma(x[m], y, acc[m][c]);
-      }
-    }
-  }
-  // sums over the lanes: in every step a lane passes on half of its values and keeps the other half
-  constexpr int VALUES = ROWS * kCols;
-  double v[VALUES];
-#pragma unroll
-  for (int q = 0; q < VALUES; ++q) v[q] = acc[q / kCols][q % kCols];
-  int mine = 0;
-  fold<VALUES, 32>(v, lane, &mine);
-  constexpr int REST = 64 / VALUES;  // lanes that hold the same value
-  if (lane % REST == 0) red[wave][mine] = v[0];
-  __syncthreads();
-  const int t = threadIdx.x, m = t / kCols, col = n0 + t % kCols;
-  if (t >= ROWS * kCols || m >= p.M || col >= p.N) return;
-  double u[kWaves];
-#pragma unroll
-  for (int w = 0; w < kWaves; ++w) u[w] = red[w][t];
-  const double sum = ((u[0] + u[1]) + (u[2] + u[3])) + ((u[4] + u[5]) + (u[6] + u[7]));
-  p.C[(long long)m * p.N + col] = (float)(sum + (p.bias ? p.bias[col] : 0.f));
-}
-
 // pack[g][stage][block of 16 rows][term][lane][8] = the terms of src[g * sg + (m / taps) * sm + m % taps + k * sk], zero
 // padded in m and k, where lane stands for row m = 16 block + lane % 16 and k = 32 stage + lane / 16 * 8 + 0 .. 7: k
 // runs over min(Kdim, Ktotal - g * Kdim) indices.
@@ -732,24 +613,6 @@ int gemm_split_operand(GemmTN* p, bool bt, const float* src, void* pack, int Kto
   p->a_gs = sg; p->a_ms = sm; p->a_ks = sk; p->a_taps = taps;
   // elements of A from p->A on
   p->a_len = (p->G - 1) * sg + (p->M - 1) / taps * sm + taps - 1 + (Ktotal - (p->G - 1) * (long long)p->Kdim - 1) * sk + 1;
-  return CCT_OK;
-}
-
-bool gemm_split_k_fits(int M, int N, int K) { return M <= 4 || (M <= 8 && K >= 256 && (long long)N * K <= (1LL << 22)); }
-
-int launch_gemm_split_k(const float* A, const float* B, const float* bias, float* C, int M, int N, int K, hipStream_t st) {
-  if (M < 1 || M > 8 || N < 1 || K < 1) return CCT_EUNSUPPORTED;
-  const FewRows p{A, B, bias, C, M, N, K};
-  const dim3 grid((unsigned)((N + kCols - 1) / kCols)), block(64 * kWaves);
-  const int rows = M <= 2 ? M : M <= 4 ? 4 : 8;
-  ProfScope ps(2.0 * M * N * K, 4.0 * ((double)M * K + (double)N * K + (double)M * N), st, "gemm_split_k<%d>", rows);
-  switch (rows) {
-    case 1: hipLaunchKernelGGL(gemm_split_k<1>, grid, block, 0, st, p); break;
-    case 2: hipLaunchKernelGGL(gemm_split_k<2>, grid, block, 0, st, p); break;
-    case 4: hipLaunchKernelGGL(gemm_split_k<4>, grid, block, 0, st, p); break;
-    default: hipLaunchKernelGGL(gemm_split_k<8>, grid, block, 0, st, p);
-  }
-  CCT_CHECK_LAUNCH();
   return CCT_OK;
 }
 

@@ -14,13 +14,13 @@ KERNEL = "gemm_split"
 
 #          name      N   C   H  W    O  K
 FC = [
-    layer("one",      1,  64, 4, 4, 130, 4),             # one image, rows in place, columns past a tile
+    layer("n9",       9,  64, 4, 4, 130, 4),             # few images, rows in place, columns past a tile
     layer("n32",     32,  37, 3, 3,  65, 3),             # 333 features: the last stage ends inside a row
     layer("n33",     33,  37, 3, 3,  65, 3),             # the same with packed rows
     layer("n65",     65,   7, 1, 1, 129, 1),             # fewer features than a stage
     layer("n130",   130, 113, 5, 5, 257, 5),             # 2825 features, 128-row tiles and a split tail
     layer("n200",   200, 300, 1, 1, 1000, 1),
-    layer("prime",    4,  49, 1, 1, 1951, 1),            # splits of unequal length
+    layer("prime",    9,  49, 1, 1, 1951, 1),            # splits of unequal length
 ]
 POINTWISE = [
     layer("p_small",  2,  33, 7,  9,  34, 1),
@@ -237,12 +237,12 @@ def test_row_tiles_k_contiguous(B, N, F, O, rows):
 @pytest.mark.parametrize("N,F,O", [(1, 9216, 1001), (2, 2047, 5), (3, 4099, 33), (4, 1, 70), (5, 2052, 6), (8, 6145, 130)])
 def test_few_images(B, N, F, O):
     """Fully connected forward on few images: whole steps of 2048 features, a part of one, up to 3 features beyond the
-    last four; columns past a workgroup's 4.  Sums of 4 to 8 products per lane and step in fp32: its tolerance."""
+    last four; columns past a workgroup's 4.  Four products at a time summed in fp32: its tolerance."""
     L = layer("fc", N, F, 1, 1, O, 1)
     x, w, b = synth.make_x(L, 8), synth.make_w(L, 8), synth.make_bias(L, 8)
     for bias in (b, None):
         got, names = ran(B, lambda: gpu_forward(B, L, x, w, bias))
-        assert len(names) == 1 and names[0].startswith("gemm_split_k<"), names
+        assert len(names) == 1 and names[0].startswith("fc_forward_few<"), names
         assert rel_err(got, oracle.conv_forward(odims(oracle, L), x, w, bias)) <= TOL_F32
 
 
@@ -254,7 +254,7 @@ def test_few_images_backward(B, N, F, O):
     L = layer("fc", N, F, 1, 1, O, 1)
     x, w, dy = synth.make_x(L, 8), synth.make_w(L, 8), synth.make_dy(L, 8)
     got, names = ran(B, lambda: gpu_backward_data(B, L, w, dy))
-    assert any(n.startswith("gemm_split_k_columns") for n in names) == (N <= 8), names
+    assert any(n.startswith("fc_backward_data_few") for n in names) == (N <= 8), names
     assert rel_err(got, oracle.conv_backward_data(odims(oracle, L), w, dy)) <= TOL_F32
     (dw, db), names = ran(B, lambda: gpu_backward_weights(B, L, x, dy))
     assert names == ["fc_outer_kernel"], names
