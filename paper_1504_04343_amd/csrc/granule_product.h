@@ -183,9 +183,12 @@ struct GranuleProduct {
   }
   __device__ __forceinline__ int column(int j) const { return wave() % WAVES_N * 64 + j * MB + ((int)threadIdx.x & 63) % MB; }
 
-  // f(row, column, value) for every result of the lane, relative to the workgroup's tile
+  // f(row, column, value) for every result of the lane, relative to the workgroup's tile.  The first row and column are
+  // worked out once: through row() and column() every result had its own, which are a quarter more instructions in all and
+  // 2 us of a short launch (conv_bwdw_img<64, 1, 8>, 3 images of 15 x 18, 5.1 us against 6.9).
   template <class F>
   __device__ __forceinline__ void for_each(F f) const {
+    const int lane = threadIdx.x & 63, w = wave();
 #pragma unroll
     for (int j = 0; j < JB; ++j)
 #pragma unroll
@@ -194,7 +197,7 @@ struct GranuleProduct {
         for (int r = 0; r < MB * MB / 64; ++r) {
           float v = acc[i][j][r];
           if constexpr (TERMS == 3) v += acc_c[i][j][r];
-          f(row(i, r), column(j), v);
+          f(w / WAVES_N * (MB * RB) + i * MB + r / 4 * 8 + lane / MB * 4 + r % 4, w % WAVES_N * 64 + j * MB + lane % MB, v);
         }
   }
 };
