@@ -72,7 +72,7 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
   const int g = blockIdx.y;
   const int m0 = tile_m * BM, n0 = tile_n * BN;
   const int kd = min(p.Kdim, Ktotal - g * p.Kdim);
-  const int stages = (kd + SK - 1) / SK;
+  const int stages = (kd + SK - 1) / SK, last = stages - 1;
 
   // ---- B: a lane supplies two neighbouring columns, 8 k of each.  In pairs an image has an even number of columns: where
   // its plane is odd, the second of its last pair is no column (what it loads is not stored)
@@ -102,17 +102,23 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
     voff[j] = BT ? (unsigned)((long long)(col - n0) * p.b_ks + kg * 8) * 4u
                  : (unsigned)(col_offset(p.bmap, col) - (long long)n_f * p.bmap.img_stride + (long long)kg * 8 * p.b_ks) * 4u;
   }
-  // k past the last one: what lies there, or zero beyond the tensor's end (A is zero there; an infinity only costs the
-  // recomputation).  The range is checked against the vector offset alone: all of an address that may lie beyond goes there.
+  // k past the last one: what lies there, or zero beyond the tensor's end; in the first stages, which may be all there are, the
+  // last one again (short_end).  A is zero there; an infinity only costs the recomputation.  The range is checked against the
+  // vector offset alone: all of an address that may lie beyond goes there.  Stages past the last one have a range of nothing: as
+  // many loads are in flight as ever, but none goes to memory (a contraction of one stage would read B three times).
   const long long b_left = p.b_len - (Bt - reinterpret_cast<const float*>(p.B));
   auto range = [](long long left) { return left < 0 ? 0 : left >= 0x1fffffff ? 0x7fffffff : (int)left * 4; };
   float raw[RAWS][2][8];
-  auto load_b = [&](int set, int t) {
-    const long long at = (long long)t * SK * (BT ? 1 : p.b_ks);
+  auto load_b = [&](int set, int t, bool short_end) {
+    const int tt = min(t, last);
+    const long long at = (long long)tt * SK * (BT ? 1 : p.b_ks);
     const __amdgpu_buffer_rsrc_t rs =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(Bt + at), 0, range(b_left - at), 0x00020000);
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(Bt + at), 0, t > last ? 0 : range(b_left - at), 0x00020000);
     unsigned ks = BT ? 4u : (unsigned)p.b_ks * 4u;
     asm volatile("" : "+s"(ks));  // the sums below are not kept in registers between the stages
+    unsigned end[2];  // the stage's last k
+#pragma unroll
+    for (int j = 0; j < 2; ++j) end[j] = voff[j] + (unsigned)(min(kd - tt * SK, SK) - 1 - kg * 8) * ks;
 #pragma unroll
     for (int e = 0; e < (BT ? 2 : 8); ++e)
 #pragma unroll
@@ -122,11 +128,11 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
 #pragma unroll
           for (int i = 0; i < 4; ++i) raw[set][j][e * 4 + i] = v[i];
         } else if constexpr (BF == kPairs) {
-          const f32x2 v = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(rs, (int)(voff[0] + e * ks), 0, 0));
+          const f32x2 v = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(rs, (int)(short_end ? min(voff[0] + e * ks, end[0]) : voff[0] + e * ks), 0, 0));
           raw[set][0][e] = v[0];
           raw[set][1][e] = v[1];
         } else {
-          raw[set][j][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (int)(voff[j] + e * ks), 0, 0));
+          raw[set][j][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (int)(short_end ? min(voff[j] + e * ks, end[j]) : voff[j] + e * ks), 0, 0));
         }
       }
   };
@@ -182,7 +188,7 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
   }
   auto move_a = [&](int t, int slot) {
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<unsigned char*>(Ap + (long long)t * p.Mpad * 192), 0, 0x7fffffff, 0x00020000);
+        const_cast<unsigned char*>(Ap + (long long)min(t, last) * p.Mpad * 192), 0, t > last ? 0 : 0x7fffffff, 0x00020000);
 #pragma unroll
     for (int u = 0; u < AP; ++u)
       if (4 * u + 4 <= UNITS || wave + 4 * u < UNITS)
@@ -191,9 +197,9 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
   };
   const long long a_left = DIRECT ? p.a_len - (Ad - reinterpret_cast<const float*>(p.A)) : 0;
   auto load_a = [&](int t) {
-    const long long at = (long long)t * SK * (AF == kRows ? 1 : p.a_ks);
+    const long long at = (long long)min(t, last) * SK * (AF == kRows ? 1 : p.a_ks);
     const __amdgpu_buffer_rsrc_t rs =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(Ad + at), 0, range(a_left - at), 0x00020000);
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(Ad + at), 0, t > last ? 0 : range(a_left - at), 0x00020000);
     unsigned ks = AF == kRows ? 4u : (unsigned)p.a_ks * 4u;
     asm volatile("" : "+s"(ks));
 #pragma unroll
@@ -244,18 +250,17 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
 #pragma unroll
       for (int r = 0; r < 4; ++r) acc_h[i][j][r] = acc_c[i][j][r] = 0.f;
 
-  const int last = stages - 1;  // past it, the last stage is fetched again: what is in flight is the same throughout
   if constexpr (DIRECT) load_a(0); else move_a(0, 0);
-  load_b(0, 0);
+  load_b(0, 0, true);
   if constexpr (DIRECT) {
     store_a(0, 0);
-    load_a(min(1, last));
+    load_a(1);
   }
-  if constexpr (EARLY) move_a(min(1, last), 1);
-  if (RAWS == 2) load_b(1, min(1, last));
+  if constexpr (EARLY) move_a(1, 1);
+  if (RAWS == 2) load_b(1, 1, true);
 #pragma unroll
   for (int n = 0; n < 32; ++n) split_step(raw[0], 0, n);
-  load_b(0, min(RAWS, last));
+  load_b(0, RAWS, false);
   if constexpr (!DIRECT) __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
 
   // Two sets of A's operands; where registers decide how many workgroups share a CU, one, read term by term
@@ -281,26 +286,30 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
   int slot = 0;  // of A
   auto after = [&](int v) { return v == SLOTS - 1 ? 0 : v + 1; };
   // One stage.  A's operands of a block of rows are read behind the MFMAs of the block before; B's next ones are split
-  // behind the last 36 MFMAs (of two blocks of rows: of all), then their registers are loaded once more.
-  auto stage = [&](int t, int set) {
+  // behind the last 36 MFMAs (of two blocks of rows: of all), then their registers are loaded once more.  The last stage does
+  // none of this for a next one (a layer of 256 -> 64 channels, 8 stages, 44.0 us with it and 42.1 without; fc6's three
+  // products 357 and 352).  It stands once: behind a branch on the parity of the stages its accumulators would meet
+  // in different registers and spill.
+  auto stage = [&](int t, int set, auto more) {
+    constexpr bool MORE = decltype(more)::value;
     const int next = after(slot);
     if constexpr (!EARLY) {
       meet();  // A of this stage is visible, nobody reads the other slot any more
-      if constexpr (!DIRECT) move_a(min(t + 1, last), next);
+      if constexpr (!DIRECT && MORE) move_a(t + 1, next);
 #pragma unroll
       for (int q = 0; q < 3; ++q) read_a(0, 2 - q, slot);
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 0; i < RB; ++i) {
-      if (EARLY && i == RB - 1) {
+      if (EARLY && MORE && i == RB - 1) {
         __builtin_amdgcn_s_waitcnt(0x0f70 | (LEFT & 15) | (LEFT >> 4 << 14));
         meet();  // A of the next stage is visible, nobody reads the slot before this one any more
-        move_a(min(t + 2, last), after(next));
+        move_a(t + 2, after(next));
       }
       auto read = [&](int q) {
         if (i + 1 < RB) read_a(i + 1, q, slot);
-        else if (EARLY) read_a(i + 1, q, next);
+        else if (EARLY && MORE) read_a(i + 1, q, next);
       };
       auto mfma = [&](int k, int x, int y, f32x4 (&acc)[2]) {
 #pragma unroll
@@ -308,8 +317,8 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
           acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[i % SETS][x]),
                                                            __builtin_bit_cast(bf16x8, b[set][j][y]), acc[j], 0, 0, 0);
           const int n = i * 12 + k + j - (RB * 12 - (RB > 2 ? 36 : 22));
-          if (RB > 2 && n >= 0 && n < 32) split_step(raw[RAWS == 2 ? set ^ 1 : 0], set ^ 1, n);
-          if (RB == 2 && n >= 0 && n < 16) {
+          if (MORE && RB > 2 && n >= 0 && n < 32) split_step(raw[RAWS == 2 ? set ^ 1 : 0], set ^ 1, n);
+          if (MORE && RB == 2 && n >= 0 && n < 16) {
             split_step(raw[RAWS == 2 ? set ^ 1 : 0], set ^ 1, 2 * n);
             split_step(raw[RAWS == 2 ? set ^ 1 : 0], set ^ 1, 2 * n + 1);
           }
@@ -327,13 +336,13 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
       mfma(8, 0, 1, acc_c[i]);
       mfma(10, 0, 0, acc_h[i]);
       if (SETS == 1) read(0);
-      if (DIRECT && i == (RB - 1) / 2) {
+      if (DIRECT && MORE && i == (RB - 1) / 2) {
         store_a(min(t + 1, last), next);
-        load_a(min(t + 2, last));
+        load_a(t + 2);
       }
     }
-    if constexpr (!DIRECT && !EARLY) __builtin_amdgcn_s_waitcnt(0x0f70);  // A of the next stage is in place
-    load_b(RAWS == 2 ? set ^ 1 : 0, min(t + 1 + RAWS, last));
+    if constexpr (!DIRECT && !EARLY && MORE) __builtin_amdgcn_s_waitcnt(0x0f70);  // A of the next stage is in place
+    if (MORE) load_b(RAWS == 2 ? set ^ 1 : 0, t + 1 + RAWS, false);
     slot = next;
   };
   if constexpr (EARLY) {
@@ -341,12 +350,22 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
 #pragma unroll
     for (int q = 0; q < 3; ++q) read_a(0, 2 - q, 0);
   }
+  constexpr std::true_type more;
+  constexpr std::false_type end;
   int t = 0;
-  for (; t + 1 < stages; t += 2) {
-    stage(t, 0);
-    stage(t + 1, 1);
+  for (; t + 2 < stages; t += 2) {
+    stage(t, 0, more);
+    stage(t + 1, 1, more);
   }
-  if (t < stages) stage(t, 0);
+  if (t < last) {
+    stage(t, 0, more);
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int q = 0; q < 3; ++q) b[0][j][q] = b[1][j][q];
+    ++t;
+  }
+  stage(t, 0, end);
   if constexpr (!DIRECT) __builtin_amdgcn_s_waitcnt(0x0f70);  // nothing is moved into LDS after the end
 
   // ---- epilogue: a lane holds rows 16 i + 4 kg .. + 3 of its two columns
