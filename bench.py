@@ -36,7 +36,7 @@ PEAK_FP32_MFMA_TFLOPS = 157.3   # MI355X published dense fp32 matrix peak
 PEAK_BF16_MFMA_TFLOPS = 2500.0
 # fp32 products on the bf16 matrix cores: three terms per operand, six bf16 products per fp32 product
 PEAK_SPLIT_TFLOPS = PEAK_BF16_MFMA_TFLOPS / 6
-MFMA_KERNELS = ("gemm_", "conv_fused", "conv_bwdw_fused", "conv_bwdw_img", "conv_granules")
+MFMA_KERNELS = ("gemm_", "conv_fused", "conv_bwdw_fused", "conv_bwdw_img", "conv_bwdw_few", "conv_granules")
 SPLIT_KERNELS = ("conv_fused_split", "gemm_split", "conv_bwdw_img", "conv_bwdw_few")
 PEAK_HBM_GBS = 8000.0
 

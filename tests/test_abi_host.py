@@ -1,6 +1,7 @@
 """Host-side checks of libcct.so that need no GPU: the library loads, exports every symbol the
 header declares, validates arguments, and its shape/selector functions obey what the paper fixes."""
 import ctypes
+import glob
 import os
 import re
 
@@ -348,3 +349,21 @@ def test_pairs_of_columns_stay_within_32_bits(B):
                 assert (got, pair.value) == (0, 0), (P, n)
             else:
                 assert (got, pair.value) == (want, even if P < 2**31 - 1 else 0), (P, n)
+
+
+def test_benchmark_counts_every_kernel_of_the_matrix_cores():
+    """What multiplies on the matrix cores is rated at their peak, at a sixth of it where fp32 operands are three terms;
+    fully connected layers on few images do not."""
+    import bench
+    for name in bench.SPLIT_KERNELS:
+        assert name.startswith(bench.MFMA_KERNELS), name
+    sources = glob.glob(os.path.join(ROOT, "paper_1504_04343_amd", "csrc", "*.hip"))
+    for path in sources:
+        text = open(path).read()
+        kernels = set(re.findall(r'ProfScope ps\([^;]*?"(\w+)', text, flags=re.S))
+        assert kernels or "ProfScope ps(" not in text, path
+        rated = {k for k in kernels if k.startswith(bench.MFMA_KERNELS)}
+        if os.path.basename(path) == "fully_connected.hip":
+            assert not rated, rated
+        elif "_mfma_f32" in text:
+            assert rated, path
