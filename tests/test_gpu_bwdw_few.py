@@ -74,3 +74,17 @@ def test_not_finite_inputs(B, L):
         big = ok & (np.abs(ref) > 1e30)
         assert (np.abs(got[big] - ref[big]) <= 1e-5 * np.abs(ref[big])).all()
         assert rel_err(got[ok & ~big], ref[ok & ~big]) <= TOL_F32
+
+
+def test_bias_gradient_of_long_columns(B):
+    """A row that leaves the rows below it under half a unit of the last place: added one by one in fp32 all 39 are lost,
+    2^-24 of the result each.  A tree of 16 values, a sum over the rows in 64 bits, 512 partial sums as
+    two sums of four in each of 64 strips and their tree: at most 4 + 1 + (2 + 2) + 6 roundings."""
+    L = layer("long", 1024, 1, 42, 34, 32, 3, 1, 0)
+    x, dy = synth.make_x(L, 6), np.zeros((L.N, L.O, L.Hout, L.Wout), np.float32)
+    dy[::8] = 1.0
+    dy[::8, :, 0] = 2.0**24
+    (dw, db), names = run(B, L, x, dy)
+    assert any(n.startswith("conv_bwdw_few") for n in names), names
+    want = dy[:, 0].astype(np.float64).sum()
+    assert np.abs(db / want - 1.0).max() <= 16 * 2.0**-24
