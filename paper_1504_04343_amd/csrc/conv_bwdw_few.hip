@@ -369,31 +369,41 @@ bool bwdw_few_plan(const cct_conv_desc_t& d, long long nimg, BwdwFewPlan* P) {
   // 32-bit byte offsets from the first of 8 images, rows of a tile past the last kernel among them
   const long long xi = (long long)d.C * d.H * d.W, yi = (long long)d.O * Hout * Wout;
   if (kImg * xi >= (1LL << 28) || kImg * yi + 96 * Hout * Wout >= (1LL << 28) || d.W + 2LL * d.pad >= (1LL << 20)) return false;
-  P->rb = Og > 64 ? 6 : Og > 32 ? 4 : 2;
   P->cb = column_blocks(N);
-  P->lds = lds_bytes(P->rb, ring, row_bytes(WX, Cg, d.K));
-  if (P->lds > 160 * 1024) return false;
-  const long long tiles = (Og + 16 * P->rb - 1) / (16 * P->rb), strips = (Wout + kPos - 1) / kPos;
-  const long long out = 4LL * d.O * N;
-  // Segments of the output rows, from the whole batch: what the rounds of workgroups (one per CU, or two where registers
-  // and LDS allow it) are estimated to take, partial sums within 256 MiB.
-  const int per_cu = P->rb * P->cb <= 6 && P->cb < 3 && P->lds <= 80 * 1024 ? 2 : 1;
+  const long long strips = (Wout + kPos - 1) / kPos, out = 4LL * d.O * N;
+  auto tiles_of = [&](int rb) { return (Og + 16 * rb - 1) / (16 * rb); };
   auto count = [&](long long images, long long segs) { return (images + kImg - 1) / kImg * strips * segs; };
   double best = 0.0;
-  for (long long n = 1; n <= std::min(Hout, 64LL); ++n) {
-    const long long rows = (Hout + n - 1) / n, segs = (Hout + rows - 1) / rows, S = count(d.N, segs);
-    if (n > 1 && S * out > (256LL << 20)) break;
-    const long long wgs = S * tiles * d.groups, full = 256 * per_cu, rest = wgs % full;
-    const int blocks = P->rb * P->cb;
-    auto round = [&](int on) { return rows * (kRowUs + kBlockUs * blocks * on) + (kFillUs + kFillBlockUs * blocks) * on; };
-    const double us = (double)(wgs / full) * round(per_cu) + (rest > 256 ? round(2) : rest ? round(1) : 0.0) +
-                      2.0 * (double)(S * out) / kPartialRate;
-    if (n == 1 || us < best) {
-      best = us;
-      P->segs = (int)segs;
-      P->seg_rows = (int)rows;
+  // Segments of the output rows, from the whole batch: what the rounds of workgroups (one per CU, or two where registers
+  // and LDS allow it) are estimated to take, partial sums within 256 MiB.
+  auto consider = [&](int rb) {
+    const int blocks = rb * P->cb;
+    const long long lds = lds_bytes(rb, ring, row_bytes(WX, Cg, d.K));
+    if (lds > 160 * 1024) return;
+    const int per_cu = blocks <= 6 && P->cb < 3 && lds <= 80 * 1024 ? 2 : 1;
+    for (long long n = 1; n <= std::min(Hout, 64LL); ++n) {
+      const long long rows = (Hout + n - 1) / n, segs = (Hout + rows - 1) / rows, S = count(d.N, segs);
+      if (n > 1 && S * out > (256LL << 20)) break;
+      const long long wgs = S * tiles_of(rb) * d.groups, full = 256 * per_cu, rest = wgs % full;
+      auto round = [&](int on) { return rows * (kRowUs + kBlockUs * blocks * on) + (kFillUs + kFillBlockUs * blocks) * on; };
+      const double us = (double)(wgs / full) * round(per_cu) + (rest > 256 ? round(2) : rest ? round(1) : 0.0) +
+                        2.0 * (double)(S * out) / kPartialRate;
+      if (best == 0.0 || us < best) {
+        best = us;
+        P->rb = rb;
+        P->lds = lds;
+        P->segs = (int)segs;
+        P->seg_rows = (int)rows;
+      }
     }
-  }
+  };
+  consider(Og > 64 ? 6 : Og > 32 ? 4 : 2);
+  // A few kernels past 96: two tiles of 64 instead of two of 96 (700 such layers 0.76 times the time, 0.93 at most; before,
+  // they were the ones that took up to 1.15 times as long as without this kernel: 47 images of 97 x 96, two groups of 14 -> 100
+  // channels, 3 x 3, 387 us for 335).  193 to 256 in four tiles instead of three still gain (464 layers, 0.83) and stay.
+  if (Og > 96 && Og <= 128) consider(4);
+  if (best == 0.0) return false;
+  const long long tiles = tiles_of(P->rb);
   const long long S = count(nimg, P->segs);
   if (S * tiles >= (1LL << 30) || S * d.O >= (1LL << 30) || d.groups > 65535) return false;
   P->S = (int)S;

@@ -17,6 +17,8 @@ SHAPES = [
     (layer("seven_s1",   33,  4, 30, 41,  65,  7, 1, 3), 96, 2),
     (layer("five",       64,  4, 32, 57,  32,  5, 1, 2), 32, 1),
     (layer("three",     128,  8, 40, 43,  40,  3, 1, 1), 64, 1),
+    (layer("past_96",   100, 10, 41, 37, 101,  3, 1, 1), 64, 1),     # 37 kernels in the second tile
+    (layer("past_96_7",  64,  3, 61, 59, 128,  7, 2, 3), 64, 2),
     (layer("three_g2",  100, 16, 33, 35,  60,  3, 2, 1, 2), 32, 1),
 ]
 
