@@ -191,6 +191,7 @@ int gemm_split_operand(GemmTN* p, bool bt, const float* src, void* pack, int Kto
 // sums of dw, ordered (tap, channel), and with `sums` S rows of dbias.  A plan for fewer images is no larger.
 struct BwdwFewPlan {
   int rb, cb, segs, seg_rows, S;
+  int images;  // of a launch; more go one launch after the other
   long long lds;
   double seconds;  // of the whole pass
 };

@@ -22,6 +22,7 @@
 // Tried: rows of all strips shared evenly over 256 workgroups instead of strips on 224 (conv1 1119 -> 1289 us: the strips
 // of the same images no longer run side by side, and dy's lines are fetched for every strip).
 #include <algorithm>
+#include <climits>
 
 #include "cct_internal.h"
 #include "gemm_common.h"
@@ -33,6 +34,7 @@ namespace {
 constexpr int kImg = 8;   // images per granule
 constexpr int kPos = 8;   // output columns of a strip
 constexpr int NT = 512;
+constexpr long long kPartialBytes = 256LL << 20;  // of the partial sums of a launch
 constexpr int kCell = 48;  // bytes of a granule's three terms
 
 struct Few {
@@ -383,7 +385,7 @@ bool bwdw_few_plan(const cct_conv_desc_t& d, long long nimg, BwdwFewPlan* P) {
     const int per_cu = blocks <= 6 && P->cb < 3 && lds <= 80 * 1024 ? 2 : 1;
     for (long long n = 1; n <= std::min(Hout, 64LL); ++n) {
       const long long rows = (Hout + n - 1) / n, segs = (Hout + rows - 1) / rows, S = count(d.N, segs);
-      if (n > 1 && S * out > (256LL << 20)) break;
+      if (n > 1 && S * out > kPartialBytes) break;
       const long long wgs = S * tiles_of(rb) * d.groups, full = 256 * per_cu, rest = wgs % full;
       auto round = [&](int on) { return rows * (kRowUs + kBlockUs * blocks * on) + (kFillUs + kFillBlockUs * blocks) * on; };
       const double us = (double)(wgs / full) * round(per_cu) + (rest > 256 ? round(2) : rest ? round(1) : 0.0) +
@@ -404,7 +406,12 @@ bool bwdw_few_plan(const cct_conv_desc_t& d, long long nimg, BwdwFewPlan* P) {
   if (Og > 96 && Og <= 128) consider(4);
   if (best == 0.0) return false;
   const long long tiles = tiles_of(P->rb);
-  const long long S = count(nimg, P->segs);
+  // The whole batch in one launch where its partial sums are no more than that, else as many images at a time as are (batch
+  // 4096 of CaffeNet's first layer: 477 MiB)
+  const long long eight = count(kImg, P->segs) * out;
+  if (eight > kPartialBytes) return false;
+  P->images = (int)std::min<long long>(kPartialBytes / eight * kImg, INT_MAX / kImg * kImg);
+  const long long S = count(std::min<long long>(nimg, P->images), P->segs);
   if (S * tiles >= (1LL << 30) || S * d.O >= (1LL << 30) || d.groups > 65535) return false;
   P->S = (int)S;
   P->seconds = 1e-6 * (best + kLaunchUs);

@@ -479,6 +479,17 @@ int launch_bwdw_img(const cct_conv_desc_t& d, const BwdwImgPlan& P, int nimg, co
                     float* dw, float* dbias, int accumulate, char* ws, hipStream_t st) {
   const int Hout = out_size(d.H, d.K, d.stride, d.pad), Wout = out_size(d.W, d.K, d.stride, d.pad);
   const int Cg = d.C / d.groups, Og = d.O / d.groups, KK = d.K * d.K, pix = Hout * Wout;
+  if (P.few && nimg > P.fp.images) {
+    for (int n0 = 0; n0 < nimg; n0 += P.fp.images) {
+      const int ni = std::min(P.fp.images, nimg - n0);
+      BwdwImgPlan part;
+      if (!bwdw_img_plan(d, ni, &part)) return CCT_EUNSUPPORTED;
+      const int rc = launch_bwdw_img(d, part, ni, x + (long long)n0 * d.C * d.H * d.W, dy + (long long)n0 * d.O * pix, dw, dbias,
+                                     accumulate || n0 > 0, ws, st);
+      if (rc) return rc;
+    }
+    return CCT_OK;
+  }
   const int Hp = d.H + 2 * d.pad, Wp = d.W + 2 * d.pad, igs = (nimg + kImg - 1) / kImg;
   auto job = [&](const float* src, long long dst_off, int C, int H, int W, int pad) {
     PrepJob j;

@@ -367,3 +367,10 @@ def test_benchmark_counts_every_kernel_of_the_matrix_cores():
             assert not rated, rated
         elif "_mfma_f32" in text:
             assert rated, path
+
+
+@pytest.mark.parametrize("shape", [(1024, 32, 56, 56, 512, 3, 1, 1), (4096, 3, 227, 227, 96, 11, 4, 0), (1024, 12, 112, 112, 256, 5, 1, 2)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_partial_sums_of_few_channels_stay_within_their_bound(B, shape):
+    """Backward-weights on conv_bwdw_few: 256 MiB of partial sums of dw at a time, and a few of the bias gradient."""
+    assert B.cct_conv_workspace_bytes(B.make_desc(*shape), B.PASS_BACKWARD_WEIGHTS) <= 260 << 20

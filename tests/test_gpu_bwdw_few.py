@@ -90,3 +90,15 @@ def test_bias_gradient_of_long_columns(B):
     assert any(n.startswith("conv_bwdw_few") for n in names), names
     want = dy[:, 0].astype(np.float64).sum()
     assert np.abs(db / want - 1.0).max() <= 16 * 2.0**-24
+
+
+def test_partial_sums_of_several_launches(B):
+    """More than 256 MiB of partial sums: two launches, the second one's added to what the first left."""
+    L = layer("two_launches", 233, 23, 6, 59, 960, 4)  # of 216 and 17 images
+    assert 30 * ((L.Wout + 7) // 8) * 4 * L.O * L.C * L.K**2 > 2**28
+    x, dy = synth.make_x(L, 7), synth.make_dy(L, 7)
+    (dw, db), names = run(B, L, x, dy)
+    assert any(n.startswith("conv_bwdw_few") for n in names), names
+    idx = np.random.default_rng(7).choice(dw.size, 2000, replace=False)
+    assert rel_err(dw.ravel()[idx], oracle.conv_backward_weights_at(odims(oracle, L), x, dy, idx)) <= TOL_F32
+    assert rel_err(db, dy.sum((0, 2, 3), dtype=np.float64)) <= TOL_F32
