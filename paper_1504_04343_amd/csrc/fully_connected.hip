@@ -11,9 +11,10 @@
 // N*O outputs (few tiles) and a long contraction, so it is split over F into partial products
 // that a second kernel sums in split order together with the bias (bit-reproducible, no atomics).
 // The backward-data product has N*F outputs, still too few tiles at CaffeNet's batch, and is split
-// over O the same way (the splits run as the groups of one launch).  The products run on gemm_split; the
-// fp32 kernels are for workspaces without room for its packed operand and for backward-weights passes
-// over up to 32 images.
+// over O the same way (the splits run as the groups of one launch).  The products run on gemm_split, over few
+// images as plain fp32 products that read or write the kernels once (fc_forward_few, fc_backward_data_few,
+// fc_outer_kernel); the fp32 matrix kernels are for workspaces without room for gemm_split's packed operand and for
+// backward-weights passes over 17 to 32 images of more than 2^22 weights.
 #include <algorithm>
 #include <cstring>
 #include <type_traits>
@@ -233,75 +234,83 @@ int launch_forward_few(const float* A, const float* B, const float* bias, float*
   return CCT_OK;
 }
 
-// dw[o][f] = sum_n dy[n][o] * x[n][f] and dbias[o] = sum_n dy[n][o] over up to 32 images, in fp32: a workgroup owns 8
-// kernels x 1024 features, a thread 4 consecutive ones, dy's values are the same for all threads.  Bound by writing dw
-// (one image of fc6, 151 MB: 43.1 us as a pack of dy, a matrix product whose stages are mostly padding, and the bias
-// gradient's launch, 29.2 now; 16 images 45.0 and 43.3), and below some MB by the one launch (12 -> 6).  17 to 32 images up
-// to 2^22 weights (15.6 and 15.0; with 2^25 the multiplications weigh, 56 and 66).
-constexpr int kOuterRows = 8;
+// dw[o][f] = sum_n dy[n][o] * x[n][f] and dbias[o] = sum_n dy[n][o] over up to IMAGES images, in fp32: a workgroup owns ROWS
+// kernels x 1024 features, a thread 4 consecutive ones; dy's values are the same for all threads and come from LDS.
+// Bound by writing dw, and in layers of some MB and less by one trip to memory: the loads of up to 16 images are on their
+// way at once (four at a time, dy's values by scalar loads between them, was a trip for every four images or even every one,
+// 32 images of 25 -> 3252 29.2 us).  In us, as a pack of dy, a matrix product whose stages are mostly padding and the bias
+// gradient's launch, and so: 9216 -> 4096 on one image 39.0 and 24.4, on 16 39.7 and 27.7; 4096 -> 1000 on 16 13.6 and
+// 7.9; 32 of 1024 -> 4096 15.7 and 10.8, of 25 -> 3252 12.0 and 11.8.  Of 6300 layers of 1 to 32 images none is slower.
+constexpr int kOuterMost = 32;  // images
+// From 17 images on 4 kernels: a thread's multiplications are what short launches take then (8: of 17 to 32 images an eighth
+// of the layers up to 1.5 times as long as behind a pack)
+constexpr int outer_rows(int N) { return N <= 16 ? 8 : 4; }
+template <int IMAGES>
 __global__ __launch_bounds__(TPB) void fc_outer_kernel(const float* __restrict__ x, const float* __restrict__ dy,
                                                        float* __restrict__ dw, float* __restrict__ dbias, int N, int O, int F) {
-  const int o0 = blockIdx.y * kOuterRows;
+  constexpr int ROWS = outer_rows(IMAGES), AHEAD = IMAGES < 16 ? IMAGES : 16;  // images whose loads are in flight
+  __shared__ __attribute__((aligned(16))) float g[kOuterMost][ROWS];
+  const int o0 = blockIdx.y * ROWS;
   const int f0 = (int)(blockIdx.x * TPB + threadIdx.x) * 4;
-  if (dbias && blockIdx.x == 0 && threadIdx.x < 64) {  // a lane sums 4 images of a kernel
-    const int o = o0 + (threadIdx.x & 7), strip = threadIdx.x >> 3;
-    float v[4];
+  const bool whole = f0 + 4 <= F;
+  float v[AHEAD][4];
+  auto load = [&](int u) {  // images past the last one: that one again, times nothing
+    const float* xn = x + (long long)min(u, N - 1) * F + min(f0, F - 1);
+    if (whole) {
+      const fc_f32x4u t = *reinterpret_cast<const fc_f32x4u*>(xn);
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int n = strip * 4 + u;
-      const float q = dy[(long long)min(n, N - 1) * O + min(o, O - 1)];
-      v[u] = n < N ? q : 0.f;
+      for (int e = 0; e < 4; ++e) v[u % AHEAD][e] = t[e];
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[u % AHEAD][e] = f0 + e < F ? xn[e] : 0.f;
     }
-    float sum = (v[0] + v[1]) + (v[2] + v[3]);
-    sum += __shfl_xor(sum, 8, 64);
-    sum += __shfl_xor(sum, 16, 64);
-    sum += __shfl_xor(sum, 32, 64);
-    if (strip == 0 && o < O) dbias[o] = sum;
+  };
+  {
+    const int n = (int)threadIdx.x / ROWS, o = (int)threadIdx.x % ROWS;
+    const float q = dy[(long long)min(n, N - 1) * O + min(o0 + o, O - 1)];
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) load(u);
+    if (n < kOuterMost) g[n][o] = n < N ? q : 0.f;
+  }
+  __syncthreads();
+  if (dbias && blockIdx.x == 0 && threadIdx.x < 8 * ROWS) {  // a lane sums 4 images of a kernel
+    const int o = (int)threadIdx.x % ROWS, strip = (int)threadIdx.x / ROWS;
+    float sum = (g[strip * 4][o] + g[strip * 4 + 1][o]) + (g[strip * 4 + 2][o] + g[strip * 4 + 3][o]);
+#pragma unroll
+    for (int off = ROWS; off < 8 * ROWS; off *= 2) sum += __shfl_xor(sum, off, 64);
+    if (strip == 0 && o0 + o < O) dbias[o0 + o] = sum;
   }
   if (f0 >= F) return;
-  const bool whole = f0 + 4 <= F;
-  float acc[kOuterRows][4];
+  float acc[ROWS][4];
 #pragma unroll
-  for (int o = 0; o < kOuterRows; ++o)
+  for (int o = 0; o < ROWS; ++o)
 #pragma unroll
     for (int e = 0; e < 4; ++e) acc[o][e] = 0.f;
-  // 4 images at a time: their loads in flight together, their products summed before they are added
-  for (int n0 = 0; n0 < N; n0 += 4) {
-    float v[4][4];
+  // the products of 4 images are summed before they are added
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const float* xn = x + (long long)min(n0 + u, N - 1) * F + f0;
-      if (whole) {
-        const fc_f32x4u q = *reinterpret_cast<const fc_f32x4u*>(xn);
+  for (int n0 = 0; n0 < IMAGES; n0 += 4) {
+    if (n0 >= N) break;
+    float t[ROWS][4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[u][e] = q[e];
-      } else {
+    for (int u = n0; u < n0 + 4; ++u) {
+      float d[ROWS];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[u][e] = f0 + e < F ? xn[e] : 0.f;
+      for (int o = 0; o < ROWS; ++o) d[o] = g[u][o];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float xv = u < N ? v[u % AHEAD][e] : 0.f;
+#pragma unroll
+        for (int o = 0; o < ROWS; ++o) t[o][e] = fmaf(d[o], xv, u == n0 ? 0.f : t[o][e]);
       }
+      if (u + AHEAD < IMAGES) load(u + AHEAD);
     }
-    const int live = min(4, N - n0);
-    auto add = [&](auto full) {
-      constexpr bool FULL = decltype(full)::value;
 #pragma unroll
-      for (int o = 0; o < kOuterRows; ++o) {
-        float t[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int o = 0; o < ROWS; ++o)
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          if (!FULL && u >= live) break;
-          const float g = dy[(long long)(n0 + u) * O + min(o0 + o, O - 1)];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) t[e] = fmaf(g, v[u][e], t[e]);
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc[o][e] += t[e];
-      }
-    };
-    if (live == 4 && O >= 64) add(std::integral_constant<bool, true>());
-    else add(std::integral_constant<bool, false>());
+      for (int e = 0; e < 4; ++e) acc[o][e] += t[o][e];
   }
 #pragma unroll
-  for (int o = 0; o < kOuterRows; ++o) {
+  for (int o = 0; o < ROWS; ++o) {
     if (o0 + o >= O) break;
     float* to = dw + (long long)(o0 + o) * F + f0;
     if (whole) {
@@ -312,6 +321,18 @@ __global__ __launch_bounds__(TPB) void fc_outer_kernel(const float* __restrict__
         if (f0 + e < F) to[e] = acc[o][e];
     }
   }
+}
+
+int launch_outer(const float* x, const float* dy, float* dw, float* dbias, int N, int O, int F, hipStream_t st) {
+  const int rows = outer_rows(N);
+  const dim3 grid((unsigned)((F + 4 * TPB - 1) / (4 * TPB)), (unsigned)((O + rows - 1) / rows)), block(TPB);
+  ProfScope ps("fc_outer_kernel", 2.0 * N * (double)O * F, 4.0 * ((double)O * F + (double)N * (F + O)), st);
+  if (N <= 4) hipLaunchKernelGGL(fc_outer_kernel<4>, grid, block, 0, st, x, dy, dw, dbias, N, O, F);
+  else if (N <= 8) hipLaunchKernelGGL(fc_outer_kernel<8>, grid, block, 0, st, x, dy, dw, dbias, N, O, F);
+  else if (N <= 16) hipLaunchKernelGGL(fc_outer_kernel<16>, grid, block, 0, st, x, dy, dw, dbias, N, O, F);
+  else hipLaunchKernelGGL(fc_outer_kernel<kOuterMost>, grid, block, 0, st, x, dy, dw, dbias, N, O, F);
+  CCT_CHECK_LAUNCH();
+  return CCT_OK;
 }
 
 // dx[n][f] = sum_o dy[n][o] * w[o][f] over up to 8 images (S > 1: one of S shares of the kernels, to part): a
@@ -461,8 +482,7 @@ double chain_seconds(int Mpad, long long tiles_n, int K, long long G) {
 // times their stages, against the partial products that are written and read once more.  Measured, fc6 at batch 256
 // (19.3 GFLOP per pass): forward 1 / 2 / 8 / 27 splits 320 / 175 / 113 / 148 us, backward-data 1 / 3 / 11 / 27 splits
 // 163 / 116 / 137 / 181; a 4096 -> 1000 layer forward 1 / 4 / 8 splits 127 / 41 / 27.  false = sizes or a workspace that it
-// cannot take, or a backward-weights pass over up to 32 images, whose product is one short stage of
-// 32 images: the fp32 kernel wastes less there (fc6, one image: 36 us against 43).
+// cannot take, or a backward-weights pass over up to 32 images, whose product is one short stage, mostly padding.
 // *estimate: its seconds; *limited: without the workspace's limit there is a faster one.
 bool fc_plan_split(const cct_conv_desc_t& d, int pass, long long max_bytes, long long F, FcPlan* P, double* estimate,
                    bool* limited) {
@@ -765,14 +785,9 @@ int fc_backward_weights(const cct_conv_desc_t& d, const FcPlan& P, const float* 
                         float* dw, float* dbias, char* ws, hipStream_t st) {
   float* pack = reinterpret_cast<float*>(ws + P.pack_off);
   int rc;
-  const long long oy = ((long long)d.O + kOuterRows - 1) / kOuterRows;
-  if (!P.split && (d.N <= 16 || (d.N <= 32 && (long long)d.O * P.F <= (1LL << 22))) && oy <= 65535) {
-    ProfScope ps("fc_outer_kernel", 2.0 * d.N * (double)d.O * P.F, 4.0 * ((double)d.O * P.F + (double)d.N * (P.F + d.O)), st);
-    hipLaunchKernelGGL(fc_outer_kernel, dim3((unsigned)((P.F + 4 * TPB - 1) / (4 * TPB)), (unsigned)oy), dim3(TPB), 0, st, x, dy, dw,
-                       dbias, d.N, d.O, P.F);
-    CCT_CHECK_LAUNCH();
-    return CCT_OK;
-  }
+  const long long oy = ((long long)d.O + outer_rows(d.N) - 1) / outer_rows(d.N);
+  if (!P.split && (d.N <= 16 || (d.N <= 32 && (long long)d.O * P.F <= (1LL << 22))) && oy <= 65535)
+    return launch_outer(x, dy, dw, dbias, d.N, d.O, P.F, st);
   if (P.split) {
     GemmTN p = fc_split_problem(P, d.O, P.F, x, dw);
     rc = gemm_split_operand(&p, false, dy, pack, d.N, 1, d.O, 0, 1, st);

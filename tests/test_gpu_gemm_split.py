@@ -247,7 +247,7 @@ def test_few_images(B, N, F, O):
 
 
 @pytest.mark.parametrize("N,F,O", [(1, 1023, 4099), (2, 257, 128), (3, 5, 33), (5, 1, 900), (8, 4098, 129), (16, 1025, 17),
-                                   (31, 70, 23)])
+                                   (31, 70, 23), (9, 1029, 21), (17, 1021, 13), (20, 5, 9), (32, 2050, 11)])
 def test_few_images_backward(B, N, F, O):
     """The gradients: shares of the kernels and none, up to 3 features beyond the last four, kernels past a
     workgroup's 8, up to 3 images beyond the last four.  Sums in fp32 of up to 4 products at a time: its tolerance."""
