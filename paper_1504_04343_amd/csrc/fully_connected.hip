@@ -525,19 +525,21 @@ bool fc_plan_split(const cct_conv_desc_t& d, int pass, long long max_bytes, long
     return gemm_split_seconds(fwd, !fwd || d.N > 32, M, (int)len(S), cols, n) +
            (n > 1 ? 2.0 * n * out / 5.5e12 + 2.5e-6 : 0.0);
   };
-  long long S = 1, least = 1;
-  double best = 1e30, shortest = 1e30;
+  long long S = 1;
+  double best = 1e30;
   *limited = false;
   auto each = [&](auto visit) {
     visit(1LL);
     for (int sp = 2; sp <= 64 && Kd >= (long long)sp * kFcMinSplitRows; sp += sp < 16 ? 1 : 4) visit((long long)sp);
   };
-  if (!bwdw) {
+  auto choose = [&](long long most) {
+    long long least = 1;
+    double shortest = 1e30;
     each([&](long long sp) {
       const long long n = count(sp);
       const double t = chain_seconds(p.Mpad, (cols + 127) / 128, (int)len(sp), n) + (n > 1 ? 2.0 * n * out / 6.0e12 : 0.0);
       if (t >= shortest) return;
-      if (need(sp) <= cap) {
+      if (need(sp) <= most) {
         shortest = t;
         least = sp;
       } else {
@@ -545,14 +547,19 @@ bool fc_plan_split(const cct_conv_desc_t& d, int pass, long long max_bytes, long
       }
     });
     S = least;
+    best = 1e30;
     each([&](long long sp) {
-      if (sp < least || need(sp) > cap) return;
+      if (sp < least || need(sp) > most) return;
       const double t = seconds(sp);
       if (t >= best) return;
       best = t;
       S = sp;
     });
-  }
+  };
+  // The recommended plan wherever it fits: fewer splits may need more room than it does, and must not turn it down then.
+  if (!bwdw) choose(kFcMaxPartBytes);
+  *limited = false;
+  if (!bwdw && max_bytes >= 0 && need(S) > max_bytes) choose(cap);
   *estimate = best;
   if (max_bytes >= 0 && need(S) > max_bytes) return false;
   p.Kdim = (int)len(S); p.Kpad = gemm_split_kpad(p.Kdim);

@@ -374,3 +374,19 @@ def test_benchmark_counts_every_kernel_of_the_matrix_cores():
 def test_partial_sums_of_few_channels_stay_within_their_bound(B, shape):
     """Backward-weights on conv_bwdw_few: 256 MiB of partial sums of dw at a time, and a few of the bias gradient."""
     assert B.cct_conv_workspace_bytes(B.make_desc(*shape), B.PASS_BACKWARD_WEIGHTS) <= 260 << 20
+
+
+@pytest.mark.parametrize("N,C,H,O,pass_", [(14, 303, 6, 1485, 1), (57, 151, 5, 3048, 1), (3, 473, 6, 1474, 1), (52, 320, 7, 11, 0),
+                                           (232, 48, 7, 1989, 1), (96, 125, 5, 2346, 1), (256, 256, 6, 4096, 0)])
+def test_recommended_workspace_gets_the_recommended_plan(B, N, C, H, O, pass_):
+    """Fully connected layers: a number of splits may need more room than a larger one (their partial products are a number
+    that divides the contraction), which must not take the call off the plan that the workspace was asked for."""
+    fc_plan = getattr(ctypes.CDLL(B.LIB_PATH), "_ZN3cct7fc_planERK15cct_conv_desc_tixPNS_6FcPlanE")
+    fc_plan.restype = ctypes.c_bool
+    d = B.make_desc(N, C, H, H, O, H)
+    plans = []
+    for room in (-1, B.cct_conv_workspace_bytes(d, pass_)):
+        plan = ctypes.create_string_buffer(256)
+        assert fc_plan(ctypes.byref(d), pass_, ctypes.c_longlong(room), plan)
+        plans.append(plan.raw)
+    assert plans[0] == plans[1]
