@@ -28,6 +28,10 @@ __device__ __forceinline__ void load_bias(float (&v)[N], const float* bias, int 
   if (bias) {
 #pragma unroll
     for (int r = 0; r < N; ++r) v[r] = bias[min(row(r), last)];
+    // waited for here: behind a branch around the stores it would be waited for, with them, in front of every one, whether
+    // there is a bias or not
+#pragma unroll
+    for (int r = 0; r < N; ++r) asm volatile("" : "+v"(v[r]));
   }
 }
 

@@ -386,7 +386,12 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
   float* __restrict__ cl0 = C + o0 + (long long)mw * p.c_ms;
   float* __restrict__ cl1 = C + o1 + (long long)mw * p.c_ms;
   const bool by_col = bias && p.bias_gs < 0;
-  const float cb0 = by_col ? bias[col[0]] : -0.f, cb1 = by_col ? bias[col[1]] : -0.f;
+  float cb[2] = {-0.f, -0.f};
+  if (by_col) {
+    cb[0] = bias[col[0]];
+    cb[1] = bias[col[1]];
+    asm volatile("" : "+v"(cb[0]), "+v"(cb[1]));  // waited for here, as in load_bias
+  }
   float bv[RB * 4];
   load_bias(bv, by_col ? nullptr : bias, p.M - 1, [&](int r) { return mw + r / 4 * 16 + r % 4; });
 #pragma unroll
@@ -402,8 +407,8 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
         v[j] *= kSplitUnscale;
       }
       if (m >= p.M) continue;
-      v[0] += by_col ? cb0 : bv[i * 4 + r];
-      v[1] += by_col ? cb1 : bv[i * 4 + r];
+      v[0] += by_col ? cb[0] : bv[i * 4 + r];
+      v[1] += by_col ? cb[1] : bv[i * 4 + r];
       const long long row = (long long)(i * 16 + r) * p.c_ms;
       if (both) {
         *reinterpret_cast<f32x2u*>(cl0 + row) = f32x2u{v[0], v[1]};
