@@ -6,7 +6,7 @@
 //     16 x 16 (v_mfma_f32_16x16x32_bf16), two accumulators each;
 //   - B goes from memory into the registers of the one wave that multiplies it, which splits it there: no LDS, no
 //     meeting of waves.  A lane supplies 8 k of two neighbouring columns per stage of 32 k.  The split of the next stage is
-//     written between the MFMAs of this one, 3 or 4 instructions at a time.  Columns are taken in pairs (8-byte loads and
+//     written between the MFMAs of this one, 3 or 4 instructions at a time (32 rows: behind them).  Columns are taken in pairs (8-byte loads and
 //     stores), one by one (planes of a few pixels), or k-contiguous (w of a forward product, 16-byte loads);
 //   - A is shared by the four waves through LDS: units of 16 rows and one term, in lane order, so that a read is 1 KiB
 //     without conflicts.  128 and 144 rows: packed that way and split once per call (launch_pack_rows_split), moved to
@@ -45,7 +45,11 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
   constexpr int UNITS = 3 * RB;
   constexpr int SLOT = UNITS * 1024;
   constexpr int AP = ((DIRECT ? RB : UNITS) + 3) / 4;  // what a wave moves of A per stage: rows of 16 or units
-  constexpr int RAWS = RB == 8 ? 2 : 1;  // stages of B in registers, as many as there is room for
+  // Stages of B in registers: as they were loaded, as many as there is room for, and split.  Two blocks of rows have one split
+  // stage, made behind the MFMAs of the one before: two of them, made between the MFMAs, spilled, four waves per SIMD hide the
+  // splitting as well, and it is memory that bounds them (2900 products of 8 to 32
+  // rows: 0.92 times the time, 1.04 at most).
+  constexpr int RAWS = RB == 8 ? 2 : 1, SPLITS = RB == 2 ? 1 : 2;
   // Three slots for A: the workgroup meets in front of a stage's last block of rows, behind which the next stage's first
   // operands are read.  Two (fp32 values, whose registers come first; 9 blocks of rows): between the stages.
   constexpr bool EARLY = !DIRECT && RB % 2 == 0;
@@ -138,7 +142,7 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
   };
   // The terms of a stage in b[t & 1].  The next stage's are made between the MFMAs of this one, a quarter of a
   // pair of values (3 or 4 instructions, less than an MFMA takes) at a time.
-  u32x4 b[2][2][3];
+  u32x4 b[SPLITS][2][3];
   float ra = 0.f, rb = 0.f;
   auto split_step = [&](float (&v)[2][8], int set, int n) {
     const int j = n >> 4, e = n >> 2 & 3;
@@ -286,7 +290,7 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
   int slot = 0;  // of A
   auto after = [&](int v) { return v == SLOTS - 1 ? 0 : v + 1; };
   // One stage.  A's operands of a block of rows are read behind the MFMAs of the block before; B's next ones are split
-  // behind the last 36 MFMAs (of two blocks of rows: of all), then their registers are loaded once more.  The last stage does
+  // behind the last 36 MFMAs (of two blocks of rows: behind all), then their registers are loaded once more.  The last stage does
   // none of this for a next one (a layer of 256 -> 64 channels, 8 stages, 44.0 us with it and 42.1 without; fc6's three
   // products 357 and 352).  It stands once: behind a branch on the parity of the stages its accumulators would meet
   // in different registers and spill.
@@ -315,13 +319,9 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
           acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[i % SETS][x]),
-                                                           __builtin_bit_cast(bf16x8, b[set][j][y]), acc[j], 0, 0, 0);
-          const int n = i * 12 + k + j - (RB * 12 - (RB > 2 ? 36 : 22));
-          if (MORE && RB > 2 && n >= 0 && n < 32) split_step(raw[RAWS == 2 ? set ^ 1 : 0], set ^ 1, n);
-          if (MORE && RB == 2 && n >= 0 && n < 16) {
-            split_step(raw[RAWS == 2 ? set ^ 1 : 0], set ^ 1, 2 * n);
-            split_step(raw[RAWS == 2 ? set ^ 1 : 0], set ^ 1, 2 * n + 1);
-          }
+                                                           __builtin_bit_cast(bf16x8, b[set % SPLITS][j][y]), acc[j], 0, 0, 0);
+          const int n = i * 12 + k + j - (RB * 12 - 36);
+          if (MORE && SPLITS == 2 && n >= 0 && n < 32) split_step(raw[RAWS == 2 ? set ^ 1 : 0], (set ^ 1) % SPLITS, n);
           __builtin_amdgcn_sched_barrier(0);
         }
       };
@@ -342,6 +342,10 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
       }
     }
     if constexpr (!DIRECT && !EARLY && MORE) __builtin_amdgcn_s_waitcnt(0x0f70);  // A of the next stage is in place
+    if (MORE && SPLITS == 1) {
+#pragma unroll
+      for (int n = 0; n < 32; ++n) split_step(raw[RAWS == 2 ? set ^ 1 : 0], 0, n);
+    }
     if (MORE) load_b(RAWS == 2 ? set ^ 1 : 0, t + 1 + RAWS, false);
     slot = next;
   };
@@ -359,10 +363,12 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
   }
   if (t < last) {
     stage(t, 0, more);
+    if constexpr (SPLITS == 2) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+      for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int q = 0; q < 3; ++q) b[0][j][q] = b[1][j][q];
+        for (int q = 0; q < 3; ++q) b[0][j][q] = b[1][j][q];
+    }
     ++t;
   }
   stage(t, 0, end);
