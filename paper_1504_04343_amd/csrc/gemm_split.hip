@@ -38,24 +38,27 @@ typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));  // 8 byte
 enum AForm { kPacked, kRows, kStrided };     // fp32: k-contiguous, or any strides
 enum BForm { kColumns, kPairs, kContiguous };  // column-contiguous: one by one, in pairs; k-contiguous
 
-template <int RB, BForm BF, AForm AF>
-__global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(GemmTN p, int Ktotal, int tiles_m, int tiles_n) {
+// ALONE: every wave splits A's values itself, without LDS and without meeting; 1: a contraction of one stage.  In products
+// of few rows, which wait for memory, fewer registers and more waves are worth it: one stage of 32 rows, 16 rows of any number
+// (14 <- 9 channels, 540000 columns in two groups: 22.6 us as a pack and a product, 36.7 with LDS, 24 so).
+template <int RB, BForm BF, AForm AF, int ALONE = 0>
+__global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : ALONE && (RB == 1 || ALONE == 1) ? 5 : 4) void gemm_split(GemmTN p, int Ktotal, int tiles_m, int tiles_n) {
   constexpr int BM = 16 * RB;
   constexpr bool DIRECT = AF != kPacked, BT = BF == kContiguous;
   constexpr int UNITS = 3 * RB;
   constexpr int SLOT = UNITS * 1024;
-  constexpr int AP = ((DIRECT ? RB : UNITS) + 3) / 4;  // what a wave moves of A per stage: rows of 16 or units
+  constexpr int AP = ALONE ? RB : ((DIRECT ? RB : UNITS) + 3) / 4;  // what a wave moves of A per stage: rows of 16 or units
   // Stages of B in registers: as they were loaded, as many as there is room for, and split.  Two blocks of rows have one split
   // stage, made behind the MFMAs of the one before: two of them, made between the MFMAs, spilled, four waves per SIMD hide the
   // splitting as well, and it is memory that bounds them (2900 products of 8 to 32
   // rows: 0.92 times the time, 1.04 at most).
-  constexpr int RAWS = RB == 8 ? 2 : 1, SPLITS = RB == 2 ? 1 : 2;
+  constexpr int RAWS = RB == 8 ? 2 : 1, SPLITS = RB <= 2 ? 1 : 2;
   // Three slots for A: the workgroup meets in front of a stage's last block of rows, behind which the next stage's first
   // operands are read.  Two (fp32 values, whose registers come first; 9 blocks of rows): between the stages.
   constexpr bool EARLY = !DIRECT && RB % 2 == 0;
   constexpr int SLOTS = EARLY ? 3 : 2;
 
-  __shared__ __attribute__((aligned(16))) unsigned char As[SLOTS * SLOT];
+  __shared__ __attribute__((aligned(16))) unsigned char As[ALONE ? 16 : SLOTS * SLOT];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -106,14 +109,15 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
     voff[j] = BT ? (unsigned)((long long)(col - n0) * p.b_ks + kg * 8) * 4u
                  : (unsigned)(col_offset(p.bmap, col) - (long long)n_f * p.bmap.img_stride + (long long)kg * 8 * p.b_ks) * 4u;
   }
-  // k past the last one: what lies there, or zero beyond the tensor's end; in the first stages, which may be all there are, the
-  // last one again (short_end).  A is zero there; an infinity only costs the recomputation.  The range is checked against the
-  // vector offset alone: all of an address that may lie beyond goes there.  Stages past the last one have a range of nothing: as
-  // many loads are in flight as ever, but none goes to memory (a contraction of one stage would read B three times).
+  // k past the last one: the last one again (in a contraction of 35 reading on was half of what came from memory); k-contiguous
+  // what lies there, or zero beyond the tensor's end.  A is zero there; an infinity only costs the recomputation.  The range is
+  // checked against the vector offset alone: all of an address that may lie beyond goes there.  Stages past the last one have a
+  // range of nothing: as many loads are in flight as ever, but none goes to memory (a contraction of one stage would read B
+  // three times).
   const long long b_left = p.b_len - (Bt - reinterpret_cast<const float*>(p.B));
   auto range = [](long long left) { return left < 0 ? 0 : left >= 0x1fffffff ? 0x7fffffff : (int)left * 4; };
   float raw[RAWS][2][8];
-  auto load_b = [&](int set, int t, bool short_end) {
+  auto load_b = [&](int set, int t) {
     const int tt = min(t, last);
     const long long at = (long long)tt * SK * (BT ? 1 : p.b_ks);
     const __amdgpu_buffer_rsrc_t rs =
@@ -132,11 +136,11 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
 #pragma unroll
           for (int i = 0; i < 4; ++i) raw[set][j][e * 4 + i] = v[i];
         } else if constexpr (BF == kPairs) {
-          const f32x2 v = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(rs, (int)(short_end ? min(voff[0] + e * ks, end[0]) : voff[0] + e * ks), 0, 0));
+          const f32x2 v = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(rs, (int)min(voff[0] + e * ks, end[0]), 0, 0));
           raw[set][0][e] = v[0];
           raw[set][1][e] = v[1];
         } else {
-          raw[set][j][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (int)(short_end ? min(voff[j] + e * ks, end[j]) : voff[j] + e * ks), 0, 0));
+          raw[set][j][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (int)min(voff[j] + e * ks, end[j]), 0, 0));
         }
       }
   };
@@ -184,7 +188,7 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
     Ad = reinterpret_cast<const float*>(p.A) + g * p.a_gs + (long long)r0 * p.a_ms;
 #pragma unroll
     for (int u = 0; u < AP; ++u) {
-      const int m = min(m0 + (wave + 4 * u) * 16 + lo, p.M - 1), r = m / p.a_taps;
+      const int m = min(m0 + (ALONE ? u : wave + 4 * u) * 16 + lo, p.M - 1), r = m / p.a_taps;
       a_voff[u] = (unsigned)((r - r0) * p.a_ms + (m - r * p.a_taps) + kg * 8 * p.a_ks) * 4u;
     }
   } else {
@@ -208,7 +212,7 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
     asm volatile("" : "+s"(ks));
 #pragma unroll
     for (int u = 0; u < AP; ++u) {
-      if (4 * u + 4 > RB && wave + 4 * u >= RB) continue;
+      if (!ALONE && 4 * u + 4 > RB && wave + 4 * u >= RB) continue;
       if constexpr (AF == kRows) {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -224,22 +228,25 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
       }
     }
   };
-  auto store_a = [&](int t, int slot) {
+  auto split_a = [&](int t, int u, u32x4 (&q)[3]) {
     const int over = kd - t * SK - kg * 8;  // a lane's values from here on are past the last k: zero
+#pragma unroll
+    for (int e = 0; e < 8; ++e) av[u][e] = e < over ? av[u][e] : 0.f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      unsigned h, m, l;
+      split_pair(av[u][2 * e], av[u][2 * e + 1], &h, &m, &l);
+      q[0][e] = h;
+      q[1][e] = m;
+      q[2][e] = l;
+    }
+  };
+  auto store_a = [&](int t, int slot) {
 #pragma unroll
     for (int u = 0; u < AP; ++u) {
       if (4 * u + 4 > RB && wave + 4 * u >= RB) continue;
       u32x4 q[3];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) av[u][e] = e < over ? av[u][e] : 0.f;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        unsigned h, m, l;
-        split_pair(av[u][2 * e], av[u][2 * e + 1], &h, &m, &l);
-        q[0][e] = h;
-        q[1][e] = m;
-        q[2][e] = l;
-      }
+      split_a(t, u, q);
 #pragma unroll
       for (int i = 0; i < 3; ++i)
         *reinterpret_cast<u32x4*>(As + slot * SLOT + ((wave + 4 * u) * 3 + i) * 1024 + lane * 16) = q[i];
@@ -255,20 +262,20 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
       for (int r = 0; r < 4; ++r) acc_h[i][j][r] = acc_c[i][j][r] = 0.f;
 
   if constexpr (DIRECT) load_a(0); else move_a(0, 0);
-  load_b(0, 0, true);
-  if constexpr (DIRECT) {
+  load_b(0, 0);
+  if constexpr (DIRECT && !ALONE) {
     store_a(0, 0);
     load_a(1);
   }
   if constexpr (EARLY) move_a(1, 1);
-  if (RAWS == 2) load_b(1, 1, true);
+  if (RAWS == 2) load_b(1, 1);
 #pragma unroll
   for (int n = 0; n < 32; ++n) split_step(raw[0], 0, n);
-  load_b(0, RAWS, false);
+  if constexpr (ALONE != 1) load_b(0, RAWS);
   if constexpr (!DIRECT) __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
 
   // Two sets of A's operands; where registers decide how many workgroups share a CU, one, read term by term
-  constexpr int SETS = RB == 2 ? 1 : 2;
+  constexpr int SETS = RB <= 2 ? 1 : 2;
   u32x4 a[SETS][3];
   auto read_a = [&](int i, int q, int at) {
     a[i % SETS][q] = *reinterpret_cast<const u32x4*>(As + at * SLOT + (i % RB * 3 + q) * 1024 + lane * 16);
@@ -297,7 +304,7 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
   auto stage = [&](int t, int set, auto more) {
     constexpr bool MORE = decltype(more)::value;
     const int next = after(slot);
-    if constexpr (!EARLY) {
+    if constexpr (!EARLY && !ALONE) {
       meet();  // A of this stage is visible, nobody reads the other slot any more
       if constexpr (!DIRECT && MORE) move_a(t + 1, next);
 #pragma unroll
@@ -311,7 +318,12 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
         meet();  // A of the next stage is visible, nobody reads the slot before this one any more
         move_a(t + 2, after(next));
       }
+      if constexpr (ALONE) {
+        split_a(t, i, a[0]);
+        if (MORE && i == RB - 1) load_a(t + 1);
+      }
       auto read = [&](int q) {
+        if (ALONE) return;
         if (i + 1 < RB) read_a(i + 1, q, slot);
         else if (EARLY && MORE) read_a(i + 1, q, next);
       };
@@ -336,7 +348,7 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
       mfma(8, 0, 1, acc_c[i]);
       mfma(10, 0, 0, acc_h[i]);
       if (SETS == 1) read(0);
-      if (DIRECT && MORE && i == (RB - 1) / 2) {
+      if (DIRECT && !ALONE && MORE && i == (RB - 1) / 2) {
         store_a(min(t + 1, last), next);
         load_a(t + 2);
       }
@@ -346,7 +358,7 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
 #pragma unroll
       for (int n = 0; n < 32; ++n) split_step(raw[RAWS == 2 ? set ^ 1 : 0], 0, n);
     }
-    if (MORE) load_b(RAWS == 2 ? set ^ 1 : 0, t + 1 + RAWS, false);
+    if (MORE) load_b(RAWS == 2 ? set ^ 1 : 0, t + 1 + RAWS);
     slot = next;
   };
   if constexpr (EARLY) {
@@ -357,19 +369,24 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
   constexpr std::true_type more;
   constexpr std::false_type end;
   int t = 0;
-  for (; t + 2 < stages; t += 2) {
-    stage(t, 0, more);
-    stage(t + 1, 1, more);
-  }
-  if (t < last) {
-    stage(t, 0, more);
-    if constexpr (SPLITS == 2) {
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int q = 0; q < 3; ++q) b[0][j][q] = b[1][j][q];
+  if constexpr (ALONE) {
+    if constexpr (ALONE != 1)
+      for (; t < last; ++t) stage(t, 0, more);
+  } else {
+    for (; t + 2 < stages; t += 2) {
+      stage(t, 0, more);
+      stage(t + 1, 1, more);
     }
-    ++t;
+    if (t < last) {
+      stage(t, 0, more);
+      if constexpr (SPLITS == 2) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int q = 0; q < 3; ++q) b[0][j][q] = b[1][j][q];
+      }
+      ++t;
+    }
   }
   stage(t, 0, end);
   if constexpr (!DIRECT) __builtin_amdgcn_s_waitcnt(0x0f70);  // nothing is moved into LDS after the end
@@ -382,7 +399,7 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : 4) void gemm_split(
   // took 2 % of fc6's products and 4 % of a 4096 -> 1000 layer's)
   float check = 0.f;
   int first = n0 + wave * 32 + 2 * lo;
-  asm volatile("" : "+v"(first));  // not kept from before
+  if constexpr (!ALONE) asm volatile("" : "+v"(first));  // not kept from before
   bool live[2];
   int col[2];
 #pragma unroll
@@ -531,7 +548,7 @@ bool gemm_split_fits(const GemmTN& p, bool bt) {
 }
 
 namespace {
-// The forms: tiles of 32 and 64 rows, which read A in place and split it themselves, and of 128 and 144, for which it is
+// The forms: tiles of 32 (16 where that is all) and 64 rows, which read A in place and split it themselves, and of 128 and 144, for which it is
 // packed first.  A launch less is what counts where the chip is not full (33 to 512 images of fully connected layers,
 // up to 2 GFLOP: 0.6 to 0.8 times the time of a pack and a product); large products split A once per column tile too often.
 
@@ -583,7 +600,7 @@ const Form* choose(bool bt, int M, int K, long long cols, long long G, Fits fits
   return best;
 }
 
-template <int RB, BForm BF, AForm AF>
+template <int RB, BForm BF, AForm AF, int ALONE = 0>
 int launch_variant(const GemmTN& p, int Ktotal, hipStream_t st) {
   const int tiles_m = (p.M + 16 * RB - 1) / (16 * RB), tiles_n = ((BF == kPairs ? p.pair_cols : p.Ncols) + BN - 1) / BN;
   const long long blocks = (long long)tiles_m * tiles_n;
@@ -591,19 +608,26 @@ int launch_variant(const GemmTN& p, int Ktotal, hipStream_t st) {
   const double mk = (double)p.M * p.Kdim * p.G, kn = (double)p.Kdim * p.Ncols * p.G;
   ProfScope ps(2.0 * p.M * kn, (AF == kPacked ? 6.0 : 4.0) * mk + 4.0 * kn + 4.0 * (double)p.M * p.Ncols * p.G, st,
                "gemm_split<%d, %s>", 16 * RB, BF == kContiguous ? "k-contiguous" : "in place");
-  hipLaunchKernelGGL((gemm_split<RB, BF, AF>), dim3((unsigned)blocks, (unsigned)p.G), dim3(NT), 0, st, p, Ktotal,
+  hipLaunchKernelGGL((gemm_split<RB, BF, AF, ALONE>), dim3((unsigned)blocks, (unsigned)p.G), dim3(NT), 0, st, p, Ktotal,
                      tiles_m, tiles_n);
   CCT_CHECK_LAUNCH();
   return CCT_OK;
 }
 
+template <BForm BF, AForm AF>
+int launch_in_place(const GemmTN& p, int Ktotal, hipStream_t st) {
+  if (p.rb == 4) return launch_variant<4, BF, AF>(p, Ktotal, st);
+  const bool one = p.Kdim <= SK;
+  if (p.M <= 16) return one ? launch_variant<1, BF, AF, 1>(p, Ktotal, st) : launch_variant<1, BF, AF, 2>(p, Ktotal, st);
+  return one ? launch_variant<2, BF, AF, 1>(p, Ktotal, st) : launch_variant<2, BF, AF>(p, Ktotal, st);
+}
+
 template <BForm BF>
 int launch_columns(const GemmTN& p, int Ktotal, hipStream_t st) {
   if (!p.a_ms) return p.rb == 8 ? launch_variant<8, BF, kPacked>(p, Ktotal, st) : launch_variant<9, BF, kPacked>(p, Ktotal, st);
-  if (p.a_ks == 1 && p.a_taps == 1)
-    return p.rb == 2 ? launch_variant<2, BF, kRows>(p, Ktotal, st) : launch_variant<4, BF, kRows>(p, Ktotal, st);
+  if (p.a_ks == 1 && p.a_taps == 1) return launch_in_place<BF, kRows>(p, Ktotal, st);
   if constexpr (BF == kContiguous) return CCT_EUNSUPPORTED;
-  else return p.rb == 2 ? launch_variant<2, BF, kStrided>(p, Ktotal, st) : launch_variant<4, BF, kStrided>(p, Ktotal, st);
+  else return launch_in_place<BF, kStrided>(p, Ktotal, st);
 }
 
 int launch_pack_rows_split(const float* src, void* pack, int G, int M, int Mpad, int Kpad, int Kdim, int Ktotal,
