@@ -212,32 +212,6 @@ __global__ __launch_bounds__(NT, RB * CB <= 6 && CB < 3 ? 4 : 2) void conv_bwdw_
   u32x4 a[3], b[CB][3];
   u32x4 q[3];
   float ra = 0.f, rb = 0.f;
-  // a quarter of a pair of values
-  auto split_step = [&](float (&v)[kImg], int n) {
-    const int e = n >> 2;
-    if (n & 3)
-      asm volatile("" : "+v"(ra), "+v"(rb));
-    else
-      asm volatile("" : "+v"(v[2 * e]), "+v"(v[2 * e + 1]));
-    switch (n & 3) {
-      case 0:
-        ra = v[2 * e] * kSplitScale;
-        rb = v[2 * e + 1] * kSplitScale;
-        q[0][e] = cvt_pk_bf16(ra, rb);
-        break;
-      case 1:
-        ra -= bf16_lo(q[0][e]);
-        rb -= bf16_hi(q[0][e]);
-        break;
-      case 2:
-        q[1][e] = cvt_pk_bf16(ra, rb);
-        ra -= bf16_lo(q[1][e]);
-        break;
-      default:
-        rb -= bf16_hi(q[1][e]);
-        q[2][e] = cvt_pk_bf16(ra, rb);
-    }
-  };
 
   for (int r = r0; r < r1; ++r) {
     const int slot = (r - r0) & 1;
@@ -276,7 +250,7 @@ __global__ __launch_bounds__(NT, RB * CB <= 6 && CB < 3 ? 4 : 2) void conv_bwdw_
               }
               if (n * PER < 16)
 #pragma unroll
-                for (int e = 0; e < PER; ++e) split_step(v, n * PER + e);
+                for (int e = 0; e < PER; ++e) split_quarter(v, q, n * PER + e, ra, rb);
               if (n == 16 / PER) {  // the buffer is free
                 if (f < UD && r + 1 < r1 && y_mine(f)) add_sum(v, f, false);
                 load_phase(v, f, r + 2, x_to & 255);

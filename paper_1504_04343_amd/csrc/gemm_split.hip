@@ -148,33 +148,7 @@ __global__ __launch_bounds__(NT, RB >= 8 ? 2 : RB == 4 ? 3 : ALONE && (RB == 1 |
   // pair of values (3 or 4 instructions, less than an MFMA takes) at a time.
   u32x4 b[SPLITS][2][3];
   float ra = 0.f, rb = 0.f;
-  auto split_step = [&](float (&v)[2][8], int set, int n) {
-    const int j = n >> 4, e = n >> 2 & 3;
-    u32x4(&q)[3] = b[set][j];
-    // keeps a step where it is written: it would be moved in front of all MFMAs
-    if (n & 3)
-      asm volatile("" : "+v"(ra), "+v"(rb));
-    else
-      asm volatile("" : "+v"(v[j][2 * e]), "+v"(v[j][2 * e + 1]));
-    switch (n & 3) {
-      case 0:
-        ra = v[j][2 * e] * kSplitScale;
-        rb = v[j][2 * e + 1] * kSplitScale;
-        q[0][e] = cvt_pk_bf16(ra, rb);
-        break;
-      case 1:
-        ra -= bf16_lo(q[0][e]);
-        rb -= bf16_hi(q[0][e]);
-        break;
-      case 2:
-        q[1][e] = cvt_pk_bf16(ra, rb);
-        ra -= bf16_lo(q[1][e]);
-        break;
-      default:
-        rb -= bf16_hi(q[1][e]);
-        q[2][e] = cvt_pk_bf16(ra, rb);
-    }
-  };
+  auto split_step = [&](float (&v)[2][8], int set, int n) { split_quarter(v[n >> 4], b[set][n >> 4], n & 15, ra, rb); };
 
   // ---- A: through LDS.  Units of 16 rows and one term, 1 KiB, in lane order: packed ones are moved there directly,
   // fp32 values pass through registers

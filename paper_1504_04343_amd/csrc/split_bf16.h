@@ -55,6 +55,35 @@ __device__ __forceinline__ void split_pair(float a, float b, unsigned* h, unsign
   *l = cvt_pk_bf16(ra - bf16_lo(*m), rb - bf16_hi(*m));
 }
 
+// A quarter of splitting a pair of 8 values, 3 or 4 instructions, for kernels that write it between their MFMAs: step
+// n = 4 e + 0 .. 3 of pair e.  ra and rb hold what is left of the pair in between.
+__device__ __forceinline__ void split_quarter(float (&v)[8], u32x4 (&q)[3], int n, float& ra, float& rb) {
+  const int e = n >> 2;
+  // keeps a step where it is written: it would be moved in front of all MFMAs
+  if (n & 3)
+    asm volatile("" : "+v"(ra), "+v"(rb));
+  else
+    asm volatile("" : "+v"(v[2 * e]), "+v"(v[2 * e + 1]));
+  switch (n & 3) {
+    case 0:
+      ra = v[2 * e] * kSplitScale;
+      rb = v[2 * e + 1] * kSplitScale;
+      q[0][e] = cvt_pk_bf16(ra, rb);
+      break;
+    case 1:
+      ra -= bf16_lo(q[0][e]);
+      rb -= bf16_hi(q[0][e]);
+      break;
+    case 2:
+      q[1][e] = cvt_pk_bf16(ra, rb);
+      ra -= bf16_lo(q[1][e]);
+      break;
+    default:
+      rb -= bf16_hi(q[1][e]);
+      q[2][e] = cvt_pk_bf16(ra, rb);
+  }
+}
+
 // One value -> h, m, l for a pack that the recomputation reads back.  A value that does not split (not finite,
 // or 2^104 and more) leaves NaN in h, which every result of its row meets, and its bits in m and l.
 __device__ __forceinline__ void split_value(float v, unsigned short* h, unsigned short* m,
