@@ -67,9 +67,9 @@ __global__ __launch_bounds__(256) void bwdw_img_prep(PrepJob j0, PrepJob j1, int
   const long long plane = (long long)j.H * j.W, img = (long long)j.C * plane;
   const float* src = j.src + (long long)ig * kImg * img + (long long)tc * kPrepCh * plane;
   const int nv = min(kImg, nimg - ig * kImg);
-  // conv2 at batch 256 145 -> 118 us.  Buffer loads whose range check supplies the zeros, so that all are on their way before the first is waited for:
-  // with a branch around each, whole groups of them were waited for in turn.  A plane is less than 2^24 pixels: 32-bit
-  // byte offsets inside a tile of channels.
+  // Buffer loads whose range check supplies the zeros, so that all are on their way before the first is waited for: with
+  // a branch around each, whole groups of them were waited for in turn (conv2 at batch 256 145 -> 118 us).  A plane is
+  // less than 2^24 pixels: 32-bit byte offsets inside a tile of channels.
   float v[kPrepCh / 8][kImg];
   const unsigned first = (unsigned)((cr * (int)plane + h * j.W + w) * 4);
 #pragma unroll
@@ -513,56 +513,57 @@ int launch_bwdw_img(const cct_conv_desc_t& d, const BwdwImgPlan& P, int nimg, co
     if (const int rc = launch_bwdw_few(d, P.fp, nimg, x, dy, part, sums, st)) return rc;
   } else {
     const PrepJob jx = job(x, P.xs_off, d.C, d.H, d.W, d.pad);
-  PrepJob jy = job(dy, P.ds_off, d.O, Hout, Wout, 0);
-  jy.sums = sums;
-  nsums = igs * jy.tiles_px;
-  const int bx = igs * jx.tiles_px * jx.tiles_c, by = igs * jy.tiles_px * jy.tiles_c;
-  const double xn = (double)nimg * d.C * d.H * d.W, yn = (double)nimg * d.O * pix;
-  {
-    ProfScope ps(P.terms == 3 ? "bwdw_img_prep<3>" : "bwdw_img_prep<1>", 0.0, (4.0 + 2.0 * P.terms) * (xn + yn), st);
-    if (P.terms == 3)
-      hipLaunchKernelGGL(bwdw_img_prep<3>, dim3((unsigned)(bx + by)), dim3(256), 0, st, jx, jy, bx, nimg);
-    else
-      hipLaunchKernelGGL(bwdw_img_prep<1>, dim3((unsigned)(bx + by)), dim3(256), 0, st, jx, jy, bx, nimg);
-    CCT_CHECK_LAUNCH();
-  }
-  ImgGemm q;
-  memset(&q, 0, sizeof(q));
-  q.xs = reinterpret_cast<const unsigned char*>(ws + P.xs_off);
-  q.ds = reinterpret_cast<const unsigned char*>(ws + P.ds_off);
-  q.part = part;
-  q.M = Og; q.N = Cg * KK; q.G = d.groups;
-  q.Cg = Cg; q.Og = Og; q.C = d.C; q.O = d.O; q.K = d.K; q.KK = KK; q.s = d.stride; q.Wp = Wp;
-  q.img_cells = (long long)Hp * Wp;
-  q.P = pix; q.Wout = Wout;
-  q.ncols = igs * pix;
-  q.split_cols = P.split_cols;
-  q.S = P.S;
-  q.tiles_m = (Og + P.BM - 1) / P.BM;
-  q.tiles_n = (q.N + BN - 1) / BN;
-  make_fastdiv_parts(pix, &q.mP, &q.sP);
-  make_fastdiv_parts(Wout, &q.mWout, &q.sWout);
-  const long long blocks = (long long)q.tiles_m * q.tiles_n * q.S;
-  if (blocks <= 0 || blocks >= 2147483647LL || d.groups > 65535) return CCT_EUNSUPPORTED;
-  {
-    ProfScope ps(2.0 * yn * Cg * KK, 2.0 * P.terms * (xn + yn) + 4.0 * q.S * (double)d.O * q.N, st,
-                 "conv_bwdw_img<%d, %d, %d>", P.BM, P.terms, P.terms == 1 ? 8 : 12);
-    const dim3 grid((unsigned)blocks, (unsigned)d.groups);
-    int rc;
-    if (P.BM == 128)
-      rc = P.terms == 3 ? launch_product<128, 3, 12>(q, grid, st) : launch_product<128, 1, 8>(q, grid, st);
-    else if (P.BM == 96)
-      rc = launch_product<96, 3, 12>(q, grid, st);
-    else
-      rc = P.terms == 3 ? launch_product<64, 3, 12>(q, grid, st) : launch_product<64, 1, 8>(q, grid, st);
-    if (rc) return rc;
-  }
+    PrepJob jy = job(dy, P.ds_off, d.O, Hout, Wout, 0);
+    jy.sums = sums;
+    nsums = igs * jy.tiles_px;
+    const int bx = igs * jx.tiles_px * jx.tiles_c, by = igs * jy.tiles_px * jy.tiles_c;
+    const double xn = (double)nimg * d.C * d.H * d.W, yn = (double)nimg * d.O * pix;
+    {
+      ProfScope ps(P.terms == 3 ? "bwdw_img_prep<3>" : "bwdw_img_prep<1>", 0.0, (4.0 + 2.0 * P.terms) * (xn + yn), st);
+      if (P.terms == 3)
+        hipLaunchKernelGGL(bwdw_img_prep<3>, dim3((unsigned)(bx + by)), dim3(256), 0, st, jx, jy, bx, nimg);
+      else
+        hipLaunchKernelGGL(bwdw_img_prep<1>, dim3((unsigned)(bx + by)), dim3(256), 0, st, jx, jy, bx, nimg);
+      CCT_CHECK_LAUNCH();
+    }
+    ImgGemm q;
+    memset(&q, 0, sizeof(q));
+    q.xs = reinterpret_cast<const unsigned char*>(ws + P.xs_off);
+    q.ds = reinterpret_cast<const unsigned char*>(ws + P.ds_off);
+    q.part = part;
+    q.M = Og; q.N = Cg * KK; q.G = d.groups;
+    q.Cg = Cg; q.Og = Og; q.C = d.C; q.O = d.O; q.K = d.K; q.KK = KK; q.s = d.stride; q.Wp = Wp;
+    q.img_cells = (long long)Hp * Wp;
+    q.P = pix; q.Wout = Wout;
+    q.ncols = igs * pix;
+    q.split_cols = P.split_cols;
+    q.S = P.S;
+    q.tiles_m = (Og + P.BM - 1) / P.BM;
+    q.tiles_n = (q.N + BN - 1) / BN;
+    make_fastdiv_parts(pix, &q.mP, &q.sP);
+    make_fastdiv_parts(Wout, &q.mWout, &q.sWout);
+    const long long blocks = (long long)q.tiles_m * q.tiles_n * q.S;
+    if (blocks <= 0 || blocks >= 2147483647LL || d.groups > 65535) return CCT_EUNSUPPORTED;
+    {
+      ProfScope ps(2.0 * yn * Cg * KK, 2.0 * P.terms * (xn + yn) + 4.0 * q.S * (double)d.O * q.N, st,
+                   "conv_bwdw_img<%d, %d, %d>", P.BM, P.terms, P.terms == 1 ? 8 : 12);
+      const dim3 grid((unsigned)blocks, (unsigned)d.groups);
+      int rc;
+      if (P.BM == 128)
+        rc = P.terms == 3 ? launch_product<128, 3, 12>(q, grid, st) : launch_product<128, 1, 8>(q, grid, st);
+      else if (P.BM == 96)
+        rc = launch_product<96, 3, 12>(q, grid, st);
+      else
+        rc = P.terms == 3 ? launch_product<64, 3, 12>(q, grid, st) : launch_product<64, 1, 8>(q, grid, st);
+      if (rc) return rc;
+    }
   }
   ImgReduce r;
   memset(&r, 0, sizeof(r));
   r.part = part; r.dw = dw; r.sums = sums; r.dbias = dbias; r.x = x; r.dy = dy;
   r.M = Og; r.N = Cg * KK; r.G = d.groups; r.S = P.S; r.K = d.K; r.KK = KK; r.Cg = Cg; r.Og = Og;
-  r.C = d.C; r.O = d.O; r.H = d.H; r.W = d.W; r.P = pix; r.Wout = Wout; make_fastdiv_parts(Wout, &r.mWout, &r.sWout); r.s = d.stride; r.pad = d.pad;
+  r.C = d.C; r.O = d.O; r.H = d.H; r.W = d.W; r.P = pix; r.Wout = Wout; r.s = d.stride; r.pad = d.pad;
+  make_fastdiv_parts(Wout, &r.mWout, &r.sWout);
   r.nimg = nimg;
   r.nsums = nsums;
   r.accumulate = accumulate;
