@@ -341,6 +341,9 @@ int launch_outer(const float* x, const float* dy, float* dw, float* dbias, int N
 // chip.  One image of fc6 (151 MB) 38.2 us on 32-row tiles of the matrix cores behind a pack, 31.4 now; 4096 -> 1000
 // 14.8 -> 11; with 16 images registers leave too few waves in flight (41 and 77).
 constexpr int kRowsWaves = 8, kRowsFeatures = 256;
+// Fewer kernels add every product in 64 bits, as a wave has at most 8 of them then: 2.5e-8 in the 2-norm at any number of
+// kernels, where sums of four are 4.7e-8 (8 images, 32 to 256 kernels).
+constexpr int kFourKernels = 64;
 template <int ROWS, class Acc = double>
 __global__ __launch_bounds__(64 * kRowsWaves) void fc_backward_data_few(const float* __restrict__ w, const float* __restrict__ dy,
                                                                   float* __restrict__ out, int N, int O, int F, int share) {
@@ -355,7 +358,7 @@ __global__ __launch_bounds__(64 * kRowsWaves) void fc_backward_data_few(const fl
   for (int n = 0; n < ROWS; ++n)
 #pragma unroll
     for (int e = 0; e < 4; ++e) acc[n][e] = 0;
-  // 4 kernels at a time: their loads in flight together, their products summed in 32 bits, where there are many, and all in
+  // 4 kernels at a time: their loads in flight together, from kFourKernels on their products summed in 32 bits and all in
   // 64 (8 images of 512 -> 64: 2-norm 6.8e-8 in 32 bits, 4.8e-8 so and on the matrix cores)
   for (int o = o_begin; o < o_end; o += 4) {
     float v[4][4];
@@ -395,7 +398,7 @@ __global__ __launch_bounds__(64 * kRowsWaves) void fc_backward_data_few(const fl
         }
       }
     };
-    if (live == 4 && O >= 64) add(std::integral_constant<bool, true>());
+    if (live == 4 && O >= kFourKernels) add(std::integral_constant<bool, true>());
     else add(std::integral_constant<bool, false>());
   }
   // the waves' sums, a row of dx at a time
