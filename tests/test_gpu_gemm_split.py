@@ -273,3 +273,64 @@ def test_odd_planes(B, L):
     assert any(n.startswith("gemm_split") for n in names), names
     assert rel_err(got, oracle.conv_forward(odims(oracle, L), x, w, b)) <= TOL_F32
     assert rel_err(gpu_backward_data(B, L, w, dy), oracle.conv_backward_data(odims(oracle, L), w, dy)) <= TOL_F32
+
+
+FEW = [(1, 2053, 70), (4, 4099, 33), (8, 300, 600), (8, 1029, 129), (16, 1029, 21), (27, 70, 23)]
+
+
+def few_passes(B, L, x, w, dy, dy_w=None):
+    """(result, oracle) of every pass that runs on a kernel for few images; dy_w: backward-weights' gradient."""
+    dy_w = dy if dy_w is None else dy_w
+    od = odims(oracle, L)
+    if L.N <= 8:
+        got, names = ran(B, lambda: gpu_forward(B, L, x, w, None))
+        assert len(names) == 1 and names[0].startswith("fc_forward_few<"), names
+        yield got, oracle.conv_forward(od, x, w, None)
+        got, names = ran(B, lambda: gpu_backward_data(B, L, w, dy))
+        assert any(n.startswith("fc_backward_data_few") for n in names), names
+        yield got, oracle.conv_backward_data(od, w, dy)
+    (dw, db), names = ran(B, lambda: gpu_backward_weights(B, L, x, dy_w))
+    assert names == ["fc_outer_kernel"], names
+    want = oracle.conv_backward_weights(od, x, dy_w)
+    yield dw, want[0]
+    yield db, want[1]
+
+
+@pytest.mark.parametrize("e,f", [(-118, 88), (70, -50), (103, -83)], ids=lambda e: "2^%d" % e)
+@pytest.mark.parametrize("N,F,O", FEW)
+def test_range_of_fp32_few_images(B, N, F, O, e, f):
+    """In the 2-norm no further from 64 bits than the bound of the split product, whatever the operands' magnitude: at most
+    4 products of a chain and, of 32 images, 8 such sums are added up in fp32, a rounding of 2^-24 each."""
+    L = layer("fc", N, F, 1, 1, O, 1)
+    x, w = np.ldexp(synth.make_x(L, 4), e).astype(np.float32), np.ldexp(synth.make_w(L, 4), f).astype(np.float32)
+    dy, dy_w = (np.ldexp(synth.make_dy(L, 4), k).astype(np.float32) for k in (e, f))
+    for got, want in few_passes(B, L, x, w, dy, dy_w):
+        assert np.linalg.norm(got.astype(np.float64) - want) <= 5e-7 * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("N,F,O", FEW)
+def test_not_finite_few_images(B, N, F, O):
+    """Infinities, NaN and values near the end of fp32's range reach exactly the results they reach in fp32, whole steps and
+    remainders alike.  1e37: products that stay in the range, where one that left it would be another infinity."""
+    L = layer("fc", N, F, 1, 1, O, 1)
+    rows = (0, 1, 1, -1) if N > 2 else (0, 0, 0, 0)
+    x, dy = (not_finite(t, rows, 1e37) for t in (synth.make_x(L, 8), synth.make_dy(L, 8)))
+    w = not_finite(synth.make_w(L, 8), (3, 7, 9, 12), 1.0)
+    if N > 2:
+        x[0, F - 1] = np.inf  # among the features beyond the last four
+        passes = few_passes(B, L, x, w, dy)
+    else:  # a single row would leave nothing finite: one operand of a pass at a time
+        passes = [*few_passes(B, L, synth.make_x(L, 8), w, synth.make_dy(L, 8))][:2]
+        passes += [*few_passes(B, L, x, w, synth.make_dy(L, 8))][2:]
+    for got, want in passes:
+        check_not_finite(got, want)
+
+
+def test_not_finite_in_tiles_of_144_rows(B):
+    """Nine blocks of 16 rows: the recomputation goes over 32 at a time, the last of which are the next tile's."""
+    L = layer("fc", 257, 4609, 1, 1, 2051, 1)
+    x, w = synth.make_x(L, 7), not_finite(synth.make_w(L, 7), (3, 7, 9, 12), 1.0)
+    x[127, 0], x[130, 31], x[143, 4608], x[144, 5], x[161, 2000], x[256, 1] = np.inf, np.nan, -np.inf, np.nan, np.inf, 1e37
+    got, names = ran(B, lambda: gpu_forward(B, L, x, w, synth.make_bias(L, 7)))
+    assert "gemm_split<144, k-contiguous>" in names, names
+    check_not_finite(got, oracle.conv_forward(odims(oracle, L), x, w, synth.make_bias(L, 7)))
