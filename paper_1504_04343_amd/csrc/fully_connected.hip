@@ -126,12 +126,14 @@ __device__ __forceinline__ void fold(double* v, int lane, int* mine) {
   }
   if constexpr (OFF > 1) fold<(N > 1 ? N / 2 : 1), OFF / 2>(v, lane, mine);
 }
-template <int ROWS>
+// ALONE: every wave has 4 columns and their whole contraction to itself, of less than one step of all waves.  Many columns
+// of few features are workgroups that share out next to nothing and meet for it.
+template <int ROWS, bool ALONE = false>
 __global__ __launch_bounds__(64 * kWaves) void fc_forward_few(FewRows p) {
-  __shared__ double red[kWaves][ROWS * kCols];
+  __shared__ double red[ALONE ? 1 : kWaves][ROWS * kCols];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const int n0 = blockIdx.x * kCols;
-  constexpr int STEP = kWaves * 64 * 4;
+  const int n0 = (ALONE ? (int)blockIdx.x * kWaves + wave : (int)blockIdx.x) * kCols;
+  constexpr int STEP = (ALONE ? 1 : kWaves) * 64 * 4;
   const float *a[ROWS], *b[kCols];
 #pragma unroll
   for (int m = 0; m < ROWS; ++m) a[m] = p.A + (long long)min(m, p.M - 1) * p.K;
@@ -142,7 +144,7 @@ __global__ __launch_bounds__(64 * kWaves) void fc_forward_few(FewRows p) {
   for (int m = 0; m < ROWS; ++m)
 #pragma unroll
     for (int c = 0; c < kCols; ++c) acc[m][c] = 0.0;
-  const int k_first = (wave * 64 + lane) * 4;
+  const int k_first = ((ALONE ? 0 : wave * 64) + lane) * 4;
   const int whole = p.K / STEP * STEP;  // up to here every lane has its 4
   fc_f32x4u bv[2][kCols], av[2][ROWS];
   auto load = [&](int set, int k) {
@@ -152,38 +154,40 @@ __global__ __launch_bounds__(64 * kWaves) void fc_forward_few(FewRows p) {
     for (int m = 0; m < ROWS; ++m) av[set][m] = *reinterpret_cast<const fc_f32x4u*>(a[m] + k);
   };
   // Sums in 64 bits: lanes' chains and their tree in 32 rounded more than the matrix cores' chains do (2-norm, 2 rows of 136:
-  // 7.0e-8, 5.7e-8 there, 2.4e-8 so; 3 of 1000 with 32 columns 1.3e-7, 8.3e-8, 2.6e-8).  In whole steps, which are of rows of
-  // 2048 and more, four products are summed in 32 first (4.7e-8; 4 rows, 4096 -> 4096: 21 us without, 16).
-  auto multiply = [&](int set) {
+  // 7.0e-8, 5.7e-8 there, 2.4e-8 so; 3 of 1000 with 32 columns 1.3e-7, 8.3e-8, 2.6e-8).  In whole steps of all waves, which
+  // are of rows of 2048 and more, four products are summed in 32 first (4.7e-8; 4 rows, 4096 -> 4096: 21 us without, 16).
+  auto multiply = [&](int set, auto four) {
 #pragma unroll
     for (int m = 0; m < ROWS; ++m)
 #pragma unroll
       for (int c = 0; c < kCols; ++c) {
-        float four = av[set][m][0] * bv[set][c][0];
+        if constexpr (decltype(four)::value) {
+          float sum = av[set][m][0] * bv[set][c][0];
 #pragma unroll
-        for (int e = 1; e < 4; ++e) four = fmaf(av[set][m][e], bv[set][c][e], four);
-        acc[m][c] += four;
+          for (int e = 1; e < 4; ++e) sum = fmaf(av[set][m][e], bv[set][c][e], sum);
+          acc[m][c] += sum;
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[m][c] = fma((double)av[set][m][e], (double)bv[set][c][e], acc[m][c]);
+        }
       }
   };
+  constexpr std::bool_constant<!ALONE> four;
+  constexpr std::false_type single;
   if (whole) {
     const int last = whole - STEP;
     load(0, k_first);
     for (int k = 0; k < whole; k += 2 * STEP) {
       load(1, k_first + min(k + STEP, last));
-      multiply(0);
+      multiply(0, four);
       load(0, k_first + min(k + 2 * STEP, last));
-      if (k + STEP < whole) multiply(1);
+      if (k + STEP < whole) multiply(1, four);
     }
   }
   const int k_rest = whole + k_first;
   if (k_rest + 4 <= p.K) {
     load(0, k_rest);
-#pragma unroll
-    for (int m = 0; m < ROWS; ++m)
-#pragma unroll
-      for (int c = 0; c < kCols; ++c)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc[m][c] = fma((double)av[0][m][e], (double)bv[0][c][e], acc[m][c]);
+    multiply(0, single);
   } else {
     for (int k = k_rest; k < p.K; ++k) {
       double x[ROWS];
@@ -205,30 +209,45 @@ __global__ __launch_bounds__(64 * kWaves) void fc_forward_few(FewRows p) {
   int mine = 0;
   fold<VALUES, 32>(v, lane, &mine);
   constexpr int REST = 64 / VALUES;  // lanes that hold the same value
+  auto store = [&](int t, double sum) {
+    const int m = t / kCols, col = n0 + t % kCols;
+    if (m < p.M && col < p.N) p.C[(long long)m * p.N + col] = (float)(sum + (p.bias ? p.bias[col] : 0.f));
+  };
+  if constexpr (ALONE) {
+    if (lane % REST == 0) store(mine, v[0]);
+    return;
+  }
   if (lane % REST == 0) red[wave][mine] = v[0];
   __syncthreads();
-  const int t = threadIdx.x, m = t / kCols, col = n0 + t % kCols;
-  if (t >= ROWS * kCols || m >= p.M || col >= p.N) return;
+  const int t = threadIdx.x;
+  if (t >= VALUES) return;
   double u[kWaves];
 #pragma unroll
   for (int w = 0; w < kWaves; ++w) u[w] = red[w][t];
-  const double sum = ((u[0] + u[1]) + (u[2] + u[3])) + ((u[4] + u[5]) + (u[6] + u[7]));
-  p.C[(long long)m * p.N + col] = (float)(sum + (p.bias ? p.bias[col] : 0.f));
+  store(t, ((u[0] + u[1]) + (u[2] + u[3])) + ((u[4] + u[5]) + (u[6] + u[7])));
 }
 
+// Columns from which the waves work alone: there it is 0.35 to 0.75 times the time with all waves, below as much or more.
+// As times of gemm_split, which ran these layers before there was this kernel (20800 layers), with all waves and alone: 3 or
+// 4 rows of up to 63 -> 4096 to 8191 1.32 and 1.00, of 256 to 511 -> 8192 and more 1.45 and 0.62; 5 to 8 rows of 256 to
+// 511 -> 4096 to 8191 1.56 and 0.57, of 1024 to 2047 -> 2048 to 4095 0.99 and 0.79, of fewer columns 0.70 and 0.86.
+bool few_alone(int M, int N, int K) { return K < 2048 && N >= (M <= 4 ? 4096 : 2048); }
 bool forward_few_fits(int M, int N, int K) { return M <= 4 || (M <= 8 && K >= 256 && (long long)N * K <= (1LL << 22)); }
 
 int launch_forward_few(const float* A, const float* B, const float* bias, float* C, int M, int N, int K, hipStream_t st) {
   if (M < 1 || M > 8 || N < 1 || K < 1) return CCT_EUNSUPPORTED;
   const FewRows p{A, B, bias, C, M, N, K};
-  const dim3 grid((unsigned)((N + kCols - 1) / kCols)), block(64 * kWaves);
+  const bool alone = few_alone(M, N, K);
+  const int cols = alone ? kCols * kWaves : kCols;
+  const dim3 grid((unsigned)(((long long)N + cols - 1) / cols)), block(64 * kWaves);
   const int rows = M <= 2 ? M : M <= 4 ? 4 : 8;
-  ProfScope ps(2.0 * M * N * K, 4.0 * ((double)M * K + (double)N * K + (double)M * N), st, "fc_forward_few<%d>", rows);
+  ProfScope ps(2.0 * M * N * K, 4.0 * ((double)M * K + (double)N * K + (double)M * N), st, alone ? "fc_forward_few<%d, alone>" : "fc_forward_few<%d>", rows);
+  auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, st, p); };
   switch (rows) {
-    case 1: hipLaunchKernelGGL(fc_forward_few<1>, grid, block, 0, st, p); break;
-    case 2: hipLaunchKernelGGL(fc_forward_few<2>, grid, block, 0, st, p); break;
-    case 4: hipLaunchKernelGGL(fc_forward_few<4>, grid, block, 0, st, p); break;
-    default: hipLaunchKernelGGL(fc_forward_few<8>, grid, block, 0, st, p);
+    case 1: launch(alone ? fc_forward_few<1, true> : fc_forward_few<1>); break;
+    case 2: launch(alone ? fc_forward_few<2, true> : fc_forward_few<2>); break;
+    case 4: launch(alone ? fc_forward_few<4, true> : fc_forward_few<4>); break;
+    default: launch(alone ? fc_forward_few<8, true> : fc_forward_few<8>);
   }
   CCT_CHECK_LAUNCH();
   return CCT_OK;

@@ -246,6 +246,22 @@ def test_few_images(B, N, F, O):
         assert rel_err(got, oracle.conv_forward(odims(oracle, L), x, w, bias)) <= TOL_F32
 
 
+@pytest.mark.parametrize("N,F,O,alone", [(1, 37, 4100, True), (2, 2047, 4099, True), (3, 3, 4096, True), (4, 2048, 4099, False),
+                                         (4, 1021, 4095, False), (5, 260, 2049, True), (8, 1023, 2050, True), (8, 517, 2047, False)])
+def test_few_images_of_many_kernels(B, N, F, O, alone):
+    """Fully connected forward where a wave has its columns alone: parts of 256 features, up to 3 beyond the last four, columns
+    past a wave's 4 and a workgroup's 32, the first sizes on both sides.  Sums in 64 bits: a result's own rounding, and that of
+    the bias, 2^-24 each; four products in fp32 from 2048 features on: 2^-24 of the sum of their magnitudes a rounding."""
+    L = layer("fc", N, F, 1, 1, O, 1)
+    x, w, b = synth.make_x(L, 8), synth.make_w(L, 8), synth.make_bias(L, 8)
+    for bias in (b, None):
+        got, names = ran(B, lambda: gpu_forward(B, L, x, w, bias))
+        assert len(names) == 1 and names[0].startswith("fc_forward_few<") and ("alone" in names[0]) == alone, names
+        want = oracle.conv_forward(odims(oracle, L), x, w, bias)
+        magnitude = oracle.conv_forward(odims(oracle, L), np.abs(x), np.abs(w), None if bias is None else np.abs(bias))
+        assert (np.abs(got - want) <= 2.0**-24 * ((2 * np.abs(want)) if F < 2048 else 6 * magnitude) + 1e-40).all()
+
+
 @pytest.mark.parametrize("N,F,O", [(1, 1023, 4099), (2, 257, 128), (3, 5, 33), (5, 1, 900), (8, 4098, 129), (16, 1025, 17),
                                    (31, 70, 23), (9, 1029, 21), (17, 1021, 13), (20, 5, 9), (32, 2050, 11)])
 def test_few_images_backward(B, N, F, O):
