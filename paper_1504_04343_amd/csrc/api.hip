@@ -652,18 +652,23 @@ double find_kernel_cost(const cct_conv_desc_t& d, int pass, int type, const Geom
   double index_bytes = 0.0, gemm_bytes = 0.0, launches = 2.0, rate = kGemmFlopsPerSec;
   if (pass == CCT_PASS_FORWARD && type == CCT_LOWER_FUSED) {
     // no lowered matrix at all; building the operand in the kernel costs the GEMM some of its rate
-    gemm_bytes = x_bytes + y_bytes;
-    rate *= kFusedGemmFactor * eff_fused(g.Mr) * fill(g.Mr, cols) * short_k(g.Kd);
+    // In fp32, rows of x that no window reaches are not read, and strided windows are fed to kernels whose tiles have 64 rows
+    // at least (with few kernels they took 1.4 times this estimate, and Type 3 half as long was passed over).
+    const bool f32 = d.precision == CCT_PREC_F32, gathered = f32 && d.stride > 1 && d.K > 1;
+    gemm_bytes = x_bytes * (f32 ? std::min(1.0, (double)d.K / d.stride) : 1.0) + y_bytes;
+    rate *= kFusedGemmFactor * (gathered ? eff(g.Mr) : eff_fused(g.Mr)) * fill(g.Mr, cols) * short_k(g.Kd);
   } else if (Layout L; tensor_split(d, pass, type, g, 1, &L)) {
     const bool fwd = pass == CCT_PASS_FORWARD;
     const double side = (fwd ? rt_elems : dt_elems) * 4.0;  // written by the product, read by lift / inverse lowering
     const double t = gemm_split_seconds(false, true, fwd ? g.Mr : g.Kd, fwd ? g.Kd : g.Mr, (long long)cols, d.groups);
     const double product = std::max(t, ((fwd ? x_bytes : y_bytes) + side) / kGemmBytesPerSec);
-    // The product, its result through memory, the gather's chain of taps.  Fitted to 145 passes of 3 x 3 layers (what a
-    // tap adds: to 21000 passes with the tiles before): off by 7 % in the mean, 15 % in nine of ten.
+    // The product, its result through memory, the gather's chain of taps.  Fitted to 3560 passes (K = 1 to 7, strides 1 and
+    // 2, 1 to 400 channels and images): off by 11 % in the mean forward, 9 % backward, 24 and 19 % in nine of ten.  (Fitted to
+    // 3 x 3 layers alone: 15 % both, 34 %, too much with few kernels and for 1 x 1 at stride 2, whose layers went to kernels
+    // that took up to 2.6 times as long: 269 images of 42 x 42, 39 -> 3 channels, K = 5 at stride 2 77 us and 199.)
     const double U = (d.K + d.stride - 1) / d.stride;  // taps per axis that a pixel of dx receives
-    return fwd ? product + side / 4.57e12 + y_bytes / 1.79e12 + d.K * d.K * 0.28e-6 + 0.8e-6
-               : product + side / 4.48e12 + x_bytes / 1.74e12 + U * U * 0.35e-6;
+    return fwd ? product + side / 5.40e12 + y_bytes / 5.29e12 + d.K * d.K * 0.183e-6 + 2.0e-6
+               : product + side / 4.49e12 + x_bytes / 2.87e12 + U * U * 0.178e-6 + 2.1e-6;
   } else if (pass == CCT_PASS_FORWARD) {
     index_bytes += x_bytes + dt_elems * es;      // lowering: read x, write D^T
     gemm_bytes += dt_elems * es;                 // GEMM reads D^T

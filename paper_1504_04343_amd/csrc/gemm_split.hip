@@ -547,6 +547,11 @@ constexpr Form kForms[4] = {
     {8, 2, {{1.226, 0.773, 1.057, 4.257, 5.98, 2.48e6, 3.112}, {1.034, 0.967, 1.682, 3.886, 5.10, 3.15e6, 0.000}}},
     {9, 2, {{1.356, 0.867, 1.333, 3.711, 6.00, 2.75e6, 2.727}, {1.333, 1.106, 0.000, 4.913, 4.80, 3.02e6, 0.000}}}};
 
+// One tile of up to 32 rows with B column-contiguous, which waves work on alone in most forms: fitted to 2870 products, off by
+// 8 % in the mean, 17 % in nine of ten (with the rates of many such tiles: a quarter, by 1.55 too much for long
+// contractions, which sent layers to kernels that took twice as long).
+constexpr Form kFewRows = {2, 5, {{0.424, 0.147, 2.033, 3.420, 0.00, 5.36e6, 0.000}, {}}};
+
 double form_us(const Form& f, bool bt, int M, int K, long long cols, long long G) {
   const Form::Rate& r = f.rate[bt];
   const unsigned long long tiles_m = ((unsigned)M + 16u * f.rb - 1) / (16u * f.rb);
@@ -565,7 +570,7 @@ const Form* choose(bool bt, int M, int K, long long cols, long long G, Fits fits
   for (const Form& f : kForms) {
     // (up to 32 rows 32 at a time, whatever the estimates say: 16 images of fc6 forward 45 us against 52 in tiles of 64)
     if (!fits(f) || (f.rb == 4 && M <= 32)) continue;
-    const double t = form_us(f, bt, M, K, cols, G);
+    const double t = form_us(f.rb == 2 && M <= 32 && !bt ? kFewRows : f, bt, M, K, cols, G);
     if (!best || t < *us) {
       best = &f;
       *us = t;

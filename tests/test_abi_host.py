@@ -390,3 +390,23 @@ def test_recommended_workspace_gets_the_recommended_plan(B, N, C, H, O, pass_):
         assert fc_plan(ctypes.byref(d), pass_, ctypes.c_longlong(room), plan)
         plans.append(plan.raw)
     assert plans[0] == plans[1]
+
+
+# Layers that estimates fitted to 3 x 3 layers alone had sent to another layout; us on it and on the fastest
+NARROW = [
+    ((269, 39, 42, 42, 3, 5, 2, 2, 1), 0, 3),      # 199 fused, 77
+    ((259, 179, 38, 38, 5, 2, 2, 1, 1), 0, 3),     # 166 fused, 66
+    ((184, 15, 53, 53, 3, 2, 1, 0, 1), 0, 3),      # 52 fused, 23
+    ((289, 78, 31, 31, 6, 3, 2, 1, 2), 0, 3),      # 90 fused, 40
+    ((271, 210, 32, 32, 11, 2, 2, 1, 1), 0, 3),    # 158 fused, 77
+    ((96, 33, 50, 53, 10, 3, 1, 0, 1), 0, 3),      # 116 fused, 56
+    ((235, 178, 56, 54, 9, 1, 2, 0, 1), 0, 4),     # 119 Type 3, 83
+    ((317, 100, 28, 26, 53, 1, 2, 0, 1), 1, 1),    # 89 Type 3, 55
+    ((262, 1012, 36, 7, 242, 1, 2, 0, 2), 1, 1),   # 251 Type 3, 159
+    ((28, 231, 56, 56, 37, 2, 2, 1, 1), 1, 1),     # 97 Type 3, 64
+]
+
+
+@pytest.mark.parametrize("shape,pass_,fastest", NARROW, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_selector_picks_the_measured_layout_with_few_kernels(B, shape, pass_, fastest):
+    assert B.cct_pick_lowering(B.make_desc(*shape), pass_) == fastest
