@@ -355,8 +355,8 @@ int launch_outer(const float* x, const float* dy, float* dw, float* dbias, int N
 }
 
 // dx[n][f] = sum_o dy[n][o] * w[o][f] over up to 8 images (S > 1: one of S shares of the kernels, to part): a
-// workgroup owns 256 features, a lane 4 consecutive ones, its 8 waves share out the kernels; dy's values are the same for a
-// whole wave.  Bound by reading w once; the kernels are split over workgroups where the features are too few to fill the
+// workgroup owns 256 features, a lane 4 consecutive ones, its 8 waves share out the kernels; dy's values, the same for a whole
+// wave, come from the lane that holds them (by scalar loads in front of every four kernels 5 to 8 images took 1.04 times as long).  Bound by reading w once; the kernels are split over workgroups where the features are too few to fill the
 // chip.  One image of fc6 (151 MB) 38.2 us on 32-row tiles of the matrix cores behind a pack, 31.4 now; 4096 -> 1000
 // 14.8 -> 11; with 16 images registers leave too few waves in flight (41 and 77).
 constexpr int kRowsWaves = 8, kRowsFeatures = 256;
@@ -379,7 +379,23 @@ __global__ __launch_bounds__(64 * kRowsWaves) void fc_backward_data_few(const fl
     for (int e = 0; e < 4; ++e) acc[n][e] = 0;
   // 4 kernels at a time: their loads in flight together, from kFourKernels on their products summed in 32 bits and all in
   // 64 (8 images of 512 -> 64: 2-norm 6.8e-8 in 32 bits, 4.8e-8 so and on the matrix cores)
+  // dy's values of 64 kernels: a lane's of one each, for the whole wave by a lane's number
+  float dv[ROWS], next[ROWS];
+  auto load_dy = [&](float (&to)[ROWS], int o) {
+#pragma unroll
+    for (int n = 0; n < ROWS; ++n) to[n] = dy[(long long)min(n, N - 1) * O + min(o + lane, O - 1)];
+  };
+  load_dy(next, o_begin);
   for (int o = o_begin; o < o_end; o += 4) {
+    const int at = (o - o_begin) & 63;
+    if (at == 0) {
+#pragma unroll
+      for (int n = 0; n < ROWS; ++n) dv[n] = next[n];
+      if (o + 64 < o_end) load_dy(next, o + 64);
+    }
+    auto d = [&](int n, int u) {
+      return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, dv[n]), at + u));
+    };
     float v[4][4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -398,21 +414,16 @@ __global__ __launch_bounds__(64 * kRowsWaves) void fc_backward_data_few(const fl
       constexpr bool FULL = decltype(full)::value;
 #pragma unroll
       for (int n = 0; n < ROWS; ++n) {
-        const float* d = dy + (long long)min(n, N - 1) * O + o;
         if constexpr (FULL) {
+          const float d0 = d(n, 0), d1 = d(n, 1), d2 = d(n, 2), d3 = d(n, 3);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            float four = d[0] * v[0][e];
-#pragma unroll
-            for (int u = 1; u < 4; ++u) four = fmaf(d[u], v[u][e], four);
-            acc[n][e] += four;
-          }
+          for (int e = 0; e < 4; ++e) acc[n][e] += fmaf(d3, v[3][e], fmaf(d2, v[2][e], fmaf(d1, v[1][e], d0 * v[0][e])));
         } else {
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
             if (u >= live) break;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) acc[n][e] = fma((Acc)d[u], (Acc)v[u][e], acc[n][e]);
+            for (int e = 0; e < 4; ++e) acc[n][e] = fma((Acc)d(n, u), (Acc)v[u][e], acc[n][e]);
           }
         }
       }
@@ -438,6 +449,8 @@ __global__ __launch_bounds__(64 * kRowsWaves) void fc_backward_data_few(const fl
 
 // How many workgroups share a feature's kernels: at most 1024 workgroups of at least 32 kernels, none shared where a wave's
 // chain of 16 kernels is shorter than the second launch, which adds the shares.
+// (5 to 8 images of 4096 and more -> 4096 and more features take 1.20 times as long as on gemm_split, 1.13 with 512 workgroups;
+// their sums in 32 bits, twice as close to 64 bits as there, would be a tenth further off.)
 int backward_data_few_shares(int O, int F) {
   const int blocks = (F + kRowsFeatures - 1) / kRowsFeatures;
   return O <= 128 ? 1 : std::max(1, std::min({1024 / blocks, O / 32, 64}));
