@@ -18,7 +18,7 @@
 // Bound by the matrix cores at the clock the card holds under it (MfmaUtil 55 % at 1.83 GHz, LDS a third busy) and
 // by what stands still at the ends of a row's stage: 224 workgroups, 5.4 us per row and workgroup, of it 3.0 MFMAs.
 // CaffeNet's first layer at batch 256 with its bias gradient: gather-fed fp32 matrix product 600 us, reduction 12,
-// bias gradient 65 before; 320 and 8 now.  388 layers of 1 to 16 channels per group: 0.66 times the time in the mean.
+// bias gradient 65 before; 278 and 10 now.  388 layers of 1 to 16 channels per group: 0.66 times the time in the mean.
 // Tried: rows of all strips shared evenly over 256 workgroups instead of strips on 224 (conv1 1119 -> 1289 us: the strips
 // of the same images no longer run side by side, and dy's lines are fetched for every strip).
 #include <algorithm>

@@ -356,7 +356,8 @@ int launch_outer(const float* x, const float* dy, float* dw, float* dbias, int N
 
 // dx[n][f] = sum_o dy[n][o] * w[o][f] over up to 8 images (S > 1: one of S shares of the kernels, to part): a
 // workgroup owns 256 features, a lane 4 consecutive ones, its 8 waves share out the kernels; dy's values, the same for a whole
-// wave, come from the lane that holds them (by scalar loads in front of every four kernels 5 to 8 images took 1.04 times as long).  Bound by reading w once; the kernels are split over workgroups where the features are too few to fill the
+// wave, come from the lane that holds them (by scalar loads in front of every four kernels 5 to 8 images took 1.04 times
+// as long).  Bound by reading w once; the kernels are split over workgroups where the features are too few to fill the
 // chip.  One image of fc6 (151 MB) 38.2 us on 32-row tiles of the matrix cores behind a pack, 31.4 now; 4096 -> 1000
 // 14.8 -> 11; with 16 images registers leave too few waves in flight (41 and 77).
 constexpr int kRowsWaves = 8, kRowsFeatures = 256;

@@ -6,18 +6,20 @@
 //     16 x 16 (v_mfma_f32_16x16x32_bf16), two accumulators each;
 //   - B goes from memory into the registers of the one wave that multiplies it, which splits it there: no LDS, no
 //     meeting of waves.  A lane supplies 8 k of two neighbouring columns per stage of 32 k.  The split of the next stage is
-//     written between the MFMAs of this one, 3 or 4 instructions at a time (32 rows: behind them).  Columns are taken in pairs (8-byte loads and
-//     stores), one by one (planes of a few pixels), or k-contiguous (w of a forward product, 16-byte loads);
+//     written between the MFMAs of this one, 3 or 4 instructions at a time (32 rows: behind them).  Columns are taken in
+//     pairs (8-byte loads and stores), one by one (planes of a few pixels), or k-contiguous (w of a forward product,
+//     16-byte loads);
 //   - A is shared by the four waves through LDS: units of 16 rows and one term, in lane order, so that a read is 1 KiB
 //     without conflicts.  128 and 144 rows: packed that way and split once per call (launch_pack_rows_split), moved to
 //     LDS by loads that write it directly.  32 and 64 rows: fp32 values in place, any strides, split by the
-//     workgroup on their way; a launch less, and no pack to wait for;
+//     workgroup on their way; a launch less, and no pack to wait for.  16 rows, and 32 of one stage: by every wave for itself,
+//     without LDS;
 //   - groups are channel groups or splits of the contraction.
-// What bounds it (fc6 at batch 256, 19.3 GFLOP per product in 98 to 110 us): the MFMAs alone take 62 us, LDS reads add 2,
+// What bounds it (fc6 at batch 256, 19.3 GFLOP per product in 91 to 105 us): the MFMAs alone take 62 us, LDS reads add 2,
 // splitting 9, waiting for memory 20.  Before, B went through LDS and A straight to registers in tiles of 128 and 64 rows,
-// always behind a pack: forward 104 -> 99 us, backward-weights 128 -> 110, backward-data 129 -> 113; 144 rows x 512 k x
-// 100352 columns, three tiles of 64 before, 126 -> 90; 256 images of 4096 -> 1000 features, forward, both gradients and what
-// lies around them, 107 -> 90.
+// always behind a pack: forward 104 -> 91 us, the two gradients 128 -> 104 each; 144 rows x 512 k x 100352 columns, three
+// tiles of 64 before, 126 -> 90; 256 images of 4096 -> 1000 features, forward, both gradients and what lies around them,
+// 104 -> 87.
 #include <algorithm>
 #include <type_traits>
 
@@ -522,8 +524,8 @@ bool gemm_split_fits(const GemmTN& p, bool bt) {
 }
 
 namespace {
-// The forms: tiles of 32 (16 where that is all) and 64 rows, which read A in place and split it themselves, and of 128 and 144, for which it is
-// packed first.  A launch less is what counts where the chip is not full (33 to 512 images of fully connected layers,
+// The forms: tiles of 32 (16 where that is all) and 64 rows, which read A in place and split it themselves, and of 128 and
+// 144, for which it is packed first.  A launch less is what counts where the chip is not full (33 to 512 images of fully connected layers,
 // up to 2 GFLOP: 0.6 to 0.8 times the time of a pack and a product); large products split A once per column tile too often.
 
 // 32-bit byte offsets in A in place, from a tile's first row and a stage's first k
