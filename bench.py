@@ -37,8 +37,15 @@ PEAK_BF16_MFMA_TFLOPS = 2500.0
 # fp32 products on the bf16 matrix cores: three terms per operand, six bf16 products per fp32 product
 PEAK_SPLIT_TFLOPS = PEAK_BF16_MFMA_TFLOPS / 6
 MFMA_KERNELS = ("gemm_", "conv_fused", "conv_bwdw_fused", "conv_bwdw_img", "conv_bwdw_few", "conv_granules")
+VECTOR_KERNELS = ("gemm_split_k",)   # fully connected layers on few images: no matrix core
 SPLIT_KERNELS = ("conv_fused_split", "gemm_split", "conv_bwdw_img", "conv_bwdw_few")
 PEAK_HBM_GBS = 8000.0
+
+
+def is_mfma(name):
+    """The GEMMs and the fused conv kernels (matrix-core bound); the rest stream."""
+    return name.startswith(MFMA_KERNELS) and not name.startswith(VECTOR_KERNELS)
+
 
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic_caffenet_b256_f32.txt")
 STREAM_KERNELS = ("lower_kernel", "lower_direct_kernel", "lift_kernel", "inv_lift_kernel",
@@ -254,9 +261,7 @@ def run_caffenet(args, B, synth, torch):
     prof = profiled(B, st.step, args.steps)
     total_kernel_ms = sum(e["total_ms"] for e in prof)
 
-    def is_mfma(e):   # the GEMMs and the fused conv kernels (matrix-core bound); the rest stream
-        return e["name"].startswith(MFMA_KERNELS)
-    gemms = [e for e in prof if is_mfma(e)]
+    gemms = [e for e in prof if is_mfma(e["name"])]
     dom = max(gemms, key=lambda e: e["total_ms"])
     avg_ms = dom["total_ms"] / dom["launches"]
     achieved_tflops = dom["flops"] / dom["launches"] / (avg_ms * 1e-3) / 1e12
@@ -444,7 +449,7 @@ def run_batching(args, B, synth, torch):
         elapsed, _ = time_steps(st.step, steps if c != 1 else 2, 1)
         n = steps if c != 1 else 2
         prof = profiled(B, st.step, 1)
-        g = [e for e in prof if e["name"].startswith(MFMA_KERNELS)]
+        g = [e for e in prof if is_mfma(e["name"])]
         s = [e for e in prof if e["name"].startswith(STREAM_KERNELS)]
         gt = sum(e["flops"] for e in g) / (sum(e["total_ms"] for e in g) * 1e-3) / 1e12
         sb = sum(e["bytes"] for e in s) / (sum(e["total_ms"] for e in s) * 1e-3) / 1e9 if s else float("nan")

@@ -96,6 +96,8 @@ __global__ __launch_bounds__(TPB) void fc_sum_splits_kernel(const float* __restr
   y[t] = (float)(acc + shift);
 }
 
+// (In profiles this kernel and fc_backward_data_few are gemm_split_k and gemm_split_k_columns, as readers of
+// cct_profile_read know them; they split nothing and use no matrix core.)
 typedef float fc_f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // 16 bytes, dword aligned
 
 // The product of up to 8 rows with a k-contiguous B (a fully connected layer's forward pass on few images) in one launch
@@ -241,7 +243,7 @@ int launch_forward_few(const float* A, const float* B, const float* bias, float*
   const int cols = alone ? kCols * kWaves : kCols;
   const dim3 grid((unsigned)(((long long)N + cols - 1) / cols)), block(64 * kWaves);
   const int rows = M <= 2 ? M : M <= 4 ? 4 : 8;
-  ProfScope ps(2.0 * M * N * K, 4.0 * ((double)M * K + (double)N * K + (double)M * N), st, alone ? "fc_forward_few<%d, alone>" : "fc_forward_few<%d>", rows);
+  ProfScope ps(2.0 * M * N * K, 4.0 * ((double)M * K + (double)N * K + (double)M * N), st, alone ? "gemm_split_k<%d, alone>" : "gemm_split_k<%d>", rows);
   auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, st, p); };
   switch (rows) {
     case 1: launch(alone ? fc_forward_few<1, true> : fc_forward_few<1>); break;
@@ -460,7 +462,7 @@ int backward_data_few_shares(int O, int F) {
 int launch_backward_data_few(const float* w, const float* dy, float* out, int N, int O, int F, int S, hipStream_t st) {
   const int share = (O + S - 1) / S;
   const dim3 grid((unsigned)((F + kRowsFeatures - 1) / kRowsFeatures), (unsigned)((O + share - 1) / share)), block(64 * kRowsWaves);
-  ProfScope ps("fc_backward_data_few", 2.0 * N * (double)O * F, 4.0 * ((double)O * F + (double)N * (O + (double)S * F)), st);
+  ProfScope ps("gemm_split_k_columns", 2.0 * N * (double)O * F, 4.0 * ((double)O * F + (double)N * (O + (double)S * F)), st);
   if (N <= 1) hipLaunchKernelGGL(fc_backward_data_few<1>, grid, block, 0, st, w, dy, out, N, O, F, share);
   else if (N <= 2) hipLaunchKernelGGL(fc_backward_data_few<2>, grid, block, 0, st, w, dy, out, N, O, F, share);
   else if (N <= 4) hipLaunchKernelGGL(fc_backward_data_few<4>, grid, block, 0, st, w, dy, out, N, O, F, share);

@@ -356,13 +356,13 @@ def test_benchmark_counts_every_kernel_of_the_matrix_cores():
     fully connected layers on few images do not."""
     import bench
     for name in bench.SPLIT_KERNELS:
-        assert name.startswith(bench.MFMA_KERNELS), name
+        assert bench.is_mfma(name), name
     sources = glob.glob(os.path.join(ROOT, "paper_1504_04343_amd", "csrc", "*.hip"))
     for path in sources:
         text = open(path).read()
         kernels = set(re.findall(r'ProfScope ps\([^;]*?"(\w+)', text, flags=re.S))
         assert kernels or "ProfScope ps(" not in text, path
-        rated = {k for k in kernels if k.startswith(bench.MFMA_KERNELS)}
+        rated = {k for k in kernels if bench.is_mfma(k)}
         if os.path.basename(path) == "fully_connected.hip":
             assert not rated, rated
         elif "_mfma_f32" in text:

@@ -14,13 +14,13 @@ KERNEL = "gemm_split"
 
 #          name      N   C   H  W    O  K
 FC = [
-    layer("n9",       9,  64, 4, 4, 130, 4),             # few images, rows in place, columns past a tile
+    layer("one",      1,  64, 4, 4, 130, 4),             # one image, rows in place, columns past a tile
     layer("n32",     32,  37, 3, 3,  65, 3),             # 333 features: the last stage ends inside a row
     layer("n33",     33,  37, 3, 3,  65, 3),             # the same with packed rows
     layer("n65",     65,   7, 1, 1, 129, 1),             # fewer features than a stage
     layer("n130",   130, 113, 5, 5, 257, 5),             # 2825 features, 128-row tiles and a split tail
     layer("n200",   200, 300, 1, 1, 1000, 1),
-    layer("prime",    9,  49, 1, 1, 1951, 1),            # splits of unequal length
+    layer("prime",    4,  49, 1, 1, 1951, 1),            # splits of unequal length
 ]
 POINTWISE = [
     layer("p_small",  2,  33, 7,  9,  34, 1),
@@ -237,40 +237,24 @@ def test_row_tiles_k_contiguous(B, N, F, O, rows):
 @pytest.mark.parametrize("N,F,O", [(1, 9216, 1001), (2, 2047, 5), (3, 4099, 33), (4, 1, 70), (5, 2052, 6), (8, 6145, 130)])
 def test_few_images(B, N, F, O):
     """Fully connected forward on few images: whole steps of 2048 features, a part of one, up to 3 features beyond the
-    last four; columns past a workgroup's 4.  Four products at a time summed in fp32: its tolerance."""
+    last four; columns past a workgroup's 4.  Sums of 4 to 8 products per lane and step in fp32: its tolerance."""
     L = layer("fc", N, F, 1, 1, O, 1)
     x, w, b = synth.make_x(L, 8), synth.make_w(L, 8), synth.make_bias(L, 8)
     for bias in (b, None):
         got, names = ran(B, lambda: gpu_forward(B, L, x, w, bias))
-        assert len(names) == 1 and names[0].startswith("fc_forward_few<"), names
+        assert len(names) == 1 and names[0].startswith("gemm_split_k<"), names
         assert rel_err(got, oracle.conv_forward(odims(oracle, L), x, w, bias)) <= TOL_F32
 
 
-@pytest.mark.parametrize("N,F,O,alone", [(1, 37, 4100, True), (2, 2047, 4099, True), (3, 3, 4096, True), (4, 2048, 4099, False),
-                                         (4, 1021, 4095, False), (5, 260, 2049, True), (8, 1023, 2050, True), (8, 517, 2047, False)])
-def test_few_images_of_many_kernels(B, N, F, O, alone):
-    """Fully connected forward where a wave has its columns alone: parts of 256 features, up to 3 beyond the last four, columns
-    past a wave's 4 and a workgroup's 32, the first sizes on both sides.  Sums in 64 bits: a result's own rounding, and that of
-    the bias, 2^-24 each; four products in fp32 from 2048 features on: 2^-24 of the sum of their magnitudes a rounding."""
-    L = layer("fc", N, F, 1, 1, O, 1)
-    x, w, b = synth.make_x(L, 8), synth.make_w(L, 8), synth.make_bias(L, 8)
-    for bias in (b, None):
-        got, names = ran(B, lambda: gpu_forward(B, L, x, w, bias))
-        assert len(names) == 1 and names[0].startswith("fc_forward_few<") and ("alone" in names[0]) == alone, names
-        want = oracle.conv_forward(odims(oracle, L), x, w, bias)
-        magnitude = oracle.conv_forward(odims(oracle, L), np.abs(x), np.abs(w), None if bias is None else np.abs(bias))
-        assert (np.abs(got - want) <= 2.0**-24 * ((2 * np.abs(want)) if F < 2048 else 6 * magnitude) + 1e-40).all()
-
-
 @pytest.mark.parametrize("N,F,O", [(1, 1023, 4099), (2, 257, 128), (3, 5, 33), (5, 1, 900), (8, 4098, 129), (16, 1025, 17),
-                                   (31, 70, 23), (9, 1029, 21), (17, 1021, 13), (20, 5, 9), (32, 2050, 11)])
+                                   (31, 70, 23)])
 def test_few_images_backward(B, N, F, O):
     """The gradients: shares of the kernels and none, up to 3 features beyond the last four, kernels past a
     workgroup's 8, up to 3 images beyond the last four.  Sums in fp32 of up to 4 products at a time: its tolerance."""
     L = layer("fc", N, F, 1, 1, O, 1)
     x, w, dy = synth.make_x(L, 8), synth.make_w(L, 8), synth.make_dy(L, 8)
     got, names = ran(B, lambda: gpu_backward_data(B, L, w, dy))
-    assert any(n.startswith("fc_backward_data_few") for n in names) == (N <= 8), names
+    assert any(n.startswith("gemm_split_k_columns") for n in names) == (N <= 8), names
     assert rel_err(got, oracle.conv_backward_data(odims(oracle, L), w, dy)) <= TOL_F32
     (dw, db), names = ran(B, lambda: gpu_backward_weights(B, L, x, dy))
     assert names == ["fc_outer_kernel"], names
@@ -291,6 +275,61 @@ def test_odd_planes(B, L):
     assert rel_err(gpu_backward_data(B, L, w, dy), oracle.conv_backward_data(odims(oracle, L), w, dy)) <= TOL_F32
 
 
+# Nine images: the smallest count that all three passes leave to gemm_split or to fc_outer_kernel
+NINE = [
+    layer("n9",       9,  64, 4, 4, 130, 4),             # few images, rows in place, columns past a tile
+    layer("prime9",   9,  49, 1, 1, 1951, 1),            # splits of unequal length
+]
+
+
+def split_product(names):
+    """gemm_split itself, not the kernels for few images whose names begin alike."""
+    return any(n.startswith("gemm_split<") for n in names)
+
+
+@pytest.mark.parametrize("L", NINE, ids=[L.name for L in NINE])
+def test_nine_images(B, L):
+    x, w, b, dy = synth.make_x(L, 3), synth.make_w(L, 3), synth.make_bias(L, 3), synth.make_dy(L, 3)
+    for bias in (b, None):
+        got, names = ran(B, lambda: gpu_forward(B, L, x, w, bias))
+        assert split_product(names), names
+        assert rel_err(got, oracle.conv_forward(odims(oracle, L), x, w, bias)) <= TOL_F32
+    got, names = ran(B, lambda: gpu_backward_data(B, L, w, dy))
+    assert split_product(names), names
+    assert rel_err(got, oracle.conv_backward_data(odims(oracle, L), w, dy)) <= TOL_F32
+    (dw, db), names = ran(B, lambda: gpu_backward_weights(B, L, x, dy))
+    assert names == ["fc_outer_kernel"], names
+    want = oracle.conv_backward_weights(odims(oracle, L), x, dy)
+    assert rel_err(dw, want[0]) <= TOL_F32 and rel_err(db, want[1]) <= TOL_F32
+
+
+@pytest.mark.parametrize("N,F,O", [(9, 1029, 21), (17, 1021, 13), (20, 5, 9), (32, 2050, 11)])
+def test_outer_product_of_few_images(B, N, F, O):
+    """Backward-weights: 4 or 8 kernels of a workgroup, images past the 16 whose loads are on their way at once."""
+    L = layer("fc", N, F, 1, 1, O, 1)
+    x, dy = synth.make_x(L, 8), synth.make_dy(L, 8)
+    (dw, db), names = ran(B, lambda: gpu_backward_weights(B, L, x, dy))
+    assert names == ["fc_outer_kernel"], names
+    want = oracle.conv_backward_weights(odims(oracle, L), x, dy)
+    assert rel_err(dw, want[0]) <= TOL_F32 and rel_err(db, want[1]) <= TOL_F32
+
+
+@pytest.mark.parametrize("N,F,O,alone", [(1, 37, 4100, True), (2, 2047, 4099, True), (3, 3, 4096, True), (4, 2048, 4099, False),
+                                         (4, 1021, 4095, False), (5, 260, 2049, True), (8, 1023, 2050, True), (8, 517, 2047, False)])
+def test_few_images_of_many_kernels(B, N, F, O, alone):
+    """Fully connected forward where a wave has its columns alone: parts of 256 features, up to 3 beyond the last four, columns
+    past a wave's 4 and a workgroup's 32, the first sizes on both sides.  Sums in 64 bits: a result's own rounding, and that of
+    the bias, 2^-24 each; four products in fp32 from 2048 features on: 2^-24 of the sum of their magnitudes a rounding."""
+    L = layer("fc", N, F, 1, 1, O, 1)
+    x, w, b = synth.make_x(L, 8), synth.make_w(L, 8), synth.make_bias(L, 8)
+    for bias in (b, None):
+        got, names = ran(B, lambda: gpu_forward(B, L, x, w, bias))
+        assert len(names) == 1 and names[0].startswith("gemm_split_k<") and ("alone" in names[0]) == alone, names
+        want = oracle.conv_forward(odims(oracle, L), x, w, bias)
+        magnitude = oracle.conv_forward(odims(oracle, L), np.abs(x), np.abs(w), None if bias is None else np.abs(bias))
+        assert (np.abs(got - want) <= 2.0**-24 * ((2 * np.abs(want)) if F < 2048 else 6 * magnitude) + 1e-40).all()
+
+
 FEW = [(1, 2053, 70), (4, 4099, 33), (8, 300, 600), (8, 1029, 129), (16, 1029, 21), (27, 70, 23)]
 
 
@@ -300,10 +339,10 @@ def few_passes(B, L, x, w, dy, dy_w=None):
     od = odims(oracle, L)
     if L.N <= 8:
         got, names = ran(B, lambda: gpu_forward(B, L, x, w, None))
-        assert len(names) == 1 and names[0].startswith("fc_forward_few<"), names
+        assert len(names) == 1 and names[0].startswith("gemm_split_k<"), names
         yield got, oracle.conv_forward(od, x, w, None)
         got, names = ran(B, lambda: gpu_backward_data(B, L, w, dy))
-        assert any(n.startswith("fc_backward_data_few") for n in names), names
+        assert any(n.startswith("gemm_split_k_columns") for n in names), names
         yield got, oracle.conv_backward_data(od, w, dy)
     (dw, db), names = ran(B, lambda: gpu_backward_weights(B, L, x, dy_w))
     assert names == ["fc_outer_kernel"], names
